@@ -4,6 +4,7 @@
 // streaming outer product.  GroupNorm scale/shift gradients are two reductions over each
 // channel of x and dy.
 #include "internal.h"
+#include "group.h"
 
 namespace dp {
 
@@ -232,14 +233,17 @@ struct GnArgs {
     float *partials;                // [n, groups]
     int n, c, hw, groups;
     float eps;
+    int vec, team, waves;           // one-sweep kernel: elements per load, lanes per channel, waves per group (gn_plan)
 };
 
 template <bool BF16>
-__global__ void __launch_bounds__(256) gn_affine_3pass_kernel(const GnArgs a)
+__global__ void __launch_bounds__(256) gn_affine_3pass_kernel(const Grouped<GnArgs> launch)
 {
     typedef typename In<BF16>::type E;
     __shared__ float red[4];
-    const int grp = blockIdx.x, i = blockIdx.y;
+    unsigned bid;
+    const GnArgs &a = launch.a[group_pick(launch, bid)];
+    const int i = bid / a.groups, grp = bid - i * a.groups;
     const int cg = a.c / a.groups;
     const size_t first = ((size_t)i * a.c + (size_t)grp * cg) * a.hw;
     const int cnt = cg * a.hw;
@@ -285,66 +289,158 @@ __global__ void __launch_bounds__(256) gn_affine_3pass_kernel(const GnArgs a)
 }
 
 // One sweep over x and dy (groups of at most GN_CMAX channels): with k = the group's first element as
-// a shift (so that the variance does not cancel), every wave takes channels in turn and accumulates
+// a shift (so that the variance does not cancel) every channel's team of lanes accumulates
 //     sum (x-k), sum (x-k)^2 for the group statistics,   sum dy (x-k), sum dy for the channel;
-// then dgamma_c = rstd (sum dy (x-k) - (mean-k) sum dy), dbeta_c = sum dy.  Four independent loads per
-// lane and stream are in flight.
+// then dgamma_c = rstd (sum dy (x-k) - (mean-k) sum dy), dbeta_c = sum dy.
+//
+// HBM-bound (x and dy are read once, 2 c floats written per example), but a layer alone is too small to get there:
+// all layers of a batch call share a launch, and the work is laid out so that a lane always has several wide loads in
+// flight.  A channel belongs to a team of `team` lanes (a power of two, about four vectors per lane), a group to
+// `waves` waves of the workgroup, so that narrow groups do not leave waves idle; a vector is the widest piece (16 .. 2
+// bytes) that divides the channel's row.  Kernel time per optimiser step beside the other layers' kernels, against one
+// launch per layer and one wave per channel with 2- or 4-byte loads: ResNet-18-GN, 8 x 32 examples, 20 layers: 1377 ->
+// 606 us (160 -> 16 launches; whole step 2.67 -> 2.07 ms); ResNet-20 in fp32, 256 examples: 963 -> 429 us.
 constexpr int GN_CMAX = 256;
 
-template <bool BF16>
-__global__ void __launch_bounds__(256) gn_affine_kernel(const GnArgs a)
+template <bool BF16, int V>
+__device__ __forceinline__ void gn_load(const typename In<BF16>::type *p, float (&o)[V])
+{
+    if constexpr (!BF16) {
+        if constexpr (V == 4) { const float4 v = *reinterpret_cast<const float4 *>(p); o[0] = v.x; o[1] = v.y; o[2] = v.z; o[3] = v.w; }
+        else if constexpr (V == 2) { const float2 v = *reinterpret_cast<const float2 *>(p); o[0] = v.x; o[1] = v.y; }
+        else o[0] = *p;
+    } else if constexpr (V == 1) {
+        o[0] = bf16_bits_to_float(*p);
+    } else {
+        uint32_t d[V / 2];
+        if constexpr (V == 8) { const uint4 v = *reinterpret_cast<const uint4 *>(p); d[0] = v.x; d[1] = v.y; d[2] = v.z; d[3] = v.w; }
+        else if constexpr (V == 4) { const uint2 v = *reinterpret_cast<const uint2 *>(p); d[0] = v.x; d[1] = v.y; }
+        else d[0] = *reinterpret_cast<const uint32_t *>(p);
+#pragma unroll
+        for (int e = 0; e < V / 2; ++e) {
+            o[2 * e] = __uint_as_float(d[e] << 16);
+            o[2 * e + 1] = __uint_as_float(d[e] & 0xFFFF0000u);
+        }
+    }
+}
+
+template <bool BF16, int V>
+__device__ __forceinline__ void gn_affine_body(const GnArgs &a, unsigned bid, float *s_dx, float *s_d, float *red)
 {
     typedef typename In<BF16>::type E;
-    __shared__ float red[4];
-    __shared__ float s_dx[GN_CMAX], s_d[GN_CMAX];
-    const int grp = blockIdx.x, i = blockIdx.y;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int waves = a.waves, team = a.team;
+    const int per_wg = 4 / waves;                                     // groups per workgroup
+    const int sub = wave / waves, wv = wave - sub * waves;
+    const long long gid = (long long)bid * per_wg + sub;
+    const bool live = gid < (long long)a.n * a.groups;                // the last workgroup may hold fewer groups
+    const int i = live ? (int)(gid / a.groups) : 0, grp = live ? (int)(gid - (long long)i * a.groups) : 0;
     const int cg = a.c / a.groups;
     const size_t first = ((size_t)i * a.c + (size_t)grp * cg) * a.hw;
-    const int cnt = cg * a.hw;
     const E *xg = static_cast<const E *>(a.x) + first;
     const E *dyg = static_cast<const E *>(a.dy) + first;
     const float k = In<BF16>::ld(xg);
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    s_dx += sub * cg;
+    s_d += sub * cg;
 
+    const int nv = a.hw / V, tl = lane & (team - 1), teams = 64 / team;
     float sx = 0.0f, sxx = 0.0f;
-    for (int cl = wave; cl < cg; cl += 4) {
+    for (int cl = wv * teams + lane / team; cl < cg; cl += waves * teams) {
         const E *xc = xg + (size_t)cl * a.hw, *dc = dyg + (size_t)cl * a.hw;
-        float dx[4] = {0.0f, 0.0f, 0.0f, 0.0f}, d1[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-        float x1[4] = {0.0f, 0.0f, 0.0f, 0.0f}, x2[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-        int p = lane;
-        for (; p + 192 < a.hw; p += 256) {
-            float xv[4], dv[4];
+        float dx[V], d1[V], x1[V], x2[V];
 #pragma unroll
-            for (int u = 0; u < 4; ++u) { xv[u] = In<BF16>::ld(xc + p + 64 * u) - k; dv[u] = In<BF16>::ld(dc + p + 64 * u); }
+        for (int e = 0; e < V; ++e) dx[e] = d1[e] = x1[e] = x2[e] = 0.0f;
+        auto add = [&](const float (&xv)[V], const float (&dv)[V]) {
 #pragma unroll
-            for (int u = 0; u < 4; ++u) { dx[u] += dv[u] * xv[u]; d1[u] += dv[u]; x1[u] += xv[u]; x2[u] += xv[u] * xv[u]; }
+            for (int e = 0; e < V; ++e) {
+                const float xs = xv[e] - k;
+                dx[e] += dv[e] * xs; d1[e] += dv[e]; x1[e] += xs; x2[e] += xs * xs;
+            }
+        };
+        int p = tl;
+        for (; p + 3 * team < nv; p += 4 * team) {
+            float xv[4][V], dv[4][V];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) { gn_load<BF16, V>(xc + (size_t)(p + u * team) * V, xv[u]); gn_load<BF16, V>(dc + (size_t)(p + u * team) * V, dv[u]); }
+#pragma unroll
+            for (int u = 0; u < 4; ++u) add(xv[u], dv[u]);
         }
-        for (; p < a.hw; p += 64) {
-            const float xv = In<BF16>::ld(xc + p) - k, dv = In<BF16>::ld(dc + p);
-            dx[0] += dv * xv; d1[0] += dv; x1[0] += xv; x2[0] += xv * xv;
+        {                                                             // up to three more vectors, loaded together
+            float xv[3][V], dv[3][V];
+#pragma unroll
+            for (int u = 0; u < 3; ++u) {
+                const int at = min(p + u * team, nv - 1);
+                gn_load<BF16, V>(xc + (size_t)at * V, xv[u]);
+                gn_load<BF16, V>(dc + (size_t)at * V, dv[u]);
+            }
+#pragma unroll
+            for (int u = 0; u < 3; ++u)
+                if (p + u * team < nv) add(xv[u], dv[u]);
         }
-        const float sdx = wave_sum((dx[0] + dx[1]) + (dx[2] + dx[3]));
-        const float sd = wave_sum((d1[0] + d1[1]) + (d1[2] + d1[3]));
-        sx += (x1[0] + x1[1]) + (x1[2] + x1[3]);
-        sxx += (x2[0] + x2[1]) + (x2[2] + x2[3]);
-        if (lane == 0) { s_dx[cl] = sdx; s_d[cl] = sd; }
+        float sdx = 0.0f, sd = 0.0f;
+#pragma unroll
+        for (int e = 0; e < V; ++e) { sdx += dx[e]; sd += d1[e]; sx += x1[e]; sxx += x2[e]; }
+        for (int off = team >> 1; off > 0; off >>= 1) { sdx += __shfl_xor(sdx, off, 64); sd += __shfl_xor(sd, off, 64); }
+        if (tl == 0 && live) { s_dx[cl] = sdx; s_d[cl] = sd; }
     }
-    const float m1 = block_sum<4>(sx, red) / (float)cnt;               // mean - k
-    const float m2 = block_sum<4>(sxx, red) / (float)cnt;
-    const float var = fmaxf(m2 - m1 * m1, 0.0f);
+    sx = wave_sum(sx);
+    sxx = wave_sum(sxx);
+    if (lane == 0) { red[wave] = sx; red[4 + wave] = sxx; }
+    __syncthreads();                                                  // also makes s_dx / s_d visible
+    sx = sxx = 0.0f;
+    for (int w = sub * waves; w < (sub + 1) * waves; ++w) { sx += red[w]; sxx += red[4 + w]; }
+    const float inv = 1.0f / (float)(cg * a.hw);
+    const float m1 = sx * inv, var = fmaxf(sxx * inv - m1 * m1, 0.0f);
     const float rstd = 1.0f / sqrtf(var + a.eps);
     float ss = 0.0f;
-    for (int cl = threadIdx.x; cl < cg; cl += 256) {                   // block_sum's barriers made s_dx / s_d visible
-        const float sg = rstd * (s_dx[cl] - m1 * s_d[cl]), sb = s_d[cl];
-        const int c = grp * cg + cl;
-        ss += sg * sg + sb * sb;
-        if (a.out_w) {
-            a.out_w[(size_t)i * a.out_stride_w + c] = sg;
-            a.out_b[(size_t)i * a.out_stride_b + c] = sb;
+    if (live) {
+        for (int cl = wv * 64 + lane; cl < cg; cl += waves * 64) {
+            const float sg = rstd * (s_dx[cl] - m1 * s_d[cl]), sb = s_d[cl];
+            const int c = grp * cg + cl;
+            ss += sg * sg + sb * sb;
+            if (a.out_w) {
+                a.out_w[(size_t)i * a.out_stride_w + c] = sg;
+                a.out_b[(size_t)i * a.out_stride_b + c] = sb;
+            }
         }
     }
-    const float tot = block_sum<4>(ss, red);
-    if (threadIdx.x == 0) a.partials[(size_t)i * a.groups + grp] = tot;
+    ss = wave_sum(ss);
+    __syncthreads();
+    if (lane == 0) red[wave] = ss;
+    __syncthreads();
+    if (lane == 0 && wv == 0 && live) {
+        float tot = 0.0f;
+        for (int w = sub * waves; w < (sub + 1) * waves; ++w) tot += red[w];
+        a.partials[(size_t)i * a.groups + grp] = tot;
+    }
+}
+
+template <bool BF16>
+__global__ void __launch_bounds__(256) gn_affine_kernel(const Grouped<GnArgs> grp)
+{
+    __shared__ float s_dx[GN_CMAX], s_d[GN_CMAX], red[8];
+    unsigned bid;
+    const GnArgs &a = grp.a[group_pick(grp, bid)];
+    if constexpr (BF16) {
+        if (a.vec == 8) { gn_affine_body<true, 8>(a, bid, s_dx, s_d, red); return; }
+    }
+    if (a.vec == 4) gn_affine_body<BF16, 4>(a, bid, s_dx, s_d, red);
+    else if (a.vec == 2) gn_affine_body<BF16, 2>(a, bid, s_dx, s_d, red);
+    else gn_affine_body<BF16, 1>(a, bid, s_dx, s_d, red);
+}
+
+// How the lanes of gn_affine_kernel are dealt to channels and groups.
+static void gn_plan(GnArgs &a, bool bf16)
+{
+    const int cg = a.c / a.groups;
+    a.vec = bf16 ? 8 : 4;
+    while (a.hw % a.vec) a.vec >>= 1;
+    const int nv = a.hw / a.vec;
+    a.team = 1;
+    while (a.team < 64 && a.team * 4 < nv) a.team <<= 1;              // about four vectors per lane,
+    while (a.team < 64 && (64 / a.team) / 2 >= cg) a.team <<= 1;      // and no more teams in a wave than the group has channels
+    a.waves = 4;
+    while (a.waves > 1 && a.waves * (64 / a.team) > cg && a.waves * 32 >= cg) a.waves >>= 1;     // (4 / waves) * cg channels fit in LDS
 }
 
 size_t gn_ws_bytes(const Geo &g, int mode)
@@ -375,24 +471,29 @@ dp_status launch_gn(const Geo &g, int mode, const void *x, const void *dy, float
         a.out_stride_b = out_stride ? out_stride : g.pb;
     }
     a.out_w = gw; a.out_b = gb;
-    const dim3 grid(g.gn_groups, g.n);
     const bool one_sweep = g.cin / g.gn_groups <= GN_CMAX;
-    if (g.bf16) {
-        if (one_sweep) hipLaunchKernelGGL(gn_affine_kernel<true>, grid, dim3(256), 0, s, a);
-        else hipLaunchKernelGGL(gn_affine_3pass_kernel<true>, grid, dim3(256), 0, s, a);
+    const void *fn;
+    long long blocks = (long long)g.n * g.gn_groups;
+    if (one_sweep) {
+        gn_plan(a, g.bf16);
+        blocks = (blocks + 4 / a.waves - 1) / (4 / a.waves);
+        fn = g.bf16 ? reinterpret_cast<const void *>(&gn_affine_kernel<true>) : reinterpret_cast<const void *>(&gn_affine_kernel<false>);
     } else {
-        if (one_sweep) hipLaunchKernelGGL(gn_affine_kernel<false>, grid, dim3(256), 0, s, a);
-        else hipLaunchKernelGGL(gn_affine_3pass_kernel<false>, grid, dim3(256), 0, s, a);
+        fn = g.bf16 ? reinterpret_cast<const void *>(&gn_affine_3pass_kernel<true>) : reinterpret_cast<const void *>(&gn_affine_3pass_kernel<false>);
     }
-    dp_status st = check_launch("gn_affine");
+    if (blocks > 0x7FFFFFFFll) return fail(DP_ERR_UNSUPPORTED, "GroupNorm: more than 2^31 groups in a call");
+    // (TIER_PRE: the timing aid brackets contractions only)
+    dp_status st = submit_kernel<GnArgs>(TIER_PRE, fn, a, (unsigned)blocks, 256, 0, s, "gn_affine");
     if (st != DP_OK) return st;
-    if (weighted) {
-        st = launch_clip_accumulate(gw, (size_t)g.cin, group_sqnorm, clip_c, g.n, (size_t)g.cin, out_w, s);
-        if (st != DP_OK) return st;
-        return launch_clip_accumulate(gb, (size_t)g.cin, group_sqnorm, clip_c, g.n, (size_t)g.cin, out_b, s);
-    }
+    const int n = g.n, c = g.cin, groups = g.gn_groups;
+    if (weighted)
+        return submit_post([=]() -> dp_status {
+            const dp_status sw = launch_clip_accumulate(gw, (size_t)c, group_sqnorm, clip_c, n, (size_t)c, out_w, s);
+            return sw != DP_OK ? sw : launch_clip_accumulate(gb, (size_t)c, group_sqnorm, clip_c, n, (size_t)c, out_b, s);
+        });
     if (!sqnorm) return st;
-    return launch_sum_partials(a.partials, g.n, g.gn_groups, sqnorm, s);
+    const float *partials = a.partials;
+    return submit_post([=]() -> dp_status { return launch_sum_partials(partials, n, groups, sqnorm, s); });
 }
 
 // Clipping units: rows[u*unit .. (u+1)*unit) of the per-example scale / shift gradients are added (in example
@@ -451,10 +552,11 @@ dp_status launch_gn_units(const Geo &g, int unit, const void *x, const void *dy,
     a.partials = reinterpret_cast<float *>(static_cast<char *>(ws) + gn_unit_head(g));
     a.c = g.cin; a.unit = unit;
     const int blocks = (g.cin + 255) / 256, units = g.n / unit;
-    hipLaunchKernelGGL(unit_rows_kernel, dim3(blocks, units), dim3(256), 0, s, a);
-    st = check_launch("unit_rows");
-    if (st != DP_OK || !sqnorm) return st;
-    return launch_sum_partials(a.partials, units, blocks, sqnorm, s);
+    return submit_post([=]() -> dp_status {
+        hipLaunchKernelGGL(unit_rows_kernel, dim3(blocks, units), dim3(256), 0, s, a);
+        const dp_status su = check_launch("unit_rows");
+        return (su != DP_OK || !sqnorm) ? su : launch_sum_partials(a.partials, units, blocks, sqnorm, s);
+    });
 }
 
 }  // namespace dp
