@@ -195,6 +195,17 @@ __device__ __forceinline__ float bf16_bits_to_float(uint16_t b)
     return __uint_as_float(((uint32_t)b) << 16);
 }
 
+// one element of an input tensor as fp32
+template <bool BF16> struct In;
+template <> struct In<true> {
+    typedef uint16_t type;
+    static __device__ __forceinline__ float ld(const uint16_t *p) { return bf16_bits_to_float(*p); }
+};
+template <> struct In<false> {
+    typedef float type;
+    static __device__ __forceinline__ float ld(const float *p) { return *p; }
+};
+
 // round to nearest, ties to even (finite inputs)
 __device__ __forceinline__ uint16_t float_to_bf16_bits(float f)
 {

@@ -1,224 +1,10 @@
-// Per-example gradients of dense layers and GroupNorm affine parameters (H1 for the layer
-// kinds that are not convolutions).  With one token per example a dense weight gradient is
-// the rank-one product dy_i (x) x_i: there is no contraction to put on MFMA, the kernel is a
-// streaming outer product.  GroupNorm scale/shift gradients are two reductions over each
-// channel of x and dy.
+// Per-example gradients of GroupNorm affine parameters: two reductions over each channel of x and dy.
 #include "internal.h"
 #include "group.h"
 
 namespace dp {
 
-template <bool BF16> struct In;
-template <> struct In<true> {
-    typedef uint16_t type;
-    static __device__ __forceinline__ float ld(const uint16_t *p) { return bf16_bits_to_float(*p); }
-};
-template <> struct In<false> {
-    typedef float type;
-    static __device__ __forceinline__ float ld(const float *p) { return *p; }
-};
-
-// ------------------------------------------------------------------------------------------
-// dense: dW_i[o,k] = sum_t dY_i[t,o] X_i[t,k];  db_i[o] = sum_t dY_i[t,o]
-// Workgroup tile: DR rows (o) x 256 columns (k); a thread owns one column, so x loads and
-// gradient stores are coalesced along k and dy values are wave-uniform.
-constexpr int DR = 16;
-
-struct DenseArgs {
-    const void *x, *dy;
-    float *out_w, *out_b;
-    size_t out_stride_w, out_stride_b;
-    float *partials;
-    const float *group_sqnorm;
-    float clip_c;
-    int n, tokens, cin, cout, has_bias;
-    int tiles_k, tiles_o;
-};
-
-template <bool BF16, bool WEIGHTED>
-__global__ void __launch_bounds__(256) dense_kernel(const DenseArgs a)
-{
-    typedef typename In<BF16>::type E;
-    __shared__ float red[4];
-    const int tile_k = blockIdx.x, tile_o = blockIdx.y;
-    const int k = tile_k * 256 + threadIdx.x;
-    const int o0 = tile_o * DR;
-    const bool k_ok = k < a.cin;
-    const E *xg = static_cast<const E *>(a.x), *dyg = static_cast<const E *>(a.dy);
-    const int i_begin = WEIGHTED ? 0 : blockIdx.z;
-    const int i_end = WEIGHTED ? a.n : blockIdx.z + 1;
-    const bool bias_thread = a.has_bias && tile_k == 0 && threadIdx.x < DR && o0 + threadIdx.x < a.cout;
-
-    float acc[DR];
-#pragma unroll
-    for (int r = 0; r < DR; ++r) acc[r] = 0.0f;
-    float accb = 0.0f;
-
-    for (int i = i_begin; i < i_end; ++i) {
-        const float f = WEIGHTED ? clip_factor(a.group_sqnorm[i], a.clip_c) : 1.0f;
-        const E *xi = xg + (size_t)i * a.tokens * a.cin;
-        const E *dyi = dyg + (size_t)i * a.tokens * a.cout;
-        for (int t = 0; t < a.tokens; ++t) {
-            const float xv = k_ok ? In<BF16>::ld(xi + (size_t)t * a.cin + k) * f : 0.0f;
-#pragma unroll
-            for (int r = 0; r < DR; ++r) {
-                const int o = o0 + r;
-                const float d = (o < a.cout) ? In<BF16>::ld(dyi + (size_t)t * a.cout + o) : 0.0f;
-                acc[r] += d * xv;
-            }
-            if (bias_thread) accb += In<BF16>::ld(dyi + (size_t)t * a.cout + o0 + threadIdx.x) * f;
-        }
-    }
-
-    if constexpr (!WEIGHTED) {
-        const int i = i_begin;
-        float ss = 0.0f;
-#pragma unroll
-        for (int r = 0; r < DR; ++r) {
-            ss += acc[r] * acc[r];
-            if (a.out_w && k_ok && o0 + r < a.cout)
-                a.out_w[(size_t)i * a.out_stride_w + (size_t)(o0 + r) * a.cin + k] = acc[r];
-        }
-        if (bias_thread) {
-            ss += accb * accb;
-            if (a.out_w) a.out_b[(size_t)i * a.out_stride_b + o0 + threadIdx.x] = accb;
-        }
-        const float tot = block_sum<4>(ss, red);
-        if (threadIdx.x == 0)
-            a.partials[(size_t)i * (a.tiles_k * a.tiles_o) + tile_o * a.tiles_k + tile_k] = tot;
-    } else {
-#pragma unroll
-        for (int r = 0; r < DR; ++r)
-            if (k_ok && o0 + r < a.cout) a.out_w[(size_t)(o0 + r) * a.cin + k] += acc[r];
-        if (bias_thread) a.out_b[o0 + threadIdx.x] += accb;
-    }
-}
-
-// One token per example: the gradient is the rank-one product dy_i (x) x_i (plus db_i = dy_i), so
-// its squared Frobenius norm is |dy_i|^2 |x_i|^2 (+ |dy_i|^2) -- the same number H2 defines, from
-// two short reductions instead of Cout*Cin products.  One workgroup per example.
-template <bool BF16>
-__global__ void __launch_bounds__(256) dense_rank1_norm_kernel(const DenseArgs a, float *sqnorm)
-{
-    typedef typename In<BF16>::type E;
-    __shared__ float red[4];
-    const int i = blockIdx.x;
-    const E *xi = static_cast<const E *>(a.x) + (size_t)i * a.cin;
-    const E *dyi = static_cast<const E *>(a.dy) + (size_t)i * a.cout;
-    float sx = 0.0f, sd = 0.0f;
-    for (int k = threadIdx.x; k < a.cin; k += 256) { const float v = In<BF16>::ld(xi + k); sx += v * v; }
-    for (int o = threadIdx.x; o < a.cout; o += 256) { const float v = In<BF16>::ld(dyi + o); sd += v * v; }
-    sx = block_sum<4>(sx, red);
-    sd = block_sum<4>(sd, red);
-    if (threadIdx.x == 0) sqnorm[i] = sd * sx + (a.has_bias ? sd : 0.0f);
-}
-
-// One token per example, clip-weighted sum: acc[o, k] += sum_i (f_i dy_i[o]) x_i[k].  Same tile
-// as dense_kernel (DR rows x 256 columns, a thread owns a column); the examples are taken 32 at
-// a time: their scaled dy values go through LDS, a thread keeps eight x loads in flight, and
-// the sum over examples runs in example order.
-template <bool BF16>
-__global__ void __launch_bounds__(256) dense_rank1_weighted_kernel(const DenseArgs a)
-{
-    typedef typename In<BF16>::type E;
-    constexpr int EB = 32;
-    __shared__ float sd[EB][DR];
-    const int tile_k = blockIdx.x, tile_o = blockIdx.y;
-    const int k = tile_k * 256 + threadIdx.x;
-    const int o0 = tile_o * DR;
-    const bool k_ok = k < a.cin;
-    const E *xg = static_cast<const E *>(a.x), *dyg = static_cast<const E *>(a.dy);
-    const bool bias_thread = a.has_bias && tile_k == 0 && threadIdx.x < DR && o0 + threadIdx.x < a.cout;
-    float acc[DR];
-#pragma unroll
-    for (int r = 0; r < DR; ++r) acc[r] = 0.0f;
-    float accb = 0.0f;
-    for (int i0 = 0; i0 < a.n; i0 += EB) {
-        __syncthreads();
-        for (int q = threadIdx.x; q < EB * DR; q += 256) {
-            const int ii = q / DR, r = q - ii * DR;
-            const int i = i0 + ii, o = o0 + r;
-            float v = 0.0f;
-            if (i < a.n && o < a.cout)
-                v = In<BF16>::ld(dyg + (size_t)i * a.cout + o) * clip_factor(a.group_sqnorm[i], a.clip_c);
-            sd[ii][r] = v;
-        }
-        __syncthreads();
-#pragma unroll 1
-        for (int ib = 0; ib < EB; ib += 8) {          // eight x loads in flight at a time
-            float xv[8];
-#pragma unroll
-            for (int u = 0; u < 8; ++u)
-                xv[u] = (k_ok && i0 + ib + u < a.n) ? In<BF16>::ld(xg + (size_t)(i0 + ib + u) * a.cin + k) : 0.0f;
-#pragma unroll
-            for (int u = 0; u < 8; ++u) {
-#pragma unroll
-                for (int r = 0; r < DR; ++r) acc[r] += sd[ib + u][r] * xv[u];
-            }
-        }
-        if (bias_thread) {
-#pragma unroll
-            for (int ii = 0; ii < EB; ++ii) accb += sd[ii][threadIdx.x];
-        }
-    }
-#pragma unroll
-    for (int r = 0; r < DR; ++r)
-        if (k_ok && o0 + r < a.cout) a.out_w[(size_t)(o0 + r) * a.cin + k] += acc[r];
-    if (bias_thread) a.out_b[o0 + threadIdx.x] += accb;
-}
-
-size_t dense_norm_partial_count(const Geo &g, int mode)
-{
-    if (mode == MODE_NORM && g.h == 1) return 1;      // rank-one closed form: one value per example
-    return (size_t)((g.cin + 255) / 256) * ((g.cout + DR - 1) / DR);
-}
-
 size_t gn_norm_partial_count(const Geo &g) { return (size_t)g.gn_groups; }
-
-size_t dense_ws_bytes(const Geo &g, int mode)
-{
-    if (mode == MODE_WEIGHTED) return 0;
-    const size_t tiles = (size_t)((g.cin + 255) / 256) * ((g.cout + DR - 1) / DR);
-    return (size_t)g.n * tiles * sizeof(float);
-}
-
-dp_status launch_dense(const Geo &g, int mode, const void *x, const void *dy, float *out_w, float *out_b,
-                       size_t out_stride, float *sqnorm, const float *group_sqnorm, float clip_c, void *ws,
-                       hipStream_t s)
-{
-    DenseArgs a;
-    a.x = x; a.dy = dy; a.out_w = out_w; a.out_b = out_b;
-    a.out_stride_w = out_stride ? out_stride : g.pw;
-    a.out_stride_b = out_stride ? out_stride : g.pb;
-    a.partials = static_cast<float *>(ws);
-    a.group_sqnorm = group_sqnorm; a.clip_c = clip_c;
-    a.n = g.n; a.tokens = g.h; a.cin = g.cin; a.cout = g.cout; a.has_bias = g.has_bias;
-    a.tiles_k = (g.cin + 255) / 256;
-    a.tiles_o = (g.cout + DR - 1) / DR;
-    const bool weighted = mode == MODE_WEIGHTED;
-    if (!weighted && !out_w && a.tokens == 1) {
-        if (!sqnorm) sqnorm = static_cast<float *>(ws);      // left as the single partial per example
-        if (g.bf16) hipLaunchKernelGGL((dense_rank1_norm_kernel<true>), dim3(g.n), dim3(256), 0, s, a, sqnorm);
-        else hipLaunchKernelGGL((dense_rank1_norm_kernel<false>), dim3(g.n), dim3(256), 0, s, a, sqnorm);
-        return check_launch("dense_rank1_norm");
-    }
-    const dim3 grid(a.tiles_k, a.tiles_o, weighted ? 1 : g.n);
-    if (weighted && a.tokens == 1) {
-        if (g.bf16) hipLaunchKernelGGL((dense_rank1_weighted_kernel<true>), grid, dim3(256), 0, s, a);
-        else hipLaunchKernelGGL((dense_rank1_weighted_kernel<false>), grid, dim3(256), 0, s, a);
-        return check_launch("dense_rank1_weighted");
-    }
-    if (g.bf16) {
-        if (weighted) hipLaunchKernelGGL((dense_kernel<true, true>), grid, dim3(256), 0, s, a);
-        else hipLaunchKernelGGL((dense_kernel<true, false>), grid, dim3(256), 0, s, a);
-    } else {
-        if (weighted) hipLaunchKernelGGL((dense_kernel<false, true>), grid, dim3(256), 0, s, a);
-        else hipLaunchKernelGGL((dense_kernel<false, false>), grid, dim3(256), 0, s, a);
-    }
-    dp_status st = check_launch("dense");
-    if (st != DP_OK || weighted || !sqnorm) return st;
-    return launch_sum_partials(a.partials, g.n, a.tiles_k * a.tiles_o, sqnorm, s);
-}
 
 // ------------------------------------------------------------------------------------------
 // GroupNorm affine, groups of more than GN_CMAX channels: one workgroup per (example, group).  Mean
