@@ -235,6 +235,29 @@ dp_status dp_unit_grad_batch(const dp_layer_desc *descs, int clip_unit, const vo
                              float *const *g_w, float *const *g_b, size_t g_stride, float *const *sqnorm,
                              void *const *ws, const size_t *ws_bytes, int n_layers, dp_stream stream);
 
+/* The batch calls above on examples that lie in SEVERAL tensors (the micro-steps of an optimiser step, each handed over in
+ * tensors of its own): x[l] and dy[l] are device arrays of desc.n example addresses (in place of the tensors), so that one
+ * launch contracts the examples of all of them; everything else as in the calls without "_at", same results up to the
+ * order of summation.  Channels-first layouts only (else DP_ERR_UNSUPPORTED).  Clipping units: the examples of a unit must
+ * follow each other in one tensor.
+ * dp_example_addresses writes such arrays: for operand o (layer l's x or dy) with n_tensors tensors of per_tensor examples,
+ *   table[(o * n_tensors + t) * per_tensor + j] = tensors[o * n_tensors + t] + j * example_bytes[o].
+ * tensors [host] n_operands * n_tensors device pointers, 16-byte aligned; example_bytes [host] n_operands; table [device]
+ * n_operands * n_tensors * per_tensor words, 8-byte aligned, to be kept until the calls that read it have run.            */
+dp_status dp_example_addresses(const void *const *tensors, const size_t *example_bytes, int n_operands, int n_tensors,
+                               int per_tensor, uint64_t *table, dp_stream stream);
+dp_status dp_per_example_grad_batch_at(const dp_layer_desc *descs, const uint64_t *const *x, const uint64_t *const *dy,
+                                       float *const *g_w, float *const *g_b, size_t g_stride, float *const *sqnorm,
+                                       void *const *ws, const size_t *ws_bytes, int32_t *partial_counts, int n_layers,
+                                       dp_stream stream);
+dp_status dp_clip_accumulate_recompute_batch_at(const dp_layer_desc *descs, const uint64_t *const *x, const uint64_t *const *dy,
+                                                const float *const *sqnorm, const float *clip_c, float *const *acc_w,
+                                                float *const *acc_b, void *const *ws, const size_t *ws_bytes, int n_layers,
+                                                dp_stream stream);
+dp_status dp_unit_grad_batch_at(const dp_layer_desc *descs, int clip_unit, const uint64_t *const *x, const uint64_t *const *dy,
+                                float *const *g_w, float *const *g_b, size_t g_stride, float *const *sqnorm,
+                                void *const *ws, const size_t *ws_bytes, int n_layers, dp_stream stream);
+
 /* group_sqnorm[g, i] = sum over the layers l of group g, in order, of sum_c partials[l][i * counts[l] + c].
  * partials [host] array of n_layers device pointers (4-byte aligned); counts, group_of_layer [host]
  * arrays of n_layers ints; group_sqnorm [device] [n_groups, n], overwritten.                       */
@@ -279,6 +302,14 @@ dp_status dp_clip_accumulate(const float *g, size_t g_stride, const float *sqnor
 dp_status dp_clip_accumulate_segments(const float *g, size_t g_stride, const float *group_sqnorm, int n_groups,
                                       const size_t *seg_begin, const int32_t *seg_group, const float *seg_clip, int n_seg,
                                       int n, size_t p, float *acc, dp_stream stream);
+
+/* The same with a place of its own in the accumulator for every segment: column e of segment k is added to
+ * acc[seg_acc[k] + e - seg_begin[k]] (the columns of g need not lie as acc does).  seg_acc [host] n_seg multiples of 4;
+ * the places must not overlap.  The rows are added in runs of `run` (a divisor of n): the sums of the runs are added to acc
+ * one after the other, as that many calls with n = run would.                                       */
+dp_status dp_clip_accumulate_columns(const float *g, size_t g_stride, const float *group_sqnorm, int n_groups,
+                                     const size_t *seg_begin, const size_t *seg_acc, const int32_t *seg_group,
+                                     const float *seg_clip, int n_seg, int n, int run, size_t p, float *acc, dp_stream stream);
 
 /* H4, recomputing form: the same sum without per-example gradients in memory,
  *   acc_w += sum_i f_i * dW_i,  acc_b += sum_i f_i * db_i,

@@ -69,6 +69,11 @@ def load_library():
         "dp_per_example_grad_batch": (it, [vp, vp, vp, vp, vp, sz, vp, vp, vp, vp, it, vp]),
         "dp_layer_norms_from_partials": (it, [vp, vp, vp, it, it, vp]),
         "dp_clip_accumulate_recompute_batch": (it, [vp, vp, vp, vp, vp, vp, vp, vp, vp, it, vp]),
+        "dp_example_addresses": (it, [vp, vp, it, it, it, vp, vp]),
+        "dp_per_example_grad_batch_at": (it, [vp, vp, vp, vp, vp, sz, vp, vp, vp, vp, it, vp]),
+        "dp_clip_accumulate_recompute_batch_at": (it, [vp, vp, vp, vp, vp, vp, vp, vp, vp, it, vp]),
+        "dp_unit_grad_batch_at": (it, [vp, it, vp, vp, vp, vp, sz, vp, vp, vp, it, vp]),
+        "dp_clip_accumulate_columns": (it, [vp, sz, vp, it, vp, vp, vp, vp, it, it, it, sz, vp, vp]),
         "dp_clip_factors": (it, [vp, fl, it, vp, vp]),
         "dp_clip_accumulate": (it, [vp, sz, vp, fl, it, sz, vp, vp]),
         "dp_clip_accumulate_segments": (it, [vp, sz, vp, it, vp, vp, vp, it, it, sz, vp, vp]),
@@ -95,6 +100,8 @@ EXPORTED = ("dp_group_clip_bounds", "dp_weight_count", "dp_bias_count", "dp_work
             "dp_unit_workspace_bytes", "dp_unit_grad", "dp_unit_grad_batch",
             "dp_norm_partial_count", "dp_per_example_grad_partials", "dp_norms_from_partials",
             "dp_per_example_grad_batch", "dp_layer_norms_from_partials", "dp_clip_accumulate_recompute_batch",
+            "dp_example_addresses", "dp_per_example_grad_batch_at", "dp_clip_accumulate_recompute_batch_at", "dp_unit_grad_batch_at",
+            "dp_clip_accumulate_columns",
             "dp_clip_factors", "dp_clip_accumulate", "dp_clip_accumulate_segments", "dp_clip_accumulate_recompute", "dp_add_noise_finalize", "dp_add_noise_finalize_update", "dp_add_example_noise",
             "dp_add_noise_finalize_flat", "dp_philox_raw", "dp_profile_next_contraction", "dp_last_error", "dp_version")
 
@@ -229,6 +236,16 @@ class LayerBatch:
         self.ws = (C.c_void_p * k)(*[int(p) for p in ws_ptrs])
         self.ws_bytes = (C.c_size_t * k)(*[int(b) for b in ws_bytes])
         self.partial_counts = (C.c_int32 * k)()          # written by dp_per_example_grad_batch
+        self._kept = {}
+
+    def fill(self, key, values):
+        """An array of device addresses that is kept and overwritten by the next fill of the same key (the library reads it
+        before its call returns)."""
+        arr = self._kept.get(key)
+        if arr is None:
+            arr = self._kept[key] = (C.c_void_p * self.n_layers)()
+        arr[:] = values
+        return arr
 
     def ptrs(self, values):
         assert len(values) == self.n_layers
@@ -239,28 +256,28 @@ class LayerBatch:
         return (C.c_float * self.n_layers)(*[float(v) for v in values])
 
 
-def dp_per_example_grad_batch(batch: "LayerBatch", x, dy, g_w, g_b, sqnorm, g_stride: int = 0, stream=None):
-    """x, dy: ctypes pointer arrays from batch.ptrs(); g_w, g_b, sqnorm: the same or None (sqnorm None: the
-    per-layer reduction is left to dp_layer_norms_from_partials).  batch.partial_counts receives the number of
-    partial sums per example each layer left at the start of its workspace."""
-    _check(load_library().dp_per_example_grad_batch(C.cast(batch.descs, C.c_void_p), C.cast(x, C.c_void_p),
-                                                    C.cast(dy, C.c_void_p),
-                                                    None if g_w is None else C.cast(g_w, C.c_void_p),
-                                                    None if g_b is None else C.cast(g_b, C.c_void_p), g_stride,
-                                                    None if sqnorm is None else C.cast(sqnorm, C.c_void_p),
-                                                    C.cast(batch.ws, C.c_void_p), C.cast(batch.ws_bytes, C.c_void_p),
-                                                    C.cast(batch.partial_counts, C.c_void_p), batch.n_layers,
-                                                    _stream(stream)))
+def dp_example_addresses(tensors, example_bytes, n_operands: int, n_tensors: int, per_tensor: int, table, stream=None):
+    """tensors: n_operands * n_tensors device addresses; example_bytes: n_operands integers; table: a device int64 tensor (or its
+    address) that receives n_operands * n_tensors * per_tensor example addresses."""
+    _check(load_library().dp_example_addresses((C.c_void_p * len(tensors))(*tensors), (C.c_size_t * len(example_bytes))(*example_bytes),
+                                               n_operands, n_tensors, per_tensor, _ptr(table), _stream(stream)))
 
 
-def dp_unit_grad_batch(batch: "LayerBatch", clip_unit: int, x, dy, g_w, g_b, sqnorm, g_stride: int = 0, stream=None):
+def dp_per_example_grad_batch(batch: "LayerBatch", x, dy, g_w, g_b, sqnorm, g_stride: int = 0, stream=None, addresses: bool = False):
+    """x, dy: ctypes pointer arrays from batch.ptrs() (addresses=True: of arrays of example addresses); g_w, g_b, sqnorm: the
+    same or None (sqnorm None: the per-layer reduction is left to dp_layer_norms_from_partials).  batch.partial_counts receives
+    the number of partial sums per example each layer left at the start of its workspace."""
+    lib = load_library()
+    _check((lib.dp_per_example_grad_batch_at if addresses else lib.dp_per_example_grad_batch)(
+        batch.descs, x, dy, g_w, g_b, g_stride, sqnorm, batch.ws, batch.ws_bytes, batch.partial_counts, batch.n_layers, _stream(stream)))
+
+
+def dp_unit_grad_batch(batch: "LayerBatch", clip_unit: int, x, dy, g_w, g_b, sqnorm, g_stride: int = 0, stream=None,
+                       addresses: bool = False):
     """dp_unit_grad for the layers of a LayerBatch; x, dy, sqnorm: ctypes pointer arrays from batch.ptrs()."""
-    _check(load_library().dp_unit_grad_batch(C.cast(batch.descs, C.c_void_p), clip_unit, C.cast(x, C.c_void_p),
-                                             C.cast(dy, C.c_void_p),
-                                             None if g_w is None else C.cast(g_w, C.c_void_p),
-                                             None if g_b is None else C.cast(g_b, C.c_void_p), g_stride,
-                                             C.cast(sqnorm, C.c_void_p), C.cast(batch.ws, C.c_void_p),
-                                             C.cast(batch.ws_bytes, C.c_void_p), batch.n_layers, _stream(stream)))
+    lib = load_library()
+    _check((lib.dp_unit_grad_batch_at if addresses else lib.dp_unit_grad_batch)(
+        batch.descs, clip_unit, x, dy, g_w, g_b, g_stride, sqnorm, batch.ws, batch.ws_bytes, batch.n_layers, _stream(stream)))
 
 
 def dp_layer_norms_from_partials(partials, counts, sqnorm, n_layers: int, n: int, stream=None):
@@ -269,13 +286,10 @@ def dp_layer_norms_from_partials(partials, counts, sqnorm, n_layers: int, n: int
                                                        C.cast(sqnorm, C.c_void_p), n_layers, n, _stream(stream)))
 
 
-def dp_clip_accumulate_recompute_batch(batch: "LayerBatch", x, dy, sqnorm, clip_c, acc_w, acc_b, stream=None):
-    _check(load_library().dp_clip_accumulate_recompute_batch(C.cast(batch.descs, C.c_void_p), C.cast(x, C.c_void_p),
-                                                             C.cast(dy, C.c_void_p), C.cast(sqnorm, C.c_void_p),
-                                                             C.cast(clip_c, C.c_void_p), C.cast(acc_w, C.c_void_p),
-                                                             None if acc_b is None else C.cast(acc_b, C.c_void_p),
-                                                             C.cast(batch.ws, C.c_void_p), C.cast(batch.ws_bytes, C.c_void_p),
-                                                             batch.n_layers, _stream(stream)))
+def dp_clip_accumulate_recompute_batch(batch: "LayerBatch", x, dy, sqnorm, clip_c, acc_w, acc_b, stream=None, addresses: bool = False):
+    lib = load_library()
+    _check((lib.dp_clip_accumulate_recompute_batch_at if addresses else lib.dp_clip_accumulate_recompute_batch)(
+        batch.descs, x, dy, sqnorm, clip_c, acc_w, acc_b, batch.ws, batch.ws_bytes, batch.n_layers, _stream(stream)))
 
 
 def dp_norms(layer_sqnorm, group_of_layer, n_layers: int, n: int, n_groups: int, group_sqnorm, stream=None):
@@ -293,14 +307,16 @@ def dp_clip_accumulate(g, sqnorm, clip_c: float, n: int, p: int, acc, g_stride: 
 
 
 class SegmentTable:
-    """Host arrays for dp_clip_accumulate_segments: column where each segment starts, its clipping group and bound."""
+    """Host arrays for dp_clip_accumulate_segments: column where each segment starts, its clipping group and bound, and (for
+    dp_clip_accumulate_columns) where it lies in the accumulator."""
 
-    def __init__(self, begins, groups, clips):
+    def __init__(self, begins, groups, clips, places=None):
         k = len(begins)
         self.n_seg = k
         self.begin = (C.c_size_t * k)(*[int(b) for b in begins])
         self.group = (C.c_int32 * k)(*[int(g) for g in groups])
         self.clip = (C.c_float * k)(*[float(c) for c in clips])
+        self.place = (C.c_size_t * k)(*[int(p) for p in (begins if places is None else places)])
 
 
 def dp_clip_accumulate_segments(g, group_sqnorm, n_groups: int, table: "SegmentTable", n: int, p: int, acc,
@@ -309,6 +325,12 @@ def dp_clip_accumulate_segments(g, group_sqnorm, n_groups: int, table: "SegmentT
                                                       C.cast(table.begin, C.c_void_p), C.cast(table.group, C.c_void_p),
                                                       C.cast(table.clip, C.c_void_p), table.n_seg, n, p, _ptr(acc),
                                                       _stream(stream)))
+
+
+def dp_clip_accumulate_columns(g, group_sqnorm, n_groups: int, table: "SegmentTable", n: int, run: int, p: int, acc, g_stride: int = 0,
+                               stream=None):
+    _check(load_library().dp_clip_accumulate_columns(_ptr(g), g_stride, _ptr(group_sqnorm), n_groups, table.begin, table.place, table.group,
+                                                     table.clip, table.n_seg, n, run, p, _ptr(acc), _stream(stream)))
 
 
 def dp_clip_accumulate_recompute(desc, x, dy, sqnorm, clip_c: float, acc_w, acc_b, ws,

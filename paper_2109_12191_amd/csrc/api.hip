@@ -89,6 +89,14 @@ dp_status flush_queue(LaunchQueue &q)
     return DP_OK;
 }
 
+// The geometry of a call whose x / dy are arrays of example addresses (dp_example_addresses).
+static dp_status read_addresses(Geo &g)
+{
+    if (g.nhwc) return fail(DP_ERR_UNSUPPORTED, "channels-last inputs are not offered with example addresses");
+    g.x_tab = g.dy_tab = 1;
+    return DP_OK;
+}
+
 static bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 
 // Validate a descriptor and derive its geometry.  Limits keep every index in 32 bits inside
@@ -435,10 +443,11 @@ static int batch_target(const std::vector<Geo> &geo)
     return per_wg < 4.0 ? 4 : (per_wg > 64.0 ? 64 : (int)per_wg);
 }
 
-dp_status dp_per_example_grad_batch(const dp_layer_desc *descs, const void *const *x, const void *const *dy,
-                                    float *const *g_w, float *const *g_b, size_t g_stride, float *const *sqnorm,
-                                    void *const *ws, const size_t *ws_bytes, int32_t *partial_counts, int n_layers,
-                                    dp_stream stream)
+// addresses: x[l], dy[l] are arrays of example addresses
+static dp_status per_example_grad_batch(bool addresses, const dp_layer_desc *descs, const void *const *x, const void *const *dy,
+                                        float *const *g_w, float *const *g_b, size_t g_stride, float *const *sqnorm,
+                                        void *const *ws, const size_t *ws_bytes, int32_t *partial_counts, int n_layers,
+                                        dp_stream stream)
 {
     if (!descs || !x || !dy || !ws || !ws_bytes)
         return fail(DP_ERR_INVALID_ARG, "descs, x, dy, ws and ws_bytes must be non-NULL host arrays");
@@ -449,6 +458,7 @@ dp_status dp_per_example_grad_batch(const dp_layer_desc *descs, const void *cons
     for (int l = 0; l < n_layers; ++l) {             // everything is validated before anything is launched
         Geo &g = geo[(size_t)l];
         DP_TRY(make_geo(&descs[l], g));
+        if (addresses) DP_TRY(read_addresses(g));
         if (g.n != geo[0].n) return fail(DP_ERR_INVALID_ARG, "layer %d: n = %d differs from layer 0's %d", l, g.n, geo[0].n);
         DP_TRY(check_ptr(x[l], "x[l]", true));
         DP_TRY(check_ptr(dy[l], "dy[l]", true));
@@ -492,9 +502,26 @@ dp_status dp_per_example_grad_batch(const dp_layer_desc *descs, const void *cons
     return launch_layer_norms(parts.data(), counts.data(), sqnorm, n_layers, geo[0].n, s);
 }
 
-dp_status dp_unit_grad_batch(const dp_layer_desc *descs, int clip_unit, const void *const *x, const void *const *dy,
-                             float *const *g_w, float *const *g_b, size_t g_stride, float *const *sqnorm,
-                             void *const *ws, const size_t *ws_bytes, int n_layers, dp_stream stream)
+dp_status dp_per_example_grad_batch(const dp_layer_desc *descs, const void *const *x, const void *const *dy,
+                                    float *const *g_w, float *const *g_b, size_t g_stride, float *const *sqnorm,
+                                    void *const *ws, const size_t *ws_bytes, int32_t *partial_counts, int n_layers,
+                                    dp_stream stream)
+{
+    return per_example_grad_batch(false, descs, x, dy, g_w, g_b, g_stride, sqnorm, ws, ws_bytes, partial_counts, n_layers, stream);
+}
+
+dp_status dp_per_example_grad_batch_at(const dp_layer_desc *descs, const uint64_t *const *x, const uint64_t *const *dy,
+                                       float *const *g_w, float *const *g_b, size_t g_stride, float *const *sqnorm,
+                                       void *const *ws, const size_t *ws_bytes, int32_t *partial_counts, int n_layers,
+                                       dp_stream stream)
+{
+    return per_example_grad_batch(true, descs, reinterpret_cast<const void *const *>(x), reinterpret_cast<const void *const *>(dy), g_w, g_b,
+                                  g_stride, sqnorm, ws, ws_bytes, partial_counts, n_layers, stream);
+}
+
+static dp_status unit_grad_batch(bool addresses, const dp_layer_desc *descs, int clip_unit, const void *const *x, const void *const *dy,
+                                 float *const *g_w, float *const *g_b, size_t g_stride, float *const *sqnorm,
+                                 void *const *ws, const size_t *ws_bytes, int n_layers, dp_stream stream)
 {
     if (!descs || !x || !dy || !sqnorm || !ws || !ws_bytes)
         return fail(DP_ERR_INVALID_ARG, "descs, x, dy, sqnorm, ws and ws_bytes must be non-NULL host arrays");
@@ -504,6 +531,10 @@ dp_status dp_unit_grad_batch(const dp_layer_desc *descs, int clip_unit, const vo
     for (int l = 0; l < n_layers; ++l) {             // everything is validated before anything is launched
         Geo &g = geo[(size_t)l];
         DP_TRY(unit_geo(&descs[l], clip_unit, g));
+        if (addresses) {
+            DP_TRY(read_addresses(g));
+            if (g.kind == DP_DENSE) g.x_tab = g.dy_tab = clip_unit;      // its "examples" are units, which start at every clip_unit-th address
+        }
         if (descs[l].n != descs[0].n) return fail(DP_ERR_INVALID_ARG, "layer %d: n = %d differs from layer 0's %d", l, descs[l].n, descs[0].n);
         DP_TRY(check_ptr(x[l], "x[l]", true));
         DP_TRY(check_ptr(dy[l], "dy[l]", true));
@@ -558,6 +589,34 @@ dp_status dp_unit_grad_batch(const dp_layer_desc *descs, int clip_unit, const vo
     return launch_layer_norms(parts.data(), counts.data(), sqnorm, n_layers, units, s);
 }
 
+dp_status dp_unit_grad_batch(const dp_layer_desc *descs, int clip_unit, const void *const *x, const void *const *dy,
+                             float *const *g_w, float *const *g_b, size_t g_stride, float *const *sqnorm,
+                             void *const *ws, const size_t *ws_bytes, int n_layers, dp_stream stream)
+{
+    return unit_grad_batch(false, descs, clip_unit, x, dy, g_w, g_b, g_stride, sqnorm, ws, ws_bytes, n_layers, stream);
+}
+
+dp_status dp_unit_grad_batch_at(const dp_layer_desc *descs, int clip_unit, const uint64_t *const *x, const uint64_t *const *dy,
+                                float *const *g_w, float *const *g_b, size_t g_stride, float *const *sqnorm,
+                                void *const *ws, const size_t *ws_bytes, int n_layers, dp_stream stream)
+{
+    return unit_grad_batch(true, descs, clip_unit, reinterpret_cast<const void *const *>(x), reinterpret_cast<const void *const *>(dy), g_w, g_b,
+                           g_stride, sqnorm, ws, ws_bytes, n_layers, stream);
+}
+
+dp_status dp_example_addresses(const void *const *tensors, const size_t *example_bytes, int n_operands, int n_tensors,
+                               int per_tensor, uint64_t *table, dp_stream stream)
+{
+    if (!tensors || !example_bytes) return fail(DP_ERR_INVALID_ARG, "tensors and example_bytes must be non-NULL host arrays");
+    if (n_operands < 1 || n_tensors < 1 || per_tensor < 1)
+        return fail(DP_ERR_INVALID_ARG, "n_operands (%d), n_tensors (%d) and per_tensor (%d) must be >= 1", n_operands, n_tensors, per_tensor);
+    DP_TRY(check_ptr(table, "table", true, 8));
+    for (size_t k = 0; k < (size_t)n_operands * n_tensors; ++k)
+        if (!tensors[k] || !aligned16(tensors[k])) return fail(DP_ERR_INVALID_ARG, "tensors[%zu] is NULL or not 16-byte aligned", k);
+    g_err[0] = 0;
+    return launch_example_addresses(tensors, example_bytes, n_operands, n_tensors, per_tensor, table, static_cast<hipStream_t>(stream));
+}
+
 dp_status dp_layer_norms_from_partials(const float *const *partials, const int32_t *counts, float *const *sqnorm,
                                        int n_layers, int n, dp_stream stream)
 {
@@ -575,10 +634,9 @@ dp_status dp_layer_norms_from_partials(const float *const *partials, const int32
     return launch_layer_norms(partials, counts, sqnorm, n_layers, n, static_cast<hipStream_t>(stream));
 }
 
-dp_status dp_clip_accumulate_recompute_batch(const dp_layer_desc *descs, const void *const *x, const void *const *dy,
-                                             const float *const *sqnorm, const float *clip_c, float *const *acc_w,
-                                             float *const *acc_b, void *const *ws, const size_t *ws_bytes, int n_layers,
-                                             dp_stream stream)
+static dp_status recompute_batch(bool addresses, const dp_layer_desc *descs, const void *const *x, const void *const *dy,
+                                 const float *const *sqnorm, const float *clip_c, float *const *acc_w, float *const *acc_b,
+                                 void *const *ws, const size_t *ws_bytes, int n_layers, dp_stream stream)
 {
     if (!descs || !x || !dy || !sqnorm || !clip_c || !acc_w || !ws || !ws_bytes)
         return fail(DP_ERR_INVALID_ARG, "descs, x, dy, sqnorm, clip_c, acc_w, ws and ws_bytes must be non-NULL host arrays");
@@ -587,6 +645,7 @@ dp_status dp_clip_accumulate_recompute_batch(const dp_layer_desc *descs, const v
     for (int l = 0; l < n_layers; ++l) {
         Geo &g = geo[(size_t)l];
         DP_TRY(make_geo(&descs[l], g));
+        if (addresses) DP_TRY(read_addresses(g));
         DP_TRY(check_ptr(x[l], "x[l]", true));
         DP_TRY(check_ptr(dy[l], "dy[l]", true));
         DP_TRY(check_ptr(sqnorm[l], "sqnorm[l]", true, 4));
@@ -613,6 +672,23 @@ dp_status dp_clip_accumulate_recompute_batch(const dp_layer_desc *descs, const v
     if (st == DP_OK) st = flush_queue(q);
     set_open_queue(nullptr);
     return st;
+}
+
+dp_status dp_clip_accumulate_recompute_batch(const dp_layer_desc *descs, const void *const *x, const void *const *dy,
+                                             const float *const *sqnorm, const float *clip_c, float *const *acc_w,
+                                             float *const *acc_b, void *const *ws, const size_t *ws_bytes, int n_layers,
+                                             dp_stream stream)
+{
+    return recompute_batch(false, descs, x, dy, sqnorm, clip_c, acc_w, acc_b, ws, ws_bytes, n_layers, stream);
+}
+
+dp_status dp_clip_accumulate_recompute_batch_at(const dp_layer_desc *descs, const uint64_t *const *x, const uint64_t *const *dy,
+                                                const float *const *sqnorm, const float *clip_c, float *const *acc_w,
+                                                float *const *acc_b, void *const *ws, const size_t *ws_bytes, int n_layers,
+                                                dp_stream stream)
+{
+    return recompute_batch(true, descs, reinterpret_cast<const void *const *>(x), reinterpret_cast<const void *const *>(dy), sqnorm, clip_c,
+                           acc_w, acc_b, ws, ws_bytes, n_layers, stream);
 }
 
 dp_status dp_norms_from_partials(const float *const *partials, const int32_t *counts, const int32_t *group_of_layer,
@@ -675,15 +751,16 @@ dp_status dp_clip_accumulate(const float *g, size_t g_stride, const float *sqnor
     return launch_clip_accumulate(g, g_stride, sqnorm, clip_c, n, p, acc, static_cast<hipStream_t>(stream));
 }
 
-dp_status dp_clip_accumulate_segments(const float *g, size_t g_stride, const float *group_sqnorm, int n_groups,
-                                      const size_t *seg_begin, const int32_t *seg_group, const float *seg_clip, int n_seg,
-                                      int n, size_t p, float *acc, dp_stream stream)
+dp_status dp_clip_accumulate_columns(const float *g, size_t g_stride, const float *group_sqnorm, int n_groups,
+                                     const size_t *seg_begin, const size_t *seg_acc, const int32_t *seg_group,
+                                     const float *seg_clip, int n_seg, int n, int run, size_t p, float *acc, dp_stream stream)
 {
     DP_TRY(check_ptr(g, "g", true));
     DP_TRY(check_ptr(group_sqnorm, "group_sqnorm", true, 4));
     DP_TRY(check_ptr(acc, "acc", true));
-    if (!seg_begin || !seg_group || !seg_clip) return fail(DP_ERR_INVALID_ARG, "segment tables must be non-NULL host arrays");
+    if (!seg_begin || !seg_acc || !seg_group || !seg_clip) return fail(DP_ERR_INVALID_ARG, "segment tables must be non-NULL host arrays");
     if (n < 1 || n_groups < 1 || n_seg < 1) return fail(DP_ERR_INVALID_ARG, "n, n_groups and n_seg must be >= 1");
+    if (run < 1 || n % run) return fail(DP_ERR_INVALID_ARG, "run = %d must be at least 1 and divide n = %d", run, n);
     if (p < 4 || p % 4) return fail(DP_ERR_INVALID_ARG, "p must be a positive multiple of 4");
     if (g_stride == 0) g_stride = p;
     if (g_stride < p || g_stride % 4) return fail(DP_ERR_INVALID_ARG, "g_stride must be a multiple of 4 and at least p");
@@ -693,11 +770,19 @@ dp_status dp_clip_accumulate_segments(const float *g, size_t g_stride, const flo
         const size_t end = k + 1 < n_seg ? seg_begin[k + 1] : p;
         if (seg_begin[k] % 4 || seg_begin[k] >= end) return fail(DP_ERR_INVALID_ARG, "segment %d: boundaries must be increasing multiples of 4 below p", k);
         if (seg_group[k] < 0 || seg_group[k] >= n_groups) return fail(DP_ERR_INVALID_ARG, "segment %d: group %d outside [0, %d)", k, seg_group[k], n_groups);
+        if (seg_acc[k] % 4) return fail(DP_ERR_INVALID_ARG, "segment %d: its place in acc must be a multiple of 4", k);
         DP_TRY(check_clip(seg_clip[k]));
     }
     g_err[0] = 0;
-    return launch_clip_accumulate_segments(g, g_stride, group_sqnorm, seg_begin, seg_group, seg_clip, n_seg, n, p, acc,
+    return launch_clip_accumulate_segments(g, g_stride, group_sqnorm, seg_begin, seg_acc, seg_group, seg_clip, n_seg, n, run, p, acc,
                                            static_cast<hipStream_t>(stream));
+}
+
+dp_status dp_clip_accumulate_segments(const float *g, size_t g_stride, const float *group_sqnorm, int n_groups,
+                                      const size_t *seg_begin, const int32_t *seg_group, const float *seg_clip, int n_seg,
+                                      int n, size_t p, float *acc, dp_stream stream)
+{
+    return dp_clip_accumulate_columns(g, g_stride, group_sqnorm, n_groups, seg_begin, seg_begin, seg_group, seg_clip, n_seg, n, n < 1 ? 1 : n, p, acc, stream);
 }
 
 dp_status dp_clip_accumulate_recompute(const dp_layer_desc *desc, const void *x, const void *dy, const float *sqnorm,

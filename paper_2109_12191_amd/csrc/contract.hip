@@ -64,6 +64,7 @@ struct ConvArgs {
     int ex_per_split;                 // weighted mode
     int ex_per_wg;                    // per-example mode, ksplit == 1: consecutive examples per workgroup
     int force_slow;                   // stride other than 1 or 2: stage every chunk element by element
+    int x_tab, dy_tab;                // Geo::x_tab / dy_tab: the operand pointers are arrays of example addresses
     int unit_major;                   // weighted mode, > 0: clipping units, each made of unit_major example ranges; the
                                       // ranges' blocks always go to the workspace, ordered (unit, tile, range in unit)
 };
@@ -299,7 +300,9 @@ __device__ __noinline__ void slow_stage_b(char *lds, const typename ElemTraits<B
 // (1x1 stride-1 conv with S % 8 == 0 for bf16): every piece is a single aligned 16-byte load.
 // LOADER 1 / 2: general geometry with stride 1 / 2 (any other stride runs LOADER 1 with every
 // chunk staged element by element).
-template <bool BF16, int WAVES_M, int WAVES_N, int TM, int TN, bool WEIGHTED, bool BIAS, int LOADER>
+// AT: the operands are arrays of example addresses, every example a tensor of its own (instantiations of their own: 3 to 6 %
+// of the time of the others where both ways share one).
+template <bool BF16, int WAVES_M, int WAVES_N, int TM, int TN, bool WEIGHTED, bool BIAS, int LOADER, bool AT>
 __global__ void __launch_bounds__(THREADS, 2) conv_contract_kernel(const Grouped<ConvArgs> grp)
 {
     unsigned bid;                                   // workgroup number within this workgroup's layer
@@ -383,6 +386,14 @@ __global__ void __launch_bounds__(THREADS, 2) conv_contract_kernel(const Grouped
 
     const size_t x_ex = (size_t)a.cin * a.h * a.w, dy_ex = (size_t)a.cout * a.S;
     const E *xg = static_cast<const E *>(a.x), *dyg = static_cast<const E *>(a.dy);
+    auto x_at = [&](int i) -> const E * {
+        if constexpr (AT) return example_at_uniform<E>(a.x, a.x_tab, i, x_ex);
+        else return xg + (size_t)i * x_ex;
+    };
+    auto dy_at = [&](int i) -> const E * {
+        if constexpr (AT) return example_at_uniform<E>(a.dy, a.dy_tab, i, dy_ex);
+        else return dyg + (size_t)i * dy_ex;
+    };
 
     // per-thread constants of the staging map: piece c = tid + 256 q -> row c / 8, K-piece c % 8.
     // Everything that does not change from chunk to chunk is computed here, once.
@@ -446,17 +457,26 @@ __global__ void __launch_bounds__(THREADS, 2) conv_contract_kernel(const Grouped
     // Position of the next chunk to fetch: example, chunk within it, and this thread's (oh, ow0);
     // advanced incrementally (no division in the loop).
     int f_i = i_begin, f_c = c_begin;
+    // AT: where the example of the next chunk is, found when the stream gets to it
+    const E *f_x = nullptr, *f_dy = nullptr;
+    if constexpr (AT) { f_x = x_at(f_i); f_dy = dy_at(f_i); }
     const int kprime0 = c_begin * KC + kp;
     const int oh0 = (LOADER == 0) ? 0 : kprime0 / a.kcolsp;
     const int ow00 = (LOADER == 0) ? kprime0 : kprime0 - oh0 * a.kcolsp;
     const int step_oh = (LOADER == 0) ? 0 : KC / a.kcolsp, step_ow = (LOADER == 0) ? KC : KC - step_oh * a.kcolsp;
     int f_oh = oh0, f_ow = ow00;
 
-    // dword pointer and element parity of example i's first element (tensors are 16-byte aligned)
-    auto ex_words = [&](const E *base, size_t ex_elems, int i, int &par) -> const uint32_t * {
-        const size_t eb = (size_t)i * ex_elems;
-        par = (int)(eb % EPD);
-        return reinterpret_cast<const uint32_t *>(base) + eb / EPD;
+    // dword an example's operand starts in and the elements before it in that dword
+    auto ex_words = [&](const E *base, size_t ex_elems, int i, const E *at, int &par) -> const uint32_t * {
+        if constexpr (AT) {
+            const uintptr_t v = reinterpret_cast<uintptr_t>(at);
+            par = (int)((v & 3u) / sizeof(E));
+            return reinterpret_cast<const uint32_t *>(v & ~(uintptr_t)3);
+        } else {
+            const size_t eb = (size_t)i * ex_elems;       // (tensors are 16-byte aligned)
+            par = (int)(eb % EPD);
+            return reinterpret_cast<const uint32_t *>(base) + eb / EPD;
+        }
     };
 
     // Issue every global load of the next chunk (no use of the data here, so no wait either).
@@ -471,7 +491,7 @@ __global__ void __launch_bounds__(THREADS, 2) conv_contract_kernel(const Grouped
                 const int hi = min(EPP, a.S - kprime);
                 const int back = (hi > 0 && hi < EPP) ? EPP - hi : 0;
                 const uint32_t meta = (uint32_t)max(hi, 0) | ((uint32_t)back << 8);
-                const E *pa_ = dyg + (size_t)i * dy_ex + (kprime - back);
+                const E *pa_ = (AT ? f_dy : dyg + (size_t)i * dy_ex) + (kprime - back);
 #pragma unroll
                 for (int q = 0; q < PA; ++q) {
                     u32x4_a4 v = {0u, 0u, 0u, 0u};
@@ -479,7 +499,7 @@ __global__ void __launch_bounds__(THREADS, 2) conv_contract_kernel(const Grouped
                     R.ra[q].d[0] = v.x; R.ra[q].d[1] = v.y; R.ra[q].d[2] = v.z; R.ra[q].d[3] = v.w;
                     R.ma[q] = meta;
                 }
-                const E *pb_ = xg + (size_t)i * x_ex + (kprime - back);
+                const E *pb_ = (AT ? f_x : xg + (size_t)i * x_ex) + (kprime - back);
 #pragma unroll
                 for (int q = 0; q < PB; ++q) {
                     u32x4_a4 v = {0u, 0u, 0u, 0u};
@@ -491,11 +511,11 @@ __global__ void __launch_bounds__(THREADS, 2) conv_contract_kernel(const Grouped
                 const int oh = f_oh, ow0 = f_ow;
                 R.oh = oh; R.ow0 = ow0;
                 const bool k_ok = oh < a.oh;
-                const bool first = (i == 0), last = (i == a.n - 1);
+                const bool first = AT || i == 0, last = AT || i == a.n - 1;         // (of its tensor)
                 {
                     // A: dY_i[m, oh, ow0 .. ow0+EPP)
                     int par;
-                    const uint32_t *wa = ex_words(dyg, dy_ex, i, par);
+                    const uint32_t *wa = ex_words(dyg, dy_ex, i, f_dy, par);
                     const int koff = k_ok ? oh * a.ow + ow0 : 0;
                     const int hi_a = k_ok ? min(a.ow - ow0, EPP) : 0;
 #pragma unroll
@@ -518,7 +538,7 @@ __global__ void __launch_bounds__(THREADS, 2) conv_contract_kernel(const Grouped
                     // B: X_i[ci, oh*s + dh, (ow0 + e)*s + dw]; only the image edge is masked here,
                     // positions past OW meet the zeros of A
                     int par;
-                    const uint32_t *wb = ex_words(xg, x_ex, i, par);
+                    const uint32_t *wb = ex_words(xg, x_ex, i, f_x, par);
                     const int ihs = oh * a.stride, iws = ow0 * a.stride;
                     const int koff = ihs * a.w + iws;
 #pragma unroll
@@ -558,7 +578,12 @@ __global__ void __launch_bounds__(THREADS, 2) conv_contract_kernel(const Grouped
         f_oh += step_oh;
         f_ow += step_ow;
         if (LOADER != 0 && f_ow >= a.kcolsp) { f_ow -= a.kcolsp; ++f_oh; }
-        if (f_c == c_end) { f_c = c_begin; ++f_i; f_oh = oh0; f_ow = ow00; }
+        if (f_c == c_end) {
+            f_c = c_begin; ++f_i; f_oh = oh0; f_ow = ow00;
+            if constexpr (AT) {
+                if (f_i < i_end) { f_x = x_at(f_i); f_dy = dy_at(f_i); }
+            }
+        }
     };
 
     // the partial last piece of a flat row was read `back` elements early: move it down (whole
@@ -575,8 +600,8 @@ __global__ void __launch_bounds__(THREADS, 2) conv_contract_kernel(const Grouped
         float f = 1.0f;
         if constexpr (WEIGHTED) f = a.group_sqnorm ? clip_factor(a.group_sqnorm[i], a.clip_c) : 1.0f;
         if (all_slow) {
-            slow_stage_a<BF16, MT, WEIGHTED>(bufA, dyg + (size_t)i * dy_ex, a.cout, a.S, a.oh, a.ow, a.kcolsp, m0, k0, f);
-            slow_stage_b<BF16, NT>(bufB, xg + (size_t)i * x_ex, cols, a.h, a.w, a.oh, a.ow, a.stride, a.kcolsp, k0);
+            slow_stage_a<BF16, MT, WEIGHTED>(bufA, dy_at(i), a.cout, a.S, a.oh, a.ow, a.kcolsp, m0, k0, f);
+            slow_stage_b<BF16, NT>(bufB, x_at(i), cols, a.h, a.w, a.oh, a.ow, a.stride, a.kcolsp, k0);
             return;
         }
         const int lds_col = (threadIdx.x & 7) * 16;
@@ -614,10 +639,10 @@ __global__ void __launch_bounds__(THREADS, 2) conv_contract_kernel(const Grouped
         }
         if constexpr (LOADER != 0) {
             // the few pieces staged as zeros because their window would have left the tensor
-            if (i == 0 || i == a.n - 1) {
+            if (AT || i == 0 || i == a.n - 1) {
                 const int oh = R.oh, ow0 = R.ow0;
-                const E *ex_a = dyg + (size_t)i * dy_ex;
-                const E *ex_b = xg + (size_t)i * x_ex;
+                const E *ex_a = dy_at(i);
+                const E *ex_b = x_at(i);
 #pragma unroll
                 for (int q = 0; q < PA; ++q) {
                     if (R.ma[q] & UNSAFE) {
@@ -907,7 +932,9 @@ __global__ void __launch_bounds__(WM * 128, (STAGES * (WM * TM + 2 * TN) * 4 <= 
     const int n_examples = __builtin_amdgcn_readfirstlane(a.n), chunks_per_ex = __builtin_amdgcn_readfirstlane(a.chunks_per_ex);
     const int ksplit = __builtin_amdgcn_readfirstlane(a.ksplit);
     const size_t x_ex = (size_t)a.cin * S, dy_ex = (size_t)cout * S;
-    const E *xg = static_cast<const E *>(a.x), *dyg = static_cast<const E *>(a.dy);
+    const int x_tab = __builtin_amdgcn_readfirstlane(a.x_tab), dy_tab = __builtin_amdgcn_readfirstlane(a.dy_tab);
+    auto x_at = [&](int i) { return example_at_uniform<E>(a.x, x_tab, i, x_ex); };
+    auto dy_at = [&](int i) { return example_at_uniform<E>(a.dy, dy_tab, i, dy_ex); };
     // the last chunk of an example when the row does not end on a chunk boundary: only some K steps hold data
     const int last_valid = S - (chunks_per_ex - 1) * KC;              // elements of a row in the last chunk: 1 .. 64
     const bool has_tail = last_valid < KC;
@@ -948,8 +975,8 @@ __global__ void __launch_bounds__(WM * 128, (STAGES * (WM * TM + 2 * TN) * 4 <= 
     }
 
     // ---- the stream of chunks to fetch: scalar base addresses advanced by constants
-    unsigned long long ga = uniform_bits(dyg + (size_t)i_begin * dy_ex + (size_t)c_begin * KC);
-    unsigned long long gb = uniform_bits(xg + (size_t)i_begin * x_ex + (size_t)c_begin * KC);
+    unsigned long long ga = uniform_bits(dy_at(i_begin) + (size_t)c_begin * KC);
+    unsigned long long gb = uniform_bits(x_at(i_begin) + (size_t)c_begin * KC);
     const unsigned long long a_jump = (unsigned long long)(dy_ex - (size_t)cpe * KC) * 2ull;      // from an example's last chunk to the next one's first
     const unsigned long long b_jump = (unsigned long long)(x_ex - (size_t)cpe * KC) * 2ull;
     const unsigned lds_wave = __builtin_amdgcn_readfirstlane((unsigned)(size_t)lds + (unsigned)wave * 1024u);
@@ -962,7 +989,7 @@ __global__ void __launch_bounds__(WM * 128, (STAGES * (WM * TM + 2 * TN) * 4 <= 
         } else {
             // offsets are unsigned, so those of the last chunk count from the start of the chunk before it.  The partial
             // last piece of the tensor's very last row would read past the tensor: it fetches the stand-in as well.
-            const unsigned guard = (tail && f_i == n_examples - 1) ? guard_mask : 0u;
+            const unsigned guard = (tail && (x_tab || dy_tab || f_i == n_examples - 1)) ? guard_mask : 0u;
 #pragma unroll
             for (int q = 0; q < NLD; ++q)
                 lds_direct_16_lanes((q < NLA ? ga : gb) - 2ull * KC, ((guard >> q) & 1u) ? stand_off[q] : tail_off[q], f_dst + q * (NWAVES * 1024),
@@ -972,18 +999,23 @@ __global__ void __launch_bounds__(WM * 128, (STAGES * (WM * TM + 2 * TN) * 4 <= 
         gb += 2ull * KC;
         f_dst += STAGE_BYTES;
         if (f_dst >= lds_wave + STAGES * STAGE_BYTES) f_dst = lds_wave;
-        if (++f_c == c_end) { f_c = c_begin; ++f_i; ga += a_jump; gb += b_jump; }
+        if (++f_c == c_end) {
+            f_c = c_begin; ++f_i; ga += a_jump; gb += b_jump;
+            if (f_i < i_end) {
+                if (dy_tab) ga = uniform_bits(dy_at(f_i) + (size_t)c_begin * KC);
+                if (x_tab) gb = uniform_bits(x_at(f_i) + (size_t)c_begin * KC);
+            }
+        }
     };
 
-    // the tensor's very last row, last example: its partial last piece fetched a stand-in; the valid dwords
-    // come through registers (taken by at most two workgroups of a launch), between two barriers
-    auto fix_very_last = [&](int stage) {
+    // the very last row of a tensor's last example: its partial last piece fetched a stand-in; the valid dwords
+    // come through registers (in one tensor of all examples, at most two workgroups of a launch), between two barriers
+    auto fix_very_last = [&](int stage, int ex_i) {
 #pragma unroll
         for (int q = 0; q < NLD; ++q) {
             if ((guard_mask >> q) & 1u) {
                 uint32_t *d4 = reinterpret_cast<uint32_t *>(lds + stage * STAGE_BYTES + (NWAVES * q + wave) * 1024 + lane * 16);
-                const char *ex = reinterpret_cast<const char *>(q < NLA ? dyg + (size_t)(n_examples - 1) * dy_ex
-                                                                        : xg + (size_t)(n_examples - 1) * x_ex);
+                const char *ex = reinterpret_cast<const char *>(q < NLA ? dy_at(ex_i) : x_at(ex_i));
                 const uint32_t *src = reinterpret_cast<const uint32_t *>(ex + byte_off[q] + (size_t)(chunks_per_ex - 1) * KC * 2);
 #pragma unroll
                 for (int d = 0; d < 3; ++d)
@@ -1173,8 +1205,8 @@ __global__ void __launch_bounds__(WM * 128, (STAGES * (WM * TM + 2 * TN) * 4 <= 
         }
         if (tail_here) {
             begin_step();
-            if (tail && ex == n_examples - 1 && edge_tile) {                    // uniform, rare
-                fix_very_last(stage);
+            if (tail && edge_tile && (x_tab || dy_tab || ex == n_examples - 1)) {           // uniform, rare
+                fix_very_last(stage, ex);
                 __syncthreads();
             }
             compute_tail(stage);
@@ -1351,20 +1383,23 @@ __global__ void __launch_bounds__(512, 1) conv_panel_kernel(const Grouped<ConvAr
     const int n_blocks = (i_end - i_begin) * STEPS;
     const unsigned row_bytes = 2u * (unsigned)S, block_bytes = 32u * row_bytes, share = block_bytes / 8u;
     const unsigned slot_bytes = block_bytes + 64u;       // padding: the last row's last K step reads 24 bytes past it
-    const E *const xg = static_cast<const E *>(a.x), *const dyg = static_cast<const E *>(a.dy);
     float *const out_w = a.out_w;
     float *const partials = a.partials;
     const bool store = out_w != nullptr;
 
     // ---- the stream of blocks to fetch
     int f_i = i_begin, f_p = 0, fetched = 0;
+    const int x_tab = __builtin_amdgcn_readfirstlane(a.x_tab), dy_tab = __builtin_amdgcn_readfirstlane(a.dy_tab);
+    auto x_at = [&](int i) { return uniform_bits(example_at_uniform<E>(a.x, x_tab, i, (size_t)J * S) + (size_t)j0 * S); };
+    auto dy_at = [&](int i) { return uniform_bits(example_at_uniform<E>(a.dy, dy_tab, i, (size_t)cout * S) + (size_t)m0 * S); };
+    unsigned long long f_x = x_at(f_i), f_dy = dy_at(f_i);           // the tile's first row of either operand
     unsigned f_slot = 0;
     const unsigned lds0 = __builtin_amdgcn_readfirstlane((unsigned)(size_t)lds);
     const unsigned long long lanes_last = __ballot(lane < S / 2 - 64 * (NL - 1));       // never empty (the host checks S)
     auto fetch = [&]() {
-        const E *src = f_p < 8 ? dyg + ((size_t)f_i * cout + m0 + 32 * f_p) * S
-                               : xg + ((size_t)f_i * J + j0 + 32 * (f_p - 8)) * S;
-        const unsigned long long base = uniform_bits(src) + (unsigned long long)((unsigned)wave * share);
+        const unsigned long long src = f_p < 8 ? f_dy + (unsigned long long)((unsigned)f_p * block_bytes)
+                                               : f_x + (unsigned long long)((unsigned)(f_p - 8) * block_bytes);
+        const unsigned long long base = src + (unsigned long long)((unsigned)wave * share);
         const unsigned dst = lds0 + f_slot * slot_bytes + (unsigned)wave * share;
 #pragma unroll
         for (int q = 0; q < NL; ++q) {
@@ -1372,7 +1407,10 @@ __global__ void __launch_bounds__(512, 1) conv_panel_kernel(const Grouped<ConvAr
             else lds_direct_16_lanes(base, (unsigned)lane * 16u + q * 1024u, dst + q * 1024u, lanes_last);
         }
         if (++f_slot == R) f_slot = 0;
-        if (++f_p == STEPS) { f_p = 0; ++f_i; }
+        if (++f_p == STEPS) {
+            f_p = 0; ++f_i;
+            if (f_i < i_end) { f_x = x_at(f_i); f_dy = dy_at(f_i); }
+        }
         ++fetched;
     };
 
@@ -1636,6 +1674,7 @@ static bool packed_weighted(const Geo &g, int mode, PackPlan &pp, Geo &g2)
     g2.kh = 1; g2.kw = 1; g2.stride = 1; g2.pad = 0;
     g2.x_elems = (size_t)J * pp.kg;
     g2.dy_elems = (size_t)g.cout * pp.kg;
+    g2.x_tab = g2.dy_tab = 0;
     return true;
 }
 
@@ -1650,6 +1689,7 @@ static bool subsampled(const Geo &g, int mode, Geo &g2)
     g2 = g;
     g2.h = g.oh; g2.w = g.ow; g2.stride = 1;
     g2.x_elems = (size_t)g.cin * s;
+    g2.x_tab = 0;
     // odd rows would go through the gather loader anyway (no gain) unless the norm-only call can then take
     // the Gram route
     if (s % 2 && !gram_norm_applicable(g2, mode)) return false;
@@ -1771,23 +1811,29 @@ static const void *fixup_of(bool weighted, bool bias)
     return reinterpret_cast<const void *>(&conv_fixup_kernel<WM, WN, TM, TN, false, false>);
 }
 
-template <bool BF16, int WM, int WN, int TM, int TN, int SIMPLE>
+template <bool BF16, int WM, int WN, int TM, int TN, int SIMPLE, bool AT>
 static const void *kernel_of2(bool weighted, bool bias)
 {
     if (weighted) {
-        if (bias) return reinterpret_cast<const void *>(&conv_contract_kernel<BF16, WM, WN, TM, TN, true, true, SIMPLE>);
-        return reinterpret_cast<const void *>(&conv_contract_kernel<BF16, WM, WN, TM, TN, true, false, SIMPLE>);
+        if (bias) return reinterpret_cast<const void *>(&conv_contract_kernel<BF16, WM, WN, TM, TN, true, true, SIMPLE, AT>);
+        return reinterpret_cast<const void *>(&conv_contract_kernel<BF16, WM, WN, TM, TN, true, false, SIMPLE, AT>);
     }
-    if (bias) return reinterpret_cast<const void *>(&conv_contract_kernel<BF16, WM, WN, TM, TN, false, true, SIMPLE>);
-    return reinterpret_cast<const void *>(&conv_contract_kernel<BF16, WM, WN, TM, TN, false, false, SIMPLE>);
+    if (bias) return reinterpret_cast<const void *>(&conv_contract_kernel<BF16, WM, WN, TM, TN, false, true, SIMPLE, AT>);
+    return reinterpret_cast<const void *>(&conv_contract_kernel<BF16, WM, WN, TM, TN, false, false, SIMPLE, AT>);
+}
+
+template <bool BF16, int WM, int WN, int TM, int TN, bool AT>
+static const void *kernel_of1(int loader, bool weighted, bool bias)
+{
+    if (loader == 0) return kernel_of2<BF16, WM, WN, TM, TN, 0, AT>(weighted, bias);
+    if (loader == 1) return kernel_of2<BF16, WM, WN, TM, TN, 1, AT>(weighted, bias);
+    return kernel_of2<BF16, WM, WN, TM, TN, 2, AT>(weighted, bias);
 }
 
 template <bool BF16, int WM, int WN, int TM, int TN>
-static const void *kernel_of(int loader, bool weighted, bool bias)
+static const void *kernel_of(int loader, bool weighted, bool bias, bool at)
 {
-    if (loader == 0) return kernel_of2<BF16, WM, WN, TM, TN, 0>(weighted, bias);
-    if (loader == 1) return kernel_of2<BF16, WM, WN, TM, TN, 1>(weighted, bias);
-    return kernel_of2<BF16, WM, WN, TM, TN, 2>(weighted, bias);
+    return at ? kernel_of1<BF16, WM, WN, TM, TN, true>(loader, weighted, bias) : kernel_of1<BF16, WM, WN, TM, TN, false>(loader, weighted, bias);
 }
 
 static dp_status launch_conv_impl(const Geo &g, int mode, const void *x, const void *dy, float *out_w, float *out_b,
@@ -1884,7 +1930,7 @@ static dp_status launch_conv_impl(const Geo &g, int mode, const void *x, const v
     const bool weighted = mode == MODE_WEIGHTED || unit > 0;
     ConvArgs a;
     a.unit_major = unit ? unit / f.ex_per_split : 0;
-    a.x = x; a.dy = dy;
+    a.x = x; a.dy = dy; a.x_tab = g.x_tab; a.dy_tab = g.dy_tab;
     a.n = g.n; a.cin = g.cin; a.cout = g.cout; a.h = f.h; a.w = f.w; a.kh = g.kh; a.kw = g.kw;
     a.stride = g.stride; a.pad = g.pad; a.oh = f.oh; a.ow = f.ow;
     a.J = g.cin * g.kh * g.kw;
@@ -1915,6 +1961,7 @@ static dp_status launch_conv_impl(const Geo &g, int mode, const void *x, const v
     const unsigned blocks = (unsigned)(((total + 7) / 8) * 8);
     const bool bias = g.has_bias != 0;
     const int loader = loader_of(g);
+    const bool at = a.x_tab || a.dy_tab;
     a.force_slow = (g.stride > 2) ? 1 : 0;
     const void *fn;
     unsigned lds_bytes = 0;
@@ -1943,8 +1990,8 @@ static dp_status launch_conv_impl(const Geo &g, int mode, const void *x, const v
                 return fail(DP_ERR_DEVICE, "conv_flat: cannot reserve %u bytes of LDS", lds_bytes);
             attr_done[f.shape][weighted ? 1 : 0].store(true);
         }
-    } else if (g.bf16) fn = (f.shape == T64) ? kernel_of<true, 2, 2, 1, 1>(loader, weighted, bias) : kernel_of<true, 2, 2, 2, 2>(loader, weighted, bias);
-    else fn = (f.shape == T64) ? kernel_of<false, 2, 2, 1, 1>(loader, weighted, bias) : kernel_of<false, 2, 2, 2, 2>(loader, weighted, bias);
+    } else if (g.bf16) fn = (f.shape == T64) ? kernel_of<true, 2, 2, 1, 1>(loader, weighted, bias, at) : kernel_of<true, 2, 2, 2, 2>(loader, weighted, bias, at);
+    else fn = (f.shape == T64) ? kernel_of<false, 2, 2, 1, 1>(loader, weighted, bias, at) : kernel_of<false, 2, 2, 2, 2>(loader, weighted, bias, at);
     dp_status st = submit_main<ConvArgs>(fn, a, blocks, (f.shape == T256x128 || f.shape == T256rows) ? 512 : THREADS, lds_bytes, s, "conv_contract");
     if (st != DP_OK) return st;
     // what follows the main kernel: at once, or after the grouped launches of a batch call

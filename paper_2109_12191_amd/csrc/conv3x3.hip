@@ -35,7 +35,8 @@ namespace {
 constexpr int C3_THREADS = 256;
 
 struct C3Args {
-    const uint16_t *x, *dy;
+    const void *x, *dy;
+    int x_tab, dy_tab;                // Geo::x_tab / dy_tab: the operand pointers are arrays of example addresses
     float *out_w;                     // per-example gradients (may be null) or, weighted, the accumulator
     size_t out_stride;
     float *partials;                  // [n, tiles] partial squared norms
@@ -193,8 +194,9 @@ __device__ __forceinline__ void c3_add_to_accumulator(const f32x16 (&acc)[9], co
 // is staged; added to the accumulator, or to the workspace when the examples are split into ranges).
 enum { C3_FULL = 0, C3_SLICED = 1, C3_WEIGHTED = 2 };
 
-// What one workgroup does; `bid` is its number within its layer.
-template <int W, int MODE, int STRIDE>
+// What one workgroup does; `bid` is its number within its layer.  AT: the operands are arrays of example addresses (a body of its
+// own: the accumulators leave no registers for both ways of addressing).
+template <int W, int MODE, int STRIDE, bool AT>
 __device__ __forceinline__ void conv3x3_body(const C3Args &a, const unsigned bid)
 {
     constexpr bool WEIGHTED = MODE == C3_WEIGHTED;
@@ -222,14 +224,13 @@ __device__ __forceinline__ void conv3x3_body(const C3Args &a, const unsigned bid
     const int wm = wave >> 1, wn = wave & 1;
     const int H = a.h;
 
-    // element offsets count from the start of the whole tensor (all n examples, below 2^31):
-    // whole-dword windows (10 elements from an even element index) may reach into the
-    // neighbouring example but never outside the tensor
+    // element offsets count from the start of the whole tensor (all n examples, below 2^31) or, where every example has an
+    // address of its own, from the dword it starts in: whole-dword windows (10 elements from an even element index) may
+    // reach into the neighbouring example of one tensor but never outside a tensor
     constexpr int XROW = (STRIDE == 1) ? W : C::WP;               // elements per row of the X tensor read here
     const int x_ex = a.cin * a.hin * XROW, dy_ex = a.cout * H * W;    // elements per example
-    const int x_end = a.n * x_ex, dy_end = a.n * dy_ex;
-    const uint32_t *xw = reinterpret_cast<const uint32_t *>(a.x);
-    const uint32_t *dyw = reinterpret_cast<const uint32_t *>(a.dy);
+    const uint16_t *xt = static_cast<const uint16_t *>(a.x), *dyt = static_cast<const uint16_t *>(a.dy);
+    int x_end = a.n * x_ex, dy_end = a.n * dy_ex;
 
     f32x16 acc[9];
 #pragma unroll
@@ -241,7 +242,21 @@ __device__ __forceinline__ void conv3x3_body(const C3Args &a, const unsigned bid
     const int c_end = WEIGHTED ? a.chunks : min(a.chunks, c_begin + a.chunks_per_split);
 
     for (int i = i_first; i < i_last; ++i) {
-    const int x_base = i * x_ex, dy_base = i * dy_ex;
+    int x_base = i * x_ex, dy_base = i * dy_ex;
+    if constexpr (AT && STRIDE == 1) {
+        const uintptr_t at = reinterpret_cast<uintptr_t>(example_at_uniform<uint16_t>(a.x, a.x_tab, i, 0));
+        xt = reinterpret_cast<const uint16_t *>(at & ~(uintptr_t)3);
+        x_base = (int)(at >> 1) & 1;
+        x_end = x_base + x_ex;
+    }
+    if constexpr (AT) {
+        const uintptr_t at = reinterpret_cast<uintptr_t>(example_at_uniform<uint16_t>(a.dy, a.dy_tab, i, 0));
+        dyt = reinterpret_cast<const uint16_t *>(at & ~(uintptr_t)3);
+        dy_base = (int)(at >> 1) & 1;
+        dy_end = dy_base + dy_ex;
+    }
+    const uint32_t *xw = reinterpret_cast<const uint32_t *>(xt);
+    const uint32_t *dyw = reinterpret_cast<const uint32_t *>(dyt);
     float f = 1.0f;
     if constexpr (WEIGHTED) f = a.group_sqnorm ? clip_factor(a.group_sqnorm[i], a.clip_c) : 1.0f;
     for (int chunk = c_begin; chunk < c_end; ++chunk) {
@@ -294,6 +309,8 @@ __device__ __forceinline__ void conv3x3_body(const C3Args &a, const unsigned bid
             return p;
         };
 
+        static_assert(C::PA_T <= 32 && C::PX_T <= 32, "a bit per piece");
+        uint32_t odd_a = 0, odd_x = 0;                // bit u: piece u is there but its window leaves the tensor
         // dY first, then X in batches of at most XB pieces per thread: the loads of a batch are all
         // issued before the first is used, and a batch is small enough to sit in registers beside
         // the 144 accumulators
@@ -303,7 +320,7 @@ __device__ __forceinline__ void conv3x3_body(const C3Args &a, const unsigned bid
 #pragma unroll
             for (int u = 0; u < C::PA_T; ++u) {
                 const PieceA p = piece_a(u);
-                if constexpr (C::ALIGNED_A) ra4[u] = *reinterpret_cast<const uint4 *>(a.dy + (p.valid ? p.rel : 0));
+                if constexpr (C::ALIGNED_A) ra4[u] = *reinterpret_cast<const uint4 *>(dyt + (p.valid ? p.rel : 0));
                 else ra[u] = piece_load_words(dyw + ((p.fast ? p.rel : 0) >> 1));
             }
 #pragma unroll
@@ -314,6 +331,7 @@ __device__ __forceinline__ void conv3x3_body(const C3Args &a, const unsigned bid
                     v = p.valid ? ra4[u] : make_uint4(0u, 0u, 0u, 0u);
                 } else {
                     uint32_t t[4];
+                    if (AT && p.valid && !p.fast) odd_a |= 1u << u;
                     piece_finish<true, 1>(t, ra[u], (uint32_t)(p.rel & 1), 0, p.fast ? p.hi : 0);
                     v = make_uint4(t[0], t[1], t[2], t[3]);
                 }
@@ -342,6 +360,7 @@ __device__ __forceinline__ void conv3x3_body(const C3Args &a, const unsigned bid
                     if (u0 + u >= C::PX_T) continue;
                     const PieceX p = piece_x(u0 + u);
                     uint32_t t[4];
+                    if (AT && p.valid && !p.fast) odd_x |= 1u << (u0 + u);
                     piece_finish<true, 1>(t, rx[u], (uint32_t)(p.rel & 1), p.fast ? p.lo : 0, p.fast ? p.hi : 0);
                     const uint4 v = make_uint4(t[0], t[1], t[2], t[3]);
                     if (p.write) *reinterpret_cast<uint4 *>(sX + p.lds_off) = v;
@@ -356,7 +375,7 @@ __device__ __forceinline__ void conv3x3_body(const C3Args &a, const unsigned bid
                 for (int u = 0; u < XB2; ++u) {
                     if (u0 + u < C::PX_T) {
                         const PieceX p = piece_x(u0 + u);
-                        rx[u] = *reinterpret_cast<const uint4 *>(a.x + (p.valid ? p.rel : 0));
+                        rx[u] = *reinterpret_cast<const uint4 *>(xt + (p.valid ? p.rel : 0));
                     }
                 }
 #pragma unroll
@@ -367,20 +386,34 @@ __device__ __forceinline__ void conv3x3_body(const C3Args &a, const unsigned bid
                 }
             }
         }
-        // Pieces whose whole-dword window would have left the tensor (only the first rows of the
-        // first example and the last rows of the last one) were written as zeros above: fill them
-        // in element by element, touching nothing but the valid elements.
-        if (i == 0 || i == a.n - 1) {
+        // Pieces whose whole-dword window would have left the tensor (the first piece of its first row, the pieces of its
+        // last ten elements) were written as zeros above: the few threads that hold one fill it in element by element,
+        // touching nothing but the valid elements.
+        if constexpr (!AT) {                          // one tensor: only its first and its last example have any
+            if (i == 0 || i == a.n - 1) {
+#pragma unroll 1
+                for (int u = 0; u < (C::ALIGNED_A ? 0 : C::PA_T); ++u) {
+                    const PieceA p = piece_a(u);
+                    if (p.valid && !p.fast) odd_a |= 1u << u;
+                }
+#pragma unroll 1
+                for (int u = 0; u < (STRIDE == 1 ? C::PX_T : 0); ++u) {
+                    const PieceX p = piece_x(u);
+                    if (p.valid && !p.fast) odd_x |= 1u << u;
+                }
+            }
+        }
+        if (odd_a | odd_x) {
             if constexpr (!C::ALIGNED_A) {
 #pragma unroll 1
-                for (int u = 0; u < C::PA_T; ++u) {
-                    const PieceA p = piece_a(u);
-                    if (p.valid && !p.fast) {
+                for (; odd_a; odd_a &= odd_a - 1) {
+                    const PieceA p = piece_a(__builtin_ctz(odd_a));
+                    {
                         uint16_t *dst = reinterpret_cast<uint16_t *>(sA + p.lds_off);
                         const int hi = min(8, p.hi);
 #pragma unroll 1
                         for (int e = 0; e < hi; ++e) {
-                            uint16_t val = a.dy[p.rel + e];
+                            uint16_t val = dyt[p.rel + e];
                             if constexpr (WEIGHTED) val = float_to_bf16_bits(bf16_bits_to_float(val) * f);
                             dst[e] = val;
                         }
@@ -388,13 +421,13 @@ __device__ __forceinline__ void conv3x3_body(const C3Args &a, const unsigned bid
                 }
             }
 #pragma unroll 1
-            for (int u = 0; u < (STRIDE == 1 ? C::PX_T : 0); ++u) {
-                const PieceX p = piece_x(u);
-                if (p.valid && !p.fast) {
+            for (; STRIDE == 1 && odd_x; odd_x &= odd_x - 1) {
+                const PieceX p = piece_x(__builtin_ctz(odd_x));
+                {
                     uint16_t *dst = reinterpret_cast<uint16_t *>(sX + p.lds_off);
                     const int hi = min(8, p.hi);
 #pragma unroll 1
-                    for (int e = p.lo; e < hi; ++e) dst[e] = a.x[p.rel + e];
+                    for (int e = p.lo; e < hi; ++e) dst[e] = xt[p.rel + e];
                 }
             }
         }
@@ -446,12 +479,12 @@ __device__ __forceinline__ void conv3x3_body(const C3Args &a, const unsigned bid
     }
 }
 
-template <int W, int MODE, int STRIDE>
+template <int W, int MODE, int STRIDE, bool AT>
 __global__ void __launch_bounds__(C3_THREADS, 2) conv3x3_kernel(const Grouped<C3Args> grp)
 {
     unsigned bid;
     const C3Args &a = grp.a[group_pick(grp, bid)];
-    conv3x3_body<W, MODE, STRIDE>(a, bid);
+    conv3x3_body<W, MODE, STRIDE, AT>(a, bid);
 }
 
 // The variants a ResNet of 224 x 224 images needs, in ONE kernel that dispatches on the layer's variant, so that all
@@ -471,7 +504,7 @@ constexpr bool c3_any_in_set(int variant, int set)
     return variant != C3_ANY_56_SLICED;
 }
 
-template <int SET>
+template <int SET, bool AT>
 __global__ void __launch_bounds__(C3_THREADS, 2) conv3x3_any_kernel(const Grouped<C3Args> grp)
 {
     unsigned bid;
@@ -479,7 +512,7 @@ __global__ void __launch_bounds__(C3_THREADS, 2) conv3x3_any_kernel(const Groupe
     const int v = __builtin_amdgcn_readfirstlane(a.variant);
 #define C3_ANY_CASE(ID, W, MODE, STRIDE)                                                  \
     if constexpr (c3_any_in_set(ID, SET)) {                                               \
-        if (v == ID) { conv3x3_body<W, MODE, STRIDE>(a, bid); return; }                   \
+        if (v == ID) { conv3x3_body<W, MODE, STRIDE, AT>(a, bid); return; }               \
     }
     C3_ANY_CASE(C3_ANY_56_SLICED, 56, C3_SLICED, 1)
     C3_ANY_CASE(C3_ANY_28_SLICED, 28, C3_SLICED, 1)
@@ -523,7 +556,8 @@ template <int W, int MODE, int STRIDE> constexpr int c3_any_variant()
 // n * cin * hin rows of `win` (even) elements; one thread per 16-byte output piece, which needs
 // the high (O') or low (E) halves of eight consecutive dwords of the input row.
 struct DeintArgs {
-    const uint16_t *x;
+    const void *x;
+    int x_tab, rows_per_ex;         // Geo::x_tab; rows of an example
     uint16_t *out;
     long long rows;
     int win, owp;
@@ -533,7 +567,6 @@ __global__ void __launch_bounds__(256) deinterleave2_kernel(const Grouped<DeintA
 {
     unsigned bid;
     const DeintArgs &a = grp.a[group_pick(grp, bid)];
-    const uint16_t *__restrict__ x = a.x;
     uint16_t *__restrict__ out = a.out;
     const long long rows = a.rows;
     const int win = a.win, owp = a.owp;
@@ -544,7 +577,14 @@ __global__ void __launch_bounds__(256) deinterleave2_kernel(const Grouped<DeintA
     const int pc = (int)(q - row * xpr);
     const bool odd_plane = pc < opr;
     const int first = odd_plane ? 8 * pc - 1 : 8 * (pc - opr);      // dword of element 0 of the piece
-    const uint32_t *src = reinterpret_cast<const uint32_t *>(x + (size_t)row * win);
+    const uint16_t *xr;
+    if (a.x_tab) {
+        const int i = (int)((unsigned)row / (unsigned)a.rows_per_ex);       // (rows < 2^31: conv3x3_applicable)
+        xr = example_at<uint16_t>(a.x, a.x_tab, i, 0) + (size_t)(row - (long long)i * a.rows_per_ex) * win;
+    } else {
+        xr = static_cast<const uint16_t *>(a.x) + (size_t)row * win;
+    }
+    const uint32_t *src = reinterpret_cast<const uint32_t *>(xr);
     const int nd = win / 2;
     uint32_t h[8];
 #pragma unroll
@@ -710,27 +750,31 @@ dp_status c3_launch_mode(const C3Args &a, unsigned blocks, hipStream_t s)
 {
     using C = C3Cfg<W, STRIDE>;
     constexpr int any = c3_any_variant<W, MODE, STRIDE>();
+    const bool at = a.dy_tab != 0;                   // (x has a table too, unless the kernel reads the parity-split copy)
     const int set = fuse_hint() == 2 ? 0 : 1;
     if (fuse_hint() && (set == 0 ? c3_any_in_set(any, 0) : c3_any_in_set(any, 1))) {
         // inside a batch call: every row width in one launch
-        const void *fn = set == 0 ? reinterpret_cast<const void *>(&conv3x3_any_kernel<0>)
-                                  : reinterpret_cast<const void *>(&conv3x3_any_kernel<1>);
-        static std::atomic<bool> any_attr_done[2];
-        if (!any_attr_done[set].load()) {
+        const void *fn = at ? (set == 0 ? reinterpret_cast<const void *>(&conv3x3_any_kernel<0, true>)
+                                        : reinterpret_cast<const void *>(&conv3x3_any_kernel<1, true>))
+                            : (set == 0 ? reinterpret_cast<const void *>(&conv3x3_any_kernel<0, false>)
+                                        : reinterpret_cast<const void *>(&conv3x3_any_kernel<1, false>));
+        static std::atomic<bool> any_attr_done[2][2];
+        if (!any_attr_done[at][set].load()) {
             if (hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, C3_ANY_LDS) != hipSuccess)
                 return fail(DP_ERR_DEVICE, "conv3x3: cannot reserve %d bytes of LDS", C3_ANY_LDS);
-            any_attr_done[set].store(true);
+            any_attr_done[at][set].store(true);
         }
         C3Args b = a;
         b.variant = any;
         return submit_main<C3Args>(fn, b, blocks, C3_THREADS, C3_ANY_LDS, s, "conv3x3");
     }
-    const void *fn = reinterpret_cast<const void *>(&conv3x3_kernel<W, MODE, STRIDE>);
-    static std::atomic<bool> attr_done;              // zero-initialised; setting the attribute twice is harmless
-    if (!attr_done.load()) {
+    const void *fn = at ? reinterpret_cast<const void *>(&conv3x3_kernel<W, MODE, STRIDE, true>)
+                        : reinterpret_cast<const void *>(&conv3x3_kernel<W, MODE, STRIDE, false>);
+    static std::atomic<bool> attr_done[2];           // zero-initialised; setting the attribute twice is harmless
+    if (!attr_done[at].load()) {
         if (hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, C::LDS) != hipSuccess)
             return fail(DP_ERR_DEVICE, "conv3x3: cannot reserve %d bytes of LDS", C::LDS);
-        attr_done.store(true);
+        attr_done[at].store(true);
     }
     return submit_main<C3Args>(fn, a, blocks, C3_THREADS, C::LDS, s, "conv3x3");
 }
@@ -851,8 +895,7 @@ dp_status launch_conv3x3(const Geo &g, int mode, const void *x, const void *dy, 
     C3Args a;
     a.variant = -1;
     a.unit_major = unit ? 1 : 0;
-    a.x = static_cast<const uint16_t *>(x);
-    a.dy = static_cast<const uint16_t *>(dy);
+    a.x = x; a.dy = dy; a.x_tab = g.x_tab; a.dy_tab = g.dy_tab;
     a.out_w = out_w;
     a.out_stride = out_stride ? out_stride : g.pw;
     a.group_sqnorm = group_sqnorm; a.clip_c = clip_c;
@@ -882,11 +925,12 @@ dp_status launch_conv3x3(const Geo &g, int mode, const void *x, const void *dy, 
         const long long rows = (long long)g.n * g.cin * g.h;
         const long long pieces = rows * ((2 * owp + 8) / 8);
         DeintArgs da;
-        da.x = a.x; da.out = reinterpret_cast<uint16_t *>(w); da.rows = rows; da.win = g.w; da.owp = owp;
+        da.x = x; da.x_tab = g.x_tab; da.rows_per_ex = g.cin * g.h; da.out = reinterpret_cast<uint16_t *>(w); da.rows = rows; da.win = g.w; da.owp = owp;
         st = submit_kernel<DeintArgs>(TIER_PRE, reinterpret_cast<const void *>(&deinterleave2_kernel), da,
                                       (unsigned)((pieces + 255) / 256), 256, 0, s, "deinterleave2");
         if (st != DP_OK) return st;
-        a.x = reinterpret_cast<const uint16_t *>(w);
+        a.x = w;
+        a.x_tab = 0;
     }
     if (g.stride == 2) {
         if (g.ow == 7) st = c3_launch_w<7, 2>(a, weighted, blocks, s);

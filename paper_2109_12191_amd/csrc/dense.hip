@@ -21,6 +21,7 @@ namespace {
 
 struct DenseArgs {
     const void *x, *dy;
+    int x_tab, dy_tab;              // Geo::x_tab / dy_tab: the operand pointers are arrays of example addresses
     float *out_w, *out_b;
     size_t out_stride_w, out_stride_b;
     float *partials;                // per-example kernels: [n, partial count]
@@ -46,8 +47,8 @@ __global__ void __launch_bounds__(256) dense_outer_kernel(const Grouped<DenseArg
     const int i = (int)(bid / (unsigned)tiles), tile = (int)(bid - (unsigned)i * (unsigned)tiles);
     const int tile_o = tile / a.tiles_k, tile_k = tile - tile_o * a.tiles_k;
     const int k = tile_k * 256 + threadIdx.x, o0 = tile_o * OUTER_ROWS;
-    const E *xi = static_cast<const E *>(a.x) + (size_t)i * a.cin;
-    const E *dyi = static_cast<const E *>(a.dy) + (size_t)i * a.cout;
+    const E *xi = example_at_uniform<E>(a.x, a.x_tab, (int)i, a.cin);
+    const E *dyi = example_at_uniform<E>(a.dy, a.dy_tab, (int)i, a.cout);
     const float xv = k < a.cin ? In<BF16>::ld(xi + k) : 0.0f;
     float *out = a.out_w + (size_t)i * a.out_stride_w + (size_t)o0 * a.cin + k;
     float ss = 0.0f;
@@ -76,8 +77,8 @@ __global__ void __launch_bounds__(256) dense_rank1_norm_kernel(const Grouped<Den
     __shared__ float red[4];
     unsigned i;
     const DenseArgs &a = grp.a[group_pick(grp, i)];
-    const E *xi = static_cast<const E *>(a.x) + (size_t)i * a.cin;
-    const E *dyi = static_cast<const E *>(a.dy) + (size_t)i * a.cout;
+    const E *xi = example_at_uniform<E>(a.x, a.x_tab, (int)i, a.cin);
+    const E *dyi = example_at_uniform<E>(a.dy, a.dy_tab, (int)i, a.cout);
     float sx = 0.0f, sd = 0.0f;
     for (int k = threadIdx.x; k < a.cin; k += 256) { const float v = In<BF16>::ld(xi + k); sx += v * v; }
     for (int o = threadIdx.x; o < a.cout; o += 256) { const float v = In<BF16>::ld(dyi + o); sd += v * v; }
@@ -206,13 +207,14 @@ __global__ void __launch_bounds__(256 * G, G == 1 ? 2 : 4) dense_tokens_kernel(c
     const int cb = t & 7, tb = (t & 127) >> 3;
     const int C = is_x ? a.cin : a.cout, col = min((is_x ? k0 : o0) + cb * 8, (C - 1) & ~7);
     const unsigned off = 2u * ((unsigned)tb * 4u * (unsigned)C + (unsigned)col);
-    const char *src = static_cast<const char *>(is_x ? a.x : a.dy);
+    const void *const operand = is_x ? a.x : a.dy;
+    const int tab = is_x ? a.x_tab : a.dy_tab;
     const bool even = (C & 1) == 0;
     char *dst = lds + ((is_x ? DT : 0) + cb * 8) * DT_PITCH + (tb & 1) * 8;
     const int slot0 = (tb >> 1) ^ cb ^ ((cb & 1) << 2);                      // slot of feature c of the block: slot0 ^ (c >> 1)
 
     const int tokens = a.tokens, cpe = (tokens + DTK - 1) / DTK, n_ex = a.n;
-    const unsigned long long total = (unsigned long long)n_ex * tokens * (unsigned)C;
+    const unsigned long long ex_elems = (unsigned long long)tokens * (unsigned)C;
     const int first_ex = WEIGHTED ? __builtin_amdgcn_readfirstlane(group) : ex, ex_step = G;
     const int mine = WEIGHTED ? (n_ex - first_ex + G - 1) / G * cpe : cpe;    // steps of this group
     const int all = WEIGHTED ? (n_ex + G - 1) / G * cpe : cpe;                // steps of the longest group
@@ -223,7 +225,16 @@ __global__ void __launch_bounds__(256 * G, G == 1 ? 2 : 4) dense_tokens_kernel(c
     uint32_t r_odd = 0;                                                       //   rows that start on an odd element,
     const uint16_t *r_slow = nullptr;                                         //   or where to stage it from element by element
     auto fetch = [&]() {
-        const unsigned long long e0 = ((unsigned long long)f_ex * tokens + (unsigned)(f_c * DTK)) * (unsigned)C;
+        // elements count from the start of the tensor, or from the dword an example with an address of its own starts in
+        const char *src = static_cast<const char *>(operand);
+        unsigned long long e0 = f_ex * ex_elems, total = n_ex * ex_elems;
+        if (tab) {
+            const unsigned long long at = reinterpret_cast<unsigned long long>(example_at_uniform<uint16_t>(operand, tab, f_ex, 0));
+            src = reinterpret_cast<const char *>(at & ~3ull);
+            e0 = (at >> 1) & 1u;
+            total = e0 + ex_elems;
+        }
+        e0 += (unsigned long long)(unsigned)(f_c * DTK) * (unsigned)C;
         const int valid = min(tokens - f_c * DTK, DTK);
         r_valid = valid;
         r_odd = 0;
@@ -377,7 +388,9 @@ __global__ void __launch_bounds__(256 * G, G == 1 ? 2 : 4) dense_rows_kernel(con
 #pragma unroll
     for (int c = 0; c < 4; ++c) off[c] = (unsigned)sizeof(E) * ((unsigned)rb * (unsigned)C + (unsigned)min(col + c, C - 1));
     if (aligned) off[0] = (unsigned)sizeof(E) * ((unsigned)rb * (unsigned)C + (unsigned)min(col, C - 4));
-    const char *src = reinterpret_cast<const char *>(static_cast<const E *>(is_x ? a.x : a.dy) + (size_t)ex * a.tokens * C);
+    const void *const operand = is_x ? a.x : a.dy;
+    const int tab = is_x ? a.x_tab : a.dy_tab;
+    const char *src = reinterpret_cast<const char *>(WEIGHTED ? static_cast<const E *>(operand) : example_at_uniform<E>(operand, tab, ex, (size_t)a.tokens * C));
     float *dst = lds + (is_x ? DRK * DR_PITCH : 0) + rb * DR_PITCH + cb * 4;
     const int tokens = a.tokens;
     const long long rows = WEIGHTED ? (long long)a.n * tokens : tokens;
@@ -390,6 +403,10 @@ __global__ void __launch_bounds__(256 * G, G == 1 ? 2 : 4) dense_rows_kernel(con
         for (int u = 0; u < 4; ++u) {
             const long long over = max(0ll, f_row + 8 * u + rb - (rows - 1));
             const char *p = src + ((f_row + 8 * u) * C - over * C) * (long long)sizeof(E);
+            if (WEIGHTED && tab) {                                             // the row's example has an address of its own
+                const long long row = f_row + 8 * u + rb - over, i = row / tokens;
+                p = reinterpret_cast<const char *>(example_at<E>(operand, tab, (int)i, 0)) + ((row - i * tokens) * C - (long long)rb * C) * (long long)sizeof(E);
+            }
             if (aligned) {
                 if constexpr (BF16) {
                     const uint2 w = *reinterpret_cast<const uint2 *>(p + off[0]);
@@ -491,7 +508,7 @@ dp_status launch_dense(const Geo &g, int mode, const void *x, const void *dy, fl
                        hipStream_t s)
 {
     DenseArgs a;
-    a.x = x; a.dy = dy; a.out_w = out_w; a.out_b = out_b;
+    a.x = x; a.dy = dy; a.x_tab = g.x_tab; a.dy_tab = g.dy_tab; a.out_w = out_w; a.out_b = out_b;
     a.out_stride_w = out_stride ? out_stride : g.pw;
     a.out_stride_b = out_stride ? out_stride : g.pb;
     a.partials = static_cast<float *>(ws);

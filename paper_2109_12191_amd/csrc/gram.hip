@@ -28,13 +28,14 @@ constexpr int GR_CB = 256;                         // channels staged at a time
 constexpr int GR_PT = GR_CB * 2 + 16;              // bytes per LDS row k (odd multiple of 16)
 
 struct GramArgs {
-    const uint16_t *a, *b;                         // dY [n][ca][S], X [n][cb][S]
+    const void *a, *b;                             // dY [n][ca][S], X [n][cb][S]
+    int a_tab, b_tab;                              // Geo::dy_tab / x_tab: the operand pointers are arrays of example addresses
     float *part;                                   // [n][sa + sb][4096]: slices of the dY Gram, then of the X Gram
     float *out;                                    // [n][GR_PARTS] partial squared norms
     int n, ca, cb, S;
     int sa, sb;                                    // channel slices (of at most `slice` channels) of dY and of X
     int slice;                                     // channels a workgroup takes: a multiple of 256
-    int total_a, total_b;                          // elements in each tensor
+    int ex_a, ex_b;                                // elements per example of each tensor
     // 3x3 pad-1 convolutions: the rows of the second operand are im2col rows (ci, kh, kw) gathered from the
     // image X [n][cin][h][w]; cb = cin * 9 then.  taps == 1: X is the operand itself.
     int taps, cin, h, w, ow, stride;
@@ -105,7 +106,7 @@ __device__ __forceinline__ void gram_part_im2col(f32x16 &acc, const GramArgs &a,
         const bool live = j < c1;
         const int ci = j / 9, tap = j - ci * 9;
         const int dh = tap / 3 - 1, dw = tap - (tap / 3) * 3 - 1;
-        const uint16_t *img = a.b + ((size_t)i * a.cin + (live ? ci : 0)) * a.h * a.w;
+        const uint16_t *img = example_at_uniform<uint16_t>(a.b, a.b_tab, i, a.ex_b) + (size_t)(live ? ci : 0) * a.h * a.w;
         uint16_t vals[64];
         int oh = 0, owc = 0;
 #pragma unroll
@@ -143,11 +144,21 @@ __global__ void __launch_bounds__(GR_THREADS) gram_partial_kernel(const Grouped<
 #pragma unroll
     for (int r = 0; r < 16; ++r) gm[r] = 0.0f;
     // one slice of one operand per workgroup: one to four blocks of 256 channels (one memory round trip each)
-    if (s < a.sa)
-        gram_part(gm, a.a, i * a.ca * a.S, a.total_a, s * a.slice, min(a.ca, (s + 1) * a.slice), a.S, lds, kb, kb2, lane);
-    else if (a.taps == 1)
-        gram_part(gm, a.b, i * a.cb * a.S, a.total_b, (s - a.sa) * a.slice, min(a.cb, (s - a.sa + 1) * a.slice), a.S, lds, kb, kb2,
-                  lane);
+    // (an example's offset in its tensor and the tensor's end; an example with an address of its own is a tensor, counted from
+    // the dword it starts in)
+    auto part = [&](const void *p, int tab, int ex, int slice, int channels) {
+        const uint16_t *tensor = static_cast<const uint16_t *>(p);
+        int base = i * ex, total = a.n * ex;
+        if (tab) {
+            const uintptr_t at = reinterpret_cast<uintptr_t>(example_at_uniform<uint16_t>(p, tab, i, 0));
+            tensor = reinterpret_cast<const uint16_t *>(at & ~(uintptr_t)3);
+            base = (int)(at >> 1) & 1;
+            total = base + ex;
+        }
+        gram_part(gm, tensor, base, total, slice * a.slice, min(channels, (slice + 1) * a.slice), a.S, lds, kb, kb2, lane);
+    };
+    if (s < a.sa) part(a.a, a.a_tab, a.ex_a, s, a.ca);
+    else if (a.taps == 1) part(a.b, a.b_tab, a.ex_b, s - a.sa, a.cb);
     else
         gram_part_im2col(gm, a, i, (s - a.sa) * a.slice, min(a.cb, (s - a.sa + 1) * a.slice), lds, kb, kb2, lane);
     float *mine = a.part + (size_t)bid * 4096;
@@ -215,14 +226,13 @@ size_t gram_ws_bytes(const Geo &g)
 dp_status launch_gram_norm(const Geo &g, const void *x, const void *dy, float *sqnorm, void *ws, hipStream_t s)
 {
     GramArgs a;
-    a.a = static_cast<const uint16_t *>(dy);
-    a.b = static_cast<const uint16_t *>(x);
+    a.a = dy; a.b = x; a.a_tab = g.dy_tab; a.b_tab = g.x_tab;
     a.n = g.n; a.ca = g.cout; a.cb = gram_rows_b(g); a.S = g.oh * g.ow;
     a.slice = gram_slice(g);
     a.sa = (g.cout + a.slice - 1) / a.slice; a.sb = (a.cb + a.slice - 1) / a.slice;
     a.taps = g.kh * g.kw; a.cin = g.cin; a.h = g.h; a.w = g.w; a.ow = g.ow; a.stride = g.stride;
-    a.total_a = g.n * g.cout * a.S;
-    a.total_b = g.n * g.cin * g.h * g.w;
+    a.ex_a = g.cout * a.S;
+    a.ex_b = g.cin * g.h * g.w;
     // the partial norms [n][16] sit at the start of the workspace, the partial Grams after them
     a.out = static_cast<float *>(ws);
     a.part = reinterpret_cast<float *>(static_cast<char *>(ws) + gram_align16((size_t)g.n * GR_PARTS * sizeof(float)));

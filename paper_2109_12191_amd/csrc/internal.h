@@ -28,6 +28,10 @@ struct Geo {
     int nhwc;               // conv / GroupNorm inputs arrive channels-last; the kernels read a transposed copy
     size_t pw, pb;          // weight / bias parameter counts
     size_t x_elems, dy_elems;   // per example
+    // Where the examples of x / dy are.  0: one after the other from the given pointer.  k > 0: the pointer is a device array of
+    // example addresses and example i starts at entry i * k (the micro-steps of a step, each in tensors of its own, contracted in
+    // one launch; k > 1: the unit of a dense layer whose units are read as examples).
+    int x_tab, dy_tab;
 };
 
 // Contraction modes of the conv / dense kernels.
@@ -118,9 +122,11 @@ dp_status launch_layer_norms(const float *const *partials, const int32_t *counts
 dp_status launch_clip_factors(const float *sqnorm, float clip_c, int n, float *f, hipStream_t s);
 dp_status launch_clip_accumulate(const float *g, size_t stride, const float *sqnorm, float clip_c, int n,
                                  size_t p, float *acc, hipStream_t s);
+dp_status launch_example_addresses(const void *const *tensors, const size_t *example_bytes, int n_operands, int n_tensors,
+                                   int per_tensor, uint64_t *table, hipStream_t s);
 dp_status launch_clip_accumulate_segments(const float *g, size_t stride, const float *group_sqnorm, const size_t *seg_begin,
-                                          const int32_t *seg_group, const float *seg_clip, int n_seg, int n, size_t p,
-                                          float *acc, hipStream_t s);
+                                          const size_t *seg_acc, const int32_t *seg_group, const float *seg_clip, int n_seg, int n, int run,
+                                          size_t p, float *acc, hipStream_t s);
 dp_status launch_noise_finalize(const float *acc, float *out, size_t p, float sigma, float clip_total,
                                 uint64_t total_batch, uint64_t seed, uint64_t step, uint32_t tensor_id,
                                 hipStream_t s);
@@ -193,6 +199,23 @@ __device__ __forceinline__ float block_sum(float v, float *red)
 __device__ __forceinline__ float bf16_bits_to_float(uint16_t b)
 {
     return __uint_as_float(((uint32_t)b) << 16);
+}
+
+// Start of example i of an operand (Geo::x_tab / dy_tab) of `elems` elements per example.
+template <typename E>
+__device__ __forceinline__ const E *example_at(const void *p, int tab, int i, size_t elems)
+{
+    if (tab) return reinterpret_cast<const E *>(static_cast<const unsigned long long *>(p)[(size_t)i * tab]);
+    return static_cast<const E *>(p) + (size_t)i * elems;
+}
+
+// The same where i is the same in every lane: the address stays in scalar registers (a value read from memory would not).
+template <typename E>
+__device__ __forceinline__ const E *example_at_uniform(const void *p, int tab, int i, size_t elems)
+{
+    const unsigned long long v = reinterpret_cast<unsigned long long>(example_at<E>(p, tab, i, elems));
+    const unsigned lo = __builtin_amdgcn_readfirstlane((unsigned)v), hi = __builtin_amdgcn_readfirstlane((unsigned)(v >> 32));
+    return reinterpret_cast<const E *>(((unsigned long long)hi << 32) | lo);
 }
 
 // one element of an input tensor as fp32

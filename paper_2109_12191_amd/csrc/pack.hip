@@ -18,7 +18,8 @@ namespace dp {
 namespace {
 
 struct PackArgs {
-    const uint16_t *x, *dy;
+    const void *x, *dy;
+    int x_tab, dy_tab;              // Geo::x_tab / dy_tab: the operand pointers are arrays of example addresses
     uint16_t *xp, *dyp;
     const float *group_sqnorm;
     float clip_c;
@@ -46,15 +47,17 @@ __global__ void __launch_bounds__(256) pack_weighted_kernel(const Grouped<PackAr
             const int taps = a.kh * a.kw;
             const int ci = j / taps, t = j - ci * taps;
             const int kh = t / a.kw, kw = t - kh * a.kw;
-            const uint16_t *src = a.x + ((size_t)i * a.cin + ci) * a.h * a.w;
+            const size_t ex_elems = (size_t)a.cin * a.h * a.w;
+            const uint16_t *ex = example_at<uint16_t>(a.x, a.x_tab, i, ex_elems);
+            const uint16_t *src = ex + (size_t)ci * a.h * a.w;
             if (taps == 1 && a.stride == 1 && a.pad == 0) {
                 // 1x1 stride 1: the im2col row is the channel itself -- eight consecutive elements from whole dwords
                 // (the run may start on an odd element), element by element only where that window would leave the tensor
-                const long long e0 = ((long long)i * a.cin + ci) * a.S + k0;
+                const uintptr_t at = reinterpret_cast<uintptr_t>(src + k0), word = at & ~(uintptr_t)3;
                 const int hi = min(8, a.S - k0);
-                if ((e0 & ~1ll) + 10 <= (long long)a.n * a.cin * a.S) {
-                    const Raw<5> raw = piece_load_words(reinterpret_cast<const uint32_t *>(a.x) + (e0 >> 1));
-                    piece_finish<true, 1>(out, raw, (uint32_t)(e0 & 1), 0, hi);
+                if (word + 20 <= reinterpret_cast<uintptr_t>(ex + ex_elems * (size_t)(a.x_tab ? 1 : a.n - i))) {     // the tensor's end
+                    const Raw<5> raw = piece_load_words(reinterpret_cast<const uint32_t *>(word));
+                    piece_finish<true, 1>(out, raw, (uint32_t)(at >> 1) & 1u, 0, hi);
                 } else {
 #pragma unroll
                     for (int u = 0; u < 8; ++u) {
@@ -90,12 +93,14 @@ __global__ void __launch_bounds__(256) pack_weighted_kernel(const Grouped<PackAr
     const int i = grp * a.eg + e;
     if (i < a.n) {
         const float f = clip_factor(a.group_sqnorm[i], a.clip_c);
-        const uint16_t *src = a.dy + ((size_t)i * a.cout + co) * a.S;
-        const long long e0 = ((long long)i * a.cout + co) * a.S + k0;
+        const size_t ex_elems = (size_t)a.cout * a.S;
+        const uint16_t *ex = example_at<uint16_t>(a.dy, a.dy_tab, i, ex_elems);
+        const uint16_t *src = ex + (size_t)co * a.S;
+        const uintptr_t at = reinterpret_cast<uintptr_t>(src + k0), word = at & ~(uintptr_t)3;
         const int hi = min(8, a.S - k0);
-        if (hi > 0 && (e0 & ~1ll) + 10 <= (long long)a.n * a.cout * a.S) {
-            const Raw<5> raw = piece_load_words(reinterpret_cast<const uint32_t *>(a.dy) + (e0 >> 1));
-            piece_finish<true, 1>(out, raw, (uint32_t)(e0 & 1), 0, hi);
+        if (hi > 0 && word + 20 <= reinterpret_cast<uintptr_t>(ex + ex_elems * (size_t)(a.dy_tab ? 1 : a.n - i))) {
+            const Raw<5> raw = piece_load_words(reinterpret_cast<const uint32_t *>(word));
+            piece_finish<true, 1>(out, raw, (uint32_t)(at >> 1) & 1u, 0, hi);
             scale_regs<true, 4>(out, f);                 // f * dY in fp32, rounded to bf16 once (nearest even)
         } else {
 #pragma unroll
@@ -113,7 +118,8 @@ __global__ void __launch_bounds__(256) pack_weighted_kernel(const Grouped<PackAr
 // into a compact [n*cin][OH*OW] tensor so that the contraction runs its plain aligned loader on
 // half (a quarter, with both strides) of the bytes.  One thread per pair of output elements.
 struct SubArgs {
-    const uint16_t *x;
+    const void *x;
+    int x_tab, cin;                 // Geo::x_tab; rows (channels) of an example
     uint16_t *out;
     long long rows;
     int h, w, oh, ow, stride;
@@ -123,7 +129,6 @@ __global__ void __launch_bounds__(256) subsample_kernel(const Grouped<SubArgs> g
 {
     unsigned bid;
     const SubArgs &a = grp.a[group_pick(grp, bid)];
-    const uint16_t *__restrict__ x = a.x;
     uint16_t *__restrict__ out = a.out;
     const long long rows = a.rows;
     const int w = a.w, ow = a.ow, stride = a.stride;
@@ -132,7 +137,13 @@ __global__ void __launch_bounds__(256) subsample_kernel(const Grouped<SubArgs> g
     if (t >= rows * pairs) return;
     const long long row = t / pairs;
     const int k = (int)(t - row * pairs) * 2;
-    const uint16_t *src = x + (size_t)row * a.h * w;
+    const uint16_t *src;
+    if (a.x_tab) {
+        const int i = (int)((unsigned)row / (unsigned)a.cin);       // (rows < 2^31: the copy is at most 96 MB)
+        src = example_at<uint16_t>(a.x, a.x_tab, i, 0) + (size_t)(row - (long long)i * a.cin) * a.h * w;
+    } else {
+        src = static_cast<const uint16_t *>(a.x) + (size_t)row * a.h * w;
+    }
     const int r0 = k / ow, c0 = k - r0 * ow;
     const uint32_t lo = src[(size_t)r0 * stride * w + c0 * stride];
     uint16_t *dst = out + (size_t)row * S + k;
@@ -205,7 +216,7 @@ dp_status launch_subsample(const Geo &g, const void *x, void *out, hipStream_t s
     const long long blocks = (threads + 255) / 256;
     if (blocks > 0x7FFFFFFFll) return fail(DP_ERR_UNSUPPORTED, "subsample: layer too large");
     SubArgs a;
-    a.x = static_cast<const uint16_t *>(x); a.out = static_cast<uint16_t *>(out); a.rows = rows;
+    a.x = x; a.x_tab = g.x_tab; a.cin = g.cin; a.out = static_cast<uint16_t *>(out); a.rows = rows;
     a.h = g.h; a.w = g.w; a.oh = g.oh; a.ow = g.ow; a.stride = g.stride;
     return submit_kernel<SubArgs>(TIER_PRE, reinterpret_cast<const void *>(&subsample_kernel), a, (unsigned)blocks, 256, 0,
                                   s, "subsample");
@@ -230,8 +241,7 @@ dp_status launch_pack_weighted(const Geo &g, const PackPlan &p, const void *x, c
                                const float *group_sqnorm, float clip_c, void *xp, void *dyp, hipStream_t s)
 {
     PackArgs a;
-    a.x = static_cast<const uint16_t *>(x);
-    a.dy = static_cast<const uint16_t *>(dy);
+    a.x = x; a.dy = dy; a.x_tab = g.x_tab; a.dy_tab = g.dy_tab;
     a.xp = static_cast<uint16_t *>(xp);
     a.dyp = static_cast<uint16_t *>(dyp);
     a.group_sqnorm = group_sqnorm; a.clip_c = clip_c;

@@ -14,6 +14,7 @@ size_t gn_norm_partial_count(const Geo &g) { return (size_t)g.gn_groups; }
 // shuffles.
 struct GnArgs {
     const void *x, *dy;
+    int x_tab, dy_tab;              // Geo::x_tab / dy_tab: the operand pointers are arrays of example addresses
     float *out_w, *out_b;           // [n, stride] rows of dgamma / dbeta (may be null)
     size_t out_stride_w, out_stride_b;
     float *partials;                // [n, groups]
@@ -31,10 +32,10 @@ __global__ void __launch_bounds__(256) gn_affine_3pass_kernel(const Grouped<GnAr
     const GnArgs &a = launch.a[group_pick(launch, bid)];
     const int i = bid / a.groups, grp = bid - i * a.groups;
     const int cg = a.c / a.groups;
-    const size_t first = ((size_t)i * a.c + (size_t)grp * cg) * a.hw;
+    const size_t ex = (size_t)a.c * a.hw, first = (size_t)grp * cg * a.hw;
     const int cnt = cg * a.hw;
-    const E *xg = static_cast<const E *>(a.x) + first;
-    const E *dyg = static_cast<const E *>(a.dy) + first;
+    const E *xg = example_at_uniform<E>(a.x, a.x_tab, i, ex) + first;
+    const E *dyg = example_at_uniform<E>(a.dy, a.dy_tab, i, ex) + first;
 
     // the mean is taken about the group's first element, so that a group far from zero keeps its spread
     const float k = In<BF16>::ld(xg);
@@ -122,9 +123,9 @@ __device__ __forceinline__ void gn_affine_body(const GnArgs &a, unsigned bid, fl
     const bool live = gid < (long long)a.n * a.groups;                // the last workgroup may hold fewer groups
     const int i = live ? (int)(gid / a.groups) : 0, grp = live ? (int)(gid - (long long)i * a.groups) : 0;
     const int cg = a.c / a.groups;
-    const size_t first = ((size_t)i * a.c + (size_t)grp * cg) * a.hw;
-    const E *xg = static_cast<const E *>(a.x) + first;
-    const E *dyg = static_cast<const E *>(a.dy) + first;
+    const size_t ex = (size_t)a.c * a.hw, first = (size_t)grp * cg * a.hw;
+    const E *xg = example_at_uniform<E>(a.x, a.x_tab, i, ex) + first;
+    const E *dyg = example_at_uniform<E>(a.dy, a.dy_tab, i, ex) + first;
     const float k = In<BF16>::ld(xg);
     s_dx += sub * cg;
     s_d += sub * cg;
@@ -242,7 +243,7 @@ dp_status launch_gn(const Geo &g, int mode, const void *x, const void *dy, float
                     hipStream_t s)
 {
     GnArgs a;
-    a.x = x; a.dy = dy;
+    a.x = x; a.dy = dy; a.x_tab = g.x_tab; a.dy_tab = g.dy_tab;
     a.partials = static_cast<float *>(ws);
     a.n = g.n; a.c = g.cin; a.hw = g.h * g.w; a.groups = g.gn_groups; a.eps = g.gn_eps;
     const bool weighted = mode == MODE_WEIGHTED;

@@ -30,8 +30,9 @@ constexpr int ST_PT = 8;                       // 16-byte pieces a thread moves 
 constexpr int ST_LINES = 9;                    // image rows per channel and step: two output rows, seven taps
 
 struct StemArgs {
-    const uint16_t *x;              // [n][cin][H][W]
-    const uint16_t *dy;             // [n][64][OH][OW]
+    const void *x;                  // [n][cin][H][W]
+    const void *dy;                 // [n][64][OH][OW]
+    int x_tab, dy_tab;              // Geo::x_tab / dy_tab: the operand pointers are arrays of example addresses
     float *part;                    // [n][slices][64][160] partial blocks
     float *out_w;                   // [n] rows of out_stride floats, or null
     size_t out_stride;
@@ -85,8 +86,8 @@ __global__ void __launch_bounds__(ST_THREADS) conv_stem_kernel(const Grouped<Ste
             meta[u] = (2 * ST_COUT * PA + line * XL + (4 * pc + 2) * 2) | ((3 + k) << 20);
         }
     }
-    const uint16_t *dy_ex = a.dy + (size_t)i * ST_COUT * a.oh * OW;
-    const uint16_t *x_ex = a.x + (size_t)i * a.cin * H * W;
+    const uint16_t *dy_ex = example_at_uniform<uint16_t>(a.dy, a.dy_tab, i, (size_t)ST_COUT * a.oh * OW);
+    const uint16_t *x_ex = example_at_uniform<uint16_t>(a.x, a.x_tab, i, (size_t)a.cin * H * W);
 
     // this lane's column of the gradient and where its runs start in a staged image row
     const int j = min(wave * 32 + (lane & 31), a.J - 1);  // columns beyond J compute a copy of the last one (never stored)
@@ -266,8 +267,7 @@ dp_status launch_stem(const Geo &g, const void *x, const void *dy, float *out_w,
     a.partials = reinterpret_cast<float *>(w);
     w += st_align16((size_t)g.n * ST_FIX_BLOCKS * sizeof(float));
     a.part = reinterpret_cast<float *>(w);
-    a.x = static_cast<const uint16_t *>(x);
-    a.dy = static_cast<const uint16_t *>(dy);
+    a.x = x; a.dy = dy; a.x_tab = g.x_tab; a.dy_tab = g.dy_tab;
     a.out_w = out_w;
     a.out_stride = out_stride ? out_stride : g.pw;
     a.n = g.n; a.cin = g.cin; a.h = g.h; a.w = g.w; a.oh = g.oh; a.ow = g.ow; a.J = g.cin * 49;

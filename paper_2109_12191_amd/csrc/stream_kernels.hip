@@ -53,9 +53,10 @@ dp_status launch_norms(const float *layer_sqnorm, const int32_t *group_of_layer,
 }
 
 // Group norms straight from the per-layer partial sums the contraction kernels leave in their
-// workspaces (so that no per-layer reduction launch is needed): one wavefront per (group, example)
-// walks the layers of the group in order and, inside a layer, that example's partials 64 at a
-// time; fixed order, same bits on every run.
+// workspaces (so that no per-layer reduction launch is needed): one workgroup per (group, example), whose waves take the
+// layers of the group in turn (up to sixteen waves: a global norm over dozens of layers is a few loads deep and not one
+// wave's walk); a wave adds that example's partials of a layer 64 at a time, then the waves' sums are added in order; fixed
+// order, same bits on every run.
 constexpr int NP_MAX = 64;                 // layers per launch
 struct NormPartialArgs {
     const float *ptr[NP_MAX];
@@ -65,23 +66,29 @@ struct NormPartialArgs {
     float *group_sqnorm;
 };
 
-__global__ void __launch_bounds__(256) norms_from_partials_kernel(const NormPartialArgs a)
+__global__ void __launch_bounds__(1024) norms_from_partials_kernel(const NormPartialArgs a)
 {
-    const int i = blockIdx.x * 4 + (threadIdx.x >> 6);
-    const int lane = threadIdx.x & 63;
-    const int g = blockIdx.y;
-    if (i >= a.n) return;
+    __shared__ float red[16];
+    const int i = blockIdx.x, g = blockIdx.y;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, waves = blockDim.x >> 6;
     float s = 0.0f;
-    for (int l = 0; l < a.n_layers; ++l) {
+    for (int l = 0, turn = 0; l < a.n_layers; ++l) {
         if (a.group[l] != g) continue;
-        const int cnt = a.count[l];
-        const float *p = a.ptr[l] + (size_t)i * cnt;
-        for (int c = lane; c < cnt; c += 64) s += p[c];
+        if (turn == wave) {
+            const int cnt = a.count[l];
+            const float *p = a.ptr[l] + (size_t)i * cnt;
+            for (int c = lane; c < cnt; c += 64) s += p[c];
+        }
+        if (++turn == waves) turn = 0;
     }
     s = wave_sum(s);
-    if (lane == 0) {
+    if (lane == 0) red[wave] = s;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        float t = 0.0f;
+        for (int w = 0; w < waves; ++w) t += red[w];
         float *dst = a.group_sqnorm + (size_t)g * a.n + i;
-        *dst = a.accumulate ? *dst + s : s;
+        *dst = a.accumulate ? *dst + t : t;
     }
 }
 
@@ -98,7 +105,9 @@ dp_status launch_norms_from_partials(const float *const *partials, const int32_t
             a.group[l] = live ? group_of_layer[l0 + l] : -1;
         }
         a.n = n; a.accumulate = l0 > 0; a.group_sqnorm = group_sqnorm;
-        hipLaunchKernelGGL(norms_from_partials_kernel, dim3((n + 3) / 4, n_groups), dim3(256), 0, s, a);
+        const int per_group = (a.n_layers + n_groups - 1) / n_groups;          // layers, on average
+        const int waves = per_group < 16 ? per_group : 16;
+        hipLaunchKernelGGL(norms_from_partials_kernel, dim3(n, n_groups), dim3(64 * waves), 0, s, a);
         const dp_status st = check_launch("norms_from_partials");
         if (st != DP_OK) return st;
     }
@@ -184,16 +193,32 @@ __device__ __forceinline__ float4 load_once(const float *p)
     return v;
 }
 
+// Columns [e, e + VEC) of `n` rows, clipped by the n squared norms at sqnorm, added to acc in runs of `run` rows (a run is a
+// micro-step: its sum is formed first, so the bits do not depend on how many micro-steps a call takes); `e` < `p` or
+// nothing to do (every thread of the workgroup takes part: the factors are staged together).
 template <int VEC>
-__global__ void __launch_bounds__(256) clip_accumulate_kernel(const float *__restrict__ g, size_t stride,
-                                                               const float *__restrict__ sqnorm, float clip_c,
-                                                               int n, size_t p, float *__restrict__ acc)
+__device__ __forceinline__ void clip_accumulate_body(const float *__restrict__ g, size_t stride, const float *__restrict__ sqnorm,
+                                                     float clip_c, int n, int run, size_t e, size_t p, float *__restrict__ acc, float *fs)
 {
-    __shared__ float fs[CA_FMAX];
-    const size_t e = ((size_t)blockIdx.x * 256 + threadIdx.x) * VEC;
-    float s[VEC];
+    float s[VEC], total[VEC];
 #pragma unroll
-    for (int v = 0; v < VEC; ++v) s[v] = 0.0f;
+    for (int v = 0; v < VEC; ++v) s[v] = total[v] = 0.0f;
+    if (e < p) {
+        if constexpr (VEC == 4) {
+            const float4 a = *reinterpret_cast<const float4 *>(acc + e);
+            total[0] = a.x; total[1] = a.y; total[2] = a.z; total[3] = a.w;
+        } else {
+            total[0] = acc[e];
+        }
+    }
+    int left = run;                                   // rows until the run ends (uniform)
+    auto row_done = [&]() {
+        if (--left == 0) {
+            left = run;
+#pragma unroll
+            for (int v = 0; v < VEC; ++v) { total[v] += s[v]; s[v] = 0.0f; }
+        }
+    };
 
     for (int base = 0; base < n; base += CA_FMAX) {
         const int cnt = min(CA_FMAX, n - base);
@@ -212,35 +237,43 @@ __global__ void __launch_bounds__(256) clip_accumulate_kernel(const float *__res
                     for (int u = 0; u < 8; ++u) {    // example order: same bits on every run
                         const float fu = fs[j + u];
                         s[0] += fu * v[u].x; s[1] += fu * v[u].y; s[2] += fu * v[u].z; s[3] += fu * v[u].w;
+                        row_done();
                     }
                 }
                 for (; j < cnt; ++j) {
                     const float4 a = load_once(row + (size_t)j * stride);
                     const float f0 = fs[j];
                     s[0] += f0 * a.x; s[1] += f0 * a.y; s[2] += f0 * a.z; s[3] += f0 * a.w;
+                    row_done();
                 }
             } else {
-                for (; j < cnt; ++j) s[0] += fs[j] * row[(size_t)j * stride];
+                for (; j < cnt; ++j) { s[0] += fs[j] * row[(size_t)j * stride]; row_done(); }
             }
         }
     }
     if (e >= p) return;
-    if constexpr (VEC == 4) {
-        float4 a = *reinterpret_cast<float4 *>(acc + e);
-        a.x += s[0]; a.y += s[1]; a.z += s[2]; a.w += s[3];
-        *reinterpret_cast<float4 *>(acc + e) = a;
-    } else {
-        acc[e] += s[0];
-    }
+    if constexpr (VEC == 4) *reinterpret_cast<float4 *>(acc + e) = make_float4(total[0], total[1], total[2], total[3]);
+    else acc[e] = total[0];
+}
+
+template <int VEC>
+__global__ void __launch_bounds__(256) clip_accumulate_kernel(const float *__restrict__ g, size_t stride,
+                                                               const float *__restrict__ sqnorm, float clip_c,
+                                                               int n, size_t p, float *__restrict__ acc)
+{
+    __shared__ float fs[CA_FMAX];
+    clip_accumulate_body<VEC>(g, stride, sqnorm, clip_c, n, n, ((size_t)blockIdx.x * 256 + threadIdx.x) * VEC, p, acc, fs);
 }
 
 // The same sum for several clipping groups in one launch: the columns [0, p) of the gradient matrix are cut
-// into segments (one per tensor or per group), each with its own bound and its own row of squared norms.
-// A thread finds the segment of its four columns by bisection of the (at most SEG_MAX + 1) boundaries it
-// gets as kernel arguments; boundaries are multiples of 4, so a thread never straddles two segments.
+// into segments (one per tensor or per group), each with its own bound, its own row of squared norms and its own place in
+// the accumulator.  A workgroup's 1024 columns lie in one segment, found by bisection of the workgroup numbers it gets as
+// kernel arguments, so the clip factors are evaluated once per workgroup and not once per thread and example.
 constexpr int SEG_MAX = 64;
 struct SegArgs {
     unsigned long long begin[SEG_MAX + 1];         // column where each segment starts; begin[n_seg] = p
+    unsigned long long acc_begin[SEG_MAX];         // and where it lies in the accumulator
+    unsigned first_block[SEG_MAX];
     float clip[SEG_MAX];
     int group[SEG_MAX];
     int n_seg;
@@ -248,49 +281,39 @@ struct SegArgs {
 
 __global__ void __launch_bounds__(256) clip_accumulate_segments_kernel(const float *__restrict__ g, size_t stride,
                                                                        const float *__restrict__ group_sqnorm,
-                                                                       const SegArgs sa, int n, size_t p,
-                                                                       float *__restrict__ acc)
+                                                                       const SegArgs sa, int n, int run, float *__restrict__ acc)
 {
-    const size_t e = ((size_t)blockIdx.x * 256 + threadIdx.x) * 4;
-    if (e >= p) return;
-    int lo = 0, hi = sa.n_seg - 1;                 // last segment with begin <= e
+    __shared__ float fs[CA_FMAX];
+    int lo = 0, hi = sa.n_seg - 1;                 // last segment whose first workgroup is not beyond this one
     while (lo < hi) {
         const int mid = (lo + hi + 1) >> 1;
-        if (sa.begin[mid] <= e) lo = mid; else hi = mid - 1;
+        if (sa.first_block[mid] <= blockIdx.x) lo = mid; else hi = mid - 1;
     }
-    const float *sq = group_sqnorm + (size_t)sa.group[lo] * n;
-    const float c = sa.clip[lo];
-    float s0 = 0.0f, s1 = 0.0f, s2 = 0.0f, s3 = 0.0f;
-    const float *row = g + e;
-#pragma unroll 8
-    for (int i = 0; i < n; ++i) {                  // example order: same bits on every run
-        const float f = clip_factor(sq[i], c);
-        const float4 v = load_once(row + (size_t)i * stride);
-        s0 += f * v.x; s1 += f * v.y; s2 += f * v.z; s3 += f * v.w;
-    }
-    float4 a = *reinterpret_cast<float4 *>(acc + e);
-    a.x += s0; a.y += s1; a.z += s2; a.w += s3;
-    *reinterpret_cast<float4 *>(acc + e) = a;
+    const size_t e = ((size_t)(blockIdx.x - sa.first_block[lo]) * 256 + threadIdx.x) * 4;
+    clip_accumulate_body<4>(g + sa.begin[lo], stride, group_sqnorm + (size_t)sa.group[lo] * n, sa.clip[lo], n, run, e,
+                            sa.begin[lo + 1] - sa.begin[lo], acc + sa.acc_begin[lo], fs);
 }
 
 dp_status launch_clip_accumulate_segments(const float *g, size_t stride, const float *group_sqnorm, const size_t *seg_begin,
-                                          const int32_t *seg_group, const float *seg_clip, int n_seg, int n, size_t p,
-                                          float *acc, hipStream_t s)
+                                          const size_t *seg_acc, const int32_t *seg_group, const float *seg_clip, int n_seg,
+                                          int n, int run, size_t p, float *acc, hipStream_t s)
 {
     for (int s0 = 0; s0 < n_seg; s0 += SEG_MAX) {
         SegArgs sa;
         sa.n_seg = n_seg - s0 < SEG_MAX ? n_seg - s0 : SEG_MAX;
-        const size_t first = seg_begin[s0], last = (s0 + sa.n_seg == n_seg) ? p : seg_begin[s0 + sa.n_seg];
+        size_t blocks = 0;
         for (int k = 0; k < SEG_MAX; ++k) {
             const bool live = k < sa.n_seg;
-            sa.begin[k] = live ? seg_begin[s0 + k] - first : last - first;
+            const size_t end = s0 + k + 1 < n_seg ? seg_begin[s0 + k + 1] : p;
+            sa.begin[k] = live ? seg_begin[s0 + k] : p;
+            sa.acc_begin[k] = live ? seg_acc[s0 + k] : 0;
+            sa.first_block[k] = (unsigned)blocks;
             sa.clip[k] = live ? seg_clip[s0 + k] : 1.0f;
             sa.group[k] = live ? seg_group[s0 + k] : 0;
+            if (live) blocks += (end - seg_begin[s0 + k] + 1023) / 1024;
         }
-        sa.begin[SEG_MAX] = last - first;
-        const size_t span = last - first;
-        hipLaunchKernelGGL(clip_accumulate_segments_kernel, dim3((unsigned)((span / 4 + 255) / 256)), dim3(256), 0, s,
-                           g + first, stride, group_sqnorm, sa, n, span, acc + first);
+        sa.begin[sa.n_seg] = s0 + sa.n_seg < n_seg ? seg_begin[s0 + sa.n_seg] : p;
+        hipLaunchKernelGGL(clip_accumulate_segments_kernel, dim3((unsigned)blocks), dim3(256), 0, s, g, stride, group_sqnorm, sa, n, run, acc);
         const dp_status st = check_launch("clip_accumulate_segments");
         if (st != DP_OK) return st;
     }
@@ -310,6 +333,50 @@ dp_status launch_clip_accumulate(const float *g, size_t stride, const float *sqn
         hipLaunchKernelGGL(clip_accumulate_kernel<1>, dim3(blocks), dim3(256), 0, s, g, stride, sqnorm, clip_c, n, p,
                            acc);
     return check_launch("clip_accumulate");
+}
+
+// ------------------------------------------------------------------------------------------
+// Addresses of the examples of several tensors: table[o][t * per_tensor + j] = tensors[o][t] + j * example_bytes[o].
+constexpr int ADDR_MAX = 224;                  // tensors per launch (kernel arguments are limited to 4 KB)
+struct AddrArgs {
+    unsigned long long tensor[ADDR_MAX], bytes[ADDR_MAX];
+    int count, per_tensor;
+    unsigned long long *table;                 // of the first tensor of the launch
+};
+
+__global__ void __launch_bounds__(256) example_addresses_kernel(const AddrArgs a)
+{
+    const int t = blockIdx.x;
+    for (int j = threadIdx.x; j < a.per_tensor; j += 256)
+        a.table[(size_t)t * a.per_tensor + j] = a.tensor[t] + (unsigned long long)j * a.bytes[t];
+}
+
+// one example per tensor: a thread per tensor
+__global__ void __launch_bounds__(256) tensor_addresses_kernel(const AddrArgs a)
+{
+    if ((int)threadIdx.x < a.count) a.table[threadIdx.x] = a.tensor[threadIdx.x];
+}
+
+dp_status launch_example_addresses(const void *const *tensors, const size_t *example_bytes, int n_operands, int n_tensors,
+                                   int per_tensor, uint64_t *table, hipStream_t s)
+{
+    const size_t all = (size_t)n_operands * n_tensors;
+    for (size_t k0 = 0; k0 < all; k0 += ADDR_MAX) {
+        AddrArgs a;
+        a.count = (int)(all - k0 < (size_t)ADDR_MAX ? all - k0 : (size_t)ADDR_MAX);
+        a.per_tensor = per_tensor;
+        a.table = reinterpret_cast<unsigned long long *>(table) + k0 * per_tensor;
+        for (int k = 0; k < ADDR_MAX; ++k) {
+            const bool live = k < a.count;
+            a.tensor[k] = live ? reinterpret_cast<unsigned long long>(tensors[k0 + k]) : 0;
+            a.bytes[k] = live ? example_bytes[(k0 + k) / n_tensors] : 0;
+        }
+        if (per_tensor == 1) hipLaunchKernelGGL(tensor_addresses_kernel, dim3(1), dim3(256), 0, s, a);
+        else hipLaunchKernelGGL(example_addresses_kernel, dim3((unsigned)a.count), dim3(256), 0, s, a);
+        const dp_status st = check_launch("example_addresses");
+        if (st != DP_OK) return st;
+    }
+    return DP_OK;
 }
 
 // ------------------------------------------------------------------------------------------

@@ -2,9 +2,14 @@
 
 This class owns device buffers (allocated through torch) and issues the library calls in
 order; it performs no arithmetic of its own.  Per micro-step:
-    dp_per_example_grad_batch (one call per group of layers that run the same kernel)  ->  dp_norms  ->
-    dp_clip_accumulate (materialised layers) and dp_clip_accumulate_recompute_batch (the rest);
-once per optimiser step: dp_add_noise_finalize per parameter tensor.
+    dp_per_example_grad_batch (one call per group of layers that run the same kernel)  ->  dp_norms_from_partials  ->
+    dp_clip_accumulate_columns (materialised layers) and dp_clip_accumulate_recompute_batch (the rest);
+once per optimiser step: dp_add_noise_finalize_flat over all parameter tensors.
+
+`run` and `capture` see the micro-steps of a whole step at once and issue several of them together where they are small:
+every example is still clipped by its own norms, but the launches hold the examples of all of them (the "_at" calls, whose
+operands are arrays of example addresses), the clipped sum reads and writes the accumulator once, and a step of 64
+one-example micro-steps is two dozen launches instead of a thousand.
 
 Each layer uses one of the two forms of the clipped sum.  "materialise" keeps the layer's
 per-example gradients of the micro-step in a [n, P] matrix (written by the contraction's
@@ -15,14 +20,178 @@ late ones (many parameters, tiny feature maps) recompute.
 """
 from __future__ import annotations
 
+import ctypes
 from typing import List, Optional, Sequence
 
 import torch
 
 from . import binding as B
 
+# Micro-steps are issued together as long as a phase reads no more than this many bytes of inputs: long launches gain nothing from
+# growing further, and addresses cost the 3x3 kernels a little.  MI355X, us per step with 1 / 2 / 4 / 8 micro-steps per phase:
+# ResNet-18-GN 8 x 32 examples (0.17 GB each) 2111 / 1940 / 1749 / 1662; ResNet-50 8 x 32 (1.39 GB each) 7597 / 7762 / 8308;
+# ResNet-50-GN at 200 x 200, 3 x 12 (0.85 GB each) 2791 / 2651, three 2557; ResNet-50 64 x 1 (0.04 GB each) in phases of
+# 16 / 32 / 64: 2606 / 2202 / 2174 against 11400 one by one.
+PHASE_BYTES = 2.6e9
+PHASE_EXAMPLES = 256           # and examples
+
+
 def _pad4(v: int) -> int:
     return (v + 3) & ~3
+
+
+class _Plan:
+    """Buffers and batch calls for phases of `n` examples: one micro-step in the caller's tensors (`tensors` = 1), or `tensors`
+    micro-steps through arrays of example addresses."""
+
+    def __init__(self, ps: "PrivatiseStep", tensors: int):
+        wl, dev = ps.wl, ps.device
+        self.ps = ps
+        self.tensors = tensors
+        self.n = wl.n * tensors
+        self.rows = self.n // ps.clip_unit
+        self.layers = ps.layers
+        L = len(self.layers)
+        self.descs = [B.make_desc(l, self.n, wl.dtype) for l in self.layers]
+        self.form = [ps._choose(l, ps._mode, self.n) for l in self.layers]
+        # columns of the per-example gradient matrix: the materialised layers in the order they lie in the parameter vector
+        self.col_w, self.col_b = [0] * L, [0] * L
+        segments = []                              # runs of columns of one clipping group that also lie together in acc
+        pos = 0
+        for i in sorted(range(L), key=lambda i: ps.off_w[i]):
+            if self.form[i] != "materialise":
+                continue
+            grp = ps.group_of_layer[i]
+            if not segments or segments[-1][2] != grp or ps.off_w[i] - pos != segments[-1][1] - segments[-1][0]:
+                segments.append((pos, ps.off_w[i], grp))
+            self.col_w[i] = pos
+            pos += _pad4(ps.pw[i])
+            self.col_b[i] = pos
+            pos += _pad4(ps.pb[i])
+        self.p_mat = pos
+        self.segments = B.SegmentTable([s[0] for s in segments], [s[2] for s in segments], [ps.group_clip[s[2]] for s in segments],
+                                       [s[1] for s in segments]) if segments else None
+        f32 = torch.float32
+        copies = ps.copies
+        self.g = [torch.empty((self.rows, self.p_mat), dtype=f32, device=dev) if self.p_mat else None for _ in range(copies)]
+        for i in range(L):                         # the columns between tensors are read by the clipped sum, never written
+            if self.form[i] == "materialise":
+                for col, size in ((self.col_w[i], ps.pw[i]), (self.col_b[i], ps.pb[i])):
+                    if size % 4:
+                        for g in self.g:
+                            g[:, col + size: col + _pad4(size)] = 0.0
+        self.group_sqnorm = [torch.zeros((ps.n_groups, self.rows), dtype=f32, device=dev) for _ in range(copies)]
+        need = [max(16, B.dp_workspace_bytes(d, B.DP_WS_PER_EXAMPLE_GRAD),
+                    B.dp_workspace_bytes(d, B.DP_WS_RECOMPUTE) if form == "recompute" else 0,
+                    B.dp_unit_workspace_bytes(d, ps.clip_unit) if ps.clip_unit > 1 else 0)
+                for d, form in zip(self.descs, self.form)]
+        # a workspace per layer (the layers of a phase are in flight together), all in one allocation per copy
+        starts, total = [], 0
+        for b in need:
+            starts.append(total)
+            total += (b + 255) & ~255
+        self.ws_bytes = need
+        self._ws_store = [torch.empty(total, dtype=torch.uint8, device=dev) for _ in range(copies)]
+        self.ws = [[store.data_ptr() + at for at in starts] for store in self._ws_store]
+        self.layer_sqnorm = [torch.zeros((L, self.rows), dtype=f32, device=dev) for _ in range(copies)] if ps.clip_unit > 1 else None
+        # Layers that run the same kernel variant go to the library in ONE batch call, which puts them into one
+        # launch (at most 16 per launch): per phase a micro-step is a dozen launches, not a hundred.
+        self.variant = [(B.dp_kernel_variant(d, B.DP_WS_PER_EXAMPLE_GRAD | B.DP_VARIANT_SHARED |
+                                             (B.DP_VARIANT_MATERIALISE if form == "materialise" else 0)),
+                         B.dp_kernel_variant(d, B.DP_WS_RECOMPUTE | B.DP_VARIANT_SHARED) if form == "recompute" or ps.clip_unit > 1 else "")
+                        for d, form in zip(self.descs, self.form)]
+        self.partials = [B.PartialTable(self.ws[c], [1] * L, ps.group_of_layer)
+                         for c in range(copies)]
+        esize = 2 if wl.dtype == "bf16" else 4
+        # algorithmic work of one call per layer: (flop, HBM bytes of the per-example call, HBM bytes of the
+        # recomputing clipped-sum call).  Bytes = the operands read once, plus the per-example gradients
+        # written when the layer materialises them, or the accumulator read and written by form (b).
+        self.work = [(l.flops * self.n,
+                      l.in_bytes(esize) * self.n + (4 * self.n * (pw + pb) if form == "materialise" else 0),
+                      l.in_bytes(esize) * self.n + 8 * (pw + pb))
+                     for l, pw, pb, form in zip(self.layers, ps.pw, ps.pb, self.form)]
+        self.groups_a = self._make_groups(range(L), 0) if ps.clip_unit == 1 else []
+        self.groups_b = self._make_groups([i for i in range(L) if self.form[i] == "recompute"], 1)
+        self.groups_u = self._make_groups(range(L), 2) if ps.clip_unit > 1 else []
+        self.b_done = [None] * copies            # per copy: events after which its buffers are free again
+
+    def _make_groups(self, layer_ids, use: int):
+        """Groups of at most 16 layers with the same kernel variant for phase `use` (0: per-example gradients,
+        1: recomputing clipped sum, 2: unit sums), largest total work first.  Each group: dict(layers, name, batch per copy,
+        constant pointer arrays)."""
+        ps = self.ps
+        by_name = {}
+        family = "conv3x3_rows<bf16,all widths,%s>" % ("weighted" if use else "per_example")
+        for li in layer_ids:
+            key = self.variant[li][1 if use == 2 else use]      # same name, same kernel: storing and norm-only layers share a launch
+            if ps.batching == "all":
+                key = "all layers"
+            elif key.startswith("conv3x3_rows<"):
+                # inside a batch call the library runs all variants of the raw-row 3x3 kernel in one launch (only
+                # four kernels run at a time on the chip: the few workgroups of a narrow layer cost none of the
+                # four inside a wide launch), so the family is one batch call
+                key = family
+            by_name.setdefault(key, []).append(li)
+        groups = []
+        for key, ids in by_name.items():
+            width = len(ids) if (ps.batching == "all" or key == family) else 16
+            for k in range(0, len(ids), width):
+                part = ids[k: k + width]
+                name = key.split("|")[0]
+                if len(part) == 1:           # a single layer is planned as a launch of its own
+                    name = B.dp_kernel_variant(self.descs[part[0]], B.DP_WS_RECOMPUTE if use else (
+                        B.DP_WS_PER_EXAMPLE_GRAD | (B.DP_VARIANT_MATERIALISE if self.form[part[0]] == "materialise" else 0)))
+                g = dict(layers=part, name=name, conv=all(self.layers[i].kind == "conv" for i in part))
+                g["batch"] = [B.LayerBatch([self.descs[i] for i in part], [self.ws[c][i] for i in part],
+                                           [self.ws_bytes[i] for i in part]) for c in range(ps.copies)]
+                if use == 2:
+                    g["usq"] = [g["batch"][c].ptrs([self.layer_sqnorm[c][i].data_ptr() for i in part])
+                                for c in range(ps.copies)]
+                if use != 1:
+                    g["counted"] = False
+                    mat = [self.form[i] == "materialise" for i in part]
+                    g0 = [g.data_ptr() if g is not None else 0 for g in self.g]
+                    g["gw"] = [g["batch"][c].ptrs([g0[c] + 4 * self.col_w[i] if m else None
+                                                   for i, m in zip(part, mat)]) if any(mat) else None for c in range(ps.copies)]
+                    g["gb"] = [g["batch"][c].ptrs([g0[c] + 4 * self.col_b[i] if (m and ps.pb[i]) else None
+                                                   for i, m in zip(part, mat)]) if any(mat) else None for c in range(ps.copies)]
+                else:
+                    acc0 = ps.acc.data_ptr()
+                    g["sq"] = [g["batch"][c].ptrs([self.group_sqnorm[c][ps.group_of_layer[i]].data_ptr() for i in part])
+                               for c in range(ps.copies)]
+                    g["clip"] = g["batch"][0].floats([ps.group_clip[ps.group_of_layer[i]] for i in part])
+                    g["acc_w"] = g["batch"][0].ptrs([acc0 + 4 * ps.off_w[i] for i in part])
+                    g["acc_b"] = g["batch"][0].ptrs([acc0 + 4 * ps.off_b[i] if ps.pb[i] else None
+                                                     for i in part])
+                g["flops"] = sum(self.layers[i].flops for i in part) * self.n
+                g["bytes"] = sum(self.work[i][2 if use == 1 else 1] for i in part)
+                g["seconds"] = self._estimate(g)
+                groups.append(g)
+        groups.sort(key=lambda g: -g["seconds"])
+        # side stream of each group: longest first onto the least loaded stream
+        load = [0.0] * max(1, ps.n_streams)
+        for gi, g in enumerate(groups):
+            k = load.index(min(load)) if ps.lanes != "round_robin" else gi % max(1, ps.n_streams)
+            g["lane"] = k
+            load[k] += g["seconds"]
+        return groups
+
+    def _estimate(self, g) -> float:
+        """Duration of a group's launch for the lane balance: its work at the rates its kernel family sustains on
+        MI355X when it has the chip to itself (measured call by call on ResNet-50 at n = 32), plus a few
+        microseconds per launch however small it is."""
+        if self.ps.lanes == "flops" or self.n <= 2:
+            # micro-steps of one or two examples: launches are bound by the walk along K of a few workgroups, not by
+            # the chip's rates; flops alone order them better (measured: 5.6 k against 5.1 k examples/s)
+            return g["flops"] / 150.0e12 + 8.0e-6
+        name = g["name"]
+        if name.startswith("conv3x3_rows"):
+            rate = 300.0e12                      # (100 .. 300: the same step time; the family is one launch per phase)
+        elif "gather" in name:
+            rate = 130.0e12
+        else:
+            rate = 400.0e12
+        return max(g["flops"] / rate, g["bytes"] / 4.5e12) + 8.0e-6
 
 
 class PrivatiseStep:
@@ -42,10 +211,10 @@ class PrivatiseStep:
         # "micro_step": the side streams of the per-example phase start every micro-step behind everything issued so
         # far; "step": only the first micro-step of a step does -- later ones follow their own stream's previous
         # micro-step (and the clipped sum that last read their buffer copy), so they overlap the norm launches and the
-        # clipped sum of the micro-step before.  Worth it when the launches are short (one or two examples each).
+        # clipped sum of the micro-step before.  Worth it when the launches are short (phases of one or two examples).
         if fork not in (None, "micro_step", "step"):
             raise ValueError(fork)
-        self.fork = fork if fork is not None else ("step" if wl.n <= 2 else "micro_step")
+        self.fork = fork
         if noise not in ("once", "per_example"):
             raise ValueError(noise)
         # "once": N(0, sigma^2 C^2) added in finalize (first equation of the Algorithm section);
@@ -62,88 +231,56 @@ class PrivatiseStep:
             raise ValueError("the micro-step size must be a multiple of clip_unit")
         if self.clip_unit > 1 and noise != "once":
             raise ValueError("per-example noise is defined for units of one example")
-        self.rows = wl.n // self.clip_unit
         L = len(self.layers)
-        self.descs = [B.make_desc(l, wl.n, wl.dtype) for l in self.layers]
-        self.pw = [B.dp_weight_count(d) for d in self.descs]
-        self.pb = [B.dp_bias_count(d) for d in self.descs]
+        descs = [B.make_desc(l, wl.n, wl.dtype) for l in self.layers]
+        self.pw = [B.dp_weight_count(d) for d in descs]
+        self.pb = [B.dp_bias_count(d) for d in descs]
         self.group_of_layer = list(wl.group_of_layer)
         self.group_clip, self.clip_total = B.dp_group_clip_bounds(wl.clip_c, wl.n_groups)
         if self.clip_unit > 1:
             self.group_clip = [c * self.clip_unit for c in self.group_clip]
             self.clip_total *= self.clip_unit
             mode = "materialise"                   # the unit sums are 1/unit of the per-example matrix: keep them
+        self._mode = mode
         self.n_groups = wl.n_groups
-        self.form = [self._choose(l, mode) for l in self.layers]
 
-        # flat parameter vector: materialised layers first (their columns double as the
-        # layout of the per-example gradient matrix), then the recomputed ones
-        order = [i for i in range(L) if self.form[i] == "materialise"] + \
-                [i for i in range(L) if self.form[i] == "recompute"]
+        # flat parameter vector: the layers that materialise in a micro-step of its own first, then the recomputed ones
+        # (a fixed layout: phases of several micro-steps may use other forms)
+        form = [self._choose(l, mode, wl.n) for l in self.layers]
+        order = [i for i in range(L) if form[i] == "materialise"] + [i for i in range(L) if form[i] == "recompute"]
         self.off_w = [0] * L
         self.off_b = [0] * L
         pos = 0
-        self.p_mat = 0
         for i in order:
             self.off_w[i] = pos
             pos += _pad4(self.pw[i])
             self.off_b[i] = pos
             pos += _pad4(self.pb[i])
-            if self.form[i] == "materialise":
-                self.p_mat = pos
         self.p_total = max(pos, 4)
         # every tensor of the flat vector with its Philox tensor id (2*layer weight, 2*layer+1 bias), in
         # the order they lie in memory: the table of the one-launch finalize
         tensors = sorted([(self.off_w[i], self.pw[i], 2 * i) for i in range(L)] +
                          [(self.off_b[i], self.pb[i], 2 * i + 1) for i in range(L) if self.pb[i]])
         self._tensors = B.TensorTable([t[0] for t in tensors], [t[1] for t in tensors], [t[2] for t in tensors])
-        mat = [i for i in order if self.form[i] == "materialise"]
-        self._segments = B.SegmentTable([self.off_w[i] for i in mat], [self.group_of_layer[i] for i in mat],
-                                        [self.group_clip[self.group_of_layer[i]] for i in mat]) if mat else None
         dev = self.device
         f32 = torch.float32
         self.acc = torch.zeros(self.p_total, dtype=f32, device=dev)
         self.out = torch.zeros(self.p_total, dtype=f32, device=dev)
-        # Workspaces and per-micro-step buffers.  With one stream all calls run in order and share
-        # one workspace.  With side streams the layers of a phase run concurrently (a workspace per
-        # layer) and the two phases of consecutive micro-steps overlap: everything a micro-step
-        # writes before its clipped sum is done -- the gradient matrix, the norms, the workspaces --
-        # exists twice and micro-steps alternate between the copies.
+        # Workspaces and per-micro-step buffers (_Plan).  With one stream all calls run in order and share
+        # one copy.  With side streams the layers of a phase run concurrently and the two phases of consecutive
+        # micro-steps overlap: everything a micro-step writes before its clipped sum is done -- the gradient matrix, the
+        # norms, the workspaces -- exists twice and micro-steps alternate between the copies.
         self.n_streams = max(1, int(streams))
         self.copies = 2 if self.n_streams > 1 else 1
-        self._g = [torch.zeros((self.rows, self.p_mat), dtype=f32, device=dev) if self.p_mat else None
-                   for _ in range(self.copies)]
-        self._group_sqnorm = [torch.zeros((self.n_groups, self.rows), dtype=f32, device=dev) for _ in range(self.copies)]
         self.group_of_layer_dev = torch.tensor(self.group_of_layer, dtype=torch.int32, device=dev)
-        need = [max(16, B.dp_workspace_bytes(d, B.DP_WS_PER_EXAMPLE_GRAD),
-                    B.dp_workspace_bytes(d, B.DP_WS_RECOMPUTE) if form == "recompute" else 0,
-                    B.dp_unit_workspace_bytes(d, self.clip_unit) if self.clip_unit > 1 else 0)
-                for d, form in zip(self.descs, self.form)]
-        # a workspace per layer (the layers of a phase are in flight together)
-        self._ws = [[torch.empty(b, dtype=torch.uint8, device=dev) for b in need] for _ in range(self.copies)]
-        self._layer_sqnorm = [torch.zeros((L, self.rows), dtype=f32, device=dev) for _ in range(self.copies)]
-        # Layers that run the same kernel variant go to the library in ONE batch call, which puts them into one
-        # launch (at most 16 per launch): per phase a micro-step is a dozen launches, not a hundred.
-        self.variant = [(B.dp_kernel_variant(d, B.DP_WS_PER_EXAMPLE_GRAD | B.DP_VARIANT_SHARED |
-                                             (B.DP_VARIANT_MATERIALISE if form == "materialise" else 0)),
-                         B.dp_kernel_variant(d, B.DP_WS_RECOMPUTE | B.DP_VARIANT_SHARED))
-                        for d, form in zip(self.descs, self.form)]
-        import ctypes
-        self._partial_counts = (ctypes.c_int32 * L)()
-        self._partials = [(ctypes.c_void_p * L)(*[self._ws[c][i].data_ptr() for i in range(L)]) for c in range(self.copies)]
-        self._layer_sqnorm_ptrs = [(ctypes.c_void_p * L)(*[self._layer_sqnorm[c][i].data_ptr() for i in range(L)])
-                                   for c in range(self.copies)]
         esize = 2 if wl.dtype == "bf16" else 4
-        # algorithmic work of one call per layer: (flop, HBM bytes of the per-example call, HBM bytes of the
-        # recomputing clipped-sum call).  Bytes = the operands read once, plus the per-example gradients
-        # written when the layer materialises them, or the accumulator read and written by form (b).
-        self.work = [(l.flops * wl.n,
-                      l.in_bytes(esize) * wl.n + (4 * wl.n * (pw + pb) if form == "materialise" else 0),
-                      l.in_bytes(esize) * wl.n + 8 * (pw + pb))
-                     for l, pw, pb, form in zip(self.layers, self.pw, self.pb, self.form)]
-        self._groups_a = self._make_groups(range(L), 0)
-        self._groups_b = self._make_groups([i for i in range(L) if self.form[i] == "recompute"], 1)
-        self._groups_u = self._make_groups(range(L), 2) if self.clip_unit > 1 else []
+        self._example_bytes = [b for l in self.layers for b in (l.x_bytes(esize), l.dy_bytes(esize))]
+        per_micro_step = max(1, sum(self._example_bytes)) * wl.n
+        self._together = max(1, min(int(PHASE_BYTES // per_micro_step), PHASE_EXAMPLES // wl.n))    # micro-steps per phase, at most
+        self._plans = {}
+        for size in {1} | set(self._phase_sizes(wl.accum)):
+            self._plan(size)
+        self._main = self._plan(max(self._phase_sizes(wl.accum)))      # the plan of a whole step's phases
         # side streams: `side` for the per-example phase, `side_b` for the clipped-sum phase
         self.side = [torch.cuda.Stream(device=dev) for _ in range(self.n_streams)] if self.n_streams > 1 else []
         # (three clipped-sum streams for eight per-example streams: measured 3 % better over the whole step than four)
@@ -152,8 +289,11 @@ class PrivatiseStep:
         self.theta = None
         self.velocity = None
         self._update = None                      # (lr, momentum, keep_gradient)
-        self._b_done = [None] * self.copies      # per copy: events after which its buffers are free again
+        self._addresses = None                   # example addresses of a step that is issued call by call
         self._last = 0                           # copy used by the most recent micro-step
+        self._phases = 0                         # phases issued since begin_step
+        self._group_sqnorm = list(self._plan(1).group_sqnorm)      # of the last micro-steps (one per copy)
+        self._g_last = None
         self.graph = None
         self.micro_steps_done = 0
         # Optimiser-step counter: the `step` word of the Philox counters.  The kernels read it from a device
@@ -165,87 +305,48 @@ class PrivatiseStep:
         # library to bracket the next contraction kernel with a pair of events
         self.probe = None
 
-    def _make_groups(self, layer_ids, use: int):
-        """Groups of at most 16 layers with the same kernel variant for phase `use` (0: per-example gradients,
-        1: recomputing clipped sum), largest total work first.  Each group: dict(layers, name, batch per copy,
-        constant pointer arrays)."""
-        by_name = {}
-        family = "conv3x3_rows<bf16,all widths,%s>" % ("weighted" if use else "per_example")
-        for li in layer_ids:
-            key = self.variant[li][1 if use == 2 else use]      # same name, same kernel: storing and norm-only layers share a launch
-            if self.batching == "all":
-                key = "all layers"
-            elif key.startswith("conv3x3_rows<"):
-                # inside a batch call the library runs all variants of the raw-row 3x3 kernel in one launch (only
-                # four kernels run at a time on the chip: the few workgroups of a narrow layer cost none of the
-                # four inside a wide launch), so the family is one batch call
-                key = family
-            by_name.setdefault(key, []).append(li)
-        groups = []
-        for key, ids in by_name.items():
-            width = len(ids) if (self.batching == "all" or key == family) else 16
-            for k in range(0, len(ids), width):
-                part = ids[k: k + width]
-                name = key.split("|")[0]
-                if len(part) == 1:           # a single layer is planned as a launch of its own
-                    name = B.dp_kernel_variant(self.descs[part[0]], B.DP_WS_RECOMPUTE if use else (
-                        B.DP_WS_PER_EXAMPLE_GRAD | (B.DP_VARIANT_MATERIALISE if self.form[part[0]] == "materialise" else 0)))
-                g = dict(layers=part, name=name, conv=all(self.layers[i].kind == "conv" for i in part))
-                g["batch"] = [B.LayerBatch([self.descs[i] for i in part], [self._ws[c][i].data_ptr() for i in part],
-                                           [self._ws[c][i].numel() for i in part]) for c in range(self.copies)]
-                if use == 2:
-                    g["usq"] = [g["batch"][c].ptrs([self._layer_sqnorm[c][i].data_ptr() for i in part])
-                                for c in range(self.copies)]
-                if use != 1:
-                    g["counted"] = False
-                    mat = [self.form[i] == "materialise" for i in part]
-                    g["gw"] = [g["batch"][c].ptrs([self._g[c][:, self.off_w[i]:].data_ptr() if m else None
-                                                   for i, m in zip(part, mat)]) for c in range(self.copies)] if any(mat) else None
-                    g["gb"] = [g["batch"][c].ptrs([self._g[c][:, self.off_b[i]:].data_ptr() if (m and self.pb[i]) else None
-                                                   for i, m in zip(part, mat)]) for c in range(self.copies)] if any(mat) else None
-                else:
-                    g["sq"] = [g["batch"][c].ptrs([self._group_sqnorm[c][self.group_of_layer[i]].data_ptr() for i in part])
-                               for c in range(self.copies)]
-                    g["clip"] = g["batch"][0].floats([self.group_clip[self.group_of_layer[i]] for i in part])
-                    g["acc_w"] = g["batch"][0].ptrs([self.acc[self.off_w[i]:].data_ptr() for i in part])
-                    g["acc_b"] = g["batch"][0].ptrs([self.acc[self.off_b[i]:].data_ptr() if self.pb[i] else None
-                                                     for i in part])
-                g["flops"] = sum(self.layers[i].flops for i in part) * self.n
-                g["bytes"] = sum(self.work[i][2 if use == 1 else 1] for i in part)
-                g["seconds"] = self._estimate(g)
-                groups.append(g)
-        groups.sort(key=lambda g: -g["seconds"])
-        # side stream of each group: longest first onto the least loaded stream
-        load = [0.0] * max(1, self.n_streams)
-        for gi, g in enumerate(groups):
-            k = load.index(min(load)) if self.lanes != "round_robin" else gi % max(1, self.n_streams)
-            g["lane"] = k
-            load[k] += g["seconds"]
-        return groups
+    def _phase_sizes(self, micro_steps: int) -> List[int]:
+        """How many micro-steps each phase of a step of `micro_steps` holds: as few phases as the bound allows, of nearly equal
+        size."""
+        phases = max(1, -(-micro_steps // self._together))
+        return [micro_steps // phases + (1 if k < micro_steps % phases else 0) for k in range(phases)]
 
-    def _estimate(self, g) -> float:
-        """Duration of a group's launch for the lane balance: its work at the rates its kernel family sustains on
-        MI355X when it has the chip to itself (measured call by call on ResNet-50 at n = 32), plus a few
-        microseconds per launch however small it is."""
-        if self.lanes == "flops" or self.wl.n <= 2:
-            # micro-steps of one or two examples: launches are bound by the walk along K of a few workgroups, not by
-            # the chip's rates; flops alone order them better (measured: 5.6 k against 5.1 k examples/s)
-            return g["flops"] / 150.0e12 + 8.0e-6
-        name = g["name"]
-        if name.startswith("conv3x3_rows"):
-            rate = 300.0e12                      # (100 .. 300: the same step time; the family is one launch per phase)
-        elif "gather" in name:
-            rate = 130.0e12
-        else:
-            rate = 400.0e12
-        return max(g["flops"] / rate, g["bytes"] / 4.5e12) + 8.0e-6
+    def _plan(self, tensors: int) -> _Plan:
+        if tensors not in self._plans:
+            self._plans[tensors] = _Plan(self, tensors)
+        return self._plans[tensors]
 
-    def _arm(self, group, use: int):
+    # ---- what a phase of a whole step looks like (tests, bench.py)
+    @property
+    def form(self):
+        return self._main.form
+
+    @property
+    def rows(self):
+        return self._main.rows
+
+    @property
+    def p_mat(self):
+        return self._main.p_mat
+
+    @property
+    def work(self):
+        return self._main.work
+
+    @property
+    def _g(self):
+        return self._main.g
+
+    @property
+    def micro_steps_per_phase(self):
+        return self._main.tensors
+
+    def _arm(self, plan: _Plan, group, use: int):
         if self.probe is not None and group["conv"]:
-            self.probe.arm(group["name"], sum(self.work[i][0] for i in group["layers"]),
-                           sum(self.work[i][1 + use] for i in group["layers"]), len(group["layers"]))
+            self.probe.arm(group["name"], sum(plan.work[i][0] for i in group["layers"]),
+                           sum(plan.work[i][1 + use] for i in group["layers"]), len(group["layers"]))
 
-    def _choose(self, layer, mode: str) -> str:
+    def _choose(self, layer, mode: str, n: int) -> str:
         if mode in ("materialise", "recompute"):
             return mode
         if mode != "auto":
@@ -261,14 +362,14 @@ class PrivatiseStep:
         # recompute (15 layers, 19.4 M parameters).  Whole-step throughput around this split: 37/17 (300 TFLOP/s: the
         # strided 3x3 layer of stage 3, whose weighted form has no raw-row kernel, and the first 1x1 of stage 4 recompute
         # too) - 2 %, 44/10 (250) - 9 %, 26/28 (360) - 3 %.
-        if self.n <= 2:
-            # micro-steps of one or two examples are bound by their launches, and a recomputing layer brings launches of its
+        if n <= 2:
+            # phases of one or two examples are bound by their launches, and a recomputing layer brings launches of its
             # own to the clipped-sum phase (measured: 5.9 k against 5.6 k examples/s with the split above)
             return "materialise"
         p = layer.pw + layer.pb
         esize = 2 if self.wl.dtype == "bf16" else 4
-        materialise = 8.0 * p * self.n / 5.0e12
-        recompute = layer.in_bytes(esize) * self.n / 4.0e12 + layer.flops * self.n / 275.0e12
+        materialise = 8.0 * p * n / 5.0e12
+        recompute = layer.in_bytes(esize) * n / 4.0e12 + layer.flops * n / 275.0e12
         return "materialise" if materialise <= recompute else "recompute"
 
     # ---- views of one layer's tensors in the flat vectors
@@ -291,7 +392,7 @@ class PrivatiseStep:
 
     @property
     def g(self) -> Optional[torch.Tensor]:
-        return self._g[self._last]
+        return self._g_last
 
     def enable_update(self, lr: float, momentum: float = 0.0, theta: Optional[torch.Tensor] = None,
                       keep_gradient: bool = True):
@@ -318,106 +419,110 @@ class PrivatiseStep:
     def begin_step(self):
         self.acc.zero_()
         self.micro_steps_done = 0
-        self._b_done = [None] * self.copies
+        self._phases = 0
+        for plan in self._plans.values():
+            plan.b_done = [None] * self.copies
 
     def micro_step(self, inputs: Sequence):
         """inputs: per layer (x, dy) device tensors of the workload's dtype, n examples each.
 
         Phase A (per-example gradients + norms of every layer) and phase B (clipped sum) of one
-        micro-step are separated by dp_norms.  Layers within a phase are independent; with side
+        micro-step are separated by the norm reduction.  Layers within a phase are independent; with side
         streams they are spread over them, and phase A of the next micro-step does not wait for
         phase B of this one (they work on different buffer copies).  The clipped sums reach the
         accumulator in the same order on every run: each tensor is updated by one call per
-        micro-step, always issued on the same stream."""
+        phase, always issued on the same stream."""
+        self._issue(self._plan(1), [x.data_ptr() for x, _ in inputs], [dy.data_ptr() for _, dy in inputs])
+
+    def _issue(self, plan: _Plan, x: Sequence[int], dy: Sequence[int]):
+        """The two phases of plan.tensors micro-steps; x, dy: per layer the address of the tensor, or of its array of example
+        addresses."""
+        at = plan.tensors > 1
         L = len(self.layers)
-        gs = self.p_mat
-        c = self.micro_steps_done % self.copies
-        self._last = c
-        g_buf, gsq, wss = self._g[c], self._group_sqnorm[c], self._ws[c]
+        gs = plan.p_mat
+        c = self._phases % self.copies
+        g_buf, gsq = plan.g[c], plan.group_sqnorm[c]
+        fork = self.fork or ("step" if plan.n <= 2 else "micro_step")
         main = torch.cuda.current_stream()
+        ms = main.cuda_stream
         # ---- phase A
         for st in self.side:
-            if self.fork == "micro_step" or self.micro_steps_done == 0:
+            if fork == "micro_step" or self._phases == 0:
                 st.wait_stream(main)
-            if self._b_done[c] is not None:           # this copy's previous clipped sum has finished
-                for ev in self._b_done[c]:
+            if plan.b_done[c] is not None:            # this copy's previous clipped sum has finished
+                for ev in plan.b_done[c]:
                     st.wait_event(ev)
-        if self.clip_unit > 1:
-            # unit sums and their norms: one batch call per kernel variant of the clip-weighted form (the kernels
-            # that run), dealt to the side streams
-            for grp in self._groups_u:
-                st = self.side[grp["lane"]] if self.side else None
-                bt = grp["batch"][c]
-                xs = bt.ptrs([inputs[i][0].data_ptr() for i in grp["layers"]])
-                dys = bt.ptrs([inputs[i][1].data_ptr() for i in grp["layers"]])
-                B.dp_unit_grad_batch(bt, self.clip_unit, xs, dys, grp["gw"][c], grp["gb"][c], grp["usq"][c], g_stride=gs,
-                                     stream=st)
-        for gi, grp in enumerate(self._groups_a if self.clip_unit == 1 else ()):
-            st = self.side[grp["lane"]] if self.side else None
+        # unit sums and their norms: one batch call per kernel variant of the clip-weighted form (the kernels
+        # that run), dealt to the side streams
+        for grp in plan.groups_u:
             bt = grp["batch"][c]
-            xs = bt.ptrs([inputs[i][0].data_ptr() for i in grp["layers"]])
-            dys = bt.ptrs([inputs[i][1].data_ptr() for i in grp["layers"]])
-            self._arm(grp, 0)
-            B.dp_per_example_grad_batch(bt, xs, dys, grp["gw"][c] if grp["gw"] else None,
-                                        grp["gb"][c] if grp["gb"] else None, None, g_stride=gs, stream=st)
+            B.dp_unit_grad_batch(bt, self.clip_unit, bt.fill("x", [x[i] for i in grp["layers"]]), bt.fill("dy", [dy[i] for i in grp["layers"]]),
+                                 grp["gw"][c], grp["gb"][c], grp["usq"][c], g_stride=gs,
+                                 stream=self.side[grp["lane"]].cuda_stream if self.side else ms, addresses=at)
+        for grp in plan.groups_a:
+            bt = grp["batch"][c]
+            self._arm(plan, grp, 0)
+            B.dp_per_example_grad_batch(bt, bt.fill("x", [x[i] for i in grp["layers"]]), bt.fill("dy", [dy[i] for i in grp["layers"]]),
+                                        grp["gw"][c], grp["gb"][c], None, g_stride=gs,
+                                        stream=self.side[grp["lane"]].cuda_stream if self.side else ms, addresses=at)
             if not grp["counted"]:                     # how many partial sums per example each layer leaves behind
                 for k, i in enumerate(grp["layers"]):
-                    self._partial_counts[i] = bt.partial_counts[k]
+                    for table in plan.partials:
+                        table.counts[i] = bt.partial_counts[k]
                 grp["counted"] = True
         for st in self.side:
             main.wait_stream(st)
-        # H2: every layer's partial sums -> per-layer norms in one launch, per-group norms in a second
+        # H2: every layer's partial sums -> per-group norms
         if self.clip_unit == 1:
-            B.dp_layer_norms_from_partials(self._partials[c], self._partial_counts, self._layer_sqnorm_ptrs[c], L, self.n)
-        B.dp_norms(self._layer_sqnorm[c], self.group_of_layer_dev, L, self.rows, self.n_groups, gsq)
+            B.dp_norms_from_partials(plan.partials[c], plan.n, self.n_groups, gsq, stream=ms)
+        else:
+            B.dp_norms(plan.layer_sqnorm[c], self.group_of_layer_dev, L, plan.rows, self.n_groups, gsq, stream=ms)
         # ---- phase B
-        for st in self.side_b:
-            st.wait_stream(main)
         sb = self.side_b
-        if self.p_mat:
-            st0 = sb[0] if sb else None
-            if self.n_groups == 1:
-                # one clipping group: every materialised tensor shares the factors -> one pass
-                B.dp_clip_accumulate(g_buf, gsq[0], self.group_clip[0], self.rows, self.p_mat,
-                                     self.acc, g_stride=gs, stream=st0)
-            else:
-                # several clipping groups: one launch over all materialised tensors, a segment per layer
-                B.dp_clip_accumulate_segments(g_buf, gsq, self.n_groups, self._segments, self.rows, self.p_mat,
-                                              self.acc, g_stride=gs, stream=st0)
+        for st in sb:
+            st.wait_stream(main)
+        if plan.p_mat:
+            # one launch over all materialised tensors, whatever their clipping groups
+            B.dp_clip_accumulate_columns(g_buf, gsq, self.n_groups, plan.segments, plan.rows, plan.rows // plan.tensors, plan.p_mat, self.acc, g_stride=gs,
+                                         stream=sb[0].cuda_stream if sb else ms)
         if self.noise == "per_example":
             for li in range(L):
-                if self.form[li] == "materialise":
-                    self._example_noise(li, sb[0] if sb else None)
-        for gi, grp in enumerate(self._groups_b):
-            st = sb[(1 + gi) % len(sb)] if sb else None
+                if plan.form[li] == "materialise":
+                    self._example_noise(plan, li, sb[0].cuda_stream if sb else ms)
+        for gi, grp in enumerate(plan.groups_b):
+            st = sb[(1 + gi) % len(sb)].cuda_stream if sb else ms
             bt = grp["batch"][c]
-            xs = bt.ptrs([inputs[i][0].data_ptr() for i in grp["layers"]])
-            dys = bt.ptrs([inputs[i][1].data_ptr() for i in grp["layers"]])
-            self._arm(grp, 1)
-            B.dp_clip_accumulate_recompute_batch(bt, xs, dys, grp["sq"][c], grp["clip"], grp["acc_w"], grp["acc_b"],
-                                                 stream=st)
+            self._arm(plan, grp, 1)
+            B.dp_clip_accumulate_recompute_batch(bt, bt.fill("x", [x[i] for i in grp["layers"]]), bt.fill("dy", [dy[i] for i in grp["layers"]]),
+                                                 grp["sq"][c], grp["clip"], grp["acc_w"], grp["acc_b"], stream=st, addresses=at)
             if self.noise == "per_example":
                 for li in grp["layers"]:
-                    self._example_noise(li, st)
+                    self._example_noise(plan, li, st)
         if sb:
             evs = []
             for st in sb:
                 ev = torch.cuda.Event()
                 ev.record(st)
                 evs.append(ev)
-            self._b_done[c] = evs
-        self.micro_steps_done += 1
+            plan.b_done[c] = evs
+        rows = self.wl.n // self.clip_unit             # of a micro-step
+        for k in range(max(0, plan.tensors - self.copies), plan.tensors):
+            self._last = (self.micro_steps_done + k) % self.copies
+            self._group_sqnorm[self._last] = gsq[:, k * rows:(k + 1) * rows]
+        self._g_last = g_buf[-rows:] if g_buf is not None else None
+        self.micro_steps_done += plan.tensors
+        self._phases += 1
 
-    def _example_noise(self, li: int, st):
-        """Per-example noise of this micro-step's examples for the tensors of layer li, on the stream that
+    def _example_noise(self, plan: _Plan, li: int, st: int):
+        """Per-example noise of this phase's examples for the tensors of layer li, on the stream that
         updates those tensors."""
         wl = self.wl
         first = self.micro_steps_done * self.n
         B.dp_add_example_noise(self.acc_w(li).data_ptr(), self.pw[li], wl.sigma, self.clip_total, wl.total_batch,
-                               wl.philox_seed, 0, 2 * li, first, self.n, step_dev=self._step_dev, stream=st)
+                               wl.philox_seed, 0, 2 * li, first, plan.n, step_dev=self._step_dev, stream=st)
         if self.pb[li]:
             B.dp_add_example_noise(self.acc_b(li).data_ptr(), self.pb[li], wl.sigma, self.clip_total, wl.total_batch,
-                                   wl.philox_seed, 0, 2 * li + 1, first, self.n, step_dev=self._step_dev, stream=st)
+                                   wl.philox_seed, 0, 2 * li + 1, first, plan.n, step_dev=self._step_dev, stream=st)
 
     def _drain(self):
         """The current stream waits for every clipped sum issued so far."""
@@ -442,10 +547,42 @@ class PrivatiseStep:
         self._step_dev.add_(1)
         self.step += 1
 
+    def _write_addresses(self, steps: Sequence[Sequence], sizes: List[int], table: Optional[torch.Tensor]) -> torch.Tensor:
+        """Example addresses of every operand (x and dy of each layer) of every phase: [operand][example of the phase], phase after
+        phase."""
+        operands, n = 2 * len(self.layers), self.wl.n
+        need = operands * n * len(steps)
+        if table is None or table.numel() < need:
+            table = torch.empty(need, dtype=torch.int64, device=self.device)
+        first = 0
+        for size in sizes:
+            part = steps[first: first + size]
+            B.dp_example_addresses([inputs[i][k].data_ptr() for i in range(len(self.layers)) for k in (0, 1) for inputs in part],
+                                   self._example_bytes, operands, size, n, table.data_ptr() + 8 * operands * n * first)
+            first += size
+        return table
+
+    def _issue_step(self, steps: Sequence[Sequence], table: Optional[torch.Tensor] = None):
+        """Every micro-step of a step, several at a time where they are small (`table`: addresses already written)."""
+        sizes = self._phase_sizes(len(steps))
+        if max(sizes) == 1:
+            for inputs in steps:
+                self.micro_step(inputs)
+            return
+        if table is None:
+            table = self._addresses = self._write_addresses(steps, sizes, self._addresses)
+        first, n, L = 0, self.wl.n, len(self.layers)
+        for size in sizes:
+            if size == 1:
+                self.micro_step(steps[first])
+            else:
+                base, row = table.data_ptr() + 8 * 2 * L * n * first, 8 * n * size
+                self._issue(self._plan(size), [base + row * 2 * i for i in range(L)], [base + row * (2 * i + 1) for i in range(L)])
+            first += size
+
     def run(self, inputs_per_micro_step: Sequence[Sequence]):
         self.begin_step()
-        for inputs in inputs_per_micro_step:
-            self.micro_step(inputs)
+        self._issue_step(inputs_per_micro_step)
         self.finalize()
         return self.out
 
@@ -456,11 +593,17 @@ class PrivatiseStep:
         assert self.probe is None or not getattr(self.probe, "enabled", False)
         step0 = self.step
         self.run(inputs_per_micro_step)          # warm-up outside capture (lazy module loads)
+        # the recorded launches read addresses of their own, which stay as long as the graph does
+        sizes = self._phase_sizes(len(inputs_per_micro_step))
+        table = self._write_addresses(inputs_per_micro_step, sizes, None) if max(sizes) > 1 else None
         torch.cuda.synchronize()
         graph = torch.cuda.CUDAGraph()
         with torch.cuda.graph(graph):
-            self.run(inputs_per_micro_step)
+            self.begin_step()
+            self._issue_step(inputs_per_micro_step, table)
+            self.finalize()
         self.graph = graph
+        self._graph_addresses = table
         self.set_step(step0)                     # recording consumed no optimiser step
         return graph
 

@@ -10,7 +10,7 @@ import oracle
 import paper_2109_12191_amd as dp
 from gpu_util import BF16_TOL, F32_TOL, assert_close, dev, host
 from test_gpu_kernels import _inputs, _oracle_grads, _run_per_example
-from workloads import dense, gn_affine, to_bf16_grid
+from workloads import Layer, conv, dense, gn_affine, to_bf16_grid
 
 pytestmark = pytest.mark.gpu
 
@@ -67,3 +67,101 @@ def test_dense_token_kernels(tokens, cin, cout, n, dtype):
     acc_w, acc_b = _run_weighted(layer, x, dy, dtype, ref_n2, clip_c)
     assert_close(acc_w, 1.0 + (f[:, None] * ref_w).sum(0), F32_TOL, "acc_w")
     assert_close(acc_b, 1.0 + (f[:, None] * ref_b).sum(0), F32_TOL, "acc_b")
+
+
+# ---- examples in several tensors (dp_example_addresses and the *_at calls): every kernel family, rows that start on odd
+# elements, one example per tensor and several; the numbers are those of one tensor, bit for bit
+def _addresses(tensors, n_per, example_bytes):
+    table = torch.empty(len(tensors) * n_per, dtype=torch.int64, device="cuda:0")
+    dp.dp_example_addresses([t.data_ptr() for t in tensors], [example_bytes], 1, len(tensors), n_per, table)
+    assert table.tolist() == [t.data_ptr() + j * example_bytes for t in tensors for j in range(n_per)]
+    return table
+
+
+_SEVERAL = [
+    ("1x1 64x64 tile", conv(64, 64, 1, 1, 12), "bf16"), ("1x1 128x128 odd tail", conv(160, 136, 1, 1, 10), "bf16"),
+    ("1x1 256x128", conv(256, 256, 1, 1, 10), "bf16"), ("1x1 whole rows", conv(256, 512, 1, 1, 14), "bf16"),
+    ("1x1 odd rows bias", conv(97, 71, 1, 1, 7, bias=True), "bf16"), ("1x1 stride 2", conv(48, 80, 1, 2, 14), "bf16"),
+    ("1x1 stride 2 gram", conv(512, 256, 1, 2, 14), "bf16"), ("1x1 gram", conv(256, 512, 1, 1, 7), "bf16"),
+    ("3x3 gram", conv(256, 512, 3, 1, 7), "bf16"), ("3x3 rows w7 odd channels", conv(65, 67, 3, 1, 7), "bf16"),
+    ("3x3 rows w14", conv(64, 70, 3, 1, 14), "bf16"), ("3x3 rows w32 short", Layer("conv", 64, 64, 3, 32, 3, 3, 1, 1, False), "bf16"),
+    ("3x3 rows s2", conv(64, 64, 3, 2, 28), "bf16"), ("3x3 general", conv(13, 70, 3, 1, 13), "bf16"),
+    ("3x3 general s2 odd", conv(17, 33, 3, 2, 15, bias=True), "bf16"), ("5x5 stride 3", Layer("conv", 6, 10, 14, 17, 5, 5, 3, 2, True), "bf16"),
+    ("tiny image", conv(3, 5, 3, 1, 3), "bf16"), ("stem", conv(3, 64, 7, 2, 64), "bf16"),
+    ("fp32 3x3", conv(12, 20, 3, 1, 11, bias=True), "f32"), ("fp32 1x1", conv(70, 90, 1, 1, 8), "f32"),
+    ("dense", dense(100, 37), "bf16"), ("dense fp32", dense(33, 70), "f32"), ("dense tokens odd", dense(37, 61, tokens=3), "bf16"),
+    ("dense tokens", dense(66, 70, tokens=70), "bf16"), ("dense tokens fp32", dense(33, 30, tokens=5), "f32"),
+    ("gn", gn_affine(32, 9, 8), "bf16"), ("gn fp32", gn_affine(16, 8, 4), "f32"), ("gn wide", gn_affine(600, 3, 2), "bf16"),
+]
+
+
+@pytest.mark.parametrize("n_per", [1, 3])
+@pytest.mark.parametrize("name,layer,dtype", _SEVERAL, ids=[c[0] for c in _SEVERAL])
+def test_examples_in_several_tensors(name, layer, dtype, n_per):
+    tensors = 33 if name in ("1x1 256x128", "1x1 whole rows") else 4          # (those kernels want 128 tiles)
+    n = tensors * n_per
+    x, dy = _inputs(layer, n, 131, dtype)
+    xd, dyd = dev(x, dtype), dev(dy, dtype)
+    es = 2 if dtype == "bf16" else 4
+    x_parts = [xd[k * n_per:(k + 1) * n_per].clone() for k in range(tensors)]
+    dy_parts = [dyd[k * n_per:(k + 1) * n_per].clone() for k in range(tensors)]
+    xt, dyt = _addresses(x_parts, n_per, layer.x_bytes(es)), _addresses(dy_parts, n_per, layer.dy_bytes(es))
+    d = dp.make_desc(layer, n, dtype)
+    ws = torch.empty(max(16, dp.dp_workspace_bytes(d), dp.dp_workspace_bytes(d, dp.DP_WS_RECOMPUTE), dp.dp_unit_workspace_bytes(d, 3)),
+                     dtype=torch.uint8, device="cuda:0")
+    batch = dp.LayerBatch([d], [ws.data_ptr()], [ws.numel()])
+    row = (layer.pw + 3) // 4 * 4
+    got = []
+    for addresses, xp, dyp in ((False, xd, dyd), (True, xt, dyt)):
+        res = []
+        g = torch.zeros((n, row + (layer.pb + 3) // 4 * 4), device="cuda:0")
+        sq, sq2 = torch.zeros(n, device="cuda:0"), torch.zeros(n, device="cuda:0")
+        args = (batch.ptrs([xp.data_ptr()]), batch.ptrs([dyp.data_ptr()]))
+        gb = batch.ptrs([g[:, row:].data_ptr()]) if layer.pb else None
+        dp.dp_per_example_grad_batch(batch, *args, batch.ptrs([g.data_ptr()]), gb, batch.ptrs([sq.data_ptr()]), g_stride=g.shape[1],
+                                     addresses=addresses)
+        dp.dp_per_example_grad_batch(batch, *args, None, None, batch.ptrs([sq2.data_ptr()]), addresses=addresses)
+        acc, acc_b = torch.ones(row, device="cuda:0"), torch.ones(max(4, layer.pb), device="cuda:0")
+        clip = float(sq.median().sqrt())
+        dp.dp_clip_accumulate_recompute_batch(batch, *args, batch.ptrs([sq.data_ptr()]), batch.floats([clip]), batch.ptrs([acc.data_ptr()]),
+                                              batch.ptrs([acc_b.data_ptr()]) if layer.pb else None, addresses=addresses)
+        res = [g, sq, sq2, acc, acc_b]
+        if n_per == 3:
+            gu, squ = torch.zeros((tensors, g.shape[1]), device="cuda:0"), torch.zeros(tensors, device="cuda:0")
+            dp.dp_unit_grad_batch(batch, 3, *args, batch.ptrs([gu.data_ptr()]), batch.ptrs([gu[:, row:].data_ptr()]) if layer.pb else None,
+                                  batch.ptrs([squ.data_ptr()]), g_stride=g.shape[1], addresses=addresses)
+            res += [gu, squ]
+        torch.cuda.synchronize()
+        got.append(res)
+    for k, (one, several) in enumerate(zip(*got)):
+        assert torch.isfinite(one).all() and torch.equal(one, several), k
+    # and they are the right numbers (the other tests check the one-tensor calls; this guards against both reading nothing)
+    if layer.pw * n < 4e6:
+        ref_w, _, ref_n2 = _oracle_grads(layer, x[:2], dy[:2])
+        assert_close(host(got[1][0])[:2, :layer.pw], ref_w, BF16_TOL, "dW")
+        assert np.allclose(host(got[1][1])[:2], ref_n2, rtol=BF16_TOL)
+
+
+def test_segments_at_places_of_their_own():
+    """dp_clip_accumulate_columns: segments around the 1024 columns of a workgroup, moved in the accumulator, against numpy."""
+    rng = np.random.default_rng(7)
+    begins, groups, clips = [0, 4, 1028, 2052, 3080], [0, 2, 1, 0, 2], [1.0, 0.5, 2.0, 0.7, float("inf")]
+    p, n = 4200, 18
+    places = [8000, 4096, 0, 2048, 5800]
+    g = rng.standard_normal((n, p + 4)).astype(np.float32)
+    sq = rng.uniform(0.2, 3.0, (3, n)).astype(np.float32)
+    acc0 = rng.standard_normal(8192).astype(np.float32)
+    want = acc0.astype(np.float64)
+    for k, b in enumerate(begins):
+        e = (begins + [p])[k + 1]
+        f = np.array([oracle.clip_factor(float(v), clips[k]) for v in sq[groups[k]]])
+        want[places[k]: places[k] + e - b] += (f[:, None] * g[:, b:e].astype(np.float64)).sum(0)
+    table, gd, sqd = dp.SegmentTable(begins, groups, clips, places), dev(g), dev(sq)
+    for run in (1, 3, 9, 18):
+        acc = dev(acc0)
+        dp.dp_clip_accumulate_columns(gd, sqd, 3, table, n, run, p, acc, g_stride=p + 4)
+        assert_close(host(acc), want, F32_TOL, "acc")
+        split = dev(acc0)                              # the same runs, a call each: the same bits
+        for k in range(0, n, run):
+            dp.dp_clip_accumulate_columns(gd[k:], sqd[:, k:k + run].contiguous(), 3, table, run, run, p, split, g_stride=p + 4)
+        assert torch.equal(acc, split), run

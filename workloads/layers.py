@@ -1,6 +1,7 @@
 """Layer shape descriptions (no arithmetic of the method lives here)."""
 from __future__ import annotations
 
+import math
 from dataclasses import dataclass
 from typing import List
 
@@ -85,15 +86,17 @@ class Layer:
         s = self.oh * self.ow
         return 2 * self.cout * self.cin * self.kh * self.kw * s
 
+    def x_bytes(self, elem_bytes: int) -> int:
+        """Bytes of x of one example."""
+        return math.prod(self.x_shape) * elem_bytes
+
+    def dy_bytes(self, elem_bytes: int) -> int:
+        """Bytes of dy of one example."""
+        return math.prod(self.dy_shape) * elem_bytes
+
     def in_bytes(self, elem_bytes: int) -> int:
         """Bytes of x and dy of one example."""
-        nx = 1
-        for d in self.x_shape:
-            nx *= d
-        ny = 1
-        for d in self.dy_shape:
-            ny *= d
-        return (nx + ny) * elem_bytes
+        return self.x_bytes(elem_bytes) + self.dy_bytes(elem_bytes)
 
 
 def conv(cin, cout, k, stride, hw, bias=False, name="") -> Layer:
