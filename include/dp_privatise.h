@@ -236,7 +236,7 @@ dp_status dp_unit_grad_batch(const dp_layer_desc *descs, int clip_unit, const vo
                              void *const *ws, const size_t *ws_bytes, int n_layers, dp_stream stream);
 
 /* The batch calls above on examples that lie in SEVERAL tensors (the micro-steps of an optimiser step, each handed over in
- * tensors of its own): x[l] and dy[l] are device arrays of desc.n example addresses (in place of the tensors), so that one
+ * tensors of its own): x[l] and dy[l] are device arrays of desc.n example addresses (8-byte aligned, in place of the tensors), so that one
  * launch contracts the examples of all of them; everything else as in the calls without "_at", same results up to the
  * order of summation.  Channels-first layouts only (else DP_ERR_UNSUPPORTED).  Clipping units: the examples of a unit must
  * follow each other in one tensor.

@@ -460,8 +460,8 @@ static dp_status per_example_grad_batch(bool addresses, const dp_layer_desc *des
         DP_TRY(make_geo(&descs[l], g));
         if (addresses) DP_TRY(read_addresses(g));
         if (g.n != geo[0].n) return fail(DP_ERR_INVALID_ARG, "layer %d: n = %d differs from layer 0's %d", l, g.n, geo[0].n);
-        DP_TRY(check_ptr(x[l], "x[l]", true));
-        DP_TRY(check_ptr(dy[l], "dy[l]", true));
+        DP_TRY(check_ptr(x[l], "x[l]", true, addresses ? 8 : 16));       // (arrays of addresses are read word by word)
+        DP_TRY(check_ptr(dy[l], "dy[l]", true, addresses ? 8 : 16));
         float *gw = g_w ? g_w[l] : nullptr, *gb = g_b ? g_b[l] : nullptr;
         DP_TRY(check_ptr(gw, "g_w[l]", false));
         DP_TRY(check_ptr(gb, "g_b[l]", false));
@@ -536,8 +536,8 @@ static dp_status unit_grad_batch(bool addresses, const dp_layer_desc *descs, int
             if (g.kind == DP_DENSE) g.x_tab = g.dy_tab = clip_unit;      // its "examples" are units, which start at every clip_unit-th address
         }
         if (descs[l].n != descs[0].n) return fail(DP_ERR_INVALID_ARG, "layer %d: n = %d differs from layer 0's %d", l, descs[l].n, descs[0].n);
-        DP_TRY(check_ptr(x[l], "x[l]", true));
-        DP_TRY(check_ptr(dy[l], "dy[l]", true));
+        DP_TRY(check_ptr(x[l], "x[l]", true, addresses ? 8 : 16));       // (arrays of addresses are read word by word)
+        DP_TRY(check_ptr(dy[l], "dy[l]", true, addresses ? 8 : 16));
         float *gw = g_w ? g_w[l] : nullptr, *gb = g_b ? g_b[l] : nullptr;
         DP_TRY(check_ptr(gw, "g_w[l]", false));
         DP_TRY(check_ptr(gb, "g_b[l]", false));
@@ -646,8 +646,8 @@ static dp_status recompute_batch(bool addresses, const dp_layer_desc *descs, con
         Geo &g = geo[(size_t)l];
         DP_TRY(make_geo(&descs[l], g));
         if (addresses) DP_TRY(read_addresses(g));
-        DP_TRY(check_ptr(x[l], "x[l]", true));
-        DP_TRY(check_ptr(dy[l], "dy[l]", true));
+        DP_TRY(check_ptr(x[l], "x[l]", true, addresses ? 8 : 16));       // (arrays of addresses are read word by word)
+        DP_TRY(check_ptr(dy[l], "dy[l]", true, addresses ? 8 : 16));
         DP_TRY(check_ptr(sqnorm[l], "sqnorm[l]", true, 4));
         DP_TRY(check_ptr(acc_w[l], "acc_w[l]", true));
         float *ab = acc_b ? acc_b[l] : nullptr;

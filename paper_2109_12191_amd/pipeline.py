@@ -565,7 +565,7 @@ class PrivatiseStep:
     def _issue_step(self, steps: Sequence[Sequence], table: Optional[torch.Tensor] = None):
         """Every micro-step of a step, several at a time where they are small (`table`: addresses already written)."""
         sizes = self._phase_sizes(len(steps))
-        if max(sizes) == 1:
+        if max(sizes) <= 1:
             for inputs in steps:
                 self.micro_step(inputs)
             return

@@ -242,3 +242,19 @@ def test_both_clip_branches_zero_example_and_infinite_bound():
             torch.cuda.synchronize()
             for li, l in enumerate(wl.layers):
                 assert_close(host(ps.out_w(li)), ref["out_w"][li], BF16_TOL, f"{mode} C={wl.clip_c} out_w[{li}] {l.name}")
+
+
+@pytest.mark.parametrize("n,accum", [(3, 3), (1, 5), (5, 1), (3, 0)])
+def test_odd_phases_and_empty_steps_match_single_micro_steps(n, accum):
+    """run() puts the micro-steps of a step together (an odd number of examples here); one after the other they give the same sums."""
+    wl = get_workload("resnet18_gn", n=n, accum=max(1, accum), hw=16)
+    inputs = [[(dev(x, wl.dtype), dev(dy, wl.dtype)) for x, dy in make_inputs(wl, m)] for m in range(accum)]
+    got, want = dp.PrivatiseStep(wl), dp.PrivatiseStep(wl)
+    got.run(inputs)
+    want.begin_step()
+    for step in inputs:
+        want.micro_step(step)
+    want.finalize()
+    torch.cuda.synchronize()
+    assert_close(host(got.acc), host(want.acc), BF16_TOL, "acc")          # (a larger phase may recompute where a smaller one materialises)
+    assert torch.isfinite(got.out).all()

@@ -274,3 +274,18 @@ def test_flat_finalize_rejects_bad_tables(lib):
     assert call(theta=FAKE, lr=float("nan")) == B.DP_ERR_INVALID_ARG
     assert call(step_dev=FAKE + 4) == B.DP_ERR_INVALID_ARG        # 8-byte alignment
     assert lib.dp_add_noise_finalize_flat(FAKE, FAKE, None, None, None, None, None, 1, 1.0, 1.0, 4, 0, 0, None, 0.0, 0.0, None) == B.DP_ERR_INVALID_ARG
+
+
+def test_arrays_of_example_addresses_need_the_alignment_of_a_word_only(lib):
+    """The array of the second operand starts 8 bytes off where a phase holds an odd number of examples: such a call gets as far as the
+    workspace check, and one that is not aligned to a word is refused."""
+    d = dp.make_desc(conv(8, 8, 1, 1, 4), 3)
+    batch = B.LayerBatch([d], [0], [0])
+    g, sq = batch.ptrs([FAKE]), batch.ptrs([FAKE])
+    for at, status in ((FAKE + 8, B.DP_ERR_WORKSPACE), (FAKE + 4, B.DP_ERR_INVALID_ARG)):
+        odd = batch.ptrs([at])
+        for x, dy in ((odd, g), (g, odd)):
+            _raises(status, dp.dp_per_example_grad_batch, batch, x, dy, g, None, sq, addresses=True, stream=0)
+            _raises(status, dp.dp_unit_grad_batch, batch, 3, x, dy, g, None, sq, addresses=True, stream=0)
+            _raises(status, dp.dp_clip_accumulate_recompute_batch, batch, x, dy, sq, batch.floats([1.0]), g, None, addresses=True, stream=0)
+            _raises(B.DP_ERR_INVALID_ARG, dp.dp_per_example_grad_batch, batch, x, dy, g, None, sq, stream=0)
