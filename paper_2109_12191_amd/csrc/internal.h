@@ -96,6 +96,13 @@ size_t stem_ws_bytes(const Geo &g);
 size_t stem_norm_partial_count(void);
 dp_status launch_stem(const Geo &g, const void *x, const void *dy, float *out_w, size_t out_stride, float *sqnorm, void *ws,
                       hipStream_t s);
+// fp32 convolutions with square odd kernels from raw image rows: conv_rows.hip
+bool conv_rows_applicable(const Geo &g, int mode);
+size_t conv_rows_ws_bytes(const Geo &g);
+size_t conv_rows_norm_partial_count(const Geo &g);
+const char *conv_rows_variant_name(const Geo &g);
+dp_status launch_conv_rows(const Geo &g, const void *x, const void *dy, float *out_w, float *out_b, size_t out_stride, float *sqnorm,
+                           void *ws, hipStream_t s);
 bool gram_norm_applicable(const Geo &g, int mode);
 size_t gram_ws_bytes(const Geo &g);
 size_t gram_norm_partial_count(void);

@@ -165,3 +165,37 @@ def test_segments_at_places_of_their_own():
         for k in range(0, n, run):
             dp.dp_clip_accumulate_columns(gd[k:], sqd[:, k:k + run].contiguous(), 3, table, run, run, p, split, g_stride=p + 4)
         assert torch.equal(acc, split), run
+
+
+# ---- fp32 convolutions from raw rows: channels around the 16 and 32 of a block, output rows that are no multiple of four, one row,
+# a kernel larger than the image, several chunks of rows with a short last one, several examples per workgroup
+@pytest.mark.parametrize("cin,cout,h,w,k,stride,n", [(1, 1, 1, 1, 1, 1, 1), (16, 17, 5, 7, 1, 2, 3), (33, 32, 8, 8, 1, 1, 2), (3, 16, 9, 6, 3, 1, 2),
+                                                     (17, 33, 2, 1, 3, 1, 3), (32, 31, 57, 56, 3, 1, 1), (40, 24, 33, 35, 3, 2, 2), (64, 64, 7, 7, 3, 1, 2),
+                                                     (5, 40, 3, 2, 5, 1, 2), (18, 20, 45, 37, 5, 2, 2), (16, 16, 12, 14, 3, 1, 8200), (2, 3, 130, 260, 3, 2, 1)])
+def test_conv_f32_raw_rows_kernel(cin, cout, h, w, k, stride, n):
+    layer = Layer("conv", cin, cout, h, w, k, k, stride, (k - 1) // 2, cout % 2 == 0)
+    assert dp.dp_kernel_variant(dp.make_desc(layer, n, "f32"), dp.DP_WS_PER_EXAMPLE_GRAD).startswith("conv_rows<f32")
+    x, dy = _inputs(layer, min(n, 5), 131, "f32")
+    if n > 5:                                     # the oracle's few examples, over and over
+        x, dy = (np.concatenate([v] * (n // 5)) for v in (x, dy))
+    gw, gb, sq = _run_per_example(layer, x, dy, "f32")
+    norms = _run_per_example(layer, x, dy, "f32", materialise=False)[2]
+    ref_w, ref_b, ref_n2 = _oracle_grads(layer, x[:5], dy[:5])
+    for got, ref in ((gw, ref_w), (gb, ref_b), (sq, ref_n2)):
+        if ref is not None and ref.size:
+            got = got.reshape((-1,) + ref.shape)
+            assert np.array_equal(got, np.broadcast_to(got[0], got.shape))      # the same bits wherever an example lies
+            assert_close(got[0], ref, F32_TOL, "gradient")
+    assert np.allclose(norms, sq, rtol=F32_TOL)
+
+
+def test_conv_f32_raw_rows_kernel_keeps_what_is_not_finite_in_its_place():
+    """An infinity in the last column of a row reaches the taps that read it and no other."""
+    layer = Layer("conv", 2, 2, 3, 5, 3, 3, 1, 1, False)
+    x, dy = _inputs(layer, 1, 137, "f32")
+    dy[:] = 1.0
+    x[0, 0, 1, 4] = np.inf
+    gw = _run_per_example(layer, x, dy, "f32")[0].reshape(2, 2, 3, 3)
+    want = np.ones((3, 3), bool)                  # the middle row, the last column: kw = 0 needs column 5 of dY, which is not there
+    want[:, 0] = False
+    assert np.array_equal(np.isinf(gw[0, 0]), want) and np.isfinite(gw[:, 1]).all() and np.isfinite(gw[:, 0, :, 0]).all()
