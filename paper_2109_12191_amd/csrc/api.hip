@@ -113,6 +113,7 @@ static dp_status make_geo(const dp_layer_desc *d, Geo &g)
     if (d->cin < 1 || d->cout < 1 || d->h < 1 || d->w < 1)
         return fail(DP_ERR_INVALID_ARG, "non-positive dimension (cin %d cout %d h %d w %d)", d->cin, d->cout, d->h, d->w);
     memset(&g, 0, sizeof(g));
+    g.unit = 1;
     g.kind = d->kind; g.bf16 = d->in_dtype == DP_BF16; g.n = d->n;
     g.nhwc = (d->layout == DP_NHWC && d->kind != DP_DENSE) ? 1 : 0;       // a dense layer's [n, tokens, features] is the same in both
     g.cin = d->cin; g.cout = d->cout; g.h = d->h; g.w = d->w;
@@ -374,6 +375,8 @@ static dp_status unit_geo(const dp_layer_desc *desc, int clip_unit, Geo &g)
         d2.n = desc->n / clip_unit;
         d2.h = desc->h * clip_unit;
         DP_TRY(make_geo(&d2, g));
+    } else if (g.kind == DP_CONV2D) {
+        g.unit = clip_unit;
     }
     return DP_OK;
 }
@@ -381,7 +384,7 @@ static dp_status unit_geo(const dp_layer_desc *desc, int clip_unit, Geo &g)
 static size_t unit_ws_kernels(const Geo &g, int kind, int clip_unit)
 {
     if (kind == DP_DENSE) return align16_api(dense_ws_bytes(g, MODE_NORM));          // g is already the reshaped layer
-    if (kind == DP_CONV2D) return align16_api(conv_unit_ws_bytes(g, clip_unit));
+    if (kind == DP_CONV2D) return align16_api(conv_ws_bytes(g, MODE_NORM));
     return align16_api(gn_unit_ws_bytes(g, clip_unit));
 }
 static size_t unit_ws_need(const Geo &g, int kind, int clip_unit) { return unit_ws_kernels(g, kind, clip_unit) + layout_copy_bytes(g); }
@@ -392,7 +395,7 @@ static dp_status launch_layer_units(const Geo &g, int clip_unit, const void *x, 
     DP_TRY_ST(channels_first_inputs(g, unit_ws_kernels(g, g.kind, clip_unit), x, dy, ws, s));
     if (g.kind == DP_DENSE)
         return launch_dense(g, g_w ? MODE_MATERIALISE : MODE_NORM, x, dy, g_w, g_b, g_stride, sqnorm, nullptr, 0.0f, ws, s);
-    if (g.kind == DP_CONV2D) return launch_conv_units(g, clip_unit, x, dy, g_w, g_b, g_stride, sqnorm, ws, s);
+    if (g.kind == DP_CONV2D) return launch_conv(g, g_w ? MODE_MATERIALISE : MODE_NORM, x, dy, g_w, g_b, g_stride, sqnorm, nullptr, 0.0f, ws, s);
     return launch_gn_units(g, clip_unit, x, dy, g_w, g_b, g_stride, sqnorm, ws, s);
 }
 
@@ -572,7 +575,7 @@ static dp_status unit_grad_batch(bool addresses, const dp_layer_desc *descs, int
         parts[(size_t)l] = static_cast<const float *>(ws[l]);
         // sqnorm == nullptr: the partial sums stay in the workspace for the one reduction launch below
         if (g.kind == DP_CONV2D) {
-            counts[(size_t)l] = (int32_t)conv_unit_norm_partial_count(g, clip_unit);     // the plan in force inside this batch
+            counts[(size_t)l] = (int32_t)conv_norm_partial_count(g, mode);               // the plan in force inside this batch
             st = launch_layer_units(g, clip_unit, x[l], dy[l], gw, gb, g_stride, nullptr, ws[l], s);
         } else if (g.kind == DP_DENSE) {
             counts[(size_t)l] = (int32_t)dense_norm_partial_count(g, mode);

@@ -65,8 +65,8 @@ struct ConvArgs {
     int ex_per_wg;                    // per-example mode, ksplit == 1: consecutive examples per workgroup
     int force_slow;                   // stride other than 1 or 2: stage every chunk element by element
     int x_tab, dy_tab;                // Geo::x_tab / dy_tab: the operand pointers are arrays of example addresses
-    int unit_major;                   // weighted mode, > 0: clipping units, each made of unit_major example ranges; the
-                                      // ranges' blocks always go to the workspace, ordered (unit, tile, range in unit)
+    int unit;                         // per-example mode: Geo::unit (ex_per_wg is a multiple of it)
+    int slice_ex;                     // per-example mode, ksplit > 1: > 0: the slices are ranges of this many examples of a unit
 };
 
 struct ColInfo {
@@ -380,6 +380,12 @@ __global__ void __launch_bounds__(THREADS, 2) conv_contract_kernel(const Grouped
         i_end = min(a.n, i_begin + a.ex_per_wg);
         c_begin = split * a.chunks_per_split;
         c_end = min(a.chunks_per_ex, c_begin + a.chunks_per_split);
+        if (a.slice_ex) {                   // a range of a unit's examples, all chunks of each
+            i_begin += split * a.slice_ex;
+            i_end = i_begin + a.slice_ex;
+            c_begin = 0;
+            c_end = a.chunks_per_ex;
+        }
     }
     const int cpe = c_end - c_begin;
     const int n_chunks = (i_end - i_begin) * cpe;
@@ -690,7 +696,8 @@ __global__ void __launch_bounds__(THREADS, 2) conv_contract_kernel(const Grouped
 
     // MFMAs of one chunk out of one LDS buffer; then, in per-example mode without K slices, the
     // epilogue of an example whose K has run out.
-    int chunk_in_ex = 0, ex = i_begin;
+    int chunk_in_ex = 0, ex = WEIGHTED ? 0 : i_begin / a.unit;     // (row of results)
+    const int cpr = WEIGHTED ? 0 : cpe * a.unit;                  // chunks of a row of results
     auto compute = [&](const char *bufA, const char *bufB) {
         const char *pa = bufA + (wm * TM * 32 + (lane & 31)) * PITCH + (lane >> 5) * 16;
         const char *pb = bufB + (wn * TN * 32 + (lane & 31)) * PITCH + (lane >> 5) * 16;
@@ -741,7 +748,7 @@ __global__ void __launch_bounds__(THREADS, 2) conv_contract_kernel(const Grouped
             }
         }
         if constexpr (!WEIGHTED) {
-            if (a.ksplit == 1 && ++chunk_in_ex == cpe) {
+            if (a.ksplit == 1 && ++chunk_in_ex == cpr) {
                 finish(ex);
                 ++ex;
                 chunk_in_ex = 0;
@@ -773,19 +780,15 @@ __global__ void __launch_bounds__(THREADS, 2) conv_contract_kernel(const Grouped
         __syncthreads();
     }
 
-    if (a.ksplit == 1 && !(WEIGHTED && a.unit_major)) {
+    if (a.ksplit == 1) {
         if constexpr (WEIGHTED) finish(0);
         return;
     }
 
     // ---- slices of one tile meet in the workspace; a second kernel (conv_fixup_kernel) adds
     // them in slice order and runs the epilogue.  Plain stores: the kernel boundary orders them.
-    const int group = WEIGHTED ? tile : (unit * tiles + tile);     // ex_per_wg == 1 when K is sliced
-    size_t slot = (size_t)group * a.ksplit + split;
-    if (WEIGHTED && a.unit_major) {                       // (unit, tile, range within the unit)
-        const int u = split / a.unit_major;
-        slot = ((size_t)u * tiles + tile) * a.unit_major + (split - u * a.unit_major);
-    }
+    const int group = WEIGHTED ? tile : (unit * tiles + tile);     // ex_per_wg == unit when K is sliced
+    const size_t slot = (size_t)group * a.ksplit + split;
     float *mine = a.ws_part + slot * (NACC * 16 * THREADS);
 #pragma unroll
     for (int t = 0; t < NACC; ++t)
@@ -920,6 +923,12 @@ __global__ void __launch_bounds__(WM * 128, (STAGES * (WM * TM + 2 * TN) * 4 <= 
         i_end = min(a.n, i_begin + a.ex_per_wg);
         c_begin = split * a.chunks_per_split;
         c_end = min(a.chunks_per_ex, c_begin + a.chunks_per_split);
+        if (a.slice_ex) {                   // a range of a unit's examples, all chunks of each
+            i_begin += split * a.slice_ex;
+            i_end = i_begin + a.slice_ex;
+            c_begin = 0;
+            c_end = a.chunks_per_ex;
+        }
     }
     i_begin = __builtin_amdgcn_readfirstlane(i_begin);
     c_begin = __builtin_amdgcn_readfirstlane(c_begin);
@@ -1122,7 +1131,9 @@ __global__ void __launch_bounds__(WM * 128, (STAGES * (WM * TM + 2 * TN) * 4 <= 
     }
     const unsigned long long block_bytes = (unsigned long long)J * 128ull;                  // 32 rows of the gradient matrix
     const unsigned long long out_ex_bytes = uniform_bits(reinterpret_cast<const void *>(a.out_stride_w * sizeof(float)));
-    unsigned long long out_corner = uniform_bits(out_w + (size_t)i_begin * a.out_stride_w + (size_t)m0 * J + n0);
+    const int per_row = __builtin_amdgcn_readfirstlane(WEIGHTED ? 1 : a.unit);              // examples of a row of results
+    int row = __builtin_amdgcn_readfirstlane(WEIGHTED ? 0 : i_begin / per_row), in_row = 0;
+    unsigned long long out_corner = uniform_bits(out_w + (size_t)row * a.out_stride_w + (size_t)m0 * J + n0);
     auto finish = [&](int i) {
         float ss = 0.0f;
         if (whole_tile) {
@@ -1194,10 +1205,12 @@ __global__ void __launch_bounds__(WM * 128, (STAGES * (WM * TM + 2 * TN) * 4 <= 
     const float *const group_sqnorm = a.group_sqnorm;
     const float clip_c = a.clip_c;
     for (int ex = i_begin; ex < i_end; ++ex) {
+        if (in_row == 0) {
 #pragma unroll
-        for (int t = 0; t < NACC; ++t)
+            for (int t = 0; t < NACC; ++t)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) acc[t][r] = 0.0f;
+                for (int r = 0; r < 16; ++r) acc[t][r] = 0.0f;
+        }
         for (int ch = 0; ch < full_here; ++ch) {
             begin_step();
             compute(stage);
@@ -1218,14 +1231,17 @@ __global__ void __launch_bounds__(WM * 128, (STAGES * (WM * TM + 2 * TN) * 4 <= 
             for (int t = 0; t < NACC; ++t)
 #pragma unroll
                 for (int r = 0; r < 16; ++r) tot[t][r] += f * acc[t][r];
-        } else if (ksplit == 1) {
-            finish(ex);
-            stores_now = stores_per_tile;
+        } else if (++in_row == per_row) {
+            in_row = 0;
+            if (ksplit == 1) {
+                finish(row++);
+                stores_now = stores_per_tile;
+            }
         }
     }
 
     if constexpr (WEIGHTED) {
-        if (ksplit == 1 && !a.unit_major) {
+        if (ksplit == 1) {
             tile_epilogue<2, TM, TN, true, false>(tot, a, 0, m0, n0, wm, wn, lane, false);
             return;
         }
@@ -1235,11 +1251,7 @@ __global__ void __launch_bounds__(WM * 128, (STAGES * (WM * TM + 2 * TN) * 4 <= 
     if constexpr (WM != 2) return;                        // never sliced (the host plans it so)
     // slices of one tile meet in the workspace (conv_fixup_kernel adds them in slice order)
     const int group = WEIGHTED ? tile : (unit * tiles + tile);
-    size_t part = (size_t)group * ksplit + split;
-    if (WEIGHTED && a.unit_major) {                       // (unit, tile, range within the unit)
-        const int u = split / a.unit_major;
-        part = ((size_t)u * tiles + tile) * a.unit_major + (split - u * a.unit_major);
-    }
+    const size_t part = (size_t)group * ksplit + split;
     float *mine = a.ws_part + part * (NACC * 16 * THREADS);
 #pragma unroll
     for (int t = 0; t < NACC; ++t)
@@ -1523,6 +1535,7 @@ struct FullPlan {
     int shape, tiles_m, tiles_n;
     int kcolsp, chunks_per_ex;
     int ksplit, chunks_per_split, ex_per_split, ex_per_wg;
+    int slice_ex;           // per-example mode: examples per slice of a clipping unit, or 0 (slices of one example's chunks)
     int nacc;               // accumulator tiles per wave
     int groups;             // groups of slices (counters)
     size_t part_floats;     // floats of partial tiles in the workspace
@@ -1560,17 +1573,17 @@ static FullPlan full_plan(const Geo &g, int mode)
         // long K and few 128x128 tiles: 64x64 tiles give four times the (example, tile) units, so K
         // needs no (or less) slicing and far fewer partial tiles travel through the workspace
         const long long t128 = (long long)((g.cout + 127) / 128) * ((J + 127) / 128);
-        if ((long long)g.n * t128 < 512) p.shape = T64;
+        if ((long long)(g.n / g.unit) * t128 < 512) p.shape = T64;
     }
     // 256 x 128 tiles, eight waves, three stages, one workgroup per compute unit: the per-example form of aligned 1x1
     // layers with short K (at most 7 chunks: never sliced below) whose tiles are all whole, when the layer still has
     // a few hundred (example, tile) units
     if (p.shape == T128 && mode != MODE_WEIGHTED && flat_direct(g) && g.cout % 256 == 0 && J % 128 == 0 && p.chunks_per_ex <= 7 &&
-        (long long)g.n * (g.cout / 256) * (J / 128) >= 128)
+        (long long)(g.n / g.unit) * (g.cout / 256) * (J / 128) >= 128)
         p.shape = T256x128;
     // whole rows travelling in blocks of 32 (conv_panel_kernel): the same layers when their rows are short and of the
     // length that kernel's LDS layout wants, and output tiles of 256 x 256 are all whole
-    const bool panel = mode != MODE_WEIGHTED && flat_direct(g) && S % 8 == 4 && S > 16 * (PANEL_KS - 1) && S <= 16 * PANEL_KS &&
+    const bool panel = mode != MODE_WEIGHTED && g.unit == 1 && flat_direct(g) && S % 8 == 4 && S > 16 * (PANEL_KS - 1) && S <= 16 * PANEL_KS &&
                        g.cout % 256 == 0 && J % 256 == 0 && (long long)g.n * (g.cout / 256) * (J / 256) >= 128;
     if (panel) p.shape = T256rows;
     p.tiles_m = (g.cout + kTileM[p.shape] - 1) / kTileM[p.shape];
@@ -1580,7 +1593,7 @@ static FullPlan full_plan(const Geo &g, int mode)
     p.nacc = per_wave_tiles + (g.has_bias ? (p.shape == T64 ? 1 : 2) : 0);
     const size_t tile_floats = (size_t)p.nacc * 16 * THREADS;
 
-    p.ksplit = 1; p.chunks_per_split = p.chunks_per_ex; p.ex_per_split = g.n; p.ex_per_wg = 1;
+    p.ksplit = 1; p.chunks_per_split = p.chunks_per_ex; p.ex_per_split = g.n; p.ex_per_wg = g.unit; p.slice_ex = 0;
     if (mode == MODE_WEIGHTED) {
         // example ranges: enough workgroups to fill the chip, with the partial tiles that are
         // written and read back (cache-resident in practice) kept below ~100 MB
@@ -1597,8 +1610,18 @@ static FullPlan full_plan(const Geo &g, int mode)
         p.ksplit = (g.n + p.ex_per_split - 1) / p.ex_per_split;
         p.groups = tiles;
     } else {
-        const long long units = (long long)g.n * tiles;
-        if (p.shape == T256rows) {
+        const long long units = (long long)(g.n / g.unit) * tiles;
+        if (g.unit > 1) {
+            // clipping units: K runs over the positions of a unit's examples; a walk that is too long, or too few of them, is cut
+            // into ranges of examples of equal size (the wide tile is never sliced)
+            const long long walk = (long long)p.chunks_per_ex * g.unit;
+            const int tgt = crowd * (p.shape == T64 ? 4 : 1);
+            long long want = 1;
+            if (crowd ? walk > tgt + tgt / 2 : units < 512 && walk >= 8) want = crowd ? (walk + tgt - 1) / tgt : 256 / units;
+            int k = 1;
+            while (k < g.unit && (k < want || g.unit % k)) ++k;
+            if (k > 1 && p.shape != T256x128) { p.ksplit = k; p.slice_ex = g.unit / k; }
+        } else if (p.shape == T256rows) {
             // a unit (example, tile) is sixteen blocks; several in a row hide the filling of the ring (measured: 1, 2, 4 within 4 %)
             long long e = crowd ? 4 : (units + 511) / 512;
             if (e > 4) e = 4;
@@ -1637,7 +1660,7 @@ static FullPlan full_plan(const Geo &g, int mode)
             if (e > g.n) e = g.n;
             p.ex_per_wg = (int)(e < 1 ? 1 : e);
         }
-        p.groups = g.n * tiles;
+        p.groups = g.n / g.unit * tiles;
     }
     p.part_floats = (p.ksplit > 1) ? (size_t)p.groups * p.ksplit * tile_floats : 0;
     return p;
@@ -1705,7 +1728,7 @@ static size_t norm_partials_per_example(const FullPlan &f)
     const size_t tiles = (size_t)f.tiles_m * f.tiles_n;
     return f.ksplit > 1 ? tiles * f.nacc * FIX_PARTS : tiles * ((f.shape == T256x128 || f.shape == T256rows) ? 8 : 4);     // unsliced: a slot per wave
 }
-static size_t norm_partials(const Geo &g, const FullPlan &f) { return (size_t)g.n * norm_partials_per_example(f); }
+static size_t norm_partials(const Geo &g, const FullPlan &f) { return (size_t)(g.n / g.unit) * norm_partials_per_example(f); }
 
 // Exact workspace need of the kernels that (g, mode) is dispatched to.
 static size_t conv_ws_bytes_mode(const Geo &g, int mode);
@@ -1841,55 +1864,7 @@ static const void *kernel_of(int loader, bool weighted, bool bias, bool at)
 
 static dp_status launch_conv_impl(const Geo &g, int mode, const void *x, const void *dy, float *out_w, float *out_b,
                                   size_t out_stride, float *sqnorm, const float *group_sqnorm, float clip_c,
-                                  void *ws, hipStream_t s, int unit = 0);
-
-// The plan of the clip-weighted kernel with one example range per clipping unit.
-static FullPlan unit_plan(const Geo &g, int unit)
-{
-    FullPlan f = full_plan(g, MODE_WEIGHTED);
-    const int tiles = f.tiles_m * f.tiles_n;
-    // a range is a whole unit, unless that leaves too few workgroups walking too long: then the largest divisor
-    // of the unit that gives about 256 of them (down to one example per range)
-    int e = unit;
-    while (e > 1 && (long long)tiles * (g.n / e) < 256 && (long long)e * f.chunks_per_ex > 32) {
-        int d = e - 1;
-        while (unit % d) --d;
-        e = d;
-    }
-    f.ex_per_split = e;
-    f.ksplit = g.n / e;
-    f.groups = tiles;
-    f.part_floats = (size_t)tiles * f.ksplit * f.nacc * 16 * THREADS;
-    return f;
-}
-
-size_t conv_unit_ws_bytes(const Geo &g, int unit)
-{
-    if (conv3x3_applicable(g, MODE_WEIGHTED)) return conv3x3_unit_ws_bytes(g, unit);
-    const FullPlan f = unit_plan(g, unit);
-    const size_t units = (size_t)(g.n / unit), tiles = (size_t)f.tiles_m * f.tiles_n;
-    return align16(units * tiles * f.nacc * FIX_PARTS * sizeof(float)) + f.part_floats * sizeof(float);
-}
-
-// partial squared norms per unit left at the start of the workspace by a call with clipping units
-size_t conv_unit_norm_partial_count(const Geo &g, int unit)
-{
-    if (conv3x3_applicable(g, MODE_WEIGHTED)) return conv3x3_unit_norm_partial_count(g);
-    const FullPlan f = unit_plan(g, unit);
-    return (size_t)f.tiles_m * f.tiles_n * f.nacc * FIX_PARTS;
-}
-
-// Sums of the per-example gradients over clipping units of `unit` consecutive examples, and their squared norms:
-// the clip-weighted kernel with factor 1 and one example range per unit (K runs over the unit's examples and
-// positions), whose slices the per-example slice-sum kernel then treats as "examples".
-dp_status launch_conv_units(const Geo &g, int unit, const void *x, const void *dy, float *out_w, float *out_b,
-                            size_t out_stride, float *sqnorm, void *ws, hipStream_t s)
-{
-    const int mode = out_w ? MODE_MATERIALISE : MODE_NORM;
-    if (conv3x3_applicable(g, MODE_WEIGHTED))
-        return launch_conv3x3(g, mode, x, dy, out_w, out_stride, sqnorm, nullptr, 0.0f, ws, s, unit);
-    return launch_conv_impl(g, mode, x, dy, out_w, out_b, out_stride, sqnorm, nullptr, 0.0f, ws, s, unit);
-}
+                                  void *ws, hipStream_t s);
 
 dp_status launch_conv(const Geo &g, int mode, const void *x, const void *dy, float *out_w, float *out_b,
                       size_t out_stride, float *sqnorm, const float *group_sqnorm, float clip_c, void *ws,
@@ -1927,13 +1902,12 @@ dp_status launch_conv(const Geo &g, int mode, const void *x, const void *dy, flo
 
 static dp_status launch_conv_impl(const Geo &g, int mode, const void *x, const void *dy, float *out_w, float *out_b,
                                   size_t out_stride, float *sqnorm, const float *group_sqnorm, float clip_c,
-                                  void *ws, hipStream_t s, int unit)
+                                  void *ws, hipStream_t s)
 {
-    // unit > 0: `mode` says whether the unit sums are stored; the kernel that runs is the weighted one
-    const FullPlan f = unit ? unit_plan(g, unit) : full_plan(g, mode);
-    const bool weighted = mode == MODE_WEIGHTED || unit > 0;
+    const FullPlan f = full_plan(g, mode);
+    const bool weighted = mode == MODE_WEIGHTED;
     ConvArgs a;
-    a.unit_major = unit ? unit / f.ex_per_split : 0;
+    a.unit = g.unit; a.slice_ex = f.slice_ex;
     a.x = x; a.dy = dy; a.x_tab = g.x_tab; a.dy_tab = g.dy_tab;
     a.n = g.n; a.cin = g.cin; a.cout = g.cout; a.h = f.h; a.w = f.w; a.kh = g.kh; a.kw = g.kw;
     a.stride = g.stride; a.pad = g.pad; a.oh = f.oh; a.ow = f.ow;
@@ -1950,15 +1924,11 @@ static dp_status launch_conv_impl(const Geo &g, int mode, const void *x, const v
     const int tiles = f.tiles_m * f.tiles_n;
     char *w = static_cast<char *>(ws);
     a.partials = nullptr;
-    const size_t unit_partials = (size_t)tiles * f.nacc * FIX_PARTS;      // per unit, from the slice-sum kernel
     if (!weighted) {
         a.partials = reinterpret_cast<float *>(w);
         w += align16(norm_partials(g, f) * sizeof(float));
-    } else if (unit) {
-        a.partials = reinterpret_cast<float *>(w);
-        w += align16((size_t)(g.n / unit) * unit_partials * sizeof(float));
     }
-    a.ws_part = (f.ksplit > 1 || unit) ? reinterpret_cast<float *>(w) : nullptr;
+    a.ws_part = f.ksplit > 1 ? reinterpret_cast<float *>(w) : nullptr;
     long long total;
     if (weighted) total = (long long)tiles * f.ksplit;
     else total = (long long)((g.n + f.ex_per_wg - 1) / f.ex_per_wg) * tiles * f.ksplit;
@@ -1999,18 +1969,6 @@ static dp_status launch_conv_impl(const Geo &g, int mode, const void *x, const v
     dp_status st = submit_main<ConvArgs>(fn, a, blocks, (f.shape == T256x128 || f.shape == T256rows) ? 512 : THREADS, lds_bytes, s, "conv_contract");
     if (st != DP_OK) return st;
     // what follows the main kernel: at once, or after the grouped launches of a batch call
-    if (unit) {
-        // every unit's slice is finished like an unsliced example: stored (if wanted) and squared
-        ConvArgs u = a;
-        u.n = g.n / unit; u.ksplit = a.unit_major;
-        const unsigned fix_blocks = (unsigned)((size_t)u.n * unit_partials);
-        const void *fix = (f.shape == T64) ? fixup_of<2, 2, 1, 1>(false, bias) : fixup_of<2, 2, 2, 2>(false, bias);
-        st = submit_kernel<ConvArgs>(TIER_POST, fix, u, fix_blocks, THREADS, 0, s, "conv_fixup");
-        if (st != DP_OK || !sqnorm) return st;
-        const float *partials = a.partials;
-        const int units = u.n, per = (int)unit_partials;
-        return submit_post([=]() -> dp_status { return launch_sum_partials(partials, units, per, sqnorm, s); });
-    }
     if (f.ksplit > 1) {
         const unsigned fix_blocks = (unsigned)(f.groups * f.nacc * FIX_PARTS);
         const void *fix = (f.shape == T64) ? fixup_of<2, 2, 1, 1>(weighted, bias) : fixup_of<2, 2, 2, 2>(weighted, bias);
@@ -2018,7 +1976,7 @@ static dp_status launch_conv_impl(const Geo &g, int mode, const void *x, const v
         if (st != DP_OK) return st;
     }
     if (weighted || !sqnorm) return DP_OK;
-    const int per_example = (int)norm_partials_per_example(f), n = g.n;
+    const int per_example = (int)norm_partials_per_example(f), n = g.n / g.unit;
     const float *partials = a.partials;
     return submit_post([=]() -> dp_status { return launch_sum_partials(partials, n, per_example, sqnorm, s); });
 }

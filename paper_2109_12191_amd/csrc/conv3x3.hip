@@ -50,8 +50,8 @@ struct C3Args {
     int ksplit, chunks_per_split;     // per-example mode: K slices
     int ex_per_split;                 // weighted mode: examples per workgroup (ksplit = example ranges)
     int variant;                      // which body conv3x3_any_kernel runs for this layer (C3_ANY_* below)
-    int unit_major;                   // weighted mode: every example range keeps its own result (clipping units): the
-                                      // slices always go to the workspace, ordered (range, tile)
+    int rows, unit;                   // per-example modes: rows of results, examples of each (Geo::unit)
+    int slice_ex;                     // per-example mode, sliced: > 0: the slices are ranges of this many examples of a unit
 };
 
 constexpr int odd16(int bytes) { return ((bytes / 16) | 1) * 16; }
@@ -209,15 +209,16 @@ __device__ __forceinline__ void conv3x3_body(const C3Args &a, const unsigned bid
     // consecutive hardware workgroup ids rotate over the 8 XCDs; give each XCD a run of
     // consecutive logical ids (the slices and tiles of the same examples share its L2)
     const int tiles = a.tiles_co * a.tiles_ci;
-    const int total = (WEIGHTED ? 1 : a.n) * tiles * a.ksplit;
+    const int total = (WEIGHTED ? 1 : a.rows) * tiles * a.ksplit;
     const int per_xcd = (total + 7) >> 3;
     const int wg = (int)(bid & 7u) * per_xcd + (int)(bid >> 3);
     if (wg >= total) return;
     const int split = wg % a.ksplit;
     const int unit = wg / a.ksplit;                   // (example, tile); weighted: tile
-    const int i_first = WEIGHTED ? split * a.ex_per_split : unit / tiles;
-    const int i_last = WEIGHTED ? min(a.n, i_first + a.ex_per_split) : i_first + 1;
-    const int tile = WEIGHTED ? unit : unit - i_first * tiles;
+    const int result = WEIGHTED ? 0 : unit / tiles;   // row of results
+    const int i_first = WEIGHTED ? split * a.ex_per_split : result * a.unit + (MODE == C3_SLICED ? split * a.slice_ex : 0);
+    const int i_last = WEIGHTED ? min(a.n, i_first + a.ex_per_split) : i_first + (MODE == C3_SLICED ? max(1, a.slice_ex) : a.unit);
+    const int tile = unit - result * tiles;
     const int tco = tile / a.tiles_ci, tci = tile - tco * a.tiles_ci;
     const int co0 = tco * 64, ci0 = tci * 64;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -238,7 +239,7 @@ __device__ __forceinline__ void conv3x3_body(const C3Args &a, const unsigned bid
 #pragma unroll
         for (int r = 0; r < 16; ++r) acc[t][r] = 0.0f;
 
-    const int c_begin = WEIGHTED ? 0 : split * a.chunks_per_split;
+    const int c_begin = WEIGHTED || MODE == C3_FULL || a.slice_ex ? 0 : split * a.chunks_per_split;
     const int c_end = WEIGHTED ? a.chunks : min(a.chunks, c_begin + a.chunks_per_split);
 
     for (int i = i_first; i < i_last; ++i) {
@@ -466,11 +467,11 @@ __device__ __forceinline__ void conv3x3_body(const C3Args &a, const unsigned bid
     }   // examples
 
     if constexpr (MODE == C3_FULL) {
-        c3_epilogue(acc, a, i_first, unit, co0, ci0, wm, wn, lane, red, lds);
-    } else if (WEIGHTED && a.ksplit == 1 && !a.unit_major) {
+        c3_epilogue(acc, a, result, unit, co0, ci0, wm, wn, lane, red, lds);
+    } else if (WEIGHTED && a.ksplit == 1) {
         c3_add_to_accumulator(acc, a, co0, ci0, wm, wn, lane, lds);
     } else {
-        const size_t slot = (WEIGHTED && a.unit_major) ? (size_t)split * tiles + tile : (size_t)unit * a.ksplit + split;
+        const size_t slot = (size_t)unit * a.ksplit + split;
         float *mine = a.ws_part + slot * (9 * 16 * C3_THREADS);
 #pragma unroll
         for (int t = 0; t < 9; ++t)
@@ -670,6 +671,7 @@ struct C3Plan {
     int tiles_co, tiles_ci, chunks;
     int ksplit, chunks_per_split;      // per-example modes: K slices; weighted: example ranges
     int ex_per_split;                  // weighted
+    int slice_ex;                      // per-example modes: examples per slice of a clipping unit, or 0
 };
 
 int rows_of_width(int ow, int stride)
@@ -701,6 +703,7 @@ C3Plan c3_plan(const Geo &g, int mode)
     p.ksplit = 1;
     p.chunks_per_split = p.chunks;
     p.ex_per_split = g.n;
+    p.slice_ex = 0;
     const long long tiles = (long long)p.tiles_co * p.tiles_ci;
     // inside a batch call: chunks per workgroup to plan for (a chunk here is about eight 128x128x64 chunks of work, but
     // slices cost a second pass over partial blocks: only very long walks are cut)
@@ -727,7 +730,19 @@ C3Plan c3_plan(const Geo &g, int mode)
         p.ksplit = (g.n + p.ex_per_split - 1) / p.ex_per_split;
         return p;
     }
-    const long long units = (long long)g.n * tiles;
+    const long long units = (long long)(g.n / g.unit) * tiles;
+    if (g.unit > 1) {
+        // clipping units are sliced by examples; few blocks that walk long are cut too (ResNet-50, 8 units of 4 examples: the three
+        // 56-wide layers are 24 blocks of 56 chunks, 0.6 ms where the rest of the phase needs as long together)
+        const long long walk = (long long)p.chunks * g.unit;
+        long long want = 1;
+        if (crowd ? walk > 3 * tgt : units < 128) want = crowd ? (walk + tgt - 1) / tgt : (128 + units - 1) / units;
+        if (units < 64 && walk >= 16 && want < 64 / units) want = 64 / units;
+        int k = 1;
+        while (k < g.unit && (k < want || g.unit % k)) ++k;                       // slices of equal size
+        if (k > 1) { p.ksplit = k; p.slice_ex = g.unit / k; }
+        return p;
+    }
     // (measured in the replayed step, where other streams fill the compute units a narrow launch leaves free: the 56-wide
     // layers run 14 chunks per workgroup unsliced rather than in three slices + a slice-sum launch)
     if (p.chunks > 1 && (crowd ? p.chunks > 3 * tgt : units < 128)) {
@@ -839,7 +854,7 @@ static size_t conv3x3_ws_bytes_plan(const Geo &g, int mode)
     const size_t tiles = (size_t)p.tiles_co * p.tiles_ci;
     const size_t split = c3_align16(c3_split_bytes(g));
     if (mode == MODE_WEIGHTED) return split + (p.ksplit > 1 ? tiles * p.ksplit * 9 * 16 * C3_THREADS * sizeof(float) : 0);
-    const size_t units = (size_t)g.n * tiles;
+    const size_t units = (size_t)(g.n / g.unit) * tiles;
     size_t b = c3_align16(units * c3_partials_per_unit(p) * sizeof(float));
     if (p.ksplit > 1) b += units * p.ksplit * 9 * 16 * C3_THREADS * sizeof(float);
     return b + split;
@@ -872,29 +887,14 @@ const char *conv3x3_variant_name(const Geo &g, int mode)
     return names.v[g.stride == 2 ? 1 : 0][mode == MODE_WEIGHTED ? 1 : 0][slot];
 }
 
-// workspace of a call with clipping units: [units, tiles, 36] partial norms, then one accumulator block per (unit, tile)
-size_t conv3x3_unit_ws_bytes(const Geo &g, int unit)
-{
-    const size_t tiles = (size_t)((g.cout + 63) / 64) * ((g.cin + 63) / 64), units = (size_t)(g.n / unit);
-    return c3_align16(units * tiles * 9 * C3_FIX_PARTS * sizeof(float)) + units * tiles * 9 * 16 * C3_THREADS * sizeof(float);
-}
-
-size_t conv3x3_unit_norm_partial_count(const Geo &g)
-{
-    return (size_t)((g.cout + 63) / 64) * ((g.cin + 63) / 64) * 9 * C3_FIX_PARTS;
-}
-
 dp_status launch_conv3x3(const Geo &g, int mode, const void *x, const void *dy, float *out_w, size_t out_stride,
-                         float *sqnorm, const float *group_sqnorm, float clip_c, void *ws, hipStream_t s, int unit)
+                         float *sqnorm, const float *group_sqnorm, float clip_c, void *ws, hipStream_t s)
 {
-    // unit > 0 (stride 1 only): sums over clipping units.  The clip-weighted kernel runs with factor 1 and one
-    // example range per unit; the per-example slice-sum kernel then finishes every unit's block like an example's.
-    const bool weighted = mode == MODE_WEIGHTED || unit > 0;
-    C3Plan p = c3_plan(g, weighted ? MODE_WEIGHTED : mode);
-    if (unit) { p.ex_per_split = unit; p.ksplit = g.n / unit; }
+    const bool weighted = mode == MODE_WEIGHTED;
+    const C3Plan p = c3_plan(g, mode);
     C3Args a;
     a.variant = -1;
-    a.unit_major = unit ? 1 : 0;
+    a.rows = g.n / g.unit; a.unit = g.unit; a.slice_ex = p.slice_ex;
     a.x = x; a.dy = dy; a.x_tab = g.x_tab; a.dy_tab = g.dy_tab;
     a.out_w = out_w;
     a.out_stride = out_stride ? out_stride : g.pw;
@@ -904,18 +904,15 @@ dp_status launch_conv3x3(const Geo &g, int mode, const void *x, const void *dy, 
     a.chunks = p.chunks; a.ksplit = p.ksplit; a.chunks_per_split = p.chunks_per_split;
     a.ex_per_split = p.ex_per_split;
     const size_t tiles = (size_t)p.tiles_co * p.tiles_ci;
-    const size_t units = weighted ? tiles : (size_t)g.n * tiles;
+    const size_t units = weighted ? tiles : (size_t)a.rows * tiles;
     char *w = static_cast<char *>(ws);
     a.partials = nullptr;
     if (!weighted) {
         a.partials = reinterpret_cast<float *>(w);
         w += c3_align16(units * c3_partials_per_unit(p) * sizeof(float));
-    } else if (unit) {
-        a.partials = reinterpret_cast<float *>(w);
-        w += c3_align16((size_t)(g.n / unit) * tiles * 9 * C3_FIX_PARTS * sizeof(float));
     }
-    a.ws_part = (p.ksplit > 1 || unit) ? reinterpret_cast<float *>(w) : nullptr;
-    if (p.ksplit > 1 || unit) w += units * p.ksplit * 9 * 16 * C3_THREADS * sizeof(float);
+    a.ws_part = p.ksplit > 1 ? reinterpret_cast<float *>(w) : nullptr;
+    if (p.ksplit > 1) w += units * p.ksplit * 9 * 16 * C3_THREADS * sizeof(float);
     const long long total = (long long)units * p.ksplit;
     const unsigned blocks = (unsigned)(((total + 7) / 8) * 8);
     dp_status st;
@@ -949,17 +946,6 @@ dp_status launch_conv3x3(const Geo &g, int mode, const void *x, const void *dy, 
     }
     if (st != DP_OK) return st;
     // what follows the main kernel: at once, or after the grouped launch of a batch call
-    if (unit) {
-        C3Args u = a;
-        u.n = g.n / unit; u.ksplit = 1;
-        const size_t per_unit = tiles * 9 * C3_FIX_PARTS;
-        st = submit_kernel<C3Args>(TIER_POST, reinterpret_cast<const void *>(&conv3x3_fixup_kernel<false>), u,
-                                   (unsigned)((size_t)u.n * per_unit), C3_THREADS, 0, s, "conv3x3_fixup");
-        if (st != DP_OK || !sqnorm) return st;
-        const float *partials = a.partials;
-        const int n_units = u.n, per = (int)per_unit;
-        return submit_post([=]() -> dp_status { return launch_sum_partials(partials, n_units, per, sqnorm, s); });
-    }
     if (p.ksplit > 1) {
         const unsigned fix_blocks = (unsigned)(units * 9 * C3_FIX_PARTS);
         const void *fix = weighted ? reinterpret_cast<const void *>(&conv3x3_fixup_kernel<true>)
@@ -968,7 +954,7 @@ dp_status launch_conv3x3(const Geo &g, int mode, const void *x, const void *dy, 
         if (st != DP_OK) return st;
     }
     if (weighted || !sqnorm) return DP_OK;
-    const int n = g.n, per_example = p.tiles_co * p.tiles_ci * (int)c3_partials_per_unit(p);
+    const int n = a.rows, per_example = p.tiles_co * p.tiles_ci * (int)c3_partials_per_unit(p);
     const float *partials = a.partials;
     return submit_post([=]() -> dp_status { return launch_sum_partials(partials, n, per_example, sqnorm, s); });
 }

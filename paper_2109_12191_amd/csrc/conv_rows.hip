@@ -50,6 +50,7 @@ struct RowsArgs {
     float *partials;                // [n][tiles_m * tiles_n]
     int n, cin, cout, h, w, oh, ow;
     int tiles_m, tiles_n, ex_per_wg;
+    int unit;                       // Geo::unit
     int q;                          // waves that share the runs of a kernel row
     int rows, chunks;               // output rows per chunk, chunks per example
     int rpr;                        // runs per output row
@@ -187,7 +188,9 @@ __global__ void __launch_bounds__(64 * K * cr_qmax(K)) conv_rows_kernel(const Gr
     typedef std::integral_constant<int, NI> wide;
 
     fetch(i_begin, 0);
+    int in_unit = 0;
     for (int i = i_begin; i < i_end; ++i) {
+        if (in_unit == 0)
 #pragma unroll
         for (int m = 0; m < 2; ++m) {
             bsum[m] = 0.0f;
@@ -212,6 +215,9 @@ __global__ void __launch_bounds__(64 * K * cr_qmax(K)) conv_rows_kernel(const Gr
                 else multiply(one{}, one{}, runs);
             }
         }
+        if (++in_unit < a.unit) continue;              // the next example adds to the same block
+        in_unit = 0;
+        const int row_i = i / a.unit;
         // the block, 16 rows at a time: summed over q in order, squared, stored
         float ss = 0.0f;
 #pragma unroll
@@ -240,7 +246,7 @@ __global__ void __launch_bounds__(64 * K * cr_qmax(K)) conv_rows_kernel(const Gr
             }
             const int len = cn * K * K;
             for (int r = wave; r < min(16, cm - m * 16); r += nwaves) {
-                float *dst = a.out_w ? a.out_w + (size_t)i * a.out_stride_w + ((size_t)(m0 + m * 16 + r) * a.cin + n0) * (K * K) : nullptr;
+                float *dst = a.out_w ? a.out_w + (size_t)row_i * a.out_stride_w + ((size_t)(m0 + m * 16 + r) * a.cin + n0) * (K * K) : nullptr;
                 for (int t = lane; t < len; t += 64) {
                     const float v = epi[r * EP + t];
                     ss += v * v;
@@ -252,7 +258,7 @@ __global__ void __launch_bounds__(64 * K * cr_qmax(K)) conv_rows_kernel(const Gr
         if (a.bias && n0 == 0 && tid < cm) {
             const float v = sbias[tid];
             ss += v * v;
-            if (a.out_b) a.out_b[(size_t)i * a.out_stride_b + m0 + tid] = v;
+            if (a.out_b) a.out_b[(size_t)row_i * a.out_stride_b + m0 + tid] = v;
         }
         ss = wave_sum(ss);
         if (lane == 0) red[wave] = ss;
@@ -260,7 +266,7 @@ __global__ void __launch_bounds__(64 * K * cr_qmax(K)) conv_rows_kernel(const Gr
         if (tid == 0) {
             float t = 0.0f;
             for (int k = 0; k < nwaves; ++k) t += red[k];
-            a.partials[(size_t)i * tiles + tile] = t;
+            a.partials[(size_t)row_i * tiles + tile] = t;
         }
     }
 }
@@ -286,7 +292,7 @@ RowsPlan rows_plan(const Geo &g, int max_rows = 64)
     p.rpr = (g.ow + 3) / 4;
     p.xp = CR_LEFT + (g.w + 3) / 4 * 4;
     const int lc = g.cout < CR_CH ? g.cout : CR_CH, ln = g.cin < CI ? g.cin : CI;      // channels that are staged
-    const double wgs = (double)g.n * p.tiles_m * p.tiles_n;
+    const double wgs = (double)(g.n / g.unit) * p.tiles_m * p.tiles_n;
     double best = 0.0;
     for (int q = 1; q <= cr_qmax(K); q *= 2)
         for (int rows = 1; rows <= g.oh && rows <= max_rows; ++rows) {
@@ -318,7 +324,7 @@ RowsPlan rows_plan(const Geo &g, int max_rows = 64)
     if (!p.ok) return p;
     // several examples in a row where there are far more (example, block) pairs than workgroups that run at a time
     int e = (int)(wgs / 4096.0);
-    p.ex_per_wg = e < 1 ? 1 : e > 8 ? 8 : e;
+    p.ex_per_wg = g.unit * (e < 1 ? 1 : e > 8 ? 8 : e);
     return p;
 }
 
@@ -343,7 +349,7 @@ bool conv_rows_applicable(const Geo &g, int mode)
 
 size_t conv_rows_norm_partial_count(const Geo &g) { return (size_t)((g.cout + CR_CH - 1) / CR_CH) * ((g.cin + cr_cin(g.kh) - 1) / cr_cin(g.kh)); }
 
-size_t conv_rows_ws_bytes(const Geo &g) { return cr_align16((size_t)g.n * conv_rows_norm_partial_count(g) * sizeof(float)); }
+size_t conv_rows_ws_bytes(const Geo &g) { return cr_align16((size_t)(g.n / g.unit) * conv_rows_norm_partial_count(g) * sizeof(float)); }
 
 const char *conv_rows_variant_name(const Geo &g)
 {
@@ -364,7 +370,7 @@ dp_status launch_conv_rows(const Geo &g, const void *x, const void *dy, float *o
     a.out_stride_b = out_stride ? out_stride : g.pb;
     a.partials = static_cast<float *>(ws);
     a.n = g.n; a.cin = g.cin; a.cout = g.cout; a.h = g.h; a.w = g.w; a.oh = g.oh; a.ow = g.ow;
-    a.tiles_m = p.tiles_m; a.tiles_n = p.tiles_n; a.ex_per_wg = p.ex_per_wg; a.q = p.q;
+    a.tiles_m = p.tiles_m; a.tiles_n = p.tiles_n; a.ex_per_wg = p.ex_per_wg; a.unit = g.unit; a.q = p.q;
     a.rows = p.rows; a.chunks = p.chunks; a.rpr = p.rpr; a.xp = p.xp; a.cha = p.cha; a.chx = p.chx; a.tm = p.tm; a.tn = p.tn;
     a.bias = g.has_bias ? 1 : 0;
     const void *fn = g.kh == 1 ? rows_fn<1>(g.stride) : g.kh == 3 ? rows_fn<3>(g.stride) : rows_fn<5>(g.stride);
@@ -378,7 +384,7 @@ dp_status launch_conv_rows(const Geo &g, const void *x, const void *dy, float *o
     const dp_status st = submit_main<RowsArgs>(fn, a, (unsigned)((total + 7) / 8 * 8), (unsigned)(64 * g.kh * p.q), p.lds, s, "conv_rows");
     if (st != DP_OK || !sqnorm) return st;
     const float *parts = a.partials;
-    const int n = g.n, count = (int)conv_rows_norm_partial_count(g);
+    const int n = g.n / g.unit, count = (int)conv_rows_norm_partial_count(g);
     return submit_post([=]() -> dp_status { return launch_sum_partials(parts, n, count, sqnorm, s); });
 }
 

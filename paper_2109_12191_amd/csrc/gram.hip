@@ -206,6 +206,7 @@ size_t gram_align16(size_t b) { return (b + 15) & ~(size_t)15; }
 
 bool gram_norm_applicable(const Geo &g, int mode)
 {
+    if (g.unit > 1) return false;                    // (the Gram identity is for one example)
     if (mode != MODE_NORM || !g.bf16 || g.has_bias) return false;
     const bool one = g.kh == 1 && g.kw == 1 && g.stride == 1 && g.pad == 0;
     const bool three = g.kh == 3 && g.kw == 3 && g.pad == 1 && (g.stride == 1 || g.stride == 2);

@@ -32,6 +32,9 @@ struct Geo {
     // example addresses and example i starts at entry i * k (the micro-steps of a step, each in tensors of its own, contracted in
     // one launch; k > 1: the unit of a dense layer whose units are read as examples).
     int x_tab, dy_tab;
+    // Per-example calls of convolutions: consecutive examples whose gradients are added up to one row of results (clipping units; K
+    // then runs over the positions of all of them).  1 otherwise; n is a multiple of it.
+    int unit;
 };
 
 // Contraction modes of the conv / dense kernels.
@@ -50,16 +53,11 @@ bool conv3x3_applicable(const Geo &g, int mode);
 size_t conv3x3_ws_bytes(const Geo &g, int mode);
 const char *conv3x3_variant_name(const Geo &g, int mode);
 dp_status launch_conv3x3(const Geo &g, int mode, const void *x, const void *dy, float *out_w, size_t out_stride,
-                         float *sqnorm, const float *group_sqnorm, float clip_c, void *ws, hipStream_t s, int unit = 0);
-size_t conv3x3_unit_ws_bytes(const Geo &g, int unit);
+                         float *sqnorm, const float *group_sqnorm, float clip_c, void *ws, hipStream_t s);
 
-// Sums of the per-example gradients over clipping units of `unit` consecutive examples (n a multiple of unit), and
-// their squared norms [n / unit]; out_w / out_b rows are units.
-size_t conv_unit_ws_bytes(const Geo &g, int unit);
-dp_status launch_conv_units(const Geo &g, int unit, const void *x, const void *dy, float *out_w, float *out_b,
-                            size_t out_stride, float *sqnorm, void *ws, hipStream_t s);
-size_t conv_unit_norm_partial_count(const Geo &g, int unit);
-size_t conv3x3_unit_norm_partial_count(const Geo &g);
+// Clipping units of normalisation layers: sums of the per-example gradients over `unit` consecutive examples (n a multiple of
+// unit), and their squared norms [n / unit]; out_w / out_b rows are units.  (Convolutions: Geo::unit; dense layers read
+// a unit as one example.)
 const float *gn_unit_partials(const Geo &g, const void *ws);
 size_t gn_unit_norm_partial_count(const Geo &g);
 size_t gn_unit_ws_bytes(const Geo &g, int unit);

@@ -277,11 +277,14 @@ dp_status launch_stem(const Geo &g, const void *x, const void *dy, float *out_w,
     dp_status st = submit_main<StemArgs>(fn, a, (unsigned)(g.n * a.slices), ST_THREADS,
                                          stem_lds_bytes(g), s, "conv_stem");
     if (st != DP_OK) return st;
+    // the ranges of a clipping unit's examples lie one after the other: to the second kernel they are those of one example
+    const int n = g.n / g.unit;
+    a.n = n;
+    a.slices *= g.unit;
     st = submit_kernel<StemArgs>(TIER_POST, reinterpret_cast<const void *>(&conv_stem_fixup_kernel), a,
-                                 (unsigned)(g.n * ST_FIX_BLOCKS), 256, 0, s, "conv_stem_fixup");
+                                 (unsigned)(n * ST_FIX_BLOCKS), 256, 0, s, "conv_stem_fixup");
     if (st != DP_OK || !sqnorm) return st;
     const float *parts = a.partials;
-    const int n = g.n;
     return submit_post([=]() -> dp_status { return launch_sum_partials(parts, n, ST_FIX_BLOCKS, sqnorm, s); });
 }
 

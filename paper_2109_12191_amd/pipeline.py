@@ -98,7 +98,7 @@ class _Plan:
         # launch (at most 16 per launch): per phase a micro-step is a dozen launches, not a hundred.
         self.variant = [(B.dp_kernel_variant(d, B.DP_WS_PER_EXAMPLE_GRAD | B.DP_VARIANT_SHARED |
                                              (B.DP_VARIANT_MATERIALISE if form == "materialise" else 0)),
-                         B.dp_kernel_variant(d, B.DP_WS_RECOMPUTE | B.DP_VARIANT_SHARED) if form == "recompute" or ps.clip_unit > 1 else "")
+                         B.dp_kernel_variant(d, B.DP_WS_RECOMPUTE | B.DP_VARIANT_SHARED) if form == "recompute" else "")
                         for d, form in zip(self.descs, self.form)]
         self.partials = [B.PartialTable(self.ws[c], [1] * L, ps.group_of_layer)
                          for c in range(copies)]
@@ -121,9 +121,9 @@ class _Plan:
         constant pointer arrays)."""
         ps = self.ps
         by_name = {}
-        family = "conv3x3_rows<bf16,all widths,%s>" % ("weighted" if use else "per_example")
+        family = "conv3x3_rows<bf16,all widths,%s>" % ("weighted" if use == 1 else "per_example")
         for li in layer_ids:
-            key = self.variant[li][1 if use == 2 else use]      # same name, same kernel: storing and norm-only layers share a launch
+            key = self.variant[li][1 if use == 1 else 0]      # same name, same kernel: storing and norm-only layers share a launch
             if ps.batching == "all":
                 key = "all layers"
             elif key.startswith("conv3x3_rows<"):
@@ -139,7 +139,7 @@ class _Plan:
                 part = ids[k: k + width]
                 name = key.split("|")[0]
                 if len(part) == 1:           # a single layer is planned as a launch of its own
-                    name = B.dp_kernel_variant(self.descs[part[0]], B.DP_WS_RECOMPUTE if use else (
+                    name = B.dp_kernel_variant(self.descs[part[0]], B.DP_WS_RECOMPUTE if use == 1 else (
                         B.DP_WS_PER_EXAMPLE_GRAD | (B.DP_VARIANT_MATERIALISE if self.form[part[0]] == "materialise" else 0)))
                 g = dict(layers=part, name=name, conv=all(self.layers[i].kind == "conv" for i in part))
                 g["batch"] = [B.LayerBatch([self.descs[i] for i in part], [self.ws[c][i] for i in part],
@@ -452,8 +452,7 @@ class PrivatiseStep:
             if plan.b_done[c] is not None:            # this copy's previous clipped sum has finished
                 for ev in plan.b_done[c]:
                     st.wait_event(ev)
-        # unit sums and their norms: one batch call per kernel variant of the clip-weighted form (the kernels
-        # that run), dealt to the side streams
+        # unit sums and their norms: one batch call per kernel variant, dealt to the side streams
         for grp in plan.groups_u:
             bt = grp["batch"][c]
             B.dp_unit_grad_batch(bt, self.clip_unit, bt.fill("x", [x[i] for i in grp["layers"]]), bt.fill("dy", [dy[i] for i in grp["layers"]]),
