@@ -36,6 +36,7 @@
 #include "group.h"
 #include "pieces.h"
 
+#include <algorithm>
 #include <atomic>
 #include <cstdio>
 #include <type_traits>
@@ -1754,7 +1755,7 @@ size_t conv_ws_bytes(const Geo &g, int mode)
 static size_t conv_ws_bytes_mode(const Geo &g, int mode)
 {
     if (stem_applicable(g, mode)) return stem_ws_bytes(g);
-    if (conv_rows_applicable(g, mode)) return conv_rows_ws_bytes(g);
+    if (conv_rows_applicable(g, mode) && g.unit > 1) return conv_rows_ws_bytes(g);
     if (gram_norm_applicable(g, mode)) return gram_ws_bytes(g);
     if (conv3x3_applicable(g, mode)) return conv3x3_ws_bytes(g, mode);
     PackPlan pp;
@@ -1768,7 +1769,9 @@ static size_t conv_ws_bytes_mode(const Geo &g, int mode)
     size_t b = 0;
     if (mode != MODE_WEIGHTED) b += align16(norm_partials(g, f) * sizeof(float));
     if (f.ksplit > 1) b += f.part_floats * sizeof(float);
-    return b;
+    // The raw-row fp32 kernel needs a few kilobytes.  What is reported stays at least what the general kernel needs: callers size
+    // buffers by it, and the entry point with built-in scratch refuses layers by it.
+    return conv_rows_applicable(g, mode) ? std::max(b, conv_rows_ws_bytes(g)) : b;
 }
 
 size_t conv_norm_partial_count(const Geo &g, int mode)
