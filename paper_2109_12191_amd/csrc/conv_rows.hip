@@ -1,4 +1,4 @@
-// Per-example weight gradients of fp32 convolutions with square odd kernels (1, 3, 5; padding (k - 1) / 2, stride 1 or 2), H1 of
+// Per-example weight gradients of fp32 convolutions with square odd kernels (3, 5; padding (k - 1) / 2, stride 1 or 2), H1 of
 // the path, from raw image rows:
 //     dW_i[co, ci, kh, kw] = sum_{oh, ow} dY_i[co, oh, ow] * Xpad_i[ci, s oh + kh - p, s ow + kw - p].
 // What bounds these layers is the fp32 matrix rate (157 TFLOP/s, 256 flop per cycle and compute unit): an im2col column per
@@ -340,7 +340,16 @@ template <int K> const void *rows_fn(int stride)
 bool conv_rows_applicable(const Geo &g, int mode)
 {
     if (mode == MODE_WEIGHTED || g.bf16) return false;
-    if (g.kh != g.kw || (g.kh != 1 && g.kh != 3 && g.kh != 5) || g.pad != (g.kh - 1) / 2 || g.stride < 1 || g.stride > 2) return false;
+    if (g.kh != g.kw || (g.kh != 3 && g.kh != 5) || g.pad != (g.kh - 1) / 2 || g.stride < 1 || g.stride > 2) return false;
+    // Blocks are not sliced along K, so a launch of few of them walks long while the general kernel cuts K; and a 5 x 5 block's
+    // epilogue (25 taps summed over the waves) wants a long K, or a stride that the general kernel gathers slowly.  us per call and
+    // noise, general / this: 3x3, 25 blocks, 20 -> 19 on 42 x 31: 123 / 164; 54 blocks, 22 -> 74 on 41 x 56: 103 / 166; 64 blocks, 64 ->
+    // 64 on 56 x 56: faster (above); 120 blocks, 25 -> 80 on 10 x 28 stride 2: 43 / 41.  5x5: 528 blocks, 86 -> 58 on 11 x 31: 114 / 170;
+    // 720, 59 -> 93 on 18 x 54: 314 / 412; 208, 52 -> 54 on 44 x 56: 254 / 225; stride 2, 304, 19 -> 126 onto 15 x 20: 118 / 152;
+    // 230, 69 -> 19 onto 21 x 24: 287 / 217.  (1x1: no element is read by two taps; 51 / 95 at 108 -> 33 on 45 x 26.)
+    const double blocks = (double)(g.n / g.unit) * conv_rows_norm_partial_count(g);
+    const int S = g.oh * g.ow;
+    if (g.kh == 3 ? blocks < 64 : blocks < 200 || S < (g.stride == 2 ? 400 : 1900)) return false;
     // offsets inside an example (rows above and below the image included) fit 32 bits; quotients of the set-up stay exact
     if ((size_t)g.cin * (g.h + 8) * g.w >= ((size_t)1 << 30) || (size_t)g.cout * (g.oh + 64) * g.ow >= ((size_t)1 << 30)) return false;
     if (g.w > 4096 || (double)g.n * conv_rows_norm_partial_count(g) >= 1.0e9) return false;
@@ -373,7 +382,7 @@ dp_status launch_conv_rows(const Geo &g, const void *x, const void *dy, float *o
     a.tiles_m = p.tiles_m; a.tiles_n = p.tiles_n; a.ex_per_wg = p.ex_per_wg; a.unit = g.unit; a.q = p.q;
     a.rows = p.rows; a.chunks = p.chunks; a.rpr = p.rpr; a.xp = p.xp; a.cha = p.cha; a.chx = p.chx; a.tm = p.tm; a.tn = p.tn;
     a.bias = g.has_bias ? 1 : 0;
-    const void *fn = g.kh == 1 ? rows_fn<1>(g.stride) : g.kh == 3 ? rows_fn<3>(g.stride) : rows_fn<5>(g.stride);
+    const void *fn = g.kh == 3 ? rows_fn<3>(g.stride) : rows_fn<5>(g.stride);
     static std::atomic<bool> attr_done[3][2];           // zero-initialised; setting the attribute twice is harmless
     if (!attr_done[g.kh / 2][g.stride - 1].load()) {
         if (hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, 156 * 1024) != hipSuccess)

@@ -34,6 +34,7 @@ from . import binding as B
 # 16 / 32 / 64: 2606 / 2202 / 2174 against 11400 one by one.
 PHASE_BYTES = 2.6e9
 PHASE_EXAMPLES = 256           # and examples
+PHASE_EXAMPLES_STORED = 64     # micro-steps of one or two examples, which store every gradient (ResNet-50: 6.5 GB per copy)
 
 
 def _pad4(v: int) -> int:
@@ -53,7 +54,9 @@ class _Plan:
         self.layers = ps.layers
         L = len(self.layers)
         self.descs = [B.make_desc(l, self.n, wl.dtype) for l in self.layers]
-        self.form = [ps._choose(l, ps._mode, self.n) for l in self.layers]
+        # the forms of a micro-step of its own: the recomputing form rounds scaled bf16 operands once more, and how many
+        # micro-steps share a phase must not decide about precision
+        self.form = [ps._choose(l, ps._mode, wl.n) for l in self.layers]
         # columns of the per-example gradient matrix: the materialised layers in the order they lie in the parameter vector
         self.col_w, self.col_b = [0] * L, [0] * L
         segments = []                              # runs of columns of one clipping group that also lie together in acc
@@ -245,7 +248,6 @@ class PrivatiseStep:
         self.n_groups = wl.n_groups
 
         # flat parameter vector: the layers that materialise in a micro-step of its own first, then the recomputed ones
-        # (a fixed layout: phases of several micro-steps may use other forms)
         form = [self._choose(l, mode, wl.n) for l in self.layers]
         order = [i for i in range(L) if form[i] == "materialise"] + [i for i in range(L) if form[i] == "recompute"]
         self.off_w = [0] * L
@@ -276,7 +278,8 @@ class PrivatiseStep:
         esize = 2 if wl.dtype == "bf16" else 4
         self._example_bytes = [b for l in self.layers for b in (l.x_bytes(esize), l.dy_bytes(esize))]
         per_micro_step = max(1, sum(self._example_bytes)) * wl.n
-        self._together = max(1, min(int(PHASE_BYTES // per_micro_step), PHASE_EXAMPLES // wl.n))    # micro-steps per phase, at most
+        self._together = max(1, min(int(PHASE_BYTES // per_micro_step),
+                                     (PHASE_EXAMPLES_STORED if wl.n <= 2 else PHASE_EXAMPLES) // wl.n))    # micro-steps per phase, at most
         self._plans = {}
         for size in {1} | set(self._phase_sizes(wl.accum)):
             self._plan(size)

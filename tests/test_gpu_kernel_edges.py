@@ -169,9 +169,9 @@ def test_segments_at_places_of_their_own():
 
 # ---- fp32 convolutions from raw rows: channels around the 16 and 32 of a block, output rows that are no multiple of four, one row,
 # a kernel larger than the image, several chunks of rows with a short last one, several examples per workgroup
-@pytest.mark.parametrize("cin,cout,h,w,k,stride,n", [(1, 1, 1, 1, 1, 1, 1), (16, 17, 5, 7, 1, 2, 3), (33, 32, 8, 8, 1, 1, 2), (3, 16, 9, 6, 3, 1, 2),
-                                                     (17, 33, 2, 1, 3, 1, 3), (32, 31, 57, 56, 3, 1, 1), (40, 24, 33, 35, 3, 2, 2), (64, 64, 7, 7, 3, 1, 2),
-                                                     (5, 40, 3, 2, 5, 1, 2), (18, 20, 45, 37, 5, 2, 2), (16, 16, 12, 14, 3, 1, 8200), (2, 3, 130, 260, 3, 2, 1)])
+@pytest.mark.parametrize("cin,cout,h,w,k,stride,n", [(1, 1, 1, 1, 3, 1, 65), (16, 17, 5, 7, 3, 2, 65), (33, 32, 8, 8, 3, 1, 65), (3, 16, 9, 6, 3, 1, 70),
+                                                     (17, 33, 2, 1, 3, 1, 65), (32, 31, 57, 56, 3, 1, 65), (40, 24, 33, 35, 3, 2, 35), (64, 64, 7, 7, 3, 1, 20),
+                                                     (5, 40, 46, 43, 5, 1, 100), (18, 20, 45, 37, 5, 2, 100), (16, 16, 12, 14, 3, 1, 8200), (2, 3, 130, 260, 3, 2, 65)])
 def test_conv_f32_raw_rows_kernel(cin, cout, h, w, k, stride, n):
     layer = Layer("conv", cin, cout, h, w, k, k, stride, (k - 1) // 2, cout % 2 == 0)
     assert dp.dp_kernel_variant(dp.make_desc(layer, n, "f32"), dp.DP_WS_PER_EXAMPLE_GRAD).startswith("conv_rows<f32")
@@ -192,10 +192,68 @@ def test_conv_f32_raw_rows_kernel(cin, cout, h, w, k, stride, n):
 def test_conv_f32_raw_rows_kernel_keeps_what_is_not_finite_in_its_place():
     """An infinity in the last column of a row reaches the taps that read it and no other."""
     layer = Layer("conv", 2, 2, 3, 5, 3, 3, 1, 1, False)
-    x, dy = _inputs(layer, 1, 137, "f32")
+    x, dy = _inputs(layer, 64, 137, "f32")
+    assert dp.dp_kernel_variant(dp.make_desc(layer, 64, "f32"), dp.DP_WS_PER_EXAMPLE_GRAD).startswith("conv_rows<f32")
     dy[:] = 1.0
     x[0, 0, 1, 4] = np.inf
-    gw = _run_per_example(layer, x, dy, "f32")[0].reshape(2, 2, 3, 3)
+    gw = _run_per_example(layer, x, dy, "f32")[0].reshape(64, 2, 2, 3, 3)[0]
     want = np.ones((3, 3), bool)                  # the middle row, the last column: kw = 0 needs column 5 of dY, which is not there
     want[:, 0] = False
     assert np.array_equal(np.isinf(gw[0, 0]), want) and np.isfinite(gw[:, 1]).all() and np.isfinite(gw[:, 0, :, 0]).all()
+
+
+# ---- clipping units in the kernels of the per-example calls: one unit (sliced into ranges of its examples), units no power of two,
+# rows that end in a part chunk, enough units for the wide tile; every layer alone and all of one unit size in a batch call
+_UNIT_ROUTES = [
+    ("stem", conv(3, 64, 7, 2, 64), "bf16"), ("3x3 rows w56 sliced", conv(64, 64, 3, 1, 56), "bf16"), ("3x3 rows w14", conv(64, 70, 3, 1, 14), "bf16"),
+    ("3x3 rows s2", conv(64, 64, 3, 2, 28), "bf16"), ("3x3 gather", conv(13, 70, 3, 1, 13), "bf16"), ("1x1 stride 2", conv(512, 256, 1, 2, 14), "bf16"),
+    ("1x1 128x128 odd tail", conv(160, 136, 1, 1, 10), "bf16"), ("1x1 whole rows", conv(256, 512, 1, 1, 14), "bf16"),
+    ("1x1 odd rows bias", conv(97, 71, 1, 1, 7, bias=True), "bf16"), ("fp32 5x5 stride 2", Layer("conv", 18, 20, 45, 37, 5, 5, 2, 2, True), "f32"),
+]
+
+
+@pytest.mark.parametrize("unit,units", [(4, 1), (3, 2), (2, 66)])
+def test_units_in_the_per_example_kernels(unit, units):
+    n = unit * units
+    # 132 examples: the geometry with 256 x 128 tiles, whose rule asks for 128 of them
+    cases = _UNIT_ROUTES if n < 100 else [("1x1 256x128", conv(256, 256, 1, 1, 10), "bf16"), ("1x1 whole rows", conv(256, 512, 1, 1, 14), "bf16")]
+    runs = []
+    for name, layer, dtype in cases:
+        few = min(n, 2 * unit)                    # the oracle's few units, over and over
+        x, dy = _inputs(layer, few, 139, dtype)
+        mean_w, mean_b = oracle.unit_mean_grad(layer, x, dy, unit)
+        xd, dyd = (dev(np.concatenate([v] * (n // few)), dtype) for v in (x, dy))
+        d = dp.make_desc(layer, n, dtype)
+        ws = torch.empty(max(16, dp.dp_unit_workspace_bytes(d, unit)), dtype=torch.uint8, device="cuda:0")
+        row = (layer.pw + 3) // 4 * 4
+        runs.append((name, layer, BF16_TOL if dtype == "bf16" else F32_TOL, mean_w, mean_b, xd, dyd, d, ws, row))
+    for together in (False, True):
+        for group in ([runs] if together else [[r] for r in runs]):
+            gs = [torch.full((units, r[9] + (r[1].pb + 3) // 4 * 4), 7.0, device="cuda:0") for r in group]
+            sq, norms = (torch.full((len(group), units), -1.0, device="cuda:0") for _ in range(2))
+            for k, r in enumerate(group):
+                batch = dp.LayerBatch([r[7]], [r[8].data_ptr()], [r[8].numel()])
+                args = batch.ptrs([r[5].data_ptr()]), batch.ptrs([r[6].data_ptr()])
+                if not together:
+                    dp.dp_unit_grad(r[7], unit, r[5], r[6], gs[k], gs[k][:, r[9]:] if r[1].pb else None, sq[k], r[8], g_stride=gs[k].shape[1])
+                dp.dp_unit_grad_batch(batch, unit, *args, None, None, batch.ptrs([norms[k].data_ptr()]))
+            if together:
+                batch = dp.LayerBatch([r[7] for r in group], [r[8].data_ptr() for r in group], [r[8].numel() for r in group])
+                # one row length for all: the longest
+                pitch = max(g.shape[1] for g in gs)
+                gs = [torch.full((units, pitch), 7.0, device="cuda:0") for _ in group]
+                dp.dp_unit_grad_batch(batch, unit, batch.ptrs([r[5].data_ptr() for r in group]), batch.ptrs([r[6].data_ptr() for r in group]),
+                                      batch.ptrs([g.data_ptr() for g in gs]),
+                                      batch.ptrs([g[:, r[9]:].data_ptr() if r[1].pb else None for g, r in zip(gs, group)]),
+                                      batch.ptrs([sq[k].data_ptr() for k in range(len(group))]), g_stride=pitch)
+            torch.cuda.synchronize()
+            for k, (name, layer, tol, mean_w, mean_b, *_, row) in enumerate(group):
+                g = host(gs[k]) / unit
+                for u in range(units):
+                    ref_w, ref_b = mean_w[u % len(mean_w)], mean_b[u % len(mean_w)] if layer.pb else None
+                    assert_close(g[u, :layer.pw], ref_w, tol, f"{name} unit {u} dW")
+                    if layer.pb:
+                        assert_close(g[u, row:row + layer.pb], ref_b, tol, f"{name} unit {u} db")
+                    n2 = oracle.sqnorm(ref_w) + (oracle.sqnorm(ref_b) if layer.pb else 0.0)
+                    for got in (sq[k, u], norms[k, u]):
+                        assert np.isclose(float(got) / unit ** 2, n2, rtol=tol), (name, u)
