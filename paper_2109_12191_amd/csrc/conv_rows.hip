@@ -343,13 +343,18 @@ bool conv_rows_applicable(const Geo &g, int mode)
     if (g.kh != g.kw || (g.kh != 3 && g.kh != 5) || g.pad != (g.kh - 1) / 2 || g.stride < 1 || g.stride > 2) return false;
     // Blocks are not sliced along K, so a launch of few of them walks long while the general kernel cuts K; and a 5 x 5 block's
     // epilogue (25 taps summed over the waves) wants a long K, or a stride that the general kernel gathers slowly.  us per call and
-    // noise, general / this: 3x3, 25 blocks, 20 -> 19 on 42 x 31: 123 / 164; 54 blocks, 22 -> 74 on 41 x 56: 103 / 166; 64 blocks, 64 ->
-    // 64 on 56 x 56: faster (above); 120 blocks, 25 -> 80 on 10 x 28 stride 2: 43 / 41.  5x5: 528 blocks, 86 -> 58 on 11 x 31: 114 / 170;
+    // noise, general / this: 3x3, 25 blocks, 20 -> 19 on 42 x 31: 123 / 164; 54 blocks, 22 -> 74 on 41 x 56: 103 / 166; 256 blocks, 64 ->
+    // 64 on 56 x 56: faster (above).  5x5: 528 blocks, 86 -> 58 on 11 x 31: 114 / 170;
     // 720, 59 -> 93 on 18 x 54: 314 / 412; 208, 52 -> 54 on 44 x 56: 254 / 225; stride 2, 304, 19 -> 126 onto 15 x 20: 118 / 152;
     // 230, 69 -> 19 onto 21 x 24: 287 / 217.  (1x1: no element is read by two taps; 51 / 95 at 108 -> 33 on 45 x 26.)
     const double blocks = (double)(g.n / g.unit) * conv_rows_norm_partial_count(g);
     const int S = g.oh * g.ow;
-    if (g.kh == 3 ? blocks < 64 : blocks < 200 || S < (g.stride == 2 ? 400 : 1900)) return false;
+    // 3x3: ragged rows and channels waste its blocks of 16 and runs of four: 61 examples, 131 -> 61 on 21 x 20 stride 2: 64 / 97; 56, 121 ->
+    // 96 on 24 x 55: 670 / 832; 16, 64 -> 64 on 32 x 32 (64 blocks): 53 / 72.  Few output channels leave the general kernel's tiles
+    // of 64 empty: 43, 88 -> 14 on 40 x 29: 187 / 71.
+    const bool even = g.cin % 16 == 0 && g.cout % 16 == 0 && g.ow % 4 == 0 && blocks >= 256;
+    const bool narrow = g.stride == 1 && g.cout <= 16 && blocks >= 100;
+    if (g.kh == 3 ? !even && !narrow : blocks < 200 || S < (g.stride == 2 ? 400 : 1900)) return false;
     // offsets inside an example (rows above and below the image included) fit 32 bits; quotients of the set-up stay exact
     if ((size_t)g.cin * (g.h + 8) * g.w >= ((size_t)1 << 30) || (size_t)g.cout * (g.oh + 64) * g.ow >= ((size_t)1 << 30)) return false;
     if (g.w > 4096 || (double)g.n * conv_rows_norm_partial_count(g) >= 1.0e9) return false;
