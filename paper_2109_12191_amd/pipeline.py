@@ -295,6 +295,7 @@ class PrivatiseStep:
         self._addresses = None                   # example addresses of a step that is issued call by call
         self._last = 0                           # copy used by the most recent micro-step
         self._phases = 0                         # phases issued since begin_step
+        self._sum_plan = None                    # plan of the last of them
         self._group_sqnorm = list(self._plan(1).group_sqnorm)      # of the last micro-steps (one per copy)
         self._g_last = None
         self.graph = None
@@ -423,6 +424,7 @@ class PrivatiseStep:
         self.acc.zero_()
         self.micro_steps_done = 0
         self._phases = 0
+        self._sum_plan = None
         for plan in self._plans.values():
             plan.b_done = [None] * self.copies
 
@@ -434,7 +436,8 @@ class PrivatiseStep:
         streams they are spread over them, and phase A of the next micro-step does not wait for
         phase B of this one (they work on different buffer copies).  The clipped sums reach the
         accumulator in the same order on every run: each tensor is updated by one call per
-        phase, always issued on the same stream."""
+        phase, issued on the same stream by every phase of one plan and behind all clipped sums of the phase before where the
+        plan changes."""
         self._issue(self._plan(1), [x.data_ptr() for x, _ in inputs], [dy.data_ptr() for _, dy in inputs])
 
     def _issue(self, plan: _Plan, x: Sequence[int], dy: Sequence[int]):
@@ -481,6 +484,11 @@ class PrivatiseStep:
             B.dp_norms(plan.layer_sqnorm[c], self.group_of_layer_dev, L, plan.rows, self.n_groups, gsq, stream=ms)
         # ---- phase B
         sb = self.side_b
+        if self._sum_plan not in (None, plan):
+            # another plan deals the layers to other streams: what it still adds to a tensor comes first (by way of the main
+            # stream, as everywhere else: in a captured step side streams must not wait for one another in a ring)
+            self._drain()
+        self._sum_plan = plan
         for st in sb:
             st.wait_stream(main)
         if plan.p_mat:

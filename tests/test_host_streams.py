@@ -1,0 +1,185 @@
+"""CPU-only checks of how PrivatiseStep orders its calls: every library call is replaced by a record of the memory it reads and
+writes, streams and events by vector clocks, and any two calls that touch the same memory (one of them writing) have to be
+ordered by the streams and events they were issued with."""
+import pytest
+import torch
+
+import paper_2109_12191_amd as dp
+from paper_2109_12191_amd import pipeline
+from workloads import get_workload
+
+
+class _Order:
+    """Streams as vector clocks, and every access so far."""
+
+    def __init__(self):
+        self.clocks, self.log, self.clashes, self.waits = {}, [], [], set()
+
+    def ring(self, origin: int):
+        """Streams other than the origin that have waited for one another, or themselves, in a ring."""
+        after = {}
+        for waiter, on in self.waits:
+            if origin not in (waiter, on):
+                after.setdefault(on, set()).add(waiter)
+        for s in after:
+            seen, todo = set(), set(after[s])
+            while todo:
+                t = todo.pop()
+                seen.add(t)
+                todo |= after.get(t, set()) - seen
+            if s in seen:
+                return s
+        return None
+
+    def call(self, stream: int, reads=(), writes=(), what=""):
+        clock = self.clocks[stream]
+        clock[stream] = clock.get(stream, 0) + 1
+        for write, spans in ((False, reads), (True, writes)):
+            for a, b in spans:
+                for a0, b0, w0, s0, at0, what0 in self.log:
+                    if (write or w0) and a < b0 and a0 < b and clock.get(s0, 0) < at0:
+                        self.clashes.append((what0, what))
+        for write, spans in ((False, reads), (True, writes)):
+            self.log += [(a, b, write, stream, clock[stream], what) for a, b in spans]
+
+
+class _Stream:
+    order = None
+    count = 0
+
+    def __init__(self, device=None):
+        _Stream.count += 1
+        self.cuda_stream = _Stream.count
+        self.clock = _Stream.order.clocks.setdefault(self.cuda_stream, {})
+
+    def _join(self, other, clock):
+        _Stream.order.waits.add((self.cuda_stream, other.cuda_stream))
+        for s, at in clock.items():
+            self.clock[s] = max(self.clock.get(s, 0), at)
+
+    def wait_stream(self, other):
+        self._join(other, other.clock)
+
+    def wait_event(self, event):
+        self._join(event.stream, event.clock)
+
+
+class _Event:
+    def record(self, stream):
+        self.stream, self.clock = stream, dict(stream.clock)
+
+
+def _addresses(array):
+    return [int(p) if p else 0 for p in array]
+
+
+@pytest.fixture
+def order(monkeypatch):
+    dp.load_library()
+    o = _Stream.order = _Order()
+    main = _Stream()
+    o.main = main.cuda_stream
+    monkeypatch.setattr(torch.cuda, "Stream", _Stream)
+    monkeypatch.setattr(torch.cuda, "Event", _Event)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda *a: main)
+    monkeypatch.setattr(torch.cuda, "is_current_stream_capturing", lambda: False)
+
+    def workspaces(bt):
+        return [(p, p + b) for p, b in zip(_addresses(bt.ws), bt.ws_bytes)]
+
+    def sizes(bt):
+        return [(dp.dp_weight_count(d), dp.dp_bias_count(d)) for d in bt.descs]
+
+    def tables(bt, x, dy, addresses):
+        return [(p, p + 8 * bt.descs[0].n) for array in (x, dy) for p in _addresses(array)] if addresses else []
+
+    def per_example(bt, x, dy, g_w, g_b, sqnorm, g_stride=0, stream=None, addresses=False):
+        writes = workspaces(bt)                    # (rows of the gradient matrix are stood for by the first one)
+        for array, k in ((g_w, 0), (g_b, 1)):
+            writes += [(p, p + 4 * s[k]) for p, s in zip(_addresses(array or []), sizes(bt)) if p]
+        bt.partial_counts[:] = [1] * bt.n_layers
+        o.call(stream, tables(bt, x, dy, addresses), writes, "per_example")
+
+    def unit_grad(bt, unit, x, dy, g_w, g_b, sqnorm, g_stride=0, stream=None, addresses=False):
+        per_example(bt, x, dy, g_w, g_b, None, g_stride, stream, addresses)
+        o.call(stream, writes=[(p, p + 4 * (bt.descs[0].n // unit)) for p in _addresses(sqnorm)], what="unit norms")
+
+    def norms_from_partials(table, n, n_groups, group_sqnorm, stream=None):
+        p = group_sqnorm.data_ptr()
+        o.call(stream, [(a, a + 4 * n) for a in _addresses(table.ptrs)], [(p, p + 4 * n_groups * n)], "norms")
+
+    def norms(layer_sqnorm, group_of_layer, n_layers, n, n_groups, group_sqnorm, stream=None):
+        p, q = layer_sqnorm.data_ptr(), group_sqnorm.data_ptr()
+        o.call(stream, [(p, p + 4 * n_layers * n)], [(q, q + 4 * n_groups * n)], "norms")
+
+    def columns(g, group_sqnorm, n_groups, table, n, run, p, acc, g_stride=0, stream=None):
+        g0, q, a0 = g.data_ptr(), group_sqnorm.data_ptr(), acc.data_ptr()
+        ends = list(table.begin[1:]) + [p]
+        o.call(stream, [(g0, g0 + 4 * p), (q, q + 4 * n_groups * n)],
+               [(a0 + 4 * at, a0 + 4 * (at + e - b)) for at, b, e in zip(table.place, table.begin, ends)], "clipped sum, stored")
+
+    def recompute(bt, x, dy, sqnorm, clip_c, acc_w, acc_b, stream=None, addresses=False):
+        n = bt.descs[0].n
+        acc = [(p, p + 4 * s[k]) for array, k in ((acc_w, 0), (acc_b, 1)) for p, s in zip(_addresses(array), sizes(bt)) if p]
+        o.call(stream, [(p, p + 4 * n) for p in _addresses(sqnorm)] + tables(bt, x, dy, addresses), workspaces(bt) + acc, "clipped sum, recomputed")
+
+    def noise(acc, p, *args, step_dev=None, stream=None):
+        o.call(stream, writes=[(acc, acc + 4 * p)], what="example noise")
+
+    def finalize(acc, out, *args, stream=None, **kw):
+        spans = [(t.data_ptr(), t.data_ptr() + 4 * t.numel()) for t in (acc, out)]
+        o.call(main.cuda_stream, spans[:1], spans[1:], "finalize")
+
+    def write_addresses(tensors, example_bytes, n_operands, n_tensors, per_tensor, table, stream=None):
+        o.call(main.cuda_stream, writes=[(table, table + 8 * n_operands * n_tensors * per_tensor)], what="addresses")
+
+    for name, fn in dict(dp_per_example_grad_batch=per_example, dp_unit_grad_batch=unit_grad, dp_norms_from_partials=norms_from_partials,
+                         dp_norms=norms, dp_clip_accumulate_columns=columns, dp_clip_accumulate_recompute_batch=recompute,
+                         dp_add_example_noise=noise, dp_add_noise_finalize_flat=finalize, dp_example_addresses=write_addresses).items():
+        monkeypatch.setattr(pipeline.B, name, fn)
+    begin = pipeline.PrivatiseStep.begin_step
+
+    def begin_step(self):
+        p = self.acc.data_ptr()
+        o.call(main.cuda_stream, writes=[(p, p + 4 * self.acc.numel())], what="begin")
+        begin(self)
+
+    monkeypatch.setattr(pipeline.PrivatiseStep, "begin_step", begin_step)
+    return o
+
+
+class _Tensor:
+    def data_ptr(self):
+        return 16
+
+
+def _steps(wl, count):
+    return [[(_Tensor(), _Tensor())] * len(wl.layers)] * count
+
+
+def _sizes(ps, sizes):
+    """Phases of the given numbers of micro-steps."""
+    ps._phase_sizes = lambda micro_steps: [s for s in sizes] if micro_steps == sum(sizes) else [1] * micro_steps
+
+
+@pytest.mark.parametrize("noise,unit", [("once", 1), ("per_example", 1), ("once", 2)])
+@pytest.mark.parametrize("name,n,hw,sizes", [("resnet18_gn", 24, 40, [6, 5]), ("resnet18_gn", 32, 24, [6, 5]), ("resnet50", 16, 64, [3, 2, 2, 1]),
+                                             ("resnet50_nano", 1, 64, [3, 2, 2]), ("resnet20", 8, 32, [2, 2, 1])])
+def test_calls_on_the_same_memory_are_ordered_when_phases_differ(order, monkeypatch, name, n, hw, sizes, noise, unit):
+    """Plans of different size deal the layers to the streams differently: a tensor's clipped sums stay in order all the same, and
+    so do the buffers."""
+    if n % unit:
+        pytest.skip("units of two examples need an even micro-step")
+    wl = get_workload(name, n=n, accum=sum(sizes), hw=hw)
+    ps = dp.PrivatiseStep(wl, device="cpu", streams=8, noise=noise, clip_unit=unit)
+    _sizes(ps, sizes)
+    for _ in range(2):
+        ps.run(_steps(wl, sum(sizes)))
+    ps.begin_step()
+    for inputs in _steps(wl, 3):                  # micro-steps one by one between whole steps
+        ps.micro_step(inputs)
+    ps.finalize()
+    ps.run(_steps(wl, sum(sizes)))
+    assert not order.clashes, (len(order.clashes), order.clashes[:4])
+    # a stream capture joins the side streams by their waits: none may hang on itself
+    assert order.ring(order.main) is None
