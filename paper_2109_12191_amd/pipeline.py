@@ -292,7 +292,8 @@ class PrivatiseStep:
         self.theta = None
         self.velocity = None
         self._update = None                      # (lr, momentum, keep_gradient)
-        self._addresses = None                   # example addresses of a step that is issued call by call
+        self._addresses = None                   # (stream, example addresses) of a step that is issued call by call
+        self._recorded_addresses = []            # and those of steps that a caller records in a graph of its own
         self._last = 0                           # copy used by the most recent micro-step
         self._phases = 0                         # phases issued since begin_step
         self._sum_plan = None                    # plan of the last of them
@@ -557,13 +558,10 @@ class PrivatiseStep:
         self._step_dev.add_(1)
         self.step += 1
 
-    def _write_addresses(self, steps: Sequence[Sequence], sizes: List[int], table: Optional[torch.Tensor]) -> torch.Tensor:
+    def _write_addresses(self, steps: Sequence[Sequence], sizes: List[int], table: torch.Tensor) -> torch.Tensor:
         """Example addresses of every operand (x and dy of each layer) of every phase: [operand][example of the phase], phase after
         phase."""
         operands, n = 2 * len(self.layers), self.wl.n
-        need = operands * n * len(steps)
-        if table is None or table.numel() < need:
-            table = torch.empty(need, dtype=torch.int64, device=self.device)
         first = 0
         for size in sizes:
             part = steps[first: first + size]
@@ -571,6 +569,20 @@ class PrivatiseStep:
                                    self._example_bytes, operands, size, n, table.data_ptr() + 8 * operands * n * first)
             first += size
         return table
+
+    def _address_table(self, micro_steps: int) -> torch.Tensor:
+        """Room for the example addresses of a step."""
+        need = 2 * len(self.layers) * self.wl.n * micro_steps
+        if torch.cuda.is_current_stream_capturing():
+            # the recorded launches write and read this table on every replay of a graph that is not ours: it stays
+            table = torch.empty(need, dtype=torch.int64, device=self.device)
+            self._recorded_addresses.append(table)
+            return table
+        # used again by the next step: whoever reads it has been waited for on this stream (finalize)
+        stream = torch.cuda.current_stream().cuda_stream
+        if self._addresses is None or self._addresses[0] != stream or self._addresses[1].numel() < need:
+            self._addresses = stream, torch.empty(need, dtype=torch.int64, device=self.device)
+        return self._addresses[1]
 
     def _issue_step(self, steps: Sequence[Sequence], table: Optional[torch.Tensor] = None):
         """Every micro-step of a step, several at a time where they are small (`table`: addresses already written)."""
@@ -580,7 +592,7 @@ class PrivatiseStep:
                 self.micro_step(inputs)
             return
         if table is None:
-            table = self._addresses = self._write_addresses(steps, sizes, self._addresses)
+            table = self._write_addresses(steps, sizes, self._address_table(len(steps)))
         first, n, L = 0, self.wl.n, len(self.layers)
         for size in sizes:
             if size == 1:
@@ -603,17 +615,19 @@ class PrivatiseStep:
         assert self.probe is None or not getattr(self.probe, "enabled", False)
         step0 = self.step
         self.run(inputs_per_micro_step)          # warm-up outside capture (lazy module loads)
-        # the recorded launches read addresses of their own, which stay as long as the graph does
         sizes = self._phase_sizes(len(inputs_per_micro_step))
-        table = self._write_addresses(inputs_per_micro_step, sizes, None) if max(sizes) > 1 else None
+        table = None
+        if max(sizes) > 1:
+            need = 2 * len(self.layers) * self.wl.n * len(inputs_per_micro_step)
+            table = self._write_addresses(inputs_per_micro_step, sizes, torch.empty(need, dtype=torch.int64, device=self.device))
         torch.cuda.synchronize()
         graph = torch.cuda.CUDAGraph()
         with torch.cuda.graph(graph):
             self.begin_step()
             self._issue_step(inputs_per_micro_step, table)
             self.finalize()
+        graph.example_addresses = table          # read by the recorded launches: kept as long as the graph is
         self.graph = graph
-        self._graph_addresses = table
         self.set_step(step0)                     # recording consumed no optimiser step
         return graph
 

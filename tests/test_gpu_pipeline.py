@@ -280,3 +280,29 @@ def test_phases_of_different_size_on_side_streams(name, n, hw, sizes):
         ps[2].set_step(0)
         ps[2].replay()
         assert torch.equal(ps[2].acc, acc) and torch.equal(ps[2].out, want)
+
+
+def test_two_recorded_steps_and_one_that_the_caller_records():
+    """Graphs over different inputs, each replayed after the others were recorded and longer steps were run."""
+    wl = get_workload("resnet18_gn", n=2, accum=3, hw=16)
+    sets = [[[(dev(x, wl.dtype), dev(dy, wl.dtype)) for x, dy in make_inputs(wl, 3 * k + m)] for m in range(3)] for k in range(3)]
+    eager = dp.PrivatiseStep(wl)
+    want = []
+    for steps in sets:
+        eager.set_step(0)
+        want.append(eager.run(steps).clone())
+    ps = dp.PrivatiseStep(wl, streams=3)
+    graphs = [ps.capture(steps) for steps in sets[:2]]
+    ps.run(sets[2])
+    torch.cuda.synchronize()
+    graphs.append(torch.cuda.CUDAGraph())
+    with torch.cuda.graph(graphs[2]):
+        ps.run(sets[2])
+    for _ in range(3):
+        ps.run(sets[0] + sets[1])                  # a longer step: a larger table
+        for graph, out in zip(graphs, want):
+            fill = [torch.full((1 << k,), -1, dtype=torch.int64, device="cuda:0") for k in range(6, 16)]     # whatever was given back
+            ps.set_step(0)
+            graph.replay()
+            torch.cuda.synchronize()
+            assert torch.equal(ps.out, out) and all(bool((f == -1).all()) for f in fill)

@@ -1,6 +1,10 @@
 """CPU-only checks of how PrivatiseStep orders its calls: every library call is replaced by a record of the memory it reads and
 writes, streams and events by vector clocks, and any two calls that touch the same memory (one of them writing) have to be
 ordered by the streams and events they were issued with."""
+import contextlib
+import gc
+import weakref
+
 import pytest
 import torch
 
@@ -183,3 +187,63 @@ def test_calls_on_the_same_memory_are_ordered_when_phases_differ(order, monkeypa
     assert not order.clashes, (len(order.clashes), order.clashes[:4])
     # a stream capture joins the side streams by their waits: none may hang on itself
     assert order.ring(order.main) is None
+
+
+class _Graph:
+    pass
+
+
+def test_a_recorded_step_keeps_its_example_addresses(order, monkeypatch):
+    """Two graphs of one PrivatiseStep, and a graph that the caller records: none reads or writes addresses that were given away."""
+    capturing = [False]
+
+    @contextlib.contextmanager
+    def graph(g):
+        capturing[0] = True
+        yield
+        capturing[0] = False
+
+    monkeypatch.setattr(torch.cuda, "CUDAGraph", _Graph)
+    monkeypatch.setattr(torch.cuda, "graph", graph)
+    monkeypatch.setattr(torch.cuda, "synchronize", lambda: None)
+    monkeypatch.setattr(torch.cuda, "is_current_stream_capturing", lambda: capturing[0])
+    tables, write = [], pipeline.B.dp_example_addresses
+
+    def seen(tensors, example_bytes, n_operands, n_tensors, per_tensor, table, stream=None):
+        tables.append(table)
+        write(tensors, example_bytes, n_operands, n_tensors, per_tensor, table, stream)
+
+    monkeypatch.setattr(pipeline.B, "dp_example_addresses", seen)
+    wl = get_workload("resnet18_gn", n=2, accum=3, hw=16)
+    ps = dp.PrivatiseStep(wl, device="cpu")
+    ps._phase_sizes = lambda micro_steps: [micro_steps]
+    graphs = [ps.capture(_steps(wl, 3)) for _ in range(2)]
+    kept = [weakref.ref(g.example_addresses) for g in graphs]
+    assert kept[0]().data_ptr() != kept[1]().data_ptr() and {k().data_ptr() for k in kept} <= set(tables)
+    with graph(None):
+        ps.run(_steps(wl, 3))
+    recorded = tables[-1]
+    for count in (3, 5, 2):                       # (a longer step needs a larger table)
+        ps.run(_steps(wl, count))
+        assert tables[-1] not in [recorded] + [k().data_ptr() for k in kept]
+    with graph(None):
+        ps.run(_steps(wl, 3))
+    assert tables[-1] != recorded
+    del graphs[0]
+    gc.collect()
+    assert kept[0]() is None and kept[1]() is not None
+
+
+def test_steps_on_another_stream_get_addresses_of_their_own(order, monkeypatch):
+    """A table is used again only on the stream on which its readers were waited for."""
+    wl = get_workload("resnet18_gn", n=2, accum=3, hw=16)
+    ps = dp.PrivatiseStep(wl, device="cpu")
+    ps._phase_sizes = lambda micro_steps: [micro_steps]
+    ps.run(_steps(wl, 3))
+    first = ps._addresses[1]
+    ps.run(_steps(wl, 3))
+    assert ps._addresses[1] is first
+    other = _Stream()
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda *a: other)
+    ps.run(_steps(wl, 3))
+    assert ps._addresses[1] is not first
