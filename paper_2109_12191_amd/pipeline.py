@@ -34,69 +34,67 @@ from . import binding as B
 # 16 / 32 / 64: 2606 / 2202 / 2174 against 11400 one by one.
 PHASE_BYTES = 2.6e9
 PHASE_EXAMPLES = 256           # and examples
-PHASE_EXAMPLES_STORED = 64     # micro-steps of one or two examples, which store every gradient (ResNet-50: 6.5 GB per copy)
+PHASE_EXAMPLES_STORED = 64     # micro-steps of one or two examples, which store every gradient
+# What a phase may hold in stored gradients, norms and workspaces, all copies together (4 % of the card's memory); a single
+# micro-step takes what it needs.
+PHASE_STORE_BYTES = 12e9
 
 
 def _pad4(v: int) -> int:
     return (v + 3) & ~3
 
 
+def _align256(v: int) -> int:
+    return (v + 255) & ~255
+
+
+class _Store:
+    """One copy of what a phase writes before its clipped sum is done: the gradient matrix, the norms and the workspaces.  The plans
+    of all phase sizes share it (a smaller phase uses the front of every buffer)."""
+
+    def __init__(self, ps: "PrivatiseStep", rows: int, ws_bytes: int):
+        dev, f32 = ps.device, torch.float32
+        self.rows, self.ws_bytes = rows, ws_bytes
+        self.g = torch.empty((rows, ps.p_mat), dtype=f32, device=dev) if ps.p_mat else None
+        if self.g is not None:                     # the columns between tensors are read by the clipped sum, never written
+            for i, form in enumerate(ps.form):
+                if form == "materialise":
+                    for col, size in ((ps.off_w[i], ps.pw[i]), (ps.off_b[i], ps.pb[i])):
+                        if size % 4:
+                            self.g[:, col + size: col + _pad4(size)] = 0.0
+        self.group_sqnorm = torch.zeros(ps.n_groups * rows, dtype=f32, device=dev)
+        self.layer_sqnorm = torch.zeros(len(ps.layers) * rows, dtype=f32, device=dev) if ps.clip_unit > 1 else None
+        self.ws = torch.empty(ws_bytes, dtype=torch.uint8, device=dev)
+        self.done = None                           # events after which its buffers are free again
+
+
 class _Plan:
-    """Buffers and batch calls for phases of `n` examples: one micro-step in the caller's tensors (`tensors` = 1), or `tensors`
+    """Views and batch calls for phases of `n` examples: one micro-step in the caller's tensors (`tensors` = 1), or `tensors`
     micro-steps through arrays of example addresses."""
 
-    def __init__(self, ps: "PrivatiseStep", tensors: int):
-        wl, dev = ps.wl, ps.device
+    def __init__(self, ps: "PrivatiseStep", tensors: int, stores: List[_Store]):
+        wl = ps.wl
         self.ps = ps
         self.tensors = tensors
+        self.stores = stores                       # the copies that are large enough
         self.n = wl.n * tensors
         self.rows = self.n // ps.clip_unit
         self.layers = ps.layers
-        L = len(self.layers)
-        self.descs = [B.make_desc(l, self.n, wl.dtype) for l in self.layers]
         # the forms of a micro-step of its own: the recomputing form rounds scaled bf16 operands once more, and how many
         # micro-steps share a phase must not decide about precision
-        self.form = [ps._choose(l, ps._mode, wl.n) for l in self.layers]
-        # columns of the per-example gradient matrix: the materialised layers in the order they lie in the parameter vector
-        self.col_w, self.col_b = [0] * L, [0] * L
-        segments = []                              # runs of columns of one clipping group that also lie together in acc
-        pos = 0
-        for i in sorted(range(L), key=lambda i: ps.off_w[i]):
-            if self.form[i] != "materialise":
-                continue
-            grp = ps.group_of_layer[i]
-            if not segments or segments[-1][2] != grp or ps.off_w[i] - pos != segments[-1][1] - segments[-1][0]:
-                segments.append((pos, ps.off_w[i], grp))
-            self.col_w[i] = pos
-            pos += _pad4(ps.pw[i])
-            self.col_b[i] = pos
-            pos += _pad4(ps.pb[i])
-        self.p_mat = pos
-        self.segments = B.SegmentTable([s[0] for s in segments], [s[2] for s in segments], [ps.group_clip[s[2]] for s in segments],
-                                       [s[1] for s in segments]) if segments else None
-        f32 = torch.float32
-        copies = ps.copies
-        self.g = [torch.empty((self.rows, self.p_mat), dtype=f32, device=dev) if self.p_mat else None for _ in range(copies)]
-        for i in range(L):                         # the columns between tensors are read by the clipped sum, never written
-            if self.form[i] == "materialise":
-                for col, size in ((self.col_w[i], ps.pw[i]), (self.col_b[i], ps.pb[i])):
-                    if size % 4:
-                        for g in self.g:
-                            g[:, col + size: col + _pad4(size)] = 0.0
-        self.group_sqnorm = [torch.zeros((ps.n_groups, self.rows), dtype=f32, device=dev) for _ in range(copies)]
-        need = [max(16, B.dp_workspace_bytes(d, B.DP_WS_PER_EXAMPLE_GRAD),
-                    B.dp_workspace_bytes(d, B.DP_WS_RECOMPUTE) if form == "recompute" else 0,
-                    B.dp_unit_workspace_bytes(d, ps.clip_unit) if ps.clip_unit > 1 else 0)
-                for d, form in zip(self.descs, self.form)]
-        # a workspace per layer (the layers of a phase are in flight together), all in one allocation per copy
+        self.form = ps.form
+        L = len(self.layers)
+        self.descs, need = ps._workspaces(tensors)
+        self.g = [st.g[: self.rows] if st.g is not None else None for st in stores]
+        self.group_sqnorm = [st.group_sqnorm[: ps.n_groups * self.rows].view(ps.n_groups, self.rows) for st in stores]
+        self.layer_sqnorm = [st.layer_sqnorm[: L * self.rows].view(L, self.rows) for st in stores] if ps.clip_unit > 1 else None
+        # a workspace per layer (the layers of a phase are in flight together)
         starts, total = [], 0
         for b in need:
             starts.append(total)
-            total += (b + 255) & ~255
+            total += _align256(b)
         self.ws_bytes = need
-        self._ws_store = [torch.empty(total, dtype=torch.uint8, device=dev) for _ in range(copies)]
-        self.ws = [[store.data_ptr() + at for at in starts] for store in self._ws_store]
-        self.layer_sqnorm = [torch.zeros((L, self.rows), dtype=f32, device=dev) for _ in range(copies)] if ps.clip_unit > 1 else None
+        self.ws = [[st.ws.data_ptr() + at for at in starts] for st in stores]
         # Layers that run the same kernel variant go to the library in ONE batch call, which puts them into one
         # launch (at most 16 per launch): per phase a micro-step is a dozen launches, not a hundred.
         self.variant = [(B.dp_kernel_variant(d, B.DP_WS_PER_EXAMPLE_GRAD | B.DP_VARIANT_SHARED |
@@ -104,7 +102,7 @@ class _Plan:
                          B.dp_kernel_variant(d, B.DP_WS_RECOMPUTE | B.DP_VARIANT_SHARED) if form == "recompute" else "")
                         for d, form in zip(self.descs, self.form)]
         self.partials = [B.PartialTable(self.ws[c], [1] * L, ps.group_of_layer)
-                         for c in range(copies)]
+                         for c in range(len(stores))]
         esize = 2 if wl.dtype == "bf16" else 4
         # algorithmic work of one call per layer: (flop, HBM bytes of the per-example call, HBM bytes of the
         # recomputing clipped-sum call).  Bytes = the operands read once, plus the per-example gradients
@@ -116,7 +114,6 @@ class _Plan:
         self.groups_a = self._make_groups(range(L), 0) if ps.clip_unit == 1 else []
         self.groups_b = self._make_groups([i for i in range(L) if self.form[i] == "recompute"], 1)
         self.groups_u = self._make_groups(range(L), 2) if ps.clip_unit > 1 else []
-        self.b_done = [None] * copies            # per copy: events after which its buffers are free again
 
     def _make_groups(self, layer_ids, use: int):
         """Groups of at most 16 layers with the same kernel variant for phase `use` (0: per-example gradients,
@@ -146,22 +143,22 @@ class _Plan:
                         B.DP_WS_PER_EXAMPLE_GRAD | (B.DP_VARIANT_MATERIALISE if self.form[part[0]] == "materialise" else 0)))
                 g = dict(layers=part, name=name, conv=all(self.layers[i].kind == "conv" for i in part))
                 g["batch"] = [B.LayerBatch([self.descs[i] for i in part], [self.ws[c][i] for i in part],
-                                           [self.ws_bytes[i] for i in part]) for c in range(ps.copies)]
+                                           [self.ws_bytes[i] for i in part]) for c in range(len(self.stores))]
                 if use == 2:
                     g["usq"] = [g["batch"][c].ptrs([self.layer_sqnorm[c][i].data_ptr() for i in part])
-                                for c in range(ps.copies)]
+                                for c in range(len(self.stores))]
                 if use != 1:
                     g["counted"] = False
                     mat = [self.form[i] == "materialise" for i in part]
                     g0 = [g.data_ptr() if g is not None else 0 for g in self.g]
-                    g["gw"] = [g["batch"][c].ptrs([g0[c] + 4 * self.col_w[i] if m else None
-                                                   for i, m in zip(part, mat)]) if any(mat) else None for c in range(ps.copies)]
-                    g["gb"] = [g["batch"][c].ptrs([g0[c] + 4 * self.col_b[i] if (m and ps.pb[i]) else None
-                                                   for i, m in zip(part, mat)]) if any(mat) else None for c in range(ps.copies)]
+                    g["gw"] = [g["batch"][c].ptrs([g0[c] + 4 * ps.off_w[i] if m else None
+                                                   for i, m in zip(part, mat)]) if any(mat) else None for c in range(len(self.stores))]
+                    g["gb"] = [g["batch"][c].ptrs([g0[c] + 4 * ps.off_b[i] if (m and ps.pb[i]) else None
+                                                   for i, m in zip(part, mat)]) if any(mat) else None for c in range(len(self.stores))]
                 else:
                     acc0 = ps.acc.data_ptr()
                     g["sq"] = [g["batch"][c].ptrs([self.group_sqnorm[c][ps.group_of_layer[i]].data_ptr() for i in part])
-                               for c in range(ps.copies)]
+                               for c in range(len(self.stores))]
                     g["clip"] = g["batch"][0].floats([ps.group_clip[ps.group_of_layer[i]] for i in part])
                     g["acc_w"] = g["batch"][0].ptrs([acc0 + 4 * ps.off_w[i] for i in part])
                     g["acc_b"] = g["batch"][0].ptrs([acc0 + 4 * ps.off_b[i] if ps.pb[i] else None
@@ -247,17 +244,26 @@ class PrivatiseStep:
         self._mode = mode
         self.n_groups = wl.n_groups
 
-        # flat parameter vector: the layers that materialise in a micro-step of its own first, then the recomputed ones
-        form = [self._choose(l, mode, wl.n) for l in self.layers]
-        order = [i for i in range(L) if form[i] == "materialise"] + [i for i in range(L) if form[i] == "recompute"]
+        self.form = [self._choose(l, mode, wl.n) for l in self.layers]
+
+        # flat parameter vector: materialised layers first (their columns double as the
+        # layout of the per-example gradient matrix), then the recomputed ones
+        mat = [i for i in range(L) if self.form[i] == "materialise"]
         self.off_w = [0] * L
         self.off_b = [0] * L
         pos = 0
-        for i in order:
+        self.p_mat = 0
+        for i in mat + [i for i in range(L) if self.form[i] == "recompute"]:
             self.off_w[i] = pos
             pos += _pad4(self.pw[i])
             self.off_b[i] = pos
             pos += _pad4(self.pb[i])
+            if self.form[i] == "materialise":
+                self.p_mat = pos
+        # runs of columns of the gradient matrix that belong to one clipping group
+        runs = [i for k, i in enumerate(mat) if k == 0 or self.group_of_layer[i] != self.group_of_layer[mat[k - 1]]]
+        self._segments = B.SegmentTable([self.off_w[i] for i in runs], [self.group_of_layer[i] for i in runs],
+                                        [self.group_clip[self.group_of_layer[i]] for i in runs]) if runs else None
         self.p_total = max(pos, 4)
         # every tensor of the flat vector with its Philox tensor id (2*layer weight, 2*layer+1 bias), in
         # the order they lie in memory: the table of the one-launch finalize
@@ -268,22 +274,26 @@ class PrivatiseStep:
         f32 = torch.float32
         self.acc = torch.zeros(self.p_total, dtype=f32, device=dev)
         self.out = torch.zeros(self.p_total, dtype=f32, device=dev)
-        # Workspaces and per-micro-step buffers (_Plan).  With one stream all calls run in order and share
-        # one copy.  With side streams the layers of a phase run concurrently and the two phases of consecutive
-        # micro-steps overlap: everything a micro-step writes before its clipped sum is done -- the gradient matrix, the
-        # norms, the workspaces -- exists twice and micro-steps alternate between the copies.
+        # Workspaces and per-phase buffers (_Store).  With one stream all calls run in order and share
+        # one copy.  With side streams the layers of a phase run concurrently and the per-example part of a phase overlaps the
+        # clipped sum of the one before: everything a phase writes before its clipped sum is done -- the gradient matrix, the
+        # norms, the workspaces -- exists twice and phases alternate between the copies.
         self.n_streams = max(1, int(streams))
         self.copies = 2 if self.n_streams > 1 else 1
         self.group_of_layer_dev = torch.tensor(self.group_of_layer, dtype=torch.int32, device=dev)
         esize = 2 if wl.dtype == "bf16" else 4
         self._example_bytes = [b for l in self.layers for b in (l.x_bytes(esize), l.dy_bytes(esize))]
-        per_micro_step = max(1, sum(self._example_bytes)) * wl.n
-        self._together = max(1, min(int(PHASE_BYTES // per_micro_step),
-                                     (PHASE_EXAMPLES_STORED if wl.n <= 2 else PHASE_EXAMPLES) // wl.n))    # micro-steps per phase, at most
+        self._needs = {}                         # micro-steps of a phase -> descriptors and workspace sizes
+        self._together = self._micro_steps_together()
+        # Micro-steps that a copy has room for.  A step of one phase never uses a second copy; micro-steps that are handed over
+        # one by one do.  Steps of more micro-steps than the workload's have more phases, not larger ones.
+        self._ws_room = None
+        sizes = self._phase_sizes(max(1, wl.accum))
+        self._ws_room = max(self._workspace_bytes(size) for size in {1, *sizes})
+        self._room = [sizes[0], sizes[0] if len(sizes) > 1 else 1][: self.copies]
+        self._stores = [None] * self.copies      # allocated when a plan first uses them
         self._plans = {}
-        for size in {1} | set(self._phase_sizes(wl.accum)):
-            self._plan(size)
-        self._main = self._plan(max(self._phase_sizes(wl.accum)))      # the plan of a whole step's phases
+        self._main = self._plan(sizes[0])        # the plan of a whole step's phases
         # side streams: `side` for the per-example phase, `side_b` for the clipped-sum phase
         self.side = [torch.cuda.Stream(device=dev) for _ in range(self.n_streams)] if self.n_streams > 1 else []
         # (three clipped-sum streams for eight per-example streams: measured 3 % better over the whole step than four)
@@ -297,7 +307,8 @@ class PrivatiseStep:
         self._last = 0                           # copy used by the most recent micro-step
         self._phases = 0                         # phases issued since begin_step
         self._sum_plan = None                    # plan of the last of them
-        self._group_sqnorm = list(self._plan(1).group_sqnorm)      # of the last micro-steps (one per copy)
+        self._group_sqnorm = [torch.zeros((self.n_groups, wl.n // self.clip_unit), dtype=f32, device=dev)
+                              for _ in range(self.copies)]         # of the last micro-steps (one per copy)
         self._g_last = None
         self.graph = None
         self.micro_steps_done = 0
@@ -310,29 +321,61 @@ class PrivatiseStep:
         # library to bracket the next contraction kernel with a pair of events
         self.probe = None
 
+    def _workspaces(self, tensors: int):
+        """Descriptors and workspace bytes of every layer in a phase of `tensors` micro-steps."""
+        if tensors not in self._needs:
+            descs = [B.make_desc(l, self.wl.n * tensors, self.wl.dtype) for l in self.layers]
+            need = [max(16, B.dp_workspace_bytes(d, B.DP_WS_PER_EXAMPLE_GRAD),
+                        B.dp_workspace_bytes(d, B.DP_WS_RECOMPUTE) if form == "recompute" else 0,
+                        B.dp_unit_workspace_bytes(d, self.clip_unit) if self.clip_unit > 1 else 0)
+                    for d, form in zip(descs, self.form)]
+            self._needs[tensors] = descs, need
+        return self._needs[tensors]
+
+    def _workspace_bytes(self, tensors: int) -> int:
+        return sum(_align256(b) for b in self._workspaces(tensors)[1])
+
+    def _micro_steps_together(self) -> int:
+        """Micro-steps per phase, at most."""
+        wl = self.wl
+        per_micro_step = max(1, sum(self._example_bytes)) * wl.n
+        most = max(1, min(int(PHASE_BYTES // per_micro_step), (PHASE_EXAMPLES_STORED if wl.n <= 2 else PHASE_EXAMPLES) // wl.n))
+        matrix = 4 * (wl.n // self.clip_unit) * self.p_mat
+        phases = max(1, -(-wl.accum // most))
+        while True:
+            size = max(1, -(-wl.accum // phases))
+            copies = self.copies if phases > 1 else 1
+            if size == 1 or copies * (size * matrix + self._workspace_bytes(size)) <= PHASE_STORE_BYTES:
+                return size
+            phases += 1
+
     def _phase_sizes(self, micro_steps: int) -> List[int]:
-        """How many micro-steps each phase of a step of `micro_steps` holds: as few phases as the bound allows, of nearly equal
+        """How many micro-steps each phase of a step of `micro_steps` holds: as few phases as the bounds allow, of nearly equal
         size."""
         phases = max(1, -(-micro_steps // self._together))
-        return [micro_steps // phases + (1 if k < micro_steps % phases else 0) for k in range(phases)]
+        while True:
+            sizes = [micro_steps // phases + (1 if k < micro_steps % phases else 0) for k in range(phases)]
+            # (the workspaces of a smaller phase may need more than those of the sizes that the buffers were made for)
+            if self._ws_room is None or sizes[0] <= 1 or all(self._workspace_bytes(size) <= self._ws_room for size in set(sizes)):
+                return sizes
+            phases += 1
 
     def _plan(self, tensors: int) -> _Plan:
         if tensors not in self._plans:
-            self._plans[tensors] = _Plan(self, tensors)
+            stores = []
+            for c, room in enumerate(self._room):
+                if tensors <= room:
+                    if self._stores[c] is None:
+                        ws = self._workspace_bytes(1) if room == 1 else self._ws_room
+                        self._stores[c] = _Store(self, room * (self.wl.n // self.clip_unit), ws)
+                    stores.append(self._stores[c])
+            self._plans[tensors] = _Plan(self, tensors, stores)
         return self._plans[tensors]
 
     # ---- what a phase of a whole step looks like (tests, bench.py)
     @property
-    def form(self):
-        return self._main.form
-
-    @property
     def rows(self):
         return self._main.rows
-
-    @property
-    def p_mat(self):
-        return self._main.p_mat
 
     @property
     def work(self):
@@ -426,8 +469,9 @@ class PrivatiseStep:
         self.micro_steps_done = 0
         self._phases = 0
         self._sum_plan = None
-        for plan in self._plans.values():
-            plan.b_done = [None] * self.copies
+        for store in self._stores:
+            if store is not None:
+                store.done = None
 
     def micro_step(self, inputs: Sequence):
         """inputs: per layer (x, dy) device tensors of the workload's dtype, n examples each.
@@ -446,8 +490,9 @@ class PrivatiseStep:
         addresses."""
         at = plan.tensors > 1
         L = len(self.layers)
-        gs = plan.p_mat
-        c = self._phases % self.copies
+        gs = self.p_mat
+        c = self._phases % len(plan.stores)
+        store = plan.stores[c]
         g_buf, gsq = plan.g[c], plan.group_sqnorm[c]
         fork = self.fork or ("step" if plan.n <= 2 else "micro_step")
         main = torch.cuda.current_stream()
@@ -456,8 +501,8 @@ class PrivatiseStep:
         for st in self.side:
             if fork == "micro_step" or self._phases == 0:
                 st.wait_stream(main)
-            if plan.b_done[c] is not None:            # this copy's previous clipped sum has finished
-                for ev in plan.b_done[c]:
+            if store.done is not None:                # this copy's previous clipped sum has finished
+                for ev in store.done:
                     st.wait_event(ev)
         # unit sums and their norms: one batch call per kernel variant, dealt to the side streams
         for grp in plan.groups_u:
@@ -492,10 +537,10 @@ class PrivatiseStep:
         self._sum_plan = plan
         for st in sb:
             st.wait_stream(main)
-        if plan.p_mat:
+        if self.p_mat:
             # one launch over all materialised tensors, whatever their clipping groups
-            B.dp_clip_accumulate_columns(g_buf, gsq, self.n_groups, plan.segments, plan.rows, plan.rows // plan.tensors, plan.p_mat, self.acc, g_stride=gs,
-                                         stream=sb[0].cuda_stream if sb else ms)
+            B.dp_clip_accumulate_columns(g_buf, gsq, self.n_groups, self._segments, plan.rows, plan.rows // plan.tensors, self.p_mat, self.acc,
+                                         g_stride=gs, stream=sb[0].cuda_stream if sb else ms)
         if self.noise == "per_example":
             for li in range(L):
                 if plan.form[li] == "materialise":
@@ -515,7 +560,7 @@ class PrivatiseStep:
                 ev = torch.cuda.Event()
                 ev.record(st)
                 evs.append(ev)
-            plan.b_done[c] = evs
+            store.done = evs
         rows = self.wl.n // self.clip_unit             # of a micro-step
         for k in range(max(0, plan.tensors - self.copies), plan.tensors):
             self._last = (self.micro_steps_done + k) % self.copies

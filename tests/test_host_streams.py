@@ -161,22 +161,18 @@ def _steps(wl, count):
     return [[(_Tensor(), _Tensor())] * len(wl.layers)] * count
 
 
-def _sizes(ps, sizes):
-    """Phases of the given numbers of micro-steps."""
-    ps._phase_sizes = lambda micro_steps: [s for s in sizes] if micro_steps == sum(sizes) else [1] * micro_steps
-
-
 @pytest.mark.parametrize("noise,unit", [("once", 1), ("per_example", 1), ("once", 2)])
-@pytest.mark.parametrize("name,n,hw,sizes", [("resnet18_gn", 24, 40, [6, 5]), ("resnet18_gn", 32, 24, [6, 5]), ("resnet50", 16, 64, [3, 2, 2, 1]),
-                                             ("resnet50_nano", 1, 64, [3, 2, 2]), ("resnet20", 8, 32, [2, 2, 1])])
+@pytest.mark.parametrize("name,n,hw,sizes", [("resnet18_gn", 24, 40, [6, 5]), ("resnet18_gn", 32, 24, [6, 5]), ("resnet50", 16, 64, [3, 3, 2]),
+                                             ("resnet50_nano", 1, 64, [3, 2, 2]), ("resnet20", 8, 32, [2, 2, 1]), ("resnet20", 8, 32, [5])])
 def test_calls_on_the_same_memory_are_ordered_when_phases_differ(order, monkeypatch, name, n, hw, sizes, noise, unit):
     """Plans of different size deal the layers to the streams differently: a tensor's clipped sums stay in order all the same, and
     so do the buffers."""
     if n % unit:
         pytest.skip("units of two examples need an even micro-step")
+    monkeypatch.setattr(pipeline.PrivatiseStep, "_micro_steps_together", lambda self: sizes[0])
     wl = get_workload(name, n=n, accum=sum(sizes), hw=hw)
     ps = dp.PrivatiseStep(wl, device="cpu", streams=8, noise=noise, clip_unit=unit)
-    _sizes(ps, sizes)
+    assert ps._phase_sizes(sum(sizes)) == sizes
     for _ in range(2):
         ps.run(_steps(wl, sum(sizes)))
     ps.begin_step()
@@ -184,6 +180,7 @@ def test_calls_on_the_same_memory_are_ordered_when_phases_differ(order, monkeypa
         ps.micro_step(inputs)
     ps.finalize()
     ps.run(_steps(wl, sum(sizes)))
+    ps.run(_steps(wl, 2 * sum(sizes) - 1))        # a step of another length
     assert not order.clashes, (len(order.clashes), order.clashes[:4])
     # a stream capture joins the side streams by their waits: none may hang on itself
     assert order.ring(order.main) is None
@@ -216,7 +213,6 @@ def test_a_recorded_step_keeps_its_example_addresses(order, monkeypatch):
     monkeypatch.setattr(pipeline.B, "dp_example_addresses", seen)
     wl = get_workload("resnet18_gn", n=2, accum=3, hw=16)
     ps = dp.PrivatiseStep(wl, device="cpu")
-    ps._phase_sizes = lambda micro_steps: [micro_steps]
     graphs = [ps.capture(_steps(wl, 3)) for _ in range(2)]
     kept = [weakref.ref(g.example_addresses) for g in graphs]
     assert kept[0]().data_ptr() != kept[1]().data_ptr() and {k().data_ptr() for k in kept} <= set(tables)
@@ -238,7 +234,6 @@ def test_steps_on_another_stream_get_addresses_of_their_own(order, monkeypatch):
     """A table is used again only on the stream on which its readers were waited for."""
     wl = get_workload("resnet18_gn", n=2, accum=3, hw=16)
     ps = dp.PrivatiseStep(wl, device="cpu")
-    ps._phase_sizes = lambda micro_steps: [micro_steps]
     ps.run(_steps(wl, 3))
     first = ps._addresses[1]
     ps.run(_steps(wl, 3))
@@ -247,3 +242,42 @@ def test_steps_on_another_stream_get_addresses_of_their_own(order, monkeypatch):
     monkeypatch.setattr(torch.cuda, "current_stream", lambda *a: other)
     ps.run(_steps(wl, 3))
     assert ps._addresses[1] is not first
+
+
+def test_buffers_do_not_grow_with_the_lengths_of_the_steps(order):
+    """Steps of every length run in the buffers of the first; a smaller phase uses the front of them."""
+    wl = get_workload("resnet50_nano", accum=16, hw=64)
+    ps = dp.PrivatiseStep(wl, device="cpu", streams=4)
+
+    def held():
+        tensors = [t for o in gc.get_objects() if type(o) is pipeline._Store for t in (o.g, o.ws, o.group_sqnorm, o.layer_sqnorm) if t is not None]
+        return sum(t.numel() * t.element_size() for t in tensors)
+
+    ps.run(_steps(wl, 16))
+    gc.collect()
+    before = held()
+    ps.begin_step()
+    ps.micro_step(_steps(wl, 1)[0])               # one at a time: the second copy, of a micro-step
+    ps.finalize()
+    one = 4 * ps.p_mat + sum(ps._plan(1).ws_bytes) + (1 << 20)
+    for count in (1, 2, 3, 7, 11, 15, 16, 17, 29):
+        ps.run(_steps(wl, count))
+    assert before <= held() <= before + one
+    assert not order.clashes
+    for plan in ps._plans.values():
+        for c, store in enumerate(plan.stores):
+            assert plan.rows <= store.rows and plan.ws[c][-1] + plan.ws_bytes[-1] <= store.ws.data_ptr() + store.ws.numel()
+            assert plan.g[c].data_ptr() == store.g.data_ptr()
+
+
+@pytest.mark.parametrize("name,n,accum,mode,streams", [("resnet18_gn", 4, 64, "materialise", 8), ("resnet50_nano", 1, 1024, "auto", 4),
+                                                       ("resnet50", 2, 64, "auto", 1), ("resnet20", 3, 80, "recompute", 2)])
+def test_a_phase_is_bounded_by_what_it_holds(order, monkeypatch, name, n, accum, mode, streams):
+    """Gradients, norms and workspaces of all copies stay within the bound, whatever the inputs weigh; one micro-step always goes."""
+    wl = get_workload(name, n=n, accum=accum, hw=64 if name != "resnet20" else 32)
+    for bound in (pipeline.PHASE_STORE_BYTES, 1e9, 1.0):
+        monkeypatch.setattr(pipeline, "PHASE_STORE_BYTES", bound)
+        ps = dp.PrivatiseStep(wl, device="cpu", mode=mode, streams=streams)
+        size, copies = ps.micro_steps_per_phase, len(ps._main.stores)
+        assert size == 1 or copies * (4 * ps._main.rows * ps.p_mat + ps._workspace_bytes(size)) <= bound
+        assert copies == (ps.copies if size == 1 or accum > size else 1)
