@@ -1667,6 +1667,21 @@ static FullPlan full_plan(const Geo &g, int mode)
     return p;
 }
 
+// us of a per-example fp32 call alone in the general kernel, with its slice sums (conv_rows.hip says what it was fitted to): the chunks
+// of all workgroups over the compute units, the epilogues, the slice-sum launch, one workgroup's walk.
+double conv_general_f32_us(const Geo &g)
+{
+    const int saved = tl_forced_crowd;
+    tl_forced_crowd = 0;
+    const FullPlan f = full_plan(g, MODE_NORM);
+    tl_forced_crowd = saved;
+    const double units = (double)(g.n / g.unit) * f.tiles_m * f.tiles_n, chunks = units * g.unit * f.chunks_per_ex;
+    const double walk = f.ksplit == 1 ? (double)f.ex_per_wg * f.chunks_per_ex : f.slice_ex ? (double)f.slice_ex * f.chunks_per_ex : f.chunks_per_split;
+    if (f.shape == T64)
+        return 10.3 + chunks / 256.0 * (g.has_bias ? 1.22 : 0.92) + units / 256.0 * 0.57 + (f.ksplit > 1 ? 4.2 : 0.0) + walk * (g.has_bias ? 1.16 : 0.72);
+    return 11.4 + chunks / 256.0 * (g.has_bias ? 2.84 : 2.69) + units / 256.0 * 1.05 + walk * (g.has_bias ? 4.2 : 2.56);
+}
+
 // Clip-weighted contraction of a bf16 layer whose packed operands are small: rewrite the
 // operands first (pack.hip) and run the aligned one-long-row variant on `g2`, the geometry of
 // the packed tensors (example ranges as its "examples", im2col rows as its input channels).

@@ -18,13 +18,16 @@
 // The next chunk's rows are loaded into registers before the MFMAs and written to LDS after them.  A finished block is
 // added up over q in LDS in a fixed order, 16 rows at a time, and leaves as contiguous rows of the gradient; its square goes to one partial
 // norm per (example, block).
-// MI355X, per-example call alone: 64 examples of 64 -> 64 3x3 on 56 x 56: 408 -> 209 us (71 TFLOP/s); 40 of 40 -> 72 5x5 stride 2 on 45 x 37: 125 -> 107 us.
+// MI355X, per-example call alone, general kernel -> this: 64 examples of 64 -> 64 3x3 with a bias on 56 x 56: 378 -> 202 us (73 TFLOP/s);
+// 40 of 40 -> 72 5x5 stride 2 with a bias on 45 x 37: 126 -> 109 us.  Where it is chosen: rows_choice.
 #include "group.h"
 #include "internal.h"
 #include "pieces.h"
 
 #include <algorithm>
 #include <atomic>
+#include <cmath>
+#include <cstring>
 
 namespace dp {
 
@@ -273,14 +276,14 @@ __global__ void __launch_bounds__(64 * K * cr_qmax(K)) conv_rows_kernel(const Gr
 
 struct RowsPlan {
     int tiles_m, tiles_n, tm, tn, q, rows, chunks, rpr, xp, cha, chx, ex_per_wg;
+    int groups, resident;           // groups of four runs per chunk; workgroups that a compute unit has room for
     unsigned lds;
     bool ok;
 };
 
 int odd_quads(int floats) { const int v = (floats + 3) / 4; return (v | 1) * 4; }     // consecutive channels start in different banks
 
-// `rows` 1 only: whether there is a plan at all (fewer rows per chunk and more waves only ever need less of everything)
-RowsPlan rows_plan(const Geo &g, int max_rows = 64)
+RowsPlan rows_plan(const Geo &g)
 {
     RowsPlan p = {};
     const int K = g.kh, S = g.stride;
@@ -295,7 +298,7 @@ RowsPlan rows_plan(const Geo &g, int max_rows = 64)
     const double wgs = (double)(g.n / g.unit) * p.tiles_m * p.tiles_n;
     double best = 0.0;
     for (int q = 1; q <= cr_qmax(K); q *= 2)
-        for (int rows = 1; rows <= g.oh && rows <= max_rows; ++rows) {
+        for (int rows = 1; rows <= g.oh && rows <= 64; ++rows) {
             const int lines = (rows - 1) * S + K;
             if (lines > 127) break;
             const long long pieces = (long long)lc * rows * p.rpr + (long long)ln * lines * ((g.w + 3) / 4);
@@ -320,6 +323,7 @@ RowsPlan rows_plan(const Geo &g, int max_rows = 64)
             best = per_example;
             p.ok = true;
             p.q = q; p.rows = rows; p.chunks = chunks; p.cha = cha; p.chx = chx; p.lds = lds;
+            p.groups = groups; p.resident = resident;
         }
     if (!p.ok) return p;
     // several examples in a row where there are far more (example, block) pairs than workgroups that run at a time
@@ -335,30 +339,58 @@ template <int K> const void *rows_fn(int stride)
     return stride == 2 ? reinterpret_cast<const void *>(&conv_rows_kernel<K, 2>) : reinterpret_cast<const void *>(&conv_rows_kernel<K, 1>);
 }
 
+// us of a per-example call alone.  Blocks are not sliced along K, so a launch lasts as long as the compute unit with most of them:
+// start and end, the MFMAs (which several workgroups on a unit slow down more than they overlap), the barriers and the waiting of
+// every chunk, the epilogue.
+double rows_us(const Geo &g, const RowsPlan &p)
+{
+    const bool k3 = g.kh == 3;
+    const double blocks = std::ceil((double)(g.n / g.unit) * p.tiles_m * p.tiles_n / 256.0), rounds = std::ceil(blocks / std::min<double>(blocks, p.resident));
+    const double chunks = (double)p.chunks * g.unit;
+    const double mfma = 32.0 * g.kh * g.kw * ((p.groups + p.q - 1) / p.q) * p.q * (p.tm / 16) * (p.tn / 16) / 2400.0;     // of a chunk, its four SIMDs busy
+    if (k3) return 12.6 + blocks * chunks * mfma * (blocks > 1.0 ? 1.96 : 1.34) + rounds * chunks * 3.55 + blocks * 1.5;
+    return 8.6 + blocks * chunks * mfma * (blocks > 1.0 ? 1.75 : 1.50) + blocks * chunks * 4.07 + blocks * 3.8;
+}
+
+// What the sizes decide, kept for the sizes seen last (a call asks several times): the plan, and whether the kernel is the faster one.
+struct RowsChoice {
+    int key[9];
+    bool use;
+    RowsPlan plan;
+};
+
+const RowsChoice &rows_choice(const Geo &g)
+{
+    static thread_local RowsChoice kept[64];
+    const int key[9] = {g.n, g.unit, g.cin, g.cout, g.h, g.w, g.kh, g.stride, 1 + g.has_bias};
+    unsigned at = 0;
+    for (int v : key) at = at * 31u + (unsigned)v;
+    RowsChoice &c = kept[(at ^ at >> 6) % 64];
+    if (std::memcmp(c.key, key, sizeof(key)) != 0) {
+        c.plan = rows_plan(g);
+        // Both times estimated, a margin of 7 % to the general kernel.  Fitted to 1249 layers in and around the networks here (3x3 and
+        // 5x5, strides 1 and 2, 3 to 256 channels, 7 to 64 rows, 8 to 512 examples, with and without a bias), both kernels measured
+        // on each: rows_us is within 6 % (90 % of the layers within 20 %), the general estimate within 5 % (15 %).  The rule takes
+        // 449 of them, 15 of those are slower by more than 3 % (at most 28 %: 29 / 37 us, 32 -> 64 onto 8 x 8); all 1249 together
+        // take 0.887 of the general kernel's time, where the faster of the two each time would be 0.880.  us, general / this: 64 -> 64 3x3 on
+        // 56 x 56, 64 examples 282 / 194, 48: 185 / 194, 128: 465 / 543; with a bias 378 / 202, 243 / 195, 618 / 553; 16 -> 16 on 32 x
+        // 32, 256: 100 / 32; 128 -> 128 on 28 x 28, 96: 295 / 435; 5x5, 40 -> 72 stride 2 on 45 x 37 with a bias, 40: 126 / 109.
+        c.use = c.plan.ok && rows_us(g, c.plan) < 0.93 * conv_general_f32_us(g);
+        std::memcpy(c.key, key, sizeof(key));
+    }
+    return c;
+}
+
 }  // namespace
 
 bool conv_rows_applicable(const Geo &g, int mode)
 {
     if (mode == MODE_WEIGHTED || g.bf16) return false;
     if (g.kh != g.kw || (g.kh != 3 && g.kh != 5) || g.pad != (g.kh - 1) / 2 || g.stride < 1 || g.stride > 2) return false;
-    // Blocks are not sliced along K, so a launch of few of them walks long while the general kernel cuts K; and a 5 x 5 block's
-    // epilogue (25 taps summed over the waves) wants a long K, or a stride that the general kernel gathers slowly.  us per call and
-    // noise, general / this: 3x3, 25 blocks, 20 -> 19 on 42 x 31: 123 / 164; 54 blocks, 22 -> 74 on 41 x 56: 103 / 166; 256 blocks, 64 ->
-    // 64 on 56 x 56: faster (above).  5x5: 528 blocks, 86 -> 58 on 11 x 31: 114 / 170;
-    // 720, 59 -> 93 on 18 x 54: 314 / 412; 208, 52 -> 54 on 44 x 56: 254 / 225; stride 2, 304, 19 -> 126 onto 15 x 20: 118 / 152;
-    // 230, 69 -> 19 onto 21 x 24: 287 / 217.  (1x1: no element is read by two taps; 51 / 95 at 108 -> 33 on 45 x 26.)
-    const double blocks = (double)(g.n / g.unit) * conv_rows_norm_partial_count(g);
-    const int S = g.oh * g.ow;
-    // 3x3: ragged rows and channels waste its blocks of 16 and runs of four: 61 examples, 131 -> 61 on 21 x 20 stride 2: 64 / 97; 56, 121 ->
-    // 96 on 24 x 55: 670 / 832; 16, 64 -> 64 on 32 x 32 (64 blocks): 53 / 72.  Few output channels leave the general kernel's tiles
-    // of 64 empty: 43, 88 -> 14 on 40 x 29: 187 / 71.
-    const bool even = g.cin % 16 == 0 && g.cout % 16 == 0 && g.ow % 4 == 0 && blocks >= 256;
-    const bool narrow = g.stride == 1 && g.cout <= 16 && blocks >= 100;
-    if (g.kh == 3 ? !even && !narrow : blocks < 200 || S < (g.stride == 2 ? 400 : 1900)) return false;
     // offsets inside an example (rows above and below the image included) fit 32 bits; quotients of the set-up stay exact
     if ((size_t)g.cin * (g.h + 8) * g.w >= ((size_t)1 << 30) || (size_t)g.cout * (g.oh + 64) * g.ow >= ((size_t)1 << 30)) return false;
     if (g.w > 4096 || (double)g.n * conv_rows_norm_partial_count(g) >= 1.0e9) return false;
-    return rows_plan(g, 1).ok;
+    return rows_choice(g).use;
 }
 
 size_t conv_rows_norm_partial_count(const Geo &g) { return (size_t)((g.cout + CR_CH - 1) / CR_CH) * ((g.cin + cr_cin(g.kh) - 1) / cr_cin(g.kh)); }
@@ -376,7 +408,7 @@ const char *conv_rows_variant_name(const Geo &g)
 dp_status launch_conv_rows(const Geo &g, const void *x, const void *dy, float *out_w, float *out_b, size_t out_stride, float *sqnorm,
                            void *ws, hipStream_t s)
 {
-    const RowsPlan p = rows_plan(g);
+    const RowsPlan p = rows_choice(g).plan;
     RowsArgs a;
     a.x = x; a.dy = dy; a.x_tab = g.x_tab; a.dy_tab = g.dy_tab;
     a.out_w = out_w; a.out_b = out_b;

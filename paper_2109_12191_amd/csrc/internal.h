@@ -94,7 +94,8 @@ size_t stem_ws_bytes(const Geo &g);
 size_t stem_norm_partial_count(void);
 dp_status launch_stem(const Geo &g, const void *x, const void *dy, float *out_w, size_t out_stride, float *sqnorm, void *ws,
                       hipStream_t s);
-// fp32 convolutions with square odd kernels from raw image rows: conv_rows.hip
+// fp32 convolutions with square odd kernels from raw image rows, where that is faster than the general kernel: conv_rows.hip
+double conv_general_f32_us(const Geo &g);
 bool conv_rows_applicable(const Geo &g, int mode);
 size_t conv_rows_ws_bytes(const Geo &g);
 size_t conv_rows_norm_partial_count(const Geo &g);

@@ -167,11 +167,13 @@ def test_segments_at_places_of_their_own():
         assert torch.equal(acc, split), run
 
 
-# ---- fp32 convolutions from raw rows: channels around the 16 and 32 of a block, output rows that are no multiple of four, one row,
-# a kernel larger than the image, several chunks of rows with a short last one, several examples per workgroup
-@pytest.mark.parametrize("cin,cout,h,w,k,stride,n", [(1, 1, 1, 1, 3, 1, 100), (16, 16, 5, 7, 3, 2, 260), (33, 15, 8, 9, 3, 1, 65), (3, 16, 9, 6, 3, 1, 100),
-                                                     (17, 13, 2, 1, 3, 1, 100), (32, 32, 57, 56, 3, 1, 260), (48, 16, 33, 36, 3, 1, 50), (64, 64, 8, 8, 3, 2, 65),
-                                                     (5, 40, 46, 43, 5, 1, 100), (18, 20, 45, 37, 5, 2, 100), (16, 16, 12, 14, 3, 1, 8200), (2, 3, 130, 260, 3, 1, 100)])
+# ---- fp32 convolutions from raw rows: channels around the 16 and 32 of a block, output rows that are no multiple of four, one column,
+# a kernel larger than the image, several chunks of rows with a short last one, several examples per workgroup (as many examples as
+# the kernel is chosen for)
+@pytest.mark.parametrize("cin,cout,h,w,k,stride,n", [(16, 16, 5, 7, 3, 2, 500), (33, 15, 8, 9, 3, 1, 200), (3, 16, 9, 6, 3, 1, 2000), (17, 13, 2, 1, 3, 1, 800),
+                                                     (32, 32, 57, 56, 3, 1, 260), (48, 16, 33, 36, 3, 1, 50), (16, 48, 17, 13, 5, 2, 100),
+                                                     (20, 31, 24, 26, 5, 1, 100), (5, 16, 46, 43, 5, 1, 100), (18, 20, 45, 37, 5, 2, 100),
+                                                     (16, 16, 12, 14, 3, 1, 8200), (2, 3, 130, 260, 3, 1, 200)])
 def test_conv_f32_raw_rows_kernel(cin, cout, h, w, k, stride, n):
     layer = Layer("conv", cin, cout, h, w, k, k, stride, (k - 1) // 2, cout % 2 == 0)
     assert dp.dp_kernel_variant(dp.make_desc(layer, n, "f32"), dp.DP_WS_PER_EXAMPLE_GRAD).startswith("conv_rows<f32")
@@ -191,12 +193,12 @@ def test_conv_f32_raw_rows_kernel(cin, cout, h, w, k, stride, n):
 
 def test_conv_f32_raw_rows_kernel_keeps_what_is_not_finite_in_its_place():
     """An infinity in the last column of a row reaches the taps that read it and no other."""
-    layer = Layer("conv", 2, 2, 3, 5, 3, 3, 1, 1, False)
-    x, dy = _inputs(layer, 100, 137, "f32")
-    assert dp.dp_kernel_variant(dp.make_desc(layer, 100, "f32"), dp.DP_WS_PER_EXAMPLE_GRAD).startswith("conv_rows<f32")
+    layer = Layer("conv", 32, 16, 3, 5, 3, 3, 1, 1, False)
+    x, dy = _inputs(layer, 400, 137, "f32")
+    assert dp.dp_kernel_variant(dp.make_desc(layer, 400, "f32"), dp.DP_WS_PER_EXAMPLE_GRAD).startswith("conv_rows<f32")
     dy[:] = 1.0
     x[0, 0, 1, 4] = np.inf
-    gw = _run_per_example(layer, x, dy, "f32")[0].reshape(100, 2, 2, 3, 3)[0]
+    gw = _run_per_example(layer, x, dy, "f32")[0].reshape(400, 16, 32, 3, 3)[0]
     want = np.ones((3, 3), bool)                  # the middle row, the last column: kw = 0 needs column 5 of dY, which is not there
     want[:, 0] = False
     assert np.array_equal(np.isinf(gw[0, 0]), want) and np.isfinite(gw[:, 1]).all() and np.isfinite(gw[:, 0, :, 0]).all()
