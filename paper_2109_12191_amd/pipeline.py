@@ -27,14 +27,20 @@ import torch
 
 from . import binding as B
 
-# Micro-steps are issued together as long as a phase reads no more than this many bytes of inputs: long launches gain nothing from
-# growing further, and addresses cost the 3x3 kernels a little.  MI355X, us per step with 1 / 2 / 4 / 8 micro-steps per phase:
-# ResNet-18-GN 8 x 32 examples (0.17 GB each) 2111 / 1940 / 1749 / 1662; ResNet-50 8 x 32 (1.39 GB each) 7597 / 7762 / 8308;
-# ResNet-50-GN at 200 x 200, 3 x 12 (0.85 GB each) 2791 / 2651, three 2557; ResNet-50 64 x 1 (0.04 GB each) in phases of
-# 16 / 32 / 64: 2606 / 2202 / 2174 against 11400 one by one.
-PHASE_BYTES = 2.6e9
-PHASE_EXAMPLES = 256           # and examples
-PHASE_EXAMPLES_STORED = 64     # micro-steps of one or two examples, which store every gradient
+# Which micro-steps are issued together (a phase): it saves launches and fills the chip where a micro-step is small.  MI355X, us per
+# step of four micro-steps on eight streams, one by one / in phases, on both sides of each line:
+#   a micro-step that reads more than this fills the chip by itself.  ResNet-50 with 24 examples (1.05 GB) 3141 / 2999, 28 (1.22 GB)
+#   3613 / 3500; 32 (1.39 GB) 3853 / 3999, 40 (1.74 GB) 4656 / 4927; at 192 x 192, 40 examples (1.28 GB) 5013 / 5245
+PHASE_MICRO_STEP_BYTES = 1.25e9
+#   examples of a phase.  ResNet-20, 64 examples a micro-step: phases of 128 / 256 901 / 757; 128: phases of 256 / 512 1478 / 1506; 256: one
+#   by one / 512 2755 / 2966.  ResNet-18-GN, 48 (8 micro-steps): one by one / 192 / 384 2840 / 2470 / 2556; 64: 256 / 512 3223 / 7084
+PHASE_EXAMPLES = 256
+#   and of micro-steps of one or two examples, which store every gradient.  ResNet-50, 64 x 1: one by one / 16 / 32 / 64 9783 / 4550 /
+#   4314 / 4105; 32 x 2: 8068 / 4546 (16) / 4317 / 4102
+PHASE_EXAMPLES_STORED = 64
+# And no phase is so large that a layer falls back to the kernel that gathers its operands element by element, because the rewritten
+# operands of a faster one outgrow their share of the workspace: ResNet-18-GN at 40 x 40, 64 examples 3656 / 5083 (two micro-steps) / 7188
+# (four), 24 (8 micro-steps): 3097 / 3028 (four) / 3825 (eight).
 # What a phase may hold in stored gradients, norms and workspaces, all copies together (4 % of the card's memory); a single
 # micro-step takes what it needs.
 PHASE_STORE_BYTES = 12e9
@@ -338,16 +344,31 @@ class PrivatiseStep:
     def _micro_steps_together(self) -> int:
         """Micro-steps per phase, at most."""
         wl = self.wl
-        per_micro_step = max(1, sum(self._example_bytes)) * wl.n
-        most = max(1, min(int(PHASE_BYTES // per_micro_step), (PHASE_EXAMPLES_STORED if wl.n <= 2 else PHASE_EXAMPLES) // wl.n))
+        if sum(self._example_bytes) * wl.n > PHASE_MICRO_STEP_BYTES:
+            return 1
+        most = max(1, (PHASE_EXAMPLES_STORED if wl.n <= 2 else PHASE_EXAMPLES) // wl.n)
         matrix = 4 * (wl.n // self.clip_unit) * self.p_mat
         phases = max(1, -(-wl.accum // most))
+        alone = None
         while True:
             size = max(1, -(-wl.accum // phases))
+            if size == 1:
+                return 1
             copies = self.copies if phases > 1 else 1
-            if size == 1 or copies * (size * matrix + self._workspace_bytes(size)) <= PHASE_STORE_BYTES:
-                return size
+            if copies * (size * matrix + self._workspace_bytes(size)) <= PHASE_STORE_BYTES:
+                alone = alone or self._gathers(1)
+                if not any(now and not before for now, before in zip(self._gathers(size), alone)):
+                    return size
             phases += 1
+
+    def _gathers(self, tensors: int) -> List[bool]:
+        """Which calls of a phase of `tensors` micro-steps run the gathering kernel: per layer the per-example and the recomputing one."""
+        flags = []
+        for d, form in zip(self._workspaces(tensors)[0], self.form):
+            stored = B.DP_VARIANT_MATERIALISE if form == "materialise" else 0
+            flags.append("gather" in B.dp_kernel_variant(d, B.DP_WS_PER_EXAMPLE_GRAD | B.DP_VARIANT_SHARED | stored))
+            flags.append(form == "recompute" and "gather" in B.dp_kernel_variant(d, B.DP_WS_RECOMPUTE | B.DP_VARIANT_SHARED))
+        return flags
 
     def _phase_sizes(self, micro_steps: int) -> List[int]:
         """How many micro-steps each phase of a step of `micro_steps` holds: as few phases as the bounds allow, of nearly equal

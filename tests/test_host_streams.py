@@ -281,3 +281,18 @@ def test_a_phase_is_bounded_by_what_it_holds(order, monkeypatch, name, n, accum,
         size, copies = ps.micro_steps_per_phase, len(ps._main.stores)
         assert size == 1 or copies * (4 * ps._main.rows * ps.p_mat + ps._workspace_bytes(size)) <= bound
         assert copies == (ps.copies if size == 1 or accum > size else 1)
+
+
+# micro-steps per phase on both sides of the lines that decide it
+@pytest.mark.parametrize("name,n,accum,hw,want", [
+    ("resnet50", 28, 4, 224, 4), ("resnet50", 32, 4, 224, 1), ("resnet50", 40, 4, 192, 1), ("resnet50", 16, 8, 224, 4), ("resnet50", 40, 4, 160, 2),
+    ("resnet20", 64, 4, 32, 4), ("resnet20", 128, 4, 32, 2), ("resnet20", 256, 4, 32, 1), ("resnet18_gn", 64, 8, 32, 4),
+    ("resnet18_gn", 24, 8, 40, 4), ("resnet18_gn", 48, 4, 40, 2), ("resnet18_gn", 64, 4, 40, 1), ("resnet18_gn", 96, 4, 24, 1),
+    ("resnet50_nano", 1, 64, 224, 64), ("resnet50_nano", 1, 1024, 224, 47)])
+def test_micro_steps_per_phase(order, name, n, accum, hw, want):
+    wl = get_workload(name, n=n, accum=accum, hw=hw)
+    ps = dp.PrivatiseStep(wl, device="cpu", streams=8)
+    size = ps.micro_steps_per_phase
+    assert size == want and ps._phase_sizes(accum)[0] == size
+    alone, together = ps._gathers(1), ps._gathers(size)
+    assert not any(now and not before for now, before in zip(together, alone))      # no layer loses its kernel
