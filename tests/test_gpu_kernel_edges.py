@@ -69,6 +69,23 @@ def test_dense_token_kernels(tokens, cin, cout, n, dtype):
     assert_close(acc_b, 1.0 + (f[:, None] * ref_b).sum(0), F32_TOL, "acc_b")
 
 
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("tokens", [1, 3, 16, 70])
+def test_dense_weighted_sum_leaves_out_an_example_that_overflows(tokens, dtype):
+    """Finite inputs whose gradient does not fit fp32: the squared norm is infinite, the factor 0, and the sum is that of the others."""
+    layer, n = dense(66, 70, tokens=tokens), 4
+    x, dy = _inputs(layer, n, 119, dtype)
+    ref_w, ref_b, ref_n2 = _oracle_grads(layer, x, dy)
+    x[1], dy[1] = 2.0 ** 127, 2.0 ** 127
+    n2 = ref_n2.copy()
+    n2[1] = np.inf
+    clip_c = float(np.sqrt(np.median(ref_n2)))
+    f = np.array([oracle.clip_factor(float(v), clip_c) if np.isfinite(v) else 0.0 for v in n2])
+    acc_w, acc_b = _run_weighted(layer, x, dy, dtype, n2, clip_c)
+    assert_close(acc_w, 1.0 + (f[:, None] * ref_w).sum(0), F32_TOL, "acc_w")
+    assert_close(acc_b, 1.0 + (f[:, None] * ref_b).sum(0), F32_TOL, "acc_b")
+
+
 # ---- examples in several tensors (dp_example_addresses and the *_at calls): every kernel family, rows that start on odd
 # elements, one example per tensor and several; the numbers are those of one tensor, bit for bit
 def _addresses(tensors, n_per, example_bytes):
