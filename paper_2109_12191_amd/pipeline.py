@@ -20,8 +20,7 @@ late ones (many parameters, tiny feature maps) recompute.
 """
 from __future__ import annotations
 
-import ctypes
-from typing import List, Optional, Sequence
+from typing import Iterable, List, Optional, Sequence
 
 import torch
 
@@ -504,7 +503,8 @@ class PrivatiseStep:
         accumulator in the same order on every run: each tensor is updated by one call per
         phase, issued on the same stream by every phase of one plan and behind all clipped sums of the phase before where the
         plan changes."""
-        self._issue(self._plan(1), [x.data_ptr() for x, _ in inputs], [dy.data_ptr() for _, dy in inputs])
+        layers = range(len(self.layers))
+        self._issue(self._plan(1), [inputs[i][0].data_ptr() for i in layers], [inputs[i][1].data_ptr() for i in layers])
 
     def _issue(self, plan: _Plan, x: Sequence[int], dy: Sequence[int]):
         """The two phases of plan.tensors micro-steps; x, dy: per layer the address of the tensor, or of its array of example
@@ -668,18 +668,25 @@ class PrivatiseStep:
                 self._issue(self._plan(size), [base + row * 2 * i for i in range(L)], [base + row * (2 * i + 1) for i in range(L)])
             first += size
 
-    def run(self, inputs_per_micro_step: Sequence[Sequence]):
+    def run(self, inputs_per_micro_step: Iterable[Sequence]):
+        """One optimiser step.  A list or tuple holds the inputs of all micro-steps, which may then be issued together; from anything
+        else they are taken, and issued, one by one (whoever makes them may use the same tensors again for the next)."""
         self.begin_step()
-        self._issue_step(inputs_per_micro_step)
+        if isinstance(inputs_per_micro_step, (list, tuple)):
+            self._issue_step(inputs_per_micro_step)
+        else:
+            for inputs in inputs_per_micro_step:
+                self.micro_step(inputs)
         self.finalize()
         return self.out
 
-    def capture(self, inputs_per_micro_step: Sequence[Sequence]):
+    def capture(self, inputs_per_micro_step: Iterable[Sequence]):
         """Record one whole optimiser step on these (persistent) input tensors into a HIP graph:
         replay() then re-issues every launch without host work.  Only kernels are recorded (the
         accumulator is cleared by a fill kernel, never by a memset node)."""
         assert self.probe is None or not getattr(self.probe, "enabled", False)
         step0 = self.step
+        inputs_per_micro_step = list(inputs_per_micro_step)
         self.run(inputs_per_micro_step)          # warm-up outside capture (lazy module loads)
         sizes = self._phase_sizes(len(inputs_per_micro_step))
         table = None

@@ -296,3 +296,25 @@ def test_micro_steps_per_phase(order, name, n, accum, hw, want):
     assert size == want and ps._phase_sizes(accum)[0] == size
     alone, together = ps._gathers(1), ps._gathers(size)
     assert not any(now and not before for now, before in zip(together, alone))      # no layer loses its kernel
+
+
+def test_micro_steps_from_a_generator_are_taken_one_by_one(order, monkeypatch):
+    """run() takes any iterable; one that is no list may hand over the same tensors again and again, so nothing is read ahead."""
+    wl = get_workload("resnet20", n=4, accum=5, hw=32)
+    ps = dp.PrivatiseStep(wl, device="cpu")
+    assert ps.micro_steps_per_phase == 5
+    seen = []
+    call = pipeline.B.dp_norms_from_partials
+    monkeypatch.setattr(pipeline.B, "dp_norms_from_partials", lambda *a, **k: (seen.append("issued"), call(*a, **k)))
+
+    def micro_steps():
+        for _ in range(5):
+            seen.append("made")
+            # (an entry may say more than (x, dy), and layers may be looked up by number)
+            yield {i: (_Tensor(), _Tensor(), "more") for i in range(len(wl.layers))}
+
+    ps.run(micro_steps())
+    assert seen == ["made", "issued"] * 5 and ps.micro_steps_done == 5
+    del seen[:]
+    ps.run(tuple(_steps(wl, 5)))
+    assert seen == ["issued"]
