@@ -239,7 +239,7 @@ def main():
                                   for k, v in sorted(contraction.items(), key=lambda kv: -at_roof(kv[1]))],
                         measured="HIP events recorded by the library around each launch of this kernel, on its stream, "
                                  "in a call-by-call single-stream pass over the same steps right after the timed region")
-    # The streaming kernels of the step, each launched as the step launches it (same buffers, same sizes) and
+    # The streaming kernels of the step, each launched as a step of single micro-steps launches it (same buffers, same sizes) and
     # bracketed by events on its stream: H4a, the clip-scale-accumulate pass over the materialised gradients of one
     # micro-step, and H5, noise + finalize over the whole parameter vector in one launch.
     streaming = {}
@@ -259,7 +259,7 @@ def main():
         k = [0]
         def _ca():
             k[0] += 1
-            dp.dp_clip_accumulate(g_bufs[k[0] % len(g_bufs)], pe._group_sqnorm[0][0], pe.group_clip[0], pe.rows, pe.p_mat,
+            dp.dp_clip_accumulate(g_bufs[k[0] % len(g_bufs)], pe.group_sqnorm[0], pe.group_clip[0], pe.rows, pe.p_mat,
                                   pe.acc, g_stride=pe.p_mat)
         sec = _time_stream(_ca)
         nbytes = 4.0 * pe.rows * pe.p_mat + 8.0 * pe.p_mat

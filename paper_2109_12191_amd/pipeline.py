@@ -108,14 +108,7 @@ class _Plan:
                         for d, form in zip(self.descs, self.form)]
         self.partials = [B.PartialTable(self.ws[c], [1] * L, ps.group_of_layer)
                          for c in range(len(stores))]
-        esize = 2 if wl.dtype == "bf16" else 4
-        # algorithmic work of one call per layer: (flop, HBM bytes of the per-example call, HBM bytes of the
-        # recomputing clipped-sum call).  Bytes = the operands read once, plus the per-example gradients
-        # written when the layer materialises them, or the accumulator read and written by form (b).
-        self.work = [(l.flops * self.n,
-                      l.in_bytes(esize) * self.n + (4 * self.n * (pw + pb) if form == "materialise" else 0),
-                      l.in_bytes(esize) * self.n + 8 * (pw + pb))
-                     for l, pw, pb, form in zip(self.layers, ps.pw, ps.pb, self.form)]
+        self.work = ps._work(tensors)
         self.groups_a = self._make_groups(range(L), 0) if ps.clip_unit == 1 else []
         self.groups_b = self._make_groups([i for i in range(L) if self.form[i] == "recompute"], 1)
         self.groups_u = self._make_groups(range(L), 2) if ps.clip_unit > 1 else []
@@ -236,6 +229,7 @@ class PrivatiseStep:
             raise ValueError("the micro-step size must be a multiple of clip_unit")
         if self.clip_unit > 1 and noise != "once":
             raise ValueError("per-example noise is defined for units of one example")
+        self.rows = wl.n // self.clip_unit         # of a micro-step
         L = len(self.layers)
         descs = [B.make_desc(l, wl.n, wl.dtype) for l in self.layers]
         self.pw = [B.dp_weight_count(d) for d in descs]
@@ -309,11 +303,10 @@ class PrivatiseStep:
         self._update = None                      # (lr, momentum, keep_gradient)
         self._addresses = None                   # (stream, example addresses) of a step that is issued call by call
         self._recorded_addresses = []            # and those of steps that a caller records in a graph of its own
-        self._last = 0                           # copy used by the most recent micro-step
         self._phases = 0                         # phases issued since begin_step
         self._sum_plan = None                    # plan of the last of them
-        self._group_sqnorm = [torch.zeros((self.n_groups, wl.n // self.clip_unit), dtype=f32, device=dev)
-                              for _ in range(self.copies)]         # of the last micro-steps (one per copy)
+        self._last_sqnorm = torch.zeros((self.n_groups, self.rows), dtype=f32, device=dev)
+        self._group_sqnorm = self._last_sqnorm   # of the most recent micro-step
         self._g_last = None
         self.graph = None
         self.micro_steps_done = 0
@@ -325,6 +318,16 @@ class PrivatiseStep:
         # optional timing probe (bench.py): an object with arm(variant, flops, bytes) that asks the
         # library to bracket the next contraction kernel with a pair of events
         self.probe = None
+
+    def _work(self, tensors: int):
+        """Algorithmic work of one call per layer: (flop, HBM bytes of the per-example call, HBM bytes of the
+        recomputing clipped-sum call).  Bytes = the operands read once, plus the per-example gradients
+        written when the layer materialises them, or the accumulator read and written by the recomputing form."""
+        n, esize = self.wl.n * tensors, 2 if self.wl.dtype == "bf16" else 4
+        return [(l.flops * n,
+                 l.in_bytes(esize) * n + (4 * n * (pw + pb) if form == "materialise" else 0),
+                 l.in_bytes(esize) * n + 8 * (pw + pb))
+                for l, pw, pb, form in zip(self.layers, self.pw, self.pb, self.form)]
 
     def _workspaces(self, tensors: int):
         """Descriptors and workspace bytes of every layer in a phase of `tensors` micro-steps."""
@@ -346,7 +349,7 @@ class PrivatiseStep:
         if sum(self._example_bytes) * wl.n > PHASE_MICRO_STEP_BYTES:
             return 1
         most = max(1, (PHASE_EXAMPLES_STORED if wl.n <= 2 else PHASE_EXAMPLES) // wl.n)
-        matrix = 4 * (wl.n // self.clip_unit) * self.p_mat
+        matrix = 4 * self.rows * self.p_mat
         phases = max(1, -(-wl.accum // most))
         alone = None
         while True:
@@ -387,23 +390,25 @@ class PrivatiseStep:
                 if tensors <= room:
                     if self._stores[c] is None:
                         ws = self._workspace_bytes(1) if room == 1 else self._ws_room
-                        self._stores[c] = _Store(self, room * (self.wl.n // self.clip_unit), ws)
+                        self._stores[c] = _Store(self, room * self.rows, ws)
                     stores.append(self._stores[c])
             self._plans[tensors] = _Plan(self, tensors, stores)
         return self._plans[tensors]
 
-    # ---- what a phase of a whole step looks like (tests, bench.py)
+    # ---- one micro-step
     @property
-    def rows(self):
-        return self._main.rows
+    def descs(self):
+        return self._workspaces(1)[0]
 
     @property
     def work(self):
-        return self._main.work
+        """Per layer: flop of one call, HBM bytes of the per-example call, HBM bytes of the recomputing clipped-sum call."""
+        return self._work(1)
 
     @property
     def _g(self):
-        return self._main.g
+        """The gradient matrices; a micro-step's rows are the first ones of a phase."""
+        return [st.g if st is not None else None for st in self._stores]
 
     @property
     def micro_steps_per_phase(self):
@@ -456,7 +461,7 @@ class PrivatiseStep:
     @property
     def group_sqnorm(self) -> torch.Tensor:
         """[groups, n] squared norms of the most recent micro-step."""
-        return self._group_sqnorm[self._last]
+        return self._group_sqnorm
 
     @property
     def g(self) -> Optional[torch.Tensor]:
@@ -506,9 +511,9 @@ class PrivatiseStep:
         layers = range(len(self.layers))
         self._issue(self._plan(1), [inputs[i][0].data_ptr() for i in layers], [inputs[i][1].data_ptr() for i in layers])
 
-    def _issue(self, plan: _Plan, x: Sequence[int], dy: Sequence[int]):
+    def _issue(self, plan: _Plan, x: Sequence[int], dy: Sequence[int], ends_step: bool = True):
         """The two phases of plan.tensors micro-steps; x, dy: per layer the address of the tensor, or of its array of example
-        addresses."""
+        addresses.  ends_step: a caller may look at the last micro-step's norms afterwards."""
         at = plan.tensors > 1
         L = len(self.layers)
         gs = self.p_mat
@@ -582,11 +587,13 @@ class PrivatiseStep:
                 ev.record(st)
                 evs.append(ev)
             store.done = evs
-        rows = self.wl.n // self.clip_unit             # of a micro-step
-        for k in range(max(0, plan.tensors - self.copies), plan.tensors):
-            self._last = (self.micro_steps_done + k) % self.copies
-            self._group_sqnorm[self._last] = gsq[:, k * rows:(k + 1) * rows]
-        self._g_last = g_buf[-rows:] if g_buf is not None else None
+        # the last micro-step's norms are a matrix of their own, as its callers read it
+        self._group_sqnorm = gsq[:, -self.rows:]
+        if not self._group_sqnorm.is_contiguous():
+            if ends_step:
+                self._last_sqnorm.copy_(self._group_sqnorm)
+            self._group_sqnorm = self._last_sqnorm
+        self._g_last = g_buf[-self.rows:] if g_buf is not None else None
         self.micro_steps_done += plan.tensors
         self._phases += 1
 
@@ -665,7 +672,8 @@ class PrivatiseStep:
                 self.micro_step(steps[first])
             else:
                 base, row = table.data_ptr() + 8 * 2 * L * n * first, 8 * n * size
-                self._issue(self._plan(size), [base + row * 2 * i for i in range(L)], [base + row * (2 * i + 1) for i in range(L)])
+                self._issue(self._plan(size), [base + row * 2 * i for i in range(L)], [base + row * (2 * i + 1) for i in range(L)],
+                            ends_step=first + size == len(steps))
             first += size
 
     def run(self, inputs_per_micro_step: Iterable[Sequence]):

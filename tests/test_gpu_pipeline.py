@@ -306,3 +306,25 @@ def test_two_recorded_steps_and_one_that_the_caller_records():
             graph.replay()
             torch.cuda.synchronize()
             assert torch.equal(ps.out, out) and all(bool((f == -1).all()) for f in fill)
+
+
+@pytest.mark.parametrize("name,n,accum,streams", [("resnet50_nano", 1, 5, 1), ("resnet50_nano", 1, 5, 3), ("conv3x3", 4, 3, 2)])
+def test_norms_of_the_last_micro_step(name, n, accum, streams):
+    """group_sqnorm after a step whose micro-steps were issued together: a contiguous matrix, the last micro-step's numbers, eager and
+    replayed."""
+    wl = get_workload(name, n=n, accum=accum, hw=32)
+    steps = [[(dev(x, wl.dtype), dev(dy, wl.dtype)) for x, dy in make_inputs(wl, m)] for m in range(accum)]
+    single, ps = dp.PrivatiseStep(wl), dp.PrivatiseStep(wl, streams=streams)
+    assert ps.micro_steps_per_phase == accum
+    single.begin_step()
+    for inputs in steps:
+        single.micro_step(inputs)
+    want = single.group_sqnorm.clone()
+    ps.run(steps)
+    assert ps.group_sqnorm.is_contiguous() and ps.group_sqnorm.shape == want.shape
+    assert torch.allclose(ps.group_sqnorm, want, rtol=1e-5, atol=0.0)
+    ps.capture(steps)
+    for _ in range(3):
+        ps.group_sqnorm.zero_()
+        ps.replay()
+        assert torch.allclose(ps.group_sqnorm, want, rtol=1e-5, atol=0.0)

@@ -318,3 +318,18 @@ def test_micro_steps_from_a_generator_are_taken_one_by_one(order, monkeypatch):
     del seen[:]
     ps.run(tuple(_steps(wl, 5)))
     assert seen == ["issued"]
+
+
+@pytest.mark.parametrize("streams", [1, 4])
+def test_what_a_step_shows_is_one_micro_steps(order, streams):
+    """Norms, rows and work are those of a micro-step, the norms a matrix of their own, however many micro-steps share a phase."""
+    wl = get_workload("resnet50_nano", accum=8, hw=64)
+    ps = dp.PrivatiseStep(wl, device="cpu", streams=streams)
+    assert ps.micro_steps_per_phase == 8 and ps.rows == 1 and ps.work[0][0] == wl.layers[0].flops and ps.descs[0].n == 1
+    for run in (lambda: ps.run(_steps(wl, 8)), lambda: ps.micro_step(_steps(wl, 1)[0]), lambda: ps.run(_steps(wl, 3))):
+        run()
+        assert ps.group_sqnorm.shape == (wl.n_groups, 1) and ps.group_sqnorm.is_contiguous() and ps.g.shape == (1, ps.p_mat)
+    # and of the last micro-step of the last phase
+    ps._plan(8).group_sqnorm[0].copy_(torch.arange(wl.n_groups * 8, dtype=torch.float32).view(wl.n_groups, 8))
+    ps.run(_steps(wl, 8))
+    assert torch.equal(ps.group_sqnorm[:, 0], torch.arange(wl.n_groups, dtype=torch.float32) * 8 + 7)
