@@ -153,7 +153,7 @@ dp_status dp_per_example_grad(const dp_layer_desc *desc /*[host]*/, const void *
  * dp_static_scratch_bytes() = 32 MiB per GPU, held from the first call on a GPU until the process ends.
  * Same kernels, same results (bit for bit) as dp_per_example_grad.  The stream's device must be the
  * current device.  A layer whose dp_workspace_bytes(desc, DP_WS_PER_EXAMPLE_GRAD) exceeds the built-in
- * size -> DP_ERR_WORKSPACE (nothing is launched).  Every call on one GPU shares that GPU's array:
+ * size -> DP_ERR_WORKSPACE (nothing is launched); a dense layer only if 4 n ceil(cin / 256) ceil(cout / 16) bytes do.  Every call on one GPU shares that GPU's array:
  * calls that overlap in time on one GPU (different streams, different host threads) race; issue them
  * on one stream, or order them with events.  Nothing in the array has to start at zero or survive
  * between calls.  Calls no hipMalloc / hipFree or other allocating routine.                        */

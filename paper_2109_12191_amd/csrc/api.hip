@@ -101,7 +101,7 @@ static bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 
 
 // Validate a descriptor and derive its geometry.  Limits keep every index in 32 bits inside
 // the kernels: per-example tensors below 2^31 elements.
-static dp_status make_geo(const dp_layer_desc *d, Geo &g)
+dp_status make_geo(const dp_layer_desc *d, Geo &g)
 {
     if (!d) return fail(DP_ERR_INVALID_ARG, "descriptor is NULL");
     if (d->kind != DP_DENSE && d->kind != DP_CONV2D && d->kind != DP_GN_AFFINE)

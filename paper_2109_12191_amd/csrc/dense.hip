@@ -13,6 +13,7 @@
 #include "group.h"
 #include "pieces.h"
 
+#include <algorithm>
 #include <atomic>
 
 namespace dp {
@@ -501,10 +502,17 @@ size_t dense_norm_partial_count(const Geo &g, int mode)
     }
 }
 
+// A slot for every OUTER_ROWS x 256 of the gradient: the layers that the entry point with built-in scratch takes
+size_t dense_scratch_bytes(const Geo &g)
+{
+    return (size_t)g.n * ((g.cin + 255) / 256) * ((g.cout + OUTER_ROWS - 1) / OUTER_ROWS) * sizeof(float);
+}
+
 size_t dense_ws_bytes(const Geo &g, int mode)
 {
     if (mode == MODE_WEIGHTED) return 0;
-    return (size_t)g.n * dense_norm_partial_count(g, MODE_MATERIALISE) * sizeof(float);      // (norm-only calls: no more)
+    const size_t need = (size_t)g.n * dense_norm_partial_count(g, MODE_MATERIALISE) * sizeof(float);      // (norm-only calls: no more)
+    return std::max(need, dense_scratch_bytes(g));
 }
 
 dp_status launch_dense(const Geo &g, int mode, const void *x, const void *dy, float *out_w, float *out_b,

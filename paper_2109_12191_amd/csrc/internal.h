@@ -108,6 +108,8 @@ size_t gram_norm_partial_count(void);
 dp_status launch_gram_norm(const Geo &g, const void *x, const void *dy, float *sqnorm, void *ws, hipStream_t s);
 
 size_t dense_ws_bytes(const Geo &g, int mode);
+size_t dense_scratch_bytes(const Geo &g);
+dp_status make_geo(const dp_layer_desc *d, Geo &g);      // api.hip: validates a descriptor and derives its geometry
 dp_status launch_dense(const Geo &g, int mode, const void *x, const void *dy, float *out_w, float *out_b,
                        size_t out_stride, float *sqnorm, const float *group_sqnorm, float clip_c, void *ws,
                        hipStream_t s);

@@ -46,13 +46,29 @@ dp_status dp_per_example_grad_static(const dp_layer_desc *desc, const void *x, c
                                      size_t g_stride, float *sqnorm, dp_stream stream)
 {
     const size_t need = dp_workspace_bytes(desc, DP_WS_PER_EXAMPLE_GRAD);     // 0 on a bad descriptor: reported below
-    if (need > SCRATCH_BYTES)
+    // A dense layer of several tokens may need more (a slot for every 64 x 64 of the gradient) than what decides whether it is
+    // taken: then its examples go through the scratch a piece at a time, which changes none of their numbers.
+    int piece = need ? desc->n : 0;
+    dp::Geo g;
+    if (need > SCRATCH_BYTES && dp::make_geo(desc, g) == DP_OK && g.kind == DP_DENSE && dp::dense_scratch_bytes(g) <= SCRATCH_BYTES)
+        piece = (int)(SCRATCH_BYTES / (need / (size_t)desc->n)) & ~7;          // (eight examples keep every address 16-byte aligned)
+    if (need > SCRATCH_BYTES && (piece == desc->n || piece < 8))
         return dp::fail(DP_ERR_WORKSPACE, "this layer needs %zu bytes of workspace, the built-in scratch holds %zu; "
                         "use dp_per_example_grad with a caller-owned workspace", need, SCRATCH_BYTES);
     void *ws = nullptr;
-    const dp_status st = scratch_of_current_device(&ws);
+    dp_status st = scratch_of_current_device(&ws);
     if (st != DP_OK) return st;
-    return dp_per_example_grad(desc, x, dy, g_w, g_b, g_stride, sqnorm, ws, SCRATCH_BYTES, stream);
+    if (need <= SCRATCH_BYTES) return dp_per_example_grad(desc, x, dy, g_w, g_b, g_stride, sqnorm, ws, SCRATCH_BYTES, stream);
+    const size_t es = g.bf16 ? 2 : 4, row_w = g_stride ? g_stride : g.pw, row_b = g_stride ? g_stride : g.pb;
+    for (int i = 0; i < g.n; i += piece) {
+        dp_layer_desc part = *desc;
+        part.n = g.n - i < piece ? g.n - i : piece;
+        st = dp_per_example_grad(&part, x ? static_cast<const char *>(x) + i * g.x_elems * es : nullptr,
+                                 dy ? static_cast<const char *>(dy) + i * g.dy_elems * es : nullptr, g_w ? g_w + i * row_w : nullptr,
+                                 g_b ? g_b + i * row_b : nullptr, g_stride, sqnorm ? sqnorm + i : nullptr, ws, SCRATCH_BYTES, stream);
+        if (st != DP_OK) return st;
+    }
+    return DP_OK;
 }
 
 }  // extern "C"

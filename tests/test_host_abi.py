@@ -289,3 +289,14 @@ def test_arrays_of_example_addresses_need_the_alignment_of_a_word_only(lib):
             _raises(status, dp.dp_unit_grad_batch, batch, 3, x, dy, g, None, sq, addresses=True, stream=0)
             _raises(status, dp.dp_clip_accumulate_recompute_batch, batch, x, dy, sq, batch.floats([1.0]), g, None, addresses=True, stream=0)
             _raises(B.DP_ERR_INVALID_ARG, dp.dp_per_example_grad_batch, batch, x, dy, g, None, sq, stream=0)
+
+
+@pytest.mark.parametrize("cin,cout,tokens,n,fits", [(16384, 8, 2, 33000, True), (16384, 8, 2, 65535, True), (64, 2064, 2, 65535, False), (256, 16, 70, 65535, True),
+                                                    (512, 1040, 2, 65535, False), (70000, 16, 3, 30583, True), (70000, 16, 3, 30650, False)])
+def test_built_in_scratch_takes_dense_layers_by_slots_of_16_by_256(lib, cin, cout, tokens, n, fits):
+    """Whatever tiles the kernels use: a layer is taken when four bytes per example and 16 x 256 of its gradient fit the scratch."""
+    d = dp.make_desc(dense(cin, cout, tokens=tokens), n, "bf16")
+    assert (4 * n * -(-cin // 256) * -(-cout // 16) <= dp.dp_static_scratch_bytes()) == fits
+    with pytest.raises(dp.DpError) as ei:                     # (a call that is taken fails at the device or the misaligned pointer)
+        dp.dp_per_example_grad_static(d, FAKE + 8, FAKE, None, None, FAKE, stream=0)
+    assert (ei.value.status == 3) == (not fits), str(ei.value)

@@ -65,3 +65,20 @@ def test_static_scratch_entry_point_rejects_what_does_not_fit():
     with pytest.raises(dp.DpError) as ei:
         dp.dp_per_example_grad_static(big, x, x, None, None, x)
     assert ei.value.status == 3 and "built-in scratch" in str(ei.value)
+
+
+@pytest.mark.parametrize("dtype,n", [("bf16", 33000), ("f32", 32771)])
+def test_static_scratch_entry_point_takes_wide_dense_layers_in_pieces(dtype, n):
+    """16384 -> 8 over two tokens: one slot for every 64 x 64 of the gradient does not fit the scratch, the layer is taken all the same."""
+    d = dp.make_desc(dense(16384, 8, tokens=2), n, dtype)
+    assert dp.dp_workspace_bytes(d) > dp.dp_static_scratch_bytes()
+    t = torch.bfloat16 if dtype == "bf16" else torch.float32
+    gen = torch.Generator(device="cuda:0").manual_seed(5)
+    x = torch.randn((n, 2, 16384), generator=gen, device="cuda:0", dtype=t)
+    dy = torch.randn((n, 2, 8), generator=gen, device="cuda:0", dtype=t)
+    ws = torch.empty(dp.dp_workspace_bytes(d), dtype=torch.uint8, device="cuda:0")
+    want, got = torch.full((n,), -1.0, device="cuda:0"), torch.full((n,), -2.0, device="cuda:0")
+    dp.dp_per_example_grad(d, x, dy, None, None, want, ws)
+    dp.dp_per_example_grad_static(d, x, dy, None, None, got)
+    torch.cuda.synchronize()
+    assert torch.equal(got, want) and float(want.min()) > 0.0
