@@ -1903,9 +1903,9 @@ dp_status launch_conv(const Geo &g, int mode, const void *x, const void *dy, flo
         w += align16(pp.dy_bytes);
         const dp_status st = launch_pack_weighted(g, pp, x, dy, group_sqnorm, clip_c, xp, dyp, s);
         if (st != DP_OK) return st;
-        // the factors are already in dYp: an infinite bound makes the kernel's own factor 1
-        return launch_conv_impl(g2, mode, xp, dyp, out_w, out_b, out_stride, nullptr, group_sqnorm,
-                                __builtin_inff(), w, s);
+        // the factors are already in dYp: no norms, and the kernel's own factor is 1 (what it would read are examples' norms, not
+        // those of its example ranges)
+        return launch_conv_impl(g2, mode, xp, dyp, out_w, out_b, out_stride, nullptr, nullptr, __builtin_inff(), w, s);
     }
     if (subsampled(g, mode, g2)) {
         // the sub-problem's own workspace comes first (its partial norms stay at the start), the copy of X after it

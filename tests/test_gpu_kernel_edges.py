@@ -86,6 +86,21 @@ def test_dense_weighted_sum_leaves_out_an_example_that_overflows(tokens, dtype):
     assert_close(acc_b, 1.0 + (f[:, None] * ref_b).sum(0), F32_TOL, "acc_b")
 
 
+def test_packed_weighted_sum_keeps_the_neighbours_of_a_broken_example():
+    """Operands packed into ranges of examples: an example whose norm is infinite or no number leaves the sum, its range does not."""
+    layer, n = conv(64, 128, 3, 1, 13), 64
+    name = dp.dp_kernel_variant(dp.make_desc(layer, n, "bf16"), dp.DP_WS_RECOMPUTE)
+    assert name == "conv_contract<bf16,128x128,weighted>"
+    x, dy = _inputs(layer, 8, 121, "bf16")
+    ref_w, _, ref_n2 = _oracle_grads(layer, x, dy)
+    x, dy, ref_w, n2 = (np.concatenate([v] * 8) for v in (x, dy, ref_w, ref_n2))
+    n2[0], n2[3] = np.inf, np.nan
+    clip_c = float(np.sqrt(np.median(ref_n2)))
+    f = np.array([oracle.clip_factor(float(v), clip_c) if np.isfinite(v) else 0.0 for v in n2])
+    acc_w, _ = _run_weighted(layer, x, dy, "bf16", n2, clip_c)
+    assert_close(acc_w, 1.0 + (f[:, None] * ref_w).sum(0), BF16_TOL, "acc_w")
+
+
 # ---- examples in several tensors (dp_example_addresses and the *_at calls): every kernel family, rows that start on odd
 # elements, one example per tensor and several; the numbers are those of one tensor, bit for bit
 def _addresses(tensors, n_per, example_bytes):
