@@ -399,10 +399,9 @@ size_t conv_rows_ws_bytes(const Geo &g) { return cr_align16((size_t)(g.n / g.uni
 
 const char *conv_rows_variant_name(const Geo &g)
 {
-    static const char *const names[3][2] = {{"conv_rows<f32,1x1,per_example>", "conv_rows<f32,1x1,s2,per_example>"},
-                                            {"conv_rows<f32,3x3,per_example>", "conv_rows<f32,3x3,s2,per_example>"},
+    static const char *const names[2][2] = {{"conv_rows<f32,3x3,per_example>", "conv_rows<f32,3x3,s2,per_example>"},
                                             {"conv_rows<f32,5x5,per_example>", "conv_rows<f32,5x5,s2,per_example>"}};
-    return names[g.kh / 2][g.stride - 1];
+    return names[g.kh / 2 - 1][g.stride - 1];
 }
 
 dp_status launch_conv_rows(const Geo &g, const void *x, const void *dy, float *out_w, float *out_b, size_t out_stride, float *sqnorm,
@@ -420,11 +419,11 @@ dp_status launch_conv_rows(const Geo &g, const void *x, const void *dy, float *o
     a.rows = p.rows; a.chunks = p.chunks; a.rpr = p.rpr; a.xp = p.xp; a.cha = p.cha; a.chx = p.chx; a.tm = p.tm; a.tn = p.tn;
     a.bias = g.has_bias ? 1 : 0;
     const void *fn = g.kh == 3 ? rows_fn<3>(g.stride) : rows_fn<5>(g.stride);
-    static std::atomic<bool> attr_done[3][2];           // zero-initialised; setting the attribute twice is harmless
-    if (!attr_done[g.kh / 2][g.stride - 1].load()) {
+    static std::atomic<bool> attr_done[2][2];           // zero-initialised; setting the attribute twice is harmless
+    if (!attr_done[g.kh / 2 - 1][g.stride - 1].load()) {
         if (hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, 156 * 1024) != hipSuccess)
             return fail(DP_ERR_DEVICE, "conv_rows: cannot reserve LDS");
-        attr_done[g.kh / 2][g.stride - 1].store(true);
+        attr_done[g.kh / 2 - 1][g.stride - 1].store(true);
     }
     const long long total = (long long)((g.n + p.ex_per_wg - 1) / p.ex_per_wg) * p.tiles_m * p.tiles_n;
     const dp_status st = submit_main<RowsArgs>(fn, a, (unsigned)((total + 7) / 8 * 8), (unsigned)(64 * g.kh * p.q), p.lds, s, "conv_rows");
