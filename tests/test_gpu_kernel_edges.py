@@ -120,7 +120,9 @@ _SEVERAL = [
     ("3x3 rows s2", conv(64, 64, 3, 2, 28), "bf16"), ("3x3 general", conv(13, 70, 3, 1, 13), "bf16"),
     ("3x3 general s2 odd", conv(17, 33, 3, 2, 15, bias=True), "bf16"), ("5x5 stride 3", Layer("conv", 6, 10, 14, 17, 5, 5, 3, 2, True), "bf16"),
     ("tiny image", conv(3, 5, 3, 1, 3), "bf16"), ("stem", conv(3, 64, 7, 2, 64), "bf16"),
-    ("fp32 3x3", conv(12, 20, 3, 1, 11, bias=True), "f32"), ("fp32 1x1", conv(70, 90, 1, 1, 8), "f32"),
+    ("fp32 3x3", conv(12, 20, 3, 1, 11, bias=True), "f32"), ("fp32 rows 3x3", conv(16, 16, 3, 1, 32), "f32"),
+    ("fp32 rows 3x3 odd channels", conv(33, 15, 3, 1, 27, bias=True), "f32"), ("fp32 rows 5x5 s2", Layer("conv", 18, 20, 45, 37, 5, 5, 2, 2, True), "f32"),
+    ("fp32 1x1", conv(70, 90, 1, 1, 8), "f32"),
     ("dense", dense(100, 37), "bf16"), ("dense fp32", dense(33, 70), "f32"), ("dense tokens odd", dense(37, 61, tokens=3), "bf16"),
     ("dense tokens", dense(66, 70, tokens=70), "bf16"), ("dense tokens fp32", dense(33, 30, tokens=5), "f32"),
     ("gn", gn_affine(32, 9, 8), "bf16"), ("gn fp32", gn_affine(16, 8, 4), "f32"), ("gn wide", gn_affine(600, 3, 2), "bf16"),
@@ -130,8 +132,10 @@ _SEVERAL = [
 @pytest.mark.parametrize("n_per", [1, 3])
 @pytest.mark.parametrize("name,layer,dtype", _SEVERAL, ids=[c[0] for c in _SEVERAL])
 def test_examples_in_several_tensors(name, layer, dtype, n_per):
-    tensors = 33 if name in ("1x1 256x128", "1x1 whole rows") else 4          # (those kernels want 128 tiles)
+    tensors = 33 if name in ("1x1 256x128", "1x1 whole rows") else 120 if name.startswith("fp32 rows") else 4      # (those kernels want many tiles)
     n = tensors * n_per
+    if name.startswith("fp32 rows"):
+        assert dp.dp_kernel_variant(dp.make_desc(layer, n, dtype), dp.DP_WS_PER_EXAMPLE_GRAD).startswith("conv_rows<f32")
     x, dy = _inputs(layer, n, 131, dtype)
     xd, dyd = dev(x, dtype), dev(dy, dtype)
     es = 2 if dtype == "bf16" else 4
@@ -291,3 +295,34 @@ def test_units_in_the_per_example_kernels(unit, units):
                     n2 = oracle.sqnorm(ref_w) + (oracle.sqnorm(ref_b) if layer.pb else 0.0)
                     for got in (sq[k, u], norms[k, u]):
                         assert np.isclose(float(got) / unit ** 2, n2, rtol=tol), (name, u)
+
+
+# the fp32 raw-row kernel adds a unit's examples to one block: units of two to four, one and several units per workgroup, tiles of
+# channels that are not whole, both kernel sizes and strides (enough units that the kernel is chosen: it needs no more workspace than the
+# partial norms of its blocks)
+@pytest.mark.parametrize("cin,cout,h,w,k,stride,n,unit", [(16, 16, 16, 16, 3, 1, 600, 2), (33, 14, 12, 12, 3, 1, 300, 3), (20, 17, 9, 11, 3, 2, 800, 4),
+                                                          (18, 20, 45, 37, 5, 2, 200, 2), (16, 16, 12, 14, 3, 1, 16600, 2)])
+def test_units_in_the_fp32_raw_row_kernel(cin, cout, h, w, k, stride, n, unit):
+    layer = Layer("conv", cin, cout, h, w, k, k, stride, (k - 1) // 2, cout % 2 == 0)
+    d, units = dp.make_desc(layer, n, "f32"), n // unit
+    blocks = -(-cout // 32) * -(-cin // (16 if k == 5 else 32))
+    assert dp.dp_unit_workspace_bytes(d, unit) == (4 * units * blocks + 15) // 16 * 16
+    x, dy = _inputs(layer, 2 * unit, 141, "f32")
+    mean_w, mean_b = oracle.unit_mean_grad(layer, x, dy, unit)
+    xd, dyd = (dev(v).repeat((n // (2 * unit),) + (1,) * (v.ndim - 1)).contiguous() for v in (x, dy))      # two units, over and over
+    ws = torch.empty(dp.dp_unit_workspace_bytes(d, unit), dtype=torch.uint8, device="cuda:0")
+    row = (layer.pw + 3) // 4 * 4
+    g = torch.full((units, row + (layer.pb + 3) // 4 * 4), 7.0, device="cuda:0")
+    sq, norms = torch.full((units,), -1.0, device="cuda:0"), torch.full((units,), -1.0, device="cuda:0")
+    dp.dp_unit_grad(d, unit, xd, dyd, g, g[:, row:] if layer.pb else None, sq, ws, g_stride=g.shape[1])
+    dp.dp_unit_grad(d, unit, xd, dyd, None, None, norms, ws)
+    torch.cuda.synchronize()
+    for u in range(2):
+        assert torch.equal(g[u::2, :layer.pw], g[u, :layer.pw].expand(units // 2, -1)) and torch.equal(sq[u::2], sq[u].expand(units // 2))
+        got = host(g[u]) / unit
+        assert_close(got[:layer.pw], mean_w[u], F32_TOL, "dW")
+        if layer.pb:
+            assert_close(got[row:row + layer.pb], mean_b[u], F32_TOL, "db")
+        n2 = oracle.sqnorm(mean_w[u]) + (oracle.sqnorm(mean_b[u]) if layer.pb else 0.0)
+        assert np.isclose(float(sq[u]) / unit ** 2, n2, rtol=F32_TOL)
+    assert np.allclose(host(norms), host(sq), rtol=F32_TOL)
