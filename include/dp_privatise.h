@@ -238,8 +238,9 @@ dp_status dp_unit_grad_batch(const dp_layer_desc *descs, int clip_unit, const vo
 /* The batch calls above on examples that lie in SEVERAL tensors (the micro-steps of an optimiser step, each handed over in
  * tensors of its own): x[l] and dy[l] are device arrays of desc.n example addresses (8-byte aligned, in place of the tensors), so that one
  * launch contracts the examples of all of them; everything else as in the calls without "_at", same results up to the
- * order of summation.  Channels-first layouts only (else DP_ERR_UNSUPPORTED).  Clipping units: the examples of a unit must
- * follow each other in one tensor.
+ * order of summation.  Channels-first layouts only (else DP_ERR_UNSUPPORTED).  An address is that of an example in a 16-byte
+ * aligned tensor of such examples (kernels load whole vectors where a row of the layer is a multiple of them).  Clipping units: the
+ * examples of a unit must follow each other in one tensor.
  * dp_example_addresses writes such arrays: for operand o (layer l's x or dy) with n_tensors tensors of per_tensor examples,
  *   table[(o * n_tensors + t) * per_tensor + j] = tensors[o * n_tensors + t] + j * example_bytes[o].
  * tensors [host] n_operands * n_tensors device pointers, 16-byte aligned; example_bytes [host] n_operands; table [device]
