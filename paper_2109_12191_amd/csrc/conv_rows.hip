@@ -276,60 +276,66 @@ __global__ void __launch_bounds__(64 * K * cr_qmax(K)) conv_rows_kernel(const Gr
 
 struct RowsPlan {
     int tiles_m, tiles_n, tm, tn, q, rows, chunks, rpr, xp, cha, chx, ex_per_wg;
-    int groups, resident;           // groups of four runs per chunk; workgroups that a compute unit has room for
     unsigned lds;
+    double us;                      // estimated time of a call alone
     bool ok;
 };
 
 int odd_quads(int floats) { const int v = (floats + 3) / 4; return (v | 1) * 4; }     // consecutive channels start in different banks
 
+// us of a per-example call alone.  A launch lasts as long as the compute unit with most blocks, which takes them in rounds of as many
+// workgroups as it has room for.  Chunk by chunk a round needs the longer of two things (a little more where they are close): what
+// the SIMD with most waves multiplies and stages for all its workgroups -- the waves of every workgroup start on the same SIMD, so K q waves count
+// as ceil(K q / 4) on it --, or one workgroup's own chain of barrier, staging and MFMAs.
+double rows_us(int k, const RowsPlan &p, double blocks, int unit, int groups, long long pieces, int resident)
+{
+    const double mfma = k == 3 ? 1.47 : 1.37, start = k == 3 ? 2.5 : 4.0, piece = k == 3 ? 0.60e-3 : 0.42e-3, epilogue = k == 3 ? 0.84 : 1.3;
+    const double wave = 32.0 * k * 4 * (p.tm / 16) * (p.tn / 16) * ((groups + p.q - 1) / p.q) / 2400.0 * ((k * p.q + 3) / 4) * mfma;
+    const double staging = piece * (double)pieces, chunks = (double)p.chunks * unit;
+    const auto round = [&](double r) {
+        const double all = r * (wave + staging), own = 0.5 * wave + start + staging;
+        return r > 0.0 ? chunks * std::sqrt(std::sqrt(all * all * all * all + own * own * own * own)) + epilogue * (p.tm / 16) * (p.q + 1) * (0.7 + 0.3 * r) : 0.0;
+    };
+    const double most = std::ceil(blocks / 256.0), r = std::min<double>(most, resident), full = std::floor(most / r);
+    return (k == 3 ? 7.8 : 6.3) + full * round(r) + round(most - full * r);
+}
+
 RowsPlan rows_plan(const Geo &g)
 {
+    RowsPlan best = {};
+    const int K = g.kh, S = g.stride, CI = cr_cin(K);
     RowsPlan p = {};
-    const int K = g.kh, S = g.stride;
     p.tiles_m = (g.cout + CR_CH - 1) / CR_CH;
-    const int CI = cr_cin(K);
     p.tiles_n = (g.cin + CI - 1) / CI;
     p.tm = g.cout > 16 ? 32 : 16;
     p.tn = CI > 16 && g.cin > 16 ? 32 : 16;
     p.rpr = (g.ow + 3) / 4;
     p.xp = CR_LEFT + (g.w + 3) / 4 * 4;
     const int lc = g.cout < CR_CH ? g.cout : CR_CH, ln = g.cin < CI ? g.cin : CI;      // channels that are staged
-    const double wgs = (double)(g.n / g.unit) * p.tiles_m * p.tiles_n;
-    double best = 0.0;
-    for (int q = 1; q <= cr_qmax(K); q *= 2)
-        for (int rows = 1; rows <= g.oh && rows <= 64; ++rows) {
-            const int lines = (rows - 1) * S + K;
-            if (lines > 127) break;
-            const long long pieces = (long long)lc * rows * p.rpr + (long long)ln * lines * ((g.w + 3) / 4);
-            if (pieces > (long long)cr_pieces(K) * 64 * K * q) break;
-            const int groups = (rows * p.rpr + 3) / 4;
-            const int cha = odd_quads(groups * 16), chx = odd_quads(lines * p.xp + 4);
-            const long long floats = (long long)p.tm * cha + (long long)p.tn * chx + 16 + groups * 4 + 16 * (p.tn * K * K + 2) + CR_CH + 64;
-            // LDS in quarters, halves or the whole of what a compute unit has: layers of different sizes share a launch
-            const unsigned need = (unsigned)(floats * 4), lds = need <= 39 * 1024 ? 39 * 1024 : need <= 78 * 1024 ? 78 * 1024 : 156 * 1024;
-            if (need > 156 * 1024) break;
-            const int chunks = (g.oh + rows - 1) / rows;
-            // cycles of a compute unit per (example, block): the MFMAs of its 4 SIMDs with the runs dealt to q waves and rounded
-            // up, LDS writes and barriers per chunk (loads at ~16 bytes per cycle overlap them only where several workgroups share
-            // the unit), the epilogue's rounds
-            const int resident = std::max(1, std::min({(int)(156 * 1024 / lds), 12 / (K * q), 8}));
-            const int share = std::min<double>(resident, std::max(1.0, wgs / 256.0));      // workgroups side by side on a unit
-            const double mfma = 32.0 * K * 4 * (p.tm / 16) * (p.tn / 16) * ((groups + q - 1) / q);       // of one wave and chunk
-            const double waves_per_simd = std::max(1.0, K * q * (double)share / 4.0);
-            const double chunk = mfma * waves_per_simd + (pieces * 1.5 + 600.0) * (share > 1 ? 0.5 * share : 1.0);
-            const double per_example = (chunks * chunk + (p.tm / 16) * (q + 1) * 300.0 + 500.0) / share;
-            if (p.ok && per_example >= best) continue;
-            best = per_example;
-            p.ok = true;
-            p.q = q; p.rows = rows; p.chunks = chunks; p.cha = cha; p.chx = chx; p.lds = lds;
-            p.groups = groups; p.resident = resident;
-        }
-    if (!p.ok) return p;
+    const double blocks = (double)(g.n / g.unit) * p.tiles_m * p.tiles_n;
     // several examples in a row where there are far more (example, block) pairs than workgroups that run at a time
-    int e = (int)(wgs / 4096.0);
+    const int e = (int)(blocks / 4096.0);
     p.ex_per_wg = g.unit * (e < 1 ? 1 : e > 8 ? 8 : e);
-    return p;
+    for (p.q = 1; p.q <= cr_qmax(K); p.q *= 2)
+        for (p.rows = 1; p.rows <= g.oh && p.rows <= 64; ++p.rows) {
+            const int lines = (p.rows - 1) * S + K;
+            if (lines > 127) break;
+            const long long pieces = (long long)lc * p.rows * p.rpr + (long long)ln * lines * ((g.w + 3) / 4);
+            if (pieces > (long long)cr_pieces(K) * 64 * K * p.q) break;
+            const int groups = (p.rows * p.rpr + 3) / 4;
+            p.cha = odd_quads(groups * 16);
+            p.chx = odd_quads(lines * p.xp + 4);
+            const long long floats = (long long)p.tm * p.cha + (long long)p.tn * p.chx + 16 + groups * 4 + 16 * (p.tn * K * K + 2) + CR_CH + 64;
+            // LDS in quarters, halves or the whole of what a compute unit has: layers of different sizes share a launch
+            const unsigned need = (unsigned)(floats * 4);
+            if (need > 156 * 1024) break;
+            p.lds = need <= 39 * 1024 ? 39 * 1024 : need <= 78 * 1024 ? 78 * 1024 : 156 * 1024;
+            p.chunks = (g.oh + p.rows - 1) / p.rows;
+            p.us = rows_us(K, p, blocks, g.unit, groups, pieces, std::max(1, std::min({(int)(156 * 1024 / p.lds), 12 / (K * p.q), 8})));
+            p.ok = true;
+            if (!best.ok || p.us < best.us) best = p;
+        }
+    return best;
 }
 
 size_t cr_align16(size_t b) { return (b + 15) & ~(size_t)15; }
@@ -337,19 +343,6 @@ size_t cr_align16(size_t b) { return (b + 15) & ~(size_t)15; }
 template <int K> const void *rows_fn(int stride)
 {
     return stride == 2 ? reinterpret_cast<const void *>(&conv_rows_kernel<K, 2>) : reinterpret_cast<const void *>(&conv_rows_kernel<K, 1>);
-}
-
-// us of a per-example call alone.  Blocks are not sliced along K, so a launch lasts as long as the compute unit with most of them:
-// start and end, the MFMAs (which several workgroups on a unit slow down more than they overlap), the barriers and the waiting of
-// every chunk, the epilogue.
-double rows_us(const Geo &g, const RowsPlan &p)
-{
-    const bool k3 = g.kh == 3;
-    const double blocks = std::ceil((double)(g.n / g.unit) * p.tiles_m * p.tiles_n / 256.0), rounds = std::ceil(blocks / std::min<double>(blocks, p.resident));
-    const double chunks = (double)p.chunks * g.unit;
-    const double mfma = 32.0 * g.kh * g.kw * ((p.groups + p.q - 1) / p.q) * p.q * (p.tm / 16) * (p.tn / 16) / 2400.0;     // of a chunk, its four SIMDs busy
-    if (k3) return 12.6 + blocks * chunks * mfma * (blocks > 1.0 ? 1.96 : 1.34) + rounds * chunks * 3.55 + blocks * 1.5;
-    return 8.6 + blocks * chunks * mfma * (blocks > 1.0 ? 1.75 : 1.50) + blocks * chunks * 4.07 + blocks * 3.8;
 }
 
 // What the sizes decide, kept for the sizes seen last (a call asks several times): the plan, and whether the kernel is the faster one.
@@ -370,12 +363,13 @@ const RowsChoice &rows_choice(const Geo &g)
         c.plan = rows_plan(g);
         // Both times estimated, a margin of 7 % to the general kernel.  Fitted to 1249 layers in and around the networks here (3x3 and
         // 5x5, strides 1 and 2, 3 to 256 channels, 7 to 64 rows, 8 to 512 examples, with and without a bias), both kernels measured
-        // on each: rows_us is within 6 % (90 % of the layers within 20 %), the general estimate within 5 % (15 %).  The rule takes
-        // 449 of them, 15 of those are slower by more than 3 % (at most 28 %: 29 / 37 us, 32 -> 64 onto 8 x 8); all 1249 together
-        // take 0.887 of the general kernel's time, where the faster of the two each time would be 0.880.  us, general / this: 64 -> 64 3x3 on
-        // 56 x 56, 64 examples 282 / 194, 48: 185 / 194, 128: 465 / 543; with a bias 378 / 202, 243 / 195, 618 / 553; 16 -> 16 on 32 x
-        // 32, 256: 100 / 32; 128 -> 128 on 28 x 28, 96: 295 / 435; 5x5, 40 -> 72 stride 2 on 45 x 37 with a bias, 40: 126 / 109.
-        c.use = c.plan.ok && rows_us(g, c.plan) < 0.93 * conv_general_f32_us(g);
+        // on each: half of the estimates are within 8 % (this kernel) and 6 % (the general one), nine of ten within 26 % and 16 %.  Where
+        // the kernels differ by a quarter or more (729 layers) the faster one is chosen in all but 15.  The rule takes 508 layers, 26 of
+        // them slower by more than 3 % (at most 30 %); all 1249 together take 0.868 of the general kernel's time, where the faster of
+        // the two each time would be 0.856.  us, general / this: 64 -> 64 3x3 on 56 x 56, 64 examples 283 / 195, 48: 188 / 193, 128: 465 /
+        // 382; with a bias 374 / 199, 242 / 195, 617 / 386; 16 -> 16 on 32 x 32, 256: 103 / 33; 128 -> 128 on 28 x 28, 256: 654 /
+        // 919; 5x5, 40 -> 72 stride 2 on 45 x 37 with a bias, 40: 128 / 108.
+        c.use = c.plan.ok && c.plan.us < 0.93 * conv_general_f32_us(g);
         std::memcpy(c.key, key, sizeof(key));
     }
     return c;
