@@ -292,8 +292,11 @@ def main():
     # The whole step against the HBM roof: algorithmic bytes of every call of a step (operands once per call, per-example
     # gradients written and read back where they are materialised, the accumulator read and written by every clipped
     # sum, finalize) over the measured step time.
-    step_bytes = wl.accum * (sum(w[1] for w in ps.work) + sum(w[2] for w, f in zip(ps.work, ps.form) if f == "recompute")
-                             + (4.0 * ps.rows * ps.p_mat + 8.0 * ps.p_mat)) + 8.0 * wl.n_params
+    # (micro-steps issued together add to the accumulator once)
+    phases = -(-wl.accum // ps.micro_steps_per_phase)
+    sums = 8.0 * (ps.p_mat + sum(pw + pb for pw, pb, f in zip(ps.pw, ps.pb, ps.form) if f == "recompute"))
+    step_bytes = (wl.accum * (sum(w[1] for w in ps.work) + sum(l.in_bytes(esize) * wl.n for l, f in zip(wl.layers, ps.form) if f == "recompute")
+                              + 4.0 * ps.rows * ps.p_mat) + phases * sums + 8.0 * wl.n_params)
     step_flops = wl.accum * (sum(w[0] for w in ps.work) + sum(w[0] for w, f in zip(ps.work, ps.form) if f == "recompute"))
     step_sec = elapsed / args.steps
     if roofline is not None:

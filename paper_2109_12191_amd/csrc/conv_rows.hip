@@ -286,7 +286,8 @@ int odd_quads(int floats) { const int v = (floats + 3) / 4; return (v | 1) * 4; 
 // us of a per-example call alone.  A launch lasts as long as the compute unit with most blocks, which takes them in rounds of as many
 // workgroups as it has room for.  Chunk by chunk a round needs the longer of two things (a little more where they are close): what
 // the SIMD with most waves multiplies and stages for all its workgroups -- the waves of every workgroup start on the same SIMD, so K q waves count
-// as ceil(K q / 4) on it --, or one workgroup's own chain of barrier, staging and MFMAs.
+// as ceil(K q / 4) on it --, or one workgroup's own chain of barrier, staging and MFMAs.  Of 596 pairs of plans measured against each
+// other the one it prefers is 2 % slower than the better one on average, 536 of them within 10 %.
 double rows_us(int k, const RowsPlan &p, double blocks, int unit, int groups, long long pieces, int resident)
 {
     const double mfma = k == 3 ? 1.47 : 1.37, start = k == 3 ? 2.5 : 4.0, piece = k == 3 ? 0.60e-3 : 0.42e-3, epilogue = k == 3 ? 0.84 : 1.3;
