@@ -227,6 +227,38 @@ def test_conv_f32_raw_rows_kernel(cin, cout, h, w, k, stride, n):
     assert np.allclose(norms, sq, rtol=F32_TOL)
 
 
+def test_conv_f32_raw_rows_kernel_in_a_batch_call():
+    """Layers of every kernel size and stride in one batch call, where the kernel is planned for a chip that other layers fill."""
+    n, few = 200, 5
+    layers = [Layer("conv", ci, co, h, w, k, k, s, (k - 1) // 2, co % 2 == 0) for ci, co, h, w, k, s in
+              [(33, 15, 8, 9, 3, 1), (48, 16, 33, 36, 3, 1), (16, 48, 17, 13, 5, 2), (20, 31, 24, 26, 5, 1), (5, 16, 46, 43, 5, 1), (18, 20, 45, 37, 5, 2),
+               (16, 32, 32, 32, 3, 2), (40, 16, 13, 17, 3, 2)]]
+    descs = [dp.make_desc(l, n, "f32") for l in layers]
+    assert all(dp.dp_kernel_variant(d, dp.DP_WS_PER_EXAMPLE_GRAD | dp.DP_VARIANT_SHARED).startswith("conv_rows<f32") for d in descs)
+    ins = [_inputs(l, few, 151 + k, "f32") for k, l in enumerate(layers)]
+    xs, dys = ([dev(v[j]).repeat((n // few,) + (1,) * (v[j].ndim - 1)).contiguous() for v in ins] for j in (0, 1))
+    ws = [torch.empty(max(16, dp.dp_workspace_bytes(d)), dtype=torch.uint8, device="cuda:0") for d in descs]
+    batch = dp.LayerBatch(descs, [t.data_ptr() for t in ws], [t.numel() for t in ws])
+    rows = [(l.pw + 3) // 4 * 4 for l in layers]
+    pitch = max(r + (l.pb + 3) // 4 * 4 for r, l in zip(rows, layers))
+    g = [torch.full((n, pitch), 7.0, device="cuda:0") for _ in layers]
+    sq, norms = (torch.full((len(layers), n), -1.0, device="cuda:0") for _ in range(2))
+    args = batch.ptrs([t.data_ptr() for t in xs]), batch.ptrs([t.data_ptr() for t in dys])
+    dp.dp_per_example_grad_batch(batch, *args, batch.ptrs([t.data_ptr() for t in g]),
+                                 batch.ptrs([t[:, r:].data_ptr() if l.pb else None for t, r, l in zip(g, rows, layers)]),
+                                 batch.ptrs([sq[k].data_ptr() for k in range(len(layers))]), g_stride=pitch)
+    dp.dp_per_example_grad_batch(batch, *args, None, None, batch.ptrs([norms[k].data_ptr() for k in range(len(layers))]))
+    torch.cuda.synchronize()
+    for k, (l, (x, dy)) in enumerate(zip(layers, ins)):
+        ref_w, ref_b, ref_n2 = _oracle_grads(l, x, dy)
+        assert torch.equal(g[k], g[k][:few].repeat(n // few, 1)) and torch.equal(sq[k], sq[k][:few].repeat(n // few))
+        got = host(g[k][:few])
+        assert_close(got[:, :l.pw], ref_w, F32_TOL, f"layer {k} dW")
+        if l.pb:
+            assert_close(got[:, rows[k]:rows[k] + l.pb], ref_b, F32_TOL, f"layer {k} db")
+        assert np.allclose(host(sq[k][:few]), ref_n2, rtol=F32_TOL) and np.allclose(host(norms[k]), host(sq[k]), rtol=F32_TOL)
+
+
 def test_conv_f32_raw_rows_kernel_keeps_what_is_not_finite_in_its_place():
     """An infinity in the last column of a row reaches the taps that read it and no other."""
     layer = Layer("conv", 32, 16, 3, 5, 3, 3, 1, 1, False)
