@@ -31,8 +31,9 @@ from . import binding as B
 #   a micro-step that reads more than this fills the chip by itself.  ResNet-50 with 24 examples (1.05 GB) 3141 / 2999, 28 (1.22 GB)
 #   3613 / 3500; 32 (1.39 GB) 3853 / 3999, 40 (1.74 GB) 4656 / 4927; at 192 x 192, 40 examples (1.28 GB) 5013 / 5245
 PHASE_MICRO_STEP_BYTES = 1.25e9
-#   examples of a phase.  ResNet-20, 64 examples a micro-step: phases of 128 / 256 901 / 757; 128: phases of 256 / 512 1478 / 1506; 256: one
-#   by one / 512 2755 / 2966.  ResNet-18-GN, 48 (8 micro-steps): one by one / 192 / 384 2840 / 2470 / 2556; 64: 256 / 512 3223 / 7084
+#   examples of a phase.  ResNet-20, 64 examples a micro-step: phases of 128 / 256 784 / 667; ResNet-18-GN, 48 (8 micro-steps): one by
+#   one / 192 2840 / 2470, 64: one by one / 256 3452 / 3223 (128: 6101 / 6338, a loss inside the line).  Beyond, ResNet-20, 256: one by one /
+#   512 2493 / 2411; ResNet-18-GN, 48: 192 / 384 2470 / 2556, 64: 256 / 512 3223 / 7084
 PHASE_EXAMPLES = 256
 #   and of micro-steps of one or two examples, which store every gradient.  ResNet-50, 64 x 1: one by one / 16 / 32 / 64 9783 / 4550 /
 #   4314 / 4105; 32 x 2: 8068 / 4546 (16) / 4317 / 4102
@@ -358,18 +359,21 @@ class PrivatiseStep:
                 return 1
             copies = self.copies if phases > 1 else 1
             if copies * (size * matrix + self._workspace_bytes(size)) <= PHASE_STORE_BYTES:
-                alone = alone or self._gathers(1)
+                if alone is None:
+                    alone = self._gathers(1)
                 if not any(now and not before for now, before in zip(self._gathers(size), alone)):
                     return size
             phases += 1
 
     def _gathers(self, tensors: int) -> List[bool]:
-        """Which calls of a phase of `tensors` micro-steps run the gathering kernel: per layer the per-example and the recomputing one."""
+        """Which calls of a phase of `tensors` micro-steps run the gathering kernel for want of room for rewritten operands (bf16 only): per
+        layer the per-example and the recomputing one."""
         flags = []
-        for d, form in zip(self._workspaces(tensors)[0], self.form):
-            stored = B.DP_VARIANT_MATERIALISE if form == "materialise" else 0
-            flags.append("gather" in B.dp_kernel_variant(d, B.DP_WS_PER_EXAMPLE_GRAD | B.DP_VARIANT_SHARED | stored))
-            flags.append(form == "recompute" and "gather" in B.dp_kernel_variant(d, B.DP_WS_RECOMPUTE | B.DP_VARIANT_SHARED))
+        if self.wl.dtype == "bf16":
+            for d, form in zip(self._workspaces(tensors)[0], self.form):
+                stored = B.DP_VARIANT_MATERIALISE if form == "materialise" else 0
+                flags.append("gather" in B.dp_kernel_variant(d, B.DP_WS_PER_EXAMPLE_GRAD | B.DP_VARIANT_SHARED | stored))
+                flags.append(form == "recompute" and "gather" in B.dp_kernel_variant(d, B.DP_WS_RECOMPUTE | B.DP_VARIANT_SHARED))
         return flags
 
     def _phase_sizes(self, micro_steps: int) -> List[int]:

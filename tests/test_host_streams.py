@@ -4,6 +4,7 @@ ordered by the streams and events they were issued with."""
 import contextlib
 import gc
 import weakref
+from dataclasses import replace
 
 import pytest
 import torch
@@ -288,9 +289,11 @@ def test_a_phase_is_bounded_by_what_it_holds(order, monkeypatch, name, n, accum,
     ("resnet50", 28, 4, 224, 4), ("resnet50", 32, 4, 224, 1), ("resnet50", 40, 4, 192, 1), ("resnet50", 16, 8, 224, 4), ("resnet50", 40, 4, 160, 2),
     ("resnet20", 64, 4, 32, 4), ("resnet20", 128, 4, 32, 2), ("resnet20", 256, 4, 32, 1), ("resnet18_gn", 64, 8, 32, 4),
     ("resnet18_gn", 24, 8, 40, 4), ("resnet18_gn", 48, 4, 40, 2), ("resnet18_gn", 64, 4, 40, 1), ("resnet18_gn", 96, 4, 24, 1),
-    ("resnet50_nano", 1, 64, 224, 64), ("resnet50_nano", 1, 1024, 224, 47)])
+    ("resnet50_nano", 1, 64, 224, 64), ("resnet50_nano", 1, 1024, 224, 47), ("resnet18_gn f32", 10, 4, 40, 4)])
 def test_micro_steps_per_phase(order, name, n, accum, hw, want):
+    name, *dtype = name.split()
     wl = get_workload(name, n=n, accum=accum, hw=hw)
+    wl = replace(wl, dtype=dtype[0] if dtype else wl.dtype)
     ps = dp.PrivatiseStep(wl, device="cpu", streams=8)
     size = ps.micro_steps_per_phase
     assert size == want and ps._phase_sizes(accum)[0] == size
