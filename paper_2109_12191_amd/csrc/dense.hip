@@ -334,7 +334,8 @@ __global__ void __launch_bounds__(256 * G, G == 1 ? 2 : 4) dense_tokens_kernel(c
             if (++c_c == cpe) {
                 c_c = 0;
                 if constexpr (WEIGHTED) {
-                    const float f = clip_factor(a.group_sqnorm[c_ex], a.clip_c);
+                    // (the same in every lane: a scalar branch)
+                    const float f = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(clip_factor(a.group_sqnorm[c_ex], a.clip_c))));
                     if (f != 0.0f) {                      // an example whose gradient overflows has factor 0: it adds nothing, and no 0 * inf
 #pragma unroll
                         for (int r = 0; r < 16; ++r) tot[r] += f * acc[r];
@@ -344,7 +345,11 @@ __global__ void __launch_bounds__(256 * G, G == 1 ? 2 : 4) dense_tokens_kernel(c
                         }
                     }
 #pragma unroll
-                    for (int r = 0; r < 16; ++r) acc[r] = accb[r] = 0.0f;
+                    for (int r = 0; r < 16; ++r) acc[r] = 0.0f;
+                    if (bias_here) {
+#pragma unroll
+                        for (int r = 0; r < 16; ++r) accb[r] = 0.0f;
+                    }
                     c_ex += ex_step;
                 }
             }
