@@ -76,11 +76,10 @@ class _Store:
 
 class _Plan:
     """Views and batch calls for phases of `n` examples: one micro-step in the caller's tensors (`tensors` = 1), or `tensors`
-    micro-steps through arrays of example addresses."""
+    micro-steps through arrays of example addresses.  (Keeps no reference to its PrivatiseStep: the buffers go when that goes.)"""
 
     def __init__(self, ps: "PrivatiseStep", tensors: int, stores: List[_Store]):
         wl = ps.wl
-        self.ps = ps
         self.tensors = tensors
         self.stores = stores                       # the copies that are large enough
         self.n = wl.n * tensors
@@ -110,15 +109,14 @@ class _Plan:
         self.partials = [B.PartialTable(self.ws[c], [1] * L, ps.group_of_layer)
                          for c in range(len(stores))]
         self.work = ps._work(tensors)
-        self.groups_a = self._make_groups(range(L), 0) if ps.clip_unit == 1 else []
-        self.groups_b = self._make_groups([i for i in range(L) if self.form[i] == "recompute"], 1)
-        self.groups_u = self._make_groups(range(L), 2) if ps.clip_unit > 1 else []
+        self.groups_a = self._make_groups(ps, range(L), 0) if ps.clip_unit == 1 else []
+        self.groups_b = self._make_groups(ps, [i for i in range(L) if self.form[i] == "recompute"], 1)
+        self.groups_u = self._make_groups(ps, range(L), 2) if ps.clip_unit > 1 else []
 
-    def _make_groups(self, layer_ids, use: int):
+    def _make_groups(self, ps: "PrivatiseStep", layer_ids, use: int):
         """Groups of at most 16 layers with the same kernel variant for phase `use` (0: per-example gradients,
         1: recomputing clipped sum, 2: unit sums), largest total work first.  Each group: dict(layers, name, batch per copy,
         constant pointer arrays)."""
-        ps = self.ps
         by_name = {}
         family = "conv3x3_rows<bf16,all widths,%s>" % ("weighted" if use == 1 else "per_example")
         for li in layer_ids:
@@ -164,7 +162,7 @@ class _Plan:
                                                      for i in part])
                 g["flops"] = sum(self.layers[i].flops for i in part) * self.n
                 g["bytes"] = sum(self.work[i][2 if use == 1 else 1] for i in part)
-                g["seconds"] = self._estimate(g)
+                g["seconds"] = self._estimate(ps, g)
                 groups.append(g)
         groups.sort(key=lambda g: -g["seconds"])
         # side stream of each group: longest first onto the least loaded stream
@@ -175,11 +173,11 @@ class _Plan:
             load[k] += g["seconds"]
         return groups
 
-    def _estimate(self, g) -> float:
+    def _estimate(self, ps: "PrivatiseStep", g) -> float:
         """Duration of a group's launch for the lane balance: its work at the rates its kernel family sustains on
         MI355X when it has the chip to itself (measured call by call on ResNet-50 at n = 32), plus a few
         microseconds per launch however small it is."""
-        if self.ps.lanes == "flops" or self.n <= 2:
+        if ps.lanes == "flops" or self.n <= 2:
             # micro-steps of one or two examples: launches are bound by the walk along K of a few workgroups, not by
             # the chip's rates; flops alone order them better (measured: 5.6 k against 5.1 k examples/s)
             return g["flops"] / 150.0e12 + 8.0e-6

@@ -336,3 +336,21 @@ def test_what_a_step_shows_is_one_micro_steps(order, streams):
     ps._plan(8).group_sqnorm[0].copy_(torch.arange(wl.n_groups * 8, dtype=torch.float32).view(wl.n_groups, 8))
     ps.run(_steps(wl, 8))
     assert torch.equal(ps.group_sqnorm[:, 0], torch.arange(wl.n_groups, dtype=torch.float32) * 8 + 7)
+
+
+def test_buffers_go_with_their_step(order):
+    """Nothing keeps a PrivatiseStep that was dropped: its memory is given back at once, not when cycles are next collected."""
+    gc.collect()
+    gc.disable()
+    try:
+        ps = dp.PrivatiseStep(get_workload("resnet18_gn", n=2, accum=3, hw=16), device="cpu", streams=4)
+        ps.run(_steps(ps.wl, 3))
+        ps.begin_step()
+        ps.micro_step(_steps(ps.wl, 1)[0])
+        ps.finalize()
+        kept = [weakref.ref(o) for o in [ps] + [st for st in ps._stores if st is not None] + list(ps._plans.values())]
+        assert len(kept) == 5
+        del ps
+        assert all(k() is None for k in kept)
+    finally:
+        gc.enable()
