@@ -334,21 +334,18 @@ __global__ void __launch_bounds__(256 * G, G == 1 ? 2 : 4) dense_tokens_kernel(c
             if (++c_c == cpe) {
                 c_c = 0;
                 if constexpr (WEIGHTED) {
-                    // (the same in every lane: a scalar branch)
-                    const float f = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(clip_factor(a.group_sqnorm[c_ex], a.clip_c))));
-                    if (f != 0.0f) {                      // an example whose gradient overflows has factor 0: it adds nothing, and no 0 * inf
+                    const float f = clip_factor(a.group_sqnorm[c_ex], a.clip_c);
+                    // an example whose gradient overflows has factor 0: it adds nothing, and no 0 * inf.  (Rare: cleared first, the additions
+                    // below as without it.  16 x 128 tokens, 768 -> 768: 24.36 us without, 24.41 so, 24.8 with a branch around the additions)
+                    if (__builtin_expect(f == 0.0f, 0)) {
 #pragma unroll
-                        for (int r = 0; r < 16; ++r) tot[r] += f * acc[r];
-                        if (bias_here) {
-#pragma unroll
-                            for (int r = 0; r < 16; ++r) totb[r] += f * accb[r];
-                        }
+                        for (int r = 0; r < 16; ++r) acc[r] = accb[r] = 0.0f;
                     }
 #pragma unroll
-                    for (int r = 0; r < 16; ++r) acc[r] = 0.0f;
+                    for (int r = 0; r < 16; ++r) { tot[r] += f * acc[r]; acc[r] = 0.0f; }
                     if (bias_here) {
 #pragma unroll
-                        for (int r = 0; r < 16; ++r) accb[r] = 0.0f;
+                        for (int r = 0; r < 16; ++r) { totb[r] += f * accb[r]; accb[r] = 0.0f; }
                     }
                     c_ex += ex_step;
                 }
