@@ -286,19 +286,24 @@ int odd_quads(int floats) { const int v = (floats + 3) / 4; return (v | 1) * 4; 
 // us of a per-example call alone.  A launch lasts as long as the compute unit with most blocks, which takes them in rounds of as many
 // workgroups as it has room for.  Chunk by chunk a round needs the longer of two things (a little more where they are close): what
 // the SIMD with most waves multiplies and stages for all its workgroups -- the waves of every workgroup start on the same SIMD, so K q waves count
-// as ceil(K q / 4) on it --, or one workgroup's own chain of barrier, staging and MFMAs.  Of 596 pairs of plans measured against each
-// other the one it prefers is 2 % slower than the better one on average, 536 of them within 10 %.
-double rows_us(int k, const RowsPlan &p, double blocks, int unit, int groups, long long pieces, int resident)
+// as ceil(K q / 4) on it --, or one workgroup's own chain of barrier, staging and MFMAs.  On 704 layers with several plans measured the one
+// it prefers is 1.6 % slower than the best of them on average, 657 of them within 10 % (one figure for pieces of all widths, and none
+// for fewer waves: 3.4 %, 601).
+double rows_us(int k, const RowsPlan &p, double blocks, int unit, int groups, long long pieces, bool even, bool shared, int resident)
 {
-    const double mfma = k == 3 ? 1.47 : 1.37, start = k == 3 ? 2.5 : 4.0, piece = k == 3 ? 0.60e-3 : 0.42e-3, epilogue = k == 3 ? 0.84 : 1.3;
+    // us per staged piece: 16-byte reads of rows that are no multiple of four columns are off their alignment and the last one is cut off
+    const double piece = k == 3 ? (even ? 0.565e-3 : 0.794e-3) : even ? 0.823e-3 : 0.995e-3;
+    const double mfma = k == 3 ? 1.2 : 1.23, start = k == 3 ? 2.3 : 4.2, share = k == 3 ? 0.53 : 0.0, epilogue = k == 3 ? 0.92 : 1.07;
     const double wave = 32.0 * k * 4 * (p.tm / 16) * (p.tn / 16) * ((groups + p.q - 1) / p.q) / 2400.0 * ((k * p.q + 3) / 4) * mfma;
     const double staging = piece * (double)pieces, chunks = (double)p.chunks * unit;
     const auto round = [&](double r) {
-        const double all = r * (wave + staging), own = 0.5 * wave + start + staging;
+        const double all = r * (wave + staging), own = share * wave + start + staging;
         return r > 0.0 ? chunks * std::sqrt(std::sqrt(all * all * all * all + own * own * own * own)) + epilogue * (p.tm / 16) * (p.q + 1) * (0.7 + 0.3 * r) : 0.0;
     };
     const double most = std::ceil(blocks / 256.0), r = std::min<double>(most, resident), full = std::floor(most / r);
-    return (k == 3 ? 7.8 : 6.3) + full * round(r) + round(most - full * r);
+    // fewer waves than fit on a kernel row measured about 1.2 times what the terms above give, but not beside other layers' workgroups
+    // (ResNet-20, 256 examples on eight streams: 716 us with the factor there, 641 without)
+    return ((k == 3 ? 8.9 : 8.7) + full * round(r) + round(most - full * r)) * (shared || p.q == cr_qmax(k) ? 1.0 : k == 3 ? 1.21 : 1.24);
 }
 
 RowsPlan rows_plan(const Geo &g, bool shared)
@@ -336,7 +341,7 @@ RowsPlan rows_plan(const Geo &g, bool shared)
             if (need > 156 * 1024) break;
             p.lds = need <= 39 * 1024 ? 39 * 1024 : need <= 78 * 1024 ? 78 * 1024 : 156 * 1024;
             p.chunks = (g.oh + p.rows - 1) / p.rows;
-            p.us = rows_us(K, p, blocks, g.unit, groups, pieces, std::max(1, std::min({(int)(156 * 1024 / p.lds), 12 / (K * p.q), 8})));
+            p.us = rows_us(K, p, blocks, g.unit, groups, pieces, g.w % 4 == 0 && g.ow % 4 == 0, shared, std::max(1, std::min({(int)(156 * 1024 / p.lds), 12 / (K * p.q), 8})));
             p.ok = true;
             if (!best.ok || p.us < best.us) best = p;
         }
@@ -367,15 +372,15 @@ const RowsChoice &rows_choice(const Geo &g)
     RowsChoice &c = kept[(at ^ at >> 6) % 64];
     if (std::memcmp(c.key, key, sizeof(key)) != 0) {
         c.plan = rows_plan(g, false);
-        // Both times estimated, a margin of 7 % to the general kernel.  Fitted to 1249 layers in and around the networks here (3x3 and
+        // Both times estimated, a margin of 3 % to the general kernel.  Fitted to 1249 layers in and around the networks here (3x3 and
         // 5x5, strides 1 and 2, 3 to 256 channels, 7 to 64 rows, 8 to 512 examples, with and without a bias), both kernels measured
-        // on each: half of the estimates are within 8 % (this kernel) and 6 % (the general one), nine of ten within 26 % and 16 %.  Where
-        // the kernels differ by a quarter or more (729 layers) the faster one is chosen in all but 15.  The rule takes 508 layers, 26 of
-        // them slower by more than 3 % (at most 30 %); all 1249 together take 0.868 of the general kernel's time, where the faster of
-        // the two each time would be 0.856.  us, general / this: 64 -> 64 3x3 on 56 x 56, 64 examples 283 / 195, 48: 188 / 193, 128: 465 /
-        // 382; with a bias 374 / 199, 242 / 195, 617 / 386; 16 -> 16 on 32 x 32, 256: 103 / 33; 128 -> 128 on 28 x 28, 256: 654 /
-        // 919; 5x5, 40 -> 72 stride 2 on 45 x 37 with a bias, 40: 128 / 108.
-        c.use = c.plan.ok && c.plan.us < 0.93 * conv_general_f32_us(g);
+        // on each: half of the estimates are within 5 % for either kernel, nine of ten within 14 %.  Where the kernels differ by a
+        // quarter or more (763 layers) the faster one is chosen in all but 5.  The rule takes 537 layers, 13 of them slower by more
+        // than 3 % (at most 31 %); all 1249 together take 0.858 of the general kernel's time, where the faster of the two each time
+        // would be 0.852.  us, general / this: 64 -> 64 3x3 on 56 x 56, 64 examples 278 / 196, 48: 185 / 192, 128: 467 / 381; with a
+        // bias 376 / 200, 245 / 194, 615 / 390; 16 -> 16 on 32 x 32, 256: 102 / 32; 128 -> 128 on 28 x 28, 256: 651 / 916; 5x5,
+        // 40 -> 72 stride 2 on 45 x 37 with a bias, 40: 128 / 107.
+        c.use = c.plan.ok && c.plan.us < 0.97 * conv_general_f32_us(g);
         if (shared && c.use) c.plan = rows_plan(g, true);
         std::memcpy(c.key, key, sizeof(key));
     }
