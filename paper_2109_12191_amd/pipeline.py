@@ -305,7 +305,8 @@ class PrivatiseStep:
         self._phases = 0                         # phases issued since begin_step
         self._sum_plan = None                    # plan of the last of them
         self._last_sqnorm = torch.zeros((self.n_groups, self.rows), dtype=f32, device=dev)
-        self._group_sqnorm = self._last_sqnorm   # of the most recent micro-step
+        self._group_sqnorm = [self._last_sqnorm] * self.copies      # of the last micro-steps (one per copy)
+        self._last = 0                           # the most recent one
         self._g_last = None
         self.graph = None
         self.micro_steps_done = 0
@@ -463,7 +464,7 @@ class PrivatiseStep:
     @property
     def group_sqnorm(self) -> torch.Tensor:
         """[groups, n] squared norms of the most recent micro-step."""
-        return self._group_sqnorm
+        return self._group_sqnorm[self._last]
 
     @property
     def g(self) -> Optional[torch.Tensor]:
@@ -589,12 +590,13 @@ class PrivatiseStep:
                 ev.record(st)
                 evs.append(ev)
             store.done = evs
+        for k in range(max(0, plan.tensors - self.copies), plan.tensors):
+            self._last = (self.micro_steps_done + k) % self.copies
+            self._group_sqnorm[self._last] = gsq[:, k * self.rows:(k + 1) * self.rows]
         # the last micro-step's norms are a matrix of their own, as its callers read it
-        self._group_sqnorm = gsq[:, -self.rows:]
-        if not self._group_sqnorm.is_contiguous():
-            if ends_step:
-                self._last_sqnorm.copy_(self._group_sqnorm)
-            self._group_sqnorm = self._last_sqnorm
+        if ends_step and not self._group_sqnorm[self._last].is_contiguous():
+            self._last_sqnorm.copy_(self._group_sqnorm[self._last])
+            self._group_sqnorm[self._last] = self._last_sqnorm
         self._g_last = g_buf[-self.rows:] if g_buf is not None else None
         self.micro_steps_done += plan.tensors
         self._phases += 1

@@ -336,6 +336,9 @@ def test_what_a_step_shows_is_one_micro_steps(order, streams):
     ps._plan(8).group_sqnorm[0].copy_(torch.arange(wl.n_groups * 8, dtype=torch.float32).view(wl.n_groups, 8))
     ps.run(_steps(wl, 8))
     assert torch.equal(ps.group_sqnorm[:, 0], torch.arange(wl.n_groups, dtype=torch.float32) * 8 + 7)
+    # as many of the last micro-steps' norms as there are buffer copies, by the number of the micro-step
+    for m in range(8 - ps.copies, 8):
+        assert torch.equal(ps._group_sqnorm[m % ps.copies][:, 0], torch.arange(wl.n_groups, dtype=torch.float32) * 8 + m)
 
 
 def test_buffers_go_with_their_step(order):
