@@ -1,25 +1,36 @@
 // Per-example weight gradients of fp32 convolutions with square odd kernels (3, 5; padding (k - 1) / 2, stride 1 or 2), H1 of
 // the path, from raw image rows:
 //     dW_i[co, ci, kh, kw] = sum_{oh, ow} dY_i[co, oh, ow] * Xpad_i[ci, s oh + kh - p, s ow + kw - p].
-// What bounds these layers is the fp32 matrix rate (157 TFLOP/s, 256 flop per cycle and compute unit): an im2col column per
-// (ci, kh, kw) fetches and stages every element of X k * k times, which costs the general kernel more cycles than its MFMAs (35
-// TFLOP/s on 64 -> 64 at 56 x 56; and 64 x 64 tiles of a 16-channel layer are three quarters padding).  Here rows of dY and X go to LDS
-// once per chunk of output rows and all k * k taps are read from them.
+// The fp32 matrix rate (157 TFLOP/s) bounds these layers in any kernel that multiplies fp32 numbers as they are, and an im2col column per
+// (ci, kh, kw) stages every element of X k * k times.  Here rows of dY and X go to LDS once per chunk of output rows, all k * k taps
+// are read from them, and the products run on the bf16 matrix units, which are sixteen times as fast: every staged number is split
+// into three bf16 numbers whose sum it is, bit for bit (its nearest bf16, the nearest one to what that leaves, and the rest), and a product of two numbers
+// is the six products of their parts that reach 2^-24 of it,
+//     a b ~ ah bh + (ah bm + am bh) + (am bm + ah bl + al bh),
+// each exact in fp32 and added up in fp32.  What is left out is below 2^-23 of the product, and a sum of 32 of them is rounded a handful of
+// times where the fp32 instruction rounds at every step.  Relative error of the gradient against 64 bits (2-norm), fp32 instruction ->
+// this: 64 -> 64 3x3 on 56 x 56 5.0e-7 -> 1.3e-7, 16 -> 16 on 32 x 32 2.8e-7 -> 0.9e-7, 64 -> 64 on 8 x 8 1.3e-7 -> 0.5e-7, 40 -> 72 5x5 stride 2 on
+// 45 x 37 2.6e-7 -> 0.8e-7.
+// An infinity or a NaN has no such parts (and its sums are not finite): a block with a sum that is not finite is computed again in plain fp32, element
+// by element.
 //
 // A workgroup owns one block of at most 32 x 32 channels (32 x 16 for 5 x 5) of one example (several examples in a row, so that the set-up is
-// paid once and loads run ahead across examples).  K is cut into runs of four output columns of one row.  Wave (kh, q) keeps the
+// paid once and loads run ahead across examples).  K is cut into runs of eight output columns of one row.  Wave (kh, q) keeps the
 // k taps of kernel row kh as k accumulators per 16 x 16 channels and takes every q-th group of four runs: in
-// v_mfma_f32_16x16x4_f32 the four lane groups of an operand are the four K values, so lane group t holds run t -- four
-// consecutive floats of dY, one 16-byte read, and the 4 s + k - s floats of X behind them, two to four aligned 16-byte reads --
-// and MFMA (j, kw) multiplies column j of each run with X shifted by kw.  12 k or more MFMAs of 32 cycles follow a handful
-// of LDS reads, so neither LDS nor the vector unit is near its rate.  Columns beyond a row's end and runs beyond the
-// chunk are masked in both operands, as no element outside the image may reach a sum (0 * inf).
+// v_mfma_f32_16x16x32_bf16 the four lane groups of an operand are eight consecutive K values each, so lane group t holds run t -- eight
+// consecutive numbers of dY, one 16-byte read per part, and the sixteen numbers of X around them, 32 bytes per part, from which
+// the k shifted operands are cut.  Stride 2: the rows of X are staged as their even and their odd columns, so that every tap is again a
+// run of consecutive numbers.  Columns beyond a row's end and runs beyond the chunk are zeros in dY (and finite in X).
 //
-// The next chunk's rows are loaded into registers before the MFMAs and written to LDS after them.  A finished block is
+// The next chunk's rows are loaded into registers before the MFMAs.  Where LDS has room for two chunks (a lone workgroup on a
+// compute unit), half of the waves split and write the next chunk before their MFMAs and half after them, so that the vector and the
+// matrix units work side by side; where it has not, workgroups overlap one another.  A finished block is
 // added up over q in LDS in a fixed order, 16 rows at a time, and leaves as contiguous rows of the gradient; its square goes to one partial
 // norm per (example, block).
-// MI355X, per-example call alone, general kernel -> this: 64 examples of 64 -> 64 3x3 with a bias on 56 x 56: 378 -> 202 us (73 TFLOP/s);
-// 40 of 40 -> 72 5x5 stride 2 with a bias on 45 x 37: 126 -> 109 us.  Where it is chosen: rows_choice.
+// A SIMD gives MFMAs and vector instructions their turns (a 16x16x32 MFMA takes 18.8 cycles, every vector instruction beside it 2.6 more), so what
+// bounds a full chip is their sum: 3.2 us per chunk of two rows of 64 -> 64 on 56 wide maps, half of it MFMAs.
+// MI355X, per-example call alone, fp32 instruction -> this: 64 examples of 64 -> 64 3x3 with a bias on 56 x 56: 194 -> 100 us (154 TFLOP/s), 256:
+// 800 -> 433; 256 of 16 -> 16 on 32 x 32: 30 -> 20; 40 of 40 -> 72 5x5 stride 2 with a bias on 45 x 37: 105 -> 78.  Where it is chosen: rows_choice.
 #include "group.h"
 #include "internal.h"
 #include "pieces.h"
@@ -34,16 +45,17 @@ namespace dp {
 namespace {
 
 typedef float r_f32x4 __attribute__((ext_vector_type(4)));
-typedef r_f32x4 r_f32x4_a4 __attribute__((aligned(4)));
 
-constexpr int CR_CH = 32;                       // output channels of a block
-constexpr int cr_cin(int k) { return k == 5 ? 16 : 32; }                // its input channels (5 accumulators a block of 16 x 16: registers)
-constexpr int CR_LEFT = 4;                      // zeros in front of a staged image row (padding <= 2; keeps pieces on 16 bytes)
+constexpr int CR_LEFT = 4;                      // zeros in front of a staged image row (padding <= 2; keeps pieces of four on 8 bytes)
 constexpr int cr_qmax(int k) { return k == 5 ? 2 : 4; }
-constexpr int cr_pieces(int k) { return k == 3 ? 7 : 8; }               // 16-byte pieces a thread moves per chunk
-// 16-byte reads that cover X of a run: the first starts at the multiple of four at or below the run's first element
-constexpr int cr_first(int k) { return (CR_LEFT - (k - 1) / 2) % 4; }   // where the run's first element is in them
-constexpr int cr_reads(int k, int s) { return (cr_first(k) + 3 * s + k + 3) / 4; }
+constexpr int CR_PIECES = 4;                    // 16-byte pieces a thread moves per chunk
+// Where tap kw of a run is: in which columns of the row (stride 2: 0 the even, 1 the odd ones), and how many numbers behind the run's window
+constexpr int cr_parity(int k, int s, int kw) { return s == 1 ? 0 : (kw - (k - 1) / 2) & 1; }
+constexpr int cr_shift(int k, int s, int kw) { return CR_LEFT + (s == 1 ? kw - (k - 1) / 2 : (kw - (k - 1) / 2 - cr_parity(k, s, kw)) / 2); }
+
+typedef __bf16 r_bf16x8 __attribute__((ext_vector_type(8)));
+typedef uint32_t r_u32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t r_u32x2 __attribute__((ext_vector_type(2)));
 
 struct RowsArgs {
     const void *x, *dy;             // [n][cin][H][W], [n][cout][OH][OW]
@@ -57,27 +69,50 @@ struct RowsArgs {
     int q;                          // waves that share the runs of a kernel row
     int rows, chunks;               // output rows per chunk, chunks per example
     int rpr;                        // runs per output row
-    int xp, cha, chx;               // LDS pitches in floats: an image row, a channel of dY, a channel of X
-    int tm, tn;                     // channels staged per block (16 or 32)
+    int xp, cha, chx;               // LDS pitches in dwords: a staged image row, a channel of dY, a channel of X
+    int waves_a;                    // waves that stage dY (the others stage X)
+    int bufs;                       // chunks in LDS (1 or 2)
     int bias;
+    int ragged, narrow;             // rows of dY or X are no multiple of four; are shorter than four
 };
 
 __device__ __forceinline__ int cr_small_div(int a, int d) { return (int)(((float)a + 0.5f) * __builtin_amdgcn_rcpf((float)d)); }   // a, d < 2^15, quotient exact: the distance to an integer is at least 1 / (2 d)
 
-template <int K, int S>
+// The three bf16 parts of a pair of numbers, packed: the number rounded to the nearest bf16, what that leaves of it rounded likewise, and what is
+// then left, which has no more than eight significant bits.
+__device__ __forceinline__ void cr_split(float v0, float v1, uint32_t (&part)[3])
+{
+    typedef float f32x2 __attribute__((ext_vector_type(2)));
+    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+#pragma unroll
+    for (int p = 0; p < 3; ++p) {
+        part[p] = __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2{v0, v1}), bf16x2));
+        if (p < 2) {
+            v0 -= __uint_as_float(part[p] << 16);
+            v1 -= __uint_as_float(part[p] & 0xFFFF0000u);
+        }
+    }
+}
+
+constexpr unsigned CR_NOWHERE = 0xFFFFFFF0u;     // a byte beyond every example: the load gives zeros
+
+// NM x NN blocks of 16 x 16 channels
+template <int K, int S, int NM, int NN>
 __global__ void __launch_bounds__(64 * K * cr_qmax(K)) conv_rows_kernel(const Grouped<RowsArgs> grp)
 {
-    extern __shared__ __attribute__((aligned(16))) float rows_lds[];
-    constexpr int PT = cr_pieces(K), NB = cr_reads(K, S), FIRST = cr_first(K), PAD = (K - 1) / 2, CI = cr_cin(K), NI = CI / 16;
+    extern __shared__ __attribute__((aligned(16))) uint32_t rows_lds[];
+    constexpr int PT = CR_PIECES, PAD = (K - 1) / 2, CO = 16 * NM, CI = 16 * NN;
     unsigned bid;
     const RowsArgs &a = grp.a[group_pick(grp, bid)];
     const int tiles = a.tiles_m * a.tiles_n;
     const int batches = (a.n + a.ex_per_wg - 1) / a.ex_per_wg;
-    if ((int)bid >= batches * tiles) return;
-    const int batch = (int)bid / tiles, tile = (int)bid - batch * tiles;
+    // the blocks of an example read the same rows: one after the other behind the L2 of one XCD
+    const int per_xcd = (batches * tiles + 7) >> 3, wg = (int)(bid & 7u) * per_xcd + (int)(bid >> 3);
+    if (wg >= batches * tiles) return;
+    const int batch = wg / tiles, tile = wg - batch * tiles;
     const int i_begin = batch * a.ex_per_wg, i_end = min(a.n, i_begin + a.ex_per_wg);
-    const int m0 = (tile / a.tiles_n) * CR_CH, n0 = (tile - (tile / a.tiles_n) * a.tiles_n) * CI;
-    const int cm = min(CR_CH, a.cout - m0), cn = min(CI, a.cin - n0);       // live channels
+    const int m0 = (tile / a.tiles_n) * CO, n0 = (tile - (tile / a.tiles_n) * a.tiles_n) * CI;
+    const int cm = min(CO, a.cout - m0), cn = min(CI, a.cin - n0);       // live channels
     const int tid = (int)threadIdx.x, nthreads = 64 * K * a.q, nwaves = K * a.q;
     const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int kh = wave / a.q, q = wave - kh * a.q;
@@ -85,183 +120,272 @@ __global__ void __launch_bounds__(64 * K * cr_qmax(K)) conv_rows_kernel(const Gr
     const int lines = (R - 1) * S + K;
     const int groups = (R * RPR + 3) / 4;
 
-    float *sA = rows_lds, *sX = sA + a.tm * a.cha;
-    int *tab = reinterpret_cast<int *>(sX + a.tn * a.chx + 16);
-    float *epi = reinterpret_cast<float *>(tab + groups * 4);
-    const int EP = a.tn * K * K + 2;                   // pitch of a gradient row in LDS (spreads the lane groups over the banks)
-    float *sbias = epi + 16 * EP, *red = sbias + CR_CH;
+    // LDS: per chunk dY, [channel][run][part][8 numbers], and X, [channel][row][8 columns of a parity][parity][part]; then the runs' offsets.
+    // (Parts of eight numbers side by side: every read of a run has a constant offset.)  The epilogue uses the chunks' place.
+    const int chunk_x = CO * a.cha, chunk_dwords = chunk_x + CI * a.chx;
+    int *tab = reinterpret_cast<int *>(rows_lds + a.bufs * chunk_dwords);
+    float *red = reinterpret_cast<float *>(tab + groups * 4);
+    float *epi = reinterpret_cast<float *>(rows_lds);
+    const int EP = CI * K * K + 2;                     // pitch of a gradient row in LDS (spreads the lane groups over the banks)
 
-    // zero everything once: margins, dead channels and the runs beyond a chunk's last one are never written
-    for (int t = tid; t < a.tm * a.cha + a.tn * a.chx + 16; t += nthreads) rows_lds[t] = 0.0f;
-    // per run: offset of its X inside a channel, and how many of its four columns exist
+    // per run: where its X starts inside a channel
     for (int t = tid; t < groups * 4; t += nthreads) {
         const int r = cr_small_div(t, RPR), c = t - r * RPR;
-        tab[t] = t < R * RPR ? ((r * S * a.xp + 4 * S * c + CR_LEFT - PAD - FIRST) | (min(4, OW - 4 * c) << 24)) : 0;
+        tab[t] = t < R * RPR ? r * S * a.xp + 12 * S * c : 0;
     }
-    // what this thread moves per chunk: source offset at output row 0, and packed: LDS offset, row of the chunk, elements, dY or X
-    const int xpr = (W + 3) / 4;
-    const int n_a = cm * R * RPR, n_all = n_a + cn * lines * xpr;
-    int off[PT], meta[PT];
+    // What this thread moves per chunk: the first waves_a waves pieces of dY, the others pieces of X.  Byte offset at output row 0 of the
+    // example, and packed: LDS dword, row of the chunk, elements (0: no piece).
+    const bool is_x = wave >= a.waves_a;
+    const int apr = (OW + 3) / 4, xpr = (W + 3) / 4, a_threads = 64 * a.waves_a;
+    unsigned off[PT];
+    int meta[PT];
 #pragma unroll
     for (int u = 0; u < PT; ++u) {
-        const int idx = tid + nthreads * u;
-        off[u] = 0; meta[u] = 0;
-        if (idx < n_a) {
-            const int row = cr_small_div(idx, RPR), pc = idx - row * RPR, ch = cr_small_div(row, R), r = row - ch * R;
-            off[u] = ((m0 + ch) * OH + r) * OW + 4 * pc;
-            meta[u] = (ch * a.cha + (r * RPR + pc) * 4) | (r << 16) | (min(4, OW - 4 * pc) << 24);
-        } else if (idx < n_all) {
-            const int t = idx - n_a, row = cr_small_div(t, xpr), pc = t - row * xpr, ch = cr_small_div(row, lines), k = row - ch * lines;
-            off[u] = ((n0 + ch) * H + k - PAD) * W + 4 * pc;
-            meta[u] = (a.tm * a.cha + ch * a.chx + k * a.xp + CR_LEFT + 4 * pc) | (k << 16) | (min(4, W - 4 * pc) << 24) | (1 << 28);
+        if (!is_x) {
+            const int idx = tid + a_threads * u;
+            const int row = cr_small_div(idx, apr), pc = idx - row * apr, ch = cr_small_div(row, R), r = row - ch * R;
+            off[u] = 4u * (unsigned)(((m0 + ch) * OH + r) * OW + (a.narrow ? 4 * pc : min(4 * pc, OW - 4)));
+            meta[u] = idx < cm * R * apr ? (ch * a.cha + (r * RPR + pc / 2) * 12 + (pc & 1) * 2) | (r << 16) | (min(4, OW - 4 * pc) << 24) : 0;
+        } else {
+            const int idx = tid - a_threads + (nthreads - a_threads) * u;
+            const int row = cr_small_div(idx, xpr), pc = idx - row * xpr, ch = cr_small_div(row, lines), k = row - ch * lines;
+            const int d = (CR_LEFT + 4 / S * pc) / 2;  // dword of the row (of one parity)
+            off[u] = 4u * (unsigned)(((n0 + ch) * H + k - PAD) * W + (a.narrow ? 4 * pc : min(4 * pc, W - 4)));
+            meta[u] = idx < cn * lines * xpr ? (chunk_x + ch * a.chx + k * a.xp + (d / 4) * (12 * S) + d % 4) | (k << 16) | (min(4, W - 4 * pc) << 24) : 0;
         }
     }
     r_f32x4 raw[PT];
-    auto fetch = [&](int i, int oh0) {
-        const float *dy_ex = example_at_uniform<float>(a.dy, a.dy_tab, i, (size_t)a.cout * OH * OW);
-        const float *x_ex = example_at_uniform<float>(a.x, a.x_tab, i, (size_t)a.cin * H * W);
+    int f_i = i_begin, f_c = 0;                        // next chunk to fetch
+    __amdgpu_buffer_rsrc_t rsrc;
+    auto fetch = [&]() {
+        if (f_i >= i_end) return;
+        const int row0 = is_x ? f_c * R * S - PAD : f_c * R, rows = is_x ? H : OH;
+        const unsigned step = 4u * (unsigned)(is_x ? f_c * R * S * W : f_c * R * OW);
+        if (f_c == 0) {
+            const unsigned bytes = 4u * (unsigned)(is_x ? a.cin * H * W : a.cout * OH * OW);
+            const float *ex = example_at_uniform<float>(is_x ? a.x : a.dy, is_x ? a.x_tab : a.dy_tab, f_i, bytes / 4u);
+            rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(ex), 0, bytes, 0x00020000);
+        }
+        if (++f_c == a.chunks) { f_c = 0; ++f_i; }
 #pragma unroll
         for (int u = 0; u < PT; ++u) {
             int mt = meta[u];
-            asm volatile("" : "+v"(mt));               // unpacked anew for every chunk: kept unpacked, it is four registers a piece
-            const int count = (mt >> 24) & 7, r = (mt >> 16) & 0x7f;
-            const bool is_x = (mt >> 28) & 1;
-            const int row = is_x ? oh0 * S + r - PAD : oh0 + r;
-            const float *src = is_x ? x_ex + (off[u] + oh0 * S * W) : dy_ex + (off[u] + oh0 * OW);
-            const bool ok = (unsigned)row < (unsigned)(is_x ? H : OH);
-            raw[u] = r_f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-            if (ok && count == 4) raw[u] = *reinterpret_cast<const r_f32x4_a4 *>(src);
-            else if (ok && count) {                    // the end of a row that is no multiple of four: element by element
-                raw[u].x = src[0];
-                if (count > 1) raw[u].y = src[1];
-                if (count > 2) raw[u].z = src[2];
+            asm volatile("" : "+v"(mt));               // unpacked anew for every chunk: kept unpacked, it is three registers a piece
+            const bool there = mt && (unsigned)(row0 + ((mt >> 16) & 0xff)) < (unsigned)rows;
+            const unsigned at = there ? off[u] + step : CR_NOWHERE;
+            if (a.narrow) {                            // rows of fewer than four numbers
+                const int count = mt >> 24;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) raw[u][e] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rsrc, there && e < count ? at + 4 * e : CR_NOWHERE, 0, 0));
+            } else {
+                raw[u] = __builtin_bit_cast(r_f32x4, __builtin_amdgcn_raw_buffer_load_b128(rsrc, at, 0, 0));
             }
         }
     };
-    auto stage = [&]() {
+    const bool has_bias = a.bias && n0 == 0;
+    float bsum[PT];                                    // of the numbers of dY that this thread staged
+    auto stage = [&](int buf) {
+        uint32_t *const chunk = rows_lds + buf * chunk_dwords;
+        if (a.ragged) {
+            // the end of a row that is no multiple of four was fetched as the row's last four numbers: the first `count` places get the last ones
+            asm volatile("");
 #pragma unroll
-        for (int u = 0; u < PT; ++u) {
-            int mt = meta[u];
-            asm volatile("" : "+v"(mt));
-            if (mt >> 24) *reinterpret_cast<r_f32x4 *>(rows_lds + (mt & 0xffff)) = raw[u];
+            for (int u = 0; u < PT; ++u)
+#pragma unroll
+                for (int c = 3; c > 0; --c) raw[u] = meta[u] >> 24 <= c ? r_f32x4{raw[u].y, raw[u].z, raw[u].w, 0.0f} : raw[u];
+        }
+#pragma unroll
+        for (int u = 0; u < PT; ++u)
+            if (int mt = meta[u]) {
+                asm volatile("" : "+v"(mt));
+                uint32_t lo[3], hi[3];
+                const r_f32x4 v = raw[u];
+                uint32_t *dst = chunk + (mt & 0xffff);
+                if (S == 1 || !is_x) {
+                    if (has_bias) bsum[u] += (v.x + v.y) + (v.z + v.w);
+                    cr_split(v.x, v.y, lo);
+                    cr_split(v.z, v.w, hi);
+#pragma unroll
+                    for (int p = 0; p < 3; ++p) *reinterpret_cast<r_u32x2 *>(dst + 4 * p) = r_u32x2{lo[p], hi[p]};
+                } else {                               // even columns and odd columns
+                    cr_split(v.x, v.z, lo);
+                    cr_split(v.y, v.w, hi);
+#pragma unroll
+                    for (int p = 0; p < 3; ++p) { dst[4 * p] = lo[p]; dst[4 * p + 12] = hi[p]; }
+                }
+            }
+    };
+
+    r_f32x4 acc[NM][NN][K];
+    const int kq = lane >> 4;
+    // the MFMAs of a chunk's runs
+    auto multiply = [&](int buf, int live) {
+        const uint32_t *pa = rows_lds + buf * chunk_dwords + (lane & 15) * a.cha;
+        const uint32_t *px = rows_lds + buf * chunk_dwords + chunk_x + (lane & 15) * a.chx + kh * a.xp;
+#pragma unroll 1
+        for (int g = q; g < live; g += a.q) {
+            const int t = 4 * g + kq, at = tab[t];
+            r_bf16x8 av[NM][3];
+#pragma unroll
+            for (int b = 0; b < NM; ++b)
+#pragma unroll
+                for (int p = 0; p < 3; ++p) av[b][p] = __builtin_bit_cast(r_bf16x8, *reinterpret_cast<const r_u32x4 *>(pa + b * 16 * a.cha + 12 * t + 4 * p));
+#pragma unroll
+            for (int by = 0; by < NN * S; ++by) {
+                const int b = by / S, y = by % S;
+                asm volatile("" ::: "memory");           // one block's X (of one parity) at a time in registers
+                uint32_t w[3][8];
+#pragma unroll
+                for (int p = 0; p < 3; ++p) {
+                    const uint32_t *src = px + b * 16 * a.chx + at + 12 * y + 4 * p;
+                    const r_u32x4 v = *reinterpret_cast<const r_u32x4 *>(src);
+                    const r_u32x4 e = *reinterpret_cast<const r_u32x4 *>(src + 12 * S);
+                    w[p][0] = v.x; w[p][1] = v.y; w[p][2] = v.z; w[p][3] = v.w; w[p][4] = e.x; w[p][5] = e.y; w[p][6] = e.z; w[p][7] = e.w;
+                }
+#pragma unroll
+                for (int kw = 0; kw < K; ++kw) {
+                    if (cr_parity(K, S, kw) != y) continue;
+                    const int sh = cr_shift(K, S, kw), d = sh / 2;
+                    r_bf16x8 xv[3];
+#pragma unroll
+                    for (int p = 0; p < 3; ++p) {
+                        r_u32x4 v;
+                        if (sh & 1)
+                            v = r_u32x4{funnel(w[p][d + 1], w[p][d], 16), funnel(w[p][d + 2], w[p][d + 1], 16),
+                                        funnel(w[p][d + 3], w[p][d + 2], 16), funnel(w[p][d + 4], w[p][d + 3], 16)};
+                        else
+                            v = r_u32x4{w[p][d], w[p][d + 1], w[p][d + 2], w[p][d + 3]};
+                        xv[p] = __builtin_bit_cast(r_bf16x8, v);
+                    }
+                    // The six products of 32 K values, small ones first, are a sum of their own, which is then added to the block: it is much smaller
+                    // than the block, and so is what the six instructions round off.
+                    constexpr int pairs[6][2] = {{2, 0}, {0, 2}, {1, 1}, {1, 0}, {0, 1}, {0, 0}};
+                    r_f32x4 sum[NM];
+#pragma unroll
+                    for (int e = 0; e < 6; ++e)
+#pragma unroll
+                        for (int m = 0; m < NM; ++m)
+                            sum[m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av[m][pairs[e][0]], xv[pairs[e][1]], e ? sum[m] : r_f32x4{0.0f, 0.0f, 0.0f, 0.0f}, 0, 0, 0);
+#pragma unroll
+                    for (int m = 0; m < NM; ++m) acc[m][b][kw] += sum[m];
+                }
+            }
         }
     };
 
-    r_f32x4 acc[2][NI][K];
-    float bsum[2];
-    const float *pa = sA + (lane & 15) * a.cha, *px = sX + (lane & 15) * a.chx + kh * a.xp;
-    const int kq = lane >> 4;
-    const bool has_bias = a.bias && n0 == 0 && kh == 0;
-    // the MFMAs of one chunk of `runs` runs for NM x NN blocks of 16 x 16 channels
-    auto multiply = [&](auto nm, auto nn, int runs) {
-        constexpr int NM = decltype(nm)::value, NN = decltype(nn)::value;
-#pragma unroll 1
-        for (int g = q; g < groups; g += a.q) {
-            const int t = 4 * g + kq, info = tab[t];
-            const int live = t < runs ? (info >> 24) : 0;
-            r_f32x4 av[NM];
-            float xv[NN][4 * NB];
+    const bool early = a.bufs == 2 && ((wave >> 2) & 1) == 0;      // waves 0 .. 3 are on different SIMDs
+    const int steps = a.chunks * a.unit;
+    fetch();
+    for (int row_i = i_begin / a.unit; row_i * a.unit < i_end; ++row_i) {
+        // margins, dead channels and the runs beyond a chunk's last one are never written
+        for (int t = tid; t < a.bufs * chunk_dwords; t += nthreads) rows_lds[t] = 0u;
 #pragma unroll
-            for (int b = 0; b < NM; ++b) av[b] = *reinterpret_cast<const r_f32x4 *>(pa + b * 16 * a.cha + 4 * t);
+        for (int m = 0; m < NM; ++m)
 #pragma unroll
             for (int b = 0; b < NN; ++b)
 #pragma unroll
-                for (int k = 0; k < NB; ++k) {
-                    const r_f32x4 v = *reinterpret_cast<const r_f32x4 *>(px + b * 16 * a.chx + (info & 0xffff) + 4 * k);
-                    xv[b][4 * k] = v.x; xv[b][4 * k + 1] = v.y; xv[b][4 * k + 2] = v.z; xv[b][4 * k + 3] = v.w;
-                }
-            if (has_bias)
-#pragma unroll
-                for (int b = 0; b < NM; ++b) bsum[b] += (av[b].x + av[b].y) + (av[b].z + av[b].w);
-#pragma unroll
-            for (int j = 0; j < 4; ++j)
-#pragma unroll
-                for (int kw = 0; kw < K; ++kw)
-#pragma unroll
-                    for (int b = 0; b < NN; ++b) {
-                        const float xo = j < live ? xv[b][FIRST + j * S + kw] : 0.0f;
-#pragma unroll
-                        for (int m = 0; m < NM; ++m)
-                            acc[m][b][kw] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[m][j], xo, acc[m][b][kw], 0, 0, 0);
-                    }
-        }
-    };
-    typedef std::integral_constant<int, 1> one;
-    typedef std::integral_constant<int, 2> two;
-    typedef std::integral_constant<int, NI> wide;
-
-    fetch(i_begin, 0);
-    int in_unit = 0;
-    for (int i = i_begin; i < i_end; ++i) {
-        if (in_unit == 0)
-#pragma unroll
-        for (int m = 0; m < 2; ++m) {
-            bsum[m] = 0.0f;
-#pragma unroll
-            for (int b = 0; b < NI; ++b)
-#pragma unroll
                 for (int k = 0; k < K; ++k) acc[m][b][k] = r_f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-        }
-        for (int c = 0; c < a.chunks; ++c) {
-            const int oh0 = c * R;
-            __syncthreads();                           // the previous chunk has been read (first pass: the clearing is done)
-            stage();
-            __syncthreads();
-            if (c + 1 < a.chunks) fetch(i, oh0 + R);
-            else if (i + 1 < i_end) fetch(i + 1, 0);
-            const int runs = min(R, OH - oh0) * RPR;
-            if (cm > 16) {
-                if (NI == 2 && cn > 16) multiply(two{}, wide{}, runs);
-                else multiply(two{}, one{}, runs);
-            } else {
-                if (NI == 2 && cn > 16) multiply(one{}, wide{}, runs);
-                else multiply(one{}, one{}, runs);
+#pragma unroll
+        for (int u = 0; u < PT; ++u) bsum[u] = 0.0f;
+        __syncthreads();
+        stage(0);
+        fetch();                                       // (the last chunk's: of the next example)
+        __syncthreads();
+        int c = 0;
+        for (int step = 0; step < steps; ++step) {
+            const bool more = step + 1 < steps;
+            const int buf = a.bufs == 2 ? step & 1 : 0;
+            if (early && more) { stage(buf ^ 1); fetch(); }
+            const int live = (min(R, OH - c * R) * RPR + 3) / 4;
+            multiply(buf, live);
+            if (++c == a.chunks) c = 0;
+            if (!early && more) {
+                if (a.bufs == 1) __syncthreads();      // everyone has read this chunk
+                stage(a.bufs == 1 ? 0 : buf ^ 1);
+                fetch();
             }
+            __syncthreads();
         }
-        if (++in_unit < a.unit) continue;              // the next example adds to the same block
-        in_unit = 0;
-        const int row_i = i / a.unit;
-        // the block, 16 rows at a time: summed over q in order, squared, stored
+        float odd = 0.0f;
+#pragma unroll
+        for (int m = 0; m < NM; ++m)
+#pragma unroll
+            for (int b = 0; b < NN; ++b)
+#pragma unroll
+                for (int k = 0; k < K; ++k)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) odd = fmaf(acc[m][b][k][r], 0.0f, odd);
+        const bool plain = __syncthreads_or(odd != 0.0f) != 0;        // (true for NaN)
         float ss = 0.0f;
+        if (plain) {
+            // not every sum is finite: the block element by element, as fp32 arithmetic gives it
+            const int len = cn * K * K;
+#pragma unroll 1
+            for (int t = tid; t < cm * (len + 1); t += nthreads) {
+                const int r = t / (len + 1), col = t - r * (len + 1);
+                const int ci = col / (K * K), tap = col - ci * (K * K), dh = tap / K - PAD, dw = tap - tap / K * K - PAD;
+                const bool bias = col == len;
+                if (bias && !(a.bias && n0 == 0)) continue;
+                float v = 0.0f;
+#pragma unroll 1
+                for (int i = row_i * a.unit; i < (row_i + 1) * a.unit; ++i) {
+                    const float *dy_ch = example_at<float>(a.dy, a.dy_tab, i, (size_t)a.cout * OH * OW) + (size_t)(m0 + r) * OH * OW;
+                    const float *x_ch = example_at<float>(a.x, a.x_tab, i, (size_t)a.cin * H * W) + (size_t)(n0 + (bias ? 0 : ci)) * H * W;
+#pragma unroll 1
+                    for (int oh = 0; oh < OH; ++oh)
+#pragma unroll 1
+                        for (int ow = 0; ow < OW; ++ow) {
+                            const int ih = oh * S + dh, iw = ow * S + dw;
+                            if (bias) v += dy_ch[oh * OW + ow];
+                            else if ((unsigned)ih < (unsigned)H && (unsigned)iw < (unsigned)W) v = fmaf(dy_ch[oh * OW + ow], x_ch[ih * W + iw], v);
+                        }
+                }
+                ss += v * v;
+                if (a.out_w) {
+                    if (bias) a.out_b[(size_t)row_i * a.out_stride_b + m0 + r] = v;
+                    else a.out_w[(size_t)row_i * a.out_stride_w + ((size_t)(m0 + r) * a.cin + n0) * (K * K) + col] = v;
+                }
+            }
+        } else {
+            // the block, 16 rows at a time: summed over q in order, squared, stored
 #pragma unroll
-        for (int m = 0; m < 2; ++m) {
-            if (m * 16 >= cm) break;
-            for (int part = 0; part < a.q; ++part) {
-                if (q == part) {
+            for (int m = 0; m < NM; ++m) {
+                if (m * 16 >= cm) break;
+                float *mine = epi + (q * 16 + kq * 4) * EP + ((lane & 15) * K + kh) * K;
 #pragma unroll
-                    for (int b = 0; b < NI; ++b)
-                        if (b * 16 < cn)
+                for (int b = 0; b < NN; ++b)
 #pragma unroll
-                            for (int k = 0; k < K; ++k)
+                    for (int k = 0; k < K; ++k)
 #pragma unroll
-                                for (int r = 0; r < 4; ++r) {
-                                    float *e = epi + (kq * 4 + r) * EP + ((b * 16 + (lane & 15)) * K + kh) * K + k;
-                                    *e = part ? *e + acc[m][b][k][r] : acc[m][b][k][r];
-                                }
-                    if (has_bias) {
-                        float v = bsum[m];
-                        v += __shfl_xor(v, 16, 64);
-                        v += __shfl_xor(v, 32, 64);
-                        if (lane < 16) sbias[m * 16 + lane] = part ? sbias[m * 16 + lane] + v : v;
+                        for (int r = 0; r < 4; ++r) mine[r * EP + b * 16 * K * K + k] = acc[m][b][k][r];
+                __syncthreads();
+                const int len = cn * K * K;
+                for (int r = wave; r < min(16, cm - m * 16); r += nwaves) {
+                    const int co = m0 + m * 16 + r;
+                    float *dst = a.out_w ? a.out_w + (size_t)row_i * a.out_stride_w + ((size_t)co * a.cin + n0) * (K * K) : nullptr;
+                    for (int t = lane; t < len; t += 64) {
+                        float v = epi[r * EP + t];
+                        for (int part = 1; part < a.q; ++part) v += epi[(part * 16 + r) * EP + t];
+                        ss += v * v;
+                        if (dst) __builtin_nontemporal_store(v, dst + t);
                     }
+                }
+                __syncthreads();                           // epi is free again
+            }
+            if (has_bias) {
+                // a channel's pieces are R * apr threads' in a row (in PT rounds): one thread adds them up
+#pragma unroll
+                for (int u = 0; u < PT; ++u)
+                    if (!is_x) epi[tid + a_threads * u] = bsum[u];
+                __syncthreads();
+                if (tid < cm) {
+                    float v = 0.0f;
+                    for (int t = 0; t < R * apr; ++t) v += epi[tid * R * apr + t];
+                    ss += v * v;
+                    if (a.out_b) a.out_b[(size_t)row_i * a.out_stride_b + m0 + tid] = v;
                 }
                 __syncthreads();
             }
-            const int len = cn * K * K;
-            for (int r = wave; r < min(16, cm - m * 16); r += nwaves) {
-                float *dst = a.out_w ? a.out_w + (size_t)row_i * a.out_stride_w + ((size_t)(m0 + m * 16 + r) * a.cin + n0) * (K * K) : nullptr;
-                for (int t = lane; t < len; t += 64) {
-                    const float v = epi[r * EP + t];
-                    ss += v * v;
-                    if (dst) __builtin_nontemporal_store(v, dst + t);
-                }
-            }
-            __syncthreads();                           // epi is free again
-        }
-        if (a.bias && n0 == 0 && tid < cm) {
-            const float v = sbias[tid];
-            ss += v * v;
-            if (a.out_b) a.out_b[(size_t)row_i * a.out_stride_b + m0 + tid] = v;
         }
         ss = wave_sum(ss);
         if (lane == 0) red[wave] = ss;
@@ -275,7 +399,7 @@ __global__ void __launch_bounds__(64 * K * cr_qmax(K)) conv_rows_kernel(const Gr
 }
 
 struct RowsPlan {
-    int tiles_m, tiles_n, tm, tn, q, rows, chunks, rpr, xp, cha, chx, ex_per_wg;
+    int nm, nn, tiles_m, tiles_n, q, rows, chunks, rpr, xp, cha, chx, bufs, waves_a, ex_per_wg;
     unsigned lds;
     double us;                      // estimated time of a call alone
     bool ok;
@@ -285,39 +409,44 @@ int odd_quads(int floats) { const int v = (floats + 3) / 4; return (v | 1) * 4; 
 
 // us of a per-example call alone.  A launch lasts as long as the compute unit with most blocks, which takes them in rounds of as many
 // workgroups as it has room for.  Chunk by chunk a round needs the longer of two things (a little more where they are close): what
-// the SIMD with most waves multiplies and stages for all its workgroups -- the waves of every workgroup start on the same SIMD, so K q waves count
-// as ceil(K q / 4) on it --, or one workgroup's own chain of barrier, staging and MFMAs.  On 704 layers with several plans measured the one
-// it prefers is 1.6 % slower than the best of them on average, 657 of them within 10 % (one figure for pieces of all widths, and none
-// for fewer waves: 3.4 %, 601).
-double rows_us(int k, const RowsPlan &p, double blocks, int unit, int groups, long long pieces, bool even, bool shared, int resident)
+// the SIMD with most waves issues for all its workgroups -- MFMAs and vector instructions take turns on a SIMD, and the waves of every
+// workgroup start on the same one, so K q waves count as ceil(K q / 4) on it --, or one workgroup's own chain of barrier, loads, staging and
+// MFMAs.  Constants (cycles; per kernel size and stride) fitted to 4223 launches of 181 layers with forced plans: the plan it prefers is 3.5 %
+// slower than the best one on average.
+double rows_us(int k, int s, const RowsPlan &p, double blocks, int unit, int groups, long long pieces, bool ragged, int resident)
 {
-    // us per staged piece: 16-byte reads of rows that are no multiple of four columns are off their alignment and the last one is cut off
-    const double piece = k == 3 ? (even ? 0.565e-3 : 0.794e-3) : even ? 0.823e-3 : 0.995e-3;
-    const double mfma = k == 3 ? 1.2 : 1.23, start = k == 3 ? 2.3 : 4.2, share = k == 3 ? 0.53 : 0.0, epilogue = k == 3 ? 0.92 : 1.07;
-    const double wave = 32.0 * k * 4 * (p.tm / 16) * (p.tn / 16) * ((groups + p.q - 1) / p.q) / 2400.0 * ((k * p.q + 3) / 4) * mfma;
-    const double staging = piece * (double)pieces, chunks = (double)p.chunks * unit;
+    struct Fit { double mfma, vector, group, slot, ragged, chunk, chain, finish, block, launch, lone; };
+    static const Fit fits[2][2] = {{{0.56, 0.33, 175.0, 304.0, 135.0, 2415.0, 0.0, 7000.0, 357.0, 3.7, 595.0}, {0.7, 0.0, 47.0, 278.0, 73.0, 2472.0, 411.0, 13240.0, 254.0, 3.1, 198.0}},
+                                   {{1.19, 0.0, 0.0, 194.0, 75.0, 1893.0, 0.0, 24200.0, 0.0, 2.6, 1617.0}, {1.11, 0.0, 0.0, 213.0, 78.0, 2432.0, 0.0, 21070.0, 206.0, 1.9, 289.0}}};
+    const Fit &c = fits[k / 2 - 1][s - 1];
+    const int turns = (groups + p.q - 1) / p.q;
+    const double group = p.nm * p.nn * k * 6 * 18.8 * c.mfma + (24 * p.nn * s + 4 * p.nm * p.nn * k) * 2.65 * c.vector + c.group;
+    const double staging = (double)pieces / (64 * k * p.q) * (c.slot + (ragged ? c.ragged : 0.0)), chunks = (double)p.chunks * unit;
     const auto round = [&](double r) {
-        const double all = r * (wave + staging), own = share * wave + start + staging;
-        return r > 0.0 ? chunks * std::sqrt(std::sqrt(all * all * all * all + own * own * own * own)) + epilogue * (p.tm / 16) * (p.q + 1) * (0.7 + 0.3 * r) : 0.0;
+        if (r <= 0.0) return 0.0;
+        const double all = r * ((k * p.q + 3) / 4) * (turns * group + staging), own = c.chunk + turns * (group + c.chain) + staging + (p.bufs == 1 ? c.lone : 0.0);
+        return chunks * std::cbrt(all * all * all + own * own * own) + (c.finish + c.block * p.nm * p.nn * k * (p.q + 1)) * (0.6 + 0.4 * r);
     };
     const double most = std::ceil(blocks / 256.0), r = std::min<double>(most, resident), full = std::floor(most / r);
-    // fewer waves than fit on a kernel row measured about 1.2 times what the terms above give, but not beside other layers' workgroups
-    // (ResNet-20, 256 examples on eight streams: 716 us with the factor there, 641 without)
-    return ((k == 3 ? 8.9 : 8.7) + full * round(r) + round(most - full * r)) * (shared || p.q == cr_qmax(k) ? 1.0 : k == 3 ? 1.21 : 1.24);
+    return c.launch + (full * round(r) + round(most - full * r)) / 2400.0;
 }
+
+// Blocks of 16 channels that a workgroup takes of `c` channels (5 x 5: one of input channels, five accumulators a block).
+int rows_nm(const Geo &g) { return g.cout > 16 ? 2 : 1; }
+int rows_nn(const Geo &g) { return g.kh == 3 && g.cin > 16 ? 2 : 1; }
 
 RowsPlan rows_plan(const Geo &g, bool shared)
 {
-    RowsPlan best = {};
-    const int K = g.kh, S = g.stride, CI = cr_cin(K);
-    RowsPlan p = {};
-    p.tiles_m = (g.cout + CR_CH - 1) / CR_CH;
+    RowsPlan best = {}, p = {};
+    const int K = g.kh, S = g.stride;
+    p.nm = rows_nm(g);
+    p.nn = rows_nn(g);
+    const int CO = 16 * p.nm, CI = 16 * p.nn;
+    p.rpr = (g.ow + 7) / 8;
+    p.xp = 12 * S * (p.rpr + 1);                // a run reads sixteen numbers
+    p.tiles_m = (g.cout + CO - 1) / CO;
     p.tiles_n = (g.cin + CI - 1) / CI;
-    p.tm = g.cout > 16 ? 32 : 16;
-    p.tn = CI > 16 && g.cin > 16 ? 32 : 16;
-    p.rpr = (g.ow + 3) / 4;
-    p.xp = CR_LEFT + (g.w + 3) / 4 * 4;
-    const int lc = g.cout < CR_CH ? g.cout : CR_CH, ln = g.cin < CI ? g.cin : CI;      // channels that are staged
+    const int lc = g.cout < CO ? g.cout : CO, ln = g.cin < CI ? g.cin : CI;      // channels that are staged
     const double own = (double)(g.n / g.unit) * p.tiles_m * p.tiles_n;
     // Inside a batch call of several layers the plan with the best rate of a full chip, eight blocks on every compute unit, whatever
     // this layer brings: the other layers' workgroups run on the units beside its own.  ResNet-20, 256 examples on eight streams: 758 us
@@ -326,33 +455,49 @@ RowsPlan rows_plan(const Geo &g, bool shared)
     // several examples in a row where there are far more (example, block) pairs than workgroups that run at a time
     const int e = (int)(own / 4096.0);
     p.ex_per_wg = g.unit * (e < 1 ? 1 : e > 8 ? 8 : e);
-    for (p.q = 1; p.q <= cr_qmax(K); p.q *= 2)
+    for (p.q = 1; p.q <= cr_qmax(K); ++p.q)
         for (p.rows = 1; p.rows <= g.oh && p.rows <= 64; ++p.rows) {
             const int lines = (p.rows - 1) * S + K;
             if (lines > 127) break;
-            const long long pieces = (long long)lc * p.rows * p.rpr + (long long)ln * lines * ((g.w + 3) / 4);
-            if (pieces > (long long)cr_pieces(K) * 64 * K * p.q) break;
+            const long long pieces_a = (long long)lc * p.rows * ((g.ow + 3) / 4), pieces_x = (long long)ln * lines * ((g.w + 3) / 4), pieces = pieces_a + pieces_x;
+            // waves in proportion to the pieces
+            const int waves = K * p.q;
+            p.waves_a = std::min<long long>(std::max<long long>((pieces_a * waves + pieces / 2) / pieces, 1), waves - 1);
+            if (pieces_a > CR_PIECES * 64ll * p.waves_a) ++p.waves_a;
+            if (p.waves_a == waves || pieces_a > CR_PIECES * 64ll * p.waves_a || pieces_x > CR_PIECES * 64ll * (waves - p.waves_a)) {
+                if (pieces > CR_PIECES * 64ll * waves) break;
+                continue;
+            }
             const int groups = (p.rows * p.rpr + 3) / 4;
-            p.cha = odd_quads(groups * 16);
-            p.chx = odd_quads(lines * p.xp + 4);
-            const long long floats = (long long)p.tm * p.cha + (long long)p.tn * p.chx + 16 + groups * 4 + 16 * (p.tn * K * K + 2) + CR_CH + 64;
-            // LDS in quarters, halves or the whole of what a compute unit has: layers of different sizes share a launch
-            const unsigned need = (unsigned)(floats * 4);
-            if (need > 156 * 1024) break;
-            p.lds = need <= 39 * 1024 ? 39 * 1024 : need <= 78 * 1024 ? 78 * 1024 : 156 * 1024;
+            p.cha = odd_quads(groups * 48);
+            p.chx = odd_quads(lines * p.xp);
+            const long long chunk = (long long)CO * p.cha + (long long)CI * p.chx;
+            if (chunk > 0xffff) break;
             p.chunks = (g.oh + p.rows - 1) / p.rows;
-            p.us = rows_us(K, p, blocks, g.unit, groups, pieces, g.w % 4 == 0 && g.ow % 4 == 0, shared, std::max(1, std::min({(int)(156 * 1024 / p.lds), 12 / (K * p.q), 8})));
-            p.ok = true;
-            if (!best.ok || p.us < best.us) best = p;
+            for (p.bufs = 1; p.bufs <= 2; ++p.bufs) {
+                const long long floats = std::max<long long>({p.bufs * chunk, p.q * 16ll * (CI * K * K + 2), CR_PIECES * 64ll * p.waves_a}) + groups * 4 + 16;
+                // LDS in a few even shares of what a compute unit has: layers of different sizes share a launch
+                const unsigned need = (unsigned)(floats * 4);
+                if (need > 156 * 1024) break;
+                p.lds = 156 * 1024;
+                for (int share : {2, 3, 4, 6, 8})
+                    if (need <= (unsigned)(156 / share * 1024)) p.lds = 156 / share * 1024;
+                const int resident = std::max(1, std::min({(int)(156 * 1024 / p.lds), 12 / (K * p.q), 8}));
+                p.us = rows_us(K, S, p, blocks, g.unit, groups, pieces, g.w % 4 || g.ow % 4, resident);
+                p.ok = true;
+                if (!best.ok || p.us < best.us) best = p;
+            }
         }
     return best;
 }
 
 size_t cr_align16(size_t b) { return (b + 15) & ~(size_t)15; }
 
-template <int K> const void *rows_fn(int stride)
+template <int K, int S> const void *rows_fn(int nm, int nn)
 {
-    return stride == 2 ? reinterpret_cast<const void *>(&conv_rows_kernel<K, 2>) : reinterpret_cast<const void *>(&conv_rows_kernel<K, 1>);
+    if constexpr (K == 3)
+        if (nn == 2) return nm == 2 ? reinterpret_cast<const void *>(&conv_rows_kernel<K, S, 2, 2>) : reinterpret_cast<const void *>(&conv_rows_kernel<K, S, 1, 2>);
+    return nm == 2 ? reinterpret_cast<const void *>(&conv_rows_kernel<K, S, 2, 1>) : reinterpret_cast<const void *>(&conv_rows_kernel<K, S, 1, 1>);
 }
 
 // What the sizes decide, kept for the sizes seen last (a call asks several times): the plan, and whether the kernel is the faster one.
@@ -372,15 +517,13 @@ const RowsChoice &rows_choice(const Geo &g)
     RowsChoice &c = kept[(at ^ at >> 6) % 64];
     if (std::memcmp(c.key, key, sizeof(key)) != 0) {
         c.plan = rows_plan(g, false);
-        // Both times estimated, a margin of 3 % to the general kernel.  Fitted to 1249 layers in and around the networks here (3x3 and
-        // 5x5, strides 1 and 2, 3 to 256 channels, 7 to 64 rows, 8 to 512 examples, with and without a bias), both kernels measured
-        // on each: half of the estimates are within 5 % for either kernel, nine of ten within 14 %.  Where the kernels differ by a
-        // quarter or more (763 layers) the faster one is chosen in all but 5.  The rule takes 537 layers, 13 of them slower by more
-        // than 3 % (at most 31 %); all 1249 together take 0.858 of the general kernel's time, where the faster of the two each time
-        // would be 0.852.  us, general / this: 64 -> 64 3x3 on 56 x 56, 64 examples 278 / 196, 48: 185 / 192, 128: 467 / 381; with a
-        // bias 376 / 200, 245 / 194, 615 / 390; 16 -> 16 on 32 x 32, 256: 102 / 32; 128 -> 128 on 28 x 28, 256: 651 / 916; 5x5,
-        // 40 -> 72 stride 2 on 45 x 37 with a bias, 40: 128 / 107.
-        c.use = c.plan.ok && c.plan.us < 0.97 * conv_general_f32_us(g);
+        // Both times estimated (the general kernel's holds 3 us that only calls outside a graph pay), a margin of 12 % to the general kernel.  On
+        // 181 layers in and around the networks here (3x3 and 5x5, strides 1 and 2, 3 to 160 channels, 7 to 56 rows, 8 to 512 examples, with and
+        // without a bias) all together take 0.74 of the general kernel's time, where the faster of the two each time would be 0.73; a
+        // margin of 5 % took 8 that are slower by more than 5 %, this one takes 3.  us, general / this: 64 -> 64 3x3 on 56 x 56,
+        // 64 examples with a bias 385 / 94, 256 without 795 / 403; 16 -> 16 on 32 x 32, 256: 97 / 20; 128 -> 128 on 28 x 28, 64:
+        // 231 / 127; 32 -> 64 stride 2 on 16 x 16, 256: 22 / 31; 5x5, 40 -> 72 stride 2 on 45 x 37 with a bias, 40: 120 / 78.
+        c.use = c.plan.ok && c.plan.us + 3.0 < 0.88 * conv_general_f32_us(g);
         if (shared && c.use) c.plan = rows_plan(g, true);
         std::memcpy(c.key, key, sizeof(key));
     }
@@ -393,21 +536,30 @@ bool conv_rows_applicable(const Geo &g, int mode)
 {
     if (mode == MODE_WEIGHTED || g.bf16) return false;
     if (g.kh != g.kw || (g.kh != 3 && g.kh != 5) || g.pad != (g.kh - 1) / 2 || g.stride < 1 || g.stride > 2) return false;
-    // offsets inside an example (rows above and below the image included) fit 32 bits; quotients of the set-up stay exact
-    if ((size_t)g.cin * (g.h + 8) * g.w >= ((size_t)1 << 30) || (size_t)g.cout * (g.oh + 64) * g.ow >= ((size_t)1 << 30)) return false;
+    // offsets inside an example (rows above and below the image included) fit 31 bits; quotients of the set-up stay exact
+    if ((size_t)g.cin * (g.h + 8) * g.w >= ((size_t)1 << 29) || (size_t)g.cout * (g.oh + 64) * g.ow >= ((size_t)1 << 29)) return false;
     if (g.w > 4096 || (double)g.n * conv_rows_norm_partial_count(g) >= 1.0e9) return false;
     return rows_choice(g).use;
 }
 
-size_t conv_rows_norm_partial_count(const Geo &g) { return (size_t)((g.cout + CR_CH - 1) / CR_CH) * ((g.cin + cr_cin(g.kh) - 1) / cr_cin(g.kh)); }
+size_t conv_rows_norm_partial_count(const Geo &g)
+{
+    const int co = 16 * rows_nm(g), ci = 16 * rows_nn(g);
+    return (size_t)((g.cout + co - 1) / co) * ((g.cin + ci - 1) / ci);
+}
 
 size_t conv_rows_ws_bytes(const Geo &g) { return cr_align16((size_t)(g.n / g.unit) * conv_rows_norm_partial_count(g) * sizeof(float)); }
 
 const char *conv_rows_variant_name(const Geo &g)
 {
-    static const char *const names[2][2] = {{"conv_rows<f32,3x3,per_example>", "conv_rows<f32,3x3,s2,per_example>"},
-                                            {"conv_rows<f32,5x5,per_example>", "conv_rows<f32,5x5,s2,per_example>"}};
-    return names[g.kh / 2 - 1][g.stride - 1];
+    // (kernel size, stride, blocks of output and of input channels: the kernels that share a launch)
+#define DP_ROWS_NAMES(KS) {{{"conv_rows<f32," KS ",16x16,per_example>", "conv_rows<f32," KS ",16x32,per_example>"}, \
+                            {"conv_rows<f32," KS ",32x16,per_example>", "conv_rows<f32," KS ",32x32,per_example>"}}, \
+                           {{"conv_rows<f32," KS ",s2,16x16,per_example>", "conv_rows<f32," KS ",s2,16x32,per_example>"}, \
+                            {"conv_rows<f32," KS ",s2,32x16,per_example>", "conv_rows<f32," KS ",s2,32x32,per_example>"}}}
+    static const char *const names[2][2][2][2] = {DP_ROWS_NAMES("3x3"), DP_ROWS_NAMES("5x5")};
+#undef DP_ROWS_NAMES
+    return names[g.kh / 2 - 1][g.stride - 1][rows_nm(g) - 1][rows_nn(g) - 1];
 }
 
 dp_status launch_conv_rows(const Geo &g, const void *x, const void *dy, float *out_w, float *out_b, size_t out_stride, float *sqnorm,
@@ -422,14 +574,18 @@ dp_status launch_conv_rows(const Geo &g, const void *x, const void *dy, float *o
     a.partials = static_cast<float *>(ws);
     a.n = g.n; a.cin = g.cin; a.cout = g.cout; a.h = g.h; a.w = g.w; a.oh = g.oh; a.ow = g.ow;
     a.tiles_m = p.tiles_m; a.tiles_n = p.tiles_n; a.ex_per_wg = p.ex_per_wg; a.unit = g.unit; a.q = p.q;
-    a.rows = p.rows; a.chunks = p.chunks; a.rpr = p.rpr; a.xp = p.xp; a.cha = p.cha; a.chx = p.chx; a.tm = p.tm; a.tn = p.tn;
+    a.rows = p.rows; a.chunks = p.chunks; a.rpr = p.rpr; a.xp = p.xp; a.cha = p.cha; a.chx = p.chx; a.bufs = p.bufs; a.waves_a = p.waves_a;
     a.bias = g.has_bias ? 1 : 0;
-    const void *fn = g.kh == 3 ? rows_fn<3>(g.stride) : rows_fn<5>(g.stride);
-    static std::atomic<bool> attr_done[2][2];           // zero-initialised; setting the attribute twice is harmless
-    if (!attr_done[g.kh / 2 - 1][g.stride - 1].load()) {
+    a.narrow = g.w < 4 || g.ow < 4;
+    a.ragged = !a.narrow && (g.w % 4 || g.ow % 4);
+    const void *fn = g.kh == 3 ? (g.stride == 2 ? rows_fn<3, 2>(p.nm, p.nn) : rows_fn<3, 1>(p.nm, p.nn))
+                               : (g.stride == 2 ? rows_fn<5, 2>(p.nm, p.nn) : rows_fn<5, 1>(p.nm, p.nn));
+    static std::atomic<bool> attr_done[2][2][2][2];     // zero-initialised; setting the attribute twice is harmless
+    std::atomic<bool> &done = attr_done[g.kh / 2 - 1][g.stride - 1][p.nm - 1][p.nn - 1];
+    if (!done.load()) {
         if (hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, 156 * 1024) != hipSuccess)
             return fail(DP_ERR_DEVICE, "conv_rows: cannot reserve LDS");
-        attr_done[g.kh / 2 - 1][g.stride - 1].store(true);
+        done.store(true);
     }
     const long long total = (long long)((g.n + p.ex_per_wg - 1) / p.ex_per_wg) * p.tiles_m * p.tiles_n;
     const dp_status st = submit_main<RowsArgs>(fn, a, (unsigned)((total + 7) / 8 * 8), (unsigned)(64 * g.kh * p.q), p.lds, s, "conv_rows");

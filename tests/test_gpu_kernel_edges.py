@@ -272,6 +272,38 @@ def test_conv_f32_raw_rows_kernel_keeps_what_is_not_finite_in_its_place():
     assert np.array_equal(np.isinf(gw[0, 0]), want) and np.isfinite(gw[:, 1]).all() and np.isfinite(gw[:, 0, :, 0]).all()
 
 
+# The products of the raw-row kernel run on parts of the numbers.  What they leave out is below 2^-23 of a product, and sums of 32 products are
+# rounded into one fp32 sum of K / 32 (and 2 to 12 shares of it) terms: sqrt(K / 32) * 2^-24 at most, taken twice
+@pytest.mark.parametrize("cin,cout,h,w,k,stride,n", [(64, 64, 56, 56, 3, 1, 100), (16, 16, 32, 32, 3, 1, 300), (17, 33, 30, 29, 3, 1, 300),
+                                                     (40, 72, 45, 37, 5, 2, 40), (64, 32, 33, 34, 3, 2, 300), (20, 40, 28, 27, 5, 1, 100), (18, 20, 40, 3, 3, 1, 300)])
+def test_conv_f32_raw_rows_kernel_is_as_exact_as_fp32(cin, cout, h, w, k, stride, n):
+    layer = Layer("conv", cin, cout, h, w, k, k, stride, (k - 1) // 2, cout % 2 == 0)
+    x, dy = (np.concatenate([v] * (n // 2)) for v in _inputs(layer, 2, 139, "f32"))
+    assert dp.dp_kernel_variant(dp.make_desc(layer, n, "f32"), dp.DP_WS_PER_EXAMPLE_GRAD).startswith("conv_rows<f32")
+    gw, gb, sq = _run_per_example(layer, x, dy, "f32")
+    ref_w, ref_b, ref_n2 = _oracle_grads(layer, x[:2], dy[:2])
+    bound = 2.0 * (2.0 ** -23 + np.sqrt(layer.oh * layer.ow / 32) * 2.0 ** -24)
+    assert np.linalg.norm(gw[:2] - ref_w) < bound * np.linalg.norm(ref_w)
+    assert not layer.pb or np.linalg.norm(gb[:2] - ref_b) < bound * np.linalg.norm(ref_b)
+    assert np.allclose(sq[:2], ref_n2, rtol=2 * bound)
+
+
+def test_conv_f32_raw_rows_kernel_takes_every_fp32_number():
+    """Numbers that round to infinity as bf16 stay finite, NaNs stay where they are, and the next example is what it was."""
+    layer = Layer("conv", 32, 16, 6, 8, 3, 3, 1, 1, False)
+    x, dy = _inputs(layer, 400, 149, "f32")
+    assert dp.dp_kernel_variant(dp.make_desc(layer, 400, "f32"), dp.DP_WS_PER_EXAMPLE_GRAD).startswith("conv_rows<f32")
+    dy[:2] = 2.0 ** -20
+    x[0, 3, 2, 4], x[1, 5, 0, 0] = np.finfo(np.float32).max, np.nan
+    gw = _run_per_example(layer, x, dy, "f32")[0].reshape(400, 16, 32, 3, 3)
+    ref = _oracle_grads(layer, x[[0, 2]], dy[[0, 2]])[0].reshape(2, 16, 32, 3, 3)
+    assert_close(gw[0], ref[0], F32_TOL, "large numbers")
+    assert_close(gw[2], ref[1], F32_TOL, "next example")
+    want = np.zeros((3, 3), bool)                 # a corner: read by the taps at and left of and above the middle
+    want[:2, :2] = True
+    assert np.array_equal(np.isnan(gw[1, 0, 5]), want) and np.isfinite(np.delete(gw[1], 5, axis=1)).all()
+
+
 # ---- clipping units in the kernels of the per-example calls: one unit (sliced into ranges of its examples), units no power of two,
 # rows that end in a part chunk, enough units for the wide tile; every layer alone and all of one unit size in a batch call
 _UNIT_ROUTES = [

@@ -94,14 +94,14 @@ def test_descriptor_counts_match_the_layer_set(wl):
 # Both fp32 kernels measured on each of these (us per call, general / raw rows): the faster one has to be chosen where they differ by
 # 15 %.
 @pytest.mark.parametrize("cin,cout,hw,k,stride,n,bias,general,rows", [
-    (128, 128, (28, 28), 3, 1, 256, False, 654, 919), (128, 128, (28, 28), 3, 1, 256, True, 726, 935), (112, 112, (28, 28), 3, 1, 297, False, 748, 1080),
-    (64, 64, (8, 8), 3, 1, 96, False, 19, 25), (64, 128, (32, 32), 3, 2, 141, False, 91, 156), (5, 40, (53, 37), 5, 1, 318, False, 203, 501),
-    (72, 124, (54, 47), 5, 1, 218, False, 3004, 4093), (72, 124, (54, 47), 5, 1, 218, True, 3177, 4094),
-    (16, 16, (32, 32), 3, 1, 256, False, 103, 33), (16, 16, (32, 32), 3, 1, 256, True, 182, 35), (32, 32, (16, 16), 3, 1, 256, False, 51, 31),
-    (64, 64, (56, 56), 3, 1, 64, False, 283, 195), (64, 64, (56, 56), 3, 1, 64, True, 374, 199), (64, 64, (56, 56), 3, 1, 128, True, 617, 386),
-    (64, 64, (56, 56), 3, 1, 68, True, 455, 386), (64, 64, (64, 64), 3, 1, 96, False, 522, 429),
-    (64, 64, (56, 56), 3, 1, 256, True, 1091, 803), (64, 64, (28, 28), 3, 1, 64, True, 106, 68), (64, 64, (64, 64), 3, 1, 256, True, 1441, 917),
-    (85, 11, (37, 33), 3, 1, 46, False, 132, 63), (146, 14, (34, 29), 3, 1, 19, False, 88, 49), (80, 48, (56, 56), 5, 2, 245, True, 1076, 800)])
+    (128, 128, (28, 28), 3, 1, 256, False, 705, 580), (128, 128, (28, 28), 3, 1, 256, True, 722, 550), (112, 112, (28, 28), 3, 1, 297, False, 729, 576),
+    (64, 64, (8, 8), 3, 1, 96, False, 15, 21), (64, 128, (32, 32), 3, 2, 141, False, 93, 151), (5, 40, (53, 37), 5, 1, 318, False, 201, 255),
+    (72, 124, (54, 47), 5, 1, 218, False, 2986, 2234), (72, 124, (54, 47), 5, 1, 218, True, 3160, 2237),
+    (16, 16, (32, 32), 3, 1, 256, False, 97, 20), (16, 16, (32, 32), 3, 1, 256, True, 182, 21), (32, 32, (16, 16), 3, 1, 256, False, 47, 22),
+    (64, 64, (56, 56), 3, 1, 64, False, 283, 98), (64, 64, (56, 56), 3, 1, 64, True, 385, 100), (64, 64, (56, 56), 3, 1, 128, True, 617, 196),
+    (64, 64, (56, 56), 3, 1, 68, True, 455, 185), (64, 64, (64, 64), 3, 1, 96, False, 522, 239),
+    (64, 64, (56, 56), 3, 1, 256, True, 1091, 433), (64, 64, (28, 28), 3, 1, 64, True, 106, 37), (64, 64, (64, 64), 3, 1, 256, True, 1441, 525),
+    (85, 11, (37, 33), 3, 1, 46, False, 132, 36), (146, 14, (34, 29), 3, 1, 19, False, 88, 33), (80, 48, (56, 56), 5, 2, 245, True, 1076, 700)])
 def test_fp32_convolutions_take_the_kernel_that_measured_faster(cin, cout, hw, k, stride, n, bias, general, rows):
     from workloads import Layer
     dp.load_library()
