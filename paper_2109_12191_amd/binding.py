@@ -12,6 +12,7 @@ DP_NCHW, DP_NHWC = 0, 1
 DP_WS_PER_EXAMPLE_GRAD, DP_WS_RECOMPUTE = 0, 1
 DP_VARIANT_SHARED = 2
 DP_VARIANT_MATERIALISE = 4
+DP_RECOMPUTE_BLOCKS = 8
 
 _STATUS_NAMES = {1: "DP_ERR_INVALID_ARG", 2: "DP_ERR_UNSUPPORTED", 3: "DP_ERR_WORKSPACE", 4: "DP_ERR_DEVICE"}
 _KINDS = {"dense": DP_DENSE, "conv": DP_CONV2D, "gn": DP_GN_AFFINE}
@@ -72,6 +73,7 @@ def load_library():
         "dp_example_addresses": (it, [vp, vp, it, it, it, vp, vp]),
         "dp_per_example_grad_batch_at": (it, [vp, vp, vp, vp, vp, sz, vp, vp, vp, vp, it, vp]),
         "dp_clip_accumulate_recompute_batch_at": (it, [vp, vp, vp, vp, vp, vp, vp, vp, vp, it, vp]),
+        "dp_clip_accumulate_recompute_blocks_batch_at": (it, [vp, vp, vp, vp, vp, vp, vp, vp, vp, it, vp]),
         "dp_unit_grad_batch_at": (it, [vp, it, vp, vp, vp, vp, sz, vp, vp, vp, it, vp]),
         "dp_clip_accumulate_columns": (it, [vp, sz, vp, it, vp, vp, vp, vp, it, it, it, sz, vp, vp]),
         "dp_clip_factors": (it, [vp, fl, it, vp, vp]),
@@ -100,7 +102,7 @@ EXPORTED = ("dp_group_clip_bounds", "dp_weight_count", "dp_bias_count", "dp_work
             "dp_unit_workspace_bytes", "dp_unit_grad", "dp_unit_grad_batch",
             "dp_norm_partial_count", "dp_per_example_grad_partials", "dp_norms_from_partials",
             "dp_per_example_grad_batch", "dp_layer_norms_from_partials", "dp_clip_accumulate_recompute_batch",
-            "dp_example_addresses", "dp_per_example_grad_batch_at", "dp_clip_accumulate_recompute_batch_at", "dp_unit_grad_batch_at",
+            "dp_example_addresses", "dp_per_example_grad_batch_at", "dp_clip_accumulate_recompute_batch_at", "dp_clip_accumulate_recompute_blocks_batch_at", "dp_unit_grad_batch_at",
             "dp_clip_accumulate_columns",
             "dp_clip_factors", "dp_clip_accumulate", "dp_clip_accumulate_segments", "dp_clip_accumulate_recompute", "dp_add_noise_finalize", "dp_add_noise_finalize_update", "dp_add_example_noise",
             "dp_add_noise_finalize_flat", "dp_philox_raw", "dp_profile_next_contraction", "dp_last_error", "dp_version")
@@ -227,9 +229,11 @@ def dp_unit_grad(desc: LayerDesc, clip_unit: int, x, dy, g_w, g_b, sqnorm, ws, g
 
 class LayerBatch:
     """Host arrays for the batch calls over a fixed set of layers: descriptors, workspaces, and (re)settable
-    pointer arrays.  Pointers are plain integers (device addresses); None becomes NULL."""
+    pointer arrays.  Pointers are plain integers (device addresses); None becomes NULL.  scale_blocks: the recomputing clipped sum (of
+    example addresses) scales finished blocks."""
 
-    def __init__(self, descs, ws_ptrs, ws_bytes):
+    def __init__(self, descs, ws_ptrs, ws_bytes, scale_blocks: bool = False):
+        self.scale_blocks = scale_blocks
         k = len(descs)
         self.n_layers = k
         self.descs = (LayerDesc * k)(*descs)
@@ -288,7 +292,10 @@ def dp_layer_norms_from_partials(partials, counts, sqnorm, n_layers: int, n: int
 
 def dp_clip_accumulate_recompute_batch(batch: "LayerBatch", x, dy, sqnorm, clip_c, acc_w, acc_b, stream=None, addresses: bool = False):
     lib = load_library()
-    _check((lib.dp_clip_accumulate_recompute_batch_at if addresses else lib.dp_clip_accumulate_recompute_batch)(
+    if batch.scale_blocks and not addresses:
+        raise ValueError("the clipped sum that scales finished blocks takes example addresses")
+    _check((lib.dp_clip_accumulate_recompute_blocks_batch_at if batch.scale_blocks else
+            lib.dp_clip_accumulate_recompute_batch_at if addresses else lib.dp_clip_accumulate_recompute_batch)(
         batch.descs, x, dy, sqnorm, clip_c, acc_w, acc_b, batch.ws, batch.ws_bytes, batch.n_layers, _stream(stream)))
 
 

@@ -175,6 +175,14 @@ static size_t ws_kernels_for(const Geo &g, int mode)
     return align16_api(b);
 }
 
+// The clip-weighted form that rounds nothing: whether the layer has it; marks the geometry for it.  (Dense kernels scale fp32 values or
+// finished blocks, GroupNorm's are fp32 throughout.)
+static bool scales_blocks(Geo &g)
+{
+    g.scale_blocks = 1;
+    return g.kind != DP_CONV2D || conv_scales_blocks(g);
+}
+
 static size_t ws_bytes_for(const Geo &g, int mode) { return ws_kernels_for(g, mode) + layout_copy_bytes(g); }
 
 // x, dy as the kernels read them: the caller's tensors, or their channels-first copies behind the first
@@ -280,6 +288,13 @@ size_t dp_workspace_bytes(const dp_layer_desc *desc, int use)
 {
     Geo g;
     if (make_geo(desc, g) != DP_OK) return 0;
+    if (use == (DP_WS_RECOMPUTE | DP_RECOMPUTE_BLOCKS)) {
+        if (!scales_blocks(g)) {
+            fail(DP_ERR_UNSUPPORTED, "no kernel scales this layer's finished blocks");
+            return 0;
+        }
+        use = DP_WS_RECOMPUTE;
+    }
     if (use != DP_WS_PER_EXAMPLE_GRAD && use != DP_WS_RECOMPUTE) {
         fail(DP_ERR_INVALID_ARG, "unknown workspace use %d", use);
         return 0;
@@ -292,7 +307,8 @@ const char *dp_kernel_variant(const dp_layer_desc *desc, int use)
     Geo g;
     if (make_geo(desc, g) != DP_OK) return "";
     const bool shared = (use & DP_VARIANT_SHARED) != 0, stored = (use & DP_VARIANT_MATERIALISE) != 0;
-    use &= ~(DP_VARIANT_SHARED | DP_VARIANT_MATERIALISE);
+    if ((use & DP_RECOMPUTE_BLOCKS) && (!(use & DP_WS_RECOMPUTE) || !scales_blocks(g))) return "";
+    use &= ~(DP_VARIANT_SHARED | DP_VARIANT_MATERIALISE | DP_RECOMPUTE_BLOCKS);
     const int mode = use == DP_WS_RECOMPUTE ? MODE_WEIGHTED : (stored ? MODE_MATERIALISE : MODE_NORM);
     if (g.kind == DP_CONV2D) return conv_variant_name(g, mode, shared);
     if (g.kind == DP_DENSE) return g.bf16 ? "dense<bf16>" : "dense<f32>";
@@ -637,7 +653,7 @@ dp_status dp_layer_norms_from_partials(const float *const *partials, const int32
     return launch_layer_norms(partials, counts, sqnorm, n_layers, n, static_cast<hipStream_t>(stream));
 }
 
-static dp_status recompute_batch(bool addresses, const dp_layer_desc *descs, const void *const *x, const void *const *dy,
+static dp_status recompute_batch(bool addresses, bool f32, const dp_layer_desc *descs, const void *const *x, const void *const *dy,
                                  const float *const *sqnorm, const float *clip_c, float *const *acc_w, float *const *acc_b,
                                  void *const *ws, const size_t *ws_bytes, int n_layers, dp_stream stream)
 {
@@ -648,6 +664,7 @@ static dp_status recompute_batch(bool addresses, const dp_layer_desc *descs, con
     for (int l = 0; l < n_layers; ++l) {
         Geo &g = geo[(size_t)l];
         DP_TRY(make_geo(&descs[l], g));
+        if (f32 && !scales_blocks(g)) return fail(DP_ERR_UNSUPPORTED, "layer %d: no kernel scales its finished blocks", l);
         if (addresses) DP_TRY(read_addresses(g));
         DP_TRY(check_ptr(x[l], "x[l]", true, addresses ? 8 : 16));       // (arrays of addresses are read word by word)
         DP_TRY(check_ptr(dy[l], "dy[l]", true, addresses ? 8 : 16));
@@ -682,7 +699,7 @@ dp_status dp_clip_accumulate_recompute_batch(const dp_layer_desc *descs, const v
                                              float *const *acc_b, void *const *ws, const size_t *ws_bytes, int n_layers,
                                              dp_stream stream)
 {
-    return recompute_batch(false, descs, x, dy, sqnorm, clip_c, acc_w, acc_b, ws, ws_bytes, n_layers, stream);
+    return recompute_batch(false, false, descs, x, dy, sqnorm, clip_c, acc_w, acc_b, ws, ws_bytes, n_layers, stream);
 }
 
 dp_status dp_clip_accumulate_recompute_batch_at(const dp_layer_desc *descs, const uint64_t *const *x, const uint64_t *const *dy,
@@ -690,7 +707,16 @@ dp_status dp_clip_accumulate_recompute_batch_at(const dp_layer_desc *descs, cons
                                                 float *const *acc_b, void *const *ws, const size_t *ws_bytes, int n_layers,
                                                 dp_stream stream)
 {
-    return recompute_batch(true, descs, reinterpret_cast<const void *const *>(x), reinterpret_cast<const void *const *>(dy), sqnorm, clip_c,
+    return recompute_batch(true, false, descs, reinterpret_cast<const void *const *>(x), reinterpret_cast<const void *const *>(dy), sqnorm, clip_c,
+                           acc_w, acc_b, ws, ws_bytes, n_layers, stream);
+}
+
+dp_status dp_clip_accumulate_recompute_blocks_batch_at(const dp_layer_desc *descs, const uint64_t *const *x, const uint64_t *const *dy,
+                                                    const float *const *sqnorm, const float *clip_c, float *const *acc_w,
+                                                    float *const *acc_b, void *const *ws, const size_t *ws_bytes, int n_layers,
+                                                    dp_stream stream)
+{
+    return recompute_batch(true, true, descs, reinterpret_cast<const void *const *>(x), reinterpret_cast<const void *const *>(dy), sqnorm, clip_c,
                            acc_w, acc_b, ws, ws_bytes, n_layers, stream);
 }
 

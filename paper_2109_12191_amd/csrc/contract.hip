@@ -1682,12 +1682,25 @@ double conv_general_f32_us(const Geo &g)
     return 11.4 + chunks / 256.0 * (g.has_bias ? 2.84 : 2.69) + units / 256.0 * 1.05 + walk * (g.has_bias ? 4.2 : 2.56);
 }
 
+// the geometry of packed operands: rows of kg values, ranges of examples (or examples) as examples
+static void packed_geometry(const Geo &g, const PackPlan &pp, Geo &g2)
+{
+    g2 = g;
+    g2.n = pp.groups;
+    g2.cin = pp.J;
+    g2.h = 1; g2.w = pp.kg; g2.oh = 1; g2.ow = pp.kg;
+    g2.kh = 1; g2.kw = 1; g2.stride = 1; g2.pad = 0;
+    g2.x_elems = (size_t)pp.J * pp.kg;
+    g2.dy_elems = (size_t)g.cout * pp.kg;
+    g2.x_tab = g2.dy_tab = 0;
+}
+
 // Clip-weighted contraction of a bf16 layer whose packed operands are small: rewrite the
 // operands first (pack.hip) and run the aligned one-long-row variant on `g2`, the geometry of
 // the packed tensors (example ranges as its "examples", im2col rows as its input channels).
 static bool packed_weighted(const Geo &g, int mode, PackPlan &pp, Geo &g2)
 {
-    if (mode != MODE_WEIGHTED || !g.bf16) return false;
+    if (mode != MODE_WEIGHTED || !g.bf16 || g.scale_blocks) return false;
     // a 1x1 stride-1 layer with even S is already K-contiguous and dword aligned: the aligned loader reads it
     // in place and scales dY while staging, which beats packing it first (measured)
     if (g.kh == 1 && g.kw == 1 && g.stride == 1 && g.pad == 0 && (g.oh * g.ow) % 2 == 0) return false;
@@ -1706,15 +1719,30 @@ static bool packed_weighted(const Geo &g, int mode, PackPlan &pp, Geo &g2)
     pp = pack_plan(g, (int)groups);
     if (pp.x_bytes + pp.dy_bytes > ((size_t)64 << 20)) return false;
     if ((long long)J * pp.kg >= (1ll << 31) || (long long)g.cout * pp.kg >= (1ll << 31)) return false;
-    g2 = g;
-    g2.n = pp.groups;
-    g2.cin = (int)J;
-    g2.h = 1; g2.w = pp.kg; g2.oh = 1; g2.ow = pp.kg;
-    g2.kh = 1; g2.kw = 1; g2.stride = 1; g2.pad = 0;
-    g2.x_elems = (size_t)J * pp.kg;
-    g2.dy_elems = (size_t)g.cout * pp.kg;
-    g2.x_tab = g2.dy_tab = 0;
+    packed_geometry(g, pp, g2);
     return true;
+}
+
+// The clip-weighted contraction whose factors meet the finished fp32 block of an example (Geo::scale_blocks) on small maps: the operands
+// are rewritten as they are, a chunk of 64 K values per example and row, and the LDS-direct kernel runs on `g2` with the examples
+// as examples.  It is the slower of the two packed forms where both may be used (a third of the K values are padding on 7 x 7 maps, and
+// every chunk ends with multiply-adds of whole blocks: ResNet-50 step of 8 x 32 examples 7427 -> 7803 us), but it rounds nothing, so
+// that it can stand in for stored gradients.
+static bool packed_blocks(const Geo &g, int mode, PackPlan &pp, Geo &g2)
+{
+    if (mode != MODE_WEIGHTED || !g.scale_blocks || !g.bf16 || g.has_bias || flat_direct(g) || g.oh * g.ow > 64) return false;
+    pp = pack_plan(g, g.n, 64);
+    if (pp.x_bytes + pp.dy_bytes > ((size_t)64 << 20)) return false;
+    packed_geometry(g, pp, g2);
+    return true;
+}
+
+// Whether a clip-weighted call of this layer scales finished fp32 blocks, nothing that is rounded to 16 bits again.
+bool conv_scales_blocks(const Geo &g)
+{
+    PackPlan pp;
+    Geo g2;
+    return !g.bf16 || flat_direct(g) || packed_blocks(g, MODE_WEIGHTED, pp, g2);
 }
 
 // Per-example calls of strided 1x1 bf16 convolutions (projection shortcuts): contract on a compact
@@ -1775,7 +1803,7 @@ static size_t conv_ws_bytes_mode(const Geo &g, int mode)
     if (conv3x3_applicable(g, mode)) return conv3x3_ws_bytes(g, mode);
     PackPlan pp;
     Geo g2;
-    if (packed_weighted(g, mode, pp, g2)) {
+    if (packed_weighted(g, mode, pp, g2) || packed_blocks(g, mode, pp, g2)) {
         const FullPlan f = full_plan(g2, mode);
         return align16(pp.x_bytes) + align16(pp.dy_bytes) + (f.ksplit > 1 ? f.part_floats * sizeof(float) : 0);
     }
@@ -1838,7 +1866,7 @@ const char *conv_variant_name(const Geo &g, int mode, bool shared)
     // the geometry the contraction kernel really sees (packed or subsampled operands are one long aligned row)
     Geo ge = g, g2;
     PackPlan pp;
-    if (packed_weighted(g, mode, pp, g2)) ge = g2;
+    if (packed_weighted(g, mode, pp, g2) || packed_blocks(g, mode, pp, g2)) ge = g2;
     else if (subsampled(g, mode, g2)) ge = g2;
     const FullPlan f = full_plan(ge, mode);
     return names.v[g.bf16 ? 1 : 0][f.shape][mode == MODE_WEIGHTED ? 1 : 0][g.has_bias ? 1 : 0][loader_of(ge)];
@@ -1895,14 +1923,16 @@ dp_status launch_conv(const Geo &g, int mode, const void *x, const void *dy, flo
         return launch_conv3x3(g, mode, x, dy, out_w, out_stride, sqnorm, group_sqnorm, clip_c, ws, s);
     PackPlan pp;
     Geo g2;
-    if (packed_weighted(g, mode, pp, g2)) {
+    const bool f32 = packed_blocks(g, mode, pp, g2);
+    if (f32 || packed_weighted(g, mode, pp, g2)) {
         char *w = static_cast<char *>(ws);
         void *xp = w;
         w += align16(pp.x_bytes);
         void *dyp = w;
         w += align16(pp.dy_bytes);
-        const dp_status st = launch_pack_weighted(g, pp, x, dy, group_sqnorm, clip_c, xp, dyp, s);
+        const dp_status st = launch_pack_weighted(g, pp, x, dy, f32 ? nullptr : group_sqnorm, clip_c, xp, dyp, s);
         if (st != DP_OK) return st;
+        if (f32) return launch_conv_impl(g2, mode, xp, dyp, out_w, out_b, out_stride, nullptr, group_sqnorm, clip_c, w, s);
         // the factors are already in dYp: no norms, and the kernel's own factor is 1 (what it would read are examples' norms, not
         // those of its example ranges)
         return launch_conv_impl(g2, mode, xp, dyp, out_w, out_b, out_stride, nullptr, nullptr, __builtin_inff(), w, s);

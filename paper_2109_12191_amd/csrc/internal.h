@@ -35,6 +35,8 @@ struct Geo {
     // Per-example calls of convolutions: consecutive examples whose gradients are added up to one row of results (clipping units; K
     // then runs over the positions of all of them).  1 otherwise; n is a multiple of it.
     int unit;
+    // Clip-weighted calls of bf16 layers: the factors meet finished fp32 blocks (conv_scales_blocks), never an operand that is rounded again.
+    int scale_blocks;
 };
 
 // Contraction modes of the conv / dense kernels.
@@ -49,6 +51,7 @@ dp_status launch_conv(const Geo &g, int mode, const void *x, const void *dy, flo
 
 // 3x3 stride-1 pad-1 bf16 convolutions staged from raw image rows (conv3x3.hip); launch_conv,
 // conv_ws_bytes and conv_variant_name route to these when conv3x3_applicable() says so.
+bool conv_scales_blocks(const Geo &g);
 bool conv3x3_applicable(const Geo &g, int mode);
 size_t conv3x3_ws_bytes(const Geo &g, int mode);
 const char *conv3x3_variant_name(const Geo &g, int mode);
@@ -70,7 +73,7 @@ struct PackPlan {
     int S, SP, J, groups, eg, kg;
     size_t x_bytes, dy_bytes;
 };
-PackPlan pack_plan(const Geo &g, int groups);
+PackPlan pack_plan(const Geo &g, int groups, int row = 0);        // row: values of an example in a packed row (0: S rounded up to 8)
 dp_status launch_pack_weighted(const Geo &g, const PackPlan &p, const void *x, const void *dy,
                                const float *group_sqnorm, float clip_c, void *xp, void *dyp, hipStream_t s);
 

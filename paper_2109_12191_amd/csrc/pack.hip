@@ -9,6 +9,7 @@
 // size or parity of S.  The clip factor is applied here, in fp32, and rounded to bf16 once
 // (nearest even) -- the same arithmetic the in-kernel scaling performs.
 // `grp` splits the examples into ranges that different workgroups contract (the K slices).
+// Without norms the operands are copied as they are (rows of 64 per example: the contraction scales each example's finished block).
 #include "group.h"
 #include "internal.h"
 #include "pieces.h"
@@ -21,7 +22,7 @@ struct PackArgs {
     const void *x, *dy;
     int x_tab, dy_tab;              // Geo::x_tab / dy_tab: the operand pointers are arrays of example addresses
     uint16_t *xp, *dyp;
-    const float *group_sqnorm;
+    const float *group_sqnorm;      // null: dY is not scaled
     float clip_c;
     int n, cin, cout, h, w, kh, kw, stride, pad, oh, ow;
     int S, SP, J;
@@ -43,7 +44,7 @@ __global__ void __launch_bounds__(256) pack_weighted_kernel(const Grouped<PackAr
         const int kk = kk8 * 8;
         const int e = kk / a.SP, k0 = kk - e * a.SP;
         const int i = grp * a.eg + e;
-        if (i < a.n) {
+        if (i < a.n && k0 < a.S) {
             const int taps = a.kh * a.kw;
             const int ci = j / taps, t = j - ci * taps;
             const int kh = t / a.kw, kw = t - kh * a.kw;
@@ -92,7 +93,7 @@ __global__ void __launch_bounds__(256) pack_weighted_kernel(const Grouped<PackAr
     const int e = kk / a.SP, k0 = kk - e * a.SP;
     const int i = grp * a.eg + e;
     if (i < a.n) {
-        const float f = clip_factor(a.group_sqnorm[i], a.clip_c);
+        const float f = a.group_sqnorm ? clip_factor(a.group_sqnorm[i], a.clip_c) : 1.0f;     // (times 1: the same bits)
         const size_t ex_elems = (size_t)a.cout * a.S;
         const uint16_t *ex = example_at<uint16_t>(a.dy, a.dy_tab, i, ex_elems);
         const uint16_t *src = ex + (size_t)co * a.S;
@@ -222,11 +223,11 @@ dp_status launch_subsample(const Geo &g, const void *x, void *out, hipStream_t s
                                   s, "subsample");
 }
 
-PackPlan pack_plan(const Geo &g, int groups)
+PackPlan pack_plan(const Geo &g, int groups, int row)
 {
     PackPlan p;
     p.S = g.oh * g.ow;
-    p.SP = (p.S + 7) / 8 * 8;
+    p.SP = row ? row : (p.S + 7) / 8 * 8;
     p.J = g.cin * g.kh * g.kw;
     p.groups = groups;
     p.eg = (g.n + groups - 1) / groups;

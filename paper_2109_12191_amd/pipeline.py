@@ -85,26 +85,39 @@ class _Plan:
         self.n = wl.n * tensors
         self.rows = self.n // ps.clip_unit
         self.layers = ps.layers
-        # the forms of a micro-step of its own: the recomputing form rounds scaled bf16 operands once more, and how many
-        # micro-steps share a phase must not decide about precision
-        self.form = ps.form
+        self.form = ps._forms(tensors)
+        self.recompute_use = ps._recompute_use(tensors)
         L = len(self.layers)
         self.descs, need = ps._workspaces(tensors)
         self.g = [st.g[: self.rows] if st.g is not None else None for st in stores]
+        self.off_w, self.off_b, self.p_mat = ps.off_w, ps.off_b, ps.p_mat
+        free = [None] * len(stores)
+        if self.form is not ps.form:
+            # only some of the layers that the matrix has columns for are stored: their columns move together, and what is left of
+            # the matrix holds the workspaces of the others
+            self.off_w, self.off_b, self.p_mat = ps._columns(self.form)
+            free = [g.data_ptr() + 4 * self.rows * self.p_mat for g in self.g]
+            self.g = [g.view(-1)[: self.rows * self.p_mat].view(self.rows, self.p_mat) for g in self.g]
         self.group_sqnorm = [st.group_sqnorm[: ps.n_groups * self.rows].view(ps.n_groups, self.rows) for st in stores]
         self.layer_sqnorm = [st.layer_sqnorm[: L * self.rows].view(L, self.rows) for st in stores] if ps.clip_unit > 1 else None
+        self.segments = ps._segments(self.form, self.off_w) if self.p_mat else None
         # a workspace per layer (the layers of a phase are in flight together)
-        starts, total = [], 0
-        for b in need:
-            starts.append(total)
-            total += _align256(b)
         self.ws_bytes = need
-        self.ws = [[st.ws.data_ptr() + at for at in starts] for st in stores]
+        self.ws = []
+        for st, spare in zip(stores, free):
+            at, spare, where = st.ws.data_ptr(), spare and _align256(spare), []
+            for b, inside in zip(need, ps._in_matrix(tensors)):
+                where.append(spare if inside else at)
+                if inside:
+                    spare += _align256(b)
+                else:
+                    at += _align256(b)
+            self.ws.append(where)
         # Layers that run the same kernel variant go to the library in ONE batch call, which puts them into one
         # launch (at most 16 per launch): per phase a micro-step is a dozen launches, not a hundred.
         self.variant = [(B.dp_kernel_variant(d, B.DP_WS_PER_EXAMPLE_GRAD | B.DP_VARIANT_SHARED |
                                              (B.DP_VARIANT_MATERIALISE if form == "materialise" else 0)),
-                         B.dp_kernel_variant(d, B.DP_WS_RECOMPUTE | B.DP_VARIANT_SHARED) if form == "recompute" else "")
+                         B.dp_kernel_variant(d, self.recompute_use | B.DP_VARIANT_SHARED) if form == "recompute" else "")
                         for d, form in zip(self.descs, self.form)]
         self.partials = [B.PartialTable(self.ws[c], [1] * L, ps.group_of_layer)
                          for c in range(len(stores))]
@@ -136,11 +149,12 @@ class _Plan:
                 part = ids[k: k + width]
                 name = key.split("|")[0]
                 if len(part) == 1:           # a single layer is planned as a launch of its own
-                    name = B.dp_kernel_variant(self.descs[part[0]], B.DP_WS_RECOMPUTE if use == 1 else (
+                    name = B.dp_kernel_variant(self.descs[part[0]], self.recompute_use if use == 1 else (
                         B.DP_WS_PER_EXAMPLE_GRAD | (B.DP_VARIANT_MATERIALISE if self.form[part[0]] == "materialise" else 0)))
                 g = dict(layers=part, name=name, conv=all(self.layers[i].kind == "conv" for i in part))
                 g["batch"] = [B.LayerBatch([self.descs[i] for i in part], [self.ws[c][i] for i in part],
-                                           [self.ws_bytes[i] for i in part]) for c in range(len(self.stores))]
+                                           [self.ws_bytes[i] for i in part], bool(self.recompute_use & B.DP_RECOMPUTE_BLOCKS))
+                              for c in range(len(self.stores))]
                 if use == 2:
                     g["usq"] = [g["batch"][c].ptrs([self.layer_sqnorm[c][i].data_ptr() for i in part])
                                 for c in range(len(self.stores))]
@@ -148,9 +162,9 @@ class _Plan:
                     g["counted"] = False
                     mat = [self.form[i] == "materialise" for i in part]
                     g0 = [g.data_ptr() if g is not None else 0 for g in self.g]
-                    g["gw"] = [g["batch"][c].ptrs([g0[c] + 4 * ps.off_w[i] if m else None
+                    g["gw"] = [g["batch"][c].ptrs([g0[c] + 4 * self.off_w[i] if m else None
                                                    for i, m in zip(part, mat)]) if any(mat) else None for c in range(len(self.stores))]
-                    g["gb"] = [g["batch"][c].ptrs([g0[c] + 4 * ps.off_b[i] if (m and ps.pb[i]) else None
+                    g["gb"] = [g["batch"][c].ptrs([g0[c] + 4 * self.off_b[i] if (m and ps.pb[i]) else None
                                                    for i, m in zip(part, mat)]) if any(mat) else None for c in range(len(self.stores))]
                 else:
                     acc0 = ps.acc.data_ptr()
@@ -258,10 +272,6 @@ class PrivatiseStep:
             pos += _pad4(self.pb[i])
             if self.form[i] == "materialise":
                 self.p_mat = pos
-        # runs of columns of the gradient matrix that belong to one clipping group
-        runs = [i for k, i in enumerate(mat) if k == 0 or self.group_of_layer[i] != self.group_of_layer[mat[k - 1]]]
-        self._segments = B.SegmentTable([self.off_w[i] for i in runs], [self.group_of_layer[i] for i in runs],
-                                        [self.group_clip[self.group_of_layer[i]] for i in runs]) if runs else None
         self.p_total = max(pos, 4)
         # every tensor of the flat vector with its Philox tensor id (2*layer weight, 2*layer+1 bias), in
         # the order they lie in memory: the table of the one-launch finalize
@@ -281,6 +291,8 @@ class PrivatiseStep:
         self.group_of_layer_dev = torch.tensor(self.group_of_layer, dtype=torch.int32, device=dev)
         esize = 2 if wl.dtype == "bf16" else 4
         self._example_bytes = [b for l in self.layers for b in (l.x_bytes(esize), l.dy_bytes(esize))]
+        self._phase_forms = {}                   # micro-steps of a phase -> forms of the layers
+        self._inside = {}                        # and whose workspaces lie in the gradient matrix
         self._needs = {}                         # micro-steps of a phase -> descriptors and workspace sizes
         self._together = self._micro_steps_together()
         # Micro-steps that a copy has room for.  A step of one phase never uses a second copy; micro-steps that are handed over
@@ -327,21 +339,75 @@ class PrivatiseStep:
         return [(l.flops * n,
                  l.in_bytes(esize) * n + (4 * n * (pw + pb) if form == "materialise" else 0),
                  l.in_bytes(esize) * n + 8 * (pw + pb))
-                for l, pw, pb, form in zip(self.layers, self.pw, self.pb, self.form)]
+                for l, pw, pb, form in zip(self.layers, self.pw, self.pb, self._forms(tensors))]
+
+    def _forms(self, tensors: int) -> List[str]:
+        """Form of every layer's clipped sum in a phase of `tensors` micro-steps: that of a micro-step, except that a phase of many
+        one- or two-example micro-steps (which store every gradient) recomputes what a micro-step of that many examples would, where
+        finished fp32 blocks are scaled (how many micro-steps share a phase must not decide about precision) and the workspaces
+        fit where the gradients would have been.  Stored, a layer's gradients cross memory twice; ResNet-50, us per step, every
+        gradient stored / this: 3 x 1 364 / 310, 8 x 1 697 / 485, 64 x 1 4080 / 2228; 2 x 2 at 192 x 192, one stream 536 / 458."""
+        n = self.wl.n * tensors
+        if (tensors == 1 or self._mode != "auto" or self.wl.n > 2 or self.clip_unit > 1 or
+                any(p % 4 for p in self.pw + self.pb)):         # (zeros between tensors have a place of their own in the matrix)
+            return self.form
+        if tensors not in self._phase_forms:
+            use, over = B.DP_WS_RECOMPUTE | B.DP_RECOMPUTE_BLOCKS, {}       # layer -> workspace less its part of the matrix
+            for i, l in enumerate(self.layers):
+                d = B.make_desc(l, n, self.wl.dtype)
+                if self._choose(l, "auto", n) == "recompute" and B.dp_kernel_variant(d, use):
+                    need = max(B.dp_workspace_bytes(d, B.DP_WS_PER_EXAMPLE_GRAD), B.dp_workspace_bytes(d, use), 16)
+                    over[i] = _align256(need) - 4 * n * (self.pw[i] + self.pb[i])
+            while over and sum(over.values()) + 256 > 0:
+                del over[max(over, key=over.get)]
+            self._phase_forms[tensors] = ["recompute" if i in over else form for i, form in enumerate(self.form)] if over else self.form
+        return self._phase_forms[tensors]
+
+    def _recompute_use(self, tensors: int) -> int:
+        """Which clipped sum the recomputing layers of a phase run."""
+        return B.DP_WS_RECOMPUTE | (B.DP_RECOMPUTE_BLOCKS if self._forms(tensors) is not self.form else 0)
+
+    def _in_matrix(self, tensors: int) -> List[bool]:
+        """Layers whose workspace lies in the gradient matrix: those that do not use their columns of it in such a phase and need
+        more than they would if they did."""
+        if self._forms(tensors) is self.form:
+            return [False] * len(self.layers)
+        if tensors not in self._inside:
+            descs, need = self._workspaces(tensors)
+            self._inside[tensors] = [now != form and b > max(16, B.dp_workspace_bytes(d, B.DP_WS_PER_EXAMPLE_GRAD))
+                                     for d, b, now, form in zip(descs, need, self._forms(tensors), self.form)]
+        return self._inside[tensors]
+
+    def _columns(self, form: Sequence[str]):
+        """Offsets of the layers' tensors (weight, bias) when the materialised ones lie side by side, and how many columns they have."""
+        off_w, off_b, pos = [0] * len(self.layers), [0] * len(self.layers), 0
+        for i in sorted((i for i, f in enumerate(form) if f == "materialise"), key=lambda i: self.off_w[i]):
+            off_w[i] = pos
+            off_b[i] = pos + _pad4(self.pw[i])
+            pos = off_b[i] + _pad4(self.pb[i])
+        return off_w, off_b, pos
+
+    def _segments(self, form: Sequence[str], off_w: Sequence[int]):
+        """Runs of columns of the gradient matrix that belong to one clipping group and lie side by side in the accumulator."""
+        mat = sorted((i for i, f in enumerate(form) if f == "materialise"), key=lambda i: off_w[i])
+        runs = [i for k, i in enumerate(mat) if k == 0 or self.group_of_layer[i] != self.group_of_layer[mat[k - 1]] or
+                off_w[i] - off_w[mat[k - 1]] != self.off_w[i] - self.off_w[mat[k - 1]]]
+        groups = [self.group_of_layer[i] for i in runs]
+        return B.SegmentTable([off_w[i] for i in runs], groups, [self.group_clip[k] for k in groups], [self.off_w[i] for i in runs])
 
     def _workspaces(self, tensors: int):
         """Descriptors and workspace bytes of every layer in a phase of `tensors` micro-steps."""
         if tensors not in self._needs:
             descs = [B.make_desc(l, self.wl.n * tensors, self.wl.dtype) for l in self.layers]
             need = [max(16, B.dp_workspace_bytes(d, B.DP_WS_PER_EXAMPLE_GRAD),
-                        B.dp_workspace_bytes(d, B.DP_WS_RECOMPUTE) if form == "recompute" else 0,
+                        B.dp_workspace_bytes(d, self._recompute_use(tensors)) if form == "recompute" else 0,
                         B.dp_unit_workspace_bytes(d, self.clip_unit) if self.clip_unit > 1 else 0)
-                    for d, form in zip(descs, self.form)]
+                    for d, form in zip(descs, self._forms(tensors))]
             self._needs[tensors] = descs, need
         return self._needs[tensors]
 
     def _workspace_bytes(self, tensors: int) -> int:
-        return sum(_align256(b) for b in self._workspaces(tensors)[1])
+        return sum(_align256(b) for b, inside in zip(self._workspaces(tensors)[1], self._in_matrix(tensors)) if not inside)
 
     def _micro_steps_together(self) -> int:
         """Micro-steps per phase, at most."""
@@ -369,10 +435,10 @@ class PrivatiseStep:
         layer the per-example and the recomputing one."""
         flags = []
         if self.wl.dtype == "bf16":
-            for d, form in zip(self._workspaces(tensors)[0], self.form):
+            for d, form in zip(self._workspaces(tensors)[0], self._forms(tensors)):
                 stored = B.DP_VARIANT_MATERIALISE if form == "materialise" else 0
                 flags.append("gather" in B.dp_kernel_variant(d, B.DP_WS_PER_EXAMPLE_GRAD | B.DP_VARIANT_SHARED | stored))
-                flags.append(form == "recompute" and "gather" in B.dp_kernel_variant(d, B.DP_WS_RECOMPUTE | B.DP_VARIANT_SHARED))
+                flags.append(form == "recompute" and "gather" in B.dp_kernel_variant(d, self._recompute_use(tensors) | B.DP_VARIANT_SHARED))
         return flags
 
     def _phase_sizes(self, micro_steps: int) -> List[int]:
@@ -439,7 +505,7 @@ class PrivatiseStep:
         # strided 3x3 layer of stage 3, whose weighted form has no raw-row kernel, and the first 1x1 of stage 4 recompute
         # too) - 2 %, 44/10 (250) - 9 %, 26/28 (360) - 3 %.
         if n <= 2:
-            # phases of one or two examples are bound by their launches, and a recomputing layer brings launches of its
+            # micro-steps of one or two examples are bound by their launches, and a recomputing layer brings launches of its
             # own to the clipped-sum phase (measured: 5.9 k against 5.6 k examples/s with the split above)
             return "materialise"
         p = layer.pw + layer.pb
@@ -468,7 +534,16 @@ class PrivatiseStep:
 
     @property
     def g(self) -> Optional[torch.Tensor]:
-        return self._g_last
+        """[rows, p_mat] stored gradients of the most recent micro-step, columns as in the accumulator (no numbers where the phase that
+        it was part of stored none)."""
+        if self._g_last is None or self._g_last.shape[1] == self.p_mat:
+            return self._g_last
+        plan, out = self._sum_plan, torch.full((self.rows, self.p_mat), float("nan"), dtype=torch.float32, device=self.device)
+        for i, form in enumerate(plan.form):
+            if form == "materialise":
+                for to, at, size in ((self.off_w[i], plan.off_w[i], self.pw[i]), (self.off_b[i], plan.off_b[i], self.pb[i])):
+                    out[:, to: to + size] = self._g_last[:, at: at + size]
+        return out
 
     def enable_update(self, lr: float, momentum: float = 0.0, theta: Optional[torch.Tensor] = None,
                       keep_gradient: bool = True):
@@ -519,7 +594,7 @@ class PrivatiseStep:
         addresses.  ends_step: a caller may look at the last micro-step's norms afterwards."""
         at = plan.tensors > 1
         L = len(self.layers)
-        gs = self.p_mat
+        gs = plan.p_mat
         c = self._phases % len(plan.stores)
         store = plan.stores[c]
         g_buf, gsq = plan.g[c], plan.group_sqnorm[c]
@@ -566,9 +641,9 @@ class PrivatiseStep:
         self._sum_plan = plan
         for st in sb:
             st.wait_stream(main)
-        if self.p_mat:
+        if gs:
             # one launch over all materialised tensors, whatever their clipping groups
-            B.dp_clip_accumulate_columns(g_buf, gsq, self.n_groups, self._segments, plan.rows, plan.rows // plan.tensors, self.p_mat, self.acc,
+            B.dp_clip_accumulate_columns(g_buf, gsq, self.n_groups, plan.segments, plan.rows, plan.rows // plan.tensors, gs, self.acc,
                                          g_stride=gs, stream=sb[0].cuda_stream if sb else ms)
         if self.noise == "per_example":
             for li in range(L):

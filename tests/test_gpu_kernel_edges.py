@@ -129,6 +129,60 @@ _SEVERAL = [
 ]
 
 
+# Maps of 1, 9, 25, 49 and 64 positions in rows of 64; ragged channel counts below, at and beyond the tiles; strides with and without
+# a remainder; aligned rows in place; dense layers of one and of several tokens.
+_BLOCKS = [conv(128, 192, 1, 1, 7), conv(72, 136, 1, 2, 13), conv(80, 65, 1, 2, 9), conv(64, 96, 3, 1, 7), conv(40, 33, 3, 2, 14), conv(128, 64, 3, 1, 8),
+           conv(64, 64, 3, 1, 3), conv(130, 60, 1, 1, 1), conv(48, 64, 1, 1, 10), dense(200, 70), dense(66, 130, 20)]
+
+
+@pytest.mark.parametrize("layer", _BLOCKS, ids=str)
+def test_clipped_sum_that_scales_finished_blocks(layer):
+    """As exact as fp32 sums are: the products of bf16 inputs are exact, and each of the few additions per position and example
+    rounds by 2^-24 of a partial sum (F32_TOL / 10, where operands scaled in bf16 would show 2^-9).  Layers share a launch with
+    another one, examples lie in tensors of their own."""
+    for n in (1, 5, 34):
+        layers = [layer, _BLOCKS[0]]
+        descs = [dp.make_desc(l, n, "bf16") for l in layers]
+        use = dp.DP_WS_RECOMPUTE | dp.DP_RECOMPUTE_BLOCKS
+        wss = [torch.empty(max(16, dp.dp_workspace_bytes(d, use)), dtype=torch.uint8, device="cuda:0").fill_(255) for d in descs]
+        ins = [_inputs(l, n, 77 + k, "bf16") for k, l in enumerate(layers)]
+        tensors = [[dev(a, "bf16").unbind(0) for a in pair] for pair in ins]
+        tensors = [[[t.clone() for t in side] for side in pair] for pair in tensors]
+        tables = [[torch.tensor([t.data_ptr() for t in side], dtype=torch.int64, device="cuda:0") for side in pair] for pair in tensors]
+        n2 = (np.random.default_rng(7).uniform(0.4, 2.0, (2, n)) ** 2).astype(np.float32)
+        n2[:, n // 2] = -1.0 if n > 1 else n2[:, 0]              # a broken example: factor 0
+        n2d = dev(n2)
+        acc_w = [torch.full((l.pw,), 0.125, dtype=torch.float32, device="cuda:0") for l in layers]
+        acc_b = [torch.full((max(l.pb, 1),), 0.125, dtype=torch.float32, device="cuda:0") for l in layers]
+        batch = dp.LayerBatch(descs, [w.data_ptr() for w in wss], [w.numel() for w in wss], scale_blocks=True)
+        dp.dp_clip_accumulate_recompute_batch(batch, batch.ptrs([t[0].data_ptr() for t in tables]), batch.ptrs([t[1].data_ptr() for t in tables]),
+                                              batch.ptrs([n2d[k].data_ptr() for k in range(2)]), batch.floats([1.0, 1.0]),
+                                              batch.ptrs([t.data_ptr() for t in acc_w]),
+                                              batch.ptrs([t.data_ptr() if l.pb else None for t, l in zip(acc_b, layers)]), addresses=True)
+        torch.cuda.synchronize()
+        for k, l in enumerate(layers):
+            f = np.array([0.0 if v < 0 else oracle.clip_factor(float(v), 1.0) for v in n2[k]])
+            ref_w, ref_b, _ = _oracle_grads(l, *ins[k])
+            assert_close(host(acc_w[k]), 0.125 + (f[:, None] * ref_w).sum(axis=0), F32_TOL / 10, f"{l} n={n} weights")
+            if l.pb:
+                assert_close(host(acc_b[k])[:l.pb], 0.125 + (f[:, None] * ref_b).sum(axis=0), F32_TOL / 10, f"{l} n={n} bias")
+
+
+def test_layers_that_cannot_scale_finished_blocks_are_refused():
+    use = dp.DP_WS_RECOMPUTE | dp.DP_RECOMPUTE_BLOCKS
+    for layer in (conv(64, 64, 3, 1, 14), conv(64, 64, 1, 1, 7, bias=True), conv(64, 64, 1, 1, 9)):
+        d = dp.make_desc(layer, 4, "bf16")
+        assert dp.dp_kernel_variant(d, use) == "" and dp.dp_workspace_bytes(d, use) == 0
+        assert dp.dp_kernel_variant(dp.make_desc(layer, 4, "f32"), use) != ""
+        t = torch.zeros(4, dtype=torch.int64, device="cuda:0")
+        batch = dp.LayerBatch([d], [t.data_ptr()], [32], scale_blocks=True)
+        acc = torch.zeros(layer.pw, dtype=torch.float32, device="cuda:0")
+        with pytest.raises(dp.DpError):
+            dp.dp_clip_accumulate_recompute_batch(batch, batch.ptrs([t.data_ptr()]), batch.ptrs([t.data_ptr()]), batch.ptrs([t.data_ptr()]),
+                                                  batch.floats([1.0]), batch.ptrs([acc.data_ptr()]),
+                                                  batch.ptrs([acc.data_ptr() if layer.pb else None]), addresses=True)
+
+
 @pytest.mark.parametrize("n_per", [1, 3])
 @pytest.mark.parametrize("name,layer,dtype", _SEVERAL, ids=[c[0] for c in _SEVERAL])
 def test_examples_in_several_tensors(name, layer, dtype, n_per):
