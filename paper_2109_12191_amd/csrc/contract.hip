@@ -1763,6 +1763,49 @@ static bool subsampled(const Geo &g, int mode, Geo &g2)
     return true;
 }
 
+// Per-example calls of bf16 layers whose rows no fast kernel is built for (odd map sizes) run on copies with longer rows (launch_widen),
+// zeros behind the values: `g2` is the geometry of the copies.  Only inside batch calls, whose layers share the copying launch (alone it
+// costs what it saves: 128 -> 512 1x1 on 13 x 13, 36 examples 16 -> 26 us), and from 12 examples on (ResNet-50 at 208 x 208, us per
+// micro-step on eight streams, general kernel / copies: 8 examples 655 / 655, at 192 x 192 449 / 476; 16 examples 982 / 929; on one stream
+// 2 x 12 1570 / 1328; ResNet-18-GN at 40 x 40, 4 x 16 1084 / 898; ResNet-50 in units of four, 4 x 32 4400 / 4202), and not where the
+// copies are much longer than the rows (ResNet-18-GN at 32 x 32, 8 x 32, whose last maps are 4 x 4: 1678 / 1754 with them at 7 x 4).
+static thread_local int tl_rows_as_they_are = 0;
+RowsAsTheyAre::RowsAsTheyAre() { ++tl_rows_as_they_are; }
+RowsAsTheyAre::~RowsAsTheyAre() { --tl_rows_as_they_are; }
+
+static bool widened(const Geo &g, int mode, Geo &g2)
+{
+    if (mode == MODE_WEIGHTED || !g.bf16 || g.has_bias || tl_rows_as_they_are || !plan_crowd() || g.n < 12) return false;
+    g2 = g;
+    if (g.kh == 1 && g.kw == 1 && g.pad == 0) {
+        const int S = g.oh * g.ow;
+        Geo sampled;
+        if (g.stride == 1 ? flat_direct(g) : (subsampled(g, mode, sampled) && (flat_direct(sampled) || gram_norm_applicable(sampled, mode)))) return false;
+        if (g.cin < 32 || g.cout < 32 || S < 32) return false;
+        const int row = S < 64 ? 64 : (S + 7) / 8 * 8;
+        g2.h = g2.oh = 1; g2.w = g2.ow = row; g2.stride = 1;
+    } else if (g.kh == 3 && g.kw == 3 && g.pad == 1 && g.stride <= 2) {
+        static const int widths[2][7] = {{7, 8, 14, 16, 28, 32, 56}, {7, 14, 28, 28, 28, 28, 28}};
+        int k = 0;
+        while (k < 7 && widths[g.stride - 1][k] < g.ow) ++k;
+        if (k == 7 || widths[g.stride - 1][k] * 5 > g.ow * 7) return false;
+        g2.ow = widths[g.stride - 1][k];
+        g2.w = g2.ow * g.stride;
+        if (g.stride == 2) g2.h = 2 * g.oh;
+        if (!conv3x3_applicable(g2, mode)) return false;
+    } else if (g.kh == 7 && g.h % 2 == 0 && g.w % 2 == 0) {
+        g2.ow = (g.ow + 15) / 16 * 16;
+        g2.w = 2 * g2.ow;
+        if (g2.ow * 5 > g.ow * 6 || !stem_applicable(g2, mode)) return false;
+    } else {
+        return false;
+    }
+    g2.x_elems = (size_t)g.cin * g2.h * g2.w;
+    g2.dy_elems = (size_t)g.cout * g2.oh * g2.ow;
+    g2.x_tab = g2.dy_tab = 0;
+    return (size_t)g.n * (g2.x_elems + g2.dy_elems) * 2 <= ((size_t)256 << 20);
+}
+
 // workspace: [partial squared norms (per-example mode)] [partial tiles]
 static size_t align16(size_t b) { return (b + 15) & ~(size_t)15; }
 
@@ -1807,6 +1850,7 @@ static size_t conv_ws_bytes_mode(const Geo &g, int mode)
         const FullPlan f = full_plan(g2, mode);
         return align16(pp.x_bytes) + align16(pp.dy_bytes) + (f.ksplit > 1 ? f.part_floats * sizeof(float) : 0);
     }
+    if (widened(g, mode, g2)) return align16(conv_ws_bytes_mode(g2, mode)) + align16(g2.x_elems * g.n * 2) + align16(g2.dy_elems * g.n * 2);
     if (subsampled(g, mode, g2)) return conv_ws_bytes_mode(g2, mode) + align16(g2.x_elems * g.n * 2);
     const FullPlan f = full_plan(g, mode);
     size_t b = 0;
@@ -1824,6 +1868,7 @@ size_t conv_norm_partial_count(const Geo &g, int mode)
     if (gram_norm_applicable(g, mode)) return gram_norm_partial_count();
     if (conv3x3_applicable(g, mode)) return conv3x3_norm_partial_count(g);
     Geo g2;
+    if (widened(g, mode, g2)) return conv_norm_partial_count(g2, mode);
     if (subsampled(g, mode, g2)) return conv_norm_partial_count(g2, mode);
     return norm_partials_per_example(full_plan(g, mode));
 }
@@ -1848,6 +1893,8 @@ const char *conv_variant_name(const Geo &g, int mode, bool shared)
     if (conv_rows_applicable(g, mode)) return conv_rows_variant_name(g);
     if (gram_norm_applicable(g, mode)) return "conv_gram_norm<bf16>";
     if (conv3x3_applicable(g, mode)) return conv3x3_variant_name(g, mode);
+    Geo wide;
+    if (widened(g, mode, wide)) return conv_variant_name(wide, mode, shared);
     struct Names {
         char v[2][4][2][2][3][72];
         Names()
@@ -1867,7 +1914,10 @@ const char *conv_variant_name(const Geo &g, int mode, bool shared)
     Geo ge = g, g2;
     PackPlan pp;
     if (packed_weighted(g, mode, pp, g2) || packed_blocks(g, mode, pp, g2)) ge = g2;
-    else if (subsampled(g, mode, g2)) ge = g2;
+    else if (subsampled(g, mode, g2)) {
+        if (gram_norm_applicable(g2, mode)) return "conv_gram_norm<bf16,sampled>";      // (a launch of its own: the others need not wait for the copy)
+        ge = g2;
+    }
     const FullPlan f = full_plan(ge, mode);
     return names.v[g.bf16 ? 1 : 0][f.shape][mode == MODE_WEIGHTED ? 1 : 0][g.has_bias ? 1 : 0][loader_of(ge)];
 }
@@ -1936,6 +1986,23 @@ dp_status launch_conv(const Geo &g, int mode, const void *x, const void *dy, flo
         // the factors are already in dYp: no norms, and the kernel's own factor is 1 (what it would read are examples' norms, not
         // those of its example ranges)
         return launch_conv_impl(g2, mode, xp, dyp, out_w, out_b, out_stride, nullptr, nullptr, __builtin_inff(), w, s);
+    }
+    if (widened(g, mode, g2)) {
+        // the workspace of the call on the copies comes first (its partial norms stay at the start), then the copies
+        char *w = static_cast<char *>(ws) + align16(conv_ws_bytes_mode(g2, mode));
+        void *const xw = w, *const dyw = w + align16(g2.x_elems * g.n * 2);
+        const bool sampled = g.kh == 1 && g.stride > 1;          // a strided 1x1 layer: only the positions that it looks at
+        const bool flat = g.kh == 1;
+        const int S = g.oh * g.ow, row = (int)(g2.dy_elems / g.cout);
+        dp_status st;
+        if (sampled) st = launch_widen(x, g.x_tab, xw, g.n, g.cin, g.h, g.w, g.oh, g.ow, g.stride, g.ow, row, s);
+        else if (flat) st = launch_widen(x, g.x_tab, xw, g.n, g.cin, 1, S, 1, S, 1, row, row, s);
+        else st = launch_widen(x, g.x_tab, xw, g.n, g.cin, g.h, g.w, g.h, g.w, 1, g2.w, (int)(g2.x_elems / g.cin), s);
+        if (st != DP_OK) return st;
+        if (flat) st = launch_widen(dy, g.dy_tab, dyw, g.n, g.cout, 1, S, 1, S, 1, row, row, s);
+        else st = launch_widen(dy, g.dy_tab, dyw, g.n, g.cout, g.oh, g.ow, g.oh, g.ow, 1, g2.ow, row, s);
+        if (st != DP_OK) return st;
+        return launch_conv(g2, mode, xw, dyw, out_w, out_b, out_stride, sqnorm, group_sqnorm, clip_c, ws, s);
     }
     if (subsampled(g, mode, g2)) {
         // the sub-problem's own workspace comes first (its partial norms stay at the start), the copy of X after it

@@ -13,7 +13,7 @@
 // launches instead of a hundred.
 //
 // On the host, launchers hand their kernels to submit_kernel() with a tier: layout changes of the
-// inputs (TIER_LAYOUT), operand pre-passes (TIER_PRE), the contraction itself (TIER_MAIN, also
+// inputs (TIER_LAYOUT), rows brought to the length that a kernel is built for (TIER_ROWS), operand pre-passes (TIER_PRE), the contraction itself (TIER_MAIN, also
 // submit_main()), the sums over K slices (TIER_POST).  With no queue open a kernel is launched at once (a group of one); inside a batch call
 // (LaunchQueue open on this thread) it is held back until flush(), which launches tier after tier,
 // the held launches of a tier grouped by kernel, and then runs the deferred follow-up calls
@@ -53,7 +53,7 @@ __device__ __forceinline__ int group_pick(const Grouped<Args> &g, unsigned &bid)
 }
 #endif
 
-enum { TIER_LAYOUT = 0, TIER_PRE = 1, TIER_MAIN = 2, TIER_POST = 3, TIER_COUNT = 4 };
+enum { TIER_LAYOUT = 0, TIER_ROWS = 1, TIER_PRE = 2, TIER_MAIN = 3, TIER_POST = 4, TIER_COUNT = 5 };
 
 struct LaunchQueue {
     struct Item {

@@ -43,6 +43,8 @@ struct Geo {
 enum Mode { MODE_NORM = 0, MODE_MATERIALISE = 1, MODE_WEIGHTED = 2 };
 
 size_t conv_ws_bytes(const Geo &g, int mode);
+// While one lives, this thread's plans never bring rows to another length (dp_per_example_grad_static: the copies do not fit its scratch)
+struct RowsAsTheyAre { RowsAsTheyAre(); ~RowsAsTheyAre(); };
 const char *conv_variant_name(const Geo &g, int mode, bool shared);
 void c3_set_forced_crowd(int v);      // conv3x3.hip: plan as alone (0), as in a shared launch (1), or by the open batch (-1)
 dp_status launch_conv(const Geo &g, int mode, const void *x, const void *dy, float *out_w, float *out_b,
@@ -86,6 +88,11 @@ size_t gn_norm_partial_count(const Geo &g);
 
 // [n][positions][channels] -> [n][channels][positions], elements of 2 or 4 bytes (pack.hip): channels-last inputs
 dp_status launch_to_channels_first(const void *in, void *out, int n, int positions, int channels, int elem_bytes, hipStream_t s);
+
+// copy of an operand whose rows get another length (pack.hip): per example `channels` planes of dh x dw values, row-major, `row` values
+// from one plane to the next; value (r, c) is in[r * step][c * step] of a plane of h x w where r < rows and c < cols, zero elsewhere
+dp_status launch_widen(const void *in, int tab, void *out, int n, int channels, int h, int w, int rows, int cols, int step, int dw, int row,
+                       hipStream_t s);
 
 // compact copy of the rows / columns a strided 1x1 convolution reads: out[n*cin][OH*OW] (pack.hip)
 dp_status launch_subsample(const Geo &g, const void *x, void *out, hipStream_t s);

@@ -293,6 +293,7 @@ class PrivatiseStep:
         self._example_bytes = [b for l in self.layers for b in (l.x_bytes(esize), l.dy_bytes(esize))]
         self._phase_forms = {}                   # micro-steps of a phase -> forms of the layers
         self._inside = {}                        # and whose workspaces lie in the gradient matrix
+        self._ws_bytes = {}                      # and how much the others take together
         self._needs = {}                         # micro-steps of a phase -> descriptors and workspace sizes
         self._together = self._micro_steps_together()
         # Micro-steps that a copy has room for.  A step of one phase never uses a second copy; micro-steps that are handed over
@@ -407,7 +408,9 @@ class PrivatiseStep:
         return self._needs[tensors]
 
     def _workspace_bytes(self, tensors: int) -> int:
-        return sum(_align256(b) for b, inside in zip(self._workspaces(tensors)[1], self._in_matrix(tensors)) if not inside)
+        if tensors not in self._ws_bytes:
+            self._ws_bytes[tensors] = sum(_align256(b) for b, inside in zip(self._workspaces(tensors)[1], self._in_matrix(tensors)) if not inside)
+        return self._ws_bytes[tensors]
 
     def _micro_steps_together(self) -> int:
         """Micro-steps per phase, at most."""

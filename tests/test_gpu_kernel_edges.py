@@ -129,6 +129,56 @@ _SEVERAL = [
 ]
 
 
+# Rows that are brought to another length: planes of whole pieces (1x1, 56- and 16-wide), of halves (28) and of neither (14, 7, parity
+# split after it); fewer than 64 positions, one beyond a multiple of 8; strides with and without a remainder; the first convolution.
+_WIDENED = [conv(64, 96, 1, 1, 7), conv(40, 33, 1, 1, 9), conv(33, 64, 1, 1, 13), conv(48, 80, 1, 2, 13), conv(32, 36, 1, 2, 26), conv(64, 64, 3, 1, 5),
+            conv(64, 72, 3, 1, 13), conv(66, 64, 3, 1, 20), conv(64, 64, 3, 1, 15), conv(64, 64, 3, 1, 40), conv(64, 64, 3, 2, 13), conv(64, 65, 3, 2, 25),
+            conv(64, 64, 3, 2, 40), Layer("conv", 64, 64, 9, 25, 3, 3, 1, 1, False), Layer("conv", 64, 64, 11, 12, 3, 3, 2, 1, False), conv(3, 64, 7, 2, 60)]
+
+
+@pytest.mark.parametrize("several", [False, True])
+@pytest.mark.parametrize("materialise", [False, True])
+def test_rows_brought_to_another_length(materialise, several):
+    """In one batch call with room for the copies alone (F32_TOL: the products of bf16 inputs are exact, sums are fp32), examples in one
+    tensor or each in one of its own.  What is around the inputs is not a number."""
+    n = 13
+    shared = dp.DP_WS_PER_EXAMPLE_GRAD | dp.DP_VARIANT_SHARED | (dp.DP_VARIANT_MATERIALISE if materialise else 0)
+    descs = [dp.make_desc(l, n, "bf16") for l in _WIDENED]
+    for l, d in zip(_WIDENED, descs):
+        assert "gather" not in dp.dp_kernel_variant(d, shared), l
+    ins = [_inputs(l, n, 30 + k, "bf16") for k, l in enumerate(_WIDENED)]
+    kept, ptrs = [], [[], []]
+    for pair in ins:
+        for side, a in enumerate(pair):
+            t, per = dev(a, "bf16").view(n, -1), a[0].size
+            room = (per + 31) // 8 * 8
+            if several:
+                own = torch.full((n, 8 + room), float("nan"), dtype=torch.bfloat16, device="cuda:0")
+                own[:, 8: 8 + per] = t
+                table = torch.tensor([own[i, 8:].data_ptr() for i in range(n)], dtype=torch.int64, device="cuda:0")
+                kept += [own, table]
+                ptrs[side].append(table.data_ptr())
+            else:
+                own = torch.full((8 + n * per + 32,), float("nan"), dtype=torch.bfloat16, device="cuda:0")
+                own[8: 8 + n * per] = t.reshape(-1)
+                kept.append(own)
+                ptrs[side].append(own[8:].data_ptr())
+    sizes = [dp.dp_workspace_bytes(d) for d in descs]
+    wss = [torch.full((b,), 255, dtype=torch.uint8, device="cuda:0") for b in sizes]
+    stride = max(l.pw for l in _WIDENED) + 3 & ~3
+    g = [torch.full((n, stride), float("nan"), dtype=torch.float32, device="cuda:0") for _ in descs]
+    sq = torch.full((len(descs), n), -1.0, device="cuda:0")
+    batch = dp.LayerBatch(descs, [w.data_ptr() for w in wss], sizes)
+    dp.dp_per_example_grad_batch(batch, batch.ptrs(ptrs[0]), batch.ptrs(ptrs[1]), batch.ptrs([t.data_ptr() for t in g]) if materialise else None, None,
+                                 batch.ptrs([sq[k].data_ptr() for k in range(len(descs))]), g_stride=stride if materialise else 0, addresses=several)
+    torch.cuda.synchronize()
+    for k, l in enumerate(_WIDENED):
+        ref_w, _, ref_n2 = _oracle_grads(l, *ins[k])
+        assert np.allclose(host(sq[k]), ref_n2, rtol=F32_TOL, atol=0), (k, l)
+        if materialise:
+            assert_close(host(g[k][:, : l.pw]), ref_w, F32_TOL, f"layer {k} {l}")
+
+
 # Maps of 1, 9, 25, 49 and 64 positions in rows of 64; ragged channel counts below, at and beyond the tiles; strides with and without
 # a remainder; aligned rows in place; dense layers of one and of several tokens.
 _BLOCKS = [conv(128, 192, 1, 1, 7), conv(72, 136, 1, 2, 13), conv(80, 65, 1, 2, 9), conv(64, 96, 3, 1, 7), conv(40, 33, 3, 2, 14), conv(128, 64, 3, 1, 8),
