@@ -88,6 +88,8 @@ __global__ void __launch_bounds__(256) gn_affine_3pass_kernel(const Grouped<GnAr
 // launch per layer and one wave per channel with 2- or 4-byte loads: ResNet-18-GN, 8 x 32 examples, 20 layers: 1377 ->
 // 606 us (160 -> 16 launches; whole step 2.67 -> 2.07 ms); ResNet-20 in fp32, 256 examples: 963 -> 429 us.
 constexpr int GN_CMAX = 256;
+constexpr int GN_WIDE_HW = 1024;             // maps of so many values, a multiple of four, are read four at a time
+constexpr int GN_SHIFTED = 9;                // GnArgs::vec: vectors of eight bf16 values that need not start with a channel
 
 template <bool BF16, int V>
 __device__ __forceinline__ void gn_load(const typename In<BF16>::type *p, float (&o)[V])
@@ -111,7 +113,9 @@ __device__ __forceinline__ void gn_load(const typename In<BF16>::type *p, float 
     }
 }
 
-template <bool BF16, int V>
+// SHIFTED: channels that do not start on 16 bytes (odd maps) are read in the aligned vectors that cover them.  The first and the last
+// of these hold values of the neighbours, which are masked; a last one that reaches beyond the tensor is read value by value.
+template <bool BF16, int V, bool SHIFTED = false>
 __device__ __forceinline__ void gn_affine_body(const GnArgs &a, unsigned bid, float *s_dx, float *s_d, float *red)
 {
     typedef typename In<BF16>::type E;
@@ -126,14 +130,24 @@ __device__ __forceinline__ void gn_affine_body(const GnArgs &a, unsigned bid, fl
     const size_t ex = (size_t)a.c * a.hw, first = (size_t)grp * cg * a.hw;
     const E *xg = example_at_uniform<E>(a.x, a.x_tab, i, ex) + first;
     const E *dyg = example_at_uniform<E>(a.dy, a.dy_tab, i, ex) + first;
+    // end of the tensor that the example lies in, as far as it is known
+    const uintptr_t x_end = reinterpret_cast<uintptr_t>(xg - first) + ex * sizeof(E) * (size_t)(a.x_tab ? 1 : a.n - i);
     const float k = In<BF16>::ld(xg);
     s_dx += sub * cg;
     s_d += sub * cg;
 
-    const int nv = a.hw / V, tl = lane & (team - 1), teams = 64 / team;
+    const int hw = a.hw, tl = lane & (team - 1), teams = 64 / team;
     float sx = 0.0f, sxx = 0.0f;
     for (int cl = wv * teams + lane / team; cl < cg; cl += waves * teams) {
         const E *xc = xg + (size_t)cl * a.hw, *dc = dyg + (size_t)cl * a.hw;
+        int nv = hw / V, off = 0, last = 0;                           // whole vectors of the channel
+        if constexpr (SHIFTED) {
+            off = (int)((reinterpret_cast<uintptr_t>(xc) & 15u) / sizeof(E));      // values before the channel in its first vector
+            last = (off + hw + V - 1) / V - 1;
+            nv = last - 1;                                            // those between the first and the last
+            xc += V - off;
+            dc += V - off;
+        }
         float dx[V], d1[V], x1[V], x2[V];
 #pragma unroll
         for (int e = 0; e < V; ++e) dx[e] = d1[e] = x1[e] = x2[e] = 0.0f;
@@ -144,25 +158,53 @@ __device__ __forceinline__ void gn_affine_body(const GnArgs &a, unsigned bid, fl
                 dx[e] += dv[e] * xs; d1[e] += dv[e]; x1[e] += xs; x2[e] += xs * xs;
             }
         };
+        constexpr int U = SHIFTED ? 3 : 4;                            // vectors in flight (a fourth costs the kernel a wave per SIMD)
         int p = tl;
-        for (; p + 3 * team < nv; p += 4 * team) {
-            float xv[4][V], dv[4][V];
+        for (; p + (U - 1) * team < nv; p += U * team) {
+            float xv[U][V], dv[U][V];
 #pragma unroll
-            for (int u = 0; u < 4; ++u) { gn_load<BF16, V>(xc + (size_t)(p + u * team) * V, xv[u]); gn_load<BF16, V>(dc + (size_t)(p + u * team) * V, dv[u]); }
+            for (int u = 0; u < U; ++u) { gn_load<BF16, V>(xc + (size_t)(p + u * team) * V, xv[u]); gn_load<BF16, V>(dc + (size_t)(p + u * team) * V, dv[u]); }
 #pragma unroll
-            for (int u = 0; u < 4; ++u) add(xv[u], dv[u]);
+            for (int u = 0; u < U; ++u) add(xv[u], dv[u]);
         }
-        {                                                             // up to three more vectors, loaded together
-            float xv[3][V], dv[3][V];
+        if (!SHIFTED || nv > 0) {                                     // the vectors that are left, loaded together
+            float xv[U - 1][V], dv[U - 1][V];
 #pragma unroll
-            for (int u = 0; u < 3; ++u) {
+            for (int u = 0; u < U - 1; ++u) {
                 const int at = min(p + u * team, nv - 1);
                 gn_load<BF16, V>(xc + (size_t)at * V, xv[u]);
                 gn_load<BF16, V>(dc + (size_t)at * V, dv[u]);
             }
 #pragma unroll
-            for (int u = 0; u < 3; ++u)
+            for (int u = 0; u < U - 1; ++u)
                 if (p + u * team < nv) add(xv[u], dv[u]);
+        }
+        if constexpr (SHIFTED) {
+#pragma unroll 1
+            for (int edge = 0; edge < 2; ++edge) {
+                if (tl != (edge ? team - 1 : 0)) continue;
+                const int e0 = edge ? last * V - off : -off;          // the channel's value that the vector starts at
+                const E *xe = xc + (off - V) + e0, *de = dc + (off - V) + e0;
+                float xv[V], dv[V];
+                if (reinterpret_cast<uintptr_t>(xe + V) <= x_end) {
+                    gn_load<BF16, V>(xe, xv);
+                    gn_load<BF16, V>(de, dv);
+                } else {
+#pragma unroll
+                    for (int e = 0; e < V; ++e) {
+                        const bool in = e0 + e >= 0 && e0 + e < hw;
+                        xv[e] = in ? In<BF16>::ld(xe + e) : k;
+                        dv[e] = in ? In<BF16>::ld(de + e) : 0.0f;
+                    }
+                }
+#pragma unroll
+                for (int e = 0; e < V; ++e) {
+                    const bool in = e0 + e >= 0 && e0 + e < hw;
+                    xv[e] = in ? xv[e] : k;
+                    dv[e] = in ? dv[e] : 0.0f;
+                }
+                add(xv, dv);
+            }
         }
         float sdx = 0.0f, sd = 0.0f;
 #pragma unroll
@@ -203,13 +245,14 @@ __device__ __forceinline__ void gn_affine_body(const GnArgs &a, unsigned bid, fl
 }
 
 template <bool BF16>
-__global__ void __launch_bounds__(256) gn_affine_kernel(const Grouped<GnArgs> grp)
+__global__ void __launch_bounds__(256, 4) gn_affine_kernel(const Grouped<GnArgs> grp)
 {
     __shared__ float s_dx[GN_CMAX], s_d[GN_CMAX], red[8];
     unsigned bid;
     const GnArgs &a = grp.a[group_pick(grp, bid)];
     if constexpr (BF16) {
         if (a.vec == 8) { gn_affine_body<true, 8>(a, bid, s_dx, s_d, red); return; }
+        if (a.vec == GN_SHIFTED) { gn_affine_body<true, 8, true>(a, bid, s_dx, s_d, red); return; }
     }
     if (a.vec == 4) gn_affine_body<BF16, 4>(a, bid, s_dx, s_d, red);
     else if (a.vec == 2) gn_affine_body<BF16, 2>(a, bid, s_dx, s_d, red);
@@ -222,7 +265,12 @@ static void gn_plan(GnArgs &a, bool bf16)
     const int cg = a.c / a.groups;
     a.vec = bf16 ? 8 : 4;
     while (a.hw % a.vec) a.vec >>= 1;
-    const int nv = a.hw / a.vec;
+    int nv = a.hw / a.vec;
+    // maps that are no multiple of eight values: eight at a time all the same.  us per call, narrower vectors / this: 1024 channels on
+    // 13 x 13, 36 examples 25.4 / 15.1; 2048 on 7 x 7, 64 examples 21.3 / 12.7; 512 on 25 x 25, 36 25.4 / 23.0; 256 on 14 x 14, 128 14.8 / 12.3.
+    // All layers of ResNet-50-GN at 200 x 200, 36 examples: 599 / 422.  Multiples of four values keep vectors of four from GN_WIDE_HW values on: a channel's
+    // two ends cost more than they bring (256 on 50 x 50, 36 examples: 26.1 / 28.7).
+    if (bf16 && a.vec < 8 && a.hw >= 16 && (a.vec < 4 || a.hw < GN_WIDE_HW)) { a.vec = GN_SHIFTED; nv = (a.hw + 14) / 8; }
     a.team = 1;
     while (a.team < 64 && a.team * 4 < nv) a.team <<= 1;              // about four vectors per lane,
     while (a.team < 64 && (64 / a.team) / 2 >= cg) a.team <<= 1;      // and no more teams in a wave than the group has channels

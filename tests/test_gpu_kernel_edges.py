@@ -129,6 +129,27 @@ _SEVERAL = [
 ]
 
 
+# maps of an odd number of values: channels start anywhere; one vector at each end, none between, several; a lane and a team per channel
+@pytest.mark.parametrize("c,hw,groups,n", [(64, 7, 32, 3), (32, 13, 8, 2), (64, 5, 4, 5), (256, 25, 32, 1), (8, 14, 8, 3), (512, 6, 2, 2), (8, 45, 4, 2)])
+def test_groupnorm_channels_that_start_anywhere(c, hw, groups, n):
+    """bf16; what lies behind the inputs is not a number."""
+    layer = gn_affine(c, hw, groups)
+    x, dy = _inputs(layer, n, 117, "bf16")
+    x = to_bf16_grid(x * 1.5 + 0.25)
+    ref_w, ref_b, ref_n2 = _oracle_grads(layer, x, dy)
+    own = [torch.full((a.size + 64,), float("nan"), dtype=torch.bfloat16, device="cuda:0") for a in (x, dy)]
+    for t, a in zip(own, (x, dy)):
+        t[: a.size] = dev(a, "bf16").view(-1)
+    d = dp.make_desc(layer, n, "bf16")
+    ws = torch.empty(max(16, dp.dp_workspace_bytes(d)), dtype=torch.uint8, device="cuda:0")
+    g, sq = torch.zeros((n, 2 * c), device="cuda:0"), torch.zeros(n, device="cuda:0")
+    dp.dp_per_example_grad(d, own[0], own[1], g, g[:, c:], sq, ws, g_stride=2 * c)
+    torch.cuda.synchronize()
+    assert_close(host(g[:, :c]), ref_w, F32_TOL, "dgamma")
+    assert_close(host(g[:, c:]), ref_b, F32_TOL, "dbeta")
+    assert np.allclose(host(sq), ref_n2, rtol=F32_TOL, atol=0)
+
+
 # Rows that are brought to another length: planes of whole pieces (1x1, 56- and 16-wide), of halves (28) and of neither (14, 7, parity
 # split after it); fewer than 64 positions, one beyond a multiple of 8; strides with and without a remainder; the first convolution.
 _WIDENED = [conv(64, 96, 1, 1, 7), conv(40, 33, 1, 1, 9), conv(33, 64, 1, 1, 13), conv(48, 80, 1, 2, 13), conv(32, 36, 1, 2, 26), conv(64, 64, 3, 1, 5),
