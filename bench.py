@@ -293,11 +293,12 @@ def main():
     # gradients written and read back where they are materialised, the accumulator read and written by every clipped
     # sum, finalize) over the measured step time.
     # (micro-steps issued together add to the accumulator once)
-    phases = -(-wl.accum // ps.micro_steps_per_phase)
-    sums = 8.0 * (ps.p_mat + sum(pw + pb for pw, pb, f in zip(ps.pw, ps.pb, ps.form) if f == "recompute"))
-    step_bytes = (wl.accum * (sum(w[1] for w in ps.work) + sum(l.in_bytes(esize) * wl.n for l, f in zip(wl.layers, ps.form) if f == "recompute")
-                              + 4.0 * ps.rows * ps.p_mat) + phases * sums + 8.0 * wl.n_params)
-    step_flops = wl.accum * (sum(w[0] for w in ps.work) + sum(w[0] for w, f in zip(ps.work, ps.form) if f == "recompute"))
+    phases, main = -(-wl.accum // ps.micro_steps_per_phase), ps._main
+    forms, part = main.form, wl.accum / main.tensors
+    sums = 8.0 * (main.p_mat + sum(pw + pb for pw, pb, f in zip(ps.pw, ps.pb, forms) if f == "recompute"))
+    step_bytes = (part * (sum(w[1] for w in main.work) + sum(l.in_bytes(esize) * main.n for l, f in zip(wl.layers, forms) if f == "recompute")
+                          + 4.0 * main.rows * main.p_mat) + phases * sums + 8.0 * wl.n_params)
+    step_flops = part * (sum(w[0] for w in main.work) + sum(w[0] for w, f in zip(main.work, forms) if f == "recompute"))
     step_sec = elapsed / args.steps
     if roofline is not None:
         roofline["whole_step"] = dict(algorithmic_bytes=step_bytes, algorithmic_flop=step_flops, GBps=step_bytes / step_sec / 1e9,
@@ -319,7 +320,7 @@ def main():
                                f"{wl.accum} accumulation = {wl.total_batch} examples/step, {wl.clip_mode} clipping "
                                f"C={wl.clip_c}, sigma={wl.sigma}, {wl.dtype} inputs, fp32 accumulators"
                                + (f", clipping units of {args.clip_unit} examples" if args.clip_unit > 1 else ""),
-                   "clipped_sum_forms": {f: ps.form.count(f) for f in sorted(set(ps.form))},
+                   "clipped_sum_forms": {f: forms.count(f) for f in sorted(set(forms))},
                    "issue": "host calls" if args.no_graph else f"HIP graph, {args.streams} side streams",
                    "finalize": "noise + SGD-momentum update fused" if args.fused_update else "noise + divide by |B|",
                    "noise_form": args.noise,
