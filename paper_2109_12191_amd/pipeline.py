@@ -35,8 +35,8 @@ PHASE_MICRO_STEP_BYTES = 1.25e9
 #   one / 192 2840 / 2470, 64: one by one / 256 3452 / 3223 (128: 6101 / 6338, a loss inside the line).  Beyond, ResNet-20, 256: one by one /
 #   512 2493 / 2411; ResNet-18-GN, 48: 192 / 384 2470 / 2556, 64: 256 / 512 3223 / 7084
 PHASE_EXAMPLES = 256
-#   and of micro-steps of one or two examples, which store every gradient.  ResNet-50, 64 x 1: one by one / 16 / 32 / 64 9783 / 4550 /
-#   4314 / 4105; 32 x 2: 8068 / 4546 (16) / 4317 / 4102
+#   and of micro-steps of one or two examples.  ResNet-50, 64 x 1: one by one / 16 / 32 / 64 10476 / 2672 / 2279 / 2224; 32 x 2: 8221 /
+#   2663 (16) / 2310 / 2236
 PHASE_EXAMPLES_STORED = 64
 # And no phase is so large that a layer falls back to the kernel that gathers its operands element by element, because the rewritten
 # operands of a faster one outgrow their share of the workspace: ResNet-18-GN at 40 x 40, 64 examples 3656 / 5083 (two micro-steps) / 7188

@@ -357,3 +357,29 @@ def test_buffers_go_with_their_step(order):
         assert all(k() is None for k in kept)
     finally:
         gc.enable()
+
+
+@pytest.mark.parametrize("n,accum,hw,streams", [(1, 64, 224, 4), (1, 3, 224, 1), (2, 16, 192, 4), (1, 24, 160, 1), (1, 8, 64, 4)])
+def test_workspaces_in_the_gradient_matrix_lie_behind_the_stored_columns(order, n, accum, hw, streams):
+    """A phase that recomputes keeps the stored columns side by side at the front of the matrix and the workspaces of the other layers in
+    the rest of it, each to itself; what it stores goes to the accumulator's places."""
+    wl = get_workload("resnet50_nano", n=n, accum=accum, hw=hw)
+    ps = dp.PrivatiseStep(wl, device="cpu", streams=streams)
+    for tensors in {accum, max(2, accum // 2), 3}:
+        plan, inside = ps._plan(tensors), ps._in_matrix(tensors)
+        if n * tensors < 3:
+            assert plan.form is ps.form
+            continue
+        assert plan.form.count("recompute") >= 10 and all(l.kind == "dense" for l, f, k in zip(ps.layers, plan.form, inside) if f == "recompute" and not k)
+        for c, store in enumerate(plan.stores):
+            first, end = store.g.data_ptr() + 4 * plan.rows * plan.p_mat, store.g.data_ptr() + 4 * store.g.numel()
+            spans = sorted((at, at + b) for at, b, k in zip(plan.ws[c], plan.ws_bytes, inside) if k)
+            assert first <= spans[0][0] and spans[-1][1] <= end and all(a[1] <= b[0] for a, b in zip(spans, spans[1:]))
+            rest = [(at, at + b) for at, b, k in zip(plan.ws[c], plan.ws_bytes, inside) if not k]
+            assert store.ws.data_ptr() <= min(rest)[0] and max(rest)[1] <= store.ws.data_ptr() + store.ws.numel()
+        ends = list(plan.segments.begin[1:]) + [plan.p_mat]
+        for i, form in enumerate(plan.form):
+            if form == "materialise":
+                k = max(s for s in range(plan.segments.n_seg) if plan.segments.begin[s] <= plan.off_w[i])
+                assert plan.off_w[i] + ps.pw[i] <= ends[k] and plan.segments.group[k] == ps.group_of_layer[i]
+                assert plan.segments.place[k] + plan.off_w[i] - plan.segments.begin[k] == ps.off_w[i]
