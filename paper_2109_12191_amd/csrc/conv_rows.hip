@@ -34,10 +34,9 @@
 #include "group.h"
 #include "internal.h"
 #include "pieces.h"
+#include "rows_plan.h"
 
-#include <algorithm>
 #include <atomic>
-#include <cmath>
 #include <cstring>
 
 namespace dp {
@@ -47,8 +46,6 @@ namespace {
 typedef float r_f32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int CR_LEFT = 4;                      // zeros in front of a staged image row (padding <= 2; keeps pieces of four on 8 bytes)
-constexpr int cr_qmax(int k) { return k == 5 ? 2 : 4; }
-constexpr int CR_PIECES = 4;                    // 16-byte pieces a thread moves per chunk
 // Where tap kw of a run is: in which columns of the row (stride 2: 0 the even, 1 the odd ones), and how many numbers behind the run's window
 constexpr int cr_parity(int k, int s, int kw) { return s == 1 ? 0 : (kw - (k - 1) / 2) & 1; }
 constexpr int cr_shift(int k, int s, int kw) { return CR_LEFT + (s == 1 ? kw - (k - 1) / 2 : (kw - (k - 1) / 2 - cr_parity(k, s, kw)) / 2); }
@@ -70,6 +67,7 @@ struct RowsArgs {
     int rows, chunks;               // output rows per chunk, chunks per example
     int rpr;                        // runs per output row
     int xp, cha, chx;               // LDS pitches in dwords: a staged image row, a channel of dY, a channel of X
+    int tail;                       // RowsPlan::tail
     int waves_a;                    // waves that stage dY (the others stage X)
     int bufs;                       // chunks in LDS (1 or 2)
     int bias;
@@ -121,9 +119,10 @@ __global__ void __launch_bounds__(64 * K * cr_qmax(K)) conv_rows_kernel(const Gr
     const int groups = (R * RPR + 3) / 4;
 
     // LDS: per chunk dY, [channel][run][part][8 numbers], and X, [channel][row][8 columns of a parity][parity][part]; then the runs' offsets.
-    // (Parts of eight numbers side by side: every read of a run has a constant offset.)  The epilogue uses the chunks' place.
+    // (Parts of eight numbers side by side: every read of a run has a constant offset.)  The epilogue uses the chunks' place, and may need more of
+    // it than they do; the table is written once for all examples of the workgroup.
     const int chunk_x = CO * a.cha, chunk_dwords = chunk_x + CI * a.chx;
-    int *tab = reinterpret_cast<int *>(rows_lds + a.bufs * chunk_dwords);
+    int *tab = reinterpret_cast<int *>(rows_lds + a.tail);
     float *red = reinterpret_cast<float *>(tab + groups * 4);
     float *epi = reinterpret_cast<float *>(rows_lds);
     const int EP = CI * K * K + 2;                     // pitch of a gradient row in LDS (spreads the lane groups over the banks)
@@ -398,99 +397,6 @@ __global__ void __launch_bounds__(64 * K * cr_qmax(K)) conv_rows_kernel(const Gr
     }
 }
 
-struct RowsPlan {
-    int nm, nn, tiles_m, tiles_n, q, rows, chunks, rpr, xp, cha, chx, bufs, waves_a, ex_per_wg;
-    unsigned lds;
-    double us;                      // estimated time of a call alone
-    bool ok;
-};
-
-int odd_quads(int floats) { const int v = (floats + 3) / 4; return (v | 1) * 4; }     // consecutive channels start in different banks
-
-// us of a per-example call alone.  A launch lasts as long as the compute unit with most blocks, which takes them in rounds of as many
-// workgroups as it has room for.  Chunk by chunk a round needs the longer of two things (a little more where they are close): what
-// the SIMD with most waves issues for all its workgroups -- MFMAs and vector instructions take turns on a SIMD, and the waves of every
-// workgroup start on the same one, so K q waves count as ceil(K q / 4) on it --, or one workgroup's own chain of barrier, loads, staging and
-// MFMAs.  Constants (cycles; per kernel size and stride) fitted to 4223 launches of 181 layers with forced plans: the plan it prefers is 3.5 %
-// slower than the best one on average.
-double rows_us(int k, int s, const RowsPlan &p, double blocks, int unit, int groups, long long pieces, bool ragged, int resident)
-{
-    struct Fit { double mfma, vector, group, slot, ragged, chunk, chain, finish, block, launch, lone; };
-    static const Fit fits[2][2] = {{{0.56, 0.33, 175.0, 304.0, 135.0, 2415.0, 0.0, 7000.0, 357.0, 3.7, 595.0}, {0.7, 0.0, 47.0, 278.0, 73.0, 2472.0, 411.0, 13240.0, 254.0, 3.1, 198.0}},
-                                   {{1.19, 0.0, 0.0, 194.0, 75.0, 1893.0, 0.0, 24200.0, 0.0, 2.6, 1617.0}, {1.11, 0.0, 0.0, 213.0, 78.0, 2432.0, 0.0, 21070.0, 206.0, 1.9, 289.0}}};
-    const Fit &c = fits[k / 2 - 1][s - 1];
-    const int turns = (groups + p.q - 1) / p.q;
-    const double group = p.nm * p.nn * k * 6 * 18.8 * c.mfma + (24 * p.nn * s + 4 * p.nm * p.nn * k) * 2.65 * c.vector + c.group;
-    const double staging = (double)pieces / (64 * k * p.q) * (c.slot + (ragged ? c.ragged : 0.0)), chunks = (double)p.chunks * unit;
-    const auto round = [&](double r) {
-        if (r <= 0.0) return 0.0;
-        const double all = r * ((k * p.q + 3) / 4) * (turns * group + staging), own = c.chunk + turns * (group + c.chain) + staging + (p.bufs == 1 ? c.lone : 0.0);
-        return chunks * std::cbrt(all * all * all + own * own * own) + (c.finish + c.block * p.nm * p.nn * k * (p.q + 1)) * (0.6 + 0.4 * r);
-    };
-    const double most = std::ceil(blocks / 256.0), r = std::min<double>(most, resident), full = std::floor(most / r);
-    return c.launch + (full * round(r) + round(most - full * r)) / 2400.0;
-}
-
-// Blocks of 16 channels that a workgroup takes of `c` channels (5 x 5: one of input channels, five accumulators a block).
-int rows_nm(const Geo &g) { return g.cout > 16 ? 2 : 1; }
-int rows_nn(const Geo &g) { return g.kh == 3 && g.cin > 16 ? 2 : 1; }
-
-RowsPlan rows_plan(const Geo &g, bool shared)
-{
-    RowsPlan best = {}, p = {};
-    const int K = g.kh, S = g.stride;
-    p.nm = rows_nm(g);
-    p.nn = rows_nn(g);
-    const int CO = 16 * p.nm, CI = 16 * p.nn;
-    p.rpr = (g.ow + 7) / 8;
-    p.xp = 12 * S * (p.rpr + 1);                // a run reads sixteen numbers
-    p.tiles_m = (g.cout + CO - 1) / CO;
-    p.tiles_n = (g.cin + CI - 1) / CI;
-    const int lc = g.cout < CO ? g.cout : CO, ln = g.cin < CI ? g.cin : CI;      // channels that are staged
-    const double own = (double)(g.n / g.unit) * p.tiles_m * p.tiles_n;
-    // Inside a batch call of several layers the plan with the best rate of a full chip, eight blocks on every compute unit, whatever
-    // this layer brings: the other layers' workgroups run on the units beside its own.  ResNet-20, 256 examples on eight streams: 758 us
-    // as alone, 641 so; 4 x 32: 473, 393.
-    const double blocks = shared ? 8.0 * 256.0 : own;
-    // several examples in a row where there are far more (example, block) pairs than workgroups that run at a time
-    const int e = (int)(own / 4096.0);
-    p.ex_per_wg = g.unit * (e < 1 ? 1 : e > 8 ? 8 : e);
-    for (p.q = 1; p.q <= cr_qmax(K); ++p.q)
-        for (p.rows = 1; p.rows <= g.oh && p.rows <= 64; ++p.rows) {
-            const int lines = (p.rows - 1) * S + K;
-            if (lines > 127) break;
-            const long long pieces_a = (long long)lc * p.rows * ((g.ow + 3) / 4), pieces_x = (long long)ln * lines * ((g.w + 3) / 4), pieces = pieces_a + pieces_x;
-            // waves in proportion to the pieces
-            const int waves = K * p.q;
-            p.waves_a = std::min<long long>(std::max<long long>((pieces_a * waves + pieces / 2) / pieces, 1), waves - 1);
-            if (pieces_a > CR_PIECES * 64ll * p.waves_a) ++p.waves_a;
-            if (p.waves_a == waves || pieces_a > CR_PIECES * 64ll * p.waves_a || pieces_x > CR_PIECES * 64ll * (waves - p.waves_a)) {
-                if (pieces > CR_PIECES * 64ll * waves) break;
-                continue;
-            }
-            const int groups = (p.rows * p.rpr + 3) / 4;
-            p.cha = odd_quads(groups * 48);
-            p.chx = odd_quads(lines * p.xp);
-            const long long chunk = (long long)CO * p.cha + (long long)CI * p.chx;
-            if (chunk > 0xffff) break;
-            p.chunks = (g.oh + p.rows - 1) / p.rows;
-            for (p.bufs = 1; p.bufs <= 2; ++p.bufs) {
-                const long long floats = std::max<long long>({p.bufs * chunk, p.q * 16ll * (CI * K * K + 2), CR_PIECES * 64ll * p.waves_a}) + groups * 4 + 16;
-                // LDS in a few even shares of what a compute unit has: layers of different sizes share a launch
-                const unsigned need = (unsigned)(floats * 4);
-                if (need > 156 * 1024) break;
-                p.lds = 156 * 1024;
-                for (int share : {2, 3, 4, 6, 8})
-                    if (need <= (unsigned)(156 / share * 1024)) p.lds = 156 / share * 1024;
-                const int resident = std::max(1, std::min({(int)(156 * 1024 / p.lds), 12 / (K * p.q), 8}));
-                p.us = rows_us(K, S, p, blocks, g.unit, groups, pieces, g.w % 4 || g.ow % 4, resident);
-                p.ok = true;
-                if (!best.ok || p.us < best.us) best = p;
-            }
-        }
-    return best;
-}
-
 size_t cr_align16(size_t b) { return (b + 15) & ~(size_t)15; }
 
 template <int K, int S> const void *rows_fn(int nm, int nn)
@@ -574,7 +480,7 @@ dp_status launch_conv_rows(const Geo &g, const void *x, const void *dy, float *o
     a.partials = static_cast<float *>(ws);
     a.n = g.n; a.cin = g.cin; a.cout = g.cout; a.h = g.h; a.w = g.w; a.oh = g.oh; a.ow = g.ow;
     a.tiles_m = p.tiles_m; a.tiles_n = p.tiles_n; a.ex_per_wg = p.ex_per_wg; a.unit = g.unit; a.q = p.q;
-    a.rows = p.rows; a.chunks = p.chunks; a.rpr = p.rpr; a.xp = p.xp; a.cha = p.cha; a.chx = p.chx; a.bufs = p.bufs; a.waves_a = p.waves_a;
+    a.rows = p.rows; a.chunks = p.chunks; a.rpr = p.rpr; a.xp = p.xp; a.cha = p.cha; a.chx = p.chx; a.bufs = p.bufs; a.tail = p.tail; a.waves_a = p.waves_a;
     a.bias = g.has_bias ? 1 : 0;
     a.narrow = g.w < 4 || g.ow < 4;
     a.ragged = !a.narrow && (g.w % 4 || g.ow % 4);

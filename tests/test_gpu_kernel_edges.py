@@ -413,6 +413,33 @@ def test_conv_f32_raw_rows_kernel_is_as_exact_as_fp32(cin, cout, h, w, k, stride
     assert np.allclose(sq[:2], ref_n2, rtol=2 * bound)
 
 
+# Blocks that are larger than the chunks whose place in LDS they take, several examples per workgroup (the last one of fewer): one channel block and
+# several, a chunk of two rows and of one.  Alone and in a batch call.
+@pytest.mark.parametrize("cin,cout,h,w,n", [(128, 16, 2, 8, 1024), (256, 16, 2, 8, 515), (64, 16, 2, 2, 2049), (128, 9, 2, 7, 1030)])
+@pytest.mark.parametrize("bias", [False, True])
+def test_conv_f32_raw_rows_kernel_where_a_block_is_larger_than_its_chunks(cin, cout, h, w, n, bias):
+    layer, few = Layer("conv", cin, cout, h, w, 5, 5, 1, 2, bias), 7
+    x, dy = _inputs(layer, few, 151, "f32")
+    ref_w, ref_b, ref_n2 = _oracle_grads(layer, x, dy)
+    x, dy, ref_w, ref_b, ref_n2 = (np.resize(v, (n,) + v.shape[1:]) for v in (x, dy, ref_w, ref_b, ref_n2))
+    assert dp.dp_kernel_variant(dp.make_desc(layer, n, "f32"), dp.DP_WS_PER_EXAMPLE_GRAD) == "conv_rows<f32,5x5,16x16,per_example>"
+    gw, gb, sq = _run_per_example(layer, x, dy, "f32")
+    xd, dyd, d = dev(x), dev(dy), dp.make_desc(layer, n, "f32")
+    sizes = [dp.dp_workspace_bytes(d)] * 2
+    wss = [torch.full((b,), 255, dtype=torch.uint8, device="cuda:0") for b in sizes]
+    row, width = (layer.pw + 3) // 4 * 4, (layer.pw + 3) // 4 * 4 + (layer.pb + 3) // 4 * 4
+    g = [torch.full((n, width), float("nan"), dtype=torch.float32, device="cuda:0") for _ in sizes]
+    norms = torch.full((2, n), -1.0, device="cuda:0")
+    batch = dp.LayerBatch([d, d], [t.data_ptr() for t in wss], sizes)
+    dp.dp_per_example_grad_batch(batch, batch.ptrs([xd.data_ptr()] * 2), batch.ptrs([dyd.data_ptr()] * 2), batch.ptrs([t.data_ptr() for t in g]),
+                                 batch.ptrs([t.data_ptr() + 4 * row for t in g]) if bias else None, batch.ptrs([v.data_ptr() for v in norms]), g_stride=width)
+    torch.cuda.synchronize()
+    for got_w, got_b, got_n2 in [(gw, gb, sq)] + [(host(t[:, :layer.pw]), host(t[:, row:row + layer.pb]), host(v)) for t, v in zip(g, norms)]:
+        assert (np.linalg.norm(got_w - ref_w, axis=1) <= F32_TOL * np.linalg.norm(ref_w, axis=1)).all()
+        assert not bias or (np.linalg.norm(got_b - ref_b, axis=1) <= F32_TOL * np.linalg.norm(ref_b, axis=1)).all()
+        assert np.allclose(got_n2, ref_n2, rtol=F32_TOL, atol=0)
+
+
 def test_conv_f32_raw_rows_kernel_takes_every_fp32_number():
     """Numbers that round to infinity as bf16 stay finite, NaNs stay where they are, and the next example is what it was."""
     layer = Layer("conv", 32, 16, 6, 8, 3, 3, 1, 1, False)

@@ -1,5 +1,8 @@
 """CPU-only checks of the host-side planning: which kernel variant every layer of the benchmark's
 ResNet-50 set is sent to, and that the workspace queries are consistent with each other."""
+import os
+import subprocess
+
 import pytest
 
 import paper_2109_12191_amd as dp
@@ -108,3 +111,12 @@ def test_fp32_convolutions_take_the_kernel_that_measured_faster(cin, cout, hw, k
     layer = Layer("conv", cin, cout, *hw, k, k, stride, (k - 1) // 2, bias)
     name = dp.dp_kernel_variant(dp.make_desc(layer, n, "f32"), dp.DP_WS_PER_EXAMPLE_GRAD)
     assert name.startswith("conv_rows<f32" if rows < general else "conv_contract<f32"), name
+
+
+def test_fp32_row_plans_keep_the_table_of_runs_clear_of_chunks_and_epilogue(tmp_path):
+    """A workgroup writes the table once and reads it for every one of its examples, whose epilogues lie where the chunks were."""
+    here, exe = os.path.dirname(os.path.abspath(__file__)), str(tmp_path / "rows_regions")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include", "-I" + os.path.join(here, "..", "paper_2109_12191_amd", "csrc"),
+                    os.path.join(here, "rows_regions.cpp"), "-o", exe], check=True)
+    run = subprocess.run([exe], capture_output=True, text=True)
+    assert run.returncode == 0, run.stdout
