@@ -114,7 +114,9 @@ __device__ __forceinline__ void gn_load(const typename In<BF16>::type *p, float 
 }
 
 // SHIFTED: channels that do not start on 16 bytes (odd maps) are read in the aligned vectors that cover them.  The first and the last
-// of these hold values of the neighbours, which are masked; a last one that reaches beyond the tensor is read value by value.
+// of these hold values of the neighbours, which are masked; a last one that reaches beyond the tensor is read value by value.  The vectors of X
+// and dY have to start at the same value: an example whose two addresses differ modulo 16 (tensors of odd examples, calls by address)
+// is read value by value, a vector placed by the other tensor would lie askew and reach out of its own.
 template <bool BF16, int V, bool SHIFTED = false>
 __device__ __forceinline__ void gn_affine_body(const GnArgs &a, unsigned bid, float *s_dx, float *s_d, float *red)
 {
@@ -132,6 +134,8 @@ __device__ __forceinline__ void gn_affine_body(const GnArgs &a, unsigned bid, fl
     const E *dyg = example_at_uniform<E>(a.dy, a.dy_tab, i, ex) + first;
     // end of the tensor that the example lies in, as far as it is known
     const uintptr_t x_end = reinterpret_cast<uintptr_t>(xg - first) + ex * sizeof(E) * (size_t)(a.x_tab ? 1 : a.n - i);
+    // (the same in every lane of a wave)
+    const bool apart = SHIFTED && ((reinterpret_cast<uintptr_t>(xg) ^ reinterpret_cast<uintptr_t>(dyg)) & 15u) != 0;
     const float k = In<BF16>::ld(xg);
     s_dx += sub * cg;
     s_d += sub * cg;
@@ -158,6 +162,14 @@ __device__ __forceinline__ void gn_affine_body(const GnArgs &a, unsigned bid, fl
                 dx[e] += dv[e] * xs; d1[e] += dv[e]; x1[e] += xs; x2[e] += xs * xs;
             }
         };
+        if (apart) {
+#pragma unroll 1
+            for (int p = tl; p < hw; p += team) {
+                const float xs = In<BF16>::ld(xg + (size_t)cl * hw + p) - k, dv = In<BF16>::ld(dyg + (size_t)cl * hw + p);
+                dx[0] += dv * xs; d1[0] += dv; x1[0] += xs; x2[0] += xs * xs;
+            }
+            nv = 0;
+        }
         constexpr int U = SHIFTED ? 3 : 4;                            // vectors in flight (a fourth costs the kernel a wave per SIMD)
         int p = tl;
         for (; p + (U - 1) * team < nv; p += U * team) {
@@ -182,7 +194,7 @@ __device__ __forceinline__ void gn_affine_body(const GnArgs &a, unsigned bid, fl
         if constexpr (SHIFTED) {
 #pragma unroll 1
             for (int edge = 0; edge < 2; ++edge) {
-                if (tl != (edge ? team - 1 : 0)) continue;
+                if (apart || tl != (edge ? team - 1 : 0)) continue;
                 const int e0 = edge ? last * V - off : -off;          // the channel's value that the vector starts at
                 const E *xe = xc + (off - V) + e0, *de = dc + (off - V) + e0;
                 float xv[V], dv[V];

@@ -150,6 +150,34 @@ def test_groupnorm_channels_that_start_anywhere(c, hw, groups, n):
     assert np.allclose(host(sq), ref_n2, rtol=F32_TOL, atol=0)
 
 
+@pytest.mark.parametrize("c,hw,groups,n", [(9, 7, 3, 9), (4, 5, 4, 11), (12, 13, 2, 5), (70, 9, 7, 3), (7, 6, 7, 7)])
+def test_groupnorm_examples_whose_two_addresses_differ(c, hw, groups, n):
+    """bf16 by address: X in a tensor per example, dY in one tensor whose examples start anywhere, and the other way round.  Waves of a
+    workgroup have examples of both kinds."""
+    layer = gn_affine(c, hw, groups)
+    x, dy = _inputs(layer, n, 118, "bf16")
+    x = to_bf16_grid(x * 1.5 + 0.25)
+    ref_w, ref_b, ref_n2 = _oracle_grads(layer, x, dy)
+    d = dp.make_desc(layer, n, "bf16")
+    together = [dev(a, "bf16") for a in (x, dy)]
+    each = [[t[i].clone() for i in range(n)] for t in together]
+    tables = [[_addresses([t], n, 2 * t[0].numel()), _addresses(e, 1, 2 * t[0].numel())] for t, e in zip(together, each)]
+    assert any((a ^ b) & 15 for a, b in zip(tables[0][0].tolist(), tables[0][1].tolist()))
+    off_b = (c + 3) // 4 * 4
+    width = 2 * off_b
+    for kx, kd in ((0, 1), (1, 0), (0, 0)):
+        need = dp.dp_workspace_bytes(d)
+        ws = torch.empty(max(16, need), dtype=torch.uint8, device="cuda:0")
+        g, sq = torch.full((n, width), 7.0, device="cuda:0"), torch.full((n,), -1.0, device="cuda:0")
+        batch = dp.LayerBatch([d], [ws.data_ptr()], [ws.numel()])
+        dp.dp_per_example_grad_batch(batch, batch.ptrs([tables[0][kx].data_ptr()]), batch.ptrs([tables[1][kd].data_ptr()]), batch.ptrs([g.data_ptr()]),
+                                     batch.ptrs([g.data_ptr() + 4 * off_b]), batch.ptrs([sq.data_ptr()]), g_stride=width, addresses=True)
+        torch.cuda.synchronize()
+        assert_close(host(g[:, :c]), ref_w, F32_TOL, "dgamma")
+        assert_close(host(g[:, off_b:off_b + c]), ref_b, F32_TOL, "dbeta")
+        assert np.allclose(host(sq), ref_n2, rtol=F32_TOL, atol=0)
+
+
 # Rows that are brought to another length: planes of whole pieces (1x1, 56- and 16-wide), of halves (28) and of neither (14, 7, parity
 # split after it); fewer than 64 positions, one beyond a multiple of 8; strides with and without a remainder; the first convolution.
 _WIDENED = [conv(64, 96, 1, 1, 7), conv(40, 33, 1, 1, 9), conv(33, 64, 1, 1, 13), conv(48, 80, 1, 2, 13), conv(32, 36, 1, 2, 26), conv(64, 64, 3, 1, 5),
