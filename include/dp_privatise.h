@@ -122,7 +122,8 @@ size_t dp_workspace_bytes(const dp_layer_desc *desc /*[host]*/, int use /*dp_ws_
 #define DP_VARIANT_MATERIALISE 4   /* or-ed into DP_WS_PER_EXAMPLE_GRAD: the variant of a call that stores the gradients
                                       (g_w given); without it the norm-only call, which may take another route */
 #define DP_RECOMPUTE_BLOCKS 8         /* or-ed into DP_WS_RECOMPUTE, for dp_workspace_bytes and dp_kernel_variant: the call that scales
-                                      finished blocks (dp_clip_accumulate_recompute_blocks_batch_at); 0 and "" for a layer without it */
+                                      finished blocks (dp_clip_accumulate_recompute_blocks_batch_at); 0 and "" for a layer without it.
+                                      Into DP_WS_PER_EXAMPLE_GRAD: dp_per_example_grad_blocks_batch_at (every layer has it) */
 const char *dp_kernel_variant(const dp_layer_desc *desc /*[host]*/, int use /*dp_ws_use*/);
 
 /* H1 (+ the layer's share of H2): per-example weight gradients of one layer
@@ -257,6 +258,13 @@ dp_status dp_clip_accumulate_recompute_batch_at(const dp_layer_desc *descs, cons
                                                 const float *const *sqnorm, const float *clip_c, float *const *acc_w,
                                                 float *const *acc_b, void *const *ws, const size_t *ws_bytes, int n_layers,
                                                 dp_stream stream);
+/* dp_per_example_grad_batch_at with norms as precise as those of stored gradients: a norm-only call takes the sum of the squares of
+ * every example's finished fp32 gradient too, where dp_per_example_grad_batch_at may go by way of Gram matrices (which lose digits where
+ * the sum over the positions cancels).  ws: dp_workspace_bytes(desc, DP_WS_PER_EXAMPLE_GRAD | DP_RECOMPUTE_BLOCKS).              */
+dp_status dp_per_example_grad_blocks_batch_at(const dp_layer_desc *descs, const uint64_t *const *x, const uint64_t *const *dy,
+                                              float *const *g_w, float *const *g_b, size_t g_stride, float *const *sqnorm,
+                                              void *const *ws, const size_t *ws_bytes, int32_t *partial_counts, int n_layers,
+                                              dp_stream stream);
 /* The recomputing form as precise as the materialised one: every example's gradient is a finished fp32 block before its factor meets
  * it, nothing is rounded to 16 bits again.  Layers: fp32 ones, dense, GroupNorm; bf16 convolutions without bias on maps of at most
  * 64 output positions whose rewritten operands take at most 64 MB, and 1x1 stride-1 ones on larger maps of even size.  Others:

@@ -71,6 +71,7 @@ def load_library():
         "dp_layer_norms_from_partials": (it, [vp, vp, vp, it, it, vp]),
         "dp_clip_accumulate_recompute_batch": (it, [vp, vp, vp, vp, vp, vp, vp, vp, vp, it, vp]),
         "dp_example_addresses": (it, [vp, vp, it, it, it, vp, vp]),
+        "dp_per_example_grad_blocks_batch_at": (it, [vp, vp, vp, vp, vp, sz, vp, vp, vp, vp, it, vp]),
         "dp_per_example_grad_batch_at": (it, [vp, vp, vp, vp, vp, sz, vp, vp, vp, vp, it, vp]),
         "dp_clip_accumulate_recompute_batch_at": (it, [vp, vp, vp, vp, vp, vp, vp, vp, vp, it, vp]),
         "dp_clip_accumulate_recompute_blocks_batch_at": (it, [vp, vp, vp, vp, vp, vp, vp, vp, vp, it, vp]),
@@ -102,7 +103,7 @@ EXPORTED = ("dp_group_clip_bounds", "dp_weight_count", "dp_bias_count", "dp_work
             "dp_unit_workspace_bytes", "dp_unit_grad", "dp_unit_grad_batch",
             "dp_norm_partial_count", "dp_per_example_grad_partials", "dp_norms_from_partials",
             "dp_per_example_grad_batch", "dp_layer_norms_from_partials", "dp_clip_accumulate_recompute_batch",
-            "dp_example_addresses", "dp_per_example_grad_batch_at", "dp_clip_accumulate_recompute_batch_at", "dp_clip_accumulate_recompute_blocks_batch_at", "dp_unit_grad_batch_at",
+            "dp_example_addresses", "dp_per_example_grad_batch_at", "dp_per_example_grad_blocks_batch_at", "dp_clip_accumulate_recompute_batch_at", "dp_clip_accumulate_recompute_blocks_batch_at", "dp_unit_grad_batch_at",
             "dp_clip_accumulate_columns",
             "dp_clip_factors", "dp_clip_accumulate", "dp_clip_accumulate_segments", "dp_clip_accumulate_recompute", "dp_add_noise_finalize", "dp_add_noise_finalize_update", "dp_add_example_noise",
             "dp_add_noise_finalize_flat", "dp_philox_raw", "dp_profile_next_contraction", "dp_last_error", "dp_version")
@@ -229,8 +230,8 @@ def dp_unit_grad(desc: LayerDesc, clip_unit: int, x, dy, g_w, g_b, sqnorm, ws, g
 
 class LayerBatch:
     """Host arrays for the batch calls over a fixed set of layers: descriptors, workspaces, and (re)settable
-    pointer arrays.  Pointers are plain integers (device addresses); None becomes NULL.  scale_blocks: the recomputing clipped sum (of
-    example addresses) scales finished blocks."""
+    pointer arrays.  Pointers are plain integers (device addresses); None becomes NULL.  scale_blocks: the calls on example addresses
+    work on finished blocks (sums of squares as norms, clipped sums that scale blocks)."""
 
     def __init__(self, descs, ws_ptrs, ws_bytes, scale_blocks: bool = False):
         self.scale_blocks = scale_blocks
@@ -272,7 +273,8 @@ def dp_per_example_grad_batch(batch: "LayerBatch", x, dy, g_w, g_b, sqnorm, g_st
     same or None (sqnorm None: the per-layer reduction is left to dp_layer_norms_from_partials).  batch.partial_counts receives
     the number of partial sums per example each layer left at the start of its workspace."""
     lib = load_library()
-    _check((lib.dp_per_example_grad_batch_at if addresses else lib.dp_per_example_grad_batch)(
+    _check((lib.dp_per_example_grad_blocks_batch_at if addresses and batch.scale_blocks else
+            lib.dp_per_example_grad_batch_at if addresses else lib.dp_per_example_grad_batch)(
         batch.descs, x, dy, g_w, g_b, g_stride, sqnorm, batch.ws, batch.ws_bytes, batch.partial_counts, batch.n_layers, _stream(stream)))
 
 

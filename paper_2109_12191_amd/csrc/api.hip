@@ -179,7 +179,7 @@ static size_t ws_kernels_for(const Geo &g, int mode)
 // finished blocks, GroupNorm's are fp32 throughout.)
 static bool scales_blocks(Geo &g)
 {
-    g.scale_blocks = 1;
+    g.blocks = 1;
     return g.kind != DP_CONV2D || conv_scales_blocks(g);
 }
 
@@ -294,6 +294,9 @@ size_t dp_workspace_bytes(const dp_layer_desc *desc, int use)
             return 0;
         }
         use = DP_WS_RECOMPUTE;
+    } else if (use == (DP_WS_PER_EXAMPLE_GRAD | DP_RECOMPUTE_BLOCKS)) {
+        g.blocks = 1;
+        use = DP_WS_PER_EXAMPLE_GRAD;
     }
     if (use != DP_WS_PER_EXAMPLE_GRAD && use != DP_WS_RECOMPUTE) {
         fail(DP_ERR_INVALID_ARG, "unknown workspace use %d", use);
@@ -307,7 +310,10 @@ const char *dp_kernel_variant(const dp_layer_desc *desc, int use)
     Geo g;
     if (make_geo(desc, g) != DP_OK) return "";
     const bool shared = (use & DP_VARIANT_SHARED) != 0, stored = (use & DP_VARIANT_MATERIALISE) != 0;
-    if ((use & DP_RECOMPUTE_BLOCKS) && (!(use & DP_WS_RECOMPUTE) || !scales_blocks(g))) return "";
+    if (use & DP_RECOMPUTE_BLOCKS) {
+        g.blocks = 1;
+        if ((use & DP_WS_RECOMPUTE) && !scales_blocks(g)) return "";
+    }
     use &= ~(DP_VARIANT_SHARED | DP_VARIANT_MATERIALISE | DP_RECOMPUTE_BLOCKS);
     const int mode = use == DP_WS_RECOMPUTE ? MODE_WEIGHTED : (stored ? MODE_MATERIALISE : MODE_NORM);
     if (g.kind == DP_CONV2D) return conv_variant_name(g, mode, shared);
@@ -463,7 +469,7 @@ static int batch_target(const std::vector<Geo> &geo)
 }
 
 // addresses: x[l], dy[l] are arrays of example addresses
-static dp_status per_example_grad_batch(bool addresses, const dp_layer_desc *descs, const void *const *x, const void *const *dy,
+static dp_status per_example_grad_batch(bool addresses, bool blocks, const dp_layer_desc *descs, const void *const *x, const void *const *dy,
                                         float *const *g_w, float *const *g_b, size_t g_stride, float *const *sqnorm,
                                         void *const *ws, const size_t *ws_bytes, int32_t *partial_counts, int n_layers,
                                         dp_stream stream)
@@ -477,6 +483,7 @@ static dp_status per_example_grad_batch(bool addresses, const dp_layer_desc *des
     for (int l = 0; l < n_layers; ++l) {             // everything is validated before anything is launched
         Geo &g = geo[(size_t)l];
         DP_TRY(make_geo(&descs[l], g));
+        g.blocks = blocks;
         if (addresses) DP_TRY(read_addresses(g));
         if (g.n != geo[0].n) return fail(DP_ERR_INVALID_ARG, "layer %d: n = %d differs from layer 0's %d", l, g.n, geo[0].n);
         DP_TRY(check_ptr(x[l], "x[l]", true, addresses ? 8 : 16));       // (arrays of addresses are read word by word)
@@ -526,7 +533,7 @@ dp_status dp_per_example_grad_batch(const dp_layer_desc *descs, const void *cons
                                     void *const *ws, const size_t *ws_bytes, int32_t *partial_counts, int n_layers,
                                     dp_stream stream)
 {
-    return per_example_grad_batch(false, descs, x, dy, g_w, g_b, g_stride, sqnorm, ws, ws_bytes, partial_counts, n_layers, stream);
+    return per_example_grad_batch(false, false, descs, x, dy, g_w, g_b, g_stride, sqnorm, ws, ws_bytes, partial_counts, n_layers, stream);
 }
 
 dp_status dp_per_example_grad_batch_at(const dp_layer_desc *descs, const uint64_t *const *x, const uint64_t *const *dy,
@@ -534,7 +541,16 @@ dp_status dp_per_example_grad_batch_at(const dp_layer_desc *descs, const uint64_
                                        void *const *ws, const size_t *ws_bytes, int32_t *partial_counts, int n_layers,
                                        dp_stream stream)
 {
-    return per_example_grad_batch(true, descs, reinterpret_cast<const void *const *>(x), reinterpret_cast<const void *const *>(dy), g_w, g_b,
+    return per_example_grad_batch(true, false, descs, reinterpret_cast<const void *const *>(x), reinterpret_cast<const void *const *>(dy), g_w, g_b,
+                                  g_stride, sqnorm, ws, ws_bytes, partial_counts, n_layers, stream);
+}
+
+dp_status dp_per_example_grad_blocks_batch_at(const dp_layer_desc *descs, const uint64_t *const *x, const uint64_t *const *dy,
+                                              float *const *g_w, float *const *g_b, size_t g_stride, float *const *sqnorm,
+                                              void *const *ws, const size_t *ws_bytes, int32_t *partial_counts, int n_layers,
+                                              dp_stream stream)
+{
+    return per_example_grad_batch(true, true, descs, reinterpret_cast<const void *const *>(x), reinterpret_cast<const void *const *>(dy), g_w, g_b,
                                   g_stride, sqnorm, ws, ws_bytes, partial_counts, n_layers, stream);
 }
 
@@ -653,7 +669,7 @@ dp_status dp_layer_norms_from_partials(const float *const *partials, const int32
     return launch_layer_norms(partials, counts, sqnorm, n_layers, n, static_cast<hipStream_t>(stream));
 }
 
-static dp_status recompute_batch(bool addresses, bool f32, const dp_layer_desc *descs, const void *const *x, const void *const *dy,
+static dp_status recompute_batch(bool addresses, bool blocks, const dp_layer_desc *descs, const void *const *x, const void *const *dy,
                                  const float *const *sqnorm, const float *clip_c, float *const *acc_w, float *const *acc_b,
                                  void *const *ws, const size_t *ws_bytes, int n_layers, dp_stream stream)
 {
@@ -664,7 +680,7 @@ static dp_status recompute_batch(bool addresses, bool f32, const dp_layer_desc *
     for (int l = 0; l < n_layers; ++l) {
         Geo &g = geo[(size_t)l];
         DP_TRY(make_geo(&descs[l], g));
-        if (f32 && !scales_blocks(g)) return fail(DP_ERR_UNSUPPORTED, "layer %d: no kernel scales its finished blocks", l);
+        if (blocks && !scales_blocks(g)) return fail(DP_ERR_UNSUPPORTED, "layer %d: no kernel scales its finished blocks", l);
         if (addresses) DP_TRY(read_addresses(g));
         DP_TRY(check_ptr(x[l], "x[l]", true, addresses ? 8 : 16));       // (arrays of addresses are read word by word)
         DP_TRY(check_ptr(dy[l], "dy[l]", true, addresses ? 8 : 16));

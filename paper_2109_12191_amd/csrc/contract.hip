@@ -1700,7 +1700,7 @@ static void packed_geometry(const Geo &g, const PackPlan &pp, Geo &g2)
 // the packed tensors (example ranges as its "examples", im2col rows as its input channels).
 static bool packed_weighted(const Geo &g, int mode, PackPlan &pp, Geo &g2)
 {
-    if (mode != MODE_WEIGHTED || !g.bf16 || g.scale_blocks) return false;
+    if (mode != MODE_WEIGHTED || !g.bf16 || g.blocks) return false;
     // a 1x1 stride-1 layer with even S is already K-contiguous and dword aligned: the aligned loader reads it
     // in place and scales dY while staging, which beats packing it first (measured)
     if (g.kh == 1 && g.kw == 1 && g.stride == 1 && g.pad == 0 && (g.oh * g.ow) % 2 == 0) return false;
@@ -1723,14 +1723,14 @@ static bool packed_weighted(const Geo &g, int mode, PackPlan &pp, Geo &g2)
     return true;
 }
 
-// The clip-weighted contraction whose factors meet the finished fp32 block of an example (Geo::scale_blocks) on small maps: the operands
+// The clip-weighted contraction whose factors meet the finished fp32 block of an example (Geo::blocks) on small maps: the operands
 // are rewritten as they are, a chunk of 64 K values per example and row, and the LDS-direct kernel runs on `g2` with the examples
 // as examples.  It is the slower of the two packed forms where both may be used (a third of the K values are padding on 7 x 7 maps, and
 // every chunk ends with multiply-adds of whole blocks: ResNet-50 step of 8 x 32 examples 7427 -> 7803 us), but it rounds nothing, so
 // that it can stand in for stored gradients.
 static bool packed_blocks(const Geo &g, int mode, PackPlan &pp, Geo &g2)
 {
-    if (mode != MODE_WEIGHTED || !g.scale_blocks || !g.bf16 || g.has_bias || flat_direct(g) || g.oh * g.ow > 64) return false;
+    if (mode != MODE_WEIGHTED || !g.blocks || !g.bf16 || g.has_bias || flat_direct(g) || g.oh * g.ow > 64) return false;
     pp = pack_plan(g, g.n, 64);
     if (pp.x_bytes + pp.dy_bytes > ((size_t)64 << 20)) return false;
     packed_geometry(g, pp, g2);

@@ -810,7 +810,7 @@ void c3_set_forced_crowd(int v) { c3_forced_crowd = v; }
 
 bool conv3x3_applicable(const Geo &g, int mode)
 {
-    if (!g.bf16 || g.has_bias || (mode == MODE_WEIGHTED && g.scale_blocks)) return false;
+    if (!g.bf16 || g.has_bias || (mode == MODE_WEIGHTED && g.blocks)) return false;
     if (g.kh != 3 || g.kw != 3 || g.pad != 1) return false;
     if (g.cin < 64 || g.cout < 64) return false;
     if (g.stride == 1) {

@@ -15,6 +15,11 @@
 // its partial 64x64 Gram (accumulator register layout) in the workspace.  Kernel 2: one
 // workgroup per example adds the slices in order, multiplies the Grams element by element and
 // reduces.  Fixed order everywhere: same bits on every run.
+//
+// How exact it is depends on the operands: the sum is of products of either sign, and what fp32 rounds off counts against the products.  Where these
+// cancel (X nearly constant over the positions and dY centred: 512 -> 2048 on 7 x 7, X = 1 + 1 % noise) the squared norm is good to 4e-4,
+// where a sum of squares is to 4e-7.  A gradient that cancels altogether may even come out negative: clip_factor leaves such an example out; raised
+// to zero it would pass unclipped.  Calls that stand in for stored gradients ask for sums of squares (Geo::blocks).
 #include "group.h"
 #include "internal.h"
 #include "pieces.h"
@@ -207,7 +212,7 @@ size_t gram_align16(size_t b) { return (b + 15) & ~(size_t)15; }
 bool gram_norm_applicable(const Geo &g, int mode)
 {
     if (g.unit > 1) return false;                    // (the Gram identity is for one example)
-    if (mode != MODE_NORM || !g.bf16 || g.has_bias) return false;
+    if (mode != MODE_NORM || !g.bf16 || g.has_bias || g.blocks) return false;
     const bool one = g.kh == 1 && g.kw == 1 && g.stride == 1 && g.pad == 0;
     const bool three = g.kh == 3 && g.kw == 3 && g.pad == 1 && (g.stride == 1 || g.stride == 2);
     if (!one && !three) return false;

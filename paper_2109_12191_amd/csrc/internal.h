@@ -35,8 +35,9 @@ struct Geo {
     // Per-example calls of convolutions: consecutive examples whose gradients are added up to one row of results (clipping units; K
     // then runs over the positions of all of them).  1 otherwise; n is a multiple of it.
     int unit;
-    // Clip-weighted calls of bf16 layers: the factors meet finished fp32 blocks (conv_scales_blocks), never an operand that is rounded again.
-    int scale_blocks;
+    // Calls of bf16 layers on finished fp32 blocks.  Clip-weighted ones: the factors meet those (conv_scales_blocks), never an operand that is
+    // rounded again.  Per-example ones: a squared norm is a sum of squares, never one of products that may cancel (gram.hip).
+    int blocks;
 };
 
 // Contraction modes of the conv / dense kernels.

@@ -86,7 +86,7 @@ class _Plan:
         self.rows = self.n // ps.clip_unit
         self.layers = ps.layers
         self.form = ps._forms(tensors)
-        self.recompute_use = ps._recompute_use(tensors)
+        self.blocks = ps._blocks(tensors)
         L = len(self.layers)
         self.descs, need = ps._workspaces(tensors)
         self.g = [st.g[: self.rows] if st.g is not None else None for st in stores]
@@ -115,9 +115,9 @@ class _Plan:
             self.ws.append(where)
         # Layers that run the same kernel variant go to the library in ONE batch call, which puts them into one
         # launch (at most 16 per launch): per phase a micro-step is a dozen launches, not a hundred.
-        self.variant = [(B.dp_kernel_variant(d, B.DP_WS_PER_EXAMPLE_GRAD | B.DP_VARIANT_SHARED |
+        self.variant = [(B.dp_kernel_variant(d, B.DP_WS_PER_EXAMPLE_GRAD | self.blocks | B.DP_VARIANT_SHARED |
                                              (B.DP_VARIANT_MATERIALISE if form == "materialise" else 0)),
-                         B.dp_kernel_variant(d, self.recompute_use | B.DP_VARIANT_SHARED) if form == "recompute" else "")
+                         B.dp_kernel_variant(d, B.DP_WS_RECOMPUTE | self.blocks | B.DP_VARIANT_SHARED) if form == "recompute" else "")
                         for d, form in zip(self.descs, self.form)]
         self.partials = [B.PartialTable(self.ws[c], [1] * L, ps.group_of_layer)
                          for c in range(len(stores))]
@@ -149,11 +149,11 @@ class _Plan:
                 part = ids[k: k + width]
                 name = key.split("|")[0]
                 if len(part) == 1:           # a single layer is planned as a launch of its own
-                    name = B.dp_kernel_variant(self.descs[part[0]], self.recompute_use if use == 1 else (
-                        B.DP_WS_PER_EXAMPLE_GRAD | (B.DP_VARIANT_MATERIALISE if self.form[part[0]] == "materialise" else 0)))
+                    name = B.dp_kernel_variant(self.descs[part[0]], self.blocks | (B.DP_WS_RECOMPUTE if use == 1 else (
+                        B.DP_WS_PER_EXAMPLE_GRAD | (B.DP_VARIANT_MATERIALISE if self.form[part[0]] == "materialise" else 0))))
                 g = dict(layers=part, name=name, conv=all(self.layers[i].kind == "conv" for i in part))
                 g["batch"] = [B.LayerBatch([self.descs[i] for i in part], [self.ws[c][i] for i in part],
-                                           [self.ws_bytes[i] for i in part], bool(self.recompute_use & B.DP_RECOMPUTE_BLOCKS))
+                                           [self.ws_bytes[i] for i in part], bool(self.blocks))
                               for c in range(len(self.stores))]
                 if use == 2:
                     g["usq"] = [g["batch"][c].ptrs([self.layer_sqnorm[c][i].data_ptr() for i in part])
@@ -345,28 +345,29 @@ class PrivatiseStep:
     def _forms(self, tensors: int) -> List[str]:
         """Form of every layer's clipped sum in a phase of `tensors` micro-steps: that of a micro-step, except that a phase of many
         one- or two-example micro-steps (which store every gradient) recomputes what a micro-step of that many examples would, where
-        finished fp32 blocks are scaled (how many micro-steps share a phase must not decide about precision) and the workspaces
+        finished fp32 blocks are squared and scaled (how many micro-steps share a phase must not decide about precision) and the workspaces
         fit where the gradients would have been.  Stored, a layer's gradients cross memory twice; ResNet-50, us per step, every
-        gradient stored / this: 3 x 1 364 / 310, 8 x 1 697 / 485, 64 x 1 4080 / 2228; 2 x 2 at 192 x 192, one stream 536 / 458."""
+        gradient stored / this: 3 x 1 361 / 320, 8 x 1 693 / 515, 64 x 1 4099 / 2454; 16 x 2 at 192 x 192 2534 / 1253."""
         n = self.wl.n * tensors
         if (tensors == 1 or self._mode != "auto" or self.wl.n > 2 or self.clip_unit > 1 or
                 any(p % 4 for p in self.pw + self.pb)):         # (zeros between tensors have a place of their own in the matrix)
             return self.form
         if tensors not in self._phase_forms:
-            use, over = B.DP_WS_RECOMPUTE | B.DP_RECOMPUTE_BLOCKS, {}       # layer -> workspace less its part of the matrix
+            norms, sums = (use | B.DP_RECOMPUTE_BLOCKS for use in (B.DP_WS_PER_EXAMPLE_GRAD, B.DP_WS_RECOMPUTE))
+            over = {}                            # layer -> workspace less its part of the matrix
             for i, l in enumerate(self.layers):
                 d = B.make_desc(l, n, self.wl.dtype)
-                if self._choose(l, "auto", n) == "recompute" and B.dp_kernel_variant(d, use):
-                    need = max(B.dp_workspace_bytes(d, B.DP_WS_PER_EXAMPLE_GRAD), B.dp_workspace_bytes(d, use), 16)
+                if self._choose(l, "auto", n) == "recompute" and B.dp_kernel_variant(d, sums):
+                    need = max(B.dp_workspace_bytes(d, norms), B.dp_workspace_bytes(d, sums), 16)
                     over[i] = _align256(need) - 4 * n * (self.pw[i] + self.pb[i])
             while over and sum(over.values()) + 256 > 0:
                 del over[max(over, key=over.get)]
             self._phase_forms[tensors] = ["recompute" if i in over else form for i, form in enumerate(self.form)] if over else self.form
         return self._phase_forms[tensors]
 
-    def _recompute_use(self, tensors: int) -> int:
-        """Which clipped sum the recomputing layers of a phase run."""
-        return B.DP_WS_RECOMPUTE | (B.DP_RECOMPUTE_BLOCKS if self._forms(tensors) is not self.form else 0)
+    def _blocks(self, tensors: int) -> int:
+        """Or-ed into the uses of a phase's calls: whether it works on finished blocks."""
+        return B.DP_RECOMPUTE_BLOCKS if self._forms(tensors) is not self.form else 0
 
     def _in_matrix(self, tensors: int) -> List[bool]:
         """Layers whose workspace lies in the gradient matrix: those that do not use their columns of it in such a phase and need
@@ -375,7 +376,7 @@ class PrivatiseStep:
             return [False] * len(self.layers)
         if tensors not in self._inside:
             descs, need = self._workspaces(tensors)
-            self._inside[tensors] = [now != form and b > max(16, B.dp_workspace_bytes(d, B.DP_WS_PER_EXAMPLE_GRAD))
+            self._inside[tensors] = [now != form and b > max(16, B.dp_workspace_bytes(d, B.DP_WS_PER_EXAMPLE_GRAD | B.DP_RECOMPUTE_BLOCKS))
                                      for d, b, now, form in zip(descs, need, self._forms(tensors), self.form)]
         return self._inside[tensors]
 
@@ -400,8 +401,9 @@ class PrivatiseStep:
         """Descriptors and workspace bytes of every layer in a phase of `tensors` micro-steps."""
         if tensors not in self._needs:
             descs = [B.make_desc(l, self.wl.n * tensors, self.wl.dtype) for l in self.layers]
-            need = [max(16, B.dp_workspace_bytes(d, B.DP_WS_PER_EXAMPLE_GRAD),
-                        B.dp_workspace_bytes(d, self._recompute_use(tensors)) if form == "recompute" else 0,
+            blocks = self._blocks(tensors)
+            need = [max(16, B.dp_workspace_bytes(d, B.DP_WS_PER_EXAMPLE_GRAD | blocks),
+                        B.dp_workspace_bytes(d, B.DP_WS_RECOMPUTE | blocks) if form == "recompute" else 0,
                         B.dp_unit_workspace_bytes(d, self.clip_unit) if self.clip_unit > 1 else 0)
                     for d, form in zip(descs, self._forms(tensors))]
             self._needs[tensors] = descs, need
@@ -438,10 +440,11 @@ class PrivatiseStep:
         layer the per-example and the recomputing one."""
         flags = []
         if self.wl.dtype == "bf16":
+            blocks = self._blocks(tensors)
             for d, form in zip(self._workspaces(tensors)[0], self._forms(tensors)):
                 stored = B.DP_VARIANT_MATERIALISE if form == "materialise" else 0
-                flags.append("gather" in B.dp_kernel_variant(d, B.DP_WS_PER_EXAMPLE_GRAD | B.DP_VARIANT_SHARED | stored))
-                flags.append(form == "recompute" and "gather" in B.dp_kernel_variant(d, self._recompute_use(tensors) | B.DP_VARIANT_SHARED))
+                flags.append("gather" in B.dp_kernel_variant(d, B.DP_WS_PER_EXAMPLE_GRAD | blocks | B.DP_VARIANT_SHARED | stored))
+                flags.append(form == "recompute" and "gather" in B.dp_kernel_variant(d, B.DP_WS_RECOMPUTE | blocks | B.DP_VARIANT_SHARED))
         return flags
 
     def _phase_sizes(self, micro_steps: int) -> List[int]:

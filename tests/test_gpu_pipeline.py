@@ -10,7 +10,7 @@ import torch
 import oracle
 import paper_2109_12191_amd as dp
 from gpu_util import BF16_TOL, F32_TOL, assert_close, dev, host
-from workloads import get_workload, make_inputs
+from workloads import Workload, conv, get_workload, make_inputs, to_bf16_grid
 
 pytestmark = pytest.mark.gpu
 
@@ -342,3 +342,33 @@ def test_norms_of_the_last_micro_step(name, n, accum, streams):
         ps.group_sqnorm.zero_()
         ps.replay()
         assert torch.allclose(ps.group_sqnorm, want, rtol=1e-5, atol=0.0)
+
+
+# Squared norms of finished fp32 gradients: 49 exact products per element, whose partial sums are up to 1 / 1 % of the result here, each rounded by
+# 2^-24; errors of elements are as good as independent, and 10^5 of them are squared and added: below 49 * 100 * 2^-24 / sqrt(10^5) = 1e-6, taken
+# ten times.  (By way of Gram matrices: 1e-4 and more.)
+def _centred(layer, n, seed):
+    """X nearly constant over the positions, dY of sum zero over them, on the bf16 grid."""
+    rng = np.random.default_rng(seed)
+    x = to_bf16_grid(1.0 + 0.01 * rng.standard_normal((n,) + tuple(layer.x_shape)).astype(np.float32))
+    dy = rng.integers(-3, 4, (n,) + tuple(layer.dy_shape)).astype(np.float32)
+    dy.reshape(n, layer.cout, -1)[:, :, -1] = -dy.reshape(n, layer.cout, -1)[:, :, :-1].sum(-1)
+    return x, (dy * 2.0 ** -7).astype(np.float32)
+
+
+@pytest.mark.parametrize("n,accum,streams", [(1, 12, 1), (2, 6, 3)])
+def test_norms_do_not_depend_on_how_many_micro_steps_share_a_phase(n, accum, streams):
+    layers = (conv(512, 2048, 1, 1, 7), conv(1024, 1024, 1, 2, 13), conv(512, 256, 3, 1, 7))
+    wl = Workload("centred", layers, n, accum, "bf16", "per_layer", 1.0, 1.0, tuple("normal" for _ in layers), 0.01, 7)
+    ins = [_centred(l, n * accum, 40 + k) for k, l in enumerate(layers)]
+    want = np.stack([[oracle.sqnorm(oracle.example_grad(l, x[i], dy[i])[0]) for i in range(n * accum)] for l, (x, dy) in zip(layers, ins)])
+    steps = [[(dev(x[m * n:(m + 1) * n], "bf16"), dev(dy[m * n:(m + 1) * n], "bf16")) for x, dy in ins] for m in range(accum)]
+    ps = dp.PrivatiseStep(wl, streams=streams)
+    assert ps.micro_steps_per_phase == accum and ps._main.form != ps.form
+    ps.run(steps)
+    together = host(ps._main.group_sqnorm[0])
+    ps.begin_step()
+    for m, inputs in enumerate(steps):
+        ps.micro_step(inputs)
+        for got in (together[:, m * n:(m + 1) * n], host(ps.group_sqnorm)):
+            assert np.allclose(got, want[:, m * n:(m + 1) * n], rtol=1e-5, atol=0), (m, got / want[:, m * n:(m + 1) * n] - 1)
