@@ -76,9 +76,10 @@ class _Store:
 
 class _Plan:
     """Views and batch calls for phases of `n` examples: one micro-step in the caller's tensors (`tensors` = 1), or `tensors`
-    micro-steps through arrays of example addresses.  (Keeps no reference to its PrivatiseStep: the buffers go when that goes.)"""
+    micro-steps through arrays of example addresses.  `only`: per-example calls of these layers and nothing else.  (Keeps no reference to its
+    PrivatiseStep: the buffers go when that goes.)"""
 
-    def __init__(self, ps: "PrivatiseStep", tensors: int, stores: List[_Store]):
+    def __init__(self, ps: "PrivatiseStep", tensors: int, stores: List[_Store], only: Optional[Sequence[int]] = None):
         wl = ps.wl
         self.tensors = tensors
         self.stores = stores                       # the copies that are large enough
@@ -122,9 +123,10 @@ class _Plan:
         self.partials = [B.PartialTable(self.ws[c], [1] * L, ps.group_of_layer)
                          for c in range(len(stores))]
         self.work = ps._work(tensors)
-        self.groups_a = self._make_groups(ps, range(L), 0) if ps.clip_unit == 1 else []
-        self.groups_b = self._make_groups(ps, [i for i in range(L) if self.form[i] == "recompute"], 1)
+        self.groups_a = self._make_groups(ps, range(L) if only is None else only, 0) if ps.clip_unit == 1 else []
+        self.groups_b = self._make_groups(ps, [i for i in range(L) if self.form[i] == "recompute"], 1) if only is None else []
         self.groups_u = self._make_groups(ps, range(L), 2) if ps.clip_unit > 1 else []
+        self.last = ps._last_plan(self.form) if self.form is not ps.form else None
 
     def _make_groups(self, ps: "PrivatiseStep", layer_ids, use: int):
         """Groups of at most 16 layers with the same kernel variant for phase `use` (0: per-example gradients,
@@ -291,6 +293,8 @@ class PrivatiseStep:
         self.group_of_layer_dev = torch.tensor(self.group_of_layer, dtype=torch.int32, device=dev)
         esize = 2 if wl.dtype == "bf16" else 4
         self._example_bytes = [b for l in self.layers for b in (l.x_bytes(esize), l.dy_bytes(esize))]
+        self._last_store = None                  # gradients of a last micro-step that its phase does not store (_last_plan)
+        self._last_plans = {}
         self._phase_forms = {}                   # micro-steps of a phase -> forms of the layers
         self._inside = {}                        # and whose workspaces lie in the gradient matrix
         self._ws_bytes = {}                      # and how much the others take together
@@ -320,7 +324,8 @@ class PrivatiseStep:
         self._last_sqnorm = torch.zeros((self.n_groups, self.rows), dtype=f32, device=dev)
         self._group_sqnorm = [self._last_sqnorm] * self.copies      # of the last micro-steps (one per copy)
         self._last = 0                           # the most recent one
-        self._g_last = None
+        self._g_last = None                      # the stored gradients among them, and the plan that they were stored by
+        self._g_plan = None
         self.graph = None
         self.micro_steps_done = 0
         # Optimiser-step counter: the `step` word of the Philox counters.  The kernels read it from a device
@@ -346,10 +351,11 @@ class PrivatiseStep:
         """Form of every layer's clipped sum in a phase of `tensors` micro-steps: that of a micro-step, except that a phase of many
         one- or two-example micro-steps (which store every gradient) recomputes what a micro-step of that many examples would, where
         finished fp32 blocks are squared and scaled (how many micro-steps share a phase must not decide about precision) and the workspaces
-        fit where the gradients would have been.  Stored, a layer's gradients cross memory twice; ResNet-50, us per step, every
-        gradient stored / this: 3 x 1 361 / 320, 8 x 1 693 / 515, 64 x 1 4099 / 2454; 16 x 2 at 192 x 192 2534 / 1253."""
+        fit where the gradients would have been.  Stored, a layer's gradients cross memory twice; ResNet-50, us per step on four streams, every
+        gradient stored / this: 3 x 1 364 / 362, 4 x 1 425 / 395, 8 x 1 693 / 548, 64 x 1 4099 / 2467; 3 x 2 at 192 x 192 574 / 491.  Not two
+        micro-steps, half of which _last_plan stores all the same: 2 x 2 on one stream 544 / 555, at 192 x 192 532 / 559."""
         n = self.wl.n * tensors
-        if (tensors == 1 or self._mode != "auto" or self.wl.n > 2 or self.clip_unit > 1 or
+        if (tensors < 3 or self._mode != "auto" or self.wl.n > 2 or self.clip_unit > 1 or
                 any(p % 4 for p in self.pw + self.pb)):         # (zeros between tensors have a place of their own in the matrix)
             return self.form
         if tensors not in self._phase_forms:
@@ -470,6 +476,18 @@ class PrivatiseStep:
             self._plans[tensors] = _Plan(self, tensors, stores)
         return self._plans[tensors]
 
+    def _last_plan(self, form: Sequence[str]) -> _Plan:
+        """Stores the gradients of one micro-step's layers that a phase of this form recomputes: whoever looks at `g` after a step finds the last
+        micro-step's whole, as a micro-step of one or two examples leaves it.  Buffers of its own (one matrix of a micro-step beside those of
+        the phase), so that its calls run beside the clipped sum: on the main stream, which has nothing else to do then (ResNet-50, 64 x 1 on four
+        streams: 2454 us without them, 2467 so, 2735 on the streams of the per-example phase; 8 x 1 515, 548, 728)."""
+        layers = tuple(i for i, f in enumerate(form) if f != self.form[i])
+        if layers not in self._last_plans:
+            if self._last_store is None:
+                self._last_store = _Store(self, self.rows, self._workspace_bytes(1))
+            self._last_plans[layers] = _Plan(self, 1, [self._last_store], layers)
+        return self._last_plans[layers]
+
     # ---- one micro-step
     @property
     def descs(self):
@@ -540,15 +558,15 @@ class PrivatiseStep:
 
     @property
     def g(self) -> Optional[torch.Tensor]:
-        """[rows, p_mat] stored gradients of the most recent micro-step, columns as in the accumulator (no numbers where the phase that
-        it was part of stored none)."""
-        if self._g_last is None or self._g_last.shape[1] == self.p_mat:
+        """[rows, p_mat] stored gradients of the most recent micro-step, columns as in the accumulator."""
+        plan = self._g_plan
+        if self._g_last is None or plan.last is None:
             return self._g_last
-        plan, out = self._sum_plan, torch.full((self.rows, self.p_mat), float("nan"), dtype=torch.float32, device=self.device)
-        for i, form in enumerate(plan.form):
-            if form == "materialise":
-                for to, at, size in ((self.off_w[i], plan.off_w[i], self.pw[i]), (self.off_b[i], plan.off_b[i], self.pb[i])):
-                    out[:, to: to + size] = self._g_last[:, at: at + size]
+        # the phase stored some of the columns side by side, the others lie in a matrix of their own already
+        out = self._last_store.g
+        if plan.p_mat:
+            for at, to, end in zip(plan.segments.begin, plan.segments.place, [*plan.segments.begin[1:], plan.p_mat]):
+                out[:, to: to + end - at] = self._g_last[:, at: end]
         return out
 
     def enable_update(self, lr: float, momentum: float = 0.0, theta: Optional[torch.Tensor] = None,
@@ -671,6 +689,12 @@ class PrivatiseStep:
                 ev.record(st)
                 evs.append(ev)
             store.done = evs
+        if ends_step and plan.last is not None:
+            skip = 8 * (plan.n - self.n)           # entries of the tables before the last micro-step's examples
+            for grp in plan.last.groups_a:
+                bt = grp["batch"][0]
+                B.dp_per_example_grad_batch(bt, bt.fill("x", [x[i] + skip for i in grp["layers"]]), bt.fill("dy", [dy[i] + skip for i in grp["layers"]]),
+                                            grp["gw"][0], grp["gb"][0], None, g_stride=self.p_mat, stream=ms, addresses=True)
         for k in range(max(0, plan.tensors - self.copies), plan.tensors):
             self._last = (self.micro_steps_done + k) % self.copies
             self._group_sqnorm[self._last] = gsq[:, k * self.rows:(k + 1) * self.rows]
@@ -678,7 +702,7 @@ class PrivatiseStep:
         if ends_step and not self._group_sqnorm[self._last].is_contiguous():
             self._last_sqnorm.copy_(self._group_sqnorm[self._last])
             self._group_sqnorm[self._last] = self._last_sqnorm
-        self._g_last = g_buf[-self.rows:] if g_buf is not None else None
+        self._g_last, self._g_plan = g_buf[-self.rows:] if g_buf is not None else None, plan
         self.micro_steps_done += plan.tensors
         self._phases += 1
 

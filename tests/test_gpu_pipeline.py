@@ -372,3 +372,36 @@ def test_norms_do_not_depend_on_how_many_micro_steps_share_a_phase(n, accum, str
         ps.micro_step(inputs)
         for got in (together[:, m * n:(m + 1) * n], host(ps.group_sqnorm)):
             assert np.allclose(got, want[:, m * n:(m + 1) * n], rtol=1e-5, atol=0), (m, got / want[:, m * n:(m + 1) * n] - 1)
+
+
+@pytest.mark.parametrize("n,accum,streams,layers", [(1, 8, 1, None), (1, 8, 4, None), (2, 5, 4, None),
+                                                    (1, 12, 3, (conv(512, 2048, 1, 1, 7), conv(1024, 1024, 1, 2, 13), conv(512, 256, 3, 1, 7)))])
+def test_stored_gradients_of_the_last_micro_step(n, accum, streams, layers):
+    """g after a step whose micro-steps were issued together, some layers (or all) recomputed: every column, as the micro-step by itself stores it,
+    eager and replayed, before and after the next step begins."""
+    wl = get_workload("resnet50_nano", n=n, accum=accum, hw=64)
+    if layers:
+        wl = Workload("all recomputed", layers, n, accum, "bf16", "per_layer", 1.0, 1.0, tuple("normal" for _ in layers), 0.01, 7)
+    steps = [[(dev(x, wl.dtype), dev(dy, wl.dtype)) for x, dy in make_inputs(wl, m)] for m in range(accum)]
+    single, ps = dp.PrivatiseStep(wl), dp.PrivatiseStep(wl, streams=streams)
+    assert ps.micro_steps_per_phase == accum and ps._main.form != ps.form and ("materialise" in ps._main.form) == (layers is None)
+    single.begin_step()
+    for inputs in steps:
+        single.micro_step(inputs)
+    want = single.g.clone()
+    ps.run(steps)
+    for _ in range(2):
+        assert ps.g.shape == want.shape and ps.g.is_contiguous()
+        assert_close(host(ps.g), host(want), F32_TOL, "g")
+        ps.begin_step()
+    ps.capture(steps)
+    for _ in range(3):
+        ps.g.fill_(float("nan"))
+        ps.replay()
+        assert_close(host(ps.g), host(want), F32_TOL, "g, replayed")
+    ps.begin_step()
+    ps.micro_step(steps[0])
+    ps.finalize()
+    single.begin_step()
+    single.micro_step(steps[0])
+    assert torch.equal(ps.g, single.g)

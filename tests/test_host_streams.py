@@ -383,3 +383,28 @@ def test_workspaces_in_the_gradient_matrix_lie_behind_the_stored_columns(order, 
                 k = max(s for s in range(plan.segments.n_seg) if plan.segments.begin[s] <= plan.off_w[i])
                 assert plan.off_w[i] + ps.pw[i] <= ends[k] and plan.segments.group[k] == ps.group_of_layer[i]
                 assert plan.segments.place[k] + plan.off_w[i] - plan.segments.begin[k] == ps.off_w[i]
+
+
+@pytest.mark.parametrize("streams,sizes", [(1, [8]), (4, [8]), (4, [5, 4])])
+def test_last_gradients_that_a_phase_does_not_store_are_stored_apart(order, monkeypatch, streams, sizes):
+    """Every layer's gradients of the last micro-step are written once, into a matrix that nothing else of the step uses, and the end of the
+    step waits for them; earlier phases write none."""
+    monkeypatch.setattr(pipeline.PrivatiseStep, "_micro_steps_together", lambda self: sizes[0])
+    wl = get_workload("resnet50_nano", accum=sum(sizes), hw=64)
+    ps = dp.PrivatiseStep(wl, device="cpu", streams=streams)
+    writes, call = [], pipeline.B.dp_per_example_grad_batch
+
+    def seen(bt, x, dy, g_w, *rest, **kw):
+        writes.extend(p for p in _addresses(g_w or []) if p)
+        call(bt, x, dy, g_w, *rest, **kw)
+
+    monkeypatch.setattr(pipeline.B, "dp_per_example_grad_batch", seen)
+    for _ in range(2):
+        del writes[:]
+        ps.run(_steps(wl, sum(sizes)))
+        apart = ps._last_store.g
+        for i, form in enumerate(ps._plan(sizes[-1]).form):
+            assert writes.count(apart.data_ptr() + 4 * ps.off_w[i]) == (form == "recompute")
+        order.call(order.main, [(apart.data_ptr(), apart.data_ptr() + 4 * apart.numel())], what="a reader")
+    assert ps.g.data_ptr() == apart.data_ptr() and ps.g.shape == (1, ps.p_mat)
+    assert not order.clashes and order.ring(order.main) is None
