@@ -1228,6 +1228,12 @@ __global__ void __launch_bounds__(WM * 128, (STAGES * (WM * TM + 2 * TN) * 4 <= 
         }
         if constexpr (WEIGHTED) {
             const float f = group_sqnorm ? clip_factor(group_sqnorm[ex], clip_c) : 1.0f;
+            if (__builtin_expect(f == 0.0f, 0)) {         // an example whose gradient is not finite adds nothing, and no 0 * inf
+#pragma unroll
+                for (int t = 0; t < NACC; ++t)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) acc[t][r] = 0.0f;
+            }
 #pragma unroll
             for (int t = 0; t < NACC; ++t)
 #pragma unroll

@@ -211,6 +211,8 @@ __device__ __forceinline__ void clip_accumulate_body(const float *__restrict__ g
             total[0] = acc[e];
         }
     }
+    // an example whose gradient is not finite has factor 0 and adds nothing: no 0 * inf
+    auto scaled = [](float f, float v) { return f * (f != 0.0f ? v : 0.0f); };
     int left = run;                                   // rows until the run ends (uniform)
     auto row_done = [&]() {
         if (--left == 0) {
@@ -236,18 +238,18 @@ __device__ __forceinline__ void clip_accumulate_body(const float *__restrict__ g
 #pragma unroll
                     for (int u = 0; u < 8; ++u) {    // example order: same bits on every run
                         const float fu = fs[j + u];
-                        s[0] += fu * v[u].x; s[1] += fu * v[u].y; s[2] += fu * v[u].z; s[3] += fu * v[u].w;
+                        s[0] += scaled(fu, v[u].x); s[1] += scaled(fu, v[u].y); s[2] += scaled(fu, v[u].z); s[3] += scaled(fu, v[u].w);
                         row_done();
                     }
                 }
                 for (; j < cnt; ++j) {
                     const float4 a = load_once(row + (size_t)j * stride);
                     const float f0 = fs[j];
-                    s[0] += f0 * a.x; s[1] += f0 * a.y; s[2] += f0 * a.z; s[3] += f0 * a.w;
+                    s[0] += scaled(f0, a.x); s[1] += scaled(f0, a.y); s[2] += scaled(f0, a.z); s[3] += scaled(f0, a.w);
                     row_done();
                 }
             } else {
-                for (; j < cnt; ++j) { s[0] += fs[j] * row[(size_t)j * stride]; row_done(); }
+                for (; j < cnt; ++j) { s[0] += scaled(fs[j], row[(size_t)j * stride]); row_done(); }
             }
         }
     }

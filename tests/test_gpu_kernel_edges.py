@@ -267,6 +267,54 @@ def test_clipped_sum_that_scales_finished_blocks(layer):
                 assert_close(host(acc_b[k])[:l.pb], 0.125 + (f[:, None] * ref_b).sum(axis=0), F32_TOL / 10, f"{l} n={n} bias")
 
 
+@pytest.mark.parametrize("layer", [l for l in _BLOCKS if l.kind == "conv"], ids=str)
+@pytest.mark.parametrize("kind", ["overflow", "infinite", "no number"])
+def test_finished_blocks_of_a_broken_example_add_nothing(layer, kind):
+    """Finite inputs whose gradient does not fit fp32, and inputs that are not finite: norm infinite or no number, factor 0, and the sum is that
+    of the others."""
+    n, bad = 6, 2
+    x, dy = _inputs(layer, n, 123, "bf16")
+    good = [i for i in range(n) if i != bad]
+    ref_w = _oracle_grads(layer, x[good], dy[good])[0]
+    x[bad], dy[bad] = 2.0 ** 127, 2.0 ** 127
+    if kind != "overflow":
+        x[bad, 0], dy[bad, -1] = np.inf if kind == "infinite" else np.nan, -np.inf
+    n2 = (np.random.default_rng(9).uniform(0.4, 2.0, n) ** 2).astype(np.float32)
+    n2[bad] = np.nan if kind == "no number" else np.inf
+    d = dp.make_desc(layer, n, "bf16")
+    ws = torch.empty(max(16, dp.dp_workspace_bytes(d, dp.DP_WS_RECOMPUTE | dp.DP_RECOMPUTE_BLOCKS)), dtype=torch.uint8, device="cuda:0")
+    xd, dyd, n2d, acc = dev(x, "bf16"), dev(dy, "bf16"), dev(n2), torch.full((layer.pw,), 0.125, device="cuda:0")
+    tables = [_addresses([t], n, 2 * t[0].numel()) for t in (xd, dyd)]
+    batch = dp.LayerBatch([d], [ws.data_ptr()], [ws.numel()], scale_blocks=True)
+    dp.dp_clip_accumulate_recompute_batch(batch, batch.ptrs([tables[0].data_ptr()]), batch.ptrs([tables[1].data_ptr()]), batch.ptrs([n2d.data_ptr()]),
+                                          batch.floats([1.0]), batch.ptrs([acc.data_ptr()]), None, addresses=True)
+    torch.cuda.synchronize()
+    f = np.array([oracle.clip_factor(float(n2[i]), 1.0) for i in good])
+    assert_close(host(acc), 0.125 + (f[:, None] * ref_w).sum(axis=0), F32_TOL / 10, "sum of the others")
+
+
+# one value at a time (an odd number of columns); eight rows at a time and those that are left; several passes over the factors
+@pytest.mark.parametrize("n,p", [(5, 7), (8, 64), (21, 4100), (1030, 12)])
+def test_stored_clipped_sum_leaves_out_rows_that_are_not_finite(n, p):
+    rng = np.random.default_rng(11)
+    g, n2 = rng.standard_normal((n, p)).astype(np.float32), (rng.uniform(0.4, 2.0, n) ** 2).astype(np.float32)
+    f = np.array([oracle.clip_factor(float(v), 1.0) for v in n2])
+    for i, (value, norm) in {1: (np.inf, np.inf), 3: (np.nan, np.nan), n - 1: (-np.inf, -1.0)}.items():
+        g[i, ::3], n2[i], f[i] = value, norm, 0.0
+    want = 0.5 + (f[:, None] * np.where(f[:, None] > 0, g, 0.0)).sum(0)
+    stride = (p + 3) // 4 * 4 if p > 7 else p
+    gd = torch.zeros((n, stride), device="cuda:0")
+    gd[:, :p] = dev(g)
+    n2d, acc = dev(n2), torch.full((stride,), 0.5, device="cuda:0")
+    dp.dp_clip_accumulate(gd, n2d, 1.0, n, p, acc, g_stride=stride)
+    assert_close(host(acc[:p]), want, F32_TOL, "one group")
+    if p % 4 == 0:
+        acc.fill_(0.5)
+        table = dp.SegmentTable([0, p // 8 * 4], [0, 0], [1.0, 1.0])
+        dp.dp_clip_accumulate_segments(gd, n2d, 1, table, n, p, acc, g_stride=stride)
+        assert_close(host(acc[:p]), want, F32_TOL, "segments")
+
+
 def test_layers_that_cannot_scale_finished_blocks_are_refused():
     use = dp.DP_WS_RECOMPUTE | dp.DP_RECOMPUTE_BLOCKS
     for layer in (conv(64, 64, 3, 1, 14), conv(64, 64, 1, 1, 7, bias=True), conv(64, 64, 1, 1, 9)):
