@@ -126,7 +126,6 @@ class _Plan:
         self.groups_a = self._make_groups(ps, range(L) if only is None else only, 0) if ps.clip_unit == 1 else []
         self.groups_b = self._make_groups(ps, [i for i in range(L) if self.form[i] == "recompute"], 1) if only is None else []
         self.groups_u = self._make_groups(ps, range(L), 2) if ps.clip_unit > 1 else []
-        self.last = ps._last_plan(self.form) if self.form is not ps.form else None
 
     def _make_groups(self, ps: "PrivatiseStep", layer_ids, use: int):
         """Groups of at most 16 layers with the same kernel variant for phase `use` (0: per-example gradients,
@@ -560,7 +559,7 @@ class PrivatiseStep:
     def g(self) -> Optional[torch.Tensor]:
         """[rows, p_mat] stored gradients of the most recent micro-step, columns as in the accumulator."""
         plan = self._g_plan
-        if self._g_last is None or plan.last is None:
+        if self._g_last is None or plan.form is self.form:
             return self._g_last
         # the phase stored some of the columns side by side, the others lie in a matrix of their own already
         out = self._last_store.g
@@ -689,9 +688,9 @@ class PrivatiseStep:
                 ev.record(st)
                 evs.append(ev)
             store.done = evs
-        if ends_step and plan.last is not None:
+        if ends_step and plan.form is not self.form:
             skip = 8 * (plan.n - self.n)           # entries of the tables before the last micro-step's examples
-            for grp in plan.last.groups_a:
+            for grp in self._last_plan(plan.form).groups_a:
                 bt = grp["batch"][0]
                 B.dp_per_example_grad_batch(bt, bt.fill("x", [x[i] + skip for i in grp["layers"]]), bt.fill("dy", [dy[i] + skip for i in grp["layers"]]),
                                             grp["gw"][0], grp["gb"][0], None, g_stride=self.p_mat, stream=ms, addresses=True)
