@@ -11,8 +11,9 @@
 // times where the fp32 instruction rounds at every step.  Relative error of the gradient against 64 bits (2-norm), fp32 instruction ->
 // this: 64 -> 64 3x3 on 56 x 56 5.0e-7 -> 1.3e-7, 16 -> 16 on 32 x 32 2.8e-7 -> 0.9e-7, 64 -> 64 on 8 x 8 1.3e-7 -> 0.5e-7, 40 -> 72 5x5 stride 2 on
 // 45 x 37 2.6e-7 -> 0.8e-7.
-// An infinity or a NaN has no such parts (and its sums are not finite): a block with a sum that is not finite is computed again in plain fp32, element
-// by element.
+// An infinity or a NaN has no such parts (and its sums are not finite): a block with a sum that is not finite is computed again with the fp32
+// instruction, a row of the output at a time (no reads ahead: it is rare).  us per call, no example broken / one / all: 64 examples of 64 -> 64 3x3 on
+// 56 x 56 112 / 482 / 508, 256 of 16 -> 16 on 32 x 32 21 / 75 / 81, 40 of 40 -> 72 5x5 stride 2 on 45 x 37 79 / 160 / 258.
 //
 // A workgroup owns one block of at most 32 x 32 channels (32 x 16 for 5 x 5) of one example (several examples in a row, so that the set-up is
 // paid once and loads run ahead across examples).  K is cut into runs of eight output columns of one row.  Wave (kh, q) keeps the
@@ -315,76 +316,101 @@ __global__ void __launch_bounds__(64 * K * cr_qmax(K)) conv_rows_kernel(const Gr
 #pragma unroll
                     for (int r = 0; r < 4; ++r) odd = fmaf(acc[m][b][k][r], 0.0f, odd);
         const bool plain = __syncthreads_or(odd != 0.0f) != 0;        // (true for NaN)
-        float ss = 0.0f;
         if (plain) {
-            // not every sum is finite: the block element by element, as fp32 arithmetic gives it
-            const int len = cn * K * K;
-#pragma unroll 1
-            for (int t = tid; t < cm * (len + 1); t += nthreads) {
-                const int r = t / (len + 1), col = t - r * (len + 1);
-                const int ci = col / (K * K), tap = col - ci * (K * K), dh = tap / K - PAD, dw = tap - tap / K * K - PAD;
-                const bool bias = col == len;
-                if (bias && !(a.bias && n0 == 0)) continue;
-                float v = 0.0f;
-#pragma unroll 1
-                for (int i = row_i * a.unit; i < (row_i + 1) * a.unit; ++i) {
-                    const float *dy_ch = example_at<float>(a.dy, a.dy_tab, i, (size_t)a.cout * OH * OW) + (size_t)(m0 + r) * OH * OW;
-                    const float *x_ch = example_at<float>(a.x, a.x_tab, i, (size_t)a.cin * H * W) + (size_t)(n0 + (bias ? 0 : ci)) * H * W;
-#pragma unroll 1
-                    for (int oh = 0; oh < OH; ++oh)
-#pragma unroll 1
-                        for (int ow = 0; ow < OW; ++ow) {
-                            const int ih = oh * S + dh, iw = ow * S + dw;
-                            if (bias) v += dy_ch[oh * OW + ow];
-                            else if ((unsigned)ih < (unsigned)H && (unsigned)iw < (unsigned)W) v = fmaf(dy_ch[oh * OW + ow], x_ch[ih * W + iw], v);
-                        }
-                }
-                ss += v * v;
-                if (a.out_w) {
-                    if (bias) a.out_b[(size_t)row_i * a.out_stride_b + m0 + r] = v;
-                    else a.out_w[(size_t)row_i * a.out_stride_w + ((size_t)(m0 + r) * a.cin + n0) * (K * K) + col] = v;
-                }
-            }
-        } else {
-            // the block, 16 rows at a time: summed over q in order, squared, stored
+            // Not every sum is finite: the block again with the fp32 instruction, a row of the output at a time (dY and the K rows of X that it meets lie
+            // in the chunks' place as they are; lane group t has column t of four).  Both operands of a position outside the image are zero.
+            // (The opaque copies keep what is worked out from them here: hoisted out of the loop over examples, it costs the products above their registers.)
+            int ow_n = OW, w_n = W, oh_n = OH, h_n = H, id = tid, rows_a = cm, rows_x = cn * K;
+            asm volatile("" : "+s"(ow_n), "+s"(w_n), "+s"(oh_n), "+s"(h_n), "+s"(rows_a), "+s"(rows_x));
+            asm volatile("" : "+v"(id));
+            const int pitch_a = ow_n | 1, pitch_x = (K * w_n) | 1, col = id & 15, four = (id >> 4) & 3;
+            float *const sx = epi + CO * pitch_a;
 #pragma unroll
-            for (int m = 0; m < NM; ++m) {
-                if (m * 16 >= cm) break;
-                float *mine = epi + (q * 16 + kq * 4) * EP + ((lane & 15) * K + kh) * K;
+            for (int m = 0; m < NM; ++m)
 #pragma unroll
                 for (int b = 0; b < NN; ++b)
 #pragma unroll
-                    for (int k = 0; k < K; ++k)
+                    for (int k = 0; k < K; ++k) acc[m][b][k] = r_f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll 1
+            for (int i = row_i * a.unit; i < (row_i + 1) * a.unit; ++i) {
+                const float *dy_ex = example_at_uniform<float>(a.dy, a.dy_tab, i, (size_t)a.cout * oh_n * ow_n) + (size_t)m0 * oh_n * ow_n;
+                const float *x_ex = example_at_uniform<float>(a.x, a.x_tab, i, (size_t)a.cin * h_n * w_n) + (size_t)n0 * h_n * w_n;
+#pragma unroll 1
+                for (int oh = 0; oh < oh_n; ++oh) {
+                    __syncthreads();                   // everyone has read the row before
+#pragma unroll 1
+                    for (int t = id; t < rows_a * ow_n; t += nthreads) {
+                        const int ch = t / ow_n, c = t - ch * ow_n;
+                        epi[ch * pitch_a + c] = dy_ex[((size_t)ch * oh_n + oh) * ow_n + c];
+                    }
+#pragma unroll 1
+                    for (int t = id; t < rows_x * w_n; t += nthreads) {
+                        const int row = t / w_n, c = t - row * w_n, ch = row / K, k = row - ch * K, ih = oh * S + k - PAD;
+                        sx[ch * pitch_x + k * w_n + c] = (unsigned)ih < (unsigned)h_n ? x_ex[((size_t)ch * h_n + ih) * w_n + c] : 0.0f;
+                    }
+                    __syncthreads();
+                    if ((unsigned)(oh * S + kh - PAD) >= (unsigned)h_n) continue;        // (the same in every lane of a wave)
+#pragma unroll 1
+                    for (int g = q; 4 * g < ow_n; g += a.q) {
+                        const int ow = 4 * g + four;
 #pragma unroll
-                        for (int r = 0; r < 4; ++r) mine[r * EP + b * 16 * K * K + k] = acc[m][b][k][r];
-                __syncthreads();
-                const int len = cn * K * K;
-                for (int r = wave; r < min(16, cm - m * 16); r += nwaves) {
-                    const int co = m0 + m * 16 + r;
-                    float *dst = a.out_w ? a.out_w + (size_t)row_i * a.out_stride_w + ((size_t)co * a.cin + n0) * (K * K) : nullptr;
-                    for (int t = lane; t < len; t += 64) {
-                        float v = epi[r * EP + t];
-                        for (int part = 1; part < a.q; ++part) v += epi[(part * 16 + r) * EP + t];
-                        ss += v * v;
-                        if (dst) __builtin_nontemporal_store(v, dst + t);
+                        for (int k = 0; k < K; ++k) {
+                            const int iw = ow * S + k - PAD;
+                            const bool there = ow < ow_n && (unsigned)iw < (unsigned)w_n;
+                            float d[NM];
+#pragma unroll
+                            for (int m = 0; m < NM; ++m) d[m] = there ? epi[(m * 16 + col) * pitch_a + ow] : 0.0f;
+#pragma unroll
+                            for (int b = 0; b < NN; ++b) {
+                                const float v = there ? sx[(b * 16 + col) * pitch_x + kh * w_n + iw] : 0.0f;
+#pragma unroll
+                                for (int m = 0; m < NM; ++m) acc[m][b][k] = __builtin_amdgcn_mfma_f32_16x16x4f32(d[m], v, acc[m][b][k], 0, 0, 0);
+                            }
+                        }
                     }
                 }
-                __syncthreads();                           // epi is free again
             }
-            if (has_bias) {
-                // a channel's pieces are R * apr threads' in a row (in PT rounds): one thread adds them up
+            __syncthreads();
+        }
+        float ss = 0.0f;
+        // the block, 16 rows at a time: summed over q in order, squared, stored
 #pragma unroll
-                for (int u = 0; u < PT; ++u)
-                    if (!is_x) epi[tid + a_threads * u] = bsum[u];
-                __syncthreads();
-                if (tid < cm) {
-                    float v = 0.0f;
-                    for (int t = 0; t < R * apr; ++t) v += epi[tid * R * apr + t];
+        for (int m = 0; m < NM; ++m) {
+            if (m * 16 >= cm) break;
+            float *mine = epi + (q * 16 + kq * 4) * EP + ((lane & 15) * K + kh) * K;
+#pragma unroll
+            for (int b = 0; b < NN; ++b)
+#pragma unroll
+                for (int k = 0; k < K; ++k)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) mine[r * EP + b * 16 * K * K + k] = acc[m][b][k][r];
+            __syncthreads();
+            const int len = cn * K * K;
+            for (int r = wave; r < min(16, cm - m * 16); r += nwaves) {
+                const int co = m0 + m * 16 + r;
+                float *dst = a.out_w ? a.out_w + (size_t)row_i * a.out_stride_w + ((size_t)co * a.cin + n0) * (K * K) : nullptr;
+                for (int t = lane; t < len; t += 64) {
+                    float v = epi[r * EP + t];
+                    for (int part = 1; part < a.q; ++part) v += epi[(part * 16 + r) * EP + t];
                     ss += v * v;
-                    if (a.out_b) a.out_b[(size_t)row_i * a.out_stride_b + m0 + tid] = v;
+                    if (dst) __builtin_nontemporal_store(v, dst + t);
                 }
-                __syncthreads();
             }
+            __syncthreads();                           // epi is free again
+        }
+        if (has_bias) {
+            // a channel's pieces are R * apr threads' in a row (in PT rounds): one thread adds them up
+#pragma unroll
+            for (int u = 0; u < PT; ++u)
+                if (!is_x) epi[tid + a_threads * u] = bsum[u];
+            __syncthreads();
+            if (tid < cm) {
+                float v = 0.0f;
+                for (int t = 0; t < R * apr; ++t) v += epi[tid * R * apr + t];
+                ss += v * v;
+                if (a.out_b) a.out_b[(size_t)row_i * a.out_stride_b + m0 + tid] = v;
+            }
+            __syncthreads();
         }
         ss = wave_sum(ss);
         if (lane == 0) red[wave] = ss;

@@ -516,6 +516,39 @@ def test_conv_f32_raw_rows_kernel_where_a_block_is_larger_than_its_chunks(cin, c
         assert np.allclose(got_n2, ref_n2, rtol=F32_TOL, atol=0)
 
 
+# ragged channels in one block and in several, rows of fewer than four numbers, no multiple of four and one column, both strides, two examples of a
+# unit; several examples per workgroup
+@pytest.mark.parametrize("cin,cout,h,w,k,stride,n,unit", [(33, 15, 27, 26, 3, 1, 300, 1), (18, 20, 45, 37, 5, 2, 40, 1), (18, 20, 40, 3, 3, 1, 300, 1), (17, 33, 30, 29, 3, 1, 300, 1),
+                                                          (64, 32, 33, 34, 3, 2, 300, 1), (64, 64, 28, 28, 3, 1, 128, 2), (20, 40, 28, 27, 5, 1, 100, 1), (16, 16, 12, 14, 3, 1, 8200, 1)])
+def test_conv_f32_raw_rows_kernel_computes_a_block_again(cin, cout, h, w, k, stride, n, unit):
+    """Numbers whose parts are not finite while the sums of fp32 products are: every element within fp32 rounding of the sum of its products'
+    magnitudes, in the broken examples and in the others."""
+    layer, few = Layer("conv", cin, cout, h, w, k, k, stride, (k - 1) // 2, cout % 2 == 0), 4
+    rng = np.random.default_rng(157)
+    x, dy = _inputs(layer, few, 157, "f32")
+    dy *= 2.0 ** -20
+    for i, c in ((1, cin - 1), (2, 0)):
+        x[i, c, rng.integers(h), rng.integers(w)], x[i, c, h - 1, w - 1] = np.finfo(np.float32).max, -np.finfo(np.float32).max
+    name = dp.dp_kernel_variant(dp.make_desc(layer, n, "f32"), dp.DP_WS_PER_EXAMPLE_GRAD)
+    assert name.startswith("conv_rows<f32"), name
+    ref_w, ref_b, _ = _oracle_grads(layer, x, dy)
+    abs_w, abs_b, _ = _oracle_grads(layer, np.abs(x), np.abs(dy))
+    ref, mag = np.concatenate([ref_w, ref_b], axis=1), np.concatenate([abs_w, abs_b], axis=1)
+    if unit > 1:
+        ref, mag = ref.reshape(few // unit, unit, -1).sum(1), mag.reshape(few // unit, unit, -1).sum(1)
+    rows = n // unit
+    ref, mag, x, dy = np.resize(ref, (rows, ref.shape[1])), np.resize(mag, (rows, ref.shape[1])), np.resize(x, (n,) + x.shape[1:]), np.resize(dy, (n,) + dy.shape[1:])
+    d = dp.make_desc(layer, n, "f32")
+    need = dp.dp_unit_workspace_bytes(d, unit) if unit > 1 else dp.dp_workspace_bytes(d)
+    ws, xd, dyd = torch.empty(max(16, need), dtype=torch.uint8, device="cuda:0"), dev(x), dev(dy)
+    row = (layer.pw + 3) // 4 * 4
+    g, sq = torch.full((rows, row + (layer.pb + 3) // 4 * 4), float("nan"), device="cuda:0"), torch.full((rows,), -1.0, device="cuda:0")
+    args = (xd, dyd, g, g[:, row:] if layer.pb else None, sq, ws)
+    dp.dp_unit_grad(d, unit, *args, g_stride=g.shape[1]) if unit > 1 else dp.dp_per_example_grad(d, *args, g_stride=g.shape[1])
+    got = host(torch.cat([g[:, :layer.pw], g[:, row:row + layer.pb]], dim=1))
+    assert (np.abs(got - ref) <= F32_TOL * mag).all(), np.abs(got / mag - ref / mag).max()
+
+
 def test_conv_f32_raw_rows_kernel_takes_every_fp32_number():
     """Numbers that round to infinity as bf16 stay finite, NaNs stay where they are, and the next example is what it was."""
     layer = Layer("conv", 32, 16, 6, 8, 3, 3, 1, 1, False)
