@@ -3,15 +3,17 @@
 //     dW_i[co, ci, kh, kw] = sum_{oh, ow} dY_i[co, oh, ow] * Xpad_i[ci, s oh + kh - p, s ow + kw - p].
 // The fp32 matrix rate (157 TFLOP/s) bounds these layers in any kernel that multiplies fp32 numbers as they are, and an im2col column per
 // (ci, kh, kw) stages every element of X k * k times.  Here rows of dY and X go to LDS once per chunk of output rows, all k * k taps
-// are read from them, and the products run on the bf16 matrix units, which are sixteen times as fast: every staged number is split
-// into three bf16 numbers whose sum it is, bit for bit (its nearest bf16, the nearest one to what that leaves, and the rest), and a product of two numbers
+// are read from them, and the products run on the bf16 matrix units, which are sixteen times as fast: every staged number, times 2^24, is split
+// into three bf16 numbers whose sum it is, bit for bit (its nearest bf16, the nearest one to what that leaves, and the rest; the smallest fp32 number
+// is 2^-149, the smallest normal bf16 2^-126), and a product of two numbers
 // is the six products of their parts that reach 2^-24 of it,
 //     a b ~ ah bh + (ah bm + am bh) + (am bm + ah bl + al bh),
 // each exact in fp32 and added up in fp32.  What is left out is below 2^-23 of the product, and a sum of 32 of them is rounded a handful of
 // times where the fp32 instruction rounds at every step.  Relative error of the gradient against 64 bits (2-norm), fp32 instruction ->
 // this: 64 -> 64 3x3 on 56 x 56 5.0e-7 -> 1.3e-7, 16 -> 16 on 32 x 32 2.8e-7 -> 0.9e-7, 64 -> 64 on 8 x 8 1.3e-7 -> 0.5e-7, 40 -> 72 5x5 stride 2 on
 // 45 x 37 2.6e-7 -> 0.8e-7.
-// An infinity or a NaN has no such parts (and its sums are not finite): a block with a sum that is not finite is computed again with the fp32
+// An infinity or a NaN has no such parts (and its sums are not finite), nor has a number from 2^104 on, and a sum from 2^80 on has no room for the factor:
+// a block with a sum that is not finite is computed again with the fp32
 // instruction, a row of the output at a time (no reads ahead: it is rare).  us per call, no example broken / one / all: 64 examples of 64 -> 64 3x3 on
 // 56 x 56 112 / 482 / 508, 256 of 16 -> 16 on 32 x 32 21 / 75 / 81, 40 of 40 -> 72 5x5 stride 2 on 45 x 37 79 / 160 / 258.
 //
@@ -93,6 +95,7 @@ __device__ __forceinline__ void cr_split(float v0, float v1, uint32_t (&part)[3]
     }
 }
 
+constexpr float CR_UP = 0x1p24f, CR_DOWN = 0x1p-24f;     // what a number is scaled by before it is split, and back (sums: twice)
 constexpr unsigned CR_NOWHERE = 0xFFFFFFF0u;     // a byte beyond every example: the load gives zeros
 
 // NM x NN blocks of 16 x 16 channels
@@ -199,10 +202,10 @@ __global__ void __launch_bounds__(64 * K * cr_qmax(K)) conv_rows_kernel(const Gr
             if (int mt = meta[u]) {
                 asm volatile("" : "+v"(mt));
                 uint32_t lo[3], hi[3];
-                const r_f32x4 v = raw[u];
+                const r_f32x4 r = raw[u], v = r * CR_UP;
                 uint32_t *dst = chunk + (mt & 0xffff);
                 if (S == 1 || !is_x) {
-                    if (has_bias) bsum[u] += (v.x + v.y) + (v.z + v.w);
+                    if (has_bias) bsum[u] += (r.x + r.y) + (r.z + r.w);
                     cr_split(v.x, v.y, lo);
                     cr_split(v.z, v.w, hi);
 #pragma unroll
@@ -372,6 +375,7 @@ __global__ void __launch_bounds__(64 * K * cr_qmax(K)) conv_rows_kernel(const Gr
             }
             __syncthreads();
         }
+        const float down = plain ? 1.0f : CR_DOWN;
         float ss = 0.0f;
         // the block, 16 rows at a time: summed over q in order, squared, stored
 #pragma unroll
@@ -383,7 +387,7 @@ __global__ void __launch_bounds__(64 * K * cr_qmax(K)) conv_rows_kernel(const Gr
 #pragma unroll
                 for (int k = 0; k < K; ++k)
 #pragma unroll
-                    for (int r = 0; r < 4; ++r) mine[r * EP + b * 16 * K * K + k] = acc[m][b][k][r];
+                    for (int r = 0; r < 4; ++r) mine[r * EP + b * 16 * K * K + k] = acc[m][b][k][r] * down;
             __syncthreads();
             const int len = cn * K * K;
             for (int r = wave; r < min(16, cm - m * 16); r += nwaves) {
@@ -392,6 +396,7 @@ __global__ void __launch_bounds__(64 * K * cr_qmax(K)) conv_rows_kernel(const Gr
                 for (int t = lane; t < len; t += 64) {
                     float v = epi[r * EP + t];
                     for (int part = 1; part < a.q; ++part) v += epi[(part * 16 + r) * EP + t];
+                    v *= down;
                     ss += v * v;
                     if (dst) __builtin_nontemporal_store(v, dst + t);
                 }

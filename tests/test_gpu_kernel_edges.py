@@ -549,6 +549,23 @@ def test_conv_f32_raw_rows_kernel_computes_a_block_again(cin, cout, h, w, k, str
     assert (np.abs(got - ref) <= F32_TOL * mag).all(), np.abs(got / mag - ref / mag).max()
 
 
+# The smallest numbers, whose parts end below the smallest ones of the narrower type: as exact as others.  (Gradients from 2^-90 on; the
+# bound is that of test_conv_f32_raw_rows_kernel_is_as_exact_as_fp32.)
+@pytest.mark.parametrize("up,down", [(60, 115), (0, 113), (-113, 0), (70, 130), (-45, 45), (90, 45)])
+@pytest.mark.parametrize("cin,cout,h,w,k,stride,n", [(16, 16, 32, 32, 3, 1, 300), (40, 72, 45, 37, 5, 2, 40)])
+def test_conv_f32_raw_rows_kernel_is_as_exact_on_small_numbers(cin, cout, h, w, k, stride, n, up, down):
+    layer = Layer("conv", cin, cout, h, w, k, k, stride, (k - 1) // 2, k == 5)
+    x, dy = _inputs(layer, 2, 163, "f32")
+    x, dy = (x * 2.0 ** up).astype(np.float32), (dy * 2.0 ** -down).astype(np.float32)
+    assert dp.dp_kernel_variant(dp.make_desc(layer, n, "f32"), dp.DP_WS_PER_EXAMPLE_GRAD).startswith("conv_rows<f32")
+    ref_w = _oracle_grads(layer, x, dy)[0]
+    gw = _run_per_example(layer, np.concatenate([x] * (n // 2)), np.concatenate([dy] * (n // 2)), "f32")[0]
+    bound = 2.0 * (2.0 ** -23 + np.sqrt(layer.oh * layer.ow / 32) * 2.0 ** -24)
+    scale = 2.0 ** (down - up)
+    for got in (gw[:2], gw[-2:]):
+        assert np.linalg.norm((got - ref_w) * scale) < bound * np.linalg.norm(ref_w * scale)
+
+
 def test_conv_f32_raw_rows_kernel_takes_every_fp32_number():
     """Numbers that round to infinity as bf16 stay finite, NaNs stay where they are, and the next example is what it was."""
     layer = Layer("conv", 32, 16, 6, 8, 3, 3, 1, 1, False)
