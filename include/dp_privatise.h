@@ -110,11 +110,17 @@ size_t dp_bias_count(const dp_layer_desc *desc /*[host]*/);
  * preserved between calls (except as dp_per_example_grad_partials documents).               */
 size_t dp_workspace_bytes(const dp_layer_desc *desc /*[host]*/, int use /*dp_ws_use*/);
 
+/* Workspace with which a layer of a batch call runs its fastest route: what the call needs (dp_workspace_bytes, dp_unit_workspace_bytes)
+ * and, for per-example calls of bf16 convolutions on maps of odd sizes, room for copies of both operands (at most 256 MB a
+ * layer; 64 -> 256 1x1 on 57 x 57, 64 examples: 150 MB).  A batch call whose workspace has no room for them reads the operands in
+ * place, more slowly; calls of one layer never make them.  clip_unit: examples of a clipping unit, or 1.  0 on a bad argument.    */
+size_t dp_batch_workspace_bytes(const dp_layer_desc *desc /*[host]*/, int use /*dp_ws_use*/, int clip_unit);
+
 /* Name of the kernel variant that dp_per_example_grad (use = DP_WS_PER_EXAMPLE_GRAD) or
  * dp_clip_accumulate_recompute (use = DP_WS_RECOMPUTE) launches for this descriptor, e.g.
  * "conv_contract<bf16,128x128,per_example>"; "" on a bad descriptor.  With DP_VARIANT_SHARED or-ed
- * into `use`: the variant the layer runs as inside a batch call of several layers (tiling is chosen
- * differently when a launch is shared); layers with equal names then share one launch, at most 16
+ * into `use`: the variant the layer runs as inside a batch call of several layers with the workspace of
+ * dp_batch_workspace_bytes (tiling is chosen differently when a launch is shared); layers with equal names then share one launch, at most 16
  * per launch, and so do all layers whose names begin with "conv3x3_rows<" (every row width, stride
  * and K slicing of that kernel runs in one launch inside a batch call).  Pure host; lets a profiler's
  * per-kernel rows be tied to layers.  The string is static.                                     */

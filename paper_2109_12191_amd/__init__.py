@@ -10,7 +10,7 @@ from .binding import (DP_BF16, DP_CONV2D, DP_DENSE, DP_F32, DP_GN_AFFINE, DP_NCH
                       dp_bias_count, dp_group_clip_bounds, dp_clip_accumulate, dp_clip_accumulate_recompute, dp_clip_factors,
                       dp_add_noise_finalize_update, dp_add_noise_finalize_flat, TensorTable, dp_add_example_noise, dp_clip_accumulate_segments, dp_clip_accumulate_columns, SegmentTable, dp_example_addresses, dp_kernel_variant, dp_last_error, dp_norms, dp_norm_partial_count, dp_norms_from_partials, dp_layer_norms_from_partials, dp_unit_grad, dp_unit_grad_batch, dp_unit_workspace_bytes,
                       dp_per_example_grad_partials, dp_per_example_grad_batch, dp_clip_accumulate_recompute_batch, LayerBatch, PartialTable, dp_per_example_grad, dp_per_example_grad_static, dp_static_scratch_bytes, dp_philox_raw, dp_profile_next_contraction, dp_version,
-                      dp_weight_count, dp_workspace_bytes, lib_path, load_library, make_desc)
+                      dp_batch_workspace_bytes, dp_weight_count, dp_workspace_bytes, lib_path, load_library, make_desc)
 from .pipeline import PrivatiseStep
 
 __all__ = [
@@ -19,5 +19,5 @@ __all__ = [
     "dp_bias_count", "dp_group_clip_bounds", "dp_clip_accumulate", "dp_clip_accumulate_recompute", "dp_clip_factors",
     "dp_add_noise_finalize_update", "dp_add_noise_finalize_flat", "TensorTable", "dp_add_example_noise", "dp_clip_accumulate_segments", "dp_clip_accumulate_columns", "SegmentTable", "dp_example_addresses", "dp_kernel_variant", "dp_last_error", "dp_norms", "dp_norm_partial_count", "dp_norms_from_partials", "dp_layer_norms_from_partials", "dp_unit_grad", "dp_unit_grad_batch", "dp_unit_workspace_bytes",
     "dp_per_example_grad_partials", "dp_per_example_grad_batch", "dp_clip_accumulate_recompute_batch", "LayerBatch", "PartialTable", "dp_per_example_grad", "dp_per_example_grad_static", "dp_static_scratch_bytes", "dp_philox_raw", "dp_profile_next_contraction", "dp_version", "dp_weight_count",
-    "dp_workspace_bytes", "lib_path", "load_library", "make_desc", "PrivatiseStep",
+    "dp_batch_workspace_bytes", "dp_workspace_bytes", "lib_path", "load_library", "make_desc", "PrivatiseStep",
 ]

@@ -63,6 +63,7 @@ def load_library():
         "dp_norms": (it, [vp, vp, it, it, it, vp, vp]),
         "dp_norm_partial_count": (sz, [dpp, it]),
         "dp_unit_workspace_bytes": (sz, [dpp, it]),
+        "dp_batch_workspace_bytes": (sz, [dpp, it, it]),
         "dp_unit_grad": (it, [dpp, it, vp, vp, vp, vp, sz, vp, vp, sz, vp]),
         "dp_unit_grad_batch": (it, [vp, it, vp, vp, vp, vp, sz, vp, vp, vp, it, vp]),
         "dp_per_example_grad_partials": (it, [dpp, vp, vp, vp, vp, sz, vp, sz, vp]),
@@ -100,7 +101,7 @@ def load_library():
 
 EXPORTED = ("dp_group_clip_bounds", "dp_weight_count", "dp_bias_count", "dp_workspace_bytes", "dp_kernel_variant", "dp_per_example_grad", "dp_norms",
             "dp_static_scratch_bytes", "dp_per_example_grad_static",
-            "dp_unit_workspace_bytes", "dp_unit_grad", "dp_unit_grad_batch",
+            "dp_unit_workspace_bytes", "dp_batch_workspace_bytes", "dp_unit_grad", "dp_unit_grad_batch",
             "dp_norm_partial_count", "dp_per_example_grad_partials", "dp_norms_from_partials",
             "dp_per_example_grad_batch", "dp_layer_norms_from_partials", "dp_clip_accumulate_recompute_batch",
             "dp_example_addresses", "dp_per_example_grad_batch_at", "dp_per_example_grad_blocks_batch_at", "dp_clip_accumulate_recompute_batch_at", "dp_clip_accumulate_recompute_blocks_batch_at", "dp_unit_grad_batch_at",
@@ -215,6 +216,11 @@ def dp_norms_from_partials(table: "PartialTable", n: int, n_groups: int, group_s
     _check(load_library().dp_norms_from_partials(C.cast(table.ptrs, C.c_void_p), C.cast(table.counts, C.c_void_p),
                                                  C.cast(table.groups, C.c_void_p), table.n_layers, n, n_groups,
                                                  _ptr(group_sqnorm), _stream(stream)))
+
+
+def dp_batch_workspace_bytes(desc: LayerDesc, use: int = DP_WS_PER_EXAMPLE_GRAD, clip_unit: int = 1) -> int:
+    """Workspace with which a layer of a batch call runs its fastest route."""
+    return int(load_library().dp_batch_workspace_bytes(C.byref(desc), use, clip_unit))
 
 
 def dp_unit_workspace_bytes(desc: LayerDesc, clip_unit: int) -> int:

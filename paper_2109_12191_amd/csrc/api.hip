@@ -228,15 +228,15 @@ static dp_status check_clip(float clip_c)
     return DP_OK;
 }
 
-static dp_status check_ws(const Geo &g, int mode, const void *ws, size_t ws_bytes)
+static dp_status check_room(size_t need, const void *ws, size_t ws_bytes)
 {
-    const size_t need = ws_bytes_for(g, mode);
     if (need == 0) return DP_OK;
     if (!ws) return fail(DP_ERR_WORKSPACE, "workspace is NULL; %zu bytes needed", need);
     if (!aligned16(ws)) return fail(DP_ERR_INVALID_ARG, "workspace is not 16-byte aligned");
     if (ws_bytes < need) return fail(DP_ERR_WORKSPACE, "workspace of %zu bytes is smaller than the %zu needed", ws_bytes, need);
     return DP_OK;
 }
+static dp_status check_ws(const Geo &g, int mode, const void *ws, size_t ws_bytes) { return check_room(ws_bytes_for(g, mode), ws, ws_bytes); }
 
 }  // namespace dp
 
@@ -284,25 +284,30 @@ size_t dp_bias_count(const dp_layer_desc *desc)
     return make_geo(desc, g) == DP_OK ? g.pb : 0;
 }
 
+// What `use` asks of a layer: the mode, its flags put into the geometry; -1 if it has no such call.
+static int mode_of_use(Geo &g, int use)
+{
+    if (use & DP_RECOMPUTE_BLOCKS) {
+        g.blocks = 1;
+        use &= ~DP_RECOMPUTE_BLOCKS;
+        if (use == DP_WS_RECOMPUTE && !scales_blocks(g)) {
+            fail(DP_ERR_UNSUPPORTED, "no kernel scales this layer's finished blocks");
+            return -1;
+        }
+    }
+    if (use != DP_WS_PER_EXAMPLE_GRAD && use != DP_WS_RECOMPUTE) {
+        fail(DP_ERR_INVALID_ARG, "unknown workspace use %d", use);
+        return -1;
+    }
+    return use == DP_WS_RECOMPUTE ? MODE_WEIGHTED : MODE_NORM;
+}
+
 size_t dp_workspace_bytes(const dp_layer_desc *desc, int use)
 {
     Geo g;
     if (make_geo(desc, g) != DP_OK) return 0;
-    if (use == (DP_WS_RECOMPUTE | DP_RECOMPUTE_BLOCKS)) {
-        if (!scales_blocks(g)) {
-            fail(DP_ERR_UNSUPPORTED, "no kernel scales this layer's finished blocks");
-            return 0;
-        }
-        use = DP_WS_RECOMPUTE;
-    } else if (use == (DP_WS_PER_EXAMPLE_GRAD | DP_RECOMPUTE_BLOCKS)) {
-        g.blocks = 1;
-        use = DP_WS_PER_EXAMPLE_GRAD;
-    }
-    if (use != DP_WS_PER_EXAMPLE_GRAD && use != DP_WS_RECOMPUTE) {
-        fail(DP_ERR_INVALID_ARG, "unknown workspace use %d", use);
-        return 0;
-    }
-    return ws_bytes_for(g, use == DP_WS_RECOMPUTE ? MODE_WEIGHTED : MODE_NORM);
+    const int mode = mode_of_use(g, use);
+    return mode < 0 ? 0 : ws_bytes_for(g, mode);
 }
 
 const char *dp_kernel_variant(const dp_layer_desc *desc, int use)
@@ -310,6 +315,7 @@ const char *dp_kernel_variant(const dp_layer_desc *desc, int use)
     Geo g;
     if (make_geo(desc, g) != DP_OK) return "";
     const bool shared = (use & DP_VARIANT_SHARED) != 0, stored = (use & DP_VARIANT_MATERIALISE) != 0;
+    g.copies = shared;
     if (use & DP_RECOMPUTE_BLOCKS) {
         g.blocks = 1;
         if ((use & DP_WS_RECOMPUTE) && !scales_blocks(g)) return "";
@@ -411,6 +417,19 @@ static size_t unit_ws_kernels(const Geo &g, int kind, int clip_unit)
 }
 static size_t unit_ws_need(const Geo &g, int kind, int clip_unit) { return unit_ws_kernels(g, kind, clip_unit) + layout_copy_bytes(g); }
 
+size_t dp_batch_workspace_bytes(const dp_layer_desc *desc, int use, int clip_unit)
+{
+    Geo g;
+    if (unit_geo(desc, clip_unit, g) != DP_OK) return 0;
+    const int mode = mode_of_use(g, use);
+    if (mode < 0) return 0;
+    if (mode == MODE_WEIGHTED) return dp_workspace_bytes(desc, use);
+    size_t need[2];
+    for (g.copies = 0; g.copies < 2; ++g.copies)
+        need[g.copies] = clip_unit == 1 ? ws_bytes_for(g, MODE_NORM) : unit_ws_need(g, desc->kind, clip_unit);
+    return need[0] > need[1] ? need[0] : need[1];
+}
+
 static dp_status launch_layer_units(const Geo &g, int clip_unit, const void *x, const void *dy, float *g_w, float *g_b,
                                     size_t g_stride, float *sqnorm, void *ws, hipStream_t s)
 {
@@ -498,7 +517,13 @@ static dp_status per_example_grad_batch(bool addresses, bool blocks, const dp_la
             if (g_stride % 4) return fail(DP_ERR_INVALID_ARG, "g_stride must be a multiple of 4");
             if (gw && (g_stride < g.pw || g_stride < g.pb)) return fail(DP_ERR_INVALID_ARG, "layer %d: g_stride smaller than the tensor", l);
         }
-        DP_TRY(check_ws(g, MODE_NORM, ws[l], ws_bytes[l]));
+        g.copies = 1;
+        size_t need = ws_bytes_for(g, MODE_NORM);
+        if (ws_bytes[l] < need) {                    // no room for copies: without them
+            g.copies = 0;
+            need = ws_bytes_for(g, MODE_NORM);
+        }
+        DP_TRY(check_room(need, ws[l], ws_bytes[l]));
     }
     hipStream_t s = static_cast<hipStream_t>(stream);
     g_err[0] = 0;
@@ -583,7 +608,12 @@ static dp_status unit_grad_batch(bool addresses, const dp_layer_desc *descs, int
             if (g_stride % 4) return fail(DP_ERR_INVALID_ARG, "g_stride must be a multiple of 4");
             if (gw && (g_stride < g.pw || g_stride < g.pb)) return fail(DP_ERR_INVALID_ARG, "layer %d: g_stride smaller than the tensor", l);
         }
-        const size_t need = unit_ws_need(g, descs[l].kind, clip_unit);
+        g.copies = 1;
+        size_t need = unit_ws_need(g, descs[l].kind, clip_unit);
+        if (ws_bytes[l] < need) {                    // no room for copies: without them
+            g.copies = 0;
+            need = unit_ws_need(g, descs[l].kind, clip_unit);
+        }
         if (need && (!ws[l] || ws_bytes[l] < need))
             return fail(DP_ERR_WORKSPACE, "layer %d: workspace of %zu bytes needed (dp_unit_workspace_bytes), %zu given", l, need,
                         ws[l] ? ws_bytes[l] : (size_t)0);

@@ -1770,18 +1770,14 @@ static bool subsampled(const Geo &g, int mode, Geo &g2)
 }
 
 // Per-example calls of bf16 layers whose rows no fast kernel is built for (odd map sizes) run on copies with longer rows (launch_widen),
-// zeros behind the values: `g2` is the geometry of the copies.  Only inside batch calls, whose layers share the copying launch (alone it
+// zeros behind the values: `g2` is the geometry of the copies.  Only inside batch calls with room for them, whose layers share the copying launch (alone it
 // costs what it saves: 128 -> 512 1x1 on 13 x 13, 36 examples 16 -> 26 us), and from 12 examples on (ResNet-50 at 208 x 208, us per
 // micro-step on eight streams, general kernel / copies: 8 examples 655 / 655, at 192 x 192 449 / 476; 16 examples 982 / 929; on one stream
 // 2 x 12 1570 / 1328; ResNet-18-GN at 40 x 40, 4 x 16 1084 / 898; ResNet-50 in units of four, 4 x 32 4400 / 4202), and not where the
 // copies are much longer than the rows (ResNet-18-GN at 32 x 32, 8 x 32, whose last maps are 4 x 4: 1678 / 1754 with them at 7 x 4).
-static thread_local int tl_rows_as_they_are = 0;
-RowsAsTheyAre::RowsAsTheyAre() { ++tl_rows_as_they_are; }
-RowsAsTheyAre::~RowsAsTheyAre() { --tl_rows_as_they_are; }
-
 static bool widened(const Geo &g, int mode, Geo &g2)
 {
-    if (mode == MODE_WEIGHTED || !g.bf16 || g.has_bias || tl_rows_as_they_are || !plan_crowd() || g.n < 12) return false;
+    if (mode == MODE_WEIGHTED || !g.bf16 || g.has_bias || !g.copies || !plan_crowd() || g.n < 12) return false;
     g2 = g;
     if (g.kh == 1 && g.kw == 1 && g.pad == 0) {
         const int S = g.oh * g.ow;

@@ -38,14 +38,14 @@ struct Geo {
     // Calls of bf16 layers on finished fp32 blocks.  Clip-weighted ones: the factors meet those (conv_scales_blocks), never an operand that is
     // rounded again.  Per-example ones: a squared norm is a sum of squares, never one of products that may cancel (gram.hip).
     int blocks;
+    // Per-example batch calls: the workspace has room for operands whose rows get another length (dp_batch_workspace_bytes).
+    int copies;
 };
 
 // Contraction modes of the conv / dense kernels.
 enum Mode { MODE_NORM = 0, MODE_MATERIALISE = 1, MODE_WEIGHTED = 2 };
 
 size_t conv_ws_bytes(const Geo &g, int mode);
-// While one lives, this thread's plans never bring rows to another length (dp_per_example_grad_static: the copies do not fit its scratch)
-struct RowsAsTheyAre { RowsAsTheyAre(); ~RowsAsTheyAre(); };
 const char *conv_variant_name(const Geo &g, int mode, bool shared);
 void c3_set_forced_crowd(int v);      // conv3x3.hip: plan as alone (0), as in a shared launch (1), or by the open batch (-1)
 dp_status launch_conv(const Geo &g, int mode, const void *x, const void *dy, float *out_w, float *out_b,

@@ -45,7 +45,6 @@ size_t dp_static_scratch_bytes(void) { return SCRATCH_BYTES; }
 dp_status dp_per_example_grad_static(const dp_layer_desc *desc, const void *x, const void *dy, float *g_w, float *g_b,
                                      size_t g_stride, float *sqnorm, dp_stream stream)
 {
-    const dp::RowsAsTheyAre rows;
     const size_t need = dp_workspace_bytes(desc, DP_WS_PER_EXAMPLE_GRAD);     // 0 on a bad descriptor: reported below
     // A dense layer of several tokens may need more (a slot for every 64 x 64 of the gradient) than what decides whether it is
     // taken: then its examples go through the scratch a piece at a time, which changes none of their numbers.

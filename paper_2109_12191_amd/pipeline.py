@@ -363,7 +363,7 @@ class PrivatiseStep:
             for i, l in enumerate(self.layers):
                 d = B.make_desc(l, n, self.wl.dtype)
                 if self._choose(l, "auto", n) == "recompute" and B.dp_kernel_variant(d, sums):
-                    need = max(B.dp_workspace_bytes(d, norms), B.dp_workspace_bytes(d, sums), 16)
+                    need = max(B.dp_batch_workspace_bytes(d, norms), B.dp_workspace_bytes(d, sums), 16)
                     over[i] = _align256(need) - 4 * n * (self.pw[i] + self.pb[i])
             while over and sum(over.values()) + 256 > 0:
                 del over[max(over, key=over.get)]
@@ -381,7 +381,7 @@ class PrivatiseStep:
             return [False] * len(self.layers)
         if tensors not in self._inside:
             descs, need = self._workspaces(tensors)
-            self._inside[tensors] = [now != form and b > max(16, B.dp_workspace_bytes(d, B.DP_WS_PER_EXAMPLE_GRAD | B.DP_RECOMPUTE_BLOCKS))
+            self._inside[tensors] = [now != form and b > max(16, B.dp_batch_workspace_bytes(d, B.DP_WS_PER_EXAMPLE_GRAD | B.DP_RECOMPUTE_BLOCKS))
                                      for d, b, now, form in zip(descs, need, self._forms(tensors), self.form)]
         return self._inside[tensors]
 
@@ -407,9 +407,9 @@ class PrivatiseStep:
         if tensors not in self._needs:
             descs = [B.make_desc(l, self.wl.n * tensors, self.wl.dtype) for l in self.layers]
             blocks = self._blocks(tensors)
-            need = [max(16, B.dp_workspace_bytes(d, B.DP_WS_PER_EXAMPLE_GRAD | blocks),
+            need = [max(16, B.dp_batch_workspace_bytes(d, B.DP_WS_PER_EXAMPLE_GRAD | blocks),
                         B.dp_workspace_bytes(d, B.DP_WS_RECOMPUTE | blocks) if form == "recompute" else 0,
-                        B.dp_unit_workspace_bytes(d, self.clip_unit) if self.clip_unit > 1 else 0)
+                        B.dp_batch_workspace_bytes(d, B.DP_WS_PER_EXAMPLE_GRAD, self.clip_unit) if self.clip_unit > 1 else 0)
                     for d, form in zip(descs, self._forms(tensors))]
             self._needs[tensors] = descs, need
         return self._needs[tensors]

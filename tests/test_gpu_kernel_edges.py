@@ -187,7 +187,8 @@ _WIDENED = [conv(64, 96, 1, 1, 7), conv(40, 33, 1, 1, 9), conv(33, 64, 1, 1, 13)
 
 @pytest.mark.parametrize("several", [False, True])
 @pytest.mark.parametrize("materialise", [False, True])
-def test_rows_brought_to_another_length(materialise, several):
+@pytest.mark.parametrize("room", [True, False])
+def test_rows_brought_to_another_length(materialise, several, room):
     """In one batch call with room for the copies alone (F32_TOL: the products of bf16 inputs are exact, sums are fp32), examples in one
     tensor or each in one of its own.  What is around the inputs is not a number."""
     n = 13
@@ -212,7 +213,8 @@ def test_rows_brought_to_another_length(materialise, several):
                 own[8: 8 + n * per] = t.reshape(-1)
                 kept.append(own)
                 ptrs[side].append(own[8:].data_ptr())
-    sizes = [dp.dp_workspace_bytes(d) for d in descs]
+    sizes = [dp.dp_batch_workspace_bytes(d) if room else dp.dp_workspace_bytes(d) for d in descs]      # (without room: read in place)
+    assert all(dp.dp_batch_workspace_bytes(d) > dp.dp_workspace_bytes(d) for d in descs)
     wss = [torch.full((b,), 255, dtype=torch.uint8, device="cuda:0") for b in sizes]
     stride = max(l.pw for l in _WIDENED) + 3 & ~3
     g = [torch.full((n, stride), float("nan"), dtype=torch.float32, device="cuda:0") for _ in descs]

@@ -120,3 +120,23 @@ def test_fp32_row_plans_keep_the_table_of_runs_clear_of_chunks_and_epilogue(tmp_
                     os.path.join(here, "rows_regions.cpp"), "-o", exe], check=True)
     run = subprocess.run([exe], capture_output=True, text=True)
     assert run.returncode == 0, run.stdout
+
+
+def test_room_for_copies_is_asked_for_by_batch_calls_alone():
+    """Layers whose rows batch calls bring to another length: the copies of both operands come on top of what a call needs, for units too;
+    nothing else asks for more."""
+    from workloads import conv, dense, gn_affine
+    for layer, n, unit in ((conv(64, 256, 1, 1, 57), 64, 1), (conv(64, 64, 3, 1, 40), 64, 1), (conv(512, 512, 1, 1, 13), 64, 2), (conv(3, 64, 7, 2, 60), 16, 2)):
+        d = dp.make_desc(layer, n, "bf16")
+        least = dp.dp_unit_workspace_bytes(d, unit)
+        assert unit > 1 or least == dp.dp_workspace_bytes(d)
+        copies = 2 * n * (layer.cin * layer.h * layer.w + layer.cout * layer.oh * layer.ow)
+        assert least < dp.dp_batch_workspace_bytes(d, dp.DP_WS_PER_EXAMPLE_GRAD, unit) and dp.dp_batch_workspace_bytes(d, clip_unit=unit) >= copies
+        assert dp.dp_batch_workspace_bytes(d, dp.DP_WS_RECOMPUTE) == dp.dp_workspace_bytes(d, dp.DP_WS_RECOMPUTE)
+    assert dp.dp_workspace_bytes(dp.make_desc(conv(64, 256, 1, 1, 57), 64, "bf16")) < 17 << 20
+    for layer, n, dtype in ((conv(64, 256, 1, 1, 56), 64, "bf16"), (conv(64, 256, 1, 1, 57), 64, "f32"), (conv(64, 256, 1, 1, 57), 8, "bf16"),
+                            (conv(64, 256, 1, 1, 57, bias=True), 64, "bf16"), (dense(64, 64, 3), 64, "bf16"), (gn_affine(64, 9, 8), 64, "bf16")):
+        d = dp.make_desc(layer, n, dtype)
+        assert dp.dp_batch_workspace_bytes(d) == dp.dp_workspace_bytes(d)
+        assert dp.dp_batch_workspace_bytes(d, clip_unit=4) == dp.dp_unit_workspace_bytes(d, 4)
+    assert dp.dp_batch_workspace_bytes(d, 3) == 0 and dp.dp_batch_workspace_bytes(d, dp.DP_WS_PER_EXAMPLE_GRAD, 3) == 0
