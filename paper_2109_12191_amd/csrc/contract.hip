@@ -1775,6 +1775,8 @@ static bool subsampled(const Geo &g, int mode, Geo &g2)
 // micro-step on eight streams, general kernel / copies: 8 examples 655 / 655, at 192 x 192 449 / 476; 16 examples 982 / 929; on one stream
 // 2 x 12 1570 / 1328; ResNet-18-GN at 40 x 40, 4 x 16 1084 / 898; ResNet-50 in units of four, 4 x 32 4400 / 4202), and not where the
 // copies are much longer than the rows (ResNet-18-GN at 32 x 32, 8 x 32, whose last maps are 4 x 4: 1678 / 1754 with them at 7 x 4).
+// A value of X that is not finite in the last columns of a row meets the zeros behind the row of dY, as in the raw-row kernel's own widths that are no
+// multiple of 8: then the taps to the left of those that read it are no numbers either (the norm is not finite either way).
 static bool widened(const Geo &g, int mode, Geo &g2)
 {
     if (mode == MODE_WEIGHTED || !g.bf16 || g.has_bias || !g.copies || !plan_crowd() || g.n < 12) return false;

@@ -35,9 +35,9 @@ PHASE_MICRO_STEP_BYTES = 1.25e9
 #   one / 192 2840 / 2470, 64: one by one / 256 3452 / 3223 (128: 6101 / 6338, a loss inside the line).  Beyond, ResNet-20, 256: one by one /
 #   512 2493 / 2411; ResNet-18-GN, 48: 192 / 384 2470 / 2556, 64: 256 / 512 3223 / 7084
 PHASE_EXAMPLES = 256
-#   and of micro-steps of one or two examples.  ResNet-50, 64 x 1: one by one / 16 / 32 / 64 10476 / 2672 / 2279 / 2224; 32 x 2: 8221 /
-#   2663 (16) / 2310 / 2236
-PHASE_EXAMPLES_STORED = 64
+#   and of micro-steps of one or two examples.  ResNet-50, 64 x 1: one by one / 16 / 32 / 64 9682 / 2774 / 2476 / 2481; 32 x 2: 7984 /
+#   2821 (16) / 2502 / 2498
+PHASE_EXAMPLES_OF_SMALL = 64
 # And no phase is so large that a layer falls back to the kernel that gathers its operands element by element, because the rewritten
 # operands of a faster one outgrow their share of the workspace: ResNet-18-GN at 40 x 40, 64 examples 3656 / 5083 (two micro-steps) / 7188
 # (four), 24 (8 micro-steps): 3097 / 3028 (four) / 3825 (eight).
@@ -424,7 +424,7 @@ class PrivatiseStep:
         wl = self.wl
         if sum(self._example_bytes) * wl.n > PHASE_MICRO_STEP_BYTES:
             return 1
-        most = max(1, (PHASE_EXAMPLES_STORED if wl.n <= 2 else PHASE_EXAMPLES) // wl.n)
+        most = max(1, (PHASE_EXAMPLES_OF_SMALL if wl.n <= 2 else PHASE_EXAMPLES) // wl.n)
         matrix = 4 * self.rows * self.p_mat
         phases = max(1, -(-wl.accum // most))
         alone = None
