@@ -33,7 +33,7 @@
 // A SIMD gives MFMAs and vector instructions their turns (a 16x16x32 MFMA takes 18.8 cycles, every vector instruction beside it 2.6 more), so what
 // bounds a full chip is their sum: 3.2 us per chunk of two rows of 64 -> 64 on 56 wide maps, half of it MFMAs.
 // MI355X, per-example call alone, fp32 instruction -> this: 64 examples of 64 -> 64 3x3 with a bias on 56 x 56: 194 -> 100 us (154 TFLOP/s), 256:
-// 800 -> 433; 256 of 16 -> 16 on 32 x 32: 30 -> 20; 40 of 40 -> 72 5x5 stride 2 with a bias on 45 x 37: 105 -> 78.  Where it is chosen: rows_choice.
+// 800 -> 433; 256 of 16 -> 16 on 32 x 32: 30 -> 20; 40 of 40 -> 72 5x5 stride 2 with a bias on 45 x 37: 105 -> 80.  Where it is chosen: rows_choice.
 #include "group.h"
 #include "internal.h"
 #include "pieces.h"
