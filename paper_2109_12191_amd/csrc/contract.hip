@@ -824,32 +824,6 @@ __global__ void __launch_bounds__(THREADS, 2) conv_contract_kernel(const Grouped
 // piece of the tensor's very last row gets its valid bytes through registers.
 // Weighted form: the clip factor is applied in fp32 to the finished per-example tile (a second set of
 // accumulators), acc_total += f_i * acc_i -- no second rounding of dY to bf16.
-// lane L: LDS[lds_base + 16 L .. +16) <- 16 bytes at base + byte_off.  base and lds_base are wave-uniform
-// (already in scalar registers).
-__device__ __forceinline__ void lds_direct_16(unsigned long long base, unsigned byte_off, unsigned lds_base)
-{
-    asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(byte_off), "s"(base), "s"(lds_base) : "memory");
-}
-// the same with only the lanes of `lanes` (wave-uniform, never empty) taking part: the others fetch nothing and leave
-// their 16 bytes of LDS as they are.  The instruction is issued once either way, so counted waits stay exact.
-__device__ __forceinline__ void lds_direct_16_lanes(unsigned long long base, unsigned byte_off, unsigned lds_base, unsigned long long lanes)
-{
-    unsigned long long saved;
-    asm volatile("s_mov_b32 m0, %3\n\t"
-                 "s_mov_b64 %0, exec\n\t"
-                 "s_mov_b64 exec, %4\n\t"
-                 "global_load_lds_dwordx4 %1, %2\n\t"
-                 "s_mov_b64 exec, %0"
-                 : "=&s"(saved)
-                 : "v"(byte_off), "s"(base), "s"(lds_base), "s"(lanes)
-                 : "memory");
-}
-template <int N>
-__device__ __forceinline__ void wait_vmcnt()
-{
-    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
-}
-
 // Wait until at most `after` (wave-uniform) of this wave's vector memory operations are outstanding, rounded down to
 // a count the instruction can encode (six bits) from a short menu: waiting for more than asked is always safe.
 __device__ __forceinline__ void wait_outstanding(int after)

@@ -27,6 +27,7 @@
 
 #include <atomic>
 #include <cstdio>
+#include <utility>
 
 namespace dp {
 
@@ -46,42 +47,58 @@ struct C3Args {
     int n, cin, cout, h;              // h: OUTPUT height (= input height for stride 1)
     int hin;                          // input height
     int tiles_co, tiles_ci;
-    int chunks;                       // ceil(H / R)
-    int ksplit, chunks_per_split;     // per-example mode: K slices
+    int ksplit, stages_per_split;     // per-example mode: K slices, in stages (C3Cfg)
     int ex_per_split;                 // weighted mode: examples per workgroup (ksplit = example ranges)
     int variant;                      // which body conv3x3_any_kernel runs for this layer (C3_ANY_* below)
     int rows, unit;                   // per-example modes: rows of results, examples of each (Geo::unit)
     int slice_ex;                     // per-example mode, sliced: > 0: the slices are ranges of this many examples of a unit
 };
 
-constexpr int odd16(int bytes) { return ((bytes / 16) | 1) * 16; }
 constexpr int C3_RP = 292;                           // floats per row staged by the store epilogue: 288 + 4
 constexpr int C3_STORE_LDS = 4 * 8 * C3_RP * 4;      // bytes the store epilogue needs: 4 waves x 8 rows
 
-// W is the OUTPUT row width.  Stride 1 reads X itself (input width W).  Stride 2 reads a copy of X
-// whose rows have been split by column parity (deinterleave2_kernel below): each row is
-//     O'[c] = X[2c - 1], c = 0 .. OWP+7   (zero for 2c-1 outside the row)   then   E[c] = X[2c], c = 0 .. OWP-1,
-// so that tap kw = 0 is O'[ow], kw = 1 is E[ow], kw = 2 is O'[ow + 1]: contiguous runs again.
+// How a layer's rows lie in LDS.  A workgroup walks STAGES of RPS output rows: the RPS rows of dY and the STRIDE * RPS rows of X below
+// them, for its 64 channels of each.  A stage is SG groups, a group is RPG consecutive rows of 64 channels: in memory one run of bytes per
+// channel, in LDS the 16-byte pieces of a run one after the other, channels PA (PX) pieces apart.  The odd pitches make the operand
+// reads of 16 channels touch 16 different 16-byte bank groups, and 64 channels a whole number of LDS-direct wave instructions: PA of them.
+// (Rows of 7 values may start between two dwords: their pieces are counted from the dword that the run starts in.)
+// D stages are in flight ahead of the one whose products run; the rings are what two workgroups of a compute unit have room for.
 template <int W, int STRIDE> struct C3Cfg {
-    static constexpr int OWP = (W + 7) / 8 * 8;
-    static constexpr int R = (STRIDE == 1) ? ((OWP == 8) ? 8 : 224 / OWP)            // output rows per chunk
-                                           : ((OWP == 16) ? 5 : (OWP == 32 ? 3 : 8));
-    static constexpr int KSTEPS = R * OWP / 16;
-    static constexpr int WP = (STRIDE == 1) ? OWP + 8 : 2 * OWP + 8;                  // elements per staged X row
-    static constexpr int E_OFF = OWP + 8;                                           // stride 2: where E starts in a row
-    static constexpr int XROWS = (STRIDE == 1) ? R + 2 : 2 * R + 1;
-    static constexpr int PPR = OWP / 8, XPR = WP / 8;         // 16-byte pieces per LDS row
-    static constexpr int PA = odd16(R * OWP * 2);             // bytes per co in LDS (odd multiple of 16)
-    static constexpr int PX = odd16(XROWS * WP * 2);          // bytes per ci in LDS
-    static constexpr int NPA = 64 * R * PPR, NPX = 64 * XROWS * XPR;
-    static constexpr int PA_T = (NPA + C3_THREADS - 1) / C3_THREADS;
-    static constexpr int PX_T = (NPX + C3_THREADS - 1) / C3_THREADS;
-    static constexpr int LDS = (64 * PA + 64 * PX > C3_STORE_LDS) ? 64 * PA + 64 * PX : C3_STORE_LDS;
-    static constexpr bool ALIGNED_A = (W % 8 == 0);
-    static_assert(OWP == 8 || OWP == 16 || OWP == 32 || OWP == 56, "supported row widths");
-    static_assert(R * OWP % 16 == 0, "whole MFMA K steps");
-    static_assert(LDS <= 80 * 1024, "two workgroups per CU");
+    static constexpr int XW = W * STRIDE;                    // row length of X
+    static constexpr int ROW_A = 2 * W, ROW_X = 2 * XW;      // bytes
+    static constexpr int PPR = (W + 7) / 8;                  // K steps of a pair of output rows: 8 columns of either
+    static constexpr bool ODD = W % 2 != 0;                  // rows of dY (stride 1: X too) start between dwords
+    static constexpr bool ODD_X = XW % 2 != 0;
+    static constexpr int RPG = STRIDE == 2 ? (W == 28 ? 2 : 4) : (W == 56 ? 1 : (W >= 28 ? 2 : (W >= 14 ? 4 : 8)));
+    static constexpr int SG = (STRIDE == 1 && W == 56) ? 2 : 1;
+    static constexpr int RPS = RPG * SG, PAIRS = RPS / 2;
+    static constexpr int GB_A = RPG * ROW_A, GB_X = RPG * STRIDE * ROW_X;      // bytes of a channel's run
+    static constexpr int NA = (GB_A + (ODD ? 2 : 0) + 15) / 16, NX = (GB_X + (ODD_X ? 2 : 0) + 15) / 16;
+    static constexpr int PA = NA | 1, PX = NX | 1;
+    static constexpr int GROUP_A = PA * 1024, GROUP_X = PX * 1024;
+    static constexpr int STAGE_A = SG * GROUP_A, STAGE_X = SG * GROUP_X;
+    static constexpr int D = STRIDE == 2 ? (PX > 15 ? 1 : 2) : (SG == 2 ? 1 : (PA == 7 ? 3 : 2));
+    static constexpr int ZEROS = 128;                        // bytes of zeros at the start: rows outside the image
+    static constexpr int RING_X = ZEROS, RING_A = ZEROS + (D + 1) * STAGE_X;
+    static constexpr int END = RING_A + (D + 2) * STAGE_A;   // dY one stage further: its next row meets this stage's last row of X
+    static constexpr int LDS = END > C3_STORE_LDS ? END : C3_STORE_LDS;
+    static constexpr int QX = SG * PX, QA = SG * PA;         // wave instructions of a stage
+    static constexpr int UX = (QX + 3) / 4, UA = (QA + 3) / 4;
+    static constexpr int BUNDLE = (QX + QA + 3) / 4;         // most of them that a wave issues per stage
+    static constexpr bool PARTIAL_A = ROW_A % 16 != 0, PARTIAL_X = ROW_X % 16 != 0;     // a tensor may end inside a piece
+    // where local row r (of a stage) of the first channel starts, for rows that start at a dword
+    static constexpr int at_a(int r) { return (r / RPG) * GROUP_A + (r % RPG) * ROW_A; }
+    static constexpr int at_x(int r) { return (r / (RPG * STRIDE)) * GROUP_X + (r % (RPG * STRIDE)) * ROW_X; }
+    static_assert(RPS % 2 == 0, "pairs of rows");
+    static_assert(LDS <= 81920 - 256, "two workgroups per CU");
+    static_assert(PPR * 16 * STRIDE <= ZEROS, "a row of zeros");
 };
+
+constexpr int c3_rows_per_stage(int ow, int stride) { return stride == 2 ? (ow == 28 ? 2 : 4) : (ow >= 28 ? 2 : (ow >= 14 ? 4 : 8)); }
+static_assert(C3Cfg<56, 1>::RPS == c3_rows_per_stage(56, 1) && C3Cfg<32, 1>::RPS == c3_rows_per_stage(32, 1) && C3Cfg<28, 1>::RPS == c3_rows_per_stage(28, 1) &&
+              C3Cfg<16, 1>::RPS == c3_rows_per_stage(16, 1) && C3Cfg<14, 1>::RPS == c3_rows_per_stage(14, 1) && C3Cfg<8, 1>::RPS == c3_rows_per_stage(8, 1) &&
+              C3Cfg<7, 1>::RPS == c3_rows_per_stage(7, 1) && C3Cfg<28, 2>::RPS == c3_rows_per_stage(28, 2) && C3Cfg<14, 2>::RPS == c3_rows_per_stage(14, 2) &&
+              C3Cfg<7, 2>::RPS == c3_rows_per_stage(7, 2), "what the host plans");
 
 // What a workgroup does with finished accumulators (all of K of one example): squared norm of
 // its 64 x 64 x 9 block and the optional store in the framework's [Cout, Cin, 3, 3] order.
@@ -97,10 +114,15 @@ __device__ __forceinline__ void c3_epilogue(const f32x16 (&acc)[9], const C3Args
     float ss = 0.0f;
     const bool store = a.out_w != nullptr;
     float *out = a.out_w + (size_t)i * a.out_stride;
+    const bool ci_there = ci0 + wn * 32 + (lane & 31) < a.cin;
+    const int co_there = a.cout - (co0 + wm * 32 + (lane >> 5) * 4);
 #pragma unroll
-    for (int t = 0; t < 9; ++t)
+    for (int r = 0; r < 16; ++r) {                    // (what stands for channels beyond the layer does not count)
+        float s = 0.0f;
 #pragma unroll
-        for (int r = 0; r < 16; ++r) ss += acc[t][r] * acc[t][r];     // channels beyond the layer are exact zeros
+        for (int t = 0; t < 9; ++t) s += acc[t][r] * acc[t][r];
+        ss += ci_there && (r >> 2) * 8 + (r & 3) < co_there ? s : 0.0f;
+    }
     // wave-uniform: whole 32-channel blocks, 16-byte aligned rows
     const bool via_lds = store && lds != nullptr && (a.cin % 32 == 0) && (a.out_stride % 4 == 0) &&
                          ((reinterpret_cast<uintptr_t>(a.out_w) & 15u) == 0);
@@ -194,17 +216,59 @@ __device__ __forceinline__ void c3_add_to_accumulator(const f32x16 (&acc)[9], co
 // is staged; added to the accumulator, or to the workspace when the examples are split into ranges).
 enum { C3_FULL = 0, C3_SLICED = 1, C3_WEIGHTED = 2 };
 
-// What one workgroup does; `bid` is its number within its layer.  AT: the operands are arrays of example addresses (a body of its
-// own: the accumulators leave no registers for both ways of addressing).
-template <int W, int MODE, int STRIDE, bool AT>
+// One 16-byte piece of an LDS row as the MFMA operand it is: columns 8j .. 8j + 7 of a row, those at or beyond the row's end zero.
+// `row`: the row's first byte; rows of 7 values: the dword it starts in, `bits` 16 where that is its high half.
+template <int W, int J>
+__device__ __forceinline__ uint4 c3_piece(const char *row, unsigned bits)
+{
+    constexpr int LEFT = W - 8 * J;                  // columns there are
+    const char *p = row + 16 * J;
+    if constexpr (W % 8 == 0) {
+        return *reinterpret_cast<const uint4 *>(p);
+    } else if constexpr (W % 2 != 0) {
+        static_assert(W == 7, "one piece");
+        const uint32_t *d = reinterpret_cast<const uint32_t *>(p);
+        const uint32_t d0 = d[0], d1 = d[1], d2 = d[2], d3 = d[3];
+        return make_uint4(funnel(d1, d0, bits), funnel(d2, d1, bits), funnel(d3, d2, bits), (bits ? d3 >> 16 : d3) & 0xFFFFu);
+    } else if constexpr (W % 4 == 0) {
+        const uint2 a = *reinterpret_cast<const uint2 *>(p);
+        if constexpr (LEFT <= 4) return make_uint4(a.x, a.y, 0u, 0u);
+        const uint2 b = *reinterpret_cast<const uint2 *>(p + 8);
+        return make_uint4(a.x, a.y, b.x, b.y);
+    } else {
+        const uint32_t *d = reinterpret_cast<const uint32_t *>(p);
+        return make_uint4(d[0], LEFT > 2 ? d[1] : 0u, LEFT > 4 ? d[2] : 0u, LEFT > 6 ? d[3] : 0u);
+    }
+}
+
+// f(0), f(1), ... with constants
+template <int... J, typename F>
+__device__ __forceinline__ void c3_each(std::integer_sequence<int, J...>, F f) { (f(std::integral_constant<int, J>{}), ...); }
+
+// the high (low) halves of two dwords side by side
+__device__ __forceinline__ uint32_t c3_high(uint32_t second, uint32_t first) { return __builtin_amdgcn_perm(second, first, 0x07060302u); }
+__device__ __forceinline__ uint32_t c3_low(uint32_t second, uint32_t first) { return __builtin_amdgcn_perm(second, first, 0x05040100u); }
+
+// the three taps of kernel row kh
+__device__ __forceinline__ void c3_taps(f32x16 (&acc)[9], int kh, uint4 dy, uint4 b0, uint4 b1, uint4 b2)
+{
+    const bf16x8 va = __builtin_bit_cast(bf16x8, dy);
+    acc[kh * 3 + 0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va, __builtin_bit_cast(bf16x8, b0), acc[kh * 3 + 0], 0, 0, 0);
+    acc[kh * 3 + 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va, __builtin_bit_cast(bf16x8, b1), acc[kh * 3 + 1], 0, 0, 0);
+    acc[kh * 3 + 2] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va, __builtin_bit_cast(bf16x8, b2), acc[kh * 3 + 2], 0, 0, 0);
+}
+
+struct C3Row { unsigned at, bits; };       // where a row lies in LDS; rows of 7: how far into its first dword it starts
+
+// What one workgroup does; `bid` is its number within its layer.
+template <int W, int MODE, int STRIDE>
 __device__ __forceinline__ void conv3x3_body(const C3Args &a, const unsigned bid)
 {
     constexpr bool WEIGHTED = MODE == C3_WEIGHTED;
     using C = C3Cfg<W, STRIDE>;
-    constexpr int XB = 6;                             // X pieces per thread in flight at once
+    using pieces_t = std::make_integer_sequence<int, C::PPR>;
     extern __shared__ __attribute__((aligned(16))) char lds[];
     __shared__ float red[4];
-    char *sX = lds, *sA = lds + 64 * C::PX;
 
     // consecutive hardware workgroup ids rotate over the 8 XCDs; give each XCD a run of
     // consecutive logical ids (the slices and tiles of the same examples share its L2)
@@ -216,22 +280,170 @@ __device__ __forceinline__ void conv3x3_body(const C3Args &a, const unsigned bid
     const int split = wg % a.ksplit;
     const int unit = wg / a.ksplit;                   // (example, tile); weighted: tile
     const int result = WEIGHTED ? 0 : unit / tiles;   // row of results
-    const int i_first = WEIGHTED ? split * a.ex_per_split : result * a.unit + (MODE == C3_SLICED ? split * a.slice_ex : 0);
-    const int i_last = WEIGHTED ? min(a.n, i_first + a.ex_per_split) : i_first + (MODE == C3_SLICED ? max(1, a.slice_ex) : a.unit);
+    const int i_first = __builtin_amdgcn_readfirstlane(WEIGHTED ? split * a.ex_per_split : result * a.unit + (MODE == C3_SLICED ? split * a.slice_ex : 0));
+    const int i_last = __builtin_amdgcn_readfirstlane(WEIGHTED ? min(a.n, i_first + a.ex_per_split) : i_first + (MODE == C3_SLICED ? max(1, a.slice_ex) : a.unit));
     const int tile = unit - result * tiles;
     const int tco = tile / a.tiles_ci, tci = tile - tco * a.tiles_ci;
-    const int co0 = tco * 64, ci0 = tci * 64;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int co0 = __builtin_amdgcn_readfirstlane(tco * 64), ci0 = __builtin_amdgcn_readfirstlane(tci * 64);
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int wm = wave >> 1, wn = wave & 1;
-    const int H = a.h;
+    const int half = lane >> 5;
+    const int H = a.h, hin = a.hin;
+    const int cin = a.cin, cout = a.cout;
 
-    // element offsets count from the start of the whole tensor (all n examples, below 2^31) or, where every example has an
-    // address of its own, from the dword it starts in: whole-dword windows (10 elements from an even element index) may
-    // reach into the neighbouring example of one tensor but never outside a tensor
-    constexpr int XROW = (STRIDE == 1) ? W : C::WP;               // elements per row of the X tensor read here
-    const int x_ex = a.cin * a.hin * XROW, dy_ex = a.cout * H * W;    // elements per example
-    const uint16_t *xt = static_cast<const uint16_t *>(a.x), *dyt = static_cast<const uint16_t *>(a.dy);
-    int x_end = a.n * x_ex, dy_end = a.n * dy_ex;
+    // Stages of an example: all of them, or a slice [k_begin, k_end).  A slice that starts inside the image has the stage before it as
+    // well, which gives its first rows their upper neighbours in dY and no products; its last rows need the stage behind it of dY.
+    const int n_stages = (H + C::RPS - 1) / C::RPS;
+    const bool cut = MODE == C3_SLICED && a.slice_ex == 0;
+    const int k_begin = cut ? split * a.stages_per_split : 0, k_end = cut ? min(n_stages, k_begin + a.stages_per_split) : n_stages;
+    const int s_begin = __builtin_amdgcn_readfirstlane(STRIDE == 1 && k_begin > 0 ? k_begin - 1 : k_begin);
+    const int x_stages = k_end - s_begin, a_stages = min(n_stages, k_end + 1) - s_begin;
+    const int T = (i_last - i_first) * x_stages, TA = (i_last - i_first) * a_stages;
+
+    // ---- global -> LDS.  Wave instruction q of a stage moves pieces 64 q .. 64 q + 63; X's are dealt to the waves from the first, dY's from the last.
+    // Pieces that hold nothing (padding, channels beyond the layer, rows below the image) fetch something of the same example, which
+    // no product reads or no result shows; so does a piece that the example's end cuts (mend() below fills it in).
+    const int x_chan = hin * C::XW, a_chan = H * W;                // elements of a channel
+    const size_t x_ex = (size_t)cin * x_chan, a_ex = (size_t)cout * a_chan;
+    const int first_x = wave, first_a = 3 - wave;
+    struct Piece { int ch, sub, pc; };
+    auto piece = [&](int q, int pitch) {
+        const int g = q / pitch, id = (q - g * pitch) * 64 + lane;
+        return Piece{id / pitch, g, id % pitch};
+    };
+    // byte offset of a lane's piece from the dword that its example's stage starts in; LAST: the example's last stage (at most
+    // that many rows of it are there).  odd: the example starts in the high half of that dword
+    auto off_x = [&](int u, unsigned odd, bool last) {
+        const Piece p = piece(first_x + 4 * u, C::PX);
+        const int c = min(ci0 + p.ch, cin - 1);
+        unsigned e = (unsigned)c * (unsigned)x_chan + odd;
+        const int pieces = C::ODD_X ? (C::GB_X + 2 * (int)(e & 1u) + 15) / 16 : C::NX;
+        const int in_run = p.sub * C::GB_X + min(p.pc, pieces - 1) * 16;
+        if constexpr (C::ODD_X) e &= ~1u;
+        const unsigned off = 2u * e + (unsigned)in_run;
+        if (!last) return off;
+        const int before = (n_stages - 1) * C::SG * C::GB_X;       // bytes of a channel above its last stage
+        const bool there = in_run < 2 * x_chan - before + (C::ODD_X ? 2 : 0);
+        return there && (size_t)off + before + 16 <= 2 * (x_ex + odd) ? off : 0u;
+    };
+    auto off_a = [&](int u, unsigned odd, bool last) {
+        const Piece p = piece(first_a + 4 * u, C::PA);
+        const int c = min(co0 + p.ch, cout - 1);
+        unsigned e = (unsigned)c * (unsigned)a_chan + odd;
+        const int pieces = C::ODD ? (C::GB_A + 2 * (int)(e & 1u) + 15) / 16 : C::NA;
+        const int in_run = p.sub * C::GB_A + min(p.pc, pieces - 1) * 16;
+        if constexpr (C::ODD) e &= ~1u;
+        const unsigned off = 2u * e + (unsigned)in_run;
+        if (!last) return off;
+        const int before = (n_stages - 1) * C::SG * C::GB_A;
+        const bool there = in_run < 2 * a_chan - before + (C::ODD ? 2 : 0);
+        return there && (size_t)off + before + 16 <= 2 * (a_ex + odd) ? off : 0u;
+    };
+    unsigned xo[C::UX], xl[C::UX], ao[C::UA], al[C::UA];
+#pragma unroll
+    for (int u = 0; u < C::UX; ++u) { xo[u] = off_x(u, 0u, false); xl[u] = off_x(u, 0u, true); }
+#pragma unroll
+    for (int u = 0; u < C::UA; ++u) { ao[u] = off_a(u, 0u, false); al[u] = off_a(u, 0u, true); }
+    const unsigned lds0 = __builtin_amdgcn_readfirstlane((unsigned)(size_t)lds);
+    auto x_at = [&](int i) { return reinterpret_cast<unsigned long long>(example_at_uniform<uint16_t>(a.x, a.x_tab, i, x_ex)); };
+    auto a_at = [&](int i) { return reinterpret_cast<unsigned long long>(example_at_uniform<uint16_t>(a.dy, a.dy_tab, i, a_ex)); };
+    struct Stream { unsigned long long base; int i, s, slot; };
+    auto fetch_x = [&](Stream &f) {
+        const bool last = f.s == n_stages - 1;
+        const unsigned odd = C::ODD_X ? (unsigned)(f.base >> 1) & 1u : 0u;
+        const unsigned long long b = (f.base & ~3ull) + (unsigned long long)f.s * (C::SG * C::GB_X);
+        const unsigned dst = lds0 + C::RING_X + f.slot * C::STAGE_X;
+#pragma unroll
+        for (int u = 0; u < C::UX; ++u) {
+            const int q = first_x + 4 * u;
+            if ((C::QX % 4 == 0 || u < C::UX - 1 || q < C::QX)) {
+                const unsigned off = C::ODD_X && odd ? off_x(u, odd, last) : (last ? xl[u] : xo[u]);
+                lds_direct_16(b, off, dst + q * 1024);
+            }
+        }
+        f.slot = f.slot == C::D ? 0 : f.slot + 1;
+        if (++f.s == k_end) {
+            f.s = s_begin;
+            if (++f.i < i_last) f.base = x_at(f.i);
+        }
+    };
+    auto fetch_a = [&](Stream &f) {
+        const bool last = f.s == n_stages - 1;
+        const unsigned odd = C::ODD ? (unsigned)(f.base >> 1) & 1u : 0u;
+        const unsigned long long b = (f.base & ~3ull) + (unsigned long long)f.s * (C::SG * C::GB_A);
+        const unsigned dst = lds0 + C::RING_A + f.slot * C::STAGE_A;
+#pragma unroll
+        for (int u = 0; u < C::UA; ++u) {
+            const int q = first_a + 4 * u;
+            if ((C::QA % 4 == 0 || u < C::UA - 1 || q < C::QA)) {
+                const unsigned off = C::ODD && odd ? off_a(u, odd, last) : (last ? al[u] : ao[u]);
+                lds_direct_16(b, off, dst + q * 1024);
+            }
+        }
+        f.slot = f.slot == C::D + 1 ? 0 : f.slot + 1;
+        if (++f.s == s_begin + a_stages) {
+            f.s = s_begin;
+            if (++f.i < i_last) f.base = a_at(f.i);
+        }
+    };
+    // the piece of an example's last channel that the example's end cuts: its values one by one (by the lane that fetched the rest of its
+    // wave instruction, after that has landed)
+    auto mend_x = [&](int i, int slot) {
+        const unsigned long long base = x_at(i);
+        const unsigned odd = C::ODD_X ? (unsigned)(base >> 1) & 1u : 0u;
+        const uint16_t *src = reinterpret_cast<const uint16_t *>(base & ~3ull);
+        const size_t end = x_ex + odd;
+#pragma unroll 1
+        for (int u = 0; u < C::UX; ++u) {
+            const int q = first_x + 4 * u;
+            const Piece p = piece(q, C::PX);
+            if (q >= C::QX || ci0 + p.ch != cin - 1 || p.pc >= C::NX) continue;
+            const int in_run = p.sub * (C::GB_X / 2) + p.pc * 8;
+            size_t e = (size_t)(cin - 1) * x_chan + odd;
+            if (C::ODD_X) e &= ~(size_t)1;
+            e += (size_t)(n_stages - 1) * (C::SG * C::GB_X / 2) + in_run;
+            if (e >= end || e + 8 <= end) continue;
+            uint16_t *dst = reinterpret_cast<uint16_t *>(lds + C::RING_X + slot * C::STAGE_X + q * 1024 + lane * 16);
+#pragma unroll 1
+            for (int k = 0; e + k < end; ++k) dst[k] = src[e + k];
+        }
+    };
+    auto mend_a = [&](int i, int slot) {
+        const unsigned long long base = a_at(i);
+        const unsigned odd = C::ODD ? (unsigned)(base >> 1) & 1u : 0u;
+        const uint16_t *src = reinterpret_cast<const uint16_t *>(base & ~3ull);
+        const size_t end = a_ex + odd;
+#pragma unroll 1
+        for (int u = 0; u < C::UA; ++u) {
+            const int q = first_a + 4 * u;
+            const Piece p = piece(q, C::PA);
+            if (q >= C::QA || co0 + p.ch != cout - 1 || p.pc >= C::NA) continue;
+            const int in_run = p.sub * (C::GB_A / 2) + p.pc * 8;
+            size_t e = (size_t)(cout - 1) * a_chan + odd;
+            if (C::ODD) e &= ~(size_t)1;
+            e += (size_t)(n_stages - 1) * (C::SG * C::GB_A / 2) + in_run;
+            if (e >= end || e + 8 <= end) continue;
+            uint16_t *dst = reinterpret_cast<uint16_t *>(lds + C::RING_A + slot * C::STAGE_A + q * 1024 + lane * 16);
+#pragma unroll 1
+            for (int k = 0; e + k < end; ++k) dst[k] = src[e + k];
+        }
+    };
+    const bool mends_x = C::PARTIAL_X && ci0 + 64 >= cin, mends_a = C::PARTIAL_A && co0 + 64 >= cout;
+    // clip-weighted form: a wave multiplies the pieces of dY that it fetched by the example's factor, rounded to bf16
+    auto scale_a = [&](int i, int slot) {
+        const float f = a.group_sqnorm ? clip_factor(a.group_sqnorm[i], a.clip_c) : 1.0f;
+#pragma unroll
+        for (int u = 0; u < C::UA; ++u) {
+            const int q = first_a + 4 * u;
+            if ((C::QA % 4 == 0 || u < C::UA - 1 || q < C::QA)) {
+                uint4 *p = reinterpret_cast<uint4 *>(lds + C::RING_A + slot * C::STAGE_A + q * 1024 + lane * 16);
+                const uint4 v = *p;
+                uint32_t t[4] = {v.x, v.y, v.z, v.w};
+                scale_regs<true, 4>(t, f);
+                *p = make_uint4(t[0], t[1], t[2], t[3]);
+            }
+        }
+    };
 
     f32x16 acc[9];
 #pragma unroll
@@ -239,232 +451,167 @@ __device__ __forceinline__ void conv3x3_body(const C3Args &a, const unsigned bid
 #pragma unroll
         for (int r = 0; r < 16; ++r) acc[t][r] = 0.0f;
 
-    const int c_begin = WEIGHTED || MODE == C3_FULL || a.slice_ex ? 0 : split * a.chunks_per_split;
-    const int c_end = WEIGHTED ? a.chunks : min(a.chunks, c_begin + a.chunks_per_split);
-
-    for (int i = i_first; i < i_last; ++i) {
-    int x_base = i * x_ex, dy_base = i * dy_ex;
-    if constexpr (AT && STRIDE == 1) {
-        const uintptr_t at = reinterpret_cast<uintptr_t>(example_at_uniform<uint16_t>(a.x, a.x_tab, i, 0));
-        xt = reinterpret_cast<const uint16_t *>(at & ~(uintptr_t)3);
-        x_base = (int)(at >> 1) & 1;
-        x_end = x_base + x_ex;
+    if (threadIdx.x < C::ZEROS / 16) *reinterpret_cast<uint4 *>(lds + threadIdx.x * 16) = make_uint4(0u, 0u, 0u, 0u);
+    Stream fx{x_at(i_first), i_first, s_begin, 0}, fa{a_at(i_first), i_first, s_begin, 0};
+    int x_issued = 0, a_issued = 0;
+    fetch_a(fa);
+    a_issued = 1;
+#pragma unroll
+    for (int k = 0; k < C::D; ++k) {
+        if (x_issued < T) { fetch_x(fx); ++x_issued; }
+        if (a_issued < TA) { fetch_a(fa); ++a_issued; }
     }
-    if constexpr (AT) {
-        const uintptr_t at = reinterpret_cast<uintptr_t>(example_at_uniform<uint16_t>(a.dy, a.dy_tab, i, 0));
-        dyt = reinterpret_cast<const uint16_t *>(at & ~(uintptr_t)3);
-        dy_base = (int)(at >> 1) & 1;
-        dy_end = dy_base + dy_ex;
-    }
-    const uint32_t *xw = reinterpret_cast<const uint32_t *>(xt);
-    const uint32_t *dyw = reinterpret_cast<const uint32_t *>(dyt);
-    float f = 1.0f;
-    if constexpr (WEIGHTED) f = a.group_sqnorm ? clip_factor(a.group_sqnorm[i], a.clip_c) : 1.0f;
-    for (int chunk = c_begin; chunk < c_end; ++chunk) {
-        const int oh0 = chunk * C::R;
-        if (chunk != c_begin || i != i_first) __syncthreads();    // everyone is done reading the previous chunk
 
-        // ---- issue global loads, then shift / mask / write LDS.  The piece -> address decode is
-        // recomputed per chunk on purpose (the opaque copy of the thread id stops the compiler
-        // from keeping ~80 registers of loop-invariant addresses alive across the MFMA loop).
-        int tid = threadIdx.x;
-        asm volatile("" : "+v"(tid));
-        struct PieceA { int rel, lds_off, hi; bool valid, fast; };
-        auto piece_a = [&](int u) {
-            PieceA p;
-            const int id = tid + C3_THREADS * u;
-            const int co = id / (C::R * C::PPR), q = id - co * (C::R * C::PPR);
-            const int r = q / C::PPR, pc = q - r * C::PPR;
-            const int oh = oh0 + r;
-            p.valid = (id < C::NPA) && (co0 + co < a.cout) && (oh < H);
-            p.rel = dy_base + ((co0 + co) * H + oh) * W + pc * 8;
-            p.lds_off = co * C::PA + (r * C::OWP + pc * 8) * 2;
-            p.hi = W - pc * 8;                        // the row's end
-            p.fast = p.valid && (p.rel & ~1) + 10 <= dy_end;
-            return p;
-        };
-        struct PieceX { int rel, lds_off, lo, hi; bool valid, fast, write; };
-        auto piece_x = [&](int u) {
-            PieceX p;
-            const int id = tid + C3_THREADS * u;
-            const int ch = id / (C::XROWS * C::XPR), q = id - ch * (C::XROWS * C::XPR);
-            const int xr = q / C::XPR, pc = q - xr * C::XPR;
-            p.write = id < C::NPX;
-            p.lds_off = ch * C::PX + (xr * C::WP + pc * 8) * 2;
-            if constexpr (STRIDE == 1) {
-                const int ih = oh0 - 1 + xr;
-                const int iw0 = pc * 8 - 1;
-                p.lo = (pc == 0) ? 1 : 0;
-                p.hi = W - iw0;                           // may be <= 0: an all-zero piece
-                p.valid = p.write && (ci0 + ch < a.cin) && (ih >= 0) && (ih < H) && (p.hi > p.lo);
-                p.rel = x_base + ((ci0 + ch) * H + ih) * W + iw0;
-                p.fast = p.valid && p.rel >= 0 && (p.rel & ~1) + 10 <= x_end;
-            } else {
-                // rows of the parity-split copy: whole aligned pieces, zeros already in place
-                const int ih = 2 * oh0 - 1 + xr;
-                p.lo = 0; p.hi = 8;
-                p.valid = p.write && (ci0 + ch < a.cin) && (ih >= 0) && (ih < a.hin);
-                p.rel = x_base + ((ci0 + ch) * a.hin + ih) * C::WP + pc * 8;
-                p.fast = p.valid;
-            }
-            return p;
-        };
+    // operand reads: lane -> channel (lane & 31) of its 32, and the upper or lower one of a pair of rows
+    const unsigned lane_x = (unsigned)((wn * 32 + (lane & 31)) * (C::PX * 16)), lane_a = (unsigned)((wm * 32 + (lane & 31)) * (C::PA * 16));
+    const int x_odd_chan = C::ODD_X ? ((ci0 + wn * 32 + (lane & 31)) * x_chan) & 1 : 0;
+    const int a_odd_chan = C::ODD ? ((co0 + wm * 32 + (lane & 31)) * a_chan) & 1 : 0;
 
-        static_assert(C::PA_T <= 32 && C::PX_T <= 32, "a bit per piece");
-        uint32_t odd_a = 0, odd_x = 0;                // bit u: piece u is there but its window leaves the tensor
-        // dY first, then X in batches of at most XB pieces per thread: the loads of a batch are all
-        // issued before the first is used, and a batch is small enough to sit in registers beside
-        // the 144 accumulators
+    int ci = i_first, cs = s_begin;                   // stage whose products run
+    int ni = i_first, ns = s_begin;                   // the stage of dY behind it in the stream
+    auto next_a = [&]() {
+        if (++ns == s_begin + a_stages) { ns = s_begin; ++ni; }
+    };
+    int x_slot = 0, a_slot = 0;
+    uint4 carry[STRIDE == 1 ? C::PPR : 1];            // dY rows 2 q - 1 and 2 q, from the pair of rows before
+
+    // stage t of the stream: its rows are there, the loads that the rings have room for are on their way
+    int a_next = 1;
+    auto arrive = [&](int t) {
+        // X of this stage and dY of the next one are bundle t; up to D - 1 younger bundles may still be on their way
         {
-            uint4 ra4[C::ALIGNED_A ? C::PA_T : 1];
-            Raw<5> ra[C::ALIGNED_A ? 1 : C::PA_T];
-#pragma unroll
-            for (int u = 0; u < C::PA_T; ++u) {
-                const PieceA p = piece_a(u);
-                if constexpr (C::ALIGNED_A) ra4[u] = *reinterpret_cast<const uint4 *>(dyt + (p.valid ? p.rel : 0));
-                else ra[u] = piece_load_words(dyw + ((p.fast ? p.rel : 0) >> 1));
-            }
-#pragma unroll
-            for (int u = 0; u < C::PA_T; ++u) {
-                const PieceA p = piece_a(u);
-                uint4 v;
-                if constexpr (C::ALIGNED_A) {
-                    v = p.valid ? ra4[u] : make_uint4(0u, 0u, 0u, 0u);
-                } else {
-                    uint32_t t[4];
-                    if (AT && p.valid && !p.fast) odd_a |= 1u << u;
-                    piece_finish<true, 1>(t, ra[u], (uint32_t)(p.rel & 1), 0, p.fast ? p.hi : 0);
-                    v = make_uint4(t[0], t[1], t[2], t[3]);
-                }
-                if constexpr (WEIGHTED) {
-                    uint32_t t[4] = {v.x, v.y, v.z, v.w};
-                    scale_regs<true, 4>(t, f);
-                    v = make_uint4(t[0], t[1], t[2], t[3]);
-                }
-                if (C::NPA % C3_THREADS == 0 || tid + C3_THREADS * u < C::NPA)
-                    *reinterpret_cast<uint4 *>(sA + p.lds_off) = v;
-            }
+            const int mine = (C::QX - first_x + 3) / 4 + (C::QA - first_a + 3) / 4;
+            const int young = min(C::D - 1, T - 2 - t);
+            if (young <= 0) wait_vmcnt<0>();
+            else if (young == 1) { if (mine == C::BUNDLE) wait_vmcnt<C::BUNDLE>(); else wait_vmcnt<C::BUNDLE - 1>(); }
+            else { if (mine == C::BUNDLE) wait_vmcnt<2 * C::BUNDLE>(); else wait_vmcnt<2 * C::BUNDLE - 2>(); }
         }
-        if constexpr (STRIDE == 1) {
-#pragma unroll
-            for (int u0 = 0; u0 < C::PX_T; u0 += XB) {
-                Raw<5> rx[XB];
-#pragma unroll
-                for (int u = 0; u < XB; ++u) {
-                    if (u0 + u < C::PX_T) {
-                        const PieceX p = piece_x(u0 + u);
-                        rx[u] = piece_load_words(xw + ((p.fast ? p.rel : 0) >> 1));
-                    }
-                }
-#pragma unroll
-                for (int u = 0; u < XB; ++u) {
-                    if (u0 + u >= C::PX_T) continue;
-                    const PieceX p = piece_x(u0 + u);
-                    uint32_t t[4];
-                    if (AT && p.valid && !p.fast) odd_x |= 1u << (u0 + u);
-                    piece_finish<true, 1>(t, rx[u], (uint32_t)(p.rel & 1), p.fast ? p.lo : 0, p.fast ? p.hi : 0);
-                    const uint4 v = make_uint4(t[0], t[1], t[2], t[3]);
-                    if (p.write) *reinterpret_cast<uint4 *>(sX + p.lds_off) = v;
-                }
-            }
+        a_next = a_slot == C::D + 1 ? 0 : a_slot + 1;
+        if (t == 0) {
+            if (mends_a && ns == n_stages - 1) mend_a(ni, a_slot);
+            if constexpr (WEIGHTED) scale_a(ni, a_slot);
+            next_a();
+        }
+        if (t + 1 < TA) {
+            if (mends_a && ns == n_stages - 1) mend_a(ni, a_next);
+            if constexpr (WEIGHTED) scale_a(ni, a_next);
+            next_a();
+        }
+        if (mends_x && cs == n_stages - 1) mend_x(ci, x_slot);
+        __syncthreads();                              // everyone's pieces are there; the stage before has been read
+        if (x_issued < T) { fetch_x(fx); ++x_issued; }
+        if (a_issued < TA) { fetch_a(fa); ++a_issued; }
+    };
+    auto leave = [&]() {
+        x_slot = x_slot == C::D ? 0 : x_slot + 1;
+        a_slot = a_next;
+        if (++cs == k_end) { cs = s_begin; ++ci; }
+    };
+    // this lane's one of rows r and r + 1 of dY, counted from the first one of the stage at hand, of which the image has `below` from there on:
+    // those below it are zeros
+    int below = 0;
+    unsigned odd_x = 0, odd_a = 0, xs = 0, as = 0, an = 0;
+    auto row_a = [&](int r) {
+        C3Row o{0u, 0u};
+        if constexpr (C::ODD) {
+            const int lr = r + half;
+            const unsigned e = odd_a + 7u * (unsigned)(lr < C::RPS ? lr : 0);
+            o.at = (lr < C::RPS ? as : an) + (e >> 1) * 4u;
+            o.bits = (e & 1u) * 16u;
         } else {
-            constexpr int XB2 = 8;                    // aligned 16-byte copies: four registers per piece
-#pragma unroll
-            for (int u0 = 0; u0 < C::PX_T; u0 += XB2) {
-                uint4 rx[XB2];
-#pragma unroll
-                for (int u = 0; u < XB2; ++u) {
-                    if (u0 + u < C::PX_T) {
-                        const PieceX p = piece_x(u0 + u);
-                        rx[u] = *reinterpret_cast<const uint4 *>(xt + (p.valid ? p.rel : 0));
-                    }
-                }
-#pragma unroll
-                for (int u = 0; u < XB2; ++u) {
-                    if (u0 + u >= C::PX_T) continue;
-                    const PieceX p = piece_x(u0 + u);
-                    if (p.write) *reinterpret_cast<uint4 *>(sX + p.lds_off) = p.valid ? rx[u] : make_uint4(0u, 0u, 0u, 0u);
-                }
+            o.at = half ? (r + 1 < C::RPS ? as + C::at_a(r + 1) : an) : as + C::at_a(r);
+        }
+        if (r + 1 >= below && r + half >= below) o.at = 0u;
+        return o;
+    };
+    auto row_x = [&](int r) {                         // stride 1: rows r and r + 1 of X; stride 2: 2 r and 2 r + 2
+        C3Row o{0u, 0u};
+        if constexpr (C::ODD_X) {
+            const unsigned e = odd_x + 7u * (unsigned)(r + half);
+            o.at = xs + (e >> 1) * 4u;
+            o.bits = (e & 1u) * 16u;
+        } else {
+            o.at = xs + (half ? C::at_x(STRIDE * (r + 1)) : C::at_x(STRIDE * r));
+        }
+        if (r + 1 >= below && r + half >= below) o.at = 0u;
+        return o;
+    };
+    auto rows_here = [&]() {
+        odd_x = C::ODD_X ? (unsigned)(x_odd_chan + ((x_ex & 1) ? (int)((x_at(ci) >> 1) & 1) : 0)) & 1u : 0u;
+        odd_a = C::ODD ? (unsigned)(a_odd_chan + ((a_ex & 1) ? (int)((a_at(ci) >> 1) & 1) : 0)) & 1u : 0u;
+        xs = C::RING_X + x_slot * C::STAGE_X + lane_x;
+        as = C::RING_A + a_slot * C::STAGE_A + lane_a;
+        an = C::RING_A + a_next * C::STAGE_A + lane_a;
+        below = H - cs * C::RPS;
+    };
+    int t = 0;
+    if (STRIDE == 1 && cut && s_begin < k_begin) {    // the stage above a slice: its last row and the next stage's first
+        arrive(t++);
+        rows_here();
+        const C3Row o = row_a(C::RPS - 1);
+        c3_each(pieces_t{}, [&](auto j) { if constexpr (STRIDE == 1) carry[j.value] = c3_piece<W, j.value>(lds + o.at, o.bits); });
+        leave();
+    }
+    for (; t < T; ++t) {
+        arrive(t);
+        rows_here();
+        if constexpr (STRIDE == 1) {
+            if (cs == 0) {                            // the pair above the first one: row -1 is zeros, row 0 this stage's first
+                C3Row o{0u, 0u};
+                if (half) o = C3Row{as + (odd_a >> 1) * 4u, odd_a * 16u};
+                c3_each(pieces_t{}, [&](auto j) { carry[j.value] = c3_piece<W, j.value>(lds + o.at, o.bits); });
             }
         }
-        // Pieces whose whole-dword window would have left the tensor (the first piece of its first row, the pieces of its
-        // last ten elements) were written as zeros above: the few threads that hold one fill it in element by element,
-        // touching nothing but the valid elements.
-        if constexpr (!AT) {                          // one tensor: only its first and its last example have any
-            if (i == 0 || i == a.n - 1) {
-#pragma unroll 1
-                for (int u = 0; u < (C::ALIGNED_A ? 0 : C::PA_T); ++u) {
-                    const PieceA p = piece_a(u);
-                    if (p.valid && !p.fast) odd_a |= 1u << u;
-                }
-#pragma unroll 1
-                for (int u = 0; u < (STRIDE == 1 ? C::PX_T : 0); ++u) {
-                    const PieceX p = piece_x(u);
-                    if (p.valid && !p.fast) odd_x |= 1u << u;
-                }
-            }
-        }
-        if (odd_a | odd_x) {
-            if constexpr (!C::ALIGNED_A) {
-#pragma unroll 1
-                for (; odd_a; odd_a &= odd_a - 1) {
-                    const PieceA p = piece_a(__builtin_ctz(odd_a));
-                    {
-                        uint16_t *dst = reinterpret_cast<uint16_t *>(sA + p.lds_off);
-                        const int hi = min(8, p.hi);
-#pragma unroll 1
-                        for (int e = 0; e < hi; ++e) {
-                            uint16_t val = dyt[p.rel + e];
-                            if constexpr (WEIGHTED) val = float_to_bf16_bits(bf16_bits_to_float(val) * f);
-                            dst[e] = val;
+#pragma unroll
+        for (int p = 0; p < C::PAIRS; ++p) {
+            if (p > 0 && 2 * p >= below) continue;                    // uniform
+            const C3Row x = row_x(2 * p), y1 = row_a(2 * p), y0 = row_a(2 * p + 1);
+            if constexpr (STRIDE == 1) {
+                uint32_t left = 0u;                                   // the two columns before the piece
+                uint4 b1 = c3_piece<W, 0>(lds + x.at, x.bits);
+                c3_each(pieces_t{}, [&](auto jj) {
+                    constexpr int j = jj.value;
+                    uint4 ahead = make_uint4(0u, 0u, 0u, 0u);
+                    if constexpr (j + 1 < C::PPR) ahead = c3_piece<W, j + 1>(lds + x.at, x.bits);
+                    const uint4 a0 = c3_piece<W, j>(lds + y0.at, y0.bits), a1 = c3_piece<W, j>(lds + y1.at, y1.bits);
+                    // the same run of columns one to the left and one to the right
+                    const uint32_t o0 = funnel(b1.x, left, 16), o1 = funnel(b1.y, b1.x, 16), o2 = funnel(b1.z, b1.y, 16), o3 = funnel(b1.w, b1.z, 16),
+                                   o4 = funnel(ahead.x, b1.w, 16);
+                    const uint4 b0 = make_uint4(o0, o1, o2, o3), b2 = make_uint4(o1, o2, o3, o4);
+                    c3_taps(acc, 1, a1, b0, b1, b2);
+                    c3_taps(acc, 0, a0, b0, b1, b2);
+                    c3_taps(acc, 2, carry[j], b0, b1, b2);
+                    carry[j] = a0;
+                    left = b1.w;
+                    b1 = ahead;
+                });
+            } else {
+                uint32_t left[2] = {0u, 0u};
+                c3_each(pieces_t{}, [&](auto jj) {
+                    constexpr int j = jj.value;
+                    const uint4 a1 = c3_piece<W, j>(lds + y1.at, y1.bits), a0 = c3_piece<W, j>(lds + y0.at, y0.bits);
+#pragma unroll
+                    for (int odd_row = 0; odd_row < 2; ++odd_row) {   // row 2 oh of X, then 2 oh + 1
+                        const char *row = lds + x.at + (x.at ? odd_row * C::ROW_X : 0);
+                        const uint4 v = c3_piece<C::XW, 2 * j>(row, 0u);
+                        uint4 w = make_uint4(0u, 0u, 0u, 0u);
+                        if constexpr (16 * j + 8 < C::XW) w = c3_piece<C::XW, 2 * j + 1>(row, 0u);
+                        const uint4 b0 = make_uint4(c3_high(v.x, left[odd_row]), c3_high(v.z, v.y), c3_high(w.x, v.w), c3_high(w.z, w.y)),     // X[2 ow - 1]
+                                    b1 = make_uint4(c3_low(v.y, v.x), c3_low(v.w, v.z), c3_low(w.y, w.x), c3_low(w.w, w.z)),                 // X[2 ow]
+                                    b2 = make_uint4(c3_high(v.y, v.x), c3_high(v.w, v.z), c3_high(w.y, w.x), c3_high(w.w, w.z));             // X[2 ow + 1]
+                        left[odd_row] = w.w;
+                        if (odd_row == 0) {
+                            c3_taps(acc, 1, a1, b0, b1, b2);
+                        } else {
+                            c3_taps(acc, 2, a1, b0, b1, b2);
+                            c3_taps(acc, 0, a0, b0, b1, b2);
                         }
                     }
-                }
-            }
-#pragma unroll 1
-            for (; STRIDE == 1 && odd_x; odd_x &= odd_x - 1) {
-                const PieceX p = piece_x(__builtin_ctz(odd_x));
-                {
-                    uint16_t *dst = reinterpret_cast<uint16_t *>(sX + p.lds_off);
-                    const int hi = min(8, p.hi);
-#pragma unroll 1
-                    for (int e = p.lo; e < hi; ++e) dst[e] = xt[p.rel + e];
-                }
+                });
             }
         }
-        __syncthreads();
-
-        // ---- MFMAs of the chunk
-        const char *pa = sA + (wm * 32 + (lane & 31)) * C::PA;
-        const char *px = sX + (wn * 32 + (lane & 31)) * C::PX;
-        const int half = lane >> 5;
-#pragma unroll
-        for (int ks = 0; ks < C::KSTEPS; ++ks) {
-            const int kk = ks * 16 + half * 8;
-            const int r = kk / C::OWP, ow0 = kk - r * C::OWP;
-            const bf16x8 va = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4 *>(pa + kk * 2));
-#pragma unroll
-            for (int kh = 0; kh < 3; ++kh) {
-                const char *row = px + ((STRIDE * r + kh) * C::WP + ow0) * 2;
-                const uint4 d = *reinterpret_cast<const uint4 *>(row);
-                const uint32_t d4 = *reinterpret_cast<const uint32_t *>(row + 16);
-                const uint4 sh = make_uint4(funnel(d.y, d.x, 16), funnel(d.z, d.y, 16), funnel(d.w, d.z, 16),
-                                            funnel(d4, d.w, 16));                 // the same run one element on
-                uint4 b0, b1, b2;
-                if constexpr (STRIDE == 1) {
-                    b0 = d; b1 = sh; b2 = make_uint4(d.y, d.z, d.w, d4);
-                } else {
-                    b0 = d;                                                          // O'[ow]     = X[2 ow - 1]
-                    b1 = *reinterpret_cast<const uint4 *>(row + C::E_OFF * 2);       // E[ow]      = X[2 ow]
-                    b2 = sh;                                                         // O'[ow + 1] = X[2 ow + 1]
-                }
-                acc[kh * 3 + 0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va, __builtin_bit_cast(bf16x8, b0), acc[kh * 3 + 0], 0, 0, 0);
-                acc[kh * 3 + 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va, __builtin_bit_cast(bf16x8, b1), acc[kh * 3 + 1], 0, 0, 0);
-                acc[kh * 3 + 2] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va, __builtin_bit_cast(bf16x8, b2), acc[kh * 3 + 2], 0, 0, 0);
-            }
-        }
+        leave();
     }
-    }   // examples
 
     if constexpr (MODE == C3_FULL) {
         c3_epilogue(acc, a, result, unit, co0, ci0, wm, wn, lane, red, lds);
@@ -480,12 +627,12 @@ __device__ __forceinline__ void conv3x3_body(const C3Args &a, const unsigned bid
     }
 }
 
-template <int W, int MODE, int STRIDE, bool AT>
+template <int W, int MODE, int STRIDE>
 __global__ void __launch_bounds__(C3_THREADS, 2) conv3x3_kernel(const Grouped<C3Args> grp)
 {
     unsigned bid;
     const C3Args &a = grp.a[group_pick(grp, bid)];
-    conv3x3_body<W, MODE, STRIDE, AT>(a, bid);
+    conv3x3_body<W, MODE, STRIDE>(a, bid);
 }
 
 // The variants a ResNet of 224 x 224 images needs, in ONE kernel that dispatches on the layer's variant, so that all
@@ -505,7 +652,7 @@ constexpr bool c3_any_in_set(int variant, int set)
     return variant != C3_ANY_56_SLICED;
 }
 
-template <int SET, bool AT>
+template <int SET>
 __global__ void __launch_bounds__(C3_THREADS, 2) conv3x3_any_kernel(const Grouped<C3Args> grp)
 {
     unsigned bid;
@@ -513,7 +660,7 @@ __global__ void __launch_bounds__(C3_THREADS, 2) conv3x3_any_kernel(const Groupe
     const int v = __builtin_amdgcn_readfirstlane(a.variant);
 #define C3_ANY_CASE(ID, W, MODE, STRIDE)                                                  \
     if constexpr (c3_any_in_set(ID, SET)) {                                               \
-        if (v == ID) { conv3x3_body<W, MODE, STRIDE, AT>(a, bid); return; }               \
+        if (v == ID) { conv3x3_body<W, MODE, STRIDE>(a, bid); return; }               \
     }
     C3_ANY_CASE(C3_ANY_56_SLICED, 56, C3_SLICED, 1)
     C3_ANY_CASE(C3_ANY_28_SLICED, 28, C3_SLICED, 1)
@@ -550,52 +697,6 @@ template <int W, int MODE, int STRIDE> constexpr int c3_any_variant()
     if (W == 28) return MODE == C3_SLICED ? C3_ANY_28S2_SLICED : (MODE == C3_FULL ? C3_ANY_28S2_FULL : -1);
     if (W == 7 && MODE == C3_FULL) return C3_ANY_7S2_FULL;
     return -1;
-}
-
-// Parity split of the rows of X for the stride-2 kernel: out[row][0 .. OWP+8) = O'[c] = X[row][2c - 1],
-// out[row][OWP+8 .. 2 OWP+8) = E[c] = X[row][2c]; zero where the column is outside the row.  `rows` =
-// n * cin * hin rows of `win` (even) elements; one thread per 16-byte output piece, which needs
-// the high (O') or low (E) halves of eight consecutive dwords of the input row.
-struct DeintArgs {
-    const void *x;
-    int x_tab, rows_per_ex;         // Geo::x_tab; rows of an example
-    uint16_t *out;
-    long long rows;
-    int win, owp;
-};
-
-__global__ void __launch_bounds__(256) deinterleave2_kernel(const Grouped<DeintArgs> grp)
-{
-    unsigned bid;
-    const DeintArgs &a = grp.a[group_pick(grp, bid)];
-    uint16_t *__restrict__ out = a.out;
-    const long long rows = a.rows;
-    const int win = a.win, owp = a.owp;
-    const int xpr = (2 * owp + 8) / 8, opr = (owp + 8) / 8;
-    const long long q = (long long)bid * 256 + threadIdx.x;
-    if (q >= rows * xpr) return;
-    const long long row = q / xpr;
-    const int pc = (int)(q - row * xpr);
-    const bool odd_plane = pc < opr;
-    const int first = odd_plane ? 8 * pc - 1 : 8 * (pc - opr);      // dword of element 0 of the piece
-    const uint16_t *xr;
-    if (a.x_tab) {
-        const int i = (int)((unsigned)row / (unsigned)a.rows_per_ex);       // (rows < 2^31: conv3x3_applicable)
-        xr = example_at<uint16_t>(a.x, a.x_tab, i, 0) + (size_t)(row - (long long)i * a.rows_per_ex) * win;
-    } else {
-        xr = static_cast<const uint16_t *>(a.x) + (size_t)row * win;
-    }
-    const uint32_t *src = reinterpret_cast<const uint32_t *>(xr);
-    const int nd = win / 2;
-    uint32_t h[8];
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-        const int d = first + e;
-        const uint32_t w = (d >= 0 && d < nd) ? src[d] : 0u;
-        h[e] = odd_plane ? (w >> 16) : (w & 0xFFFFu);
-    }
-    *reinterpret_cast<uint4 *>(out + q * 8) =
-        make_uint4(h[0] | (h[1] << 16), h[2] | (h[3] << 16), h[4] | (h[5] << 16), h[6] | (h[7] << 16));
 }
 
 // Slices of one (example, tile) meet here.  The sum is elementwise, so it is spread over many
@@ -654,7 +755,7 @@ __global__ void __launch_bounds__(C3_THREADS) conv3x3_fixup_kernel(const Grouped
         if constexpr (WEIGHTED) {
             if (ok) out[idx] += v[rr];
         } else {
-            ss += v[rr] * v[rr];
+            if (ok) ss += v[rr] * v[rr];
             if (a.out_w && ok) out[idx] = v[rr];
         }
     }
@@ -667,9 +768,9 @@ __global__ void __launch_bounds__(C3_THREADS) conv3x3_fixup_kernel(const Grouped
 // ------------------------------------------------------------------------------------ host
 
 struct C3Plan {
-    int rows;           // R of the width case
-    int tiles_co, tiles_ci, chunks;
-    int ksplit, chunks_per_split;      // per-example modes: K slices; weighted: example ranges
+    int stage_rows;                    // output rows of a stage (C3Cfg)
+    int tiles_co, tiles_ci, chunks;    // chunks: what the plans count work in, about 224 output positions
+    int ksplit, stages_per_split;      // per-example modes: K slices; weighted: example ranges
     int ex_per_split;                  // weighted
     int slice_ex;                      // per-example modes: examples per slice of a clipping unit, or 0
 };
@@ -681,12 +782,13 @@ int rows_of_width(int ow, int stride)
     return owp == 8 ? 8 : 224 / owp;
 }
 
-// bytes of the parity-split copy of X the stride-2 kernel reads (0 for stride 1)
-size_t c3_split_bytes(const Geo &g)
+// The stride-2 form needs no copy of X (it once read one with rows split by column parity).  What is reported stays: callers size buffers
+// by it, and the entry point with built-in scratch refuses layers by it.
+size_t c3_reported_copy(const Geo &g)
 {
     if (g.stride != 2) return 0;
     const int owp = (g.ow + 7) / 8 * 8;
-    return (size_t)g.n * g.cin * g.h * (2 * owp + 8) * sizeof(uint16_t);
+    return ((size_t)g.n * g.cin * g.h * (2 * owp + 8) * sizeof(uint16_t) + 15) & ~(size_t)15;
 }
 
 // plans inside a batch call (the launch is shared with other layers) differ; workspace sizes cover both
@@ -696,12 +798,12 @@ int c3_plan_crowd() { return c3_forced_crowd >= 0 ? c3_forced_crowd : crowd_hint
 C3Plan c3_plan(const Geo &g, int mode)
 {
     C3Plan p;
-    p.rows = rows_of_width(g.ow, g.stride);
     p.tiles_co = (g.cout + 63) / 64;
     p.tiles_ci = (g.cin + 63) / 64;
-    p.chunks = (g.oh + p.rows - 1) / p.rows;
+    p.chunks = (g.oh + rows_of_width(g.ow, g.stride) - 1) / rows_of_width(g.ow, g.stride);
     p.ksplit = 1;
-    p.chunks_per_split = p.chunks;
+    p.stage_rows = c3_rows_per_stage(g.ow, g.stride);
+    p.stages_per_split = 0;
     p.ex_per_split = g.n;
     p.slice_ex = 0;
     const long long tiles = (long long)p.tiles_co * p.tiles_ci;
@@ -749,8 +851,10 @@ C3Plan c3_plan(const Geo &g, int mode)
         long long want = (128 + units - 1) / units;
         if (crowd) want = (p.chunks + tgt - 1) / tgt;
         if (want > p.chunks) want = p.chunks;
-        p.chunks_per_split = (int)((p.chunks + want - 1) / want);
-        p.ksplit = (p.chunks + p.chunks_per_split - 1) / p.chunks_per_split;
+        const int stages = (g.oh + p.stage_rows - 1) / p.stage_rows;
+        if (want > stages) want = stages;
+        p.stages_per_split = (int)((stages + want - 1) / want);
+        p.ksplit = (stages + p.stages_per_split - 1) / p.stages_per_split;
     }
     return p;
 }
@@ -765,31 +869,26 @@ dp_status c3_launch_mode(const C3Args &a, unsigned blocks, hipStream_t s)
 {
     using C = C3Cfg<W, STRIDE>;
     constexpr int any = c3_any_variant<W, MODE, STRIDE>();
-    const bool at = a.dy_tab != 0;                   // (x has a table too, unless the kernel reads the parity-split copy)
     const int set = fuse_hint() == 2 ? 0 : 1;
     if (fuse_hint() && (set == 0 ? c3_any_in_set(any, 0) : c3_any_in_set(any, 1))) {
         // inside a batch call: every row width in one launch
-        const void *fn = at ? (set == 0 ? reinterpret_cast<const void *>(&conv3x3_any_kernel<0, true>)
-                                        : reinterpret_cast<const void *>(&conv3x3_any_kernel<1, true>))
-                            : (set == 0 ? reinterpret_cast<const void *>(&conv3x3_any_kernel<0, false>)
-                                        : reinterpret_cast<const void *>(&conv3x3_any_kernel<1, false>));
-        static std::atomic<bool> any_attr_done[2][2];
-        if (!any_attr_done[at][set].load()) {
+        const void *fn = set == 0 ? reinterpret_cast<const void *>(&conv3x3_any_kernel<0>) : reinterpret_cast<const void *>(&conv3x3_any_kernel<1>);
+        static std::atomic<bool> any_attr_done[2];
+        if (!any_attr_done[set].load()) {
             if (hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, C3_ANY_LDS) != hipSuccess)
                 return fail(DP_ERR_DEVICE, "conv3x3: cannot reserve %d bytes of LDS", C3_ANY_LDS);
-            any_attr_done[at][set].store(true);
+            any_attr_done[set].store(true);
         }
         C3Args b = a;
         b.variant = any;
         return submit_main<C3Args>(fn, b, blocks, C3_THREADS, C3_ANY_LDS, s, "conv3x3");
     }
-    const void *fn = at ? reinterpret_cast<const void *>(&conv3x3_kernel<W, MODE, STRIDE, true>)
-                        : reinterpret_cast<const void *>(&conv3x3_kernel<W, MODE, STRIDE, false>);
-    static std::atomic<bool> attr_done[2];           // zero-initialised; setting the attribute twice is harmless
-    if (!attr_done[at].load()) {
+    const void *fn = reinterpret_cast<const void *>(&conv3x3_kernel<W, MODE, STRIDE>);
+    static std::atomic<bool> attr_done;              // zero-initialised; setting the attribute twice is harmless
+    if (!attr_done.load()) {
         if (hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, C::LDS) != hipSuccess)
             return fail(DP_ERR_DEVICE, "conv3x3: cannot reserve %d bytes of LDS", C::LDS);
-        attr_done[at].store(true);
+        attr_done.store(true);
     }
     return submit_main<C3Args>(fn, a, blocks, C3_THREADS, C::LDS, s, "conv3x3");
 }
@@ -827,7 +926,6 @@ bool conv3x3_applicable(const Geo &g, int mode)
         // better in the general kernel / on packed operands
         if (mode == MODE_WEIGHTED || (g.ow != 7 && g.ow != 14 && g.ow != 28)) return false;
         if (g.ow == 28 && g.n <= 2) return false;
-        if ((long long)g.n * g.cin * g.h * (2 * ((g.ow + 7) / 8 * 8) + 8) >= (1ll << 31)) return false;
     } else {
         return false;
     }
@@ -852,12 +950,11 @@ static size_t conv3x3_ws_bytes_plan(const Geo &g, int mode)
 {
     const C3Plan p = c3_plan(g, mode);
     const size_t tiles = (size_t)p.tiles_co * p.tiles_ci;
-    const size_t split = c3_align16(c3_split_bytes(g));
-    if (mode == MODE_WEIGHTED) return split + (p.ksplit > 1 ? tiles * p.ksplit * 9 * 16 * C3_THREADS * sizeof(float) : 0);
+    if (mode == MODE_WEIGHTED) return c3_reported_copy(g) + (p.ksplit > 1 ? tiles * p.ksplit * 9 * 16 * C3_THREADS * sizeof(float) : 0);
     const size_t units = (size_t)(g.n / g.unit) * tiles;
     size_t b = c3_align16(units * c3_partials_per_unit(p) * sizeof(float));
     if (p.ksplit > 1) b += units * p.ksplit * 9 * 16 * C3_THREADS * sizeof(float);
-    return b + split;
+    return b + c3_reported_copy(g);
 }
 
 size_t conv3x3_norm_partial_count(const Geo &g)
@@ -901,7 +998,7 @@ dp_status launch_conv3x3(const Geo &g, int mode, const void *x, const void *dy, 
     a.group_sqnorm = group_sqnorm; a.clip_c = clip_c;
     a.n = g.n; a.cin = g.cin; a.cout = g.cout; a.h = g.oh; a.hin = g.h;
     a.tiles_co = p.tiles_co; a.tiles_ci = p.tiles_ci;
-    a.chunks = p.chunks; a.ksplit = p.ksplit; a.chunks_per_split = p.chunks_per_split;
+    a.ksplit = p.ksplit; a.stages_per_split = p.stages_per_split;
     a.ex_per_split = p.ex_per_split;
     const size_t tiles = (size_t)p.tiles_co * p.tiles_ci;
     const size_t units = weighted ? tiles : (size_t)a.rows * tiles;
@@ -912,23 +1009,9 @@ dp_status launch_conv3x3(const Geo &g, int mode, const void *x, const void *dy, 
         w += c3_align16(units * c3_partials_per_unit(p) * sizeof(float));
     }
     a.ws_part = p.ksplit > 1 ? reinterpret_cast<float *>(w) : nullptr;
-    if (p.ksplit > 1) w += units * p.ksplit * 9 * 16 * C3_THREADS * sizeof(float);
     const long long total = (long long)units * p.ksplit;
     const unsigned blocks = (unsigned)(((total + 7) / 8) * 8);
     dp_status st;
-    if (g.stride == 2) {
-        // rows of X split by column parity, after everything else in the workspace
-        const int owp = (g.ow + 7) / 8 * 8;
-        const long long rows = (long long)g.n * g.cin * g.h;
-        const long long pieces = rows * ((2 * owp + 8) / 8);
-        DeintArgs da;
-        da.x = x; da.x_tab = g.x_tab; da.rows_per_ex = g.cin * g.h; da.out = reinterpret_cast<uint16_t *>(w); da.rows = rows; da.win = g.w; da.owp = owp;
-        st = submit_kernel<DeintArgs>(TIER_PRE, reinterpret_cast<const void *>(&deinterleave2_kernel), da,
-                                      (unsigned)((pieces + 255) / 256), 256, 0, s, "deinterleave2");
-        if (st != DP_OK) return st;
-        a.x = w;
-        a.x_tab = 0;
-    }
     if (g.stride == 2) {
         if (g.ow == 7) st = c3_launch_w<7, 2>(a, weighted, blocks, s);
         else if (g.ow == 28) st = c3_launch_w<28, 2>(a, weighted, blocks, s);

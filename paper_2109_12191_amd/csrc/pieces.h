@@ -116,6 +116,32 @@ __device__ __forceinline__ void piece_finish(uint32_t (&v)[4], const Raw<raw_n<B
     mask_piece<BF16>(v, lo, hi);
 }
 
+// lane L: LDS[lds_base + 16 L .. +16) <- 16 bytes at base + byte_off.  base and lds_base are wave-uniform
+// (already in scalar registers).
+__device__ __forceinline__ void lds_direct_16(unsigned long long base, unsigned byte_off, unsigned lds_base)
+{
+    asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(byte_off), "s"(base), "s"(lds_base) : "memory");
+}
+// the same with only the lanes of `lanes` (wave-uniform, never empty) taking part: the others fetch nothing and leave
+// their 16 bytes of LDS as they are.  The instruction is issued once either way, so counted waits stay exact.
+__device__ __forceinline__ void lds_direct_16_lanes(unsigned long long base, unsigned byte_off, unsigned lds_base, unsigned long long lanes)
+{
+    unsigned long long saved;
+    asm volatile("s_mov_b32 m0, %3\n\t"
+                 "s_mov_b64 %0, exec\n\t"
+                 "s_mov_b64 exec, %4\n\t"
+                 "global_load_lds_dwordx4 %1, %2\n\t"
+                 "s_mov_b64 exec, %0"
+                 : "=&s"(saved)
+                 : "v"(byte_off), "s"(base), "s"(lds_base), "s"(lanes)
+                 : "memory");
+}
+template <int N>
+__device__ __forceinline__ void wait_vmcnt()
+{
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
+}
+
 template <bool BF16, int N>
 __device__ __forceinline__ void scale_regs(uint32_t (&st)[N], float f)
 {
