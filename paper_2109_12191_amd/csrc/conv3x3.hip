@@ -1,23 +1,26 @@
-// Per-example weight gradients of 3x3, stride-1, pad-1 convolutions (bf16) from raw image rows.
+// Per-example weight gradients of 3x3, pad-1 convolutions of stride 1 and 2 (bf16) from raw image rows.
 //
 // Same contraction as the general kernel (H1 of the path; per example i
-//     dW_i[co, ci, kh, kw] = sum_{oh, ow} dY_i[co, oh, ow] * Xpad_i[ci, oh + kh - 1, ow + kw - 1]),
+//     dW_i[co, ci, kh, kw] = sum_{oh, ow} dY_i[co, oh, ow] * Xpad_i[ci, s oh + kh - 1, s ow + kw - 1]),
 // but the nine taps of one input channel are nine shifted views of the SAME rows of X, so a
-// workgroup stages each row once and builds all nine MFMA operands from it:
+// workgroup fetches each row once and builds all nine MFMA operands from it:
 //
 //   * a workgroup owns 64 output channels x 64 input channels x 9 taps of one example (four
-//     waves, each 32 co x 32 ci x 9 taps = nine 32x32 accumulator tiles) and walks chunks of R
-//     output rows;
-//   * per chunk it stages dY[64 co][R rows] (K-contiguous, rows padded to OWP = W rounded up to
-//     8) and X[64 ci][R + 2 rows][WP = OWP + 8 columns] into LDS; X is stored with column
-//     c = iw + 1, zeros for iw = -1, iw >= W and rows outside the image, so every tap reads
-//     plain in-range LDS;
-//   * per 16 values of K a lane reads 16 bytes of dY and, per kernel row kh, 20 bytes of X
-//     starting at column ow0: tap kw = 0 is dwords 0..3, kw = 1 the same five dwords shifted by
-//     one element, kw = 2 dwords 1..4 -- nine MFMAs from four LDS reads.
+//     waves, each 32 co x 32 ci x 9 taps = nine 32x32 accumulator tiles) and walks stages of a few rows (C3Cfg);
+//   * rows travel global -> LDS as they lie in memory (16-byte LDS-direct loads), in rings: no registers, no masks, no shifts on the way;
+//   * a K step is eight columns of a pair of rows (the two halves of a wave hold one row each).  Stride 1: a run of X, and the same run one column
+//     to the left and to the right, meets dY of the row below it (kh = 0), of its own (kh = 1) and of the row above (kh = 2): nine MFMAs from one
+//     16-byte read of X, two of dY (the third is the first one of the pair before) and eight funnel shifts.  Stride 2: the even and the odd
+//     columns of two rows of X are put together by byte permutes, 24 for nine MFMAs.  What lies outside the image is zeros: a row is
+//     read from a few bytes of zeros, columns behind a row's end are cleared in registers, the column before it is a zero shifted in.
+//   * a workgroup that is done with a row of results (an example's, or a clipping unit's) stores it and goes on with the next one, whose rows
+//     are on their way meanwhile.
 //
-// Against the general kernel this cuts global/L2 reads of X by ~9x (each row is fetched once
-// per workgroup instead of once per tap) and LDS reads per MFMA by ~3x.
+// Bound by the matrix units, at the clock that they leave the chip, where two workgroups share a compute unit (85 % of the cycles of a stage are
+// MFMAs); by the stores where blocks are stored and K is short.  One call, us and TFLOP/s, before (rows staged through registers, nine operands
+// built from three rows of X per K step: 13-25 vector instructions per MFMA) and now: 64 -> 64 at 56 x 56, 128 examples, 135 (219) -> 48 (616);
+// 128 -> 128 at 28 x 28, 128, 56 (532) -> 33 (899); 256 -> 256 at 14 x 14, 256, 93 (634) -> 68 (866), stored 185 -> 156 (3.9 TB/s), clip-weighted
+// 142 (416) -> 96 (616); 128 -> 128 at 16 x 16, 256, 47 (415) -> 20 (947); 128 -> 128 stride 2 onto 28 x 28, 64, 76 (195) -> 27 (559).
 //
 // K may be sliced over workgroups (few tiles, long K): slices store their accumulators in the
 // workspace and a second kernel adds them in slice order, so results are run-to-run identical.
@@ -47,15 +50,19 @@ struct C3Args {
     int n, cin, cout, h;              // h: OUTPUT height (= input height for stride 1)
     int hin;                          // input height
     int tiles_co, tiles_ci;
+    int stages;                       // of an example (C3Cfg)
     int ksplit, stages_per_split;     // per-example mode: K slices, in stages (C3Cfg)
     int ex_per_split;                 // weighted mode: examples per workgroup (ksplit = example ranges)
     int variant;                      // which body conv3x3_any_kernel runs for this layer (C3_ANY_* below)
     int rows, unit;                   // per-example modes: rows of results, examples of each (Geo::unit)
+    int rows_per_wg;                  // per-example mode, not sliced: rows of results that a workgroup makes
+    int total;                        // workgroups that have something to do
     int slice_ex;                     // per-example mode, sliced: > 0: the slices are ranges of this many examples of a unit
 };
 
 constexpr int C3_RP = 292;                           // floats per row staged by the store epilogue: 288 + 4
-constexpr int C3_STORE_LDS = 4 * 8 * C3_RP * 4;      // bytes the store epilogue needs: 4 waves x 8 rows
+constexpr int C3_ADD_LDS = 4 * 8 * C3_RP * 4;        // bytes that adding to the accumulator needs: 4 waves x 8 rows
+constexpr int C3_STORE_LDS = 4 * 2 * C3_RP * 4;      // and storing a block: 4 waves x 2 rows, beside the rings (they fill while it runs)
 
 // How a layer's rows lie in LDS.  A workgroup walks STAGES of RPS output rows: the RPS rows of dY and the STRIDE * RPS rows of X below
 // them, for its 64 channels of each.  A stage is SG groups, a group is RPG consecutive rows of 64 channels: in memory one run of bytes per
@@ -78,42 +85,39 @@ template <int W, int STRIDE> struct C3Cfg {
     static constexpr int GROUP_A = PA * 1024, GROUP_X = PX * 1024;
     static constexpr int STAGE_A = SG * GROUP_A, STAGE_X = SG * GROUP_X;
     static constexpr int D = STRIDE == 2 ? (PX > 15 ? 1 : 2) : (SG == 2 ? 1 : (PA == 7 ? 3 : 2));
+    static constexpr int QX = SG * PX, QA = SG * PA;         // wave instructions of a stage
+    static constexpr int UB = (QX + QA + 3) / 4;             // that a wave issues for X of a stage and dY of the next one together
+    static constexpr int DUMP_SIZE = (QX + QA) % 4 ? 1024 : 0;           // (so that all waves issue the same number: what the last ones fetch lands here)
     static constexpr int ZEROS = 128;                        // bytes of zeros at the start: rows outside the image
     static constexpr int RING_X = ZEROS, RING_A = ZEROS + (D + 1) * STAGE_X;
-    static constexpr int END = RING_A + (D + 2) * STAGE_A;   // dY one stage further: its next row meets this stage's last row of X
-    static constexpr int LDS = END > C3_STORE_LDS ? END : C3_STORE_LDS;
-    static constexpr int QX = SG * PX, QA = SG * PA;         // wave instructions of a stage
-    static constexpr int UX = (QX + 3) / 4, UA = (QA + 3) / 4;
-    static constexpr int BUNDLE = (QX + QA + 3) / 4;         // most of them that a wave issues per stage
+    static constexpr int DUMP = RING_A + (D + 2) * STAGE_A, END = DUMP + DUMP_SIZE;      // dY one stage further: its next row meets this stage's last row of X
+    static constexpr bool STREAMS = END + C3_STORE_LDS <= 81920 - 256;       // several rows of results by a workgroup, one after the other
+    static constexpr int STORE = STREAMS ? END : 0;
+    static constexpr int LDS = STREAMS ? END + C3_STORE_LDS : END;
     static constexpr bool PARTIAL_A = ROW_A % 16 != 0, PARTIAL_X = ROW_X % 16 != 0;     // a tensor may end inside a piece
     // where local row r (of a stage) of the first channel starts, for rows that start at a dword
     static constexpr int at_a(int r) { return (r / RPG) * GROUP_A + (r % RPG) * ROW_A; }
     static constexpr int at_x(int r) { return (r / (RPG * STRIDE)) * GROUP_X + (r % (RPG * STRIDE)) * ROW_X; }
     static_assert(RPS % 2 == 0, "pairs of rows");
     static_assert(LDS <= 81920 - 256, "two workgroups per CU");
+    static_assert(END >= C3_ADD_LDS, "room for the epilogues");
     static_assert(PPR * 16 * STRIDE <= ZEROS, "a row of zeros");
 };
 
 constexpr int c3_rows_per_stage(int ow, int stride) { return stride == 2 ? (ow == 28 ? 2 : 4) : (ow >= 28 ? 2 : (ow >= 14 ? 4 : 8)); }
+constexpr bool c3_streams(int ow, int stride) { return stride == 1 || ow == 7; }
+static_assert(C3Cfg<56, 1>::STREAMS && C3Cfg<32, 1>::STREAMS && C3Cfg<28, 1>::STREAMS && C3Cfg<16, 1>::STREAMS && C3Cfg<14, 1>::STREAMS && C3Cfg<8, 1>::STREAMS &&
+              C3Cfg<7, 1>::STREAMS && C3Cfg<7, 2>::STREAMS, "what the host plans");
 static_assert(C3Cfg<56, 1>::RPS == c3_rows_per_stage(56, 1) && C3Cfg<32, 1>::RPS == c3_rows_per_stage(32, 1) && C3Cfg<28, 1>::RPS == c3_rows_per_stage(28, 1) &&
               C3Cfg<16, 1>::RPS == c3_rows_per_stage(16, 1) && C3Cfg<14, 1>::RPS == c3_rows_per_stage(14, 1) && C3Cfg<8, 1>::RPS == c3_rows_per_stage(8, 1) &&
               C3Cfg<7, 1>::RPS == c3_rows_per_stage(7, 1) && C3Cfg<28, 2>::RPS == c3_rows_per_stage(28, 2) && C3Cfg<14, 2>::RPS == c3_rows_per_stage(14, 2) &&
               C3Cfg<7, 2>::RPS == c3_rows_per_stage(7, 2), "what the host plans");
 
-// What a workgroup does with finished accumulators (all of K of one example): squared norm of
-// its 64 x 64 x 9 block and the optional store in the framework's [Cout, Cin, 3, 3] order.
-//
-// In the accumulator layout a lane holds, per tap, one input channel and sixteen output channels,
-// so a direct store writes 4 bytes every 36.  When the layer's channel counts allow it the block
-// goes through LDS instead (`lds`, free once the MFMAs are done): each wave lays down eight
-// output-channel rows of 32 ci x 9 taps = 288 consecutive floats of the gradient, and reads them
-// back as 16-byte pieces that leave as fully coalesced 1152-byte row segments.
-__device__ __forceinline__ void c3_epilogue(const f32x16 (&acc)[9], const C3Args &a, int i, int unit, int co0, int ci0,
-                                            int wm, int wn, int lane, float *red, char *lds)
+// Finished accumulators (all of K of one row of results): this wave's share of the squared norm of the 64 x 64 x 9 block, in lane 63.
+__device__ __forceinline__ float c3_squares(const f32x16 (&acc)[9], const C3Args &a, int co0, int ci0, int wm, int wn, int lane)
 {
+    asm volatile("" : "+v"(lane), "+s"(co0), "+s"(ci0));             // (nothing of this is worth a register during the products)
     float ss = 0.0f;
-    const bool store = a.out_w != nullptr;
-    float *out = a.out_w + (size_t)i * a.out_stride;
     const bool ci_there = ci0 + wn * 32 + (lane & 31) < a.cin;
     const int co_there = a.cout - (co0 + wm * 32 + (lane >> 5) * 4);
 #pragma unroll
@@ -123,49 +127,58 @@ __device__ __forceinline__ void c3_epilogue(const f32x16 (&acc)[9], const C3Args
         for (int t = 0; t < 9; ++t) s += acc[t][r] * acc[t][r];
         ss += ci_there && (r >> 2) * 8 + (r & 3) < co_there ? s : 0.0f;
     }
+    return wave_sum_last_lane(ss);
+}
+
+// The block in the framework's [Cout, Cin, 3, 3] order; returns whether this wave issued all of its 48 stores.
+//
+// In the accumulator layout a lane holds, per tap, one input channel and sixteen output channels,
+// so a direct store writes 4 bytes every 36.  When the layer's channel counts allow it the block
+// goes through LDS instead (`buf`, this wave's own): the wave lays down two output-channel
+// rows of 32 ci x 9 taps = 288 consecutive floats of the gradient, and reads them
+// back as 16-byte pieces that leave as fully coalesced 1152-byte row segments.
+__device__ __forceinline__ bool c3_store(const f32x16 (&acc)[9], const C3Args &a, int i, int co0, int ci0, int wm, int wn, int lane, float *buf)
+{
+    asm volatile("" : "+v"(lane), "+s"(co0), "+s"(ci0), "+s"(i));    // (as above)
+    float *out = a.out_w + (size_t)i * a.out_stride;
     // wave-uniform: whole 32-channel blocks, 16-byte aligned rows
-    const bool via_lds = store && lds != nullptr && (a.cin % 32 == 0) && (a.out_stride % 4 == 0) &&
-                         ((reinterpret_cast<uintptr_t>(a.out_w) & 15u) == 0);
-    if (via_lds) {
-        float *buf = reinterpret_cast<float *>(lds) + (threadIdx.x >> 6) * (8 * C3_RP);
+    if ((a.cin % 32 == 0) && (a.out_stride % 4 == 0) && ((reinterpret_cast<uintptr_t>(a.out_w) & 15u) == 0)) {
         const int cil = lane & 31, half = lane >> 5;
         const int cib = ci0 + wn * 32;                                // first input channel of this wave
+        const int left = cib < a.cin ? a.cout - co0 - wm * 32 : 0;    // output channels there are
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            __syncthreads();                                          // previous pass read / MFMAs done with LDS
+        for (int r = 0; r < 16; ++r) {                                // (a wave's LDS instructions run in order: no waits between the passes)
 #pragma unroll
-            for (int rr = 0; rr < 4; ++rr)
+            for (int t = 0; t < 9; ++t) buf[half * C3_RP + cil * 9 + t] = acc[t][r];
+            const int co = (r >> 2) * 8 + (r & 3);                    // and co + 4
 #pragma unroll
-                for (int t = 0; t < 9; ++t) buf[(half * 4 + rr) * C3_RP + cil * 9 + t] = acc[t][q * 4 + rr];
-            __syncthreads();
-#pragma unroll
-            for (int it = 0; it < 9; ++it) {
-                const int f4 = it * 64 + lane;                        // 8 rows x 72 pieces
-                const int row = f4 / 72, c4 = f4 - row * 72;
-                const int co = co0 + wm * 32 + q * 8 + row;
-                const float4 v = *reinterpret_cast<const float4 *>(buf + row * C3_RP + c4 * 4);
-                if (co < a.cout && cib < a.cin)
-                    *reinterpret_cast<float4 *>(out + ((size_t)co * a.cin + cib) * 9 + c4 * 4) = v;
+            for (int it = 0; it < 3; ++it) {
+                const int f4 = it * 64 + lane;                        // 2 rows x 72 pieces
+                if (it < 2 || f4 < 144) {
+                    const int row = f4 >= 72 ? 1 : 0, c4 = f4 - row * 72;
+                    const float4 v = *reinterpret_cast<const float4 *>(buf + row * C3_RP + c4 * 4);
+                    if (co + row * 4 < left)
+                        *reinterpret_cast<float4 *>(out + ((size_t)(co0 + wm * 32 + co + row * 4) * a.cin + cib) * 9 + c4 * 4) = v;
+                }
             }
         }
-    } else if (store) {
-        const int ci = ci0 + wn * 32 + (lane & 31);
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            const int co = co0 + wm * 32 + (r >> 2) * 8 + (lane >> 5) * 4 + (r & 3);
-            const bool ok = co < a.cout && ci < a.cin;
-            const size_t base = ((size_t)co * a.cin + ci) * 9;
-#pragma unroll
-            for (int t = 0; t < 9; ++t)
-                if (ok) out[base + t] = acc[t][r];
-        }
+        return left >= 32;
     }
-    const float tot = block_sum<4>(ss, red);
-    if (threadIdx.x == 0) a.partials[unit] = tot;
+    const int ci = ci0 + wn * 32 + (lane & 31);
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+        const int co = co0 + wm * 32 + (r >> 2) * 8 + (lane >> 5) * 4 + (r & 3);
+        const bool ok = co < a.cout && ci < a.cin;
+        const size_t base = ((size_t)co * a.cin + ci) * 9;
+#pragma unroll
+        for (int t = 0; t < 9; ++t)
+            if (ok) out[base + t] = acc[t][r];
+    }
+    return false;
 }
 
 // Weighted sum of one tile over all examples: acc[co, ci, tap] += block, through LDS in the same
-// coalesced row form as the store above when the shapes allow, else element by element.
+// coalesced row form as the store above (eight rows a wave) when the shapes allow, else element by element.
 __device__ __forceinline__ void c3_add_to_accumulator(const f32x16 (&acc)[9], const C3Args &a, int co0, int ci0,
                                                       int wm, int wn, int lane, char *lds)
 {
@@ -175,14 +188,13 @@ __device__ __forceinline__ void c3_add_to_accumulator(const f32x16 (&acc)[9], co
         float *buf = reinterpret_cast<float *>(lds) + (threadIdx.x >> 6) * (8 * C3_RP);
         const int cil = lane & 31, half = lane >> 5;
         const int cib = ci0 + wn * 32;
+        __syncthreads();                              // the rings are no longer read
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-            __syncthreads();
 #pragma unroll
             for (int rr = 0; rr < 4; ++rr)
 #pragma unroll
                 for (int t = 0; t < 9; ++t) buf[(half * 4 + rr) * C3_RP + cil * 9 + t] = acc[t][q * 4 + rr];
-            __syncthreads();
 #pragma unroll
             for (int it = 0; it < 9; ++it) {
                 const int f4 = it * 64 + lane;
@@ -266,25 +278,26 @@ __device__ __forceinline__ void conv3x3_body(const C3Args &a, const unsigned bid
 {
     constexpr bool WEIGHTED = MODE == C3_WEIGHTED;
     using C = C3Cfg<W, STRIDE>;
-    using pieces_t = std::make_integer_sequence<int, C::PPR>;
     extern __shared__ __attribute__((aligned(16))) char lds[];
-    __shared__ float red[4];
+    __shared__ float red[2][4];
 
     // consecutive hardware workgroup ids rotate over the 8 XCDs; give each XCD a run of
     // consecutive logical ids (the slices and tiles of the same examples share its L2)
-    const int tiles = a.tiles_co * a.tiles_ci;
-    const int total = (WEIGHTED ? 1 : a.rows) * tiles * a.ksplit;
-    const int per_xcd = (total + 7) >> 3;
-    const int wg = (int)(bid & 7u) * per_xcd + (int)(bid >> 3);
-    if (wg >= total) return;
-    const int split = wg % a.ksplit;
-    const int unit = wg / a.ksplit;                   // (example, tile); weighted: tile
-    const int result = WEIGHTED ? 0 : unit / tiles;   // row of results
-    const int i_first = __builtin_amdgcn_readfirstlane(WEIGHTED ? split * a.ex_per_split : result * a.unit + (MODE == C3_SLICED ? split * a.slice_ex : 0));
-    const int i_last = __builtin_amdgcn_readfirstlane(WEIGHTED ? min(a.n, i_first + a.ex_per_split) : i_first + (MODE == C3_SLICED ? max(1, a.slice_ex) : a.unit));
-    const int tile = unit - result * tiles;
-    const int tco = tile / a.tiles_ci, tci = tile - tco * a.tiles_ci;
-    const int co0 = __builtin_amdgcn_readfirstlane(tco * 64), ci0 = __builtin_amdgcn_readfirstlane(tci * 64);
+    const int total = a.total, per_xcd = (total + 7) >> 3;
+    const unsigned wg = (bid & 7u) * (unsigned)per_xcd + (bid >> 3);
+    if ((int)wg >= total) return;
+    // full: some rows of results, one after the other, of a tile; sliced: a slice of a row's tile; weighted: a range of examples of a tile
+    const unsigned tiles = a.tiles_co * a.tiles_ci;
+    const unsigned pick = MODE == C3_SLICED ? wg / (unsigned)a.ksplit : wg;
+    const int group = __builtin_amdgcn_readfirstlane(pick / tiles), tile = __builtin_amdgcn_readfirstlane(pick % tiles);
+    const int split = MODE == C3_FULL ? 0 : (WEIGHTED ? group : __builtin_amdgcn_readfirstlane(wg % (unsigned)a.ksplit));
+    const int row0 = MODE == C3_FULL ? group * a.rows_per_wg : (WEIGHTED ? 0 : group);
+    const int per_row = a.unit;                       // examples that add up to a row
+    const int row1 = MODE == C3_FULL ? min(a.rows, row0 + a.rows_per_wg) : row0 + 1;
+    const int i_first = WEIGHTED ? split * a.ex_per_split : row0 * a.unit + (MODE == C3_SLICED ? split * a.slice_ex : 0);
+    const int i_last = WEIGHTED ? min(a.n, i_first + a.ex_per_split) : (MODE == C3_SLICED ? i_first + max(1, a.slice_ex) : row1 * a.unit);
+    const int tco = __builtin_amdgcn_readfirstlane((unsigned)tile / (unsigned)a.tiles_ci), tci = tile - tco * a.tiles_ci;
+    const int co0 = tco * 64, ci0 = tci * 64;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int wm = wave >> 1, wn = wave & 1;
     const int half = lane >> 5;
@@ -293,220 +306,231 @@ __device__ __forceinline__ void conv3x3_body(const C3Args &a, const unsigned bid
 
     // Stages of an example: all of them, or a slice [k_begin, k_end).  A slice that starts inside the image has the stage before it as
     // well, which gives its first rows their upper neighbours in dY and no products; its last rows need the stage behind it of dY.
-    const int n_stages = (H + C::RPS - 1) / C::RPS;
+    const int n_stages = a.stages;
     const bool cut = MODE == C3_SLICED && a.slice_ex == 0;
     const int k_begin = cut ? split * a.stages_per_split : 0, k_end = cut ? min(n_stages, k_begin + a.stages_per_split) : n_stages;
-    const int s_begin = __builtin_amdgcn_readfirstlane(STRIDE == 1 && k_begin > 0 ? k_begin - 1 : k_begin);
-    const int x_stages = k_end - s_begin, a_stages = min(n_stages, k_end + 1) - s_begin;
-    const int T = (i_last - i_first) * x_stages, TA = (i_last - i_first) * a_stages;
+    const int s_begin = STRIDE == 1 && k_begin > 0 ? k_begin - 1 : k_begin;
+    const int a_end = min(n_stages, cut ? k_end + 1 : k_end);
+    const int T = (i_last - i_first) * (k_end - s_begin);
 
-    // ---- global -> LDS.  Wave instruction q of a stage moves pieces 64 q .. 64 q + 63; X's are dealt to the waves from the first, dY's from the last.
+    // ---- global -> LDS.  A bundle is X of a stage and dY of the next one of the stream; its wave instruction q moves pieces 64 q .. 64 q + 63 of X, or
+    // from QX on of dY, and belongs to wave q % 4.
     // Pieces that hold nothing (padding, channels beyond the layer, rows below the image) fetch something of the same example, which
-    // no product reads or no result shows; so does a piece that the example's end cuts (mend() below fills it in).
+    // no product reads or no result shows.  The piece that an example's end cuts ends with it instead; the values move to their place
+    // in LDS when they are there (mend).
     const int x_chan = hin * C::XW, a_chan = H * W;                // elements of a channel
-    const size_t x_ex = (size_t)cin * x_chan, a_ex = (size_t)cout * a_chan;
-    const int first_x = wave, first_a = 3 - wave;
-    struct Piece { int ch, sub, pc; };
-    auto piece = [&](int q, int pitch) {
-        const int g = q / pitch, id = (q - g * pitch) * 64 + lane;
-        return Piece{id / pitch, g, id % pitch};
+    const unsigned x_ex = (unsigned)cin * (unsigned)x_chan, a_ex = (unsigned)cout * (unsigned)a_chan;         // and of an example: below 2^31
+    struct Operand { int c0, channels, chan; unsigned ex; };
+    const Operand ox{ci0, cin, x_chan, x_ex}, oa{co0, cout, a_chan, a_ex};
+    struct Where { unsigned off, last; int cut; };                 // byte offset from the dword that the example's stage starts in; the same in an example's
+                                                                   // last stage, and values that it was moved back by there
+    // lane's piece of wave instruction q.  odd: the example starts in the high half of its first dword
+    auto where = [&](auto is_x, int q, unsigned odd) {
+        constexpr bool X = decltype(is_x)::value;
+        constexpr unsigned pitch = X ? C::PX : C::PA;
+        constexpr int run = X ? C::GB_X : C::GB_A;
+        constexpr bool shifted = X ? C::ODD_X : C::ODD;
+        const Operand &o = X ? ox : oa;
+        const unsigned g = (unsigned)q / pitch, id = ((unsigned)q - g * pitch) * 64 + lane, ch = id / pitch, pc = id - ch * pitch;
+        unsigned e = (unsigned)min(o.c0 + (int)ch, o.channels - 1) * (unsigned)o.chan + odd;
+        const int pieces = shifted ? (run + 2 * (int)(e & 1u) + 15) / 16 : (X ? C::NX : C::NA);
+        const int in_run = (int)g * run + min((int)pc, pieces - 1) * 16;
+        if constexpr (shifted) e &= ~1u;
+        Where w{2u * e + (unsigned)in_run, 0u, 0};
+        const int before = (n_stages - 1) * C::SG * (run / 2);     // elements of a channel above its last stage
+        const int over = (int)(e + (unsigned)(in_run / 2 + before + 8) - (o.ex + odd));
+        w.last = w.off;
+        if (in_run / 2 >= o.chan - before + (shifted ? 1 : 0) || over >= 8) {
+            w.last = 0u;
+        } else if (over > 0) {
+            if (shifted && ((o.ex + odd) & 1)) {
+                w.last = 0u;                                       // (an example of an odd number of values may end inside a dword: mend_odd)
+            } else {
+                w.last = w.off - 2u * (unsigned)over;
+                w.cut = o.c0 + (int)ch < o.channels ? over : 0;
+            }
+        }
+        return w;
     };
-    // byte offset of a lane's piece from the dword that its example's stage starts in; LAST: the example's last stage (at most
-    // that many rows of it are there).  odd: the example starts in the high half of that dword
-    auto off_x = [&](int u, unsigned odd, bool last) {
-        const Piece p = piece(first_x + 4 * u, C::PX);
-        const int c = min(ci0 + p.ch, cin - 1);
-        unsigned e = (unsigned)c * (unsigned)x_chan + odd;
-        const int pieces = C::ODD_X ? (C::GB_X + 2 * (int)(e & 1u) + 15) / 16 : C::NX;
-        const int in_run = p.sub * C::GB_X + min(p.pc, pieces - 1) * 16;
-        if constexpr (C::ODD_X) e &= ~1u;
-        const unsigned off = 2u * e + (unsigned)in_run;
-        if (!last) return off;
-        const int before = (n_stages - 1) * C::SG * C::GB_X;       // bytes of a channel above its last stage
-        const bool there = in_run < 2 * x_chan - before + (C::ODD_X ? 2 : 0);
-        return there && (size_t)off + before + 16 <= 2 * (x_ex + odd) ? off : 0u;
+    typedef std::true_type is_x;
+    typedef std::false_type is_a;
+    // instruction u of this wave: always X, always dY, or either
+    auto kind = [&](auto uu) {
+        constexpr int u = decltype(uu)::value;
+        return 4 * u + 3 < C::QX ? true : (4 * u >= C::QX ? false : wave + 4 * u < C::QX);
     };
-    auto off_a = [&](int u, unsigned odd, bool last) {
-        const Piece p = piece(first_a + 4 * u, C::PA);
-        const int c = min(co0 + p.ch, cout - 1);
-        unsigned e = (unsigned)c * (unsigned)a_chan + odd;
-        const int pieces = C::ODD ? (C::GB_A + 2 * (int)(e & 1u) + 15) / 16 : C::NA;
-        const int in_run = p.sub * C::GB_A + min(p.pc, pieces - 1) * 16;
-        if constexpr (C::ODD) e &= ~1u;
-        const unsigned off = 2u * e + (unsigned)in_run;
-        if (!last) return off;
-        const int before = (n_stages - 1) * C::SG * C::GB_A;
-        const bool there = in_run < 2 * a_chan - before + (C::ODD ? 2 : 0);
-        return there && (size_t)off + before + 16 <= 2 * (a_ex + odd) ? off : 0u;
-    };
-    unsigned xo[C::UX], xl[C::UX], ao[C::UA], al[C::UA];
-#pragma unroll
-    for (int u = 0; u < C::UX; ++u) { xo[u] = off_x(u, 0u, false); xl[u] = off_x(u, 0u, true); }
-#pragma unroll
-    for (int u = 0; u < C::UA; ++u) { ao[u] = off_a(u, 0u, false); al[u] = off_a(u, 0u, true); }
+    using bundle_t = std::make_integer_sequence<int, C::UB>;
+    unsigned off[C::UB], off_last[C::UB];
+    int x_cut = 0, a_cut = 0;                                      // at most one piece of a lane: 16 u + values
+    c3_each(bundle_t{}, [&](auto uu) {
+        constexpr int u = decltype(uu)::value;
+        const int q = wave + 4 * u;
+        const bool x = kind(uu);
+        const Where w = x ? where(is_x{}, q, 0u) : where(is_a{}, min(q - C::QX, C::QA - 1), 0u);
+        x_cut |= C::PARTIAL_X && x && w.cut ? 16 * u + w.cut : 0;
+        a_cut |= C::PARTIAL_A && !x && w.cut && q < C::QX + C::QA ? 16 * u + w.cut : 0;
+        off[u] = w.off;
+        off_last[u] = w.last;
+    });
+    const bool x_cuts = C::PARTIAL_X && __ballot(x_cut != 0) != 0, a_cuts = C::PARTIAL_A && __ballot(a_cut != 0) != 0;
+    const bool odd_x_ex = C::ODD_X && (x_ex & 1), odd_a_ex = C::ODD && (a_ex & 1);
     const unsigned lds0 = __builtin_amdgcn_readfirstlane((unsigned)(size_t)lds);
-    auto x_at = [&](int i) { return reinterpret_cast<unsigned long long>(example_at_uniform<uint16_t>(a.x, a.x_tab, i, x_ex)); };
-    auto a_at = [&](int i) { return reinterpret_cast<unsigned long long>(example_at_uniform<uint16_t>(a.dy, a.dy_tab, i, a_ex)); };
-    struct Stream { unsigned long long base; int i, s, slot; };
-    auto fetch_x = [&](Stream &f) {
-        const bool last = f.s == n_stages - 1;
-        const unsigned odd = C::ODD_X ? (unsigned)(f.base >> 1) & 1u : 0u;
-        const unsigned long long b = (f.base & ~3ull) + (unsigned long long)f.s * (C::SG * C::GB_X);
-        const unsigned dst = lds0 + C::RING_X + f.slot * C::STAGE_X;
-#pragma unroll
-        for (int u = 0; u < C::UX; ++u) {
-            const int q = first_x + 4 * u;
-            if ((C::QX % 4 == 0 || u < C::UX - 1 || q < C::QX)) {
-                const unsigned off = C::ODD_X && odd ? off_x(u, odd, last) : (last ? xl[u] : xo[u]);
-                lds_direct_16(b, off, dst + q * 1024);
-            }
+    const unsigned long long x_ptr = reinterpret_cast<unsigned long long>(a.x), a_ptr = reinterpret_cast<unsigned long long>(a.dy);
+    const int x_tab = a.x_tab, a_tab = a.dy_tab;
+    // (by scalar loads: a wait for a vector load would wait for everything that is on its way to LDS)
+    auto x_at = [&](int i) { return x_tab ? scalar_load<unsigned long long>(x_ptr, (size_t)i * x_tab) : x_ptr + 2ull * x_ex * (unsigned)i; };
+    auto a_at = [&](int i) { return a_tab ? scalar_load<unsigned long long>(a_ptr, (size_t)i * a_tab) : a_ptr + 2ull * a_ex * (unsigned)i; };
+    // The next bundle to fetch: stages (and their examples) of X and dY, where they come from and go.  Past the end of the stream the last stages are
+    // fetched again, into slots that nobody reads any more: counts of what is on its way stay the same to the end.
+    unsigned long long fx_base = x_at(i_first), fa_base = a_at(i_first);
+    int fx_i = i_first, fx_s = s_begin, fa_i = i_first, fa_s = s_begin;
+    unsigned fx_dst = lds0 + C::RING_X, fa_dst = lds0 + C::RING_A;
+    auto fetch = [&](auto uu) {
+        constexpr int u = decltype(uu)::value;
+        const bool x = kind(uu);
+        const int q = wave + 4 * u;
+        const bool last = (x ? fx_s : fa_s) == n_stages - 1;
+        const unsigned long long base = x ? fx_base : fa_base;
+        const unsigned odd = (x ? odd_x_ex : odd_a_ex) ? (unsigned)(base >> 1) & 1u : 0u;
+        const unsigned long long b = ((x ? C::ODD_X : C::ODD) ? base & ~3ull : base) + (unsigned)(x ? fx_s * (C::SG * C::GB_X) : fa_s * (C::SG * C::GB_A));
+        unsigned dst = x ? fx_dst + q * 1024 : fa_dst + (q - C::QX) * 1024;
+        if (4 * u + 3 >= C::QX + C::QA && q >= C::QX + C::QA) dst = lds0 + C::DUMP;
+        unsigned o = last ? off_last[u] : off[u];
+        if (odd) {
+            const Where w = x ? where(is_x{}, q, 1u) : where(is_a{}, min(q - C::QX, C::QA - 1), 1u);
+            o = last ? w.last : w.off;
         }
-        f.slot = f.slot == C::D ? 0 : f.slot + 1;
-        if (++f.s == k_end) {
-            f.s = s_begin;
-            if (++f.i < i_last) f.base = x_at(f.i);
+        lds_direct_16(b, o, dst);
+    };
+    auto fetched_x = [&]() {
+        fx_dst = fx_dst == lds0 + C::RING_X + C::D * C::STAGE_X ? lds0 + C::RING_X : fx_dst + C::STAGE_X;
+        if (++fx_s == k_end) {
+            if (fx_i + 1 < i_last) { fx_s = s_begin; fx_base = x_at(++fx_i); }
+            else --fx_s;
         }
     };
-    auto fetch_a = [&](Stream &f) {
-        const bool last = f.s == n_stages - 1;
-        const unsigned odd = C::ODD ? (unsigned)(f.base >> 1) & 1u : 0u;
-        const unsigned long long b = (f.base & ~3ull) + (unsigned long long)f.s * (C::SG * C::GB_A);
-        const unsigned dst = lds0 + C::RING_A + f.slot * C::STAGE_A;
-#pragma unroll
-        for (int u = 0; u < C::UA; ++u) {
-            const int q = first_a + 4 * u;
-            if ((C::QA % 4 == 0 || u < C::UA - 1 || q < C::QA)) {
-                const unsigned off = C::ODD && odd ? off_a(u, odd, last) : (last ? al[u] : ao[u]);
-                lds_direct_16(b, off, dst + q * 1024);
-            }
-        }
-        f.slot = f.slot == C::D + 1 ? 0 : f.slot + 1;
-        if (++f.s == s_begin + a_stages) {
-            f.s = s_begin;
-            if (++f.i < i_last) f.base = a_at(f.i);
+    auto fetched_a = [&]() {
+        fa_dst = fa_dst == lds0 + C::RING_A + (C::D + 1) * C::STAGE_A ? lds0 + C::RING_A : fa_dst + C::STAGE_A;
+        if (++fa_s == a_end) {
+            if (fa_i + 1 < i_last) { fa_s = s_begin; fa_base = a_at(++fa_i); }
+            else --fa_s;
         }
     };
-    // the piece of an example's last channel that the example's end cuts: its values one by one (by the lane that fetched the rest of its
-    // wave instruction, after that has landed)
-    auto mend_x = [&](int i, int slot) {
-        const unsigned long long base = x_at(i);
-        const unsigned odd = C::ODD_X ? (unsigned)(base >> 1) & 1u : 0u;
+    // by the lane that fetched the piece, after that has landed
+    auto mend = [&](int gone, char *piece) {
+        if (gone) {
+            ulonglong2 *p = reinterpret_cast<ulonglong2 *>(piece);
+            ulonglong2 v = *p;
+            const int bits = 16 * gone;
+            v.x = bits < 64 ? (v.x >> bits) | (v.y << (64 - bits)) : v.y >> (bits - 64);
+            v.y = bits < 64 ? v.y >> bits : 0ull;
+            *p = v;
+        }
+    };
+    // the same in examples of an odd number of values: value by value from memory
+    auto mend_odd = [&](auto which, unsigned long long base, char *stage) {
+        constexpr bool X = decltype(which)::value;
+        constexpr unsigned pitch = X ? C::PX : C::PA, run = (X ? C::GB_X : C::GB_A) / 2;
+        const Operand &o = X ? ox : oa;
+        const unsigned odd = (unsigned)(base >> 1) & 1u;
         const uint16_t *src = reinterpret_cast<const uint16_t *>(base & ~3ull);
-        const size_t end = x_ex + odd;
+        const unsigned end = o.ex + odd;
 #pragma unroll 1
-        for (int u = 0; u < C::UX; ++u) {
-            const int q = first_x + 4 * u;
-            const Piece p = piece(q, C::PX);
-            if (q >= C::QX || ci0 + p.ch != cin - 1 || p.pc >= C::NX) continue;
-            const int in_run = p.sub * (C::GB_X / 2) + p.pc * 8;
-            size_t e = (size_t)(cin - 1) * x_chan + odd;
-            if (C::ODD_X) e &= ~(size_t)1;
-            e += (size_t)(n_stages - 1) * (C::SG * C::GB_X / 2) + in_run;
-            if (e >= end || e + 8 <= end) continue;
-            uint16_t *dst = reinterpret_cast<uint16_t *>(lds + C::RING_X + slot * C::STAGE_X + q * 1024 + lane * 16);
+        for (int u = 0; u < C::UB; ++u) {
+            const int q = wave + 4 * u - (X ? 0 : C::QX);
+            if (q < 0 || q >= (X ? C::QX : C::QA)) continue;
+            const unsigned g = (unsigned)q / pitch, id = ((unsigned)q - g * pitch) * 64 + lane, ch = id / pitch, pc = id - ch * pitch;
+            if (o.c0 + (int)ch != o.channels - 1 || pc >= (unsigned)(X ? C::NX : C::NA)) continue;
+            const unsigned e = (((unsigned)(o.channels - 1) * (unsigned)o.chan + odd) & ~1u) + (unsigned)(n_stages - 1) * (C::SG * run) + g * run + pc * 8;
+            uint16_t *dst = reinterpret_cast<uint16_t *>(stage + q * 1024 + lane * 16);
 #pragma unroll 1
-            for (int k = 0; e + k < end; ++k) dst[k] = src[e + k];
+            for (unsigned k = 0; k < 8 && e + k < end; ++k) dst[k] = src[e + k];
         }
     };
-    auto mend_a = [&](int i, int slot) {
-        const unsigned long long base = a_at(i);
-        const unsigned odd = C::ODD ? (unsigned)(base >> 1) & 1u : 0u;
-        const uint16_t *src = reinterpret_cast<const uint16_t *>(base & ~3ull);
-        const size_t end = a_ex + odd;
-#pragma unroll 1
-        for (int u = 0; u < C::UA; ++u) {
-            const int q = first_a + 4 * u;
-            const Piece p = piece(q, C::PA);
-            if (q >= C::QA || co0 + p.ch != cout - 1 || p.pc >= C::NA) continue;
-            const int in_run = p.sub * (C::GB_A / 2) + p.pc * 8;
-            size_t e = (size_t)(cout - 1) * a_chan + odd;
-            if (C::ODD) e &= ~(size_t)1;
-            e += (size_t)(n_stages - 1) * (C::SG * C::GB_A / 2) + in_run;
-            if (e >= end || e + 8 <= end) continue;
-            uint16_t *dst = reinterpret_cast<uint16_t *>(lds + C::RING_A + slot * C::STAGE_A + q * 1024 + lane * 16);
-#pragma unroll 1
-            for (int k = 0; e + k < end; ++k) dst[k] = src[e + k];
+    // ---- what has to be done to the pieces of a stage that this wave fetched, once they have landed and before the barrier that shows them to the
+    // others: a piece that an example's end cut; dY in the clip-weighted form: times the example's factor, rounded to bf16
+    auto touch_x = [&](int i, int s, int slot) {
+        if (C::PARTIAL_X && s == n_stages - 1 && i < i_last) {
+            if (odd_x_ex) { if (ci0 + 64 >= cin) mend_odd(is_x{}, x_at(i), lds + C::RING_X + slot * C::STAGE_X); }
+            else if (x_cuts) mend(x_cut & 15, lds + C::RING_X + slot * C::STAGE_X + (wave + 4 * (x_cut >> 4)) * 1024 + lane * 16);
         }
     };
-    const bool mends_x = C::PARTIAL_X && ci0 + 64 >= cin, mends_a = C::PARTIAL_A && co0 + 64 >= cout;
-    // clip-weighted form: a wave multiplies the pieces of dY that it fetched by the example's factor, rounded to bf16
-    auto scale_a = [&](int i, int slot) {
-        const float f = a.group_sqnorm ? clip_factor(a.group_sqnorm[i], a.clip_c) : 1.0f;
-#pragma unroll
-        for (int u = 0; u < C::UA; ++u) {
-            const int q = first_a + 4 * u;
-            if ((C::QA % 4 == 0 || u < C::UA - 1 || q < C::QA)) {
-                uint4 *p = reinterpret_cast<uint4 *>(lds + C::RING_A + slot * C::STAGE_A + q * 1024 + lane * 16);
-                const uint4 v = *p;
-                uint32_t t[4] = {v.x, v.y, v.z, v.w};
-                scale_regs<true, 4>(t, f);
-                *p = make_uint4(t[0], t[1], t[2], t[3]);
-            }
+    auto touch_a = [&](int i, int s, int slot) {
+        if (C::PARTIAL_A && s == n_stages - 1 && i < i_last) {
+            if (odd_a_ex) { if (co0 + 64 >= cout) mend_odd(is_a{}, a_at(i), lds + C::RING_A + slot * C::STAGE_A); }
+            else if (a_cuts) mend(a_cut & 15, lds + C::RING_A + slot * C::STAGE_A + (wave + 4 * (a_cut >> 4) - C::QX) * 1024 + lane * 16);
         }
     };
+    // the factors of 64 examples, one a lane
+    const float *sqnorms = WEIGHTED ? a.group_sqnorm : nullptr;
+    float factors = 1.0f;
+    int factors_at = i_first;
+    auto load_factors = [&](int from) {
+        factors_at = from;
+        if (sqnorms) factors = clip_factor(sqnorms[min(from + lane, i_last - 1)], a.clip_c);
+    };
+    constexpr int US = C::QX / 4;                     // a wave's first instruction that may be dY's
+    struct Scaled { uint4 v[C::UB - US]; };
+    auto scale_at = [&](auto uu, int slot) {          // where what instruction u fetched lies, if it is dY's
+        constexpr int u = decltype(uu)::value;
+        const int q = wave + 4 * u;
+        const bool here = (4 * u >= C::QX || q >= C::QX) && (4 * u + 3 < C::QX + C::QA || q < C::QX + C::QA);
+        return here ? lds + C::RING_A + slot * C::STAGE_A + (q - C::QX) * 1024 + lane * 16 : lds + C::DUMP + lane * 16;
+    };
+    auto scale_read = [&](int slot) {
+        Scaled o;
+        c3_each(std::make_integer_sequence<int, C::UB - US>{}, [&](auto k) {
+            o.v[k.value] = *reinterpret_cast<const uint4 *>(scale_at(std::integral_constant<int, US + decltype(k)::value>{}, slot));
+        });
+        return o;
+    };
+    auto scale_write = [&](Scaled &o, float f, int slot) {
+        c3_each(std::make_integer_sequence<int, C::UB - US>{}, [&](auto k) {
+            uint32_t t[4] = {o.v[k.value].x, o.v[k.value].y, o.v[k.value].z, o.v[k.value].w};
+            scale_regs<true, 4>(t, f);
+            *reinterpret_cast<uint4 *>(scale_at(std::integral_constant<int, US + decltype(k)::value>{}, slot)) = make_uint4(t[0], t[1], t[2], t[3]);
+        });
+    };
+    static_assert(!WEIGHTED || C::DUMP + 1024 <= C::LDS, "a place for what is not dY's");
 
     f32x16 acc[9];
+    auto clear = [&]() {
 #pragma unroll
-    for (int t = 0; t < 9; ++t)
+        for (int t = 0; t < 9; ++t)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) acc[t][r] = 0.0f;
+            for (int r = 0; r < 16; ++r) acc[t][r] = 0.0f;
+    };
 
-    if (threadIdx.x < C::ZEROS / 16) *reinterpret_cast<uint4 *>(lds + threadIdx.x * 16) = make_uint4(0u, 0u, 0u, 0u);
-    Stream fx{x_at(i_first), i_first, s_begin, 0}, fa{a_at(i_first), i_first, s_begin, 0};
-    int x_issued = 0, a_issued = 0;
-    fetch_a(fa);
-    a_issued = 1;
+    // ---- dY of stage 0, then bundles 0 .. D - 1; bundle t + D is issued during stage t, into what stage t - 1 has left
+    c3_each(bundle_t{}, [&](auto uu) {
+        if (!kind(uu) && wave + 4 * decltype(uu)::value < C::QX + C::QA) fetch(uu);
+    });
+    fetched_a();
 #pragma unroll
     for (int k = 0; k < C::D; ++k) {
-        if (x_issued < T) { fetch_x(fx); ++x_issued; }
-        if (a_issued < TA) { fetch_a(fa); ++a_issued; }
+        c3_each(bundle_t{}, fetch);
+        fetched_x();
+        fetched_a();
     }
+    clear();
+    if (threadIdx.x < C::ZEROS / 16) *reinterpret_cast<uint4 *>(lds + threadIdx.x * 16) = make_uint4(0u, 0u, 0u, 0u);
 
     // operand reads: lane -> channel (lane & 31) of its 32, and the upper or lower one of a pair of rows
     const unsigned lane_x = (unsigned)((wn * 32 + (lane & 31)) * (C::PX * 16)), lane_a = (unsigned)((wm * 32 + (lane & 31)) * (C::PA * 16));
     const int x_odd_chan = C::ODD_X ? ((ci0 + wn * 32 + (lane & 31)) * x_chan) & 1 : 0;
     const int a_odd_chan = C::ODD ? ((co0 + wm * 32 + (lane & 31)) * a_chan) & 1 : 0;
 
-    int ci = i_first, cs = s_begin;                   // stage whose products run
-    int ni = i_first, ns = s_begin;                   // the stage of dY behind it in the stream
-    auto next_a = [&]() {
-        if (++ns == s_begin + a_stages) { ns = s_begin; ++ni; }
+    int ci = i_first, cs = s_begin, x_slot = 0, a_slot = 0;        // the stage whose products run
+    int na_i = i_first, na_s = s_begin, na_slot = 0;               // the stage of dY that is touched next
+    auto touched_a = [&]() {
+        na_slot = na_slot == C::D + 1 ? 0 : na_slot + 1;
+        if (++na_s == a_end) { na_s = s_begin; ++na_i; }
     };
-    int x_slot = 0, a_slot = 0;
-    uint4 carry[STRIDE == 1 ? C::PPR : 1];            // dY rows 2 q - 1 and 2 q, from the pair of rows before
-
-    // stage t of the stream: its rows are there, the loads that the rings have room for are on their way
-    int a_next = 1;
-    auto arrive = [&](int t) {
-        // X of this stage and dY of the next one are bundle t; up to D - 1 younger bundles may still be on their way
-        {
-            const int mine = (C::QX - first_x + 3) / 4 + (C::QA - first_a + 3) / 4;
-            const int young = min(C::D - 1, T - 2 - t);
-            if (young <= 0) wait_vmcnt<0>();
-            else if (young == 1) { if (mine == C::BUNDLE) wait_vmcnt<C::BUNDLE>(); else wait_vmcnt<C::BUNDLE - 1>(); }
-            else { if (mine == C::BUNDLE) wait_vmcnt<2 * C::BUNDLE>(); else wait_vmcnt<2 * C::BUNDLE - 2>(); }
-        }
-        a_next = a_slot == C::D + 1 ? 0 : a_slot + 1;
-        if (t == 0) {
-            if (mends_a && ns == n_stages - 1) mend_a(ni, a_slot);
-            if constexpr (WEIGHTED) scale_a(ni, a_slot);
-            next_a();
-        }
-        if (t + 1 < TA) {
-            if (mends_a && ns == n_stages - 1) mend_a(ni, a_next);
-            if constexpr (WEIGHTED) scale_a(ni, a_next);
-            next_a();
-        }
-        if (mends_x && cs == n_stages - 1) mend_x(ci, x_slot);
-        __syncthreads();                              // everyone's pieces are there; the stage before has been read
-        if (x_issued < T) { fetch_x(fx); ++x_issued; }
-        if (a_issued < TA) { fetch_a(fa); ++a_issued; }
+    auto factor_of = [&](int i) {
+        if (i - factors_at >= 64) load_factors(i);
+        return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, factors), i - factors_at));
     };
-    auto leave = [&]() {
-        x_slot = x_slot == C::D ? 0 : x_slot + 1;
-        a_slot = a_next;
-        if (++cs == k_end) { cs = s_begin; ++ci; }
-    };
+    auto slot_after = [](int slot, int slots) { return slot + 1 == slots ? 0 : slot + 1; };
     // this lane's one of rows r and r + 1 of dY, counted from the first one of the stage at hand, of which the image has `below` from there on:
     // those below it are zeros
     int below = 0;
@@ -536,94 +560,208 @@ __device__ __forceinline__ void conv3x3_body(const C3Args &a, const unsigned bid
         if (r + 1 >= below && r + half >= below) o.at = 0u;
         return o;
     };
-    auto rows_here = [&]() {
-        odd_x = C::ODD_X ? (unsigned)(x_odd_chan + ((x_ex & 1) ? (int)((x_at(ci) >> 1) & 1) : 0)) & 1u : 0u;
-        odd_a = C::ODD ? (unsigned)(a_odd_chan + ((a_ex & 1) ? (int)((a_at(ci) >> 1) & 1) : 0)) & 1u : 0u;
+    auto begin = [&]() {                              // a stage begins: everyone's pieces are there, those of the stage before have been read
+        __syncthreads();
+        odd_x = C::ODD_X ? (unsigned)(x_odd_chan + (odd_x_ex ? (int)((x_at(ci) >> 1) & 1) : 0)) & 1u : 0u;
+        odd_a = C::ODD ? (unsigned)(a_odd_chan + (odd_a_ex ? (int)((a_at(ci) >> 1) & 1) : 0)) & 1u : 0u;
         xs = C::RING_X + x_slot * C::STAGE_X + lane_x;
         as = C::RING_A + a_slot * C::STAGE_A + lane_a;
-        an = C::RING_A + a_next * C::STAGE_A + lane_a;
+        an = C::RING_A + slot_after(a_slot, C::D + 2) * C::STAGE_A + lane_a;
         below = H - cs * C::RPS;
     };
+    int stores = 0;                                   // for how many more waits the stores of a row of results are younger than what is waited for
+    // this wave's pieces of what the next stage reads (bundle t + 1) have landed: as many bundles as were issued after it are on their way
+    auto landed = [&](auto young) {
+        constexpr int n = decltype(young)::value * C::UB;
+        if (MODE == C3_FULL && stores > 0) { wait_vmcnt<n + 48 < 63 ? n + 48 : 63>(); --stores; }
+        else wait_vmcnt<n>();
+    };
+    Scaled scaled;
+    float f = 1.0f;
+    auto prepare = [&](auto young) {
+        landed(young);
+        touch_a(na_i, na_s, na_slot);
+        touch_x(ci + (cs + 1 == k_end ? 1 : 0), cs + 1 == k_end ? s_begin : cs + 1, slot_after(x_slot, C::D + 1));
+        if constexpr (WEIGHTED) {
+            scaled = scale_read(na_slot);
+            f = factor_of(min(na_i, i_last - 1));
+        }
+    };
+    auto prepared = [&]() {
+        if constexpr (WEIGHTED) scale_write(scaled, f, na_slot);
+        touched_a();
+    };
+    auto leave = [&]() {
+        x_slot = slot_after(x_slot, C::D + 1);
+        a_slot = slot_after(a_slot, C::D + 2);
+        if (++cs == k_end) { cs = s_begin; ++ci; }
+    };
+    using pieces_t = std::make_integer_sequence<int, C::PPR>;
+    uint4 carry[STRIDE == 1 ? C::PPR : 1];            // dY rows 2 q - 1 and 2 q, from the pair of rows before
+    auto carry_from = [&](const C3Row o) {
+        c3_each(pieces_t{}, [&](auto j) { if constexpr (STRIDE == 1) carry[j.value] = c3_piece<W, j.value>(lds + o.at, o.bits); });
+    };
+    // the operands of a K step: a piece of the rows of X and of both pairs of rows of dY
+    struct Ops { uint4 x[STRIDE == 1 ? 1 : 4], a0, a1; };
+    struct Rows { C3Row x, y0, y1; };
+    auto rows_of = [&](int p) { return Rows{row_x(2 * p), row_a(2 * p + 1), row_a(2 * p)}; };
+    auto load = [&](const Rows &r, auto jj) {
+        constexpr int j = decltype(jj)::value;
+        Ops o;
+        if constexpr (STRIDE == 1) {
+            o.x[0] = c3_piece<W, j>(lds + r.x.at, r.x.bits);
+        } else {
+#pragma unroll
+            for (int k = 0; k < 2; ++k) {             // row 2 oh of X, then 2 oh + 1
+                const char *row = lds + r.x.at + (r.x.at ? k * C::ROW_X : 0);
+                o.x[2 * k] = c3_piece<C::XW, 2 * j>(row, 0u);
+                if constexpr (16 * j + 8 < C::XW) o.x[2 * k + 1] = c3_piece<C::XW, 2 * j + 1>(row, 0u);
+                else o.x[2 * k + 1] = make_uint4(0u, 0u, 0u, 0u);
+            }
+        }
+        o.a1 = c3_piece<W, j>(lds + r.y1.at, r.y1.bits);
+        o.a0 = c3_piece<W, j>(lds + r.y0.at, r.y0.bits);
+        return o;
+    };
+    // Work that is not products is dealt out between them, three MFMAs at a time, so that the matrix units have something meanwhile: the next bundle's
+    // loads in the first half of a stage's first pair of rows, then the wait for the bundle before and the factors.
+    constexpr int SLOTS = 3 * C::PPR;
+    auto between = [&](auto kk) {
+        constexpr int k = decltype(kk)::value;
+        c3_each(bundle_t{}, [&](auto uu) { if constexpr (decltype(uu)::value * ((SLOTS + 1) / 2) / C::UB == k) fetch(uu); });
+        if constexpr (k == (SLOTS - 1) / 2) { fetched_x(); fetched_a(); }
+        if constexpr (C::D > 1 && k == (SLOTS + 1) / 2) prepare(std::integral_constant<int, C::D - 1>{});
+        if constexpr (C::D > 1 && k == SLOTS - 1) prepared();
+    };
+
+    // ---- the first bundle
+    if constexpr (WEIGHTED) load_factors(i_first);
+    wait_vmcnt<(C::D - 1) * C::UB>();
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+        touch_a(na_i, na_s, na_slot);
+        if constexpr (WEIGHTED) {
+            Scaled o = scale_read(na_slot);
+            scale_write(o, factor_of(min(na_i, i_last - 1)), na_slot);
+        }
+        touched_a();
+    }
+    touch_x(ci, cs, 0);
     int t = 0;
     if (STRIDE == 1 && cut && s_begin < k_begin) {    // the stage above a slice: its last row and the next stage's first
-        arrive(t++);
-        rows_here();
-        const C3Row o = row_a(C::RPS - 1);
-        c3_each(pieces_t{}, [&](auto j) { if constexpr (STRIDE == 1) carry[j.value] = c3_piece<W, j.value>(lds + o.at, o.bits); });
+        begin();
+        carry_from(row_a(C::RPS - 1));
+        c3_each(bundle_t{}, fetch);
+        fetched_x();
+        fetched_a();
+        prepare(std::integral_constant<int, C::D - 1>{});
+        prepared();
         leave();
+        ++t;
     }
+    int row = row0, in_row = 0, half_red = 0;
     for (; t < T; ++t) {
-        arrive(t);
-        rows_here();
-        if constexpr (STRIDE == 1) {
-            if (cs == 0) {                            // the pair above the first one: row -1 is zeros, row 0 this stage's first
-                C3Row o{0u, 0u};
-                if (half) o = C3Row{as + (odd_a >> 1) * 4u, odd_a * 16u};
-                c3_each(pieces_t{}, [&](auto j) { carry[j.value] = c3_piece<W, j.value>(lds + o.at, o.bits); });
-            }
+        begin();
+        if (MODE == C3_FULL && row > row0 && in_row == 0 && cs == s_begin && threadIdx.x == 0) {       // (the barrier has just shown the waves' shares)
+            const float *r = red[half_red ^ 1];
+            a.partials[(row - 1) * tiles + tile] = r[0] + r[1] + r[2] + r[3];
         }
-#pragma unroll
-        for (int p = 0; p < C::PAIRS; ++p) {
-            if (p > 0 && 2 * p >= below) continue;                    // uniform
-            const C3Row x = row_x(2 * p), y1 = row_a(2 * p), y0 = row_a(2 * p + 1);
-            if constexpr (STRIDE == 1) {
-                uint32_t left = 0u;                                   // the two columns before the piece
-                uint4 b1 = c3_piece<W, 0>(lds + x.at, x.bits);
-                c3_each(pieces_t{}, [&](auto jj) {
-                    constexpr int j = jj.value;
-                    uint4 ahead = make_uint4(0u, 0u, 0u, 0u);
-                    if constexpr (j + 1 < C::PPR) ahead = c3_piece<W, j + 1>(lds + x.at, x.bits);
-                    const uint4 a0 = c3_piece<W, j>(lds + y0.at, y0.bits), a1 = c3_piece<W, j>(lds + y1.at, y1.bits);
+        if constexpr (STRIDE == 1) {
+            // the pair above the first one: row -1 is zeros, row 0 this stage's first
+            if (cs == 0) carry_from(half ? C3Row{as + (odd_a >> 1) * 4u, odd_a * 16u} : C3Row{0u, 0u});
+        }
+        Rows rows = rows_of(0);
+        Ops next = load(rows, std::integral_constant<int, 0>{});
+        c3_each(std::make_integer_sequence<int, C::PAIRS>{}, [&](auto pp) {
+            constexpr int p = decltype(pp)::value;
+            if (p > 0 && 2 * p >= below) return;      // uniform
+            uint32_t left[2] = {0u, 0u};              // the two columns before the piece
+            const Rows rows2 = p + 1 < C::PAIRS ? rows_of(p + 1) : rows;
+            c3_each(pieces_t{}, [&](auto jj) {
+                constexpr int j = decltype(jj)::value;
+                auto gap = [&](auto g) {
+                    if constexpr (p == 0) between(std::integral_constant<int, 3 * j + decltype(g)::value>{});
+                };
+                // the operands of the step after this one are read while its products run
+                const Ops o = next;
+                if constexpr (j + 1 < C::PPR) next = load(rows, std::integral_constant<int, j + 1>{});
+                else if constexpr (p + 1 < C::PAIRS) next = load(rows2, std::integral_constant<int, 0>{});
+                if constexpr (STRIDE == 1) {
+                    const uint4 b1 = o.x[0];
+                    const uint32_t right = j + 1 < C::PPR ? next.x[0].x : 0u;
                     // the same run of columns one to the left and one to the right
-                    const uint32_t o0 = funnel(b1.x, left, 16), o1 = funnel(b1.y, b1.x, 16), o2 = funnel(b1.z, b1.y, 16), o3 = funnel(b1.w, b1.z, 16),
-                                   o4 = funnel(ahead.x, b1.w, 16);
+                    const uint32_t o0 = funnel(b1.x, left[0], 16), o1 = funnel(b1.y, b1.x, 16), o2 = funnel(b1.z, b1.y, 16), o3 = funnel(b1.w, b1.z, 16),
+                                   o4 = funnel(right, b1.w, 16);
                     const uint4 b0 = make_uint4(o0, o1, o2, o3), b2 = make_uint4(o1, o2, o3, o4);
-                    c3_taps(acc, 1, a1, b0, b1, b2);
-                    c3_taps(acc, 0, a0, b0, b1, b2);
+                    c3_taps(acc, 1, o.a1, b0, b1, b2);
+                    gap(std::integral_constant<int, 0>{});
+                    c3_taps(acc, 0, o.a0, b0, b1, b2);
+                    gap(std::integral_constant<int, 1>{});
                     c3_taps(acc, 2, carry[j], b0, b1, b2);
-                    carry[j] = a0;
-                    left = b1.w;
-                    b1 = ahead;
-                });
-            } else {
-                uint32_t left[2] = {0u, 0u};
-                c3_each(pieces_t{}, [&](auto jj) {
-                    constexpr int j = jj.value;
-                    const uint4 a1 = c3_piece<W, j>(lds + y1.at, y1.bits), a0 = c3_piece<W, j>(lds + y0.at, y0.bits);
+                    gap(std::integral_constant<int, 2>{});
+                    carry[j] = o.a0;
+                    left[0] = b1.w;
+                } else {
 #pragma unroll
-                    for (int odd_row = 0; odd_row < 2; ++odd_row) {   // row 2 oh of X, then 2 oh + 1
-                        const char *row = lds + x.at + (x.at ? odd_row * C::ROW_X : 0);
-                        const uint4 v = c3_piece<C::XW, 2 * j>(row, 0u);
-                        uint4 w = make_uint4(0u, 0u, 0u, 0u);
-                        if constexpr (16 * j + 8 < C::XW) w = c3_piece<C::XW, 2 * j + 1>(row, 0u);
-                        const uint4 b0 = make_uint4(c3_high(v.x, left[odd_row]), c3_high(v.z, v.y), c3_high(w.x, v.w), c3_high(w.z, w.y)),     // X[2 ow - 1]
-                                    b1 = make_uint4(c3_low(v.y, v.x), c3_low(v.w, v.z), c3_low(w.y, w.x), c3_low(w.w, w.z)),                 // X[2 ow]
-                                    b2 = make_uint4(c3_high(v.y, v.x), c3_high(v.w, v.z), c3_high(w.y, w.x), c3_high(w.w, w.z));             // X[2 ow + 1]
-                        left[odd_row] = w.w;
-                        if (odd_row == 0) {
-                            c3_taps(acc, 1, a1, b0, b1, b2);
+                    for (int k = 0; k < 2; ++k) {
+                        const uint4 v = o.x[2 * k], w = o.x[2 * k + 1];
+                        const uint4 b0 = make_uint4(c3_high(v.x, left[k]), c3_high(v.z, v.y), c3_high(w.x, v.w), c3_high(w.z, w.y)),       // X[2 ow - 1]
+                                    b1 = make_uint4(c3_low(v.y, v.x), c3_low(v.w, v.z), c3_low(w.y, w.x), c3_low(w.w, w.z)),             // X[2 ow]
+                                    b2 = make_uint4(c3_high(v.y, v.x), c3_high(v.w, v.z), c3_high(w.y, w.x), c3_high(w.w, w.z));         // X[2 ow + 1]
+                        left[k] = w.w;
+                        if (k == 0) {
+                            c3_taps(acc, 1, o.a1, b0, b1, b2);
+                            gap(std::integral_constant<int, 0>{});
                         } else {
-                            c3_taps(acc, 2, a1, b0, b1, b2);
-                            c3_taps(acc, 0, a0, b0, b1, b2);
+                            c3_taps(acc, 2, o.a1, b0, b1, b2);
+                            gap(std::integral_constant<int, 1>{});
+                            c3_taps(acc, 0, o.a0, b0, b1, b2);
+                            gap(std::integral_constant<int, 2>{});
                         }
                     }
-                });
-            }
+                }
+            });
+            rows = rows2;
+        });
+        if constexpr (C::D == 1) {
+            prepare(std::integral_constant<int, 0>{});
+            prepared();
         }
         leave();
+        if constexpr (MODE == C3_FULL) {
+            if (cs == s_begin && ++in_row == per_row) {
+                // a row of results: its share of the norm, its gradient; the next row's stages are on their way meanwhile
+                in_row = 0;
+                const float ss = c3_squares(acc, a, co0, ci0, wm, wn, lane);
+                if (lane == 63) red[half_red][wave] = ss;
+                half_red ^= 1;
+                if (a.out_w) {
+                    if (!C::STREAMS) { wait_vmcnt<0>(); __syncthreads(); }       // (one row alone: the rings are free)
+                    const bool all = c3_store(acc, a, row, co0, ci0, wm, wn, lane, reinterpret_cast<float *>(lds + C::STORE) + wave * (2 * C3_RP));
+                    stores = all ? C::D - 1 : 0;
+                }
+                ++row;
+                clear();
+            }
+        }
     }
+    wait_vmcnt<0>();                                  // (the stages that were fetched again)
 
     if constexpr (MODE == C3_FULL) {
-        c3_epilogue(acc, a, result, unit, co0, ci0, wm, wn, lane, red, lds);
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            const float *r = red[half_red ^ 1];
+            a.partials[(row - 1) * tiles + tile] = r[0] + r[1] + r[2] + r[3];
+        }
     } else if (WEIGHTED && a.ksplit == 1) {
         c3_add_to_accumulator(acc, a, co0, ci0, wm, wn, lane, lds);
     } else {
-        const size_t slot = (size_t)unit * a.ksplit + split;
-        float *mine = a.ws_part + slot * (9 * 16 * C3_THREADS);
+        const size_t slot = (size_t)(WEIGHTED ? (unsigned)tile : pick) * a.ksplit + split;
+        float *mine_part = a.ws_part + slot * (9 * 16 * C3_THREADS);
 #pragma unroll
         for (int t = 0; t < 9; ++t)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) mine[(t * 16 + r) * C3_THREADS + threadIdx.x] = acc[t][r];
+            for (int r = 0; r < 16; ++r) mine_part[(t * 16 + r) * C3_THREADS + threadIdx.x] = acc[t][r];
     }
 }
 
@@ -773,6 +911,7 @@ struct C3Plan {
     int ksplit, stages_per_split;      // per-example modes: K slices; weighted: example ranges
     int ex_per_split;                  // weighted
     int slice_ex;                      // per-example modes: examples per slice of a clipping unit, or 0
+    int rows_per_wg;                   // per-example modes, not sliced: rows of results per workgroup
 };
 
 int rows_of_width(int ow, int stride)
@@ -795,7 +934,7 @@ size_t c3_reported_copy(const Geo &g)
 thread_local int c3_forced_crowd = -1;
 int c3_plan_crowd() { return c3_forced_crowd >= 0 ? c3_forced_crowd : crowd_hint(); }
 
-C3Plan c3_plan(const Geo &g, int mode)
+C3Plan c3_plan_slices(const Geo &g, int mode)
 {
     C3Plan p;
     p.tiles_co = (g.cout + 63) / 64;
@@ -806,6 +945,7 @@ C3Plan c3_plan(const Geo &g, int mode)
     p.stages_per_split = 0;
     p.ex_per_split = g.n;
     p.slice_ex = 0;
+    p.rows_per_wg = 1;
     const long long tiles = (long long)p.tiles_co * p.tiles_ci;
     // inside a batch call: chunks per workgroup to plan for (a chunk here is about eight 128x128x64 chunks of work, but
     // slices cost a second pass over partial blocks: only very long walks are cut)
@@ -817,13 +957,10 @@ C3Plan c3_plan(const Geo &g, int mode)
         // example ranges: about 256 workgroups, partial blocks in the workspace kept below ~100 MB; in a launch
         // shared with other layers, ranges of at most 48 chunks
         long long want = (256 + tiles - 1) / tiles;
-        // (measured in the replayed step: one range -- no partial blocks, no slice-sum launch, a narrow launch that the
-        // other streams overlap -- beats four ranges by 4 % of the whole step; a walk is still capped at 48 chunks)
-        // and a layer of few tiles still brings 32 workgroups
-        if (crowd) {
-            want = ((long long)g.n * p.chunks + 47) / 48;
-            if (want * tiles < 32) want = (32 + tiles - 1) / tiles;
-        }
+        // (measured in the replayed step: a narrow launch that the other streams overlap, without partial blocks and slice-sum launch, beats
+        // ranges that would fill the chip.  ResNet-50, 32 examples: one range per tile 6690 us a step, two for the 14-wide layers (16 tiles)
+        // 6850, four 7030; a walk is still capped at 48 chunks)
+        if (crowd) want = ((long long)g.n * p.chunks + 47) / 48;
         const long long cap = (long long)(96.0e6 / (4.0 * 9 * 16 * C3_THREADS * (double)tiles));
         if (want > cap) want = cap;
         if (want > g.n) want = g.n;
@@ -856,6 +993,21 @@ C3Plan c3_plan(const Geo &g, int mode)
         p.stages_per_split = (int)((stages + want - 1) / want);
         p.ksplit = (stages + p.stages_per_split - 1) / p.stages_per_split;
     }
+    return p;
+}
+
+C3Plan c3_plan(const Geo &g, int mode)
+{
+    C3Plan p = c3_plan_slices(g, mode);
+    if (mode == MODE_WEIGHTED || p.ksplit > 1 || !c3_streams(g.ow, g.stride)) return p;
+    // Starting a workgroup costs as much as three stages: one that walks fewer than sixteen takes several rows of results in a row, as long as
+    // two workgroups are left for every compute unit (in a launch that other layers share: a workgroup for every second one)
+    const long long stages = (long long)g.unit * ((g.oh + p.stage_rows - 1) / p.stage_rows), rows = g.n / g.unit, tiles = (long long)p.tiles_co * p.tiles_ci;
+    long long k = 16 / stages;
+    const long long most = rows * tiles / (c3_plan_crowd() ? 128 : 512);
+    if (k > most) k = most;
+    if (k > rows) k = rows;
+    if (k > 1) p.rows_per_wg = (int)k;
     return p;
 }
 
@@ -991,13 +1143,13 @@ dp_status launch_conv3x3(const Geo &g, int mode, const void *x, const void *dy, 
     const C3Plan p = c3_plan(g, mode);
     C3Args a;
     a.variant = -1;
-    a.rows = g.n / g.unit; a.unit = g.unit; a.slice_ex = p.slice_ex;
+    a.rows = g.n / g.unit; a.unit = g.unit; a.slice_ex = p.slice_ex; a.rows_per_wg = p.rows_per_wg;
     a.x = x; a.dy = dy; a.x_tab = g.x_tab; a.dy_tab = g.dy_tab;
     a.out_w = out_w;
     a.out_stride = out_stride ? out_stride : g.pw;
     a.group_sqnorm = group_sqnorm; a.clip_c = clip_c;
     a.n = g.n; a.cin = g.cin; a.cout = g.cout; a.h = g.oh; a.hin = g.h;
-    a.tiles_co = p.tiles_co; a.tiles_ci = p.tiles_ci;
+    a.tiles_co = p.tiles_co; a.tiles_ci = p.tiles_ci; a.stages = (g.oh + p.stage_rows - 1) / p.stage_rows;
     a.ksplit = p.ksplit; a.stages_per_split = p.stages_per_split;
     a.ex_per_split = p.ex_per_split;
     const size_t tiles = (size_t)p.tiles_co * p.tiles_ci;
@@ -1009,8 +1161,9 @@ dp_status launch_conv3x3(const Geo &g, int mode, const void *x, const void *dy, 
         w += c3_align16(units * c3_partials_per_unit(p) * sizeof(float));
     }
     a.ws_part = p.ksplit > 1 ? reinterpret_cast<float *>(w) : nullptr;
-    const long long total = (long long)units * p.ksplit;
+    const long long total = weighted || p.ksplit > 1 ? (long long)units * p.ksplit : (long long)((a.rows + p.rows_per_wg - 1) / p.rows_per_wg) * tiles;
     const unsigned blocks = (unsigned)(((total + 7) / 8) * 8);
+    a.total = (int)total;
     dp_status st;
     if (g.stride == 2) {
         if (g.ow == 7) st = c3_launch_w<7, 2>(a, weighted, blocks, s);

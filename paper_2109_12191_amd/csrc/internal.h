@@ -237,6 +237,14 @@ __device__ __forceinline__ const E *example_at_uniform(const void *p, int tab, i
     return reinterpret_cast<const E *>(((unsigned long long)hi << 32) | lo);
 }
 
+// Element i of an array that nothing writes while the kernel runs, by a scalar load (i and the address are the same in every lane).
+template <typename E>
+__device__ __forceinline__ E scalar_load(unsigned long long array, size_t i)
+{
+    typedef const E __attribute__((address_space(4))) *constant;
+    return reinterpret_cast<constant>(array)[i];
+}
+
 // one element of an input tensor as fp32
 template <bool BF16> struct In;
 template <> struct In<true> {

@@ -670,3 +670,60 @@ def test_units_in_the_fp32_raw_row_kernel(cin, cout, h, w, k, stride, n, unit):
         n2 = oracle.sqnorm(mean_w[u]) + (oracle.sqnorm(mean_b[u]) if layer.pb else 0.0)
         assert np.isclose(float(sq[u]) / unit ** 2, n2, rtol=F32_TOL)
     assert np.allclose(host(norms), host(sq), rtol=F32_TOL)
+
+
+# The bf16 raw-row 3x3 kernel where a workgroup makes several rows of results one after the other: the last group of them short, tiles of few
+# channels, rows of 7 whose examples start between dwords (odd channels), one stage and several per example, pieces that an
+# example's end cuts.  Alone, from 1024 blocks on; every gradient is compared with a batch call of two layers, whose plan is another one.
+@pytest.mark.parametrize("cin,cout,h,w,stride,n", [(64, 64, 7, 7, 1, 1030), (65, 67, 7, 7, 1, 519), (64, 130, 9, 7, 1, 700), (72, 65, 14, 14, 1, 515),
+                                                   (64, 64, 13, 14, 1, 1027), (64, 64, 8, 8, 1, 1538), (64, 64, 10, 16, 1, 1025), (64, 64, 14, 14, 2, 1029),
+                                                   (128, 65, 28, 28, 2, 300), (64, 64, 5, 28, 1, 1026), (64, 65, 3, 56, 1, 600), (64, 64, 2, 32, 1, 1100)])
+def test_conv3x3_rows_of_results_in_a_row(cin, cout, h, w, stride, n):
+    layer = Layer("conv", cin, cout, h, w, 3, 3, stride, 1, False)
+    d = dp.make_desc(layer, n, "bf16")
+    assert dp.dp_kernel_variant(d, dp.DP_WS_PER_EXAMPLE_GRAD | dp.DP_VARIANT_MATERIALISE).startswith("conv3x3_rows")
+    gen = torch.Generator(device="cuda:0")
+    gen.manual_seed(331)
+    x = torch.randn((n,) + tuple(layer.x_shape), generator=gen, device="cuda:0").bfloat16()
+    dy = (torch.randn((n,) + tuple(layer.dy_shape), generator=gen, device="cuda:0") * 0.05).bfloat16()
+    f32 = dict(dtype=torch.float32, device="cuda:0")
+
+    def batch(count):
+        ws = [torch.empty(max(16, dp.dp_workspace_bytes(d, dp.DP_WS_PER_EXAMPLE_GRAD)), dtype=torch.uint8, device="cuda:0") for _ in range(count)]
+        g = [torch.full((n, (layer.pw + 3) & ~3), 7.0, **f32) for _ in range(count)]
+        sq = [torch.full((n,), -1.0, **f32) for _ in range(count)]
+        if count == 1:
+            dp.dp_per_example_grad(d, x, dy, g[0], None, sq[0], ws[0], g_stride=g[0].shape[1])
+        else:
+            bt = dp.LayerBatch([d] * count, [t.data_ptr() for t in ws], [t.numel() for t in ws])
+            dp.dp_per_example_grad_batch(bt, bt.ptrs([x.data_ptr()] * count), bt.ptrs([dy.data_ptr()] * count), bt.ptrs([t.data_ptr() for t in g]), None,
+                                         bt.ptrs([t.data_ptr() for t in sq]), g_stride=g[0].shape[1])
+        torch.cuda.synchronize()
+        return [t[:, :layer.pw] for t in g], sq
+
+    (g,), (sq,) = batch(1)
+    (a, b), (sa, sb) = batch(2)
+    assert torch.equal(a, b) and torch.equal(sa, sb)
+    # the two plans add the same products in other orders: sums of at most 784 terms, sqrt(784) 2^-24 = 1.7e-6 of their size
+    assert float((g - a).norm() / g.norm()) < 1e-5 and float((g - a).abs().max() / g.abs().max()) < 1e-5
+    assert torch.allclose(sq, sa, rtol=1e-5)
+    assert torch.allclose(sq, g.square().sum(1), rtol=1e-4)
+    for i in (0, 1, n // 2, n - 2, n - 1):
+        ref, _ = oracle.example_grad(layer, host(x[i]), host(dy[i]))
+        assert_close(host(g[i]), ref.reshape(-1), F32_TOL, f"example {i}")        # (bf16 products are exact in fp32)
+
+
+# The clip-weighted form where a range holds more examples than a wave has lanes for factors, and where it ends inside a range
+@pytest.mark.parametrize("cin,cout,h,w,n", [(320, 320, 7, 7, 1700), (64, 72, 14, 14, 131), (1024, 1024, 8, 8, 70), (65, 65, 7, 7, 67), (64, 64, 16, 28, 9)])
+def test_conv3x3_weighted_ranges(cin, cout, h, w, n):
+    layer = Layer("conv", cin, cout, h, w, 3, 3, 1, 1, False)
+    d = dp.make_desc(layer, n, "bf16")
+    assert dp.dp_kernel_variant(d, dp.DP_WS_RECOMPUTE).startswith("conv3x3_rows")
+    x, dy = _inputs(layer, n, 337, "bf16")
+    rng = np.random.default_rng(41)
+    n2 = (rng.uniform(0.3, 2.5, n) ** 2).astype(np.float32)
+    n2[0] = 0.0
+    got, _ = _run_weighted(layer, x, dy, "bf16", n2, 1.0)
+    f = np.array([oracle.clip_factor(float(v), 1.0) for v in n2])
+    idx = rng.choice(layer.pw, size=2000, replace=False)
+    assert_close(got[idx] - 1.0, oracle.weighted_sum_elems(layer, x, dy, f, idx), BF16_TOL, "increment")
