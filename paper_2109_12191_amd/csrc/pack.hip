@@ -115,6 +115,92 @@ __global__ void __launch_bounds__(256) pack_weighted_kernel(const Grouped<PackAr
     *reinterpret_cast<uint4 *>(a.dyp + qd * 8) = make_uint4(out[0], out[1], out[2], out[3]);
 }
 
+// X of layers with taps whose planes fit into LDS (small maps, which is what is packed): a workgroup takes some examples of some channels, whose planes
+// are contiguous in memory, into LDS once and writes their rows (all taps) from there, consecutive examples side by side.  The kernel above
+// reads a value once per tap, and neighbouring threads read different examples.  Us a launch, both
+// operands there / X here and dY there: ResNet-18-GN, 256 examples, 202 / 82 + 40; ResNet-50-GN at 200 x 200, 36 examples, 222 / 100 + 67; 64 examples of
+// ResNet-50 for finished blocks 155 / 60 + 82.  Twice the LDS and pieces per workgroup: ResNet-50, 32 examples on one stream, 2312 -> 2337 us a step of two
+// (a layer alone is too few workgroups).
+struct PackStaged {
+    const void *in;
+    uint16_t *out;
+    int tab, n, channels, h, w;     // Geo::x_tab; planes of an example
+    int taps, kw, stride, pad, ow;
+    int S, SP, eg, kg;              // positions, values of an example in a packed row, examples of a range, values of a packed row
+    int cb, eb;                     // channels and examples of a workgroup
+    unsigned c_blocks, e_blocks;    // workgroups of a range
+    unsigned by_ed, by_rp, by_p8, by_taps, by_kw, by_ow;             // divisors as factors (pack_div)
+};
+constexpr int PACK_LDS = 12 * 1024, PACK_PLANE = 32 * 1024, PACK_EB = 16;
+
+// x / d for x * d < 2^32; by = ceil(2^32 / d), 0 for d = 1
+__device__ __forceinline__ unsigned pack_div(unsigned x, unsigned by) { return by ? __umulhi(x, by) : x; }
+
+__global__ void __launch_bounds__(256) pack_staged_kernel(const Grouped<PackStaged> layers)
+{
+    extern __shared__ __attribute__((aligned(16))) uint32_t words[];
+    __shared__ unsigned odd[PACK_EB];
+    unsigned bid;
+    const PackStaged &a = layers.a[group_pick(layers, bid)];
+    const unsigned per_range = a.c_blocks * a.e_blocks, grp = bid / per_range, r = bid - grp * per_range;
+    const unsigned cblk = r / a.e_blocks, eblk = r - cblk * a.e_blocks;
+    const int e0 = (int)eblk * a.eb, ne = min(a.eb, a.eg - e0), i0 = (int)grp * a.eg + e0, c0 = (int)cblk * a.cb, nc = min(a.cb, a.channels - c0);
+    const int plane = a.h * a.w, count = nc * plane;
+    const unsigned ed = (unsigned)(a.cb * plane + 3) / 2;            // dwords of an example in LDS
+    const size_t ex_elems = (size_t)a.channels * plane;
+    const int there = min(ne, a.n - i0);                             // examples of this workgroup that there are (a last range may be short)
+    if (threadIdx.x < (unsigned)max(there, 0)) {
+        const int i = i0 + (int)threadIdx.x;
+        odd[threadIdx.x] = (unsigned)(reinterpret_cast<uintptr_t>(example_at<uint16_t>(a.in, a.tab, i, ex_elems) + (size_t)c0 * plane) >> 1) & 1u;
+    }
+    // whole dwords around an example's planes, a last half dword by itself (it may be the tensor's last value)
+    const unsigned total_in = there > 0 ? (unsigned)there * ed : 0u;
+    for (unsigned q0 = threadIdx.x; q0 < total_in; q0 += 1024) {
+        uint32_t v[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const unsigned q = q0 + 256u * k, e = pack_div(q, a.by_ed), d = q - e * ed;
+            v[k] = 0u;
+            if (q < total_in) {
+                const uintptr_t at = reinterpret_cast<uintptr_t>(example_at<uint16_t>(a.in, a.tab, i0 + (int)e, ex_elems) + (size_t)c0 * plane);
+                const int left = count - (int)(2 * d - ((at >> 1) & 1u));            // values from this dword's first half on
+                const uintptr_t word = (at & ~(uintptr_t)3) + 4ull * d;
+                if (left >= 2) v[k] = *reinterpret_cast<const uint32_t *>(word);
+                else if (left == 1) v[k] = *reinterpret_cast<const uint16_t *>(word);
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+            if (q0 + 256u * k < total_in) words[q0 + 256u * k] = v[k];
+    }
+    __syncthreads();
+    const uint16_t *halves = reinterpret_cast<const uint16_t *>(words);
+    const unsigned p8 = (unsigned)a.SP / 8, rp = (unsigned)a.eb * p8, total = (unsigned)(nc * a.taps) * rp;
+    for (unsigned p = threadIdx.x; p < total; p += 256) {
+        const unsigned row = pack_div(p, a.by_rp), q = p - row * rp, e = pack_div(q, a.by_p8), k8 = q - e * p8;
+        if ((int)e >= ne) continue;
+        const unsigned ci = pack_div(row, a.by_taps), t = row - ci * (unsigned)a.taps;
+        const int k0 = (int)k8 * 8;
+        uint32_t out[4] = {0u, 0u, 0u, 0u};
+        if ((int)e < there && k0 < a.S) {
+            const unsigned base = e * ed * 2 + odd[e] + ci * (unsigned)plane;
+            const int kh = (int)pack_div(t, a.by_kw), kw = (int)t - kh * a.kw;
+            const int oh = (int)pack_div((unsigned)k0, a.by_ow);
+            int ow = k0 - oh * a.ow, ih = oh * a.stride + kh - a.pad, iw = ow * a.stride + kw - a.pad;
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                uint32_t v = 0u;
+                if (k0 + u < a.S && (unsigned)ih < (unsigned)a.h && (unsigned)iw < (unsigned)a.w) v = halves[base + (unsigned)(ih * a.w + iw)];
+                out[u >> 1] |= v << ((u & 1) * 16);
+                iw += a.stride;
+                if (++ow == a.ow) { ow = 0; iw = kw - a.pad; ih += a.stride; }
+            }
+        }
+        const size_t at = ((size_t)grp * ((size_t)a.channels * a.taps) + (size_t)(c0 * a.taps) + row) * (size_t)a.kg + (size_t)(e0 + (int)e) * a.SP + k0;
+        *reinterpret_cast<uint4 *>(a.out + at) = make_uint4(out[0], out[1], out[2], out[3]);
+    }
+}
+
 // Rows of another length (launch_widen): what the raw-row, LDS-direct and stem kernels are not built for is brought to the next length
 // that they are, with zeros behind the values (zeros add nothing to a contraction).  Bound by memory: every value is read and written
 // once.  One thread per 16 bytes of output, from whole dwords where it lies in one row or its halves do; else value by value, and
@@ -350,6 +436,43 @@ PackPlan pack_plan(const Geo &g, int groups, int row)
     return p;
 }
 
+static unsigned pack_by(unsigned d) { return d > 1 ? (unsigned)(((1ull << 32) + d - 1) / d) : 0u; }
+
+// X through pack_staged_kernel, if a plane of it fits; `done` says whether.  (Operands without taps stay with the kernel above: staged, ResNet-50 at 32
+// examples was as fast alone and 2 % slower beside other kernels, which its LDS keeps off a compute unit.)
+static dp_status launch_pack_staged(const Geo &g, const PackPlan &p, const void *in, void *out, hipStream_t s, bool &done)
+{
+    const int channels = g.cin;
+    const int plane = g.h * g.w, taps = g.kh * g.kw, p8 = p.SP / 8;
+    done = plane * 2 <= PACK_PLANE;
+    if (!done) return DP_OK;
+    PackStaged a;
+    a.in = in; a.out = static_cast<uint16_t *>(out);
+    a.tab = g.x_tab; a.n = g.n; a.channels = channels; a.h = g.h; a.w = g.w;
+    a.taps = taps; a.kw = g.kw; a.stride = g.stride; a.pad = g.pad; a.ow = g.ow;
+    a.S = p.S; a.SP = p.SP; a.eg = p.eg; a.kg = p.kg;
+    // examples: runs of half a kilobyte in a row of the copy; channels: what LDS and about 2300 pieces have room for
+    int eb = 1;
+    while (eb < PACK_EB && eb * p.SP * 2 < 512 && (eb * 2) * plane * 2 <= PACK_LDS && eb < p.eg) eb *= 2;
+    int cb = PACK_LDS / (eb * plane * 2);
+    if (cb > 2304 / (taps * eb * p8)) cb = 2304 / (taps * eb * p8);
+    if (cb > channels) cb = channels;
+    if (cb < 1) cb = 1;
+    a.cb = cb; a.eb = eb;
+    a.c_blocks = (unsigned)((channels + cb - 1) / cb);
+    a.e_blocks = (unsigned)((p.eg + eb - 1) / eb);
+    const unsigned ed = (unsigned)(cb * plane + 3) / 2, rp = (unsigned)(eb * p8);
+    a.by_ed = pack_by(ed); a.by_rp = pack_by(rp); a.by_p8 = pack_by((unsigned)p8); a.by_taps = pack_by((unsigned)taps); a.by_kw = pack_by((unsigned)g.kw); a.by_ow = pack_by((unsigned)g.ow);
+    // (pack_div: what is divided is below 2^32 / the divisor)
+    const unsigned long long most = (unsigned long long)cb * taps * rp;
+    if ((unsigned long long)eb * ed * ed >= (1ull << 32) || most * rp >= (1ull << 32)) { done = false; return DP_OK; }
+    const unsigned long long blocks = (unsigned long long)p.groups * a.c_blocks * a.e_blocks;
+    if (blocks > 0x7FFFFFFFull) return fail(DP_ERR_UNSUPPORTED, "pack: layer too large");
+    // (layers share a launch if they ask for the same LDS; a piece is read from up to five dwords, which may lie behind the planes)
+    return submit_kernel<PackStaged>(TIER_PRE, reinterpret_cast<const void *>(&pack_staged_kernel), a, (unsigned)blocks, 256,
+                                     (plane * 2 <= PACK_LDS ? PACK_LDS : PACK_PLANE) + 256, s, "pack_staged");
+}
+
 dp_status launch_pack_weighted(const Geo &g, const PackPlan &p, const void *x, const void *dy,
                                const float *group_sqnorm, float clip_c, void *xp, void *dyp, hipStream_t s)
 {
@@ -363,6 +486,12 @@ dp_status launch_pack_weighted(const Geo &g, const PackPlan &p, const void *x, c
     a.S = p.S; a.SP = p.SP; a.J = p.J; a.groups = p.groups; a.eg = p.eg; a.kg8 = p.kg / 8;
     a.x_pieces = (long long)p.groups * p.J * a.kg8;
     a.dy_pieces = (long long)p.groups * g.cout * a.kg8;
+    if (g.kh * g.kw > 1) {
+        bool done;
+        const dp_status st = launch_pack_staged(g, p, x, xp, s, done);
+        if (st != DP_OK) return st;
+        if (done) a.x_pieces = 0;
+    }
     const long long blocks = (a.x_pieces + a.dy_pieces + 255) / 256;
     if (blocks > 0x7FFFFFFFll) return fail(DP_ERR_UNSUPPORTED, "pack: layer too large");
     return submit_kernel<PackArgs>(TIER_PRE, reinterpret_cast<const void *>(&pack_weighted_kernel), a, (unsigned)blocks,

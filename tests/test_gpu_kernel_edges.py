@@ -727,3 +727,33 @@ def test_conv3x3_weighted_ranges(cin, cout, h, w, n):
     f = np.array([oracle.clip_factor(float(v), 1.0) for v in n2])
     idx = rng.choice(layer.pw, size=2000, replace=False)
     assert_close(got[idx] - 1.0, oracle.weighted_sum_elems(layer, x, dy, f, idx), BF16_TOL, "increment")
+
+
+# Packed operands taken through LDS: planes of odd size and odd channel counts (examples that start between dwords), ranges of examples that are
+# no multiple of a workgroup's, channels that are none either, strides, taps with and without padding, a plane too large for it
+@pytest.mark.parametrize("layer,n", [(conv(33, 70, 1, 1, 5), 19), (conv(65, 64, 1, 2, 13), 7), (conv(67, 65, 3, 2, 14), 37), (conv(513, 64, 3, 1, 4), 21),
+                                     (conv(40, 33, 3, 1, 9), 5), (conv(64, 64, 3, 2, 8), 257), (Layer("conv", 12, 40, 11, 13, 5, 5, 2, 2, False), 6),
+                                     (Layer("conv", 3, 40, 130, 140, 3, 3, 4, 1, False), 3), (Layer("conv", 31, 64, 1, 7, 3, 3, 1, 1, False), 18)],
+                         ids=lambda v: str(v) if isinstance(v, int) else f"{v.cin}-{v.cout}-{v.kh}x{v.kw}s{v.stride}-{v.h}x{v.w}")
+@pytest.mark.parametrize("several", [False, True])
+def test_packed_operands(layer, n, several):
+    x, dy = _inputs(layer, n, 347, "bf16")
+    rng = np.random.default_rng(43)
+    n2 = (rng.uniform(0.3, 2.5, n) ** 2).astype(np.float32)
+    f = np.array([oracle.clip_factor(float(v), 1.0) for v in n2])
+    idx = rng.choice(layer.pw, size=min(layer.pw, 3000), replace=False)
+    ref = oracle.weighted_sum_elems(layer, x, dy, f, idx)
+    if not several:
+        got, _ = _run_weighted(layer, x, dy, "bf16", n2, 1.0)
+    else:
+        d = dp.make_desc(layer, n, "bf16")
+        ws = [torch.empty(max(16, dp.dp_workspace_bytes(d, dp.DP_WS_RECOMPUTE)), dtype=torch.uint8, device="cuda:0") for _ in range(2)]
+        acc = [torch.ones(layer.pw, device="cuda:0") for _ in range(2)]
+        xd, dyd, sq = dev(x, "bf16"), dev(dy, "bf16"), dev(n2)
+        bt = dp.LayerBatch([d, d], [t.data_ptr() for t in ws], [t.numel() for t in ws])
+        dp.dp_clip_accumulate_recompute_batch(bt, bt.ptrs([xd.data_ptr()] * 2), bt.ptrs([dyd.data_ptr()] * 2), bt.ptrs([sq.data_ptr()] * 2), bt.floats([1.0, 1.0]),
+                                              bt.ptrs([t.data_ptr() for t in acc]), bt.ptrs([None, None]))
+        torch.cuda.synchronize()
+        assert torch.equal(acc[0], acc[1])
+        got = host(acc[0])
+    assert_close(got[idx] - 1.0, ref, BF16_TOL, "increment")
