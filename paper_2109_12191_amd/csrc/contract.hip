@@ -1504,12 +1504,193 @@ __global__ void __launch_bounds__(512, 1) conv_panel_kernel(const Grouped<ConvAr
     }
 }
 
+// ---------------------------------------------------------------------------------------------
+// Clip-weighted and norm-only forms for the same short rows, inside batch calls.  A workgroup of eight waves owns 128 x 256 of the matrix and walks a
+// range of examples in stages of 128 whole rows: the example's dY rows, then its X rows in two halves.  Wave w keeps 32 dY rows (w & 3) in REGISTERS as
+// MFMA operands and multiplies them with its half (w >> 2) of the X rows: 32 x 64 values a stage, two chains of KS MFMAs.  NORM: their squares are summed
+// per example.  Else acc += f_i dW_i with f_i on the finished fp32 block of an example, as in conv_flat_kernel: nothing is rounded to 16 bits, so
+// this can stand in for stored gradients.
+// Stages are contiguous in memory and copied as they lie, a kilobyte a wave instruction, through a ring of three in LDS, two ahead of the one at hand, over the
+// examples' boundaries.  The load path takes 800 cycles for a stage, so its instructions are dealt out between LDS reads and
+// MFMAs, and the multiply-adds of finished blocks between the next ones' MFMAs: 128 -> 117 us.
+// Bound by one workgroup on a compute unit: 3300 of its 6900 cycles an example are MFMAs, the rest the step that reads dY's operands, waits and LDS reads
+// (8-byte halves).  The 13 layers of ResNet-50 on 14 x 14 maps, 32 examples, us: clip-weighted 119 in one range (104 workgroups; conv_flat_kernel 158), norm-only 62
+// (conv_panel_kernel 85).  With the gradients stored, those layers take conv_panel_kernel 150 and the clipped sum over them 86, both at the rate of
+// memory: step of 8 x 32 examples 6680 -> 6360 us where all but the last micro-step do without.
+constexpr int PANELW_THREADS = 512, PANELW_M = 128, PANELW_N = 256;
+
+template <int KS, bool NORM>
+__global__ void __launch_bounds__(PANELW_THREADS, 1) conv_row_stages_kernel(const Grouped<ConvArgs> grp)
+{
+    constexpr int U = (KS * 16 / 4 + 7) / 8;              // wave instructions of a stage per wave, at most
+    extern __shared__ __attribute__((aligned(16))) char lds[];
+    unsigned bid;
+    const ConvArgs &a = grp.a[group_pick_runs(grp, bid)];
+    const int tiles = a.tiles_m * a.tiles_n, wg = (int)bid;
+    if (wg >= tiles * a.ksplit) return;
+    const int range = wg / tiles, tile = wg - range * tiles;
+    const int tile_m = tile / a.tiles_n, tile_n = tile - tile_m * a.tiles_n;
+    const int m0 = __builtin_amdgcn_readfirstlane(tile_m * PANELW_M), j0 = __builtin_amdgcn_readfirstlane(tile_n * PANELW_N);
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int half = lane >> 5, cb = wave & 3, hx = wave >> 2;
+    const int S = __builtin_amdgcn_readfirstlane(a.S), cout = __builtin_amdgcn_readfirstlane(a.cout), J = __builtin_amdgcn_readfirstlane(a.J);
+    const int i_begin = __builtin_amdgcn_readfirstlane(range * a.ex_per_split), i_end = __builtin_amdgcn_readfirstlane(min(a.n, i_begin + a.ex_per_split));
+    const unsigned long long x_ptr = uniform_bits(a.x), dy_ptr = uniform_bits(a.dy);
+    const int x_tab = __builtin_amdgcn_readfirstlane(a.x_tab), dy_tab = __builtin_amdgcn_readfirstlane(a.dy_tab);
+    const size_t x_ex = (size_t)J * S, dy_ex = (size_t)cout * S;
+    // (by scalar loads: a wait for a vector load would wait for everything that is on its way to LDS)
+    auto x_at = [&](int i) { return (x_tab ? scalar_load<unsigned long long>(x_ptr, (size_t)i * x_tab) : x_ptr + 2 * x_ex * (unsigned)i) + 2ull * (unsigned)j0 * (unsigned)S; };
+    auto dy_at = [&](int i) { return (dy_tab ? scalar_load<unsigned long long>(dy_ptr, (size_t)i * dy_tab) : dy_ptr + 2 * dy_ex * (unsigned)i) + 2ull * (unsigned)m0 * (unsigned)S; };
+
+    const unsigned pitch = 2u * (unsigned)S, stage = 128u * pitch;            // a stage as it lies in memory: S / 4 kilobytes
+    const int Q = S / 4;
+    const unsigned lds0 = __builtin_amdgcn_readfirstlane((unsigned)(size_t)lds);
+    int f_i = i_begin, f_p = 0;                       // the stage to fetch: dY of an example, X's first half, its second
+    unsigned f_dst = lds0;
+    unsigned long long f_x = x_at(f_i), f_dy = dy_at(f_i);
+    auto fetch = [&](int u) {                         // (past the end the last stage again, into a slot that nobody reads)
+        const unsigned long long src = (f_p == 0 ? f_dy : f_x + (f_p == 2 ? stage : 0u)) + (unsigned)wave * 1024u;
+        if (u < U - 1 || wave + 8 * u < Q) lds_direct_16(src + u * 8192u, (unsigned)lane * 16u, f_dst + (unsigned)(wave + 8 * u) * 1024u);
+    };
+    auto fetched = [&]() {
+        f_dst = f_dst == lds0 + 2 * stage ? lds0 : f_dst + stage;
+        if (++f_p == 3) {
+            if (f_i + 1 < i_end) { f_p = 0; ++f_i; f_x = x_at(f_i); f_dy = dy_at(f_i); }
+            else f_p = 2;
+        }
+    };
+    const bool more = wave + 8 * (U - 1) < Q;         // this wave issues U instructions a stage, the others U - 1
+    const char *slot = lds;
+    auto begin = [&]() {                              // the next stage: its rows are there, the one before has been read
+        if (more) wait_vmcnt<U>(); else wait_vmcnt<U - 1>();
+        __syncthreads();
+    };
+    auto leave = [&]() { slot = slot == lds + 2 * stage ? lds : slot + stage; };
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) fetch(u);
+        fetched();
+    }
+
+    const float *const group_sqnorm = a.group_sqnorm;
+    const float clip_c = a.clip_c;
+    float factors = 1.0f;                             // of 64 examples, one a lane
+    int factors_at = i_begin - 64;
+    uint32_t kmask[4];                                // last K step: what lies behind the row
+#pragma unroll
+    for (int d = 0; d < 4; ++d) {
+        const int e0 = (KS - 1) * 16 + half * 8 + 2 * d;
+        kmask[d] = (e0 < S ? 0x0000FFFFu : 0u) | (e0 + 1 < S ? 0xFFFF0000u : 0u);
+    }
+    const unsigned frag = (unsigned)(lane & 31) * pitch + (unsigned)half * 16u;
+    auto masked = [&](uint4 v, int ks) {
+        if (ks == KS - 1) { v.x &= kmask[0]; v.y &= kmask[1]; v.z &= kmask[2]; v.w &= kmask[3]; }
+        return v;
+    };
+    f32x16 tot[NORM ? 1 : 4];
+    float ss[4], sums = 0.0f;                         // norms: squares of the example at hand; examples' sums, one a lane (at most 64)
+#pragma unroll
+    for (int t = 0; t < (NORM ? 0 : 4); ++t)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) tot[t][r] = 0.0f;
+    const f32x16 zero = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
+    // The loads of the stage after next are dealt out between a stage's LDS reads and MFMAs (50 kilobytes take the load path 800 cycles), and so are the
+    // multiply-adds of the blocks before.
+    f32x16 done[2] = {zero, zero};                    // finished blocks that are not added yet, and their factor
+    float done_f = 0.0f;
+    for (int i = i_begin; i < i_end; ++i) {
+        begin();
+        uint4 dy[KS];
+        static_for<KS>([&](auto kk) {
+            constexpr int ks = decltype(kk)::value;
+            dy[ks] = masked(lds_read16_halves(slot + (unsigned)(cb * 32) * pitch + frag + ks * 32), ks);
+            if constexpr (ks % 2 == 0) fetch(ks / 2);
+        });
+        fetched();
+        leave();
+        if (!NORM && i - factors_at >= 64) {
+            factors_at = i;
+            if (group_sqnorm) factors = clip_factor(group_sqnorm[min(i + lane, i_end - 1)], clip_c);
+        }
+        const float f = NORM ? 1.0f : __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, factors), i - factors_at));
+        ss[0] = ss[1] = ss[2] = ss[3] = 0.0f;
+        static_for<2>([&](auto hh) {
+            constexpr int h = decltype(hh)::value, before = 2 - 2 * h;        // running sums that the blocks before belong to
+            begin();
+            const char *b0 = slot + (unsigned)(hx * 64) * pitch + frag, *b1 = b0 + 32 * pitch;
+            f32x16 acc[2];
+            static_for<KS>([&](auto kk) {
+                constexpr int ks = decltype(kk)::value;
+                const uint4 v0 = masked(lds_read16_halves(b0 + ks * 32), ks), v1 = masked(lds_read16_halves(b1 + ks * 32), ks);
+                acc[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, dy[ks]), __builtin_bit_cast(bf16x8, v0), ks == 0 ? zero : acc[0], 0, 0, 0);
+                acc[1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, dy[ks]), __builtin_bit_cast(bf16x8, v1), ks == 0 ? zero : acc[1], 0, 0, 0);
+                if constexpr (ks % 2 == 0) fetch(ks / 2);
+                static_for<3>([&](auto qq) {
+                    constexpr int q = 3 * ks + decltype(qq)::value;
+                    if constexpr (!NORM && q < 32) tot[before + q / 16][q % 16] += done_f * done[q / 16][q % 16];
+                });
+            });
+            fetched();
+            leave();
+            if constexpr (NORM) {
+#pragma unroll
+                for (int q = 0; q < 32; ++q) ss[q & 3] += acc[q / 16][q % 16] * acc[q / 16][q % 16];
+                return;
+            }
+            done[0] = acc[0];
+            done[1] = acc[1];
+            if (f == 0.0f) done[0] = done[1] = zero;  // (an example whose gradient is not finite adds nothing, and no 0 * inf)
+            done_f = f;
+        });
+        if constexpr (NORM) {
+            const float all = wave_sum_last_lane((ss[0] + ss[1]) + (ss[2] + ss[3]));
+            const float last = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, all), 63));     // (with every lane taking part)
+            sums = lane == i - i_begin ? last : sums;
+        }
+    }
+    if constexpr (NORM) {
+        wait_vmcnt<0>();                              // (the stages that were fetched again)
+        if (lane < i_end - i_begin) a.partials[((size_t)(i_begin + lane) * tiles + tile) * 8 + wave] = sums;
+        return;
+    }
+#pragma unroll
+    for (int q = 0; q < (NORM ? 0 : 32); ++q) tot[2 + q / 16][q % 16] += done_f * done[q / 16][q % 16];
+    wait_vmcnt<0>();                                  // (the stages that were fetched again)
+    if constexpr (NORM) return;
+    float *const out = (a.ksplit > 1 ? a.ws_part + (size_t)range * cout * J : a.out_w) + (size_t)(m0 + cb * 32 + half * 4) * J + j0 + (lane & 31);
+#pragma unroll
+    for (int t = 0; t < (NORM ? 0 : 4); ++t)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            float *p = out + (size_t)((r >> 2) * 8 + (r & 3)) * J + (t >> 1) * 128 + hx * 64 + (t & 1) * 32;
+            *p = a.ksplit > 1 ? tot[t][r] : *p + tot[t][r];
+        }
+}
+
+// The ranges' sums are added to the accumulator, in order.  Four values a thread.
+__global__ void __launch_bounds__(256) conv_panel_sum_kernel(const Grouped<ConvArgs> grp)
+{
+    unsigned bid;
+    const ConvArgs &a = grp.a[group_pick(grp, bid)];
+    const size_t at = ((size_t)bid * 256 + threadIdx.x) * 4, all = (size_t)a.cout * a.J;
+    if (at >= all) return;
+    float4 v = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    for (int s = 0; s < a.ksplit; ++s) {
+        const float4 w = *reinterpret_cast<const float4 *>(a.ws_part + (size_t)s * all + at);
+        v.x += w.x; v.y += w.y; v.z += w.z; v.w += w.w;
+    }
+    float4 *out = reinterpret_cast<float4 *>(a.out_w + at);
+    const float4 o = *out;
+    *out = make_float4(o.x + v.x, o.y + v.y, o.z + v.z, o.w + v.w);
+}
+
 // ------------------------------------------------------------------------------------ host
 
-enum TileShape { T64 = 0, T128 = 1, T256x128 = 2, T256rows = 3 };
-static const int kTileM[4] = {64, 128, 256, 256};
-static const int kTileN[4] = {64, 128, 128, 256};
-static const char *kTileName[4] = {"64x64", "128x128", "256x128", "256x256rows"};
+enum TileShape { T64 = 0, T128 = 1, T256x128 = 2, T256rows = 3, T128rows = 4, T_COUNT = 5 };
+static const int kTileM[T_COUNT] = {64, 128, 256, 256, PANELW_M};
+static const int kTileN[T_COUNT] = {64, 128, 128, 256, PANELW_N};
+static const char *kTileName[T_COUNT] = {"64x64", "128x128", "256x128", "256x256rows", "128x256rows"};
 constexpr int PANEL_KS = 13;                 // K steps the row-panel kernel is built for: 192 < S <= 208
 
 struct FullPlan {
@@ -1567,6 +1748,9 @@ static FullPlan full_plan(const Geo &g, int mode)
     const bool panel = mode != MODE_WEIGHTED && g.unit == 1 && flat_direct(g) && S % 8 == 4 && S > 16 * (PANEL_KS - 1) && S <= 16 * PANEL_KS &&
                        g.cout % 256 == 0 && J % 256 == 0 && (long long)g.n * (g.cout / 256) * (J / 256) >= 128;
     if (panel) p.shape = T256rows;
+    // and their clip-weighted and norm-only forms in batch calls (conv_row_stages_kernel)
+    if ((mode == MODE_WEIGHTED || (panel && mode == MODE_NORM)) && crowd && flat_direct(g) && S % 8 == 4 && S > 16 * (PANEL_KS - 1) && S <= 16 * PANEL_KS && g.cout % PANELW_M == 0 && J % PANELW_N == 0)
+        p.shape = T128rows;
     p.tiles_m = (g.cout + kTileM[p.shape] - 1) / kTileM[p.shape];
     p.tiles_n = (J + kTileN[p.shape] - 1) / kTileN[p.shape];
     const int tiles = p.tiles_m * p.tiles_n;
@@ -1575,6 +1759,22 @@ static FullPlan full_plan(const Geo &g, int mode)
     const size_t tile_floats = (size_t)p.nacc * 16 * THREADS;
 
     p.ksplit = 1; p.chunks_per_split = p.chunks_per_ex; p.ex_per_split = g.n; p.ex_per_wg = g.unit; p.slice_ex = 0;
+    if (p.shape == T128rows && mode == MODE_NORM) {
+        p.ex_per_wg = g.n < 8 ? g.n : 8;                 // (the filling of the ring and the last examples' tail)
+        p.groups = tiles;
+        p.part_floats = 0;
+        return p;
+    }
+    if (p.shape == T128rows) {
+        // ranges of up to 16 examples: us a step of ResNet-50, ranges of 32 / 16: 8 x 32 6400 / 6360 on eight streams, 32 x 1 1160 / 1111 on four,
+        // 16 x 2 on one 1425 / 1373
+        p.ksplit = (g.n + 15) / 16;
+        p.ex_per_split = (g.n + p.ksplit - 1) / p.ksplit;
+        p.ksplit = (g.n + p.ex_per_split - 1) / p.ex_per_split;
+        p.groups = tiles;
+        p.part_floats = p.ksplit > 1 ? (size_t)p.ksplit * g.cout * J : 0;
+        return p;
+    }
     if (mode == MODE_WEIGHTED) {
         // example ranges: enough workgroups to fill the chip, with the partial tiles that are
         // written and read back (cache-resident in practice) kept below ~100 MB
@@ -1791,7 +1991,7 @@ static size_t align16(size_t b) { return (b + 15) & ~(size_t)15; }
 static size_t norm_partials_per_example(const FullPlan &f)
 {
     const size_t tiles = (size_t)f.tiles_m * f.tiles_n;
-    return f.ksplit > 1 ? tiles * f.nacc * FIX_PARTS : tiles * ((f.shape == T256x128 || f.shape == T256rows) ? 8 : 4);     // unsliced: a slot per wave
+    return f.ksplit > 1 ? tiles * f.nacc * FIX_PARTS : tiles * ((f.shape == T256x128 || f.shape == T256rows || f.shape == T128rows) ? 8 : 4);     // unsliced: a slot per wave
 }
 static size_t norm_partials(const Geo &g, const FullPlan &f) { return (size_t)(g.n / g.unit) * norm_partials_per_example(f); }
 
@@ -1874,12 +2074,12 @@ const char *conv_variant_name(const Geo &g, int mode, bool shared)
     Geo wide;
     if (widened(g, mode, wide)) return conv_variant_name(wide, mode, shared);
     struct Names {
-        char v[2][4][2][2][3][72];
+        char v[2][T_COUNT][2][2][3][72];
         Names()
         {
             static const char *const ld[3] = {"", ",gather", ",gather2"};
             for (int b = 0; b < 2; ++b)
-                for (int s = 0; s < 4; ++s)
+                for (int s = 0; s < T_COUNT; ++s)
                     for (int w = 0; w < 2; ++w)
                         for (int bi = 0; bi < 2; ++bi)
                             for (int l = 0; l < 3; ++l)
@@ -1896,7 +2096,9 @@ const char *conv_variant_name(const Geo &g, int mode, bool shared)
         if (gram_norm_applicable(g2, mode)) return "conv_gram_norm<bf16,sampled>";      // (a launch of its own: the others need not wait for the copy)
         ge = g2;
     }
-    const FullPlan f = full_plan(ge, mode);
+    FullPlan f = full_plan(ge, mode);
+    // (whole-row layers have one name, stored or not: calls group layers by it, and the library launches what stores and what does not apart)
+    if (f.shape == T128rows && mode != MODE_WEIGHTED) f.shape = T256rows;
     return names.v[g.bf16 ? 1 : 0][f.shape][mode == MODE_WEIGHTED ? 1 : 0][g.has_bias ? 1 : 0][loader_of(ge)];
 }
 
@@ -2036,7 +2238,10 @@ static dp_status launch_conv_impl(const Geo &g, int mode, const void *x, const v
         // aligned one-row-per-channel geometry: operands go global -> LDS directly.  Two workgroups per compute unit
         // (64 KB of LDS each): 64x64 tiles four stages deep, 128x128 tiles two stages deep (measured: a second
         // resident workgroup hides more than two more stages do).
-        if (f.shape == T256rows) {                         // per-example form only (full_plan)
+        if (f.shape == T128rows) {                         // clip-weighted and norm-only forms (full_plan)
+            fn = weighted ? reinterpret_cast<const void *>(&conv_row_stages_kernel<PANEL_KS, false>) : reinterpret_cast<const void *>(&conv_row_stages_kernel<PANEL_KS, true>);
+            lds_bytes = 3 * 128 * 2 * 16 * PANEL_KS + 64;          // (what lies behind a last row is read and cleared)
+        } else if (f.shape == T256rows) {                  // per-example form only (full_plan)
             fn = reinterpret_cast<const void *>(&conv_panel_kernel<PANEL_KS>);
             lds_bytes = (unsigned)PANEL_RING * (64u * (unsigned)a.S + 64u) + 8u * 64u;      // ring + each wave's marks
         } else if (f.shape == T256x128) {                  // per-example form only (full_plan)
@@ -2049,7 +2254,7 @@ static dp_status launch_conv_impl(const Geo &g, int mode, const void *x, const v
             fn = weighted ? reinterpret_cast<const void *>(&conv_flat_kernel<2, 2, 2, true, 2>) : reinterpret_cast<const void *>(&conv_flat_kernel<2, 2, 2, false, 2>);
             lds_bytes = 2 * 256 * 128;
         }
-        static std::atomic<bool> attr_done[4][2];        // zero-initialised; setting the attribute twice is harmless
+        static std::atomic<bool> attr_done[T_COUNT][2];        // zero-initialised; setting the attribute twice is harmless
         if (!attr_done[f.shape][weighted ? 1 : 0].load()) {
             // the row-panel kernel's ring grows with S: reserve for the longest row it takes
             const unsigned reserve = f.shape == T256rows ? (unsigned)PANEL_RING * (64u * 16u * PANEL_KS + 64u) + 8u * 64u : lds_bytes;
@@ -2059,6 +2264,22 @@ static dp_status launch_conv_impl(const Geo &g, int mode, const void *x, const v
         }
     } else if (g.bf16) fn = (f.shape == T64) ? kernel_of<true, 2, 2, 1, 1>(loader, weighted, bias, at) : kernel_of<true, 2, 2, 2, 2>(loader, weighted, bias, at);
     else fn = (f.shape == T64) ? kernel_of<false, 2, 2, 1, 1>(loader, weighted, bias, at) : kernel_of<false, 2, 2, 2, 2>(loader, weighted, bias, at);
+    if (f.shape == T128rows) {
+        if (!weighted) {                                   // (the kernel knows ranges of examples)
+            a.ex_per_split = f.ex_per_wg;
+            a.ksplit = (g.n + f.ex_per_wg - 1) / f.ex_per_wg;
+        }
+        dp_status st = submit_main<ConvArgs>(fn, a, blocks, PANELW_THREADS, lds_bytes, s, "conv_row_stages");
+        if (st != DP_OK || (weighted && f.ksplit == 1)) return st;
+        if (!weighted) {
+            if (!sqnorm) return DP_OK;
+            const int n = g.n, per_example = (int)norm_partials_per_example(f);
+            const float *partials = a.partials;
+            return submit_post([=]() -> dp_status { return launch_sum_partials(partials, n, per_example, sqnorm, s); });
+        }
+        return submit_kernel<ConvArgs>(TIER_POST, reinterpret_cast<const void *>(&conv_panel_sum_kernel), a, (unsigned)(((size_t)a.cout * a.J + 1023) / 1024), 256, 0, s,
+                                       "conv_panel_sum");
+    }
     dp_status st = submit_main<ConvArgs>(fn, a, blocks, (f.shape == T256x128 || f.shape == T256rows) ? 512 : THREADS, lds_bytes, s, "conv_contract");
     if (st != DP_OK) return st;
     // what follows the main kernel: at once, or after the grouped launches of a batch call

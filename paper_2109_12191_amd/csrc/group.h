@@ -51,6 +51,20 @@ __device__ __forceinline__ int group_pick(const Grouped<Args> &g, unsigned &bid)
     bid = blockIdx.x - g.first_block[l];
     return l;
 }
+
+// The same with the workgroups of the whole launch dealt to the XCDs in runs: consecutive ones, so also those of a layer, share an L2 (`bid` needs no further
+// mapping).  For the clip-weighted forms, whose workgroups of a layer walk through the same examples side by side.
+template <typename Args>
+__device__ __forceinline__ int group_pick_runs(const Grouped<Args> &g, unsigned &bid)
+{
+    const unsigned b = (blockIdx.x & 7u) * (g.first_block[GROUP_MAX] >> 3) + (blockIdx.x >> 3);
+    int l = 0;
+#pragma unroll
+    for (int k = 1; k < GROUP_MAX; ++k)
+        if (k < g.count && b >= g.first_block[k]) l = k;
+    bid = b - g.first_block[l];
+    return l;
+}
 #endif
 
 enum { TIER_LAYOUT = 0, TIER_ROWS = 1, TIER_PRE = 2, TIER_MAIN = 3, TIER_POST = 4, TIER_COUNT = 5 };

@@ -38,6 +38,10 @@ PHASE_EXAMPLES = 256
 #   and of micro-steps of one or two examples.  ResNet-50, 64 x 1: one by one / 16 / 32 / 64 9682 / 2774 / 2476 / 2481; 32 x 2: 7984 /
 #   2821 (16) / 2502 / 2498
 PHASE_EXAMPLES_OF_SMALL = 64
+# From how many examples on the layers whose clipped sum the whole-row kernel makes (from finished fp32 blocks) need no stored gradients: it runs
+# two ranges of examples then.  ResNet-50 in phases of one-example micro-steps on four streams, stored / this: 16 708 / 720, 24 (of two, one stream) 1173 / 1157,
+# 32 1150 / 1111, 64 2140 / 2050.
+ROWS_EXAMPLES = 17
 # And no phase is so large that a layer falls back to the kernel that gathers its operands element by element, because the rewritten
 # operands of a faster one outgrow their share of the workspace: ResNet-18-GN at 40 x 40, 64 examples 3656 / 5083 (two micro-steps) / 7188
 # (four), 24 (8 micro-steps): 3097 / 3028 (four) / 3825 (eight).
@@ -79,17 +83,17 @@ class _Plan:
     micro-steps through arrays of example addresses.  `only`: per-example calls of these layers and nothing else.  (Keeps no reference to its
     PrivatiseStep: the buffers go when that goes.)"""
 
-    def __init__(self, ps: "PrivatiseStep", tensors: int, stores: List[_Store], only: Optional[Sequence[int]] = None):
+    def __init__(self, ps: "PrivatiseStep", tensors: int, stores: List[_Store], only: Optional[Sequence[int]] = None, more: bool = False):
         wl = ps.wl
         self.tensors = tensors
         self.stores = stores                       # the copies that are large enough
         self.n = wl.n * tensors
         self.rows = self.n // ps.clip_unit
         self.layers = ps.layers
-        self.form = ps._forms(tensors)
+        self.form = ps._forms(tensors, more)
         self.blocks = ps._blocks(tensors)
         L = len(self.layers)
-        self.descs, need = ps._workspaces(tensors)
+        self.descs, need = ps._workspaces(tensors, more)
         self.g = [st.g[: self.rows] if st.g is not None else None for st in stores]
         self.off_w, self.off_b, self.p_mat = ps.off_w, ps.off_b, ps.p_mat
         free = [None] * len(stores)
@@ -107,7 +111,7 @@ class _Plan:
         self.ws = []
         for st, spare in zip(stores, free):
             at, spare, where = st.ws.data_ptr(), spare and _align256(spare), []
-            for b, inside in zip(need, ps._in_matrix(tensors)):
+            for b, inside in zip(need, ps._in_matrix(tensors) if self.blocks else [False] * L):
                 where.append(spare if inside else at)
                 if inside:
                     spare += _align256(b)
@@ -122,7 +126,7 @@ class _Plan:
                         for d, form in zip(self.descs, self.form)]
         self.partials = [B.PartialTable(self.ws[c], [1] * L, ps.group_of_layer)
                          for c in range(len(stores))]
-        self.work = ps._work(tensors)
+        self.work = ps._work(tensors, more)
         self.groups_a = self._make_groups(ps, range(L) if only is None else only, 0) if ps.clip_unit == 1 else []
         self.groups_b = self._make_groups(ps, [i for i in range(L) if self.form[i] == "recompute"], 1) if only is None else []
         self.groups_u = self._make_groups(ps, range(L), 2) if ps.clip_unit > 1 else []
@@ -142,6 +146,9 @@ class _Plan:
                 # four kernels run at a time on the chip: the few workgroups of a narrow layer cost none of the
                 # four inside a wide launch), so the family is one batch call
                 key = family
+            elif "256x256rows" in key:
+                # what stores and what does not are launches of their own, which run side by side on streams of their own
+                key += "|" + self.form[li]
             by_name.setdefault(key, []).append(li)
         groups = []
         for key, ids in by_name.items():
@@ -295,6 +302,7 @@ class PrivatiseStep:
         self._last_store = None                  # gradients of a last micro-step that its phase does not store (_last_plan)
         self._last_plans = {}
         self._phase_forms = {}                   # micro-steps of a phase -> forms of the layers
+        self._lean_forms = {}                    # and of one that others follow
         self._inside = {}                        # and whose workspaces lie in the gradient matrix
         self._ws_bytes = {}                      # and how much the others take together
         self._needs = {}                         # micro-steps of a phase -> descriptors and workspace sizes
@@ -336,7 +344,7 @@ class PrivatiseStep:
         # library to bracket the next contraction kernel with a pair of events
         self.probe = None
 
-    def _work(self, tensors: int):
+    def _work(self, tensors: int, more: bool = False):
         """Algorithmic work of one call per layer: (flop, HBM bytes of the per-example call, HBM bytes of the
         recomputing clipped-sum call).  Bytes = the operands read once, plus the per-example gradients
         written when the layer materialises them, or the accumulator read and written by the recomputing form."""
@@ -344,9 +352,9 @@ class PrivatiseStep:
         return [(l.flops * n,
                  l.in_bytes(esize) * n + (4 * n * (pw + pb) if form == "materialise" else 0),
                  l.in_bytes(esize) * n + 8 * (pw + pb))
-                for l, pw, pb, form in zip(self.layers, self.pw, self.pb, self._forms(tensors))]
+                for l, pw, pb, form in zip(self.layers, self.pw, self.pb, self._forms(tensors, more))]
 
-    def _forms(self, tensors: int) -> List[str]:
+    def _forms(self, tensors: int, more: bool = False) -> List[str]:
         """Form of every layer's clipped sum in a phase of `tensors` micro-steps: that of a micro-step, except that a phase of many
         one- or two-example micro-steps (which store every gradient) recomputes what a micro-step of that many examples would, where
         finished fp32 blocks are squared and scaled (how many micro-steps share a phase must not decide about precision) and the workspaces
@@ -354,6 +362,19 @@ class PrivatiseStep:
         gradient stored / this: 3 x 1 364 / 362, 4 x 1 425 / 395, 8 x 1 693 / 548, 64 x 1 4099 / 2467; 3 x 2 at 192 x 192 574 / 491.  Not two
         micro-steps, half of which _last_plan stores all the same: 2 x 2 on one stream 544 / 555, at 192 x 192 532 / 559."""
         n = self.wl.n * tensors
+        more = more and self.wl.accum > 1            # (workspaces have room for it)
+        if more and tensors not in self._lean_forms:
+            # A phase that others follow keeps no gradients of the layers whose clipped sum the whole-row kernel makes from finished fp32 blocks (the
+            # same precision): 8 bytes per value and example less through memory.  ResNet-50, us a step on eight streams, every phase stores / this:
+            # 8 x 32 6680 / 6360, 2 x 48 2700 / 2660; with GroupNorm 2 x 24 1940 / 1905; 8 x 24 on one stream 5960 / 5840.  The last one stores: `g` is whole
+            # after a step.
+            form = self._forms(tensors)
+            rows = [] if n < ROWS_EXAMPLES or self._mode != "auto" or self.clip_unit > 1 or form is not self.form or any(p % 4 for p in self.pw + self.pb) else [
+                i for i, l in enumerate(self.layers) if form[i] == "materialise" and l.kind == "conv" and "128x256rows" in B.dp_kernel_variant(
+                    B.make_desc(l, n, self.wl.dtype), B.DP_WS_RECOMPUTE | B.DP_VARIANT_SHARED)]
+            self._lean_forms[tensors] = ["recompute" if i in rows else f for i, f in enumerate(form)] if rows else form
+        if more:
+            return self._lean_forms[tensors]
         if (tensors < 3 or self._mode != "auto" or self.wl.n > 2 or self.clip_unit > 1 or
                 any(p % 4 for p in self.pw + self.pb)):         # (zeros between tensors have a place of their own in the matrix)
             return self.form
@@ -362,7 +383,8 @@ class PrivatiseStep:
             over = {}                            # layer -> workspace less its part of the matrix
             for i, l in enumerate(self.layers):
                 d = B.make_desc(l, n, self.wl.dtype)
-                if self._choose(l, "auto", n) == "recompute" and B.dp_kernel_variant(d, sums):
+                variant = B.dp_kernel_variant(d, sums | B.DP_VARIANT_SHARED)
+                if variant and ((n >= ROWS_EXAMPLES and "128x256rows" in variant) or self._choose(l, "auto", n) == "recompute"):
                     need = max(B.dp_batch_workspace_bytes(d, norms), B.dp_workspace_bytes(d, sums), 16)
                     over[i] = _align256(need) - 4 * n * (self.pw[i] + self.pb[i])
             while over and sum(over.values()) + 256 > 0:
@@ -402,15 +424,15 @@ class PrivatiseStep:
         groups = [self.group_of_layer[i] for i in runs]
         return B.SegmentTable([off_w[i] for i in runs], groups, [self.group_clip[k] for k in groups], [self.off_w[i] for i in runs])
 
-    def _workspaces(self, tensors: int):
-        """Descriptors and workspace bytes of every layer in a phase of `tensors` micro-steps."""
+    def _workspaces(self, tensors: int, more: bool = False):
+        """Descriptors and workspace bytes of every layer in a phase of `tensors` micro-steps (the same whether others follow)."""
         if tensors not in self._needs:
             descs = [B.make_desc(l, self.wl.n * tensors, self.wl.dtype) for l in self.layers]
             blocks = self._blocks(tensors)
             need = [max(16, B.dp_batch_workspace_bytes(d, B.DP_WS_PER_EXAMPLE_GRAD | blocks),
                         B.dp_workspace_bytes(d, B.DP_WS_RECOMPUTE | blocks) if form == "recompute" else 0,
                         B.dp_batch_workspace_bytes(d, B.DP_WS_PER_EXAMPLE_GRAD, self.clip_unit) if self.clip_unit > 1 else 0)
-                    for d, form in zip(descs, self._forms(tensors))]
+                    for d, form in zip(descs, self._forms(tensors, True))]
             self._needs[tensors] = descs, need
         return self._needs[tensors]
 
@@ -463,8 +485,10 @@ class PrivatiseStep:
                 return sizes
             phases += 1
 
-    def _plan(self, tensors: int) -> _Plan:
-        if tensors not in self._plans:
+    def _plan(self, tensors: int, more: bool = False) -> _Plan:
+        """Of phases of `tensors` micro-steps; more: of those that others of their step follow."""
+        key = (tensors, more and self._forms(tensors, True) is not self._forms(tensors))
+        if key not in self._plans:
             stores = []
             for c, room in enumerate(self._room):
                 if tensors <= room:
@@ -472,8 +496,8 @@ class PrivatiseStep:
                         ws = self._workspace_bytes(1) if room == 1 else self._ws_room
                         self._stores[c] = _Store(self, room * self.rows, ws)
                     stores.append(self._stores[c])
-            self._plans[tensors] = _Plan(self, tensors, stores)
-        return self._plans[tensors]
+            self._plans[key] = _Plan(self, tensors, stores, None, key[1])
+        return self._plans[key]
 
     def _last_plan(self, form: Sequence[str]) -> _Plan:
         """Stores the gradients of one micro-step's layers that a phase of this form recomputes: whoever looks at `g` after a step finds the last
@@ -609,8 +633,11 @@ class PrivatiseStep:
         accumulator in the same order on every run: each tensor is updated by one call per
         phase, issued on the same stream by every phase of one plan and behind all clipped sums of the phase before where the
         plan changes."""
+        self._micro_step(inputs, False)
+
+    def _micro_step(self, inputs: Sequence, more: bool):
         layers = range(len(self.layers))
-        self._issue(self._plan(1), [inputs[i][0].data_ptr() for i in layers], [inputs[i][1].data_ptr() for i in layers])
+        self._issue(self._plan(1, more), [inputs[i][0].data_ptr() for i in layers], [inputs[i][1].data_ptr() for i in layers], ends_step=not more)
 
     def _issue(self, plan: _Plan, x: Sequence[int], dy: Sequence[int], ends_step: bool = True):
         """The two phases of plan.tensors micro-steps; x, dy: per layer the address of the tensor, or of its array of example
@@ -769,19 +796,20 @@ class PrivatiseStep:
         """Every micro-step of a step, several at a time where they are small (`table`: addresses already written)."""
         sizes = self._phase_sizes(len(steps))
         if max(sizes) <= 1:
-            for inputs in steps:
-                self.micro_step(inputs)
+            for k, inputs in enumerate(steps):
+                self._micro_step(inputs, k + 1 < len(steps))
             return
         if table is None:
             table = self._write_addresses(steps, sizes, self._address_table(len(steps)))
         first, n, L = 0, self.wl.n, len(self.layers)
         for size in sizes:
+            more = first + size < len(steps)
             if size == 1:
-                self.micro_step(steps[first])
+                self._micro_step(steps[first], more)
             else:
                 base, row = table.data_ptr() + 8 * 2 * L * n * first, 8 * n * size
-                self._issue(self._plan(size), [base + row * 2 * i for i in range(L)], [base + row * (2 * i + 1) for i in range(L)],
-                            ends_step=first + size == len(steps))
+                self._issue(self._plan(size, more), [base + row * 2 * i for i in range(L)], [base + row * (2 * i + 1) for i in range(L)],
+                            ends_step=not more)
             first += size
 
     def run(self, inputs_per_micro_step: Iterable[Sequence]):

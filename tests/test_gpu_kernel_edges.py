@@ -757,3 +757,72 @@ def test_packed_operands(layer, n, several):
         assert torch.equal(acc[0], acc[1])
         got = host(acc[0])
     assert_close(got[idx] - 1.0, ref, BF16_TOL, "increment")
+
+
+# Layers on 14 x 14 maps in batch calls whose rows travel in stages: norm-only (ranges of eight examples, the last one short; from 128 blocks on)
+# and clip-weighted (one range; several of up to sixteen with a sum behind them), tiles of both matrices' directions, whole tensors and examples by address, an example
+# that is left out
+@pytest.mark.parametrize("cin,cout,n", [(256, 256, 131), (256, 512, 66), (512, 128, 67), (768, 384, 33), (1024, 256, 32), (256, 128, 1)])
+@pytest.mark.parametrize("at", [False, True])
+def test_row_stages(cin, cout, n, at):
+    layer = conv(cin, cout, 1, 1, 14)
+    d = dp.make_desc(layer, n, "bf16")
+    assert dp.dp_kernel_variant(d, dp.DP_WS_RECOMPUTE | dp.DP_VARIANT_SHARED) == "conv_contract<bf16,128x256rows,weighted>"
+    x, dy = _inputs(layer, n, 353, "bf16")
+    if n > 40:
+        dy[5] = 3e38                               # this example's gradient overflows: no number in its norm, nothing in the sum
+    rng = np.random.default_rng(47)
+    n2 = (rng.uniform(0.3, 2.5, n) ** 2).astype(np.float32)
+    f = np.array([oracle.clip_factor(float(v), 1.0) for v in n2])
+    if n > 40:
+        n2[5], f[5] = np.inf, 0.0
+    xd, dyd, sqd = dev(x, "bf16"), dev(dy, "bf16"), dev(n2)
+    ws = [torch.empty(max(16, dp.dp_workspace_bytes(d, dp.DP_WS_RECOMPUTE), dp.dp_workspace_bytes(d)), dtype=torch.uint8, device="cuda:0") for _ in range(2)]
+    sq = [torch.full((n,), -1.0, device="cuda:0") for _ in range(2)]
+    acc = [torch.ones(layer.pw, device="cuda:0") for _ in range(2)]
+    bt = dp.LayerBatch([d, d], [t.data_ptr() for t in ws], [t.numel() for t in ws])
+    if at:
+        tables = [torch.tensor([t.data_ptr() + i * t[0].numel() * 2 for i in range(n)], dtype=torch.int64, device="cuda:0") for t in (xd, dyd)]
+        px, pdy = ([t.data_ptr()] * 2 for t in tables)
+    else:
+        px, pdy = [xd.data_ptr()] * 2, [dyd.data_ptr()] * 2
+    dp.dp_per_example_grad_batch(bt, bt.ptrs(px), bt.ptrs(pdy), None, None, bt.ptrs([t.data_ptr() for t in sq]), addresses=at)
+    dp.dp_clip_accumulate_recompute_batch(bt, bt.ptrs(px), bt.ptrs(pdy), bt.ptrs([sqd.data_ptr()] * 2), bt.floats([1.0, 1.0]),
+                                          bt.ptrs([t.data_ptr() for t in acc]), bt.ptrs([None, None]), addresses=at)
+    torch.cuda.synchronize()
+    assert torch.equal(acc[0], acc[1])
+    keep = [i for i in range(n) if f[i] != 0.0]
+    g = np.stack([dy[i].reshape(cout, 196).astype(np.float64) @ x[i].reshape(cin, 196).astype(np.float64).T for i in keep])
+    # fp32 sums of 196 products (sqrt(196) 2^-24 = 8e-7), of their squares and of at most 131 scaled blocks
+    for t in sq:
+        assert np.allclose(host(t)[keep], (g * g).sum((1, 2)), rtol=1e-5)
+    assert_close(host(acc[0]) - 1.0, (f[keep][:, None, None] * g).sum(0).reshape(-1), 1e-5, "increment")
+
+
+# Steps of several micro-steps keep no gradients of such layers but the last one's: accumulator against single micro-steps, gradients of the last one whole
+@pytest.mark.parametrize("streams", [1, 3])
+def test_phases_that_others_follow(streams):
+    from workloads.configs import Workload
+    from workloads.device import make_device_inputs
+    layers = (conv(64, 256, 1, 1, 14, name="a"), conv(256, 256, 1, 1, 14, name="b"), conv(256, 256, 3, 1, 14, name="c"), conv(1024, 256, 1, 1, 14, name="d"),
+              dense(64, 12, name="fc"))
+    wl = Workload("rows", layers, 130, 3, "bf16", "per_layer", 1.0, 0.0, tuple("abs" for _ in layers), 0.01, 77)
+    inputs = make_device_inputs(wl, wl.accum, torch.device("cuda:0"))
+    whole, single = (dp.PrivatiseStep(wl, streams=streams) for _ in range(2))
+    assert whole.p_mat == single.p_mat and whole._plan(1, True).p_mat < whole.p_mat
+    whole.run(inputs)
+    single.begin_step()
+    for step in inputs:
+        single.micro_step(step)
+    single.finalize()
+    torch.cuda.synchronize()
+    # the same blocks, squared and scaled in fp32 in another order
+    assert_close(host(whole.acc), host(single.acc), 1e-5, "accumulator")
+    assert_close(host(whole.group_sqnorm), host(single.group_sqnorm), 1e-5, "norms")
+    assert torch.equal(whole.g, single.g)
+    first = whole.acc.clone()
+    whole.capture(inputs)
+    for _ in range(3):
+        whole.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(whole.acc, first) and torch.equal(whole.g, single.g)
