@@ -87,9 +87,35 @@ __global__ void __launch_bounds__(256) gn_affine_3pass_kernel(const Grouped<GnAr
 // bytes) that divides the channel's row.  Kernel time per optimiser step beside the other layers' kernels, against one
 // launch per layer and one wave per channel with 2- or 4-byte loads: ResNet-18-GN, 8 x 32 examples, 20 layers: 1377 ->
 // 606 us (160 -> 16 launches; whole step 2.67 -> 2.07 ms); ResNet-20 in fp32, 256 examples: 963 -> 429 us.
+//
+// A group of a few kilobytes is a wave's work for a microsecond, of which its sums were the longer part: with the sums in
+// registers (below), the example found by a 32-bit scalar division instead of one in 64 bits per lane, and no barriers
+// where a wave has its group for itself, ResNet-18-GN's whole step of 64 examples went from 1.31 to 1.27 ms, that of
+// 200 x 200 images, 36 examples, from 1.77 to 1.74 ms.
 constexpr int GN_CMAX = 256;
 constexpr int GN_WIDE_HW = 1024;             // maps of so many values, a multiple of four, are read four at a time
 constexpr int GN_SHIFTED = 9;                // GnArgs::vec: vectors of eight bf16 values that need not start with a channel
+
+// Sums over the lanes of a wave, and over its aligned teams of a power of two of lanes (in every lane of the team), by data-parallel-primitive moves as far as
+// rows of sixteen lanes go.  (Shuffles through LDS took a wave longer than its loads on small groups.)
+__device__ __forceinline__ float gn_wave_sum(float v)
+{
+    return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, wave_sum_last_lane(v)), 63));
+}
+template <int CTRL>
+__device__ __forceinline__ float gn_moved(float v)
+{
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xf, 0xf, true));
+}
+__device__ __forceinline__ void gn_team_sum(float &a, float &b, int team)
+{
+    if (team == 64) { a = gn_wave_sum(a); b = gn_wave_sum(b); return; }
+    if (team > 1) { a += gn_moved<0xB1>(a); b += gn_moved<0xB1>(b); }         // quad_perm 1 0 3 2
+    if (team > 2) { a += gn_moved<0x4E>(a); b += gn_moved<0x4E>(b); }         // quad_perm 2 3 0 1
+    if (team > 4) { a += gn_moved<0x141>(a); b += gn_moved<0x141>(b); }       // row_half_mirror
+    if (team > 8) { a += gn_moved<0x140>(a); b += gn_moved<0x140>(b); }       // row_mirror
+    if (team > 16) { a += __shfl_xor(a, 16, 64); b += __shfl_xor(b, 16, 64); }
+}
 
 template <bool BF16, int V>
 __device__ __forceinline__ void gn_load(const typename In<BF16>::type *p, float (&o)[V])
@@ -121,13 +147,17 @@ template <bool BF16, int V, bool SHIFTED = false>
 __device__ __forceinline__ void gn_affine_body(const GnArgs &a, unsigned bid, float *s_dx, float *s_d, float *red)
 {
     typedef typename In<BF16>::type E;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int waves = a.waves, team = a.team;
-    const int per_wg = 4 / waves;                                     // groups per workgroup
-    const int sub = wave / waves, wv = wave - sub * waves;
-    const long long gid = (long long)bid * per_wg + sub;
-    const bool live = gid < (long long)a.n * a.groups;                // the last workgroup may hold fewer groups
-    const int i = live ? (int)(gid / a.groups) : 0, grp = live ? (int)(gid - (long long)i * a.groups) : 0;
+    const int shift = waves == 4 ? 2 : waves - 1;                     // (waves: 1, 2 or 4)
+    const int per_wg = 4 >> shift;                                    // groups per workgroup
+    const int sub = wave >> shift, wv = wave & (waves - 1);
+    const long long gid = (long long)bid * per_wg + sub, all = (long long)a.n * a.groups;
+    const bool live = gid < all;                                      // the last workgroup may hold fewer groups
+    int i = 0;
+    if (live) i = all < (1ll << 31) ? (int)((unsigned)gid / (unsigned)a.groups) : (int)(gid / a.groups);
+    i = __builtin_amdgcn_readfirstlane(i);
+    const int grp = live ? (int)(gid - (long long)i * a.groups) : 0;
     const int cg = a.c / a.groups;
     const size_t ex = (size_t)a.c * a.hw, first = (size_t)grp * cg * a.hw;
     const E *xg = example_at_uniform<E>(a.x, a.x_tab, i, ex) + first;
@@ -221,15 +251,20 @@ __device__ __forceinline__ void gn_affine_body(const GnArgs &a, unsigned bid, fl
         float sdx = 0.0f, sd = 0.0f;
 #pragma unroll
         for (int e = 0; e < V; ++e) { sdx += dx[e]; sd += d1[e]; sx += x1[e]; sxx += x2[e]; }
-        for (int off = team >> 1; off > 0; off >>= 1) { sdx += __shfl_xor(sdx, off, 64); sd += __shfl_xor(sd, off, 64); }
+        gn_team_sum(sdx, sd, team);
         if (tl == 0 && live) { s_dx[cl] = sdx; s_d[cl] = sd; }
     }
-    sx = wave_sum(sx);
-    sxx = wave_sum(sxx);
-    if (lane == 0) { red[wave] = sx; red[4 + wave] = sxx; }
-    __syncthreads();                                                  // also makes s_dx / s_d visible
-    sx = sxx = 0.0f;
-    for (int w = sub * waves; w < (sub + 1) * waves; ++w) { sx += red[w]; sxx += red[4 + w]; }
+    sx = gn_wave_sum(sx);
+    sxx = gn_wave_sum(sxx);
+    if (waves > 1) {
+        if (lane == 0) { red[wave] = sx; red[4 + wave] = sxx; }
+        __syncthreads();                                              // also makes s_dx / s_d visible
+        sx = sxx = 0.0f;
+        for (int w = sub * waves; w < (sub + 1) * waves; ++w) { sx += red[w]; sxx += red[4 + w]; }
+    } else {
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");        // (a wave's own s_dx / s_d: its LDS instructions run in order)
+        __builtin_amdgcn_wave_barrier();
+    }
     const float inv = 1.0f / (float)(cg * a.hw);
     const float m1 = sx * inv, var = fmaxf(sxx * inv - m1 * m1, 0.0f);
     const float rstd = 1.0f / sqrtf(var + a.eps);
@@ -245,15 +280,15 @@ __device__ __forceinline__ void gn_affine_body(const GnArgs &a, unsigned bid, fl
             }
         }
     }
-    ss = wave_sum(ss);
-    __syncthreads();
-    if (lane == 0) red[wave] = ss;
-    __syncthreads();
-    if (lane == 0 && wv == 0 && live) {
-        float tot = 0.0f;
-        for (int w = sub * waves; w < (sub + 1) * waves; ++w) tot += red[w];
-        a.partials[(size_t)i * a.groups + grp] = tot;
+    ss = gn_wave_sum(ss);
+    if (waves > 1) {
+        __syncthreads();
+        if (lane == 0) red[wave] = ss;
+        __syncthreads();
+        ss = 0.0f;
+        for (int w = sub * waves; w < (sub + 1) * waves; ++w) ss += red[w];
     }
+    if (lane == 0 && wv == 0 && live) a.partials[(size_t)i * a.groups + grp] = ss;
 }
 
 template <bool BF16>

@@ -33,6 +33,20 @@ def test_groupnorm_lane_plans(c, hw, groups, n, dtype):
     assert np.allclose(sq, ref_n2, rtol=tol)
 
 
+# every team of 1 .. 64 lanes in a group that one wave has for itself (no barriers), and in one that the waves of a workgroup share
+@pytest.mark.parametrize("cg,side", [(64, 1), (64, 2), (16, 2), (16, 3), (16, 8), (8, 5), (4, 7), (2, 11), (1, 13), (130, 2), (70, 3), (20, 5),
+                                     (12, 7), (6, 11), (5, 13), (5, 16)])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_groupnorm_teams(cg, side, dtype):
+    layer = gn_affine(3 * cg, side, 3)
+    x, dy = _inputs(layer, 3, 114, dtype)
+    ref_w, ref_b, ref_n2 = _oracle_grads(layer, x, dy)
+    gw, gb, sq = _run_per_example(layer, x, dy, dtype)
+    tol = F32_TOL if dtype == "f32" else BF16_TOL
+    assert_close(gw, ref_w, tol, "dgamma")
+    assert_close(gb, ref_b, tol, "dbeta")
+    assert np.allclose(sq, ref_n2, rtol=tol)
+
 
 def _run_weighted(layer, x, dy, dtype, n2, clip_c):
     """acc_w, acc_b of the recomputing clipped sum, started from ones."""
