@@ -10,7 +10,7 @@ import torch
 import oracle
 import paper_2109_12191_amd as dp
 from gpu_util import BF16_TOL, F32_TOL, assert_close, dev, host
-from workloads import conv, dense, gn_affine, to_bf16_grid
+from workloads import Layer, conv, dense, gn_affine, to_bf16_grid
 from workloads.configs import Workload
 
 pytestmark = pytest.mark.gpu
@@ -110,6 +110,29 @@ def test_unit_batch_call_matches_the_oracle_and_the_single_layer_calls(unit, uni
         dp.dp_unit_grad(descs[k], unit, xs[k], dys[k], one, oneb if l.pb else None, sq1, wss[k])
         torch.cuda.synchronize()
         assert_close(host(gws[k]), host(one), 2e-5, f"{cases[k][0]} against the single-layer call")
+        assert np.allclose(host(sq[k]), host(sq1), rtol=3e-5, atol=0)
+
+
+# 56-wide 3x3 layers whose K is finely sliced, in one launch with a narrower layer, against the single-layer calls (their own kernels): both add
+# the same products in other orders, sqrt(4 * 3136) 2^-24 = 7e-6 of a sum's size
+@pytest.mark.parametrize("cin,cout,h,unit,units", [(64, 64, 56, 4, 2), (64, 65, 56, 2, 4), (72, 64, 6, 3, 1)])
+def test_sliced_wide_rows_share_a_launch(cin, cout, h, unit, units):
+    layers = [Layer("conv", cin, cout, h, 56, 3, 3, 1, 1, False), conv(64, 64, 3, 1, 14)]
+    n = unit * units
+    descs = [dp.make_desc(l, n, "bf16") for l in layers]
+    ins = [_inputs(l, n, 5400 + k, "bf16") for k, l in enumerate(layers)]
+    xs, dys = [dev(x, "bf16") for x, _ in ins], [dev(dy, "bf16") for _, dy in ins]
+    wss = [torch.empty(max(16, dp.dp_unit_workspace_bytes(d, unit)), dtype=torch.uint8, device="cuda:0") for d in descs]
+    sq = torch.full((2, units), -1.0, device="cuda:0")
+    gws = [torch.full((units, l.pw), 7.0, device="cuda:0") for l in layers]
+    batch = dp.LayerBatch(descs, [w.data_ptr() for w in wss], [w.numel() for w in wss])
+    dp.dp_unit_grad_batch(batch, unit, batch.ptrs([t.data_ptr() for t in xs]), batch.ptrs([t.data_ptr() for t in dys]),
+                          batch.ptrs([t.data_ptr() for t in gws]), batch.ptrs([None, None]), batch.ptrs([sq[k].data_ptr() for k in range(2)]))
+    for k, l in enumerate(layers):
+        one, sq1 = torch.zeros((units, l.pw), device="cuda:0"), torch.zeros(units, device="cuda:0")
+        dp.dp_unit_grad(descs[k], unit, xs[k], dys[k], one, None, sq1, wss[k])
+        torch.cuda.synchronize()
+        assert_close(host(gws[k]), host(one), 2e-5, "against the single-layer call")
         assert np.allclose(host(sq[k]), host(sq1), rtol=3e-5, atol=0)
 
 
