@@ -34,11 +34,10 @@ HBM_PEAK = 8.0e12
 # streaming kernels of known size in the same runs (clip_accumulate_kernel and noise_finalize_flat_kernel, 16 bytes
 # per lane like the contraction's loads: FETCH_SIZE reads half of their bytes, WRITE_SIZE all of them).
 PMC_FETCH_SCALE, PMC_WRITE_SCALE = 2.0, 1.0
-PMC_KIB_PER_LAUNCH = {          # variant -> (FETCH_SIZE, WRITE_SIZE)
-    "conv_contract<bf16,256x256rows,per_example>": (105134.5, 491793.3),
-    "conv_contract<bf16,128x128,per_example>": (194900.0, 98327.9),
-    "conv_contract<bf16,64x64,per_example>": (201359.4, 12813.6),
-    "conv_contract<bf16,128x128,weighted>": (137733.2, 37888.0),
+PMC_KIB_PER_LAUNCH = {          # variant (of launches that are alike in every micro-step) -> (FETCH_SIZE, WRITE_SIZE)
+    "conv_contract<bf16,128x128,per_example>": (195033.5, 98327.8),
+    "conv_contract<bf16,64x64,per_example>": (201687.6, 12813.4),
+    "conv_contract<bf16,128x128,weighted>": (137548.6, 37888.0),
 }
 
 
@@ -292,13 +291,16 @@ def main():
     # The whole step against the HBM roof: algorithmic bytes of every call of a step (operands once per call, per-example
     # gradients written and read back where they are materialised, the accumulator read and written by every clipped
     # sum, finalize) over the measured step time.
-    # (micro-steps issued together add to the accumulator once)
-    phases, main = -(-wl.accum // ps.micro_steps_per_phase), ps._main
-    forms, part = main.form, wl.accum / main.tensors
-    sums = 8.0 * (main.p_mat + sum(pw + pb for pw, pb, f in zip(ps.pw, ps.pb, forms) if f == "recompute"))
-    step_bytes = (part * (sum(w[1] for w in main.work) + sum(l.in_bytes(esize) * main.n for l, f in zip(wl.layers, forms) if f == "recompute")
-                          + 4.0 * main.rows * main.p_mat) + phases * sums + 8.0 * wl.n_params)
-    step_flops = part * (sum(w[0] for w in main.work) + sum(w[0] for w, f in zip(main.work, forms) if f == "recompute"))
+    # (micro-steps issued together add to the accumulator once; phases that others follow may store fewer layers than the last one)
+    sizes, forms = ps._phase_sizes(wl.accum), ps._main.form
+    step_bytes, step_flops = 8.0 * wl.n_params, 0.0
+    for k, size in enumerate(sizes):
+        plan = ps._plan(size, k + 1 < len(sizes))
+        again = [f == "recompute" for f in plan.form]
+        stored = sum(pw + pb for pw, pb, r in zip(ps.pw, ps.pb, again) if not r)
+        step_bytes += (sum(w[1] for w in plan.work) + sum(l.in_bytes(esize) * plan.n for l, r in zip(wl.layers, again) if r)
+                       + 4.0 * plan.rows * stored + 8.0 * wl.n_params)
+        step_flops += sum(w[0] * (1 + r) for w, r in zip(plan.work, again))
     step_sec = elapsed / args.steps
     if roofline is not None:
         roofline["whole_step"] = dict(algorithmic_bytes=step_bytes, algorithmic_flop=step_flops, GBps=step_bytes / step_sec / 1e9,

@@ -487,7 +487,9 @@ class PrivatiseStep:
 
     def _plan(self, tensors: int, more: bool = False) -> _Plan:
         """Of phases of `tensors` micro-steps; more: of those that others of their step follow."""
-        key = (tensors, more and self._forms(tensors, True) is not self._forms(tensors))
+        key = (tensors, more)
+        if key not in self._plans and more and self._forms(tensors, True) is self._forms(tensors):
+            self._plans[key] = self._plan(tensors)
         if key not in self._plans:
             stores = []
             for c, room in enumerate(self._room):
@@ -496,7 +498,7 @@ class PrivatiseStep:
                         ws = self._workspace_bytes(1) if room == 1 else self._ws_room
                         self._stores[c] = _Store(self, room * self.rows, ws)
                     stores.append(self._stores[c])
-            self._plans[key] = _Plan(self, tensors, stores, None, key[1])
+            self._plans[key] = _Plan(self, tensors, stores, None, more)
         return self._plans[key]
 
     def _last_plan(self, form: Sequence[str]) -> _Plan:
