@@ -51,6 +51,15 @@ void set_open_queue(LaunchQueue *q) { g_queue = q; }
 int crowd_hint() { return g_queue ? g_queue->crowd : 0; }
 int fuse_hint() { return g_queue ? g_queue->fuse : 0; }
 
+// Work per workgroup a batch call plans for, in units of one 128x128x64 chunk: the convolutions' multiply-adds
+// spread over about three rounds of workgroups on 256 compute units, but neither so little that a workgroup's
+// start-up dominates nor so much that one workgroup becomes the critical path.
+int crowd_of(double macs)
+{
+    const double per_wg = macs / (128.0 * 128.0 * 64.0) / 768.0;
+    return per_wg < 4.0 ? 4 : (per_wg > 64.0 ? 64 : (int)per_wg);
+}
+
 dp_status flush_queue(LaunchQueue &q)
 {
     set_open_queue(nullptr);                         // from here on everything is launched at once
@@ -474,17 +483,13 @@ dp_status dp_unit_grad(const dp_layer_desc *desc, int clip_unit, const void *x, 
     return launch_layer_units(g, clip_unit, x, dy, g_w, g_b, g_stride, sqnorm, ws, s);
 }
 
-// Work per workgroup a batch call plans for, in units of one 128x128x64 chunk: the convolutions' multiply-adds
-// spread over about three rounds of workgroups on 256 compute units, but neither so little that a workgroup's
-// start-up dominates nor so much that one workgroup becomes the critical path.
 static int batch_target(const std::vector<Geo> &geo)
 {
     if (geo.size() < 2) return 0;
     double macs = 0.0;
     for (const Geo &g : geo)
-        if (g.kind == DP_CONV2D) macs += (double)g.n * g.cout * g.cin * g.kh * g.kw * g.oh * g.ow;
-    const double per_wg = macs / (128.0 * 128.0 * 64.0) / 768.0;
-    return per_wg < 4.0 ? 4 : (per_wg > 64.0 ? 64 : (int)per_wg);
+        if (g.kind == DP_CONV2D) macs += conv_macs(g);
+    return crowd_of(macs);
 }
 
 // addresses: x[l], dy[l] are arrays of example addresses

@@ -28,6 +28,7 @@
 #include "group.h"
 #include "pieces.h"
 
+#include <algorithm>
 #include <atomic>
 #include <cstdio>
 #include <utility>
@@ -908,7 +909,7 @@ __global__ void __launch_bounds__(C3_THREADS) conv3x3_fixup_kernel(const Grouped
 
 struct C3Plan {
     int stage_rows;                    // output rows of a stage (C3Cfg)
-    int tiles_co, tiles_ci, chunks;    // chunks: what the plans count work in, about 224 output positions
+    int tiles_co, tiles_ci, chunks;    // chunks: a unit of work that slices of K are planned in, about 224 output positions (not what the kernel walks in)
     int ksplit, stages_per_split;      // per-example modes: K slices; weighted: example ranges
     int ex_per_split;                  // weighted
     int slice_ex;                      // per-example modes: examples per slice of a clipping unit, or 0
@@ -955,13 +956,20 @@ C3Plan c3_plan_slices(const Geo &g, int mode)
     // walk of a workgroup is what such a launch waits for
     if (crowd && mode != MODE_WEIGHTED && (long long)g.n * tiles * p.chunks <= 128) tgt = 1;
     if (mode == MODE_WEIGHTED) {
-        // example ranges: about 256 workgroups, partial blocks in the workspace kept below ~100 MB; in a launch
-        // shared with other layers, ranges of at most 48 chunks
+        // Example ranges, partial blocks in the workspace kept below ~100 MB.  A layer alone: about 256 workgroups.
         long long want = (256 + tiles - 1) / tiles;
-        // (measured in the replayed step: a narrow launch that the other streams overlap, without partial blocks and slice-sum launch, beats
-        // ranges that would fill the chip.  ResNet-50, 32 examples: one range per tile 6690 us a step, two for the 14-wide layers (16 tiles)
-        // 6850, four 7030; a walk is still capped at 48 chunks)
-        if (crowd) want = ((long long)g.n * p.chunks + 47) / 48;
+        if (crowd) {
+            // In a launch shared with other layers ranges are long: without partial blocks and slice-sum launch a narrow launch that the other streams
+            // of a replayed step overlap beats one that fills the chip (ResNet-50, 32 examples, crowd 32: one range per tile 6690 us a step, two
+            // for the 14-wide layers, 16 tiles, 6850, four 7030).  But no longer than the launch is worth: `crowd` grows with all of its work, and a
+            // walk has about four stages per unit of it (that range of 32 examples is 128 stages), and 48 chunks.  Where the launch is
+            // small (crowd < 8; at 4 it may be any amount below) a layer of few tiles still brings 32 workgroups.  Two such layers by themselves, us, with the
+            // 48 chunks alone / so: 64 -> 64 at 14 x 14, 48 examples, 241 / 25; at 28 x 28, 32, 169 / 32; 256 -> 256 at 14 x 14, 48, 240 / 78; four
+            // of 128 -> 128 at 28 x 28, 16, 129 / 62.  (Sixteen tiles and more keep their one range there: 256 -> 256 at 14 x 14, 4 examples, 33; two ranges 47.)
+            const long long stages = (long long)g.n * ((g.oh + p.stage_rows - 1) / p.stage_rows);
+            want = std::max((stages + 4 * crowd - 1) / (4 * crowd), ((long long)g.n * p.chunks + 47) / 48);
+            if (crowd < 8 && tiles <= 8 && want * tiles < 32) want = (32 + tiles - 1) / tiles;
+        }
         const long long cap = (long long)(96.0e6 / (4.0 * 9 * 16 * C3_THREADS * (double)tiles));
         if (want > cap) want = cap;
         if (want > g.n) want = g.n;
@@ -1093,7 +1101,8 @@ size_t conv3x3_ws_bytes(const Geo &g, int mode)
     const int saved = c3_forced_crowd;
     c3_forced_crowd = 0;
     const size_t alone = conv3x3_ws_bytes_plan(g, mode);
-    c3_forced_crowd = 4;                             // smallest target: most slices
+    // the smallest target that a batch call with this layer can have: most slices
+    c3_forced_crowd = mode == MODE_WEIGHTED ? crowd_of(conv_macs(g)) : 4;
     const size_t shared = conv3x3_ws_bytes_plan(g, mode);
     c3_forced_crowd = saved;
     return alone > shared ? alone : shared;

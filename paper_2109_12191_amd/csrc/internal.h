@@ -47,6 +47,9 @@ enum Mode { MODE_NORM = 0, MODE_MATERIALISE = 1, MODE_WEIGHTED = 2 };
 
 size_t conv_ws_bytes(const Geo &g, int mode);
 const char *conv_variant_name(const Geo &g, int mode, bool shared);
+// multiply-adds of a call, and the work per workgroup (LaunchQueue::crowd) of a batch call whose convolutions have that many together
+inline double conv_macs(const Geo &g) { return (double)g.n * g.cout * g.cin * g.kh * g.kw * g.oh * g.ow; }
+int crowd_of(double macs);
 void c3_set_forced_crowd(int v);      // conv3x3.hip: plan as alone (0), as in a shared launch (1), or by the open batch (-1)
 dp_status launch_conv(const Geo &g, int mode, const void *x, const void *dy, float *out_w, float *out_b,
                       size_t out_stride, float *sqnorm, const float *group_sqnorm, float clip_c, void *ws,

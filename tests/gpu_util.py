@@ -2,6 +2,7 @@
 import numpy as np
 import torch
 
+import ctypes
 import os
 import sys
 import time
@@ -52,3 +53,30 @@ def progress(msg: str):
     if os.path.isdir(_PROGRESS):
         with open(os.path.join(_PROGRESS, "test_progress.log"), "a") as f:
             f.write(line + "\n")
+
+
+class _KernelNode(ctypes.Structure):
+    _fields_ = [("block", ctypes.c_uint32 * 3), ("extra", ctypes.c_void_p), ("func", ctypes.c_void_p), ("grid", ctypes.c_uint32 * 3),
+                ("params", ctypes.c_void_p), ("lds", ctypes.c_uint32)]
+
+
+def launches(call):
+    """Workgroups of every kernel that `call` launches, in the order they were recorded in (nothing runs but a first call)."""
+    call()
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph(keep_graph=True)
+    with torch.cuda.graph(graph):
+        call()
+    with open("/proc/self/maps") as maps:
+        path = next(l.split()[-1] for l in maps if "libamdhip64.so" in l)
+    hip, raw, count = ctypes.CDLL(path), ctypes.c_void_p(graph.raw_cuda_graph()), ctypes.c_size_t(0)
+    assert hip.hipGraphGetNodes(raw, None, ctypes.byref(count)) == 0
+    nodes = (ctypes.c_void_p * count.value)()
+    assert hip.hipGraphGetNodes(raw, nodes, ctypes.byref(count)) == 0
+    found = []
+    for node in nodes:
+        kind, node_params = ctypes.c_int(-1), _KernelNode()
+        assert hip.hipGraphNodeGetType(ctypes.c_void_p(node), ctypes.byref(kind)) == 0 and kind.value == 0, "not a kernel"
+        assert hip.hipGraphKernelNodeGetParams(ctypes.c_void_p(node), ctypes.byref(node_params)) == 0
+        found.append(node_params.grid[0] * node_params.grid[1] * node_params.grid[2])
+    return found

@@ -8,7 +8,7 @@ import torch
 
 import oracle
 import paper_2109_12191_amd as dp
-from gpu_util import BF16_TOL, F32_TOL, assert_close, dev, host
+from gpu_util import BF16_TOL, F32_TOL, assert_close, dev, host, launches
 from test_gpu_kernels import _inputs, _oracle_grads, _run_per_example
 from workloads import Layer, conv, dense, gn_affine, to_bf16_grid
 
@@ -840,3 +840,45 @@ def test_phases_that_others_follow(streams):
         whole.replay()
         torch.cuda.synchronize()
         assert torch.equal(whole.acc, first) and torch.equal(whole.g, single.g)
+
+
+def _weighted_batch(layers, n, seed=359):
+    """A clip-weighted batch call of bf16 layers, and what it works on."""
+    gen = torch.Generator(device="cuda:0")
+    gen.manual_seed(seed)
+    descs = [dp.make_desc(l, n, "bf16") for l in layers]
+    xs, dys = ([torch.randn((n,) + tuple(shape), generator=gen, device="cuda:0").bfloat16() for shape in shapes]
+               for shapes in ([l.x_shape for l in layers], [l.dy_shape for l in layers]))
+    ws = [torch.empty(max(16, dp.dp_workspace_bytes(d, dp.DP_WS_RECOMPUTE)), dtype=torch.uint8, device="cuda:0") for d in descs]
+    sq = torch.rand(n, generator=gen, device="cuda:0") + 0.5
+    acc = [torch.zeros(l.pw, device="cuda:0") for l in layers]
+    bt = dp.LayerBatch(descs, [t.data_ptr() for t in ws], [t.numel() for t in ws])
+    args = (bt, bt.ptrs([t.data_ptr() for t in xs]), bt.ptrs([t.data_ptr() for t in dys]), bt.ptrs([sq.data_ptr()] * len(layers)), bt.floats([1.0] * len(layers)),
+            bt.ptrs([t.data_ptr() for t in acc]), bt.ptrs([None] * len(layers)))
+    return (lambda: dp.dp_clip_accumulate_recompute_batch(*args)), (xs, dys, ws, sq, acc)
+
+
+# The clip-weighted 3x3 form in batch calls: layers of few tiles still bring workgroups (up to what whole examples allow); in a full
+# launch a tile is one workgroup, without slice sums
+@pytest.mark.parametrize("layers,n,least", [([conv(64, 64, 3, 1, 14)] * 2, 48, 48), ([conv(64, 64, 3, 1, 28)] * 2, 32, 64), ([conv(64, 64, 3, 1, 7)] * 2, 128, 64),
+                                            ([conv(256, 256, 3, 1, 14)] * 2, 48, 128), ([conv(128, 128, 3, 1, 28)] * 4, 16, 96)],
+                         ids=lambda v: str(v) if isinstance(v, int) else f"{len(v)}x{v[0].cin}-{v[0].h}")
+def test_conv3x3_weighted_batches_fill_the_chip(layers, n, least):
+    call, (xs, dys, _, sq, acc) = _weighted_batch(layers, n)
+    for t in acc:
+        t.zero_()
+    main = launches(call)[0]
+    assert main >= least, main
+    # recorded, not run: one call's sums, of which some are compared with products in fp64
+    f = torch.clamp(1.0 / sq.double().sqrt(), max=1.0)
+    for x, dy, got, l in zip(xs, dys, acc, layers):
+        scaled = (dy.double() * f[:, None, None, None]).float().bfloat16().double()
+        ref = torch.nn.functional.unfold(x[:, :4].double(), 3, padding=1)
+        ref = sum(scaled[i].reshape(l.cout, -1) @ ref[i].T for i in range(n))
+        assert_close(host(got.reshape(l.cout, l.cin, 9)[:, :4]).reshape(-1), host(ref).reshape(-1), 1e-4, "sum")
+
+
+def test_conv3x3_weighted_batches_of_a_full_launch_walk_one_range():
+    layers = [conv(256, 256, 3, 1, 14)] * 5 + [conv(512, 512, 3, 1, 7)] * 2
+    call, _kept = _weighted_batch(layers, 32)
+    assert launches(call) == [5 * 16 + 2 * 64]
