@@ -1887,17 +1887,26 @@ static bool packed_weighted(const Geo &g, int mode, PackPlan &pp, Geo &g2)
     const long long J = (long long)g.cin * g.kh * g.kw;
     const int shape = (g.cout > 64 && J > 64) ? T128 : T64;
     const long long tiles = (long long)((g.cout + kTileM[shape] - 1) / kTileM[shape]) * ((J + kTileN[shape] - 1) / kTileN[shape]);
-    long long groups = (256 + tiles - 1) / tiles;
-    if (plan_crowd()) {
+    auto plan = [&](long long groups) { return pack_plan(g, (int)std::max(1ll, std::min(groups, (long long)g.n))); };
+    auto bytes = [](const PackPlan &p) { return p.x_bytes + p.dy_bytes; };
+    const size_t most = (size_t)64 << 20;
+    if (const int crowd = plan_crowd()) {
         // sharing the launch with other layers: example ranges of about twice the target number of chunks
-        const long long sp = ((long long)g.oh * g.ow + 7) / 8 * 8;
-        const long long per = (long long)2 * plan_crowd() * (shape == T64 ? 4 : 1) * 64;
-        groups = ((long long)g.n * sp + per - 1) / per;
+        const long long positions = (long long)g.n * (((long long)g.oh * g.ow + 7) / 8 * 8);
+        auto ranges = [&](int target) {
+            const long long per = (long long)2 * target * (shape == T64 ? 4 : 1) * 64;
+            return (positions + per - 1) / per;
+        };
+        // Ranges are of equal length, so the last one may be mostly padding (three examples in two ranges take the room of four).  Workspaces are
+        // sized for the smallest target: fewer ranges than it makes must not need more than it does.
+        const size_t reported = bytes(plan(ranges(4)));
+        if (reported > most) return false;
+        long long groups = ranges(crowd);
+        while (bytes(pp = plan(groups)) > reported) ++groups;
+    } else {
+        pp = plan((256 + tiles - 1) / tiles);
+        if (bytes(pp) > most) return false;
     }
-    if (groups > g.n) groups = g.n;
-    if (groups < 1) groups = 1;
-    pp = pack_plan(g, (int)groups);
-    if (pp.x_bytes + pp.dy_bytes > ((size_t)64 << 20)) return false;
     if ((long long)J * pp.kg >= (1ll << 31) || (long long)g.cout * pp.kg >= (1ll << 31)) return false;
     packed_geometry(g, pp, g2);
     return true;

@@ -882,3 +882,26 @@ def test_conv3x3_weighted_batches_of_a_full_launch_walk_one_range():
     layers = [conv(256, 256, 3, 1, 14)] * 5 + [conv(512, 512, 3, 1, 7)] * 2
     call, _kept = _weighted_batch(layers, 32)
     assert launches(call) == [5 * 16 + 2 * 64]
+
+
+# Packed operands in a batch call whose target makes ranges that the number of examples is no multiple of (here two of two for three examples):
+# everything stays inside the workspace that was asked for
+@pytest.mark.parametrize("layer,other,n", [(Layer("conv", 176, 64, 46, 46, 3, 3, 1, 1, False), conv(512, 512, 3, 1, 28), 3),
+                                           (Layer("conv", 96, 64, 40, 44, 3, 3, 1, 1, False), conv(512, 512, 3, 1, 28), 5)], ids=["3", "5"])
+def test_packed_operands_stay_in_the_workspace(layer, other, n):
+    descs = [dp.make_desc(l, n, "bf16") for l in (layer, other)]
+    need = [max(16, dp.dp_workspace_bytes(d, dp.DP_WS_RECOMPUTE)) for d in descs]
+    guard = 16 << 20
+    ws = [torch.full((b + guard,), 0x5A, dtype=torch.uint8, device="cuda:0") for b in need]
+    ins = [_inputs(l, n, 367 + k, "bf16") for k, l in enumerate((layer, other))]
+    xs, dys = [dev(x, "bf16") for x, _ in ins], [dev(dy, "bf16") for _, dy in ins]
+    n2 = (np.random.default_rng(53).uniform(0.3, 2.5, n) ** 2).astype(np.float32)
+    sq, acc = dev(n2), [torch.zeros(l.pw, device="cuda:0") for l in (layer, other)]
+    bt = dp.LayerBatch(descs, [t.data_ptr() for t in ws], need)
+    dp.dp_clip_accumulate_recompute_batch(bt, bt.ptrs([t.data_ptr() for t in xs]), bt.ptrs([t.data_ptr() for t in dys]), bt.ptrs([sq.data_ptr()] * 2),
+                                          bt.floats([1.0, 1.0]), bt.ptrs([t.data_ptr() for t in acc]), bt.ptrs([None, None]))
+    torch.cuda.synchronize()
+    assert all(bool((t[b:] == 0x5A).all()) for t, b in zip(ws, need))
+    f = np.array([oracle.clip_factor(float(v), 1.0) for v in n2])
+    idx = np.random.default_rng(59).choice(layer.pw, size=1000, replace=False)
+    assert_close(host(acc[0])[idx], oracle.weighted_sum_elems(layer, *ins[0], f, idx), BF16_TOL, "increment")
