@@ -1748,8 +1748,14 @@ static FullPlan full_plan(const Geo &g, int mode)
     const bool panel = mode != MODE_WEIGHTED && g.unit == 1 && flat_direct(g) && S % 8 == 4 && S > 16 * (PANEL_KS - 1) && S <= 16 * PANEL_KS &&
                        g.cout % 256 == 0 && J % 256 == 0 && (long long)g.n * (g.cout / 256) * (J / 256) >= 128;
     if (panel) p.shape = T256rows;
-    // and their clip-weighted and norm-only forms in batch calls (conv_row_stages_kernel)
-    if ((mode == MODE_WEIGHTED || (panel && mode == MODE_NORM)) && crowd && flat_direct(g) && S % 8 == 4 && S > 16 * (PANEL_KS - 1) && S <= 16 * PANEL_KS && g.cout % PANELW_M == 0 && J % PANELW_N == 0)
+    // and their clip-weighted and norm-only forms in batch calls (conv_row_stages_kernel).  A clip-weighted range is a walk of up to sixteen examples,
+    // 58 us, so the call needs the work to fill the chip with them, and the examples to make them of.  A batch call by itself, us, conv_flat_kernel /
+    // this: 256 -> 256, 13 layers, 16 examples (crowd 3) 33 / 67, 64 (13) 113 / 60; 2 layers, 128 examples (4) 40 / 56; 256 -> 1024, 4 layers, 32
+    // examples (8) 47 / 57, 64 (16) 76 / 61; 1024 -> 2048, 2 layers, 16 examples (16) 63 / 72, 24 (24) 81 / 64; few examples of wide matrices: 13
+    // layers of 1024 -> 2048, 8 examples (53) 173 / 187, 4 layers, 12 examples (24) 71 / 67.
+    const bool weighted_rows = mode == MODE_WEIGHTED && ((crowd >= 13 && g.n >= 17) || (crowd >= 17 && g.n >= 12));
+    if ((weighted_rows || (panel && mode == MODE_NORM && crowd)) && flat_direct(g) && S % 8 == 4 && S > 16 * (PANEL_KS - 1) && S <= 16 * PANEL_KS &&
+        g.cout % PANELW_M == 0 && J % PANELW_N == 0)
         p.shape = T128rows;
     p.tiles_m = (g.cout + kTileM[p.shape] - 1) / kTileM[p.shape];
     p.tiles_n = (J + kTileN[p.shape] - 1) / kTileN[p.shape];
@@ -1767,8 +1773,9 @@ static FullPlan full_plan(const Geo &g, int mode)
     }
     if (p.shape == T128rows) {
         // ranges of up to 16 examples: us a step of ResNet-50, ranges of 32 / 16: 8 x 32 6400 / 6360 on eight streams, 32 x 1 1160 / 1111 on four,
-        // 16 x 2 on one 1425 / 1373
-        p.ksplit = (g.n + 15) / 16;
+        // 16 x 2 on one 1425 / 1373; longer ones where the copies of the matrix would take more than 96 MB
+        const long long cap = std::max(1ll, (long long)(96.0e6 / (4.0 * (double)g.cout * J)));
+        p.ksplit = (int)std::min((long long)(g.n + 15) / 16, cap);
         p.ex_per_split = (g.n + p.ksplit - 1) / p.ksplit;
         p.ksplit = (g.n + p.ex_per_split - 1) / p.ex_per_split;
         p.groups = tiles;
@@ -2012,7 +2019,8 @@ size_t conv_ws_bytes(const Geo &g, int mode)
 {
     size_t need = 0;
     const int saved = tl_forced_crowd;
-    for (int crowd = 0; crowd <= 4; crowd += 4) {   // a call alone and a call inside a batch (smallest target: most slices)
+    // a call alone, and a call inside a batch: the smallest target, of which there are most slices, and one that the clip-weighted whole-row kernel is chosen at
+    for (int crowd : {0, 4, 64}) {
         tl_forced_crowd = crowd;
         size_t b = conv_ws_bytes_mode(g, mode == MODE_WEIGHTED ? MODE_WEIGHTED : MODE_NORM);
         if (mode != MODE_WEIGHTED) {

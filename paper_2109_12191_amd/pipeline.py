@@ -38,10 +38,10 @@ PHASE_EXAMPLES = 256
 #   and of micro-steps of one or two examples.  ResNet-50, 64 x 1: one by one / 16 / 32 / 64 9682 / 2774 / 2476 / 2481; 32 x 2: 7984 /
 #   2821 (16) / 2502 / 2498
 PHASE_EXAMPLES_OF_SMALL = 64
-# From how many examples on the layers whose clipped sum the whole-row kernel makes (from finished fp32 blocks) need no stored gradients: it runs
-# two ranges of examples then.  ResNet-50 in phases of one-example micro-steps on four streams, stored / this: 16 708 / 720, 24 (of two, one stream) 1173 / 1157,
-# 32 1150 / 1111, 64 2140 / 2050.
-ROWS_EXAMPLES = 17
+# How much work a batch call needs for the library to run its clip-weighted layers on 14 x 14 maps in the whole-row kernel (from finished fp32 blocks), in rounds of
+# 768 workgroups of one 128 x 128 x 64 chunk: from there on those layers need no stored gradients.  ResNet-50 in phases of one-example
+# micro-steps on four streams, stored / this: 16 examples (13) 708 / 720, 24 (19, of two on one stream) 1173 / 1157, 32 (26) 1150 / 1111, 64 (53) 2140 / 2050.
+ROWS_WORK = 17
 # And no phase is so large that a layer falls back to the kernel that gathers its operands element by element, because the rewritten
 # operands of a faster one outgrow their share of the workspace: ResNet-18-GN at 40 x 40, 64 examples 3656 / 5083 (two micro-steps) / 7188
 # (four), 24 (8 micro-steps): 3097 / 3028 (four) / 3825 (eight).
@@ -369,9 +369,9 @@ class PrivatiseStep:
             # 8 x 32 6680 / 6360, 2 x 48 2700 / 2660; with GroupNorm 2 x 24 1940 / 1905; 8 x 24 on one stream 5960 / 5840.  The last one stores: `g` is whole
             # after a step.
             form = self._forms(tensors)
-            rows = [] if n < ROWS_EXAMPLES or self._mode != "auto" or self.clip_unit > 1 or form is not self.form or any(p % 4 for p in self.pw + self.pb) else [
-                i for i, l in enumerate(self.layers) if form[i] == "materialise" and l.kind == "conv" and "128x256rows" in B.dp_kernel_variant(
-                    B.make_desc(l, n, self.wl.dtype), B.DP_WS_RECOMPUTE | B.DP_VARIANT_SHARED)]
+            rows = [] if self._mode != "auto" or self.clip_unit > 1 or form is not self.form or any(p % 4 for p in self.pw + self.pb) else (
+                self._in_whole_rows([B.dp_kernel_variant(B.make_desc(l, n, self.wl.dtype), B.DP_WS_RECOMPUTE | B.DP_VARIANT_SHARED) for l in self.layers], n))
+            rows = [i for i in rows if form[i] == "materialise"]
             self._lean_forms[tensors] = ["recompute" if i in rows else f for i, f in enumerate(form)] if rows else form
         if more:
             return self._lean_forms[tensors]
@@ -381,16 +381,23 @@ class PrivatiseStep:
         if tensors not in self._phase_forms:
             norms, sums = (use | B.DP_RECOMPUTE_BLOCKS for use in (B.DP_WS_PER_EXAMPLE_GRAD, B.DP_WS_RECOMPUTE))
             over = {}                            # layer -> workspace less its part of the matrix
-            for i, l in enumerate(self.layers):
-                d = B.make_desc(l, n, self.wl.dtype)
-                variant = B.dp_kernel_variant(d, sums | B.DP_VARIANT_SHARED)
-                if variant and ((n >= ROWS_EXAMPLES and "128x256rows" in variant) or self._choose(l, "auto", n) == "recompute"):
+            descs = [B.make_desc(l, n, self.wl.dtype) for l in self.layers]
+            variants = [B.dp_kernel_variant(d, sums | B.DP_VARIANT_SHARED) for d in descs]
+            rows = self._in_whole_rows(variants, n)
+            for i, (l, d, variant) in enumerate(zip(self.layers, descs, variants)):
+                if variant and (i in rows or self._choose(l, "auto", n) == "recompute"):
                     need = max(B.dp_batch_workspace_bytes(d, norms), B.dp_workspace_bytes(d, sums), 16)
                     over[i] = _align256(need) - 4 * n * (self.pw[i] + self.pb[i])
             while over and sum(over.values()) + 256 > 0:
                 del over[max(over, key=over.get)]
             self._phase_forms[tensors] = ["recompute" if i in over else form for i, form in enumerate(self.form)] if over else self.form
         return self._phase_forms[tensors]
+
+    def _in_whole_rows(self, variants: Sequence[str], n: int) -> List[int]:
+        """Layers that run in the whole-row kernel when the recomputing calls of `n` examples hold all that could (at most 16 a call)."""
+        ids = [i for i, v in enumerate(variants) if "128x256rows" in v]
+        calls = [ids[k: k + 16] for k in range(0, len(ids), 16)]
+        return [i for call in calls if len(call) > 1 and n * sum(self.layers[i].flops for i in call) >= ROWS_WORK * 768 * 2 * 128 * 128 * 64 for i in call]
 
     def _blocks(self, tensors: int) -> int:
         """Or-ed into the uses of a phase's calls: whether it works on finished blocks."""

@@ -773,15 +773,35 @@ def test_packed_operands(layer, n, several):
     assert_close(got[idx] - 1.0, ref, BF16_TOL, "increment")
 
 
-# Layers on 14 x 14 maps in batch calls whose rows travel in stages: norm-only (ranges of eight examples, the last one short; from 128 blocks on)
-# and clip-weighted (one range; several of up to sixteen with a sum behind them), tiles of both matrices' directions, whole tensors and examples by address, an example
-# that is left out
-@pytest.mark.parametrize("cin,cout,n", [(256, 256, 131), (256, 512, 66), (512, 128, 67), (768, 384, 33), (1024, 256, 32), (256, 128, 1)])
+def _weighted_batch(layers, n, seed=359):
+    """A clip-weighted batch call of bf16 layers, and what it works on."""
+    gen = torch.Generator(device="cuda:0")
+    gen.manual_seed(seed)
+    descs = [dp.make_desc(l, n, "bf16") for l in layers]
+    xs, dys = ([torch.randn((n,) + tuple(shape), generator=gen, device="cuda:0").bfloat16() for shape in shapes]
+               for shapes in ([l.x_shape for l in layers], [l.dy_shape for l in layers]))
+    ws = [torch.empty(max(16, dp.dp_workspace_bytes(d, dp.DP_WS_RECOMPUTE)), dtype=torch.uint8, device="cuda:0") for d in descs]
+    sq = torch.rand(n, generator=gen, device="cuda:0") + 0.5
+    acc = [torch.zeros(l.pw, device="cuda:0") for l in layers]
+    bt = dp.LayerBatch(descs, [t.data_ptr() for t in ws], [t.numel() for t in ws])
+    args = (bt, bt.ptrs([t.data_ptr() for t in xs]), bt.ptrs([t.data_ptr() for t in dys]), bt.ptrs([sq.data_ptr()] * len(layers)), bt.floats([1.0] * len(layers)),
+            bt.ptrs([t.data_ptr() for t in acc]), bt.ptrs([None] * len(layers)))
+    return (lambda: dp.dp_clip_accumulate_recompute_batch(*args)), (xs, dys, ws, sq, acc)
+
+
+# Layers in batch calls whose rows travel in stages, of 196 and of 204 values (where other waves issue the seventh load of a stage): norm-only (ranges of eight
+# examples, the last one short; from 128 blocks on) and clip-weighted (one range; several of up to sixteen with a sum behind them; twelve examples and a
+# call of enough work, which a third layer stands for), tiles of both matrices' directions, whole tensors and examples by address, an example that is left out
+@pytest.mark.parametrize("cin,cout,n,hw", [(256, 256, 131, (14, 14)), (256, 512, 66, (14, 14)), (512, 128, 67, (14, 14)), (768, 384, 33, (14, 14)),
+                                           (1024, 256, 32, (14, 14)), (256, 128, 1, (14, 14)), (256, 256, 12, (14, 14)), (256, 512, 65, (12, 17)), (512, 512, 19, (17, 12))])
 @pytest.mark.parametrize("at", [False, True])
-def test_row_stages(cin, cout, n, at):
-    layer = conv(cin, cout, 1, 1, 14)
+def test_row_stages(cin, cout, n, hw, at):
+    layer, filler = Layer("conv", cin, cout, *hw), conv(1024, 1024, 3, 1, 14)
+    S = hw[0] * hw[1]
     d = dp.make_desc(layer, n, "bf16")
-    assert dp.dp_kernel_variant(d, dp.DP_WS_RECOMPUTE | dp.DP_VARIANT_SHARED) == "conv_contract<bf16,128x256rows,weighted>"
+    rows = "128x256rows" in dp.dp_kernel_variant(d, dp.DP_WS_RECOMPUTE | dp.DP_VARIANT_SHARED)
+    assert rows == (n >= 12)
+    descs = [d, d, dp.make_desc(filler, n, "bf16")]
     x, dy = _inputs(layer, n, 353, "bf16")
     if n > 40:
         dy[5] = 3e38                               # this example's gradient overflows: no number in its norm, nothing in the sum
@@ -790,27 +810,63 @@ def test_row_stages(cin, cout, n, at):
     f = np.array([oracle.clip_factor(float(v), 1.0) for v in n2])
     if n > 40:
         n2[5], f[5] = np.inf, 0.0
-    xd, dyd, sqd = dev(x, "bf16"), dev(dy, "bf16"), dev(n2)
-    ws = [torch.empty(max(16, dp.dp_workspace_bytes(d, dp.DP_WS_RECOMPUTE), dp.dp_workspace_bytes(d)), dtype=torch.uint8, device="cuda:0") for _ in range(2)]
-    sq = [torch.full((n,), -1.0, device="cuda:0") for _ in range(2)]
-    acc = [torch.ones(layer.pw, device="cuda:0") for _ in range(2)]
-    bt = dp.LayerBatch([d, d], [t.data_ptr() for t in ws], [t.numel() for t in ws])
+    xd, dyd, sqd = [dev(x, "bf16")] * 2, [dev(dy, "bf16")] * 2, dev(n2)
+    xd.append(torch.ones((n,) + tuple(filler.x_shape), dtype=torch.bfloat16, device="cuda:0"))
+    dyd.append(xd[2])
+    ws = [torch.empty(max(16, dp.dp_workspace_bytes(e, dp.DP_WS_RECOMPUTE), dp.dp_workspace_bytes(e)), dtype=torch.uint8, device="cuda:0") for e in descs]
+    sq = [torch.full((n,), -1.0, device="cuda:0") for _ in range(3)]
+    acc = [torch.ones(p, device="cuda:0") for p in (layer.pw, layer.pw, filler.pw)]
+    bt = dp.LayerBatch(descs, [t.data_ptr() for t in ws], [t.numel() for t in ws])
     if at:
-        tables = [torch.tensor([t.data_ptr() + i * t[0].numel() * 2 for i in range(n)], dtype=torch.int64, device="cuda:0") for t in (xd, dyd)]
-        px, pdy = ([t.data_ptr()] * 2 for t in tables)
+        tables = [[torch.tensor([t.data_ptr() + i * t[0].numel() * 2 for i in range(n)], dtype=torch.int64, device="cuda:0") for t in ts] for ts in (xd, dyd)]
+        px, pdy = ([t.data_ptr() for t in ts] for ts in tables)
     else:
-        px, pdy = [xd.data_ptr()] * 2, [dyd.data_ptr()] * 2
-    dp.dp_per_example_grad_batch(bt, bt.ptrs(px), bt.ptrs(pdy), None, None, bt.ptrs([t.data_ptr() for t in sq]), addresses=at)
-    dp.dp_clip_accumulate_recompute_batch(bt, bt.ptrs(px), bt.ptrs(pdy), bt.ptrs([sqd.data_ptr()] * 2), bt.floats([1.0, 1.0]),
-                                          bt.ptrs([t.data_ptr() for t in acc]), bt.ptrs([None, None]), addresses=at)
+        px, pdy = [t.data_ptr() for t in xd], [t.data_ptr() for t in dyd]
+
+    def norms():
+        dp.dp_per_example_grad_batch(bt, bt.ptrs(px), bt.ptrs(pdy), None, None, bt.ptrs([t.data_ptr() for t in sq]), addresses=at)
+
+    def sums():
+        dp.dp_clip_accumulate_recompute_batch(bt, bt.ptrs(px), bt.ptrs(pdy), bt.ptrs([sqd.data_ptr()] * 3), bt.floats([1.0] * 3),
+                                              bt.ptrs([t.data_ptr() for t in acc]), bt.ptrs([None] * 3), addresses=at)
+
+    norms()
+    main = launches(sums)
+    if rows:                                       # two layers of whole-row tiles, one workgroup a range of up to sixteen examples
+        groups = (cout // 128) * (cin // 256) * -(-n // 16)
+        assert 2 * -(-groups // 8) * 8 in main, (main, groups)
     torch.cuda.synchronize()
     assert torch.equal(acc[0], acc[1])
     keep = [i for i in range(n) if f[i] != 0.0]
-    g = np.stack([dy[i].reshape(cout, 196).astype(np.float64) @ x[i].reshape(cin, 196).astype(np.float64).T for i in keep])
-    # fp32 sums of 196 products (sqrt(196) 2^-24 = 8e-7), of their squares and of at most 131 scaled blocks
-    for t in sq:
+    g = np.stack([dy[i].reshape(cout, S).astype(np.float64) @ x[i].reshape(cin, S).astype(np.float64).T for i in keep])
+    # fp32 sums of about 200 products (sqrt(204) 2^-24 = 9e-7), of their squares and of at most 131 scaled blocks
+    for t in sq[:2]:
         assert np.allclose(host(t)[keep], (g * g).sum((1, 2)), rtol=1e-5)
     assert_close(host(acc[0]) - 1.0, (f[keep][:, None, None] * g).sum(0).reshape(-1), 1e-5, "increment")
+
+
+# And where the call is too little for ranges of sixteen examples: the layers bring the workgroups that they bring in the other kernel
+@pytest.mark.parametrize("cin,cout,count,n", [(256, 256, 2, 16), (512, 128, 4, 16), (256, 1024, 2, 32), (1024, 256, 2, 4)])
+def test_row_stages_are_left_to_calls_that_fill_the_chip(cin, cout, count, n):
+    call, _kept = _weighted_batch([conv(cin, cout, 1, 1, 14)] * count, n)
+    assert launches(call)[0] >= 32 * count
+
+
+# The ranges' copies of a matrix stay below 96 MB, the ranges get longer instead
+def test_row_stages_keep_their_copies_small():
+    layers = [conv(2048, 1024, 1, 1, 14), conv(512, 512, 3, 1, 14)]
+    n = 240
+    d = dp.make_desc(layers[0], n, "bf16")
+    assert "128x256rows" in dp.dp_kernel_variant(d, dp.DP_WS_RECOMPUTE | dp.DP_VARIANT_SHARED)
+    assert dp.dp_workspace_bytes(d, dp.DP_WS_RECOMPUTE) <= 96_000_000
+    call, (xs, dys, _, sq, acc) = _weighted_batch(layers, n)
+    for t in acc:
+        t.zero_()
+    assert 8 * 8 * 11 in launches(call)            # (fifteen ranges of sixteen would be 126 MB)
+    f = torch.clamp(1.0 / sq.double().sqrt(), max=1.0)
+    x, dy = xs[0].reshape(n, 2048, 196)[:, :8].double(), (dys[0].reshape(n, 1024, 196).double() * f[:, None, None])
+    ref = sum(dy[i] @ x[i].T for i in range(n))
+    assert_close(host(acc[0].reshape(1024, 2048)[:, :8]).reshape(-1), host(ref).reshape(-1), 1e-5, "sum")
 
 
 # Steps of several micro-steps keep no gradients of such layers but the last one's: accumulator against single micro-steps, gradients of the last one whole
@@ -819,7 +875,7 @@ def test_phases_that_others_follow(streams):
     from workloads.configs import Workload
     from workloads.device import make_device_inputs
     layers = (conv(64, 256, 1, 1, 14, name="a"), conv(256, 256, 1, 1, 14, name="b"), conv(256, 256, 3, 1, 14, name="c"), conv(1024, 256, 1, 1, 14, name="d"),
-              dense(64, 12, name="fc"))
+              conv(256, 1024, 1, 1, 14, name="e"), dense(64, 12, name="fc"))
     wl = Workload("rows", layers, 130, 3, "bf16", "per_layer", 1.0, 0.0, tuple("abs" for _ in layers), 0.01, 77)
     inputs = make_device_inputs(wl, wl.accum, torch.device("cuda:0"))
     whole, single = (dp.PrivatiseStep(wl, streams=streams) for _ in range(2))
@@ -840,22 +896,6 @@ def test_phases_that_others_follow(streams):
         whole.replay()
         torch.cuda.synchronize()
         assert torch.equal(whole.acc, first) and torch.equal(whole.g, single.g)
-
-
-def _weighted_batch(layers, n, seed=359):
-    """A clip-weighted batch call of bf16 layers, and what it works on."""
-    gen = torch.Generator(device="cuda:0")
-    gen.manual_seed(seed)
-    descs = [dp.make_desc(l, n, "bf16") for l in layers]
-    xs, dys = ([torch.randn((n,) + tuple(shape), generator=gen, device="cuda:0").bfloat16() for shape in shapes]
-               for shapes in ([l.x_shape for l in layers], [l.dy_shape for l in layers]))
-    ws = [torch.empty(max(16, dp.dp_workspace_bytes(d, dp.DP_WS_RECOMPUTE)), dtype=torch.uint8, device="cuda:0") for d in descs]
-    sq = torch.rand(n, generator=gen, device="cuda:0") + 0.5
-    acc = [torch.zeros(l.pw, device="cuda:0") for l in layers]
-    bt = dp.LayerBatch(descs, [t.data_ptr() for t in ws], [t.numel() for t in ws])
-    args = (bt, bt.ptrs([t.data_ptr() for t in xs]), bt.ptrs([t.data_ptr() for t in dys]), bt.ptrs([sq.data_ptr()] * len(layers)), bt.floats([1.0] * len(layers)),
-            bt.ptrs([t.data_ptr() for t in acc]), bt.ptrs([None] * len(layers)))
-    return (lambda: dp.dp_clip_accumulate_recompute_batch(*args)), (xs, dys, ws, sq, acc)
 
 
 # The clip-weighted 3x3 form in batch calls: layers of few tiles still bring workgroups (up to what whole examples allow); in a full
