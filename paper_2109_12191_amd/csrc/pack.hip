@@ -131,6 +131,11 @@ struct PackStaged {
     unsigned c_blocks, e_blocks;    // workgroups of a range
     unsigned by_ed, by_rp, by_p8, by_taps, by_kw, by_ow;             // divisors as factors (pack_div)
 };
+// It is one more launch, of workgroups that take longer: only where its share of the copies is worth that.  Us of a clip-weighted call, all in the kernel above /
+// so, on both sides of each line.  A layer alone: 128 -> 128 stride 2 on 56 x 56, 8 examples (14 MB) 38 / 43, 16 (29 MB) 50 / 48, 32 (58 MB) 96 / 69; 64 -> 64
+// stride 2 on 80 x 80, 8 (15 MB) 40 / 47, 16 (29 MB) 55 / 49; at two examples and less 13 / 24.  A layer of a batch call, whose others are likely to bring
+// their own: two of 5x5, 16 -> 32 stride 2 on 80 x 80, 8 examples (10 MB each) 57 / 69, 16 (20 MB) 73 / 70; of 64 -> 64 stride 2 on 32 x 32, 64 (19 MB) 76 / 59.
+constexpr size_t PACK_STAGED_ALONE = (size_t)24 << 20, PACK_STAGED_SHARED = (size_t)12 << 20;
 constexpr int PACK_LDS = 12 * 1024, PACK_PLANE = 32 * 1024, PACK_EB = 16;
 
 // x / d for x * d < 2^32; by = ceil(2^32 / d), 0 for d = 1
@@ -444,7 +449,7 @@ static dp_status launch_pack_staged(const Geo &g, const PackPlan &p, const void 
 {
     const int channels = g.cin;
     const int plane = g.h * g.w, taps = g.kh * g.kw, p8 = p.SP / 8;
-    done = plane * 2 <= PACK_PLANE;
+    done = plane * 2 <= PACK_PLANE && (p.x_bytes >= PACK_STAGED_ALONE || (crowd_hint() && p.x_bytes >= PACK_STAGED_SHARED));
     if (!done) return DP_OK;
     PackStaged a;
     a.in = in; a.out = static_cast<uint16_t *>(out);

@@ -743,8 +743,8 @@ def test_conv3x3_weighted_ranges(cin, cout, h, w, n):
     assert_close(got[idx] - 1.0, oracle.weighted_sum_elems(layer, x, dy, f, idx), BF16_TOL, "increment")
 
 
-# Packed operands taken through LDS: planes of odd size and odd channel counts (examples that start between dwords), ranges of examples that are
-# no multiple of a workgroup's, channels that are none either, strides, taps with and without padding, a plane too large for it
+# Packed operands: planes of odd size and odd channel counts (examples that start between dwords), ranges of examples that are
+# no multiple of a workgroup's, channels that are none either, strides, taps with and without padding; small copies, which one launch makes
 @pytest.mark.parametrize("layer,n", [(conv(33, 70, 1, 1, 5), 19), (conv(65, 64, 1, 2, 13), 7), (conv(67, 65, 3, 2, 14), 37), (conv(513, 64, 3, 1, 4), 21),
                                      (conv(40, 33, 3, 1, 9), 5), (conv(64, 64, 3, 2, 8), 257), (Layer("conv", 12, 40, 11, 13, 5, 5, 2, 2, False), 6),
                                      (Layer("conv", 3, 40, 130, 140, 3, 3, 4, 1, False), 3), (Layer("conv", 31, 64, 1, 7, 3, 3, 1, 1, False), 18)],
@@ -752,41 +752,48 @@ def test_conv3x3_weighted_ranges(cin, cout, h, w, n):
 @pytest.mark.parametrize("several", [False, True])
 def test_packed_operands(layer, n, several):
     x, dy = _inputs(layer, n, 347, "bf16")
+    _check_packed(layer, n, several, x, dy)
+
+
+def _check_packed(layer, n, several, x, dy):
+    """The clip-weighted sum of the layer alone, or of two of it in a batch call, against the oracle; how many kernels that takes."""
     rng = np.random.default_rng(43)
     n2 = (rng.uniform(0.3, 2.5, n) ** 2).astype(np.float32)
     f = np.array([oracle.clip_factor(float(v), 1.0) for v in n2])
     idx = rng.choice(layer.pw, size=min(layer.pw, 3000), replace=False)
     ref = oracle.weighted_sum_elems(layer, x, dy, f, idx)
-    if not several:
-        got, _ = _run_weighted(layer, x, dy, "bf16", n2, 1.0)
-    else:
-        d = dp.make_desc(layer, n, "bf16")
-        ws = [torch.empty(max(16, dp.dp_workspace_bytes(d, dp.DP_WS_RECOMPUTE)), dtype=torch.uint8, device="cuda:0") for _ in range(2)]
-        acc = [torch.ones(layer.pw, device="cuda:0") for _ in range(2)]
-        xd, dyd, sq = dev(x, "bf16"), dev(dy, "bf16"), dev(n2)
-        bt = dp.LayerBatch([d, d], [t.data_ptr() for t in ws], [t.numel() for t in ws])
-        dp.dp_clip_accumulate_recompute_batch(bt, bt.ptrs([xd.data_ptr()] * 2), bt.ptrs([dyd.data_ptr()] * 2), bt.ptrs([sq.data_ptr()] * 2), bt.floats([1.0, 1.0]),
-                                              bt.ptrs([t.data_ptr() for t in acc]), bt.ptrs([None, None]))
-        torch.cuda.synchronize()
-        assert torch.equal(acc[0], acc[1])
-        got = host(acc[0])
-    assert_close(got[idx] - 1.0, ref, BF16_TOL, "increment")
+    d, count = dp.make_desc(layer, n, "bf16"), 2 if several else 1
+    ws = [torch.empty(max(16, dp.dp_workspace_bytes(d, dp.DP_WS_RECOMPUTE)), dtype=torch.uint8, device="cuda:0") for _ in range(count)]
+    acc = [torch.ones(layer.pw, device="cuda:0") for _ in range(count)]
+    xd, dyd, sq = dev(x, "bf16"), dev(dy, "bf16"), dev(n2)
+    bt = dp.LayerBatch([d] * count, [t.data_ptr() for t in ws], [t.numel() for t in ws])
+    kernels = launches(lambda: dp.dp_clip_accumulate_recompute_batch(
+        bt, bt.ptrs([xd.data_ptr()] * count), bt.ptrs([dyd.data_ptr()] * count), bt.ptrs([sq.data_ptr()] * count), bt.floats([1.0] * count),
+        bt.ptrs([t.data_ptr() for t in acc]), bt.ptrs([None] * count)))
+    assert torch.equal(acc[0], acc[-1])
+    assert_close(host(acc[0])[idx] - 1.0, ref, BF16_TOL, "increment")
+    return len(kernels)
 
 
-def _weighted_batch(layers, n, seed=359):
-    """A clip-weighted batch call of bf16 layers, and what it works on."""
-    gen = torch.Generator(device="cuda:0")
-    gen.manual_seed(seed)
-    descs = [dp.make_desc(l, n, "bf16") for l in layers]
-    xs, dys = ([torch.randn((n,) + tuple(shape), generator=gen, device="cuda:0").bfloat16() for shape in shapes]
-               for shapes in ([l.x_shape for l in layers], [l.dy_shape for l in layers]))
-    ws = [torch.empty(max(16, dp.dp_workspace_bytes(d, dp.DP_WS_RECOMPUTE)), dtype=torch.uint8, device="cuda:0") for d in descs]
-    sq = torch.rand(n, generator=gen, device="cuda:0") + 0.5
-    acc = [torch.zeros(l.pw, device="cuda:0") for l in layers]
-    bt = dp.LayerBatch(descs, [t.data_ptr() for t in ws], [t.numel() for t in ws])
-    args = (bt, bt.ptrs([t.data_ptr() for t in xs]), bt.ptrs([t.data_ptr() for t in dys]), bt.ptrs([sq.data_ptr()] * len(layers)), bt.floats([1.0] * len(layers)),
-            bt.ptrs([t.data_ptr() for t in acc]), bt.ptrs([None] * len(layers)))
-    return (lambda: dp.dp_clip_accumulate_recompute_batch(*args)), (xs, dys, ws, sq, acc)
+# X taken through LDS, in a launch of its own, where the copies are large: planes of an odd size and odd channel counts, ranges of examples and
+# channels that are no multiple of a workgroup's, planes that only just fit (one channel of one example a workgroup); from 24 MB on for a layer
+# alone, 12 MB in a batch call
+@pytest.mark.parametrize("layer,n", [(conv(67, 65, 3, 2, 14), 401), (conv(513, 64, 3, 1, 4), 181), (conv(40, 33, 3, 1, 9), 421), (Layer("conv", 12, 40, 11, 13, 5, 5, 2, 2, False), 907),
+                                     (conv(64, 64, 3, 2, 8), 1501), (Layer("conv", 23, 40, 80, 101, 3, 3, 2, 1, False), 31), (Layer("conv", 7, 36, 127, 129, 3, 3, 3, 1, False), 111)],
+                         ids=lambda v: str(v) if isinstance(v, int) else f"{v.cin}-{v.cout}-{v.kh}x{v.kw}s{v.stride}-{v.h}x{v.w}")
+def test_packed_operands_through_lds(layer, n):
+    x, dy = _inputs(layer, n, 347, "bf16")
+    copy = 2 * n * layer.cin * layer.kh * layer.kw * ((layer.oh * layer.ow + 7) // 8 * 8)
+    assert (24 << 20) <= copy <= (27 << 20)
+    assert _check_packed(layer, n, False, x, dy) == 4                 # X, dY, the contraction, the sum over ranges
+    half, third = -(-n // 2) + n // 100, n // 3                       # 12 MB a layer; less
+    assert _check_packed(layer, half, False, x[:half], dy[:half]) == 3
+
+    def ranges(examples):                                             # of a batch call of as little work as these
+        return -(-examples * ((layer.oh * layer.ow + 7) // 8 * 8) // (512 if layer.cout > 64 else 2048))
+
+    assert _check_packed(layer, half, True, x[:half], dy[:half]) == 3 + (ranges(half) > 1)
+    assert _check_packed(layer, third, True, x[:third], dy[:third]) == 2 + (ranges(third) > 1)
 
 
 # Layers in batch calls whose rows travel in stages, of 196 and of 204 values (where other waves issue the seventh load of a stage): norm-only (ranges of eight
