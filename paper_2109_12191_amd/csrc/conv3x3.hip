@@ -1010,12 +1010,15 @@ C3Plan c3_plan(const Geo &g, int mode)
     C3Plan p = c3_plan_slices(g, mode);
     if (mode == MODE_WEIGHTED || p.ksplit > 1 || !c3_streams(g.ow, g.stride)) return p;
     // Starting a workgroup costs as much as three stages: one that walks fewer than sixteen takes several rows of results in a row, as long as
-    // two workgroups are left for every compute unit (in a launch that other layers share: a workgroup for every second one)
+    // two workgroups are left for every compute unit (in a launch that other layers share: a workgroup for every second one).  Where they are
+    // stored, at most four: of more the last workgroups' stores are left alone at the end (512 -> 512 at 7 x 7, us for at most 16 / 8 / 4 / 2 / 1: two layers of 48
+    // examples 205 / 189 / 183 / 178 / 187, four of 8 59 / 59 / 59 / 63 / 71, one of 128 249 / 242 / 237 / 233 / 249, of 32 60 / 60 / 60 / 64 / 69).
     const long long stages = (long long)g.unit * ((g.oh + p.stage_rows - 1) / p.stage_rows), rows = g.n / g.unit, tiles = (long long)p.tiles_co * p.tiles_ci;
     long long k = 16 / stages;
     const long long most = rows * tiles / (c3_plan_crowd() ? 128 : 512);
     if (k > most) k = most;
     if (k > rows) k = rows;
+    if (mode == MODE_MATERIALISE && k > 4) k = 4;
     if (k > 1) p.rows_per_wg = (int)k;
     return p;
 }

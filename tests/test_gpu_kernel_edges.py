@@ -686,7 +686,7 @@ def test_units_in_the_fp32_raw_row_kernel(cin, cout, h, w, k, stride, n, unit):
     assert np.allclose(host(norms), host(sq), rtol=F32_TOL)
 
 
-# The bf16 raw-row 3x3 kernel where a workgroup makes several rows of results one after the other: the last group of them short, tiles of few
+# The bf16 raw-row 3x3 kernel where a workgroup makes several rows of results one after the other (up to sixteen, of stored ones four): the last group of them short, tiles of few
 # channels, rows of 7 whose examples start between dwords (odd channels), one stage and several per example, pieces that an
 # example's end cuts.  Alone, from 1024 blocks on; every gradient is compared with a batch call of two layers, whose plan is another one.
 @pytest.mark.parametrize("cin,cout,h,w,stride,n", [(64, 64, 7, 7, 1, 1030), (65, 67, 7, 7, 1, 519), (64, 130, 9, 7, 1, 700), (72, 65, 14, 14, 1, 515),
@@ -702,16 +702,16 @@ def test_conv3x3_rows_of_results_in_a_row(cin, cout, h, w, stride, n):
     dy = (torch.randn((n,) + tuple(layer.dy_shape), generator=gen, device="cuda:0") * 0.05).bfloat16()
     f32 = dict(dtype=torch.float32, device="cuda:0")
 
-    def batch(count):
+    def batch(count, stored=True):
         ws = [torch.empty(max(16, dp.dp_workspace_bytes(d, dp.DP_WS_PER_EXAMPLE_GRAD)), dtype=torch.uint8, device="cuda:0") for _ in range(count)]
-        g = [torch.full((n, (layer.pw + 3) & ~3), 7.0, **f32) for _ in range(count)]
+        g = [torch.full((n, (layer.pw + 3) & ~3), 7.0, **f32) for _ in range(count if stored else 0)]
         sq = [torch.full((n,), -1.0, **f32) for _ in range(count)]
         if count == 1:
-            dp.dp_per_example_grad(d, x, dy, g[0], None, sq[0], ws[0], g_stride=g[0].shape[1])
+            dp.dp_per_example_grad(d, x, dy, g[0] if stored else None, None, sq[0], ws[0], g_stride=g[0].shape[1] if stored else 0)
         else:
             bt = dp.LayerBatch([d] * count, [t.data_ptr() for t in ws], [t.numel() for t in ws])
-            dp.dp_per_example_grad_batch(bt, bt.ptrs([x.data_ptr()] * count), bt.ptrs([dy.data_ptr()] * count), bt.ptrs([t.data_ptr() for t in g]), None,
-                                         bt.ptrs([t.data_ptr() for t in sq]), g_stride=g[0].shape[1])
+            dp.dp_per_example_grad_batch(bt, bt.ptrs([x.data_ptr()] * count), bt.ptrs([dy.data_ptr()] * count), bt.ptrs([t.data_ptr() for t in g]) if stored else None,
+                                         None, bt.ptrs([t.data_ptr() for t in sq]), g_stride=g[0].shape[1] if stored else 0)
         torch.cuda.synchronize()
         return [t[:, :layer.pw] for t in g], sq
 
@@ -722,6 +722,9 @@ def test_conv3x3_rows_of_results_in_a_row(cin, cout, h, w, stride, n):
     assert float((g - a).norm() / g.norm()) < 1e-5 and float((g - a).abs().max() / g.abs().max()) < 1e-5
     assert torch.allclose(sq, sa, rtol=1e-5)
     assert torch.allclose(sq, g.square().sum(1), rtol=1e-4)
+    for count in (1, 2):                           # norms alone (7 x 7 and 8 x 8: from products of rows, in another kernel)
+        for t in batch(count, stored=False)[1]:
+            assert torch.allclose(t, sq, rtol=1e-3 if h * w <= 64 else 1e-5)
     for i in (0, 1, n // 2, n - 2, n - 1):
         ref, _ = oracle.example_grad(layer, host(x[i]), host(dy[i]))
         assert_close(host(g[i]), ref.reshape(-1), F32_TOL, f"example {i}")        # (bf16 products are exact in fp32)
@@ -952,3 +955,16 @@ def test_packed_operands_stay_in_the_workspace(layer, other, n):
     f = np.array([oracle.clip_factor(float(v), 1.0) for v in n2])
     idx = np.random.default_rng(59).choice(layer.pw, size=1000, replace=False)
     assert_close(host(acc[0])[idx], oracle.weighted_sum_elems(layer, *ins[0], f, idx), BF16_TOL, "increment")
+
+
+@pytest.mark.parametrize("count,n,rows", [(2, 48, 4), (1, 128, 4), (4, 8, 4), (1, 16, 2)])
+def test_conv3x3_stored_rows_in_a_row_are_at_most_four(count, n, rows):
+    layer = conv(512, 512, 3, 1, 7)
+    d = dp.make_desc(layer, n, "bf16")
+    x = torch.ones((n,) + tuple(layer.x_shape), dtype=torch.bfloat16, device="cuda:0")
+    ws = [torch.empty(dp.dp_workspace_bytes(d), dtype=torch.uint8, device="cuda:0") for _ in range(count)]
+    g, sq = torch.empty((n, layer.pw), device="cuda:0"), torch.zeros(n, device="cuda:0")
+    bt = dp.LayerBatch([d] * count, [t.data_ptr() for t in ws], [t.numel() for t in ws])
+    main = launches(lambda: dp.dp_per_example_grad_batch(bt, bt.ptrs([x.data_ptr()] * count), bt.ptrs([x.data_ptr()] * count), bt.ptrs([g.data_ptr()] * count), None,
+                                                         bt.ptrs([sq.data_ptr()] * count)))[0]
+    assert main == count * 64 * (n // rows)
