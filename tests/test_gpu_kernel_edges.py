@@ -799,6 +799,22 @@ def test_packed_operands_through_lds(layer, n):
     assert _check_packed(layer, third, True, x[:third], dy[:third]) == 2 + (ranges(third) > 1)
 
 
+def _weighted_batch(layers, n, seed=359):
+    """A clip-weighted batch call of bf16 layers, and what it works on."""
+    gen = torch.Generator(device="cuda:0")
+    gen.manual_seed(seed)
+    descs = [dp.make_desc(l, n, "bf16") for l in layers]
+    xs, dys = ([torch.randn((n,) + tuple(shape), generator=gen, device="cuda:0").bfloat16() for shape in shapes]
+               for shapes in ([l.x_shape for l in layers], [l.dy_shape for l in layers]))
+    ws = [torch.empty(max(16, dp.dp_workspace_bytes(d, dp.DP_WS_RECOMPUTE)), dtype=torch.uint8, device="cuda:0") for d in descs]
+    sq = torch.rand(n, generator=gen, device="cuda:0") + 0.5
+    acc = [torch.zeros(l.pw, device="cuda:0") for l in layers]
+    bt = dp.LayerBatch(descs, [t.data_ptr() for t in ws], [t.numel() for t in ws])
+    args = (bt, bt.ptrs([t.data_ptr() for t in xs]), bt.ptrs([t.data_ptr() for t in dys]), bt.ptrs([sq.data_ptr()] * len(layers)), bt.floats([1.0] * len(layers)),
+            bt.ptrs([t.data_ptr() for t in acc]), bt.ptrs([None] * len(layers)))
+    return (lambda: dp.dp_clip_accumulate_recompute_batch(*args)), (xs, dys, ws, sq, acc)
+
+
 # Layers in batch calls whose rows travel in stages, of 196 and of 204 values (where other waves issue the seventh load of a stage): norm-only (ranges of eight
 # examples, the last one short; from 128 blocks on) and clip-weighted (one range; several of up to sixteen with a sum behind them; twelve examples and a
 # call of enough work, which a third layer stands for), tiles of both matrices' directions, whole tensors and examples by address, an example that is left out
