@@ -2113,9 +2113,7 @@ const char *conv_variant_name(const Geo &g, int mode, bool shared)
         if (gram_norm_applicable(g2, mode)) return "conv_gram_norm<bf16,sampled>";      // (a launch of its own: the others need not wait for the copy)
         ge = g2;
     }
-    FullPlan f = full_plan(ge, mode);
-    // (whole-row layers have one name, stored or not: calls group layers by it, and the library launches what stores and what does not apart)
-    if (f.shape == T128rows && mode != MODE_WEIGHTED) f.shape = T256rows;
+    const FullPlan f = full_plan(ge, mode);
     return names.v[g.bf16 ? 1 : 0][f.shape][mode == MODE_WEIGHTED ? 1 : 0][g.has_bias ? 1 : 0][loader_of(ge)];
 }
 

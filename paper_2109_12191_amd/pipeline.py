@@ -138,7 +138,7 @@ class _Plan:
         by_name = {}
         family = "conv3x3_rows<bf16,all widths,%s>" % ("weighted" if use == 1 else "per_example")
         for li in layer_ids:
-            key = self.variant[li][1 if use == 1 else 0]      # same name, same kernel: storing and norm-only layers share a launch
+            key = self.variant[li][1 if use == 1 else 0]      # same name, same kernel
             if ps.batching == "all":
                 key = "all layers"
             elif key.startswith("conv3x3_rows<"):
@@ -146,16 +146,13 @@ class _Plan:
                 # four kernels run at a time on the chip: the few workgroups of a narrow layer cost none of the
                 # four inside a wide launch), so the family is one batch call
                 key = family
-            elif "256x256rows" in key:
-                # what stores and what does not are launches of their own, which run side by side on streams of their own
-                key += "|" + self.form[li]
             by_name.setdefault(key, []).append(li)
         groups = []
         for key, ids in by_name.items():
             width = len(ids) if (ps.batching == "all" or key == family) else 16
             for k in range(0, len(ids), width):
                 part = ids[k: k + width]
-                name = key.split("|")[0]
+                name = key
                 if len(part) == 1:           # a single layer is planned as a launch of its own
                     name = B.dp_kernel_variant(self.descs[part[0]], self.blocks | (B.DP_WS_RECOMPUTE if use == 1 else (
                         B.DP_WS_PER_EXAMPLE_GRAD | (B.DP_VARIANT_MATERIALISE if self.form[part[0]] == "materialise" else 0))))

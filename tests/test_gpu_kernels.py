@@ -697,13 +697,15 @@ def test_batch_call_matches_the_single_layer_calls_and_the_oracle(n, materialise
 
 @pytest.mark.parametrize("materialise", [False, True])
 def test_batch_call_of_whole_row_blocks_with_a_ragged_last_group_of_examples(materialise):
-    """Two 1x1 layers on 14x14 maps in one batch call: the kernel that moves whole rows in blocks of 32, several examples
-    per workgroup (66 examples: the last group is short), gradients and norms against the oracle."""
+    """Two 1x1 layers on 14x14 maps in one batch call: gradients that are stored come from the kernel that moves whole rows in blocks of 32,
+    norms alone from the one that moves them in stages; several examples per workgroup (66 examples: the last group is short), gradients and norms
+    against the oracle."""
     dtype, n = "bf16", 66
     layers = [conv(256, 512, 1, 1, 14), conv(512, 256, 1, 1, 14)]
     descs = [dp.make_desc(l, n, dtype) for l in layers]
     for d in descs:
-        assert dp.dp_kernel_variant(d, dp.DP_WS_PER_EXAMPLE_GRAD | dp.DP_VARIANT_SHARED) == "conv_contract<bf16,256x256rows,per_example>"
+        name = dp.dp_kernel_variant(d, dp.DP_WS_PER_EXAMPLE_GRAD | dp.DP_VARIANT_SHARED | (dp.DP_VARIANT_MATERIALISE if materialise else 0))
+        assert name == f"conv_contract<bf16,{'256x256rows' if materialise else '128x256rows'},per_example>"
     ins = [_inputs(l, n, 1300 + k, dtype) for k, l in enumerate(layers)]
     xs = [dev(x, dtype) for x, _ in ins]
     dys = [dev(dy, dtype) for _, dy in ins]
