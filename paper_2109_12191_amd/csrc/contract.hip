@@ -1905,8 +1905,8 @@ static bool packed_weighted(const Geo &g, int mode, PackPlan &pp, Geo &g2)
             return (positions + per - 1) / per;
         };
         // Ranges are of equal length, so the last one may be mostly padding (three examples in two ranges take the room of four).  Workspaces are
-        // sized for the smallest target: fewer ranges than it makes must not need more than it does.
-        const size_t reported = bytes(plan(ranges(4)));
+        // sized for the smallest target that a call with this layer can have: fewer ranges than it makes must not need more than it does.
+        const size_t reported = bytes(plan(ranges(crowd_of(conv_macs(g)))));
         if (reported > most) return false;
         long long groups = ranges(crowd);
         while (bytes(pp = plan(groups)) > reported) ++groups;
@@ -2019,8 +2019,9 @@ size_t conv_ws_bytes(const Geo &g, int mode)
 {
     size_t need = 0;
     const int saved = tl_forced_crowd;
-    // a call alone, and a call inside a batch: the smallest target, of which there are most slices, and one that the clip-weighted whole-row kernel is chosen at
-    for (int crowd : {0, 4, 64}) {
+    // a call alone, and a call inside a batch: the smallest target that it can have with this layer, of which there are most slices, and one that the
+    // clip-weighted whole-row kernel is chosen at
+    for (int crowd : {0, mode == MODE_WEIGHTED ? crowd_of(conv_macs(g)) : 4, 64}) {
         tl_forced_crowd = crowd;
         size_t b = conv_ws_bytes_mode(g, mode == MODE_WEIGHTED ? MODE_WEIGHTED : MODE_NORM);
         if (mode != MODE_WEIGHTED) {

@@ -300,3 +300,9 @@ def test_built_in_scratch_takes_dense_layers_by_slots_of_16_by_256(lib, cin, cou
     with pytest.raises(dp.DpError) as ei:                     # (a call that is taken fails at the device or the misaligned pointer)
         dp.dp_per_example_grad_static(d, FAKE + 8, FAKE, None, None, FAKE, stream=0)
     assert (ei.value.status == 3) == (not fits), str(ei.value)
+
+
+def test_clip_weighted_workspaces_are_for_calls_that_there_can_be(lib):
+    """A batch call with this layer has at least the layer's own work: no room for the slices of a smaller one."""
+    d = dp.make_desc(conv(512, 1024, 1, 1, 14), 123, "bf16")
+    assert dp.dp_workspace_bytes(d, dp.DP_WS_RECOMPUTE) == 16 * 512 * 1024 * 4          # sixteen ranges, the call alone
