@@ -102,8 +102,8 @@ size_t dp_bias_count(const dp_layer_desc *desc /*[host]*/);
  * bad descriptor).  What it holds, depending on the layer: partial squared norms (one float
  * per example and output tile, or per slice-sum workgroup), the partial tiles of contractions
  * whose K (or example range) is cut into slices, and rewritten copies of the operands where a
- * kernel reads them in another layout (sampled positions of a strided 1x1 conv, parity-split
- * rows of a strided 3x3 conv, K-contiguous pre-scaled operands of the clip-weighted form);
+ * kernel reads them in another layout (sampled positions of a strided 1x1 conv,
+ * K-contiguous pre-scaled operands of the clip-weighted form);
  * DP_WS_RECOMPUTE of a GroupNorm layer: n*2*cin floats.  From a few KB to a few tens of MB.
  * Partial sums go through the workspace so that reductions run in a fixed order: the same
  * inputs give the same bits on every call.  The contents are scratch: nothing has to be
@@ -163,7 +163,8 @@ dp_status dp_per_example_grad(const dp_layer_desc *desc /*[host]*/, const void *
  * dp_static_scratch_bytes() = 32 MiB per GPU, held from the first call on a GPU until the process ends.
  * Same kernels, same results (bit for bit) as dp_per_example_grad.  The stream's device must be the
  * current device.  A layer whose dp_workspace_bytes(desc, DP_WS_PER_EXAMPLE_GRAD) exceeds the built-in
- * size -> DP_ERR_WORKSPACE (nothing is launched); a dense layer only if 4 n ceil(cin / 256) ceil(cout / 16) bytes do.  Every call on one GPU shares that GPU's array:
+ * size -> DP_ERR_WORKSPACE (nothing is launched); a dense layer only if 4 n ceil(cin / 256) ceil(cout / 16) bytes do; a bf16 3x3 layer of stride 2 that runs in the
+ * raw-row kernel also if they do so with 2 n cin h (16 ceil(ow / 8) + 8) bytes more.  Every call on one GPU shares that GPU's array:
  * calls that overlap in time on one GPU (different streams, different host threads) race; issue them
  * on one stream, or order them with events.  Nothing in the array has to start at zero or survive
  * between calls.  Calls no hipMalloc / hipFree or other allocating routine.                        */

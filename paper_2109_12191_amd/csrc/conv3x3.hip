@@ -923,15 +923,6 @@ int rows_of_width(int ow, int stride)
     return owp == 8 ? 8 : 224 / owp;
 }
 
-// The stride-2 form needs no copy of X (it once read one with rows split by column parity).  What is reported stays: callers size buffers
-// by it, and the entry point with built-in scratch refuses layers by it.
-size_t c3_reported_copy(const Geo &g)
-{
-    if (g.stride != 2) return 0;
-    const int owp = (g.ow + 7) / 8 * 8;
-    return ((size_t)g.n * g.cin * g.h * (2 * owp + 8) * sizeof(uint16_t) + 15) & ~(size_t)15;
-}
-
 // plans inside a batch call (the launch is shared with other layers) differ; workspace sizes cover both
 thread_local int c3_forced_crowd = -1;
 int c3_plan_crowd() { return c3_forced_crowd >= 0 ? c3_forced_crowd : crowd_hint(); }
@@ -1111,15 +1102,23 @@ size_t conv3x3_ws_bytes(const Geo &g, int mode)
     return alone > shared ? alone : shared;
 }
 
+// What the layers are counted with that the entry point with built-in scratch takes: layers of stride 2 with a copy of X besides, its rows split by
+// column parity, that their kernel once read.
+size_t conv3x3_scratch_bytes(const Geo &g)
+{
+    const size_t columns = 2 * (size_t)((g.ow + 7) / 8 * 8) + 8;
+    return conv3x3_ws_bytes(g, MODE_MATERIALISE) + (g.stride == 2 ? c3_align16((size_t)g.n * g.cin * g.h * columns * sizeof(uint16_t)) : 0);
+}
+
 static size_t conv3x3_ws_bytes_plan(const Geo &g, int mode)
 {
     const C3Plan p = c3_plan(g, mode);
     const size_t tiles = (size_t)p.tiles_co * p.tiles_ci;
-    if (mode == MODE_WEIGHTED) return c3_reported_copy(g) + (p.ksplit > 1 ? tiles * p.ksplit * 9 * 16 * C3_THREADS * sizeof(float) : 0);
+    if (mode == MODE_WEIGHTED) return p.ksplit > 1 ? tiles * p.ksplit * 9 * 16 * C3_THREADS * sizeof(float) : 0;
     const size_t units = (size_t)(g.n / g.unit) * tiles;
     size_t b = c3_align16(units * c3_partials_per_unit(p) * sizeof(float));
     if (p.ksplit > 1) b += units * p.ksplit * 9 * 16 * C3_THREADS * sizeof(float);
-    return b + c3_reported_copy(g);
+    return b;
 }
 
 size_t conv3x3_norm_partial_count(const Geo &g)

@@ -60,6 +60,7 @@ dp_status launch_conv(const Geo &g, int mode, const void *x, const void *dy, flo
 bool conv_scales_blocks(const Geo &g);
 bool conv3x3_applicable(const Geo &g, int mode);
 size_t conv3x3_ws_bytes(const Geo &g, int mode);
+size_t conv3x3_scratch_bytes(const Geo &g);
 const char *conv3x3_variant_name(const Geo &g, int mode);
 dp_status launch_conv3x3(const Geo &g, int mode, const void *x, const void *dy, float *out_w, size_t out_stride,
                          float *sqnorm, const float *group_sqnorm, float clip_c, void *ws, hipStream_t s);

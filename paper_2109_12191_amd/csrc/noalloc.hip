@@ -45,11 +45,13 @@ size_t dp_static_scratch_bytes(void) { return SCRATCH_BYTES; }
 dp_status dp_per_example_grad_static(const dp_layer_desc *desc, const void *x, const void *dy, float *g_w, float *g_b,
                                      size_t g_stride, float *sqnorm, dp_stream stream)
 {
-    const size_t need = dp_workspace_bytes(desc, DP_WS_PER_EXAMPLE_GRAD);     // 0 on a bad descriptor: reported below
+    size_t need = dp_workspace_bytes(desc, DP_WS_PER_EXAMPLE_GRAD);           // 0 on a bad descriptor: reported below
     // A dense layer of several tokens may need more (a slot for every 64 x 64 of the gradient) than what decides whether it is
     // taken: then its examples go through the scratch a piece at a time, which changes none of their numbers.
     int piece = need ? desc->n : 0;
     dp::Geo g;
+    if (need && dp::make_geo(desc, g) == DP_OK && g.kind == DP_CONV2D && dp::conv3x3_applicable(g, dp::MODE_MATERIALISE) && dp::conv3x3_scratch_bytes(g) > need)
+        need = dp::conv3x3_scratch_bytes(g);
     if (need > SCRATCH_BYTES && dp::make_geo(desc, g) == DP_OK && g.kind == DP_DENSE && dp::dense_scratch_bytes(g) <= SCRATCH_BYTES)
         piece = (int)(SCRATCH_BYTES / (need / (size_t)desc->n)) & ~7;          // (eight examples keep every address 16-byte aligned)
     if (need > SCRATCH_BYTES && (piece == desc->n || piece < 8))

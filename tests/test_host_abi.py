@@ -302,6 +302,22 @@ def test_built_in_scratch_takes_dense_layers_by_slots_of_16_by_256(lib, cin, cou
     assert (ei.value.status == 3) == (not fits), str(ei.value)
 
 
+@pytest.mark.parametrize("cin,cout,hw,n,fits", [(512, 512, 14, 97, True), (512, 512, 14, 98, False), (128, 192, 28, 117, True), (128, 192, 28, 118, False)])
+def test_strided_3x3_layers_ask_for_what_they_use(lib, cin, cout, hw, n, fits):
+    """Partial norms, no room for another form of X.  The entry point with built-in scratch takes the layers that it took when there was one."""
+    d = dp.make_desc(conv(cin, cout, 3, 2, hw), n, "bf16")
+    assert dp.dp_kernel_variant(d, dp.DP_WS_PER_EXAMPLE_GRAD | dp.DP_VARIANT_MATERIALISE) == f"conv3x3_rows<bf16,w{hw // 2},s2,per_example>"
+    partials = (4 * n * (cin // 64) * (cout // 64) + 15) // 16 * 16
+    copy = 2 * n * cin * hw * (16 * -(-hw // 16) + 8)
+    if hw > 14:                                               # (on 7 x 7 norms alone take another route, with its own workspace)
+        assert dp.dp_workspace_bytes(d) == partials
+    assert dp.dp_workspace_bytes(d) < copy + partials
+    assert (copy + partials <= dp.dp_static_scratch_bytes()) == fits
+    with pytest.raises(dp.DpError) as ei:                     # (a call that is taken fails at the device or the misaligned pointer)
+        dp.dp_per_example_grad_static(d, FAKE + 8, FAKE, None, None, FAKE, stream=0)
+    assert (ei.value.status == 3) == (not fits), str(ei.value)
+
+
 def test_clip_weighted_workspaces_are_for_calls_that_there_can_be(lib):
     """A batch call with this layer has at least the layer's own work: no room for the slices of a smaller one."""
     d = dp.make_desc(conv(512, 1024, 1, 1, 14), 123, "bf16")
