@@ -789,7 +789,7 @@ enum { C3_ANY_56_SLICED = 0, C3_ANY_28_SLICED, C3_ANY_28_FULL, C3_ANY_14_FULL, C
 constexpr bool c3_any_in_set(int variant, int set)
 {
     if (variant < 0) return false;
-    return set == 1 || variant <= C3_ANY_7S2_FULL || variant >= C3_ANY_28S2_FULL;
+    return set == 1 || variant <= C3_ANY_7S2_FULL;
 }
 
 template <int SET>
@@ -1073,13 +1073,12 @@ bool conv3x3_applicable(const Geo &g, int mode)
         default: return false;
         }
     } else if (g.stride == 2) {
-        // even images only (rows split by column parity, output exactly half the size)
+        // even images only (a row of dY meets two whole rows of X), and the widths and forms that there are bodies for
         if (g.h % 2 || g.w % 2 || g.oh * 2 != g.h || g.ow * 2 != g.w) return false;
-        // measured: worthwhile for the per-example calls on 14- and 7-wide outputs, and on 28-wide ones (chunks of
-        // three rows) once a micro-step holds more than two examples: the layer then rides in the launch of the other
-        // 3x3 layers (+ 0.4 % for the step; - 0.9 % with one example per micro-step); the clip-weighted form does
-        // better in the general kernel / on packed operands
         if (mode == MODE_WEIGHTED || (g.ow != 7 && g.ow != 14 && g.ow != 28)) return false;
+        // Calls of one and two examples onto 28 columns stay with the kernel that gathers its operands, although this one is faster there by now (us, gathered /
+        // this: two layers of 128 -> 128, one example 25 / 21, two 28 / 26, alone 20 / 21; ResNet-50, sixteen micro-steps of one example by themselves
+        // 3270 / 3087): its slices take up to twice the workspace, and the entry point with built-in scratch would refuse layers that it takes.
         if (g.ow == 28 && g.n <= 2) return false;
     } else {
         return false;
