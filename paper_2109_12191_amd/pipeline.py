@@ -93,7 +93,7 @@ class _Plan:
         self.form = ps._forms(tensors, more)
         self.blocks = ps._blocks(tensors)
         L = len(self.layers)
-        self.descs, need = ps._workspaces(tensors, more)
+        self.descs, need = ps._workspaces(tensors)
         self.g = [st.g[: self.rows] if st.g is not None else None for st in stores]
         self.off_w, self.off_b, self.p_mat = ps.off_w, ps.off_b, ps.p_mat
         free = [None] * len(stores)
@@ -330,6 +330,7 @@ class PrivatiseStep:
         self._last = 0                           # the most recent one
         self._g_last = None                      # the stored gradients among them, and the plan that they were stored by
         self._g_plan = None
+        self._not_stored = None                  # phase and inputs of a last micro-step whose gradients are not all stored (within a step)
         self.graph = None
         self.micro_steps_done = 0
         # Optimiser-step counter: the `step` word of the Philox counters.  The kernels read it from a device
@@ -428,7 +429,7 @@ class PrivatiseStep:
         groups = [self.group_of_layer[i] for i in runs]
         return B.SegmentTable([off_w[i] for i in runs], groups, [self.group_clip[k] for k in groups], [self.off_w[i] for i in runs])
 
-    def _workspaces(self, tensors: int, more: bool = False):
+    def _workspaces(self, tensors: int):
         """Descriptors and workspace bytes of every layer in a phase of `tensors` micro-steps (the same whether others follow)."""
         if tensors not in self._needs:
             descs = [B.make_desc(l, self.wl.n * tensors, self.wl.dtype) for l in self.layers]
@@ -721,12 +722,9 @@ class PrivatiseStep:
                 ev.record(st)
                 evs.append(ev)
             store.done = evs
-        if ends_step and plan.form is not self.form:
-            skip = 8 * (plan.n - self.n)           # entries of the tables before the last micro-step's examples
-            for grp in self._last_plan(plan.form).groups_a:
-                bt = grp["batch"][0]
-                B.dp_per_example_grad_batch(bt, bt.fill("x", [x[i] + skip for i in grp["layers"]]), bt.fill("dy", [dy[i] + skip for i in grp["layers"]]),
-                                            grp["gw"][0], grp["gb"][0], None, g_stride=self.p_mat, stream=ms, addresses=True)
+        self._not_stored = (plan, x, dy) if plan.form is not self.form else None
+        if ends_step:
+            self._store_last()
         for k in range(max(0, plan.tensors - self.copies), plan.tensors):
             self._last = (self.micro_steps_done + k) % self.copies
             self._group_sqnorm[self._last] = gsq[:, k * self.rows:(k + 1) * self.rows]
@@ -737,6 +735,19 @@ class PrivatiseStep:
         self._g_last, self._g_plan = g_buf[-self.rows:] if g_buf is not None else None, plan
         self.micro_steps_done += plan.tensors
         self._phases += 1
+
+    def _store_last(self):
+        """The gradients of the last micro-step's layers that the last phase did not store."""
+        if self._not_stored is None:
+            return
+        plan, x, dy = self._not_stored
+        self._not_stored = None
+        at = plan.tensors > 1
+        skip = 8 * (plan.n - self.n) if at else 0      # entries of the tables before the last micro-step's examples
+        for grp in self._last_plan(plan.form).groups_a:
+            bt = grp["batch"][0]
+            B.dp_per_example_grad_batch(bt, bt.fill("x", [x[i] + skip for i in grp["layers"]]), bt.fill("dy", [dy[i] + skip for i in grp["layers"]]),
+                                        grp["gw"][0], grp["gb"][0], None, g_stride=self.p_mat, stream=torch.cuda.current_stream().cuda_stream, addresses=at)
 
     def _example_noise(self, plan: _Plan, li: int, st: int):
         """Per-example noise of this phase's examples for the tensors of layer li, on the stream that
@@ -799,7 +810,14 @@ class PrivatiseStep:
         return self._addresses[1]
 
     def _issue_step(self, steps: Sequence[Sequence], table: Optional[torch.Tensor] = None):
-        """Every micro-step of a step, several at a time where they are small (`table`: addresses already written)."""
+        """Every micro-step of a step, several at a time where they are small (`table`: addresses already written).  A step that is broken off
+        leaves the gradients of its last micro-step behind whole."""
+        try:
+            self._issue_phases(steps, table)
+        finally:
+            self._store_last()
+
+    def _issue_phases(self, steps: Sequence[Sequence], table: Optional[torch.Tensor]):
         sizes = self._phase_sizes(len(steps))
         if max(sizes) <= 1:
             for k, inputs in enumerate(steps):

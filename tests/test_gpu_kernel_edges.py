@@ -922,6 +922,13 @@ def test_phases_that_others_follow(streams):
         whole.replay()
         torch.cuda.synchronize()
         assert torch.equal(whole.acc, first) and torch.equal(whole.g, single.g)
+    # broken off behind a phase that stored less
+    with pytest.raises(IndexError):
+        whole.run([*inputs[:2], []])
+    single.begin_step()
+    single.micro_step(inputs[1])
+    torch.cuda.synchronize()
+    assert whole.micro_steps_done == 2 and torch.equal(whole.g, single.g)
 
 
 # The clip-weighted 3x3 form in batch calls: layers of few tiles still bring workgroups (up to what whole examples allow); in a full

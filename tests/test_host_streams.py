@@ -11,7 +11,8 @@ import torch
 
 import paper_2109_12191_amd as dp
 from paper_2109_12191_amd import pipeline
-from workloads import get_workload
+from workloads import conv, get_workload
+from workloads.configs import Workload
 
 
 class _Order:
@@ -408,3 +409,60 @@ def test_last_gradients_that_a_phase_does_not_store_are_stored_apart(order, monk
         order.call(order.main, [(apart.data_ptr(), apart.data_ptr() + 4 * apart.numel())], what="a reader")
     assert ps.g.data_ptr() == apart.data_ptr() and ps.g.shape == (1, ps.p_mat)
     assert not order.clashes and order.ring(order.main) is None
+
+
+def _rows_workload(n, accum):
+    """Two layers whose gradients phases that others follow do not store, one whose they do."""
+    layers = (conv(1024, 256, 1, 1, 14, name="a"), conv(64, 64, 3, 1, 14, name="b"), conv(256, 1024, 1, 1, 14, name="c"))
+    return Workload("rows", layers, n, accum, "bf16", "per_layer", 1.0, 0.0, ("abs",) * 3, 0.01, 77)
+
+
+@pytest.mark.parametrize("noise", ["once", "per_example"])
+@pytest.mark.parametrize("sizes,streams", [([1, 1, 1], 8), ([2, 2, 1], 8), ([3, 2], 3), ([2, 2, 1], 1)])
+def test_calls_are_ordered_where_phases_that_others_follow_store_less(order, monkeypatch, sizes, streams, noise):
+    """The last phase's plan is another one, of another division of the matrix; steps of another length and single micro-steps in between."""
+    monkeypatch.setattr(pipeline.PrivatiseStep, "_micro_steps_together", lambda self: sizes[0])
+    wl = _rows_workload(140, sum(sizes))
+    ps = dp.PrivatiseStep(wl, device="cpu", streams=streams, noise=noise)
+    lean, last = ps._plan(sizes[0], True), ps._plan(sizes[-1])
+    assert lean.form == ["recompute", "materialise", "recompute"] and last.form is ps.form and lean.p_mat < last.p_mat == ps.p_mat
+    for steps in (sum(sizes), sum(sizes), 1, 2 * sum(sizes) - 1):
+        ps.run(_steps(wl, steps))
+        assert ps._g_plan.form is ps.form and ps.micro_steps_done == steps
+    ps.begin_step()
+    for inputs in _steps(wl, 3):
+        ps.micro_step(inputs)
+    ps.finalize()
+    ps.run(_steps(wl, sum(sizes)))
+    assert not order.clashes, (len(order.clashes), order.clashes[:4])
+    assert order.ring(order.main) is None
+
+
+@pytest.mark.parametrize("streams", [1, 4])
+@pytest.mark.parametrize("name,sizes,phase", [("rows", [1, 1, 1], 2), ("rows", [2, 2, 1], 1), ("resnet50_nano", [5, 4], 1)])
+def test_a_step_that_is_broken_off_leaves_the_last_gradients_whole(order, monkeypatch, name, sizes, phase, streams):
+    """What the last phase before that did not store is stored then, apart, and the current stream comes after it."""
+    monkeypatch.setattr(pipeline.PrivatiseStep, "_micro_steps_together", lambda self: sizes[0])
+    wl = _rows_workload(140, sum(sizes)) if name == "rows" else get_workload(name, accum=sum(sizes), hw=64)
+    ps = dp.PrivatiseStep(wl, device="cpu", streams=streams)
+    norms, writes, call = [], [], pipeline.B.dp_per_example_grad_batch
+
+    def broken(*args, **kw):
+        norms.append(1)
+        if len(norms) > phase:
+            raise KeyboardInterrupt
+
+    def seen(bt, x, dy, g_w, *rest, **kw):
+        writes.extend(p for p in _addresses(g_w or []) if p)
+        call(bt, x, dy, g_w, *rest, **kw)
+
+    monkeypatch.setattr(pipeline.B, "dp_norms_from_partials", broken)
+    monkeypatch.setattr(pipeline.B, "dp_per_example_grad_batch", seen)
+    with pytest.raises(KeyboardInterrupt):
+        ps.run(_steps(wl, sum(sizes)))
+    apart, form = ps._last_store.g, ps._plan(sizes[phase - 1], True).form
+    assert form.count("recompute") >= 2
+    for i, f in enumerate(form):
+        assert writes.count(apart.data_ptr() + 4 * ps.off_w[i]) == (f != ps.form[i])
+    order.call(order.main, [(apart.data_ptr(), apart.data_ptr() + 4 * apart.numel())], what="a reader")
+    assert ps.g.data_ptr() == apart.data_ptr() and ps.g.shape == (ps.rows, ps.p_mat) and ps._not_stored is None
