@@ -292,7 +292,7 @@ def main():
     # gradients written and read back where they are materialised, the accumulator read and written by every clipped
     # sum, finalize) over the measured step time.
     # (micro-steps issued together add to the accumulator once; phases that others follow may store fewer layers than the last one)
-    sizes, forms = ps._phase_sizes(wl.accum), ps._main.form
+    sizes, forms = ps._phase_sizes(wl.accum), []
     step_bytes, step_flops = 8.0 * wl.n_params, 0.0
     for k, size in enumerate(sizes):
         plan = ps._plan(size, k + 1 < len(sizes))
@@ -301,6 +301,11 @@ def main():
         step_bytes += (sum(w[1] for w in plan.work) + sum(l.in_bytes(esize) * plan.n for l, r in zip(wl.layers, again) if r)
                        + 4.0 * plan.rows * stored + 8.0 * wl.n_params)
         step_flops += sum(w[0] * (1 + r) for w, r in zip(plan.work, again))
+        counts = {f: plan.form.count(f) for f in sorted(set(plan.form))}
+        if forms and all(forms[-1].get(f, 0) == counts.get(f, 0) for f in ("materialise", "recompute")):
+            forms[-1]["phases"] += 1
+        else:
+            forms.append({"phases": 1, **counts})
     step_sec = elapsed / args.steps
     if roofline is not None:
         roofline["whole_step"] = dict(algorithmic_bytes=step_bytes, algorithmic_flop=step_flops, GBps=step_bytes / step_sec / 1e9,
@@ -322,7 +327,7 @@ def main():
                                f"{wl.accum} accumulation = {wl.total_batch} examples/step, {wl.clip_mode} clipping "
                                f"C={wl.clip_c}, sigma={wl.sigma}, {wl.dtype} inputs, fp32 accumulators"
                                + (f", clipping units of {args.clip_unit} examples" if args.clip_unit > 1 else ""),
-                   "clipped_sum_forms": {f: forms.count(f) for f in sorted(set(forms))},
+                   "clipped_sum_forms": forms,
                    "issue": "host calls" if args.no_graph else f"HIP graph, {args.streams} side streams",
                    "finalize": "noise + SGD-momentum update fused" if args.fused_update else "noise + divide by |B|",
                    "noise_form": args.noise,
