@@ -13,11 +13,15 @@
 //     16-byte read of X, two of dY (the third is the first one of the pair before) and eight funnel shifts.  Stride 2: the even and the odd
 //     columns of two rows of X are put together by byte permutes, 24 for nine MFMAs.  What lies outside the image is zeros: a row is
 //     read from a few bytes of zeros, columns behind a row's end are cleared in registers, the column before it is a zero shifted in.
+//     Zeros times what is not finite are no numbers.  Which rows lie outside decides where that shows in an example whose norm is not finite either way: a value of X
+//     in the first (stride 1) or last row that is not finite makes the taps kh = 2 or kh = 0 of its channel NaN, which do not read it (they meet zeros of dY); one of
+//     dY there leaves the taps alone that do not read it (no row of X above the image is walked, below it one where the height is odd).  Clearing X for those taps instead
+//     costs 24 instructions for nine MFMAs in the rows concerned: 2-9 % of this kernel, ResNet-50's step of 8 x 32 6455 -> 6530 us.
 //   * a workgroup that is done with a row of results (an example's, or a clipping unit's) stores it and goes on with the next one, whose rows
 //     are on their way meanwhile.
 //
-// Bound by the matrix units, at the clock that they leave the chip, where two workgroups share a compute unit (85 % of the cycles of a stage are
-// MFMAs); by the stores where blocks are stored and K is short.  One call, us and TFLOP/s, before (rows staged through registers, nine operands
+// Bound by the matrix units where two workgroups share a compute unit (the best calls below reach 900-950 TFLOP/s of dense bf16's 2500; a whole launch of
+// ResNet-50's layers, whose 56-wide ones leave the chip half empty, 670); by the stores where blocks are stored and K is short.  One call, us and TFLOP/s, before (rows staged through registers, nine operands
 // built from three rows of X per K step: 13-25 vector instructions per MFMA) and now: 64 -> 64 at 56 x 56, 128 examples, 135 (219) -> 48 (616);
 // 128 -> 128 at 28 x 28, 128, 56 (532) -> 33 (899); 256 -> 256 at 14 x 14, 256, 93 (634) -> 68 (866), stored 185 -> 156 (3.9 TB/s), clip-weighted
 // 142 (416) -> 96 (616); 128 -> 128 at 16 x 16, 256, 47 (415) -> 20 (947); 128 -> 128 stride 2 onto 28 x 28, 64, 76 (195) -> 27 (559).

@@ -991,3 +991,24 @@ def test_conv3x3_stored_rows_in_a_row_are_at_most_four(count, n, rows):
     main = launches(lambda: dp.dp_per_example_grad_batch(bt, bt.ptrs([x.data_ptr()] * count), bt.ptrs([x.data_ptr()] * count), bt.ptrs([g.data_ptr()] * count), None,
                                                          bt.ptrs([sq.data_ptr()] * count)))[0]
     assert main == count * 64 * (n // rows)
+
+
+# Values of X in the first and last row that are not finite stay with their example and their input channels
+@pytest.mark.parametrize("w,stride", [(7, 1), (8, 1), (14, 1), (28, 1), (56, 1), (28, 2), (14, 2)])
+def test_conv3x3_keeps_what_is_not_finite_in_its_example_and_channel(w, stride):
+    layer, n, rng = conv(64, 64, 3, stride, w), 5, np.random.default_rng(61)
+    x, dy = _inputs(layer, n, 373, "bf16")
+    clean_w, _, clean_sq = _run_per_example(layer, x, dy, "bf16")
+    for row, channel, value in ((0, 3, np.inf), (w - 1, 40, np.nan)):
+        x[2, channel, row, rng.integers(w)] = value
+    d = dp.make_desc(layer, n, "bf16")
+    ws = torch.empty(dp.dp_workspace_bytes(d), dtype=torch.uint8, device="cuda:0")
+    g, sq = torch.zeros((n, layer.pw), device="cuda:0"), torch.zeros(n, device="cuda:0")
+    dp.dp_per_example_grad(d, dev(x, "bf16"), dev(dy, "bf16"), g, None, sq, ws)
+    g, sq = g.cpu().numpy().reshape(n, 64, 64, 9), sq.cpu().numpy()
+    keep = [0, 1, 3, 4]
+    assert np.array_equal(g[keep], clean_w.reshape(n, 64, 64, 9)[keep]) and np.array_equal(sq[keep], clean_sq[keep]) and not np.isfinite(sq[2])
+    others = [c for c in range(64) if c not in (3, 40)]
+    assert np.array_equal(g[2][:, others], clean_w.reshape(n, 64, 64, 9)[2][:, others])
+    # the centre row of taps reads both values; what does not read them is no number or what it was
+    assert not np.isfinite(g[2][:, (3, 40), 3:6]).all(axis=(1, 2)).any()
