@@ -931,6 +931,35 @@ def test_phases_that_others_follow(streams):
     assert whole.micro_steps_done == 2 and torch.equal(whole.g, single.g)
 
 
+# The same with noise for every example, with momentum, with one bound for all layers, phases of several micro-steps whose last one is shorter, and steps of other
+# lengths in between, against single micro-steps: the same blocks and the same deviates, added in another order
+@pytest.mark.parametrize("n,together,noise,clip", [(140, 1, "per_example", "per_layer"), (60, 3, "once", "global"), (70, 2, "per_example", "global")])
+@pytest.mark.parametrize("streams", [1, 4])
+def test_phases_that_others_follow_in_steps_of_any_length(monkeypatch, n, together, noise, clip, streams):
+    from workloads.configs import Workload
+    from workloads.device import make_device_inputs
+    layers = (conv(1024, 256, 1, 1, 14, name="a"), conv(64, 64, 3, 1, 14, name="b"), conv(256, 1024, 1, 1, 14, name="c"), gn_affine(32, 14, 4))
+    wl = Workload("rows", layers, n, 5, "bf16", clip, 1.0, 0.5, tuple("normal" for _ in layers), 0.01, 79, philox_seed=5)
+    inputs = make_device_inputs(wl, wl.accum, torch.device("cuda:0"))
+    single = dp.PrivatiseStep(wl, noise=noise)
+    monkeypatch.setattr(dp.PrivatiseStep, "_micro_steps_together", lambda self: together)
+    whole = dp.PrivatiseStep(wl, streams=streams, noise=noise)
+    assert whole._plan(together, True).form.count("recompute") >= 2 and whole._plan(together, True).p_mat < whole.p_mat
+    for ps in (whole, single):
+        ps.enable_update(lr=0.1, momentum=0.9)
+    for length in (5, 2, 1, 5, 4):
+        whole.run(inputs[:length])
+        single.begin_step()
+        for step in inputs[:length]:
+            single.micro_step(step)
+        single.finalize()
+        torch.cuda.synchronize()
+        assert torch.allclose(whole.g, single.g, rtol=1e-5, atol=1e-5 * float(single.g.abs().max()))
+        for got, want, what in ((whole.acc, single.acc, "accumulator"), (whole.group_sqnorm, single.group_sqnorm, "norms"), (whole.out, single.out, "gradient"),
+                                (whole.theta, single.theta, "parameters"), (whole.velocity, single.velocity, "momentum")):
+            assert_close(host(got), host(want), 1e-5, f"{what}, {length} micro-steps")
+
+
 # The clip-weighted 3x3 form in batch calls: layers of few tiles still bring workgroups (up to what whole examples allow); in a full
 # launch a tile is one workgroup, without slice sums
 @pytest.mark.parametrize("layers,n,least", [([conv(64, 64, 3, 1, 14)] * 2, 48, 48), ([conv(64, 64, 3, 1, 28)] * 2, 32, 64), ([conv(64, 64, 3, 1, 7)] * 2, 128, 64),
