@@ -136,6 +136,9 @@ struct PackStaged {
 // stride 2 on 80 x 80, 8 (15 MB) 40 / 47, 16 (29 MB) 55 / 49; at two examples and less 13 / 24.  A layer of a batch call, whose others are likely to bring
 // their own: two of 5x5, 16 -> 32 stride 2 on 80 x 80, 8 examples (10 MB each) 57 / 69, 16 (20 MB) 73 / 70; of 64 -> 64 stride 2 on 32 x 32, 64 (19 MB) 76 / 59.
 constexpr size_t PACK_STAGED_ALONE = (size_t)24 << 20, PACK_STAGED_SHARED = (size_t)12 << 20;
+// And where that makes a workgroup for every compute unit: few large planes do not.  The first convolution (3 -> 64 7x7 stride 2 on 112 x 112: a workgroup a
+// plane, each of which writes 300 KB), alone, 48 examples, 82 / 130 us; in a batch call with another layer, 16 examples, 75 / 146.
+constexpr unsigned PACK_STAGED_BLOCKS = 256;
 constexpr int PACK_LDS = 12 * 1024, PACK_PLANE = 32 * 1024, PACK_EB = 16;
 
 // x / d for x * d < 2^32; by = ceil(2^32 / d), 0 for d = 1
@@ -472,6 +475,7 @@ static dp_status launch_pack_staged(const Geo &g, const PackPlan &p, const void 
     const unsigned long long most = (unsigned long long)cb * taps * rp;
     if ((unsigned long long)eb * ed * ed >= (1ull << 32) || most * rp >= (1ull << 32)) { done = false; return DP_OK; }
     const unsigned long long blocks = (unsigned long long)p.groups * a.c_blocks * a.e_blocks;
+    if (blocks < PACK_STAGED_BLOCKS) { done = false; return DP_OK; }
     if (blocks > 0x7FFFFFFFull) return fail(DP_ERR_UNSUPPORTED, "pack: layer too large");
     // (layers share a launch if they ask for the same LDS; a piece is read from up to five dwords, which may lie behind the planes)
     return submit_kernel<PackStaged>(TIER_PRE, reinterpret_cast<const void *>(&pack_staged_kernel), a, (unsigned)blocks, 256,

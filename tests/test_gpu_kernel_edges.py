@@ -986,6 +986,15 @@ def test_conv3x3_weighted_batches_of_a_full_launch_walk_one_range():
     assert launches(call) == [5 * 16 + 2 * 64]
 
 
+# Few large planes stay in the launch that packs both operands
+@pytest.mark.parametrize("count", [1, 2])
+def test_packed_planes_that_are_few_share_a_launch(count):
+    layer, n = Layer("conv", 3, 64, 112, 112, 7, 7, 2, 3, False), 36
+    call, _kept = _weighted_batch([layer] * count, n)
+    assert launches(call)[0] > 10000               # a thread for every eight values of both operands
+    assert len(launches(call)) == 3                # the contraction and the sum over ranges
+
+
 # Packed operands in a batch call whose target makes ranges that the number of examples is no multiple of (here two of two for three examples):
 # everything stays inside the workspace that was asked for
 @pytest.mark.parametrize("layer,other,n", [(Layer("conv", 176, 64, 46, 46, 3, 3, 1, 1, False), conv(512, 512, 3, 1, 28), 3),
