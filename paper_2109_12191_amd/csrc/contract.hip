@@ -1905,11 +1905,19 @@ static bool packed_weighted(const Geo &g, int mode, PackPlan &pp, Geo &g2)
             return (positions + per - 1) / per;
         };
         // Ranges are of equal length, so the last one may be mostly padding (three examples in two ranges take the room of four).  Workspaces are
-        // sized for the smallest target that a call with this layer can have: fewer ranges than it makes must not need more than it does.
+        // sized for the smallest target that a call with this layer can have: fewer ranges than it makes must not need more than it does.  The next number of
+        // ranges on either side that does not: the one that leaves the shorter walk (full_plan deals them to workgroups once more).
         const size_t reported = bytes(plan(ranges(crowd_of(conv_macs(g)))));
         if (reported > most) return false;
-        long long groups = ranges(crowd);
-        while (bytes(pp = plan(groups)) > reported) ++groups;
+        long long more = ranges(crowd), fewer = more;
+        while (bytes(plan(more)) > reported) ++more;
+        while (bytes(plan(fewer)) > reported) --fewer;             // (one range has no padding)
+        auto walk = [&](const PackPlan &p) {
+            const long long chunks = ((long long)p.kg + 63) / 64, per = (long long)2 * crowd * (shape == T64 ? 4 : 1);
+            const long long want = std::max(1ll, std::min((long long)p.groups, (p.groups * chunks + per - 1) / per));
+            return (p.groups + want - 1) / want * chunks;
+        };
+        pp = walk(plan(more)) < walk(plan(fewer)) ? plan(more) : plan(fewer);
     } else {
         pp = plan((256 + tiles - 1) / tiles);
         if (bytes(pp) > most) return false;

@@ -995,6 +995,12 @@ def test_packed_planes_that_are_few_share_a_launch(count):
     assert len(launches(call)) == 3                # the contraction and the sum over ranges
 
 
+# Ranges that fit the workspace are chosen for the shorter walk: four of six examples, a workgroup each (six of four would be three workgroups a tile)
+def test_packed_ranges_leave_short_walks():
+    call, _kept = _weighted_batch([Layer("conv", 64, 256, 56, 27, 3, 3, 1, 1, False), conv(512, 512, 3, 1, 30)], 24)
+    assert 2 * 5 * 4 in launches(call)
+
+
 # Packed operands in a batch call whose target makes ranges that the number of examples is no multiple of (here two of two for three examples):
 # everything stays inside the workspace that was asked for
 @pytest.mark.parametrize("layer,other,n", [(Layer("conv", 176, 64, 46, 46, 3, 3, 1, 1, False), conv(512, 512, 3, 1, 28), 3),
