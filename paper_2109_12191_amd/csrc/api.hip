@@ -49,6 +49,9 @@ static thread_local LaunchQueue *g_queue = nullptr;
 LaunchQueue *open_queue() { return g_queue; }
 void set_open_queue(LaunchQueue *q) { g_queue = q; }
 int crowd_hint() { return g_queue ? g_queue->crowd : 0; }
+int crowd3_hint() { return g_queue ? g_queue->crowd3 : 0; }
+double macs3_hint() { return g_queue ? g_queue->macs3 : 0.0; }
+int crowd_rows_hint() { return g_queue ? g_queue->crowd_rows : 0; }
 int fuse_hint() { return g_queue ? g_queue->fuse : 0; }
 
 // Work per workgroup a batch call plans for, in units of one 128x128x64 chunk: the convolutions' multiply-adds
@@ -492,6 +495,19 @@ static int batch_target(const std::vector<Geo> &geo)
     return crowd_of(macs);
 }
 
+// What of a batch call's work goes into launches that are planned by it; g_w: per-example calls: what is stored.  (The queue is open.)
+static void launch_targets(LaunchQueue &q, const std::vector<Geo> &geo, bool weighted, float *const *g_w)
+{
+    if (geo.size() < 2) return;
+    double macs[3] = {0.0, 0.0, 0.0};
+    for (size_t l = 0; l < geo.size(); ++l)
+        if (geo[l].kind == DP_CONV2D)
+            macs[conv_shared_launch(geo[l], weighted ? MODE_WEIGHTED : (g_w && g_w[l] ? MODE_MATERIALISE : MODE_NORM))] += conv_macs(geo[l]);
+    q.macs3 = macs[CONV_ROWS3];
+    q.crowd3 = crowd_of(q.macs3);
+    q.crowd_rows = crowd_of(macs[CONV_WHOLE_ROWS]);
+}
+
 // addresses: x[l], dy[l] are arrays of example addresses
 static dp_status per_example_grad_batch(bool addresses, bool blocks, const dp_layer_desc *descs, const void *const *x, const void *const *dy,
                                         float *const *g_w, float *const *g_b, size_t g_stride, float *const *sqnorm,
@@ -537,6 +553,7 @@ static dp_status per_example_grad_batch(bool addresses, bool blocks, const dp_la
     q.crowd = batch_target(geo);
     q.fuse = geo[0].n <= 2 ? 2 : 1;
     set_open_queue(&q);
+    launch_targets(q, geo, false, g_w);
     std::vector<const float *> parts((size_t)n_layers);
     std::vector<int32_t> counts((size_t)n_layers);
     dp_status st = DP_OK;
@@ -632,6 +649,7 @@ static dp_status unit_grad_batch(bool addresses, const dp_layer_desc *descs, int
     q.crowd = batch_target(geo);
     q.fuse = geo[0].n <= 2 ? 2 : 1;
     set_open_queue(&q);
+    launch_targets(q, geo, false, g_w);
     std::vector<const float *> parts((size_t)n_layers);
     std::vector<int32_t> counts((size_t)n_layers);
     dp_status st = DP_OK;
@@ -734,6 +752,7 @@ static dp_status recompute_batch(bool addresses, bool blocks, const dp_layer_des
     q.crowd = batch_target(geo);
     q.fuse = geo[0].n <= 2 ? 2 : 1;
     set_open_queue(&q);
+    launch_targets(q, geo, true, nullptr);
     dp_status st = DP_OK;
     for (int l = 0; l < n_layers && st == DP_OK; ++l) {
         const Geo &g = geo[(size_t)l];

@@ -1718,6 +1718,13 @@ static bool flat_direct(const Geo &g)
     return g.bf16 && flat && !g.has_bias && (g.oh * g.ow) % 2 == 0 && g.oh * g.ow >= 64;
 }
 
+// and of conv_row_stages_kernel, whose rows are of the length that its LDS layout wants
+static bool whole_rows(const Geo &g)
+{
+    const int S = g.oh * g.ow;
+    return flat_direct(g) && S % 8 == 4 && S > 16 * (PANEL_KS - 1) && S <= 16 * PANEL_KS && g.cout % PANELW_M == 0 && g.cin % PANELW_N == 0;
+}
+
 static FullPlan full_plan(const Geo &g, int mode)
 {
     FullPlan p;
@@ -1753,9 +1760,9 @@ static FullPlan full_plan(const Geo &g, int mode)
     // this: 256 -> 256, 13 layers, 16 examples (crowd 3) 33 / 67, 64 (13) 113 / 60; 2 layers, 128 examples (4) 40 / 56; 256 -> 1024, 4 layers, 32
     // examples (8) 47 / 57, 64 (16) 76 / 61; 1024 -> 2048, 2 layers, 16 examples (16) 63 / 72, 24 (24) 81 / 64; few examples of wide matrices: 13
     // layers of 1024 -> 2048, 8 examples (53) 173 / 187, 4 layers, 12 examples (24) 71 / 67.
-    const bool weighted_rows = mode == MODE_WEIGHTED && ((crowd >= 13 && g.n >= 17) || (crowd >= 17 && g.n >= 12));
-    if ((weighted_rows || (panel && mode == MODE_NORM && crowd)) && flat_direct(g) && S % 8 == 4 && S > 16 * (PANEL_KS - 1) && S <= 16 * PANEL_KS &&
-        g.cout % PANELW_M == 0 && J % PANELW_N == 0)
+    const int rows_crowd = tl_forced_crowd >= 0 ? tl_forced_crowd : crowd_rows_hint();
+    const bool weighted_rows = mode == MODE_WEIGHTED && ((rows_crowd >= 13 && g.n >= 17) || (rows_crowd >= 17 && g.n >= 12));
+    if ((weighted_rows || (panel && mode == MODE_NORM && crowd)) && whole_rows(g))
         p.shape = T128rows;
     p.tiles_m = (g.cout + kTileM[p.shape] - 1) / kTileM[p.shape];
     p.tiles_n = (J + kTileN[p.shape] - 1) / kTileN[p.shape];
@@ -2075,6 +2082,15 @@ size_t conv_norm_partial_count(const Geo &g, int mode)
     if (widened(g, mode, g2)) return conv_norm_partial_count(g2, mode);
     if (subsampled(g, mode, g2)) return conv_norm_partial_count(g2, mode);
     return norm_partials_per_example(full_plan(g, mode));
+}
+
+int conv_shared_launch(const Geo &g, int mode)
+{
+    if (stem_applicable(g, mode) || conv_rows_applicable(g, mode) || gram_norm_applicable(g, mode)) return CONV_OTHER;
+    if (conv3x3_applicable(g, mode)) return CONV_ROWS3;
+    Geo g2;
+    if (widened(g, mode, g2)) return conv_shared_launch(g2, mode);
+    return mode == MODE_WEIGHTED && whole_rows(g) ? CONV_WHOLE_ROWS : CONV_OTHER;
 }
 
 // loader of the contraction kernel for a geometry as the kernel sees it

@@ -930,6 +930,7 @@ int rows_of_width(int ow, int stride)
 // plans inside a batch call (the launch is shared with other layers) differ; workspace sizes cover both
 thread_local int c3_forced_crowd = -1;
 int c3_plan_crowd() { return c3_forced_crowd >= 0 ? c3_forced_crowd : crowd_hint(); }
+int c3_launch_crowd() { return c3_forced_crowd >= 0 ? c3_forced_crowd : crowd3_hint(); }         // of this kernel's launch alone
 
 C3Plan c3_plan_slices(const Geo &g, int mode)
 {
@@ -956,14 +957,16 @@ C3Plan c3_plan_slices(const Geo &g, int mode)
         if (crowd) {
             // In a launch shared with other layers ranges are long: without partial blocks and slice-sum launch a narrow launch that the other streams
             // of a replayed step overlap beats one that fills the chip (ResNet-50, 32 examples, crowd 32: one range per tile 6690 us a step, two
-            // for the 14-wide layers, 16 tiles, 6850, four 7030).  But no longer than the launch is worth: `crowd` grows with all of its work, and a
-            // walk has about four stages per unit of it (that range of 32 examples is 128 stages), and 48 chunks.  Where the launch is
-            // small (crowd < 8; at 4 it may be any amount below) a layer of few tiles still brings 32 workgroups.  Two such layers by themselves, us, with the
-            // 48 chunks alone / so: 64 -> 64 at 14 x 14, 48 examples, 241 / 25; at 28 x 28, 32, 169 / 32; 256 -> 256 at 14 x 14, 48, 240 / 78; four
-            // of 128 -> 128 at 28 x 28, 16, 129 / 62.  (Sixteen tiles and more keep their one range there: 256 -> 256 at 14 x 14, 4 examples, 33; two ranges 47.)
+            // for the 14-wide layers, 16 tiles, 6850, four 7030).  But no longer than the launch is worth: `crowd` (of this kernel's launch, not of the whole
+            // call, whose other kernels wait for it) grows with its work, and a walk has about four stages per unit of it (that range of 32 examples
+            // is 128 stages), and 48 chunks.  A layer of few tiles brings 32 workgroups, and so does one on 7 x 7 or 8 x 8 maps, whose stages take longest.
+            // Two such layers by themselves, us, with the 48 chunks alone / so: 64 -> 64 at 14 x 14, 48 examples, 241 / 25; at 28 x 28, 32, 169 / 32; 256 -> 256 at
+            // 14 x 14, 48, 240 / 78; four of 128 -> 128 at 28 x 28, 16, 129 / 62; beside another kernel's layer 256 -> 64 at 7 x 7, 32, 538 / 484 the two.
+            // (Sixteen tiles and more on larger maps keep their one range in small launches too: 256 -> 256 at 14 x 14, 4 examples, 33; two ranges 40.)
             const long long stages = (long long)g.n * ((g.oh + p.stage_rows - 1) / p.stage_rows);
+            crowd = c3_launch_crowd();
             want = std::max((stages + 4 * crowd - 1) / (4 * crowd), ((long long)g.n * p.chunks + 47) / 48);
-            if (crowd < 8 && tiles <= 8 && want * tiles < 32) want = (32 + tiles - 1) / tiles;
+            if ((tiles <= 8 || g.ow <= 8) && want * tiles < 32) want = (32 + tiles - 1) / tiles;
         }
         const long long cap = (long long)(96.0e6 / (4.0 * 9 * 16 * C3_THREADS * (double)tiles));
         if (want > cap) want = cap;
@@ -1004,13 +1007,14 @@ C3Plan c3_plan(const Geo &g, int mode)
 {
     C3Plan p = c3_plan_slices(g, mode);
     if (mode == MODE_WEIGHTED || p.ksplit > 1 || !c3_streams(g.ow, g.stride)) return p;
-    // Starting a workgroup costs as much as three stages: one that walks fewer than sixteen takes several rows of results in a row, as long as
-    // two workgroups are left for every compute unit (in a launch that other layers share: a workgroup for every second one).  Where they are
+    // Starting a workgroup costs as much as three stages: one that walks fewer than sixteen takes several rows of results in a row, as long as the launch (of
+    // which this layer's work is a share) has two workgroups left for every compute unit, and a layer of a shared one a workgroup for every second one.  Where they are
     // stored, at most four: of more the last workgroups' stores are left alone at the end (512 -> 512 at 7 x 7, us for at most 16 / 8 / 4 / 2 / 1: two layers of 48
-    // examples 205 / 189 / 183 / 178 / 187, four of 8 59 / 59 / 59 / 63 / 71, one of 128 249 / 242 / 237 / 233 / 249, of 32 60 / 60 / 60 / 64 / 69).
+    // examples 205 / 189 / 183 / 178 / 187, four of 8 59 / 59 / 59 / 63 / 71, one of 128 249 / 242 / 237 / 233 / 249, of 32 60 / 60 / 60 / 64 / 69; 512 -> 64 at
+    // 8 x 8, 48 examples, beside a 1x1 layer, 3 / 1, 38 / 31).
     const long long stages = (long long)g.unit * ((g.oh + p.stage_rows - 1) / p.stage_rows), rows = g.n / g.unit, tiles = (long long)p.tiles_co * p.tiles_ci;
-    long long k = 16 / stages;
-    const long long most = rows * tiles / (c3_plan_crowd() ? 128 : 512);
+    long long k = 16 / stages, most = rows * tiles / 512;
+    if (c3_launch_crowd()) most = std::min(rows * tiles / 128, (long long)((double)(rows * tiles) * std::max(1.0, macs3_hint() / conv_macs(g)) / 512.0));
     if (k > most) k = most;
     if (k > rows) k = rows;
     if (mode == MODE_MATERIALISE && k > 4) k = 4;

@@ -83,6 +83,9 @@ struct LaunchQueue {
     hipStream_t stream = nullptr;
     int crowd = 0;                      // > 0: launches are shared with other layers; the work a workgroup should
                                         // get, in units of one 128x128x64 chunk (about a million multiply-adds)
+    int crowd3 = 0, crowd_rows = 0;     // the same of the launch that the call's raw-row 3x3 layers share, and of that of its layers
+                                        // that the clip-weighted whole-row kernel can take
+    double macs3 = 0.0;                 // multiply-adds of the former
     int fuse = 0;                       // > 0: launchers hand in the kernels that dispatch on the variant INSIDE the kernel
                                         // (one launch for all row widths of the 3x3 kernel): only four kernels run at a
                                         // time, and a narrow launch inside a wide one costs none of them.  2: micro-steps
@@ -95,6 +98,9 @@ LaunchQueue *open_queue();
 void set_open_queue(LaunchQueue *q);
 // 0, or inside a batch call of several layers the work per workgroup to plan for (see LaunchQueue::crowd)
 int crowd_hint();
+int crowd3_hint();
+double macs3_hint();
+int crowd_rows_hint();
 // which variant-dispatching kernels the open batch wants (see LaunchQueue::fuse); 0: none
 int fuse_hint();
 // Launch the held main kernels grouped by kernel, then the deferred follow-ups.

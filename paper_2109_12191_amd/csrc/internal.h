@@ -47,6 +47,9 @@ enum Mode { MODE_NORM = 0, MODE_MATERIALISE = 1, MODE_WEIGHTED = 2 };
 
 size_t conv_ws_bytes(const Geo &g, int mode);
 const char *conv_variant_name(const Geo &g, int mode, bool shared);
+// which launch of a batch call a convolution shares with others of its kind
+enum { CONV_OTHER = 0, CONV_ROWS3 = 1, CONV_WHOLE_ROWS = 2 };
+int conv_shared_launch(const Geo &g, int mode);
 // multiply-adds of a call, and the work per workgroup (LaunchQueue::crowd) of a batch call whose convolutions have that many together
 inline double conv_macs(const Geo &g) { return (double)g.n * g.cout * g.cin * g.kh * g.kw * g.oh * g.ow; }
 int crowd_of(double macs);

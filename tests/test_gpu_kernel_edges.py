@@ -822,7 +822,7 @@ def _weighted_batch(layers, n, seed=359):
                                            (1024, 256, 32, (14, 14)), (256, 128, 1, (14, 14)), (256, 256, 12, (14, 14)), (256, 512, 65, (12, 17)), (512, 512, 19, (17, 12))])
 @pytest.mark.parametrize("at", [False, True])
 def test_row_stages(cin, cout, n, hw, at):
-    layer, filler = Layer("conv", cin, cout, *hw), conv(1024, 1024, 3, 1, 14)
+    layer, filler = Layer("conv", cin, cout, *hw), conv(4096, 2048, 1, 1, 14)
     S = hw[0] * hw[1]
     d = dp.make_desc(layer, n, "bf16")
     rows = "128x256rows" in dp.dp_kernel_variant(d, dp.DP_WS_RECOMPUTE | dp.DP_VARIANT_SHARED)
@@ -860,7 +860,7 @@ def test_row_stages(cin, cout, n, hw, at):
     main = launches(sums)
     if rows:                                       # two layers of whole-row tiles, one workgroup a range of up to sixteen examples
         groups = (cout // 128) * (cin // 256) * -(-n // 16)
-        assert 2 * -(-groups // 8) * 8 in main, (main, groups)
+        assert 2 * -(-groups // 8) * 8 + 16 * 16 * min(-(-n // 16), 2) in main, (main, groups)        # (two copies of the third one's matrix are 67 MB)
     torch.cuda.synchronize()
     assert torch.equal(acc[0], acc[1])
     keep = [i for i in range(n) if f[i] != 0.0]
@@ -978,6 +978,29 @@ def test_conv3x3_weighted_batches_fill_the_chip(layers, n, least):
         ref = torch.nn.functional.unfold(x[:, :4].double(), 3, padding=1)
         ref = sum(scaled[i].reshape(l.cout, -1) @ ref[i].T for i in range(n))
         assert_close(host(got.reshape(l.cout, l.cin, 9)[:, :4]).reshape(-1), host(ref).reshape(-1), 1e-4, "sum")
+
+
+# The same beside a layer that another kernel runs, however much work that is, and on small maps (tiles x ranges of each such layer)
+@pytest.mark.parametrize("layers,n,blocks", [([conv(256, 64, 3, 1, 7), conv(256, 256, 5, 1, 20)], 32, 4 * 8), ([conv(64, 64, 3, 1, 14), conv(512, 512, 5, 1, 14)], 48, 24),
+                                             ([conv(193, 256, 3, 1, 7), conv(128, 128, 5, 1, 8)], 12, 16 * 2)],
+                         ids=lambda v: str(v) if isinstance(v, int) else f"{v[0].cin}-{v[0].h}")
+def test_conv3x3_weighted_layers_beside_other_kernels(layers, n, blocks):
+    call, _kept = _weighted_batch(layers, n)
+    assert blocks in launches(call)
+
+
+# Stored and norm-only: a small launch keeps a workgroup per row of results, whatever else the call holds
+def test_conv3x3_rows_of_a_small_launch_are_not_put_in_a_row():
+    layers, n = [conv(512, 64, 3, 1, 8), conv(256, 256, 1, 1, 14)], 48
+    descs = [dp.make_desc(l, n, "bf16") for l in layers]
+    xs, dys = [torch.ones((n,) + tuple(l.x_shape), dtype=torch.bfloat16, device="cuda:0") for l in layers], [
+        torch.ones((n,) + tuple(l.dy_shape), dtype=torch.bfloat16, device="cuda:0") for l in layers]
+    ws = [torch.empty(max(16, dp.dp_workspace_bytes(d)), dtype=torch.uint8, device="cuda:0") for d in descs]
+    g, sq = [torch.empty((n, l.pw), device="cuda:0") for l in layers], torch.zeros((2, n), device="cuda:0")
+    bt = dp.LayerBatch(descs, [t.data_ptr() for t in ws], [t.numel() for t in ws])
+    main = launches(lambda: dp.dp_per_example_grad_batch(bt, bt.ptrs([t.data_ptr() for t in xs]), bt.ptrs([t.data_ptr() for t in dys]), bt.ptrs([t.data_ptr() for t in g]), None,
+                                                         bt.ptrs([sq[k].data_ptr() for k in range(2)])))
+    assert 8 * n in main, main
 
 
 def test_conv3x3_weighted_batches_of_a_full_launch_walk_one_range():
