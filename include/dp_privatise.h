@@ -121,7 +121,7 @@ size_t dp_batch_workspace_bytes(const dp_layer_desc *desc /*[host]*/, int use /*
  * "conv_contract<bf16,128x128,per_example>"; "" on a bad descriptor.  With DP_VARIANT_SHARED or-ed
  * into `use`: the variant the layer runs as inside a batch call of several layers with the workspace of
  * dp_batch_workspace_bytes (tiling is chosen differently when a launch is shared; the name is that of a call whose layers fill the chip: in one of
- * little work the clip-weighted "128x256rows" layers run as the others do); layers with equal names then share one launch, at most 16
+ * less work clip-weighted layers may run as "128x256rows" or as the others do); layers with equal names then share one launch, at most 16
  * per launch, and so do all layers whose names begin with "conv3x3_rows<" (every row width, stride
  * and K slicing of that kernel runs in one launch inside a batch call).  Pure host; lets a profiler's
  * per-kernel rows be tied to layers.  The string is static.                                     */

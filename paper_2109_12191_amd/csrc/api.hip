@@ -59,7 +59,7 @@ int fuse_hint() { return g_queue ? g_queue->fuse : 0; }
 // start-up dominates nor so much that one workgroup becomes the critical path.
 int crowd_of(double macs)
 {
-    const double per_wg = macs / (128.0 * 128.0 * 64.0) / 768.0;
+    const double per_wg = macs / CROWD_UNIT;
     return per_wg < 4.0 ? 4 : (per_wg > 64.0 ? 64 : (int)per_wg);
 }
 
@@ -505,7 +505,7 @@ static void launch_targets(LaunchQueue &q, const std::vector<Geo> &geo, bool wei
             macs[conv_shared_launch(geo[l], weighted ? MODE_WEIGHTED : (g_w && g_w[l] ? MODE_MATERIALISE : MODE_NORM))] += conv_macs(geo[l]);
     q.macs3 = macs[CONV_ROWS3];
     q.crowd3 = crowd_of(q.macs3);
-    q.crowd_rows = crowd_of(macs[CONV_WHOLE_ROWS]);
+    q.crowd_rows = macs[CONV_WHOLE_ROWS] < 4.0 * CROWD_UNIT ? 0 : crowd_of(macs[CONV_WHOLE_ROWS]);          // (0: less than any plan is made for)
 }
 
 // addresses: x[l], dy[l] are arrays of example addresses

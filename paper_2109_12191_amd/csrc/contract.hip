@@ -1710,6 +1710,7 @@ struct FullPlan {
 // example ranges of the weighted form are as long as they can be.  Workspace sizes cover both cases.
 static thread_local int tl_forced_crowd = -1;
 static int plan_crowd() { return tl_forced_crowd >= 0 ? tl_forced_crowd : crowd_hint(); }
+static thread_local int tl_forced_rows = -1;      // >= 0: whether clip-weighted layers of whole rows take the kernel for them, whatever the work
 
 // geometry of the LDS-direct kernel: bf16, one aligned row of S >= 64 (even) elements per channel, no bias
 static bool flat_direct(const Geo &g)
@@ -1723,6 +1724,21 @@ static bool whole_rows(const Geo &g)
 {
     const int S = g.oh * g.ow;
     return flat_direct(g) && S % 8 == 4 && S > 16 * (PANEL_KS - 1) && S <= 16 * PANEL_KS && g.cout % PANELW_M == 0 && g.cin % PANELW_N == 0;
+}
+
+// Whether the clip-weighted calls of n examples are faster in it than in conv_flat_kernel.  crowd: work of the call's layers that it can take (LaunchQueue::crowd_rows).
+// A range is a walk of E <= 16 examples by one workgroup a compute unit: rounds of 11 + 2.75 E us, 23 + 2.75 n where there is one range, whose workgroups add to the
+// accumulator themselves (8 examples 45, 16 67; 18 examples in two ranges 39, 24 46, 32 55), 256 workgroups a round (crowd 2 E).  conv_flat_kernel spreads any call
+// over the chip, but leaves it more copies of the matrix to add: about 26 + 3.25 us per unit of crowd.  Both sides, us, that / this: 256 -> 256, 6 layers, 130 examples
+// (crowd 12) 104 / 56, 13 layers, 100 examples (20) 177 / 65, 2 layers, 128 examples (4) 40 / 56; 1024 -> 1024, 2 layers, 12 examples (6) 36 / 56, 3 layers, 40
+// examples (30) 140 / 105; 256 -> 384, 16 layers, 17 examples (6) 65 / 40; 2048 -> 384, 10 layers, 7 examples (13) 78 / 48; 5 examples of 1024 -> 1024, 10
+// layers (12, two rounds) 62 / 72; one of 1024 -> 2048, 16 layers (8) 57 / 98.  410 random calls of 1 to 256 examples: 1.4 % above the faster of the two in the mean
+// (always this 6, never 25).
+static bool rows_pay(int n, int crowd)
+{
+    if (crowd < 4 || n < 3) return false;
+    const int ranges = (n + 15) / 16, e = (n + ranges - 1) / ranges, rounds = (crowd + 2 * e - 1) / (2 * e);
+    return rounds * ((ranges == 1 ? 92 : 44) + 11 * e) <= 104 + 13 * crowd;           // (quarters of a microsecond)
 }
 
 static FullPlan full_plan(const Geo &g, int mode)
@@ -1755,13 +1771,9 @@ static FullPlan full_plan(const Geo &g, int mode)
     const bool panel = mode != MODE_WEIGHTED && g.unit == 1 && flat_direct(g) && S % 8 == 4 && S > 16 * (PANEL_KS - 1) && S <= 16 * PANEL_KS &&
                        g.cout % 256 == 0 && J % 256 == 0 && (long long)g.n * (g.cout / 256) * (J / 256) >= 128;
     if (panel) p.shape = T256rows;
-    // and their clip-weighted and norm-only forms in batch calls (conv_row_stages_kernel).  A clip-weighted range is a walk of up to sixteen examples,
-    // 58 us, so the call needs the work to fill the chip with them, and the examples to make them of.  A batch call by itself, us, conv_flat_kernel /
-    // this: 256 -> 256, 13 layers, 16 examples (crowd 3) 33 / 67, 64 (13) 113 / 60; 2 layers, 128 examples (4) 40 / 56; 256 -> 1024, 4 layers, 32
-    // examples (8) 47 / 57, 64 (16) 76 / 61; 1024 -> 2048, 2 layers, 16 examples (16) 63 / 72, 24 (24) 81 / 64; few examples of wide matrices: 13
-    // layers of 1024 -> 2048, 8 examples (53) 173 / 187, 4 layers, 12 examples (24) 71 / 67.
+    // and their clip-weighted and norm-only forms in batch calls (conv_row_stages_kernel)
     const int rows_crowd = tl_forced_crowd >= 0 ? tl_forced_crowd : crowd_rows_hint();
-    const bool weighted_rows = mode == MODE_WEIGHTED && ((rows_crowd >= 13 && g.n >= 17) || (rows_crowd >= 17 && g.n >= 12));
+    const bool weighted_rows = mode == MODE_WEIGHTED && (tl_forced_rows >= 0 ? tl_forced_rows : rows_pay(g.n, rows_crowd));
     if ((weighted_rows || (panel && mode == MODE_NORM && crowd)) && whole_rows(g))
         p.shape = T128rows;
     p.tiles_m = (g.cout + kTileM[p.shape] - 1) / kTileM[p.shape];
@@ -2034,18 +2046,22 @@ size_t conv_ws_bytes(const Geo &g, int mode)
 {
     size_t need = 0;
     const int saved = tl_forced_crowd;
-    // a call alone, and a call inside a batch: the smallest target that it can have with this layer, of which there are most slices, and one that the
-    // clip-weighted whole-row kernel is chosen at
-    for (int crowd : {0, mode == MODE_WEIGHTED ? crowd_of(conv_macs(g)) : 4, 64}) {
-        tl_forced_crowd = crowd;
-        size_t b = conv_ws_bytes_mode(g, mode == MODE_WEIGHTED ? MODE_WEIGHTED : MODE_NORM);
-        if (mode != MODE_WEIGHTED) {
+    // a call alone, and a call inside a batch: the smallest target that it can have with this layer, of which there are most slices, and (per-example calls) the largest;
+    // a clip-weighted layer of whole rows in either kernel, whichever a call's work chooses
+    const bool weighted = mode == MODE_WEIGHTED;
+    for (int k = 0; k < 3; ++k) {
+        const int crowds[2][3] = {{0, 4, 64}, {0, crowd_of(conv_macs(g)), 64}};
+        tl_forced_crowd = crowds[weighted][k];
+        if (weighted) tl_forced_rows = k == 2;
+        size_t b = conv_ws_bytes_mode(g, weighted ? MODE_WEIGHTED : MODE_NORM);
+        if (!weighted) {
             const size_t m = conv_ws_bytes_mode(g, MODE_MATERIALISE);
             if (m > b) b = m;
         }
         if (b > need) need = b;
     }
     tl_forced_crowd = saved;
+    tl_forced_rows = -1;
     return need;
 }
 

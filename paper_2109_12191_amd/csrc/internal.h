@@ -53,6 +53,7 @@ int conv_shared_launch(const Geo &g, int mode);
 // multiply-adds of a call, and the work per workgroup (LaunchQueue::crowd) of a batch call whose convolutions have that many together
 inline double conv_macs(const Geo &g) { return (double)g.n * g.cout * g.cin * g.kh * g.kw * g.oh * g.ow; }
 int crowd_of(double macs);
+constexpr double CROWD_UNIT = 768.0 * 128.0 * 128.0 * 64.0;
 void c3_set_forced_crowd(int v);      // conv3x3.hip: plan as alone (0), as in a shared launch (1), or by the open batch (-1)
 dp_status launch_conv(const Geo &g, int mode, const void *x, const void *dy, float *out_w, float *out_b,
                       size_t out_stride, float *sqnorm, const float *group_sqnorm, float clip_c, void *ws,

@@ -38,11 +38,13 @@ PHASE_EXAMPLES = 256
 #   and of micro-steps of one or two examples.  ResNet-50, 64 x 1: one by one / 16 / 32 / 64 9682 / 2774 / 2476 / 2481; 32 x 2: 7984 /
 #   2821 (16) / 2502 / 2498
 PHASE_EXAMPLES_OF_SMALL = 64
-# How much work a batch call needs for its clip-weighted layers on 14 x 14 maps to run in the whole-row kernel (from finished fp32 blocks) and to gain by it, in rounds of
-# 768 workgroups of one 128 x 128 x 64 chunk, with seventeen examples (two ranges) and more / with twelve: from there on those layers need no stored
-# gradients.  ResNet-50 in phases of one-example micro-steps on four streams, stored / this: 16 examples (13) 708 / 720, 18 (14, on one) 953 / 933, 20 (16)
-# 902 / 873, 24 (19, of two on one stream) 1173 / 1157, 32 (26) 1150 / 1111, 64 (53) 2140 / 2050.
-ROWS_WORK = 14, 17
+# How much work a batch call needs for its clip-weighted layers on 14 x 14 maps to gain by the whole-row kernel (from finished fp32 blocks) so much that they need no
+# stored gradients, in rounds of 768 workgroups of one 128 x 128 x 64 chunk, with seventeen examples (two ranges) and more / with twelve.
+# Us a step, stored / this: six layers of 256 -> 256, six micro-steps of 110 examples (10.5) 624 / 479 on three streams; 256 -> 256 and 1024 -> 256, 130 examples (10.4) 644 / 545;
+# those beside a 3x3 and other layers 1258 / 1216 on three streams, 1195 / 1300 on eight, with 64 examples (5.1) 542 / 548.  ResNet-50 in phases of
+# one-example micro-steps on four streams: 16 examples (13) 708 / 720, 18 (14, on one) 953 / 933, 20 (16) 902 / 873, 24 (19, of two on one stream) 1173 / 1157,
+# 32 (26) 1150 / 1111, 64 (53) 2140 / 2050.
+ROWS_WORK = 10, 17
 # And no phase is so large that a layer falls back to the kernel that gathers its operands element by element, because the rewritten
 # operands of a faster one outgrow their share of the workspace: ResNet-18-GN at 40 x 40, 64 examples 3656 / 5083 (two micro-steps) / 7188
 # (four), 24 (8 micro-steps): 3097 / 3028 (four) / 3825 (eight).
@@ -394,7 +396,7 @@ class PrivatiseStep:
 
     def _in_whole_rows(self, variants: Sequence[str], n: int) -> List[int]:
         """Layers that run in the whole-row kernel when the recomputing calls of `n` examples hold all that could (at most 16 a call)."""
-        ids = [i for i, v in enumerate(variants) if "128x256rows" in v]
+        ids = [i for i, v in enumerate(variants) if "128x256rows" in v and n >= 12]
         calls, least = [ids[k: k + 16] for k in range(0, len(ids), 16)], ROWS_WORK[0 if n >= 17 else 1] * 768 * 2 * 128 * 128 * 64
         return [i for call in calls if len(call) > 1 and n * sum(self.layers[i].flops for i in call) >= least for i in call]
 

@@ -878,6 +878,21 @@ def test_row_stages_are_left_to_calls_that_fill_the_chip(cin, cout, count, n):
     assert launches(call)[0] >= 32 * count
 
 
+# And taken where the other kernel leaves copies of small matrices to add, or few examples are ranges that the chip finishes at once
+@pytest.mark.parametrize("cin,cout,count,n", [(256, 256, 6, 130), (256, 256, 8, 100), (256, 384, 16, 17), (2048, 384, 10, 7), (512, 256, 13, 20)])
+def test_row_stages_are_taken_where_their_rounds_are_shorter(cin, cout, count, n):
+    call, (xs, dys, _, sq, acc) = _weighted_batch([conv(cin, cout, 1, 1, 14)] * count, n)
+    for t in acc:
+        t.zero_()
+    ranges = -(-n // 16)
+    ranges = -(-n // -(-n // ranges))
+    assert launches(call)[0] == count * -(-(cout // 128) * (cin // 256) * ranges // 8) * 8
+    f = torch.clamp(1.0 / sq.double().sqrt(), max=1.0)
+    for x, dy, got in ((xs[0], dys[0], acc[0]), (xs[-1], dys[-1], acc[-1])):
+        x, dy = x.reshape(n, cin, 196)[:, :8].double(), dy.reshape(n, cout, 196).double() * f[:, None, None]
+        assert_close(host(got.reshape(cout, cin)[:, :8]).reshape(-1), host(sum(dy[i] @ x[i].T for i in range(n))).reshape(-1), 1e-5, "sum")
+
+
 # The ranges' copies of a matrix stay below 96 MB, the ranges get longer instead
 def test_row_stages_keep_their_copies_small():
     layers = [conv(2048, 1024, 1, 1, 14), conv(512, 512, 3, 1, 14)]
