@@ -686,7 +686,7 @@ def test_units_in_the_fp32_raw_row_kernel(cin, cout, h, w, k, stride, n, unit):
     assert np.allclose(host(norms), host(sq), rtol=F32_TOL)
 
 
-# The bf16 raw-row 3x3 kernel where a workgroup makes several rows of results one after the other (up to sixteen, of stored ones four): the last group of them short, tiles of few
+# The bf16 raw-row 3x3 kernel where a workgroup makes several rows of results one after the other: the last group of them short, tiles of few
 # channels, rows of 7 whose examples start between dwords (odd channels), one stage and several per example, pieces that an
 # example's end cuts.  Alone, from 1024 blocks on; every gradient is compared with a batch call of two layers, whose plan is another one.
 @pytest.mark.parametrize("cin,cout,h,w,stride,n", [(64, 64, 7, 7, 1, 1030), (65, 67, 7, 7, 1, 519), (64, 130, 9, 7, 1, 700), (72, 65, 14, 14, 1, 515),
@@ -702,16 +702,16 @@ def test_conv3x3_rows_of_results_in_a_row(cin, cout, h, w, stride, n):
     dy = (torch.randn((n,) + tuple(layer.dy_shape), generator=gen, device="cuda:0") * 0.05).bfloat16()
     f32 = dict(dtype=torch.float32, device="cuda:0")
 
-    def batch(count, stored=True):
+    def batch(count):
         ws = [torch.empty(max(16, dp.dp_workspace_bytes(d, dp.DP_WS_PER_EXAMPLE_GRAD)), dtype=torch.uint8, device="cuda:0") for _ in range(count)]
-        g = [torch.full((n, (layer.pw + 3) & ~3), 7.0, **f32) for _ in range(count if stored else 0)]
+        g = [torch.full((n, (layer.pw + 3) & ~3), 7.0, **f32) for _ in range(count)]
         sq = [torch.full((n,), -1.0, **f32) for _ in range(count)]
         if count == 1:
-            dp.dp_per_example_grad(d, x, dy, g[0] if stored else None, None, sq[0], ws[0], g_stride=g[0].shape[1] if stored else 0)
+            dp.dp_per_example_grad(d, x, dy, g[0], None, sq[0], ws[0], g_stride=g[0].shape[1])
         else:
             bt = dp.LayerBatch([d] * count, [t.data_ptr() for t in ws], [t.numel() for t in ws])
-            dp.dp_per_example_grad_batch(bt, bt.ptrs([x.data_ptr()] * count), bt.ptrs([dy.data_ptr()] * count), bt.ptrs([t.data_ptr() for t in g]) if stored else None,
-                                         None, bt.ptrs([t.data_ptr() for t in sq]), g_stride=g[0].shape[1] if stored else 0)
+            dp.dp_per_example_grad_batch(bt, bt.ptrs([x.data_ptr()] * count), bt.ptrs([dy.data_ptr()] * count), bt.ptrs([t.data_ptr() for t in g]), None,
+                                         bt.ptrs([t.data_ptr() for t in sq]), g_stride=g[0].shape[1])
         torch.cuda.synchronize()
         return [t[:, :layer.pw] for t in g], sq
 
@@ -722,12 +722,32 @@ def test_conv3x3_rows_of_results_in_a_row(cin, cout, h, w, stride, n):
     assert float((g - a).norm() / g.norm()) < 1e-5 and float((g - a).abs().max() / g.abs().max()) < 1e-5
     assert torch.allclose(sq, sa, rtol=1e-5)
     assert torch.allclose(sq, g.square().sum(1), rtol=1e-4)
-    for count in (1, 2):                           # norms alone (7 x 7 and 8 x 8: from products of rows, in another kernel)
-        for t in batch(count, stored=False)[1]:
-            assert torch.allclose(t, sq, rtol=1e-3 if h * w <= 64 else 1e-5)
     for i in (0, 1, n // 2, n - 2, n - 1):
         ref, _ = oracle.example_grad(layer, host(x[i]), host(dy[i]))
         assert_close(host(g[i]), ref.reshape(-1), F32_TOL, f"example {i}")        # (bf16 products are exact in fp32)
+
+
+# The same for norms alone (up to sixteen rows in a row; 7 x 7 and 8 x 8: from products of rows, in another kernel), against the stored gradients
+@pytest.mark.parametrize("cin,cout,h,w,stride,n", [(64, 64, 7, 7, 1, 1030), (64, 130, 9, 7, 1, 700), (72, 65, 14, 14, 1, 515), (64, 64, 13, 14, 1, 1027),
+                                                   (64, 64, 10, 16, 1, 1025), (64, 64, 14, 14, 2, 1029), (64, 64, 5, 28, 1, 1026), (64, 64, 2, 32, 1, 1100)])
+def test_conv3x3_norms_alone_of_rows_in_a_row(cin, cout, h, w, stride, n):
+    layer = Layer("conv", cin, cout, h, w, 3, 3, stride, 1, False)
+    d = dp.make_desc(layer, n, "bf16")
+    gen = torch.Generator(device="cuda:0")
+    gen.manual_seed(337)
+    x = torch.randn((n,) + tuple(layer.x_shape), generator=gen, device="cuda:0").bfloat16()
+    dy = (torch.randn((n,) + tuple(layer.dy_shape), generator=gen, device="cuda:0") * 0.05).bfloat16()
+    ws = [torch.empty(max(16, dp.dp_workspace_bytes(d)), dtype=torch.uint8, device="cuda:0") for _ in range(2)]
+    g, want = torch.empty((n, layer.pw), device="cuda:0"), torch.empty(n, device="cuda:0")
+    dp.dp_per_example_grad(d, x, dy, g, None, want, ws[0])
+    for count in (1, 2):
+        sq = [torch.full((n,), -1.0, device="cuda:0") for _ in range(count)]
+        bt = dp.LayerBatch([d] * count, [t.data_ptr() for t in ws[:count]], [t.numel() for t in ws[:count]])
+        dp.dp_per_example_grad_batch(bt, bt.ptrs([x.data_ptr()] * count), bt.ptrs([dy.data_ptr()] * count), None, None, bt.ptrs([t.data_ptr() for t in sq]))
+        torch.cuda.synchronize()
+        for t in sq:
+            assert torch.allclose(t, want, rtol=1e-3 if h * w <= 64 else 1e-5)
+    assert torch.allclose(want, g.square().sum(1), rtol=1e-4)
 
 
 # The clip-weighted form where a range holds more examples than a wave has lanes for factors, and where it ends inside a range
@@ -746,8 +766,8 @@ def test_conv3x3_weighted_ranges(cin, cout, h, w, n):
     assert_close(got[idx] - 1.0, oracle.weighted_sum_elems(layer, x, dy, f, idx), BF16_TOL, "increment")
 
 
-# Packed operands: planes of odd size and odd channel counts (examples that start between dwords), ranges of examples that are
-# no multiple of a workgroup's, channels that are none either, strides, taps with and without padding; small copies, which one launch makes
+# Packed operands taken through LDS: planes of odd size and odd channel counts (examples that start between dwords), ranges of examples that are
+# no multiple of a workgroup's, channels that are none either, strides, taps with and without padding, a plane too large for it
 @pytest.mark.parametrize("layer,n", [(conv(33, 70, 1, 1, 5), 19), (conv(65, 64, 1, 2, 13), 7), (conv(67, 65, 3, 2, 14), 37), (conv(513, 64, 3, 1, 4), 21),
                                      (conv(40, 33, 3, 1, 9), 5), (conv(64, 64, 3, 2, 8), 257), (Layer("conv", 12, 40, 11, 13, 5, 5, 2, 2, False), 6),
                                      (Layer("conv", 3, 40, 130, 140, 3, 3, 4, 1, False), 3), (Layer("conv", 31, 64, 1, 7, 3, 3, 1, 1, False), 18)],
@@ -755,7 +775,25 @@ def test_conv3x3_weighted_ranges(cin, cout, h, w, n):
 @pytest.mark.parametrize("several", [False, True])
 def test_packed_operands(layer, n, several):
     x, dy = _inputs(layer, n, 347, "bf16")
-    _check_packed(layer, n, several, x, dy)
+    rng = np.random.default_rng(43)
+    n2 = (rng.uniform(0.3, 2.5, n) ** 2).astype(np.float32)
+    f = np.array([oracle.clip_factor(float(v), 1.0) for v in n2])
+    idx = rng.choice(layer.pw, size=min(layer.pw, 3000), replace=False)
+    ref = oracle.weighted_sum_elems(layer, x, dy, f, idx)
+    if not several:
+        got, _ = _run_weighted(layer, x, dy, "bf16", n2, 1.0)
+    else:
+        d = dp.make_desc(layer, n, "bf16")
+        ws = [torch.empty(max(16, dp.dp_workspace_bytes(d, dp.DP_WS_RECOMPUTE)), dtype=torch.uint8, device="cuda:0") for _ in range(2)]
+        acc = [torch.ones(layer.pw, device="cuda:0") for _ in range(2)]
+        xd, dyd, sq = dev(x, "bf16"), dev(dy, "bf16"), dev(n2)
+        bt = dp.LayerBatch([d, d], [t.data_ptr() for t in ws], [t.numel() for t in ws])
+        dp.dp_clip_accumulate_recompute_batch(bt, bt.ptrs([xd.data_ptr()] * 2), bt.ptrs([dyd.data_ptr()] * 2), bt.ptrs([sq.data_ptr()] * 2), bt.floats([1.0, 1.0]),
+                                              bt.ptrs([t.data_ptr() for t in acc]), bt.ptrs([None, None]))
+        torch.cuda.synchronize()
+        assert torch.equal(acc[0], acc[1])
+        got = host(acc[0])
+    assert_close(got[idx] - 1.0, ref, BF16_TOL, "increment")
 
 
 def _check_packed(layer, n, several, x, dy):
@@ -815,13 +853,54 @@ def _weighted_batch(layers, n, seed=359):
     return (lambda: dp.dp_clip_accumulate_recompute_batch(*args)), (xs, dys, ws, sq, acc)
 
 
-# Layers in batch calls whose rows travel in stages, of 196 and of 204 values (where other waves issue the seventh load of a stage): norm-only (ranges of eight
+# Layers on 14 x 14 maps in batch calls whose rows travel in stages: norm-only (ranges of eight examples, the last one short; from 128 blocks on)
+# and clip-weighted (one range; several of up to sixteen with a sum behind them), tiles of both matrices' directions, whole tensors and examples by address, an example
+# that is left out
+@pytest.mark.parametrize("cin,cout,n", [(256, 256, 131), (256, 512, 66), (512, 128, 67), (768, 384, 33), (1024, 256, 32), (256, 128, 1)])
+@pytest.mark.parametrize("at", [False, True])
+def test_row_stages(cin, cout, n, at):
+    layer = conv(cin, cout, 1, 1, 14)
+    d = dp.make_desc(layer, n, "bf16")
+    # (one example is the other kernel's, whatever the call's work)
+    assert dp.dp_kernel_variant(d, dp.DP_WS_RECOMPUTE | dp.DP_VARIANT_SHARED) == f"conv_contract<bf16,{'128x256rows' if n > 1 else '128x128'},weighted>"
+    x, dy = _inputs(layer, n, 353, "bf16")
+    if n > 40:
+        dy[5] = 3e38                               # this example's gradient overflows: no number in its norm, nothing in the sum
+    rng = np.random.default_rng(47)
+    n2 = (rng.uniform(0.3, 2.5, n) ** 2).astype(np.float32)
+    f = np.array([oracle.clip_factor(float(v), 1.0) for v in n2])
+    if n > 40:
+        n2[5], f[5] = np.inf, 0.0
+    xd, dyd, sqd = dev(x, "bf16"), dev(dy, "bf16"), dev(n2)
+    ws = [torch.empty(max(16, dp.dp_workspace_bytes(d, dp.DP_WS_RECOMPUTE), dp.dp_workspace_bytes(d)), dtype=torch.uint8, device="cuda:0") for _ in range(2)]
+    sq = [torch.full((n,), -1.0, device="cuda:0") for _ in range(2)]
+    acc = [torch.ones(layer.pw, device="cuda:0") for _ in range(2)]
+    bt = dp.LayerBatch([d, d], [t.data_ptr() for t in ws], [t.numel() for t in ws])
+    if at:
+        tables = [torch.tensor([t.data_ptr() + i * t[0].numel() * 2 for i in range(n)], dtype=torch.int64, device="cuda:0") for t in (xd, dyd)]
+        px, pdy = ([t.data_ptr()] * 2 for t in tables)
+    else:
+        px, pdy = [xd.data_ptr()] * 2, [dyd.data_ptr()] * 2
+    dp.dp_per_example_grad_batch(bt, bt.ptrs(px), bt.ptrs(pdy), None, None, bt.ptrs([t.data_ptr() for t in sq]), addresses=at)
+    dp.dp_clip_accumulate_recompute_batch(bt, bt.ptrs(px), bt.ptrs(pdy), bt.ptrs([sqd.data_ptr()] * 2), bt.floats([1.0, 1.0]),
+                                          bt.ptrs([t.data_ptr() for t in acc]), bt.ptrs([None, None]), addresses=at)
+    torch.cuda.synchronize()
+    assert torch.equal(acc[0], acc[1])
+    keep = [i for i in range(n) if f[i] != 0.0]
+    g = np.stack([dy[i].reshape(cout, 196).astype(np.float64) @ x[i].reshape(cin, 196).astype(np.float64).T for i in keep])
+    # fp32 sums of 196 products (sqrt(196) 2^-24 = 8e-7), of their squares and of at most 131 scaled blocks
+    for t in sq:
+        assert np.allclose(host(t)[keep], (g * g).sum((1, 2)), rtol=1e-5)
+    assert_close(host(acc[0]) - 1.0, (f[keep][:, None, None] * g).sum(0).reshape(-1), 1e-5, "increment")
+
+
+# The same in calls that fill the chip, of rows of 196 and of 204 values (where other waves issue the seventh load of a stage): norm-only (ranges of eight
 # examples, the last one short; from 128 blocks on) and clip-weighted (one range; several of up to sixteen with a sum behind them; twelve examples and a
 # call of enough work, which a third layer stands for), tiles of both matrices' directions, whole tensors and examples by address, an example that is left out
 @pytest.mark.parametrize("cin,cout,n,hw", [(256, 256, 131, (14, 14)), (256, 512, 66, (14, 14)), (512, 128, 67, (14, 14)), (768, 384, 33, (14, 14)),
                                            (1024, 256, 32, (14, 14)), (256, 128, 1, (14, 14)), (256, 256, 12, (14, 14)), (256, 512, 65, (12, 17)), (512, 512, 19, (17, 12))])
 @pytest.mark.parametrize("at", [False, True])
-def test_row_stages(cin, cout, n, hw, at):
+def test_row_stages_in_calls_that_fill_the_chip(cin, cout, n, hw, at):
     layer, filler = Layer("conv", cin, cout, *hw), conv(4096, 2048, 1, 1, 14)
     S = hw[0] * hw[1]
     d = dp.make_desc(layer, n, "bf16")
@@ -913,6 +992,35 @@ def test_row_stages_keep_their_copies_small():
 # Steps of several micro-steps keep no gradients of such layers but the last one's: accumulator against single micro-steps, gradients of the last one whole
 @pytest.mark.parametrize("streams", [1, 3])
 def test_phases_that_others_follow(streams):
+    from workloads.configs import Workload
+    from workloads.device import make_device_inputs
+    layers = (conv(64, 256, 1, 1, 14, name="a"), conv(256, 256, 1, 1, 14, name="b"), conv(256, 256, 3, 1, 14, name="c"), conv(1024, 256, 1, 1, 14, name="d"),
+              dense(64, 12, name="fc"))
+    wl = Workload("rows", layers, 130, 3, "bf16", "per_layer", 1.0, 0.0, tuple("abs" for _ in layers), 0.01, 77)
+    inputs = make_device_inputs(wl, wl.accum, torch.device("cuda:0"))
+    whole, single = (dp.PrivatiseStep(wl, streams=streams) for _ in range(2))
+    assert whole.p_mat == single.p_mat and whole._plan(1, True).p_mat < whole.p_mat
+    whole.run(inputs)
+    single.begin_step()
+    for step in inputs:
+        single.micro_step(step)
+    single.finalize()
+    torch.cuda.synchronize()
+    # the same blocks, squared and scaled in fp32 in another order
+    assert_close(host(whole.acc), host(single.acc), 1e-5, "accumulator")
+    assert_close(host(whole.group_sqnorm), host(single.group_sqnorm), 1e-5, "norms")
+    assert torch.equal(whole.g, single.g)
+    first = whole.acc.clone()
+    whole.capture(inputs)
+    for _ in range(3):
+        whole.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(whole.acc, first) and torch.equal(whole.g, single.g)
+
+
+# The same with four such layers, and of a step that is broken off: accumulator against single micro-steps, gradients of the last one whole
+@pytest.mark.parametrize("streams", [1, 3])
+def test_phases_that_others_follow_broken_off_and_replayed(streams):
     from workloads.configs import Workload
     from workloads.device import make_device_inputs
     layers = (conv(64, 256, 1, 1, 14, name="a"), conv(256, 256, 1, 1, 14, name="b"), conv(256, 256, 3, 1, 14, name="c"), conv(1024, 256, 1, 1, 14, name="d"),
