@@ -52,6 +52,7 @@ int crowd_hint() { return g_queue ? g_queue->crowd : 0; }
 int crowd3_hint() { return g_queue ? g_queue->crowd3 : 0; }
 double macs3_hint() { return g_queue ? g_queue->macs3 : 0.0; }
 int crowd_rows_hint() { return g_queue ? g_queue->crowd_rows : 0; }
+size_t taps_hint() { return g_queue ? g_queue->taps : 0; }
 int fuse_hint() { return g_queue ? g_queue->fuse : 0; }
 
 // Work per workgroup a batch call plans for, in units of one 128x128x64 chunk: the convolutions' multiply-adds
@@ -503,6 +504,8 @@ static void launch_targets(LaunchQueue &q, const std::vector<Geo> &geo, bool wei
     for (size_t l = 0; l < geo.size(); ++l)
         if (geo[l].kind == DP_CONV2D)
             macs[conv_shared_launch(geo[l], weighted ? MODE_WEIGHTED : (g_w && g_w[l] ? MODE_MATERIALISE : MODE_NORM))] += conv_macs(geo[l]);
+    for (const Geo &g : geo)
+        if (weighted && g.kind == DP_CONV2D) q.taps += conv_staged_copy(g);
     q.macs3 = macs[CONV_ROWS3];
     q.crowd3 = crowd_of(q.macs3);
     q.crowd_rows = macs[CONV_WHOLE_ROWS] < 4.0 * CROWD_UNIT ? 0 : crowd_of(macs[CONV_WHOLE_ROWS]);          // (0: less than any plan is made for)

@@ -2109,6 +2109,14 @@ int conv_shared_launch(const Geo &g, int mode)
     return mode == MODE_WEIGHTED && whole_rows(g) ? CONV_WHOLE_ROWS : CONV_OTHER;
 }
 
+size_t conv_staged_copy(const Geo &g)
+{
+    if (!g.bf16 || !pack_staged_fits(g) || conv3x3_applicable(g, MODE_WEIGHTED)) return 0;
+    // (at least: less the padding of a last range)
+    const size_t S = (size_t)g.oh * g.ow, row = g.blocks ? 64 : (S + 7) / 8 * 8, x = 2 * row * g.n * g.cin * g.kh * g.kw, dy = 2 * row * g.n * g.cout;
+    return x + dy > ((size_t)64 << 20) || (g.blocks && (S > 64 || g.has_bias)) ? 0 : x;
+}
+
 // loader of the contraction kernel for a geometry as the kernel sees it
 static int loader_of(const Geo &g)
 {

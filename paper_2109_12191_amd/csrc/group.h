@@ -86,6 +86,7 @@ struct LaunchQueue {
     int crowd3 = 0, crowd_rows = 0;     // the same of the launch that the call's raw-row 3x3 layers share, and of that of its layers
                                         // that the clip-weighted whole-row kernel can take
     double macs3 = 0.0;                 // multiply-adds of the former
+    size_t taps = 0;                    // clip-weighted: bytes of the copies of X that the call's layers with taps can pack through LDS
     int fuse = 0;                       // > 0: launchers hand in the kernels that dispatch on the variant INSIDE the kernel
                                         // (one launch for all row widths of the 3x3 kernel): only four kernels run at a
                                         // time, and a narrow launch inside a wide one costs none of them.  2: micro-steps
@@ -101,6 +102,7 @@ int crowd_hint();
 int crowd3_hint();
 double macs3_hint();
 int crowd_rows_hint();
+size_t taps_hint();
 // which variant-dispatching kernels the open batch wants (see LaunchQueue::fuse); 0: none
 int fuse_hint();
 // Launch the held main kernels grouped by kernel, then the deferred follow-ups.

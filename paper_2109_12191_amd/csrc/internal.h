@@ -50,6 +50,9 @@ const char *conv_variant_name(const Geo &g, int mode, bool shared);
 // which launch of a batch call a convolution shares with others of its kind
 enum { CONV_OTHER = 0, CONV_ROWS3 = 1, CONV_WHOLE_ROWS = 2 };
 int conv_shared_launch(const Geo &g, int mode);
+// bytes of the copy of X that a clip-weighted call of this layer packs by way of LDS, if that pays, or 0
+size_t conv_staged_copy(const Geo &g);
+bool pack_staged_fits(const Geo &g);
 // multiply-adds of a call, and the work per workgroup (LaunchQueue::crowd) of a batch call whose convolutions have that many together
 inline double conv_macs(const Geo &g) { return (double)g.n * g.cout * g.cin * g.kh * g.kw * g.oh * g.ow; }
 int crowd_of(double macs);

@@ -131,14 +131,17 @@ struct PackStaged {
     unsigned c_blocks, e_blocks;    // workgroups of a range
     unsigned by_ed, by_rp, by_p8, by_taps, by_kw, by_ow;             // divisors as factors (pack_div)
 };
-// It is one more launch, of workgroups that take longer: only where its share of the copies is worth that.  Us of a clip-weighted call, all in the kernel above /
-// so, on both sides of each line.  A layer alone: 128 -> 128 stride 2 on 56 x 56, 8 examples (14 MB) 38 / 43, 16 (29 MB) 50 / 48, 32 (58 MB) 96 / 69; 64 -> 64
-// stride 2 on 80 x 80, 8 (15 MB) 40 / 47, 16 (29 MB) 55 / 49; at two examples and less 13 / 24.  A layer of a batch call, whose others are likely to bring
-// their own: two of 5x5, 16 -> 32 stride 2 on 80 x 80, 8 examples (10 MB each) 57 / 69, 16 (20 MB) 73 / 70; of 64 -> 64 stride 2 on 32 x 32, 64 (19 MB) 76 / 59.
-constexpr size_t PACK_STAGED_ALONE = (size_t)24 << 20, PACK_STAGED_SHARED = (size_t)12 << 20;
-// And where that makes a workgroup for every compute unit: few large planes do not.  The first convolution (3 -> 64 7x7 stride 2 on 112 x 112: a workgroup a
-// plane, each of which writes 300 KB), alone, 48 examples, 82 / 130 us; in a batch call with another layer, 16 examples, 75 / 146.
-constexpr unsigned PACK_STAGED_BLOCKS = 256;
+// It is one more launch, of workgroups that take longer: only where a layer's copies, or those of a batch call's layers together, are worth that.  Us of a clip-weighted call, all in the kernel
+// above / so, on both sides of the line.  A layer alone: 128 -> 128 stride 2 on 56 x 56, 8 examples (14 MB) 38 / 43, 16 (29 MB) 50 / 48, 32 (58 MB) 96 / 69; 64 -> 64
+// stride 2 on 80 x 80, 8 (15 MB) 40 / 47, 16 (29 MB) 55 / 49; at two examples and less 13 / 24.  Batch calls: two of 5x5, 16 -> 32 stride 2 on 80 x 80, 8 examples
+// (20 MB) 57 / 69, 16 (40 MB) 73 / 70; two of 64 -> 64 stride 2 on 32 x 32, 64 (38 MB) 76 / 59; four of 290 -> 64 stride 2 on 18 x 18, 16 (29 MB) 53 / 45; six of
+// 512 -> 64 stride 2 on 11 x 64, 4 (42 MB) 53 / 41; ten of 64 -> 256 on 36 x 37, 4 (61 MB) 106 / 93; one of 243 -> 64 stride 2 on 32 x 32, 16 (18 MB), beside
+// 119 -> 64 stride 2 on 21 x 21 (4 MB) 71 / 57.
+constexpr size_t PACK_STAGED = (size_t)24 << 20, PACK_STAGED_SHARED = (size_t)12 << 20;         // (alone or together; one layer in a batch call)
+// And where a workgroup's planes are not much to write (of 24 MB there are as many as compute units then): few large planes are.  The first convolution (3 -> 64 7x7 stride 2 on
+// 112 x 112: a workgroup a plane, each of which writes 300 KB), alone, 48 examples, 82 / 130 us; in a batch call with another layer, 16 examples, 75 / 146; ten
+// of 64 -> 55 5x5 on 25 x 25, 3 examples (192 workgroups each that write 32 KB), 67 / 61.
+constexpr size_t PACK_STAGED_WRITES = (size_t)96 << 10;
 constexpr int PACK_LDS = 12 * 1024, PACK_PLANE = 32 * 1024, PACK_EB = 16;
 
 // x / d for x * d < 2^32; by = ceil(2^32 / d), 0 for d = 1
@@ -446,13 +449,15 @@ PackPlan pack_plan(const Geo &g, int groups, int row)
 
 static unsigned pack_by(unsigned d) { return d > 1 ? (unsigned)(((1ull << 32) + d - 1) / d) : 0u; }
 
-// X through pack_staged_kernel, if a plane of it fits; `done` says whether.  (Operands without taps stay with the kernel above: staged, ResNet-50 at 32
+bool pack_staged_fits(const Geo &g) { return g.kh * g.kw > 1 && g.h * g.w * 2 <= PACK_PLANE; }
+
+// X through pack_staged_kernel, if a plane of it fits and it pays; `done` says whether.  (Operands without taps stay with the kernel above: staged, ResNet-50 at 32
 // examples was as fast alone and 2 % slower beside other kernels, which its LDS keeps off a compute unit.)
 static dp_status launch_pack_staged(const Geo &g, const PackPlan &p, const void *in, void *out, hipStream_t s, bool &done)
 {
     const int channels = g.cin;
     const int plane = g.h * g.w, taps = g.kh * g.kw, p8 = p.SP / 8;
-    done = plane * 2 <= PACK_PLANE && (p.x_bytes >= PACK_STAGED_ALONE || (crowd_hint() && p.x_bytes >= PACK_STAGED_SHARED));
+    done = pack_staged_fits(g) && (p.x_bytes >= (crowd_hint() ? PACK_STAGED_SHARED : PACK_STAGED) || taps_hint() >= PACK_STAGED);
     if (!done) return DP_OK;
     PackStaged a;
     a.in = in; a.out = static_cast<uint16_t *>(out);
@@ -475,7 +480,7 @@ static dp_status launch_pack_staged(const Geo &g, const PackPlan &p, const void 
     const unsigned long long most = (unsigned long long)cb * taps * rp;
     if ((unsigned long long)eb * ed * ed >= (1ull << 32) || most * rp >= (1ull << 32)) { done = false; return DP_OK; }
     const unsigned long long blocks = (unsigned long long)p.groups * a.c_blocks * a.e_blocks;
-    if (blocks < PACK_STAGED_BLOCKS) { done = false; return DP_OK; }
+    if (p.x_bytes > blocks * PACK_STAGED_WRITES) { done = false; return DP_OK; }
     if (blocks > 0x7FFFFFFFull) return fail(DP_ERR_UNSUPPORTED, "pack: layer too large");
     // (layers share a launch if they ask for the same LDS; a piece is read from up to five dwords, which may lie behind the planes)
     return submit_kernel<PackStaged>(TIER_PRE, reinterpret_cast<const void *>(&pack_staged_kernel), a, (unsigned)blocks, 256,

@@ -1083,6 +1083,23 @@ def test_phases_that_others_follow_in_steps_of_any_length(monkeypatch, n, togeth
             assert_close(host(got), host(want), 1e-5, f"{what}, {length} micro-steps")
 
 
+# Packed layers whose copies are worth the launch through LDS together; three launches of copies and contraction, and one of sums over ranges
+@pytest.mark.parametrize("layer,count,n", [(conv(290, 64, 3, 2, 18), 4, 16), (Layer("conv", 512, 64, 11, 64, 3, 3, 2, 1, False), 6, 4), (conv(64, 55, 5, 1, 25), 10, 3)],
+                         ids=lambda v: str(v) if isinstance(v, int) else f"{v.cin}-{v.cout}-{v.kh}x{v.kw}s{v.stride}-{v.h}x{v.w}")
+def test_packed_copies_of_several_layers_go_through_lds_together(layer, count, n):
+    few, _few = _weighted_batch([layer] * 2, n)
+    call, (xs, dys, _, sq, acc) = _weighted_batch([layer] * count, n)
+    for t in acc:
+        t.zero_()
+    assert len(launches(call)) == len(launches(few)) + 1             # (two layers: all copies in one launch)
+    f = torch.clamp(1.0 / sq.double().sqrt(), max=1.0)
+    x, dy, got = xs[-1], dys[-1], acc[-1]
+    scaled = (dy.double() * f[:, None, None, None]).float().bfloat16().double()
+    ref = torch.nn.functional.unfold(x[:, :4].double(), layer.kh, padding=layer.pad, stride=layer.stride)
+    ref = sum(scaled[i].reshape(layer.cout, -1) @ ref[i].T for i in range(n))
+    assert_close(host(got.reshape(layer.cout, layer.cin, -1)[:, :4]).reshape(-1), host(ref).reshape(-1), 1e-4, "sum")
+
+
 # The clip-weighted 3x3 form in batch calls: layers of few tiles still bring workgroups (up to what whole examples allow); in a full
 # launch a tile is one workgroup, without slice sums
 @pytest.mark.parametrize("layers,n,least", [([conv(64, 64, 3, 1, 14)] * 2, 48, 48), ([conv(64, 64, 3, 1, 28)] * 2, 32, 64), ([conv(64, 64, 3, 1, 7)] * 2, 128, 64),
