@@ -1926,17 +1926,25 @@ static bool packed_weighted(const Geo &g, int mode, PackPlan &pp, Geo &g2)
         // Ranges are of equal length, so the last one may be mostly padding (three examples in two ranges take the room of four).  Workspaces are
         // sized for the smallest target that a call with this layer can have: fewer ranges than it makes must not need more than it does.  The next number of
         // ranges on either side that does not: the one that leaves the shorter walk (full_plan deals them to workgroups once more).
-        const size_t reported = bytes(plan(ranges(crowd_of(conv_macs(g)))));
+        const long long first = ranges(crowd_of(conv_macs(g)));
+        pp = plan(first);
+        const size_t reported = bytes(pp);
         if (reported > most) return false;
         long long more = ranges(crowd), fewer = more;
-        while (bytes(plan(more)) > reported) ++more;
-        while (bytes(plan(fewer)) > reported) --fewer;             // (one range has no padding)
+        if (more != first) {
+            while (bytes(plan(more)) > reported) ++more;
+            while (bytes(plan(fewer)) > reported) --fewer;         // (one range has no padding)
+            pp = plan(more);
+        }
         auto walk = [&](const PackPlan &p) {
             const long long chunks = ((long long)p.kg + 63) / 64, per = (long long)2 * crowd * (shape == T64 ? 4 : 1);
             const long long want = std::max(1ll, std::min((long long)p.groups, (p.groups * chunks + per - 1) / per));
             return (p.groups + want - 1) / want * chunks;
         };
-        pp = walk(plan(more)) < walk(plan(fewer)) ? plan(more) : plan(fewer);
+        if (fewer != more) {
+            const PackPlan other = plan(fewer);
+            if (walk(other) <= walk(pp)) pp = other;
+        }
     } else {
         pp = plan((256 + tiles - 1) / tiles);
         if (bytes(pp) > most) return false;
@@ -2046,12 +2054,11 @@ size_t conv_ws_bytes(const Geo &g, int mode)
 {
     size_t need = 0;
     const int saved = tl_forced_crowd;
-    // a call alone, and a call inside a batch: the smallest target that it can have with this layer, of which there are most slices, and (per-example calls) the largest;
-    // a clip-weighted layer of whole rows in either kernel, whichever a call's work chooses
+    // a call alone, and a call inside a batch: the smallest target that it can have with this layer, of which there are most slices; a clip-weighted layer of whole rows
+    // in either kernel, whichever a call's work chooses
     const bool weighted = mode == MODE_WEIGHTED;
-    for (int k = 0; k < 3; ++k) {
-        const int crowds[2][3] = {{0, 4, 64}, {0, crowd_of(conv_macs(g)), 64}};
-        tl_forced_crowd = crowds[weighted][k];
+    for (int k = 0; k < (weighted && whole_rows(g) ? 3 : 2); ++k) {
+        tl_forced_crowd = k == 0 ? 0 : (weighted ? crowd_of(conv_macs(g)) : 4);
         if (weighted) tl_forced_rows = k == 2;
         size_t b = conv_ws_bytes_mode(g, weighted ? MODE_WEIGHTED : MODE_NORM);
         if (!weighted) {
