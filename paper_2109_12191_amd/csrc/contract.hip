@@ -1806,8 +1806,10 @@ static FullPlan full_plan(const Geo &g, int mode)
         // written and read back (cache-resident in practice) kept below ~100 MB
         long long want = (512 + tiles - 1) / tiles;
         if (crowd) {                                     // example ranges of about twice the target
-            const long long per = (long long)2 * crowd * (p.shape == T64 ? 4 : 1);
+            const long long per = (long long)2 * crowd * (p.shape == T64 ? 4 : 1), alone = want;
             want = ((long long)g.n * p.chunks_per_ex + per - 1) / per;
+            // (layers that conv_row_stages_kernel takes in most calls come with the workspace of that and of a call alone)
+            if (want > alone && whole_rows(g)) want = alone;
         }
         const long long cap = (long long)(96.0e6 / (4.0 * (double)tiles * (double)tile_floats));
         if (want > cap) want = cap;

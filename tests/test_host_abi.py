@@ -322,3 +322,8 @@ def test_clip_weighted_workspaces_are_for_calls_that_there_can_be(lib):
     """A batch call with this layer has at least the layer's own work: no room for the slices of a smaller one."""
     d = dp.make_desc(conv(512, 1024, 1, 1, 14), 123, "bf16")
     assert dp.dp_workspace_bytes(d, dp.DP_WS_RECOMPUTE) == 16 * 512 * 1024 * 4          # sixteen ranges, the call alone
+
+
+def test_clip_weighted_whole_row_workspaces_hold_no_more_slices_than_a_call_alone_has(lib):
+    d = dp.make_desc(conv(512, 256, 1, 1, 14), 129, "bf16")
+    assert dp.dp_workspace_bytes(d, dp.DP_WS_RECOMPUTE) == 43 * 512 * 256 * 4           # 43 ranges of three examples, the call alone
